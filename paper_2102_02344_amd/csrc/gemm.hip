@@ -22,6 +22,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   if (q == 0 && i < count) out[i] = (sh[0][li] + sh[1][li]) + (sh[2][li] + sh[3][li]);
 }
 
+int gemm_f32_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st);
 int gemm_big_launch(const GemmDesc& d, const GemmArgs& a, bool v16, bool n16, dim3 grid, hipStream_t st);
 
 static inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -214,10 +215,13 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   // bf16 problems whose operands can be fetched in whole 8/16-byte pieces take the deep-prefetch
   // kernel (branch-free buffer loads, several k-tiles in flight).
   const bool pf = v16 || v8;
-  if (pf) {
+  if (d.dtype == HFTA_F32) {
+    rc = gemm_f32_launch(d, a, st);
+    if (rc == HFTA_EUNSUPPORTED) rc = launch_layout<float>(d, a, grid, st);
+  } else if (pf) {
     rc = gemm_pf_launch(d, a, v16, n16, grid, st);
   } else {
-    rc = d.dtype == HFTA_BF16 ? launch_layout<bf16_raw>(d, a, grid, st) : launch_layout<float>(d, a, grid, st);
+    rc = launch_layout<bf16_raw>(d, a, grid, st);
   }
   if (rc != HFTA_OK) return rc;
   if (splits > 1 && !d.keep_partials) return reduce_partials(d, G, splits, st);
