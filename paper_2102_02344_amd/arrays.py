@@ -35,7 +35,23 @@ def _bn_bwd_one_pass(B, Nb, ci, co, L, dt):
     return hb.conv1x1_bn_bwd_one_pass(B, Nb, ci, co, L, dt)
 
 
-class ParamArena:
+class _Views:
+    """Views of an object's own buffers, made once each: slicing a tensor costs as much host time as
+    marshalling a library call, and a step takes over a hundred of them."""
+
+    def _cut(self, buf: torch.Tensor, n: int) -> torch.Tensor:
+        """``buf[:n]``."""
+        return self._view((id(buf), n), buf, lambda: buf[:n])
+
+    def _view(self, key, buf: torch.Tensor, make):
+        cache = self.__dict__.setdefault("_view_cache", {})
+        hit = cache.get(key)
+        if hit is None or hit[0] is not buf:                 # also when another tensor took the buffer's place
+            hit = cache[key] = (buf, make())
+        return hit[1]
+
+
+class ParamArena(_Views):
     """Parameter-major storage of B models' parameters, gradients and Adam state.
 
     Fused parameter j is one ``[B][n_j]`` tensor (the fusion rules table concatenates weights
@@ -90,13 +106,16 @@ class ParamArena:
 
     def w(self, name: str) -> torch.Tensor:
         """Weights as the GEMMs read them (storage dtype)."""
-        return self._seg(self.lowp if self.lowp is not None else self.theta, name)
+        return self._segment("w", self.lowp if self.lowp is not None else self.theta, name)
 
     def master(self, name: str) -> torch.Tensor:
-        return self._seg(self.theta, name)
+        return self._segment("theta", self.theta, name)
 
     def g(self, name: str) -> torch.Tensor:
-        return self._seg(self.grad, name)
+        return self._segment("grad", self.grad, name)
+
+    def _segment(self, kind: str, buf: torch.Tensor, name: str) -> torch.Tensor:
+        return self._view((kind, name), buf, lambda: self._seg(buf, name))
 
     def param_host(self, buf: torch.Tensor, name: str, b: int) -> np.ndarray:
         shp = dict(self.shapes)[name]
@@ -304,7 +323,7 @@ class FusedPointNetCls(ParamArena):
         each operator in place against the oracle on the very bits the GPU consumed)."""
         s, B, Nb, L, dt = self.spec, self.B, self.Nb, self.L, self.dt
         eps, mom = self.BN_EPS, self.BN_MOMENTUM
-        P = probe if probe is not None else (lambda op, **kw: None)
+        P = probe
         # per-point MLP
         x, ci = self.points, s.conv[0]
         for i in range(self.nconv):
@@ -325,9 +344,10 @@ class FusedPointNetCls(ParamArena):
                     x = self.tail_x
                 else:
                     hb.conv1x1_bn_maxpool_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), *tail)
-                P("conv1x1_bn_maxpool_fwd", layer=k, x=x, w=self.w(k + ".w"), b=self.w(k + ".b"),
-                  g=self.master(k + ".bn.g"), bt=self.master(k + ".bn.b"), v=self.pooled, idx=self.pool_idx,
-                  mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"], zhit=self.zhit)
+                if P is not None:
+                    P("conv1x1_bn_maxpool_fwd", layer=k, x=x, w=self.w(k + ".w"), b=self.w(k + ".b"),
+                      g=self.master(k + ".bn.g"), bt=self.master(k + ".bn.b"), v=self.pooled, idx=self.pool_idx,
+                      mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"], zhit=self.zhit)
                 ci = co
                 break
             if i in self.unfused and i < self.nconv - 1:
@@ -352,7 +372,7 @@ class FusedPointNetCls(ParamArena):
                     hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"), *bnp,
                                       self.z[i], _cs(B, co, L), y, None if y is None else _cs(B, co, L), hb.ACT_RELU, 0.0,
                                       self.ws)
-                if probe is not None:
+                if P is not None:
                     P("conv1x1_fwd", layer=k, x=self._act(i - 1) if self.prenorm[i] else x, w=self.w(k + ".w"),
                       b=self.w(k + ".b"), y=self.z[i])
                     P("bn_fwd", layer=k, layout="conv", x=self.z[i], g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"),
@@ -361,7 +381,8 @@ class FusedPointNetCls(ParamArena):
                 continue
             hb.conv1x1_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"),
                            self.z[i], _cs(B, co, L))
-            P("conv1x1_fwd", layer=k, x=x, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
+            if P is not None:
+                P("conv1x1_fwd", layer=k, x=x, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
             if i == self.nconv - 1:
                 # last per-point layer: BatchNorm + ReLU + max over points in one operator; the
                 # activated [Nb, B*C, L] tensor is never written
@@ -370,9 +391,10 @@ class FusedPointNetCls(ParamArena):
                                   self.master(k + ".bn.b"), eps, mom, self.running[k + ".bn.rm"],
                                   self.running[k + ".bn.rv"], self.saved[k + ".bn.mean"],
                                   self.saved[k + ".bn.invstd"], self.pooled, self.pool_idx, vs, hb.ACT_RELU)
-                P("bn_fwd_maxpool", layer=k, x=self.z[i], g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"),
-                  v=self.pooled, idx=self.pool_idx, mean=self.saved[k + ".bn.mean"],
-                  invstd=self.saved[k + ".bn.invstd"])
+                if P is not None:
+                    P("bn_fwd_maxpool", layer=k, x=self.z[i], g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"),
+                      v=self.pooled, idx=self.pool_idx, mean=self.saved[k + ".bn.mean"],
+                      invstd=self.saved[k + ".bn.invstd"])
                 ci = co
                 break
         Cp = ci
@@ -384,33 +406,38 @@ class FusedPointNetCls(ParamArena):
             last = i == self.nfc - 1
             if last or s.fc_bn:
                 hb.linear_fwd_ws(B, Nb, fx, fy, dt, h, self.w(k + ".w"), self.w(k + ".b"), self.fz[i], workspace=self.ws)
-                P("linear_fwd", layer=k, x=h, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.fz[i], act=0)
+                if P is not None:
+                    P("linear_fwd", layer=k, x=h, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.fz[i], act=0)
                 if not last:
                     ls = (Nb * fy, fy, 1, 1)
                     hb.bn_fwd(B, Nb, fy, 1, dt, self.fz[i], ls, self.master(k + ".bn.g"), self.master(k + ".bn.b"),
                               eps, mom, self.running[k + ".bn.rm"], self.running[k + ".bn.rv"],
                               self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"], self.fh[i], ls, hb.ACT_RELU)
-                    P("bn_fwd", layer=k, layout="linear", x=self.fz[i], g=self.master(k + ".bn.g"),
-                      b=self.master(k + ".bn.b"), y=self.fh[i], mean=self.saved[k + ".bn.mean"],
-                      invstd=self.saved[k + ".bn.invstd"])
+                    if P is not None:
+                        P("bn_fwd", layer=k, layout="linear", x=self.fz[i], g=self.master(k + ".bn.g"),
+                          b=self.master(k + ".bn.b"), y=self.fh[i], mean=self.saved[k + ".bn.mean"],
+                          invstd=self.saved[k + ".bn.invstd"])
             else:
                 hb.linear_fwd_ws(B, Nb, fx, fy, dt, h, self.w(k + ".w"), self.w(k + ".b"), self.fh[i], hb.ACT_RELU,
                                  workspace=self.ws)
-                P("linear_fwd", layer=k, x=h, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.fh[i], act=1)
+                if P is not None:
+                    P("linear_fwd", layer=k, x=h, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.fh[i], act=1)
             if last:
                 h = self.fz[i]
             else:
                 h = self.fh[i]
                 if i == self.nfc - 2 and s.dropout_p > 0:
                     hb.dropout(B * Nb * fy, dt, h, self.drop_mask, s.dropout_p, self.fdrop)
-                    P("dropout", x=h, mask=self.drop_mask, y=self.fdrop)
+                    if P is not None:
+                        P("dropout", x=h, mask=self.drop_mask, y=self.fdrop)
                     h = self.fdrop
             fx = fy
         logits = h
         K = s.fc[-1]
-        d = self.fd[0][:B * Nb * K]
+        d = self._cut(self.fd[0], B * Nb * K)
         hb.softmax_xent(B, Nb, K, dt, logits, self.labels, self.loss, d)
-        P("softmax_xent", logits=logits, labels=self.labels, loss=self.loss, d=d.view(B, Nb, K))
+        if P is not None:
+            P("softmax_xent", logits=logits, labels=self.labels, loss=self.loss, d=d.view(B, Nb, K))
 
         # backward: head
         cur = 0
@@ -421,23 +448,26 @@ class FusedPointNetCls(ParamArena):
             if not last:
                 n = B * Nb * fy
                 if i == self.nfc - 2 and s.dropout_p > 0:
-                    nd = self.fd[cur ^ 1][:n]
+                    nd = self._cut(self.fd[cur ^ 1], n)
                     hb.dropout(n, dt, d, self.drop_mask, s.dropout_p, nd)
-                    P("dropout", x=d.view(B, Nb, fy), mask=self.drop_mask, y=nd.view(B, Nb, fy))
+                    if P is not None:
+                        P("dropout", x=d.view(B, Nb, fy), mask=self.drop_mask, y=nd.view(B, Nb, fy))
                     d, cur = nd, cur ^ 1
-                nd = self.fd[cur ^ 1][:n]
+                nd = self._cut(self.fd[cur ^ 1], n)
                 if s.fc_bn:
                     ls = (Nb * fy, fy, 1, 1)
                     hb.bn_bwd(B, Nb, fy, 1, dt, self.fz[i], ls, d, ls, self.master(k + ".bn.g"),
                               self.master(k + ".bn.b"), self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"],
                               nd, ls, self.g(k + ".bn.g"), self.g(k + ".bn.b"), hb.ACT_RELU, 0.0, self.g(k + ".b"))
-                    P("bn_bwd", layer=k, layout="linear", x=self.fz[i], dy=d.view(B, Nb, fy),
-                      g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
-                      invstd=self.saved[k + ".bn.invstd"], dx=nd.view(B, Nb, fy), dg=self.g(k + ".bn.g"),
-                      db=self.g(k + ".bn.b"))
+                    if P is not None:
+                        P("bn_bwd", layer=k, layout="linear", x=self.fz[i], dy=d.view(B, Nb, fy),
+                          g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
+                          invstd=self.saved[k + ".bn.invstd"], dx=nd.view(B, Nb, fy), dg=self.g(k + ".bn.g"),
+                          db=self.g(k + ".bn.b"))
                 else:
                     hb.act_bwd(n, dt, self.fh[i], d, nd, hb.ACT_RELU, 0.0, 1)
-                    P("relu_bwd_from_output", y=self.fh[i], dy=d.view(B, Nb, fy), dx=nd.view(B, Nb, fy))
+                    if P is not None:
+                        P("relu_bwd_from_output", y=self.fh[i], dy=d.view(B, Nb, fy), dx=nd.view(B, Nb, fy))
                 d, cur = nd, cur ^ 1
             if i == 0:
                 hin = self.pooled
@@ -445,12 +475,13 @@ class FusedPointNetCls(ParamArena):
                 hin = self.fdrop
             else:
                 hin = self.fh[i - 1]
-            nd = self.fd[cur ^ 1][:B * Nb * fx]
+            nd = self._cut(self.fd[cur ^ 1], B * Nb * fx)
             # a bias that feeds a BatchNorm gets its gradient from that BatchNorm's backward (dx_sum)
             own_db = self.g(k + ".b") if (last or not s.fc_bn) else None
             hb.linear_bwd(B, Nb, fx, fy, dt, hin, self.w(k + ".w"), d, nd, self.g(k + ".w"), own_db, self.ws)
-            P("linear_bwd", layer=k, x=hin, w=self.w(k + ".w"), dy=d.view(B, Nb, fy), dx=nd.view(B, Nb, fx),
-              dw=self.g(k + ".w"), db=self.g(k + ".b"))
+            if P is not None:
+                P("linear_bwd", layer=k, x=hin, w=self.w(k + ".w"), dy=d.view(B, Nb, fy), dx=nd.view(B, Nb, fx),
+                  dw=self.g(k + ".w"), db=self.g(k + ".b"))
             d, cur = nd, cur ^ 1
 
         # backward: pool and per-point MLP
@@ -463,7 +494,7 @@ class FusedPointNetCls(ParamArena):
             k = f"conv{i}"
             cs = _cs(B, co, L)
             if i == self.nconv - 1 and self.fused_tail:
-                xin, dxin = self.a[i - 1], self.dbuf[cur][:Nb * B * ci * L]
+                xin, dxin = self.a[i - 1], self._cut(self.dbuf[cur], Nb * B * ci * L)
                 tail = (self.zhit, self.tail_moments, dpool, self.pool_idx, (Nb * co, co, 1), self.master(k + ".bn.g"),
                         self.master(k + ".bn.b"), self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"], dxin,
                         _cs(B, ci, L), self.g(k + ".w"), self.g(k + ".b"), self.g(k + ".bn.g"), self.g(k + ".bn.b"),
@@ -472,18 +503,19 @@ class FusedPointNetCls(ParamArena):
                     xin = self.tail_x
                 hb.conv1x1_bn_maxpool_bwd(B, Nb, ci, co, L, dt, xin, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"),
                                           None, None, *tail)
-                P("conv1x1_bn_maxpool_bwd", layer=k, x=xin, w=self.w(k + ".w"), b=self.w(k + ".b"),
-                  dv=dpool.view(B, Nb, co), idx=self.pool_idx, g=self.master(k + ".bn.g"),
-                  bt=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
-                  dx=dxin.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"), dg=self.g(k + ".bn.g"),
-                  dbt=self.g(k + ".bn.b"))
+                if P is not None:
+                    P("conv1x1_bn_maxpool_bwd", layer=k, x=xin, w=self.w(k + ".w"), b=self.w(k + ".b"),
+                      dv=dpool.view(B, Nb, co), idx=self.pool_idx, g=self.master(k + ".bn.g"),
+                      bt=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
+                      dx=dxin.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"), dg=self.g(k + ".bn.g"),
+                      dbt=self.g(k + ".bn.b"))
                 da = dxin
                 continue
             xin = self.points if i == 0 else self.a[i - 1]
             if i < self.nconv - 1 and (i in self.unfused or self.one_pass[i]):
                 # BatchNorm backward + convolution backward in one call: dz stays on chip.  The data
                 # gradient goes to the other buffer (dY is still being read while it is written).
-                dxin = None if i == 0 else self.dbuf[cur ^ 1][:Nb * B * ci * L]
+                dxin = None if i == 0 else self._cut(self.dbuf[cur ^ 1], Nb * B * ci * L)
                 if i in self.unfused:
                     self._layer_bwd_unfused(i, xin, ci, co, da, dxin)
                 else:
@@ -497,36 +529,39 @@ class FusedPointNetCls(ParamArena):
                                                   self.master(kp + ".bn.b"), self.saved[kp + ".bn.mean"],
                                                   self.saved[kp + ".bn.invstd"], hb.ACT_RELU, 0.0, self.w(k + ".w"),
                                                   self.z[i], cs, da, cs, *bnp, *out, self.bn_sums[i - 1])
-                        if probe is not None:
+                        if P is not None:
                             xin = self._act(i - 1)
                     else:
                         hb.conv1x1_bn_bwd(B, Nb, ci, co, L, dt, xin, _cs(B, ci, L), self.w(k + ".w"), self.z[i], cs, da, cs,
                                           *bnp, *out)
-                    P("conv1x1_bn_bwd", layer=k, x=xin, w=self.w(k + ".w"), z=self.z[i], dy=da.view(Nb, B * co, L),
-                      g=self.master(k + ".bn.g"), bt=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
-                      invstd=self.saved[k + ".bn.invstd"], dx=None if i == 0 else dxin.view(Nb, B * ci, L),
-                      dw=self.g(k + ".w"), db=self.g(k + ".b"), dg=self.g(k + ".bn.g"), dbt=self.g(k + ".bn.b"))
+                    if P is not None:
+                        P("conv1x1_bn_bwd", layer=k, x=xin, w=self.w(k + ".w"), z=self.z[i], dy=da.view(Nb, B * co, L),
+                          g=self.master(k + ".bn.g"), bt=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
+                          invstd=self.saved[k + ".bn.invstd"], dx=None if i == 0 else dxin.view(Nb, B * ci, L),
+                          dw=self.g(k + ".w"), db=self.g(k + ".b"), dg=self.g(k + ".bn.g"), dbt=self.g(k + ".bn.b"))
                 da, cur = dxin, cur ^ 1
                 continue
-            dz = self.dbuf[cur ^ 1][:Nb * B * co * L]
+            dz = self._cut(self.dbuf[cur ^ 1], Nb * B * co * L)
             if i == self.nconv - 1:     # BatchNorm backward through the max over points
                 hb.bn_bwd_maxpool(B, Nb, co, L, dt, self.z[i], cs, dpool, self.pool_idx, (Nb * co, co, 1),
                                   self.master(k + ".bn.g"), self.master(k + ".bn.b"), self.saved[k + ".bn.mean"],
                                   self.saved[k + ".bn.invstd"], dz, cs, self.g(k + ".bn.g"), self.g(k + ".bn.b"),
                                   hb.ACT_RELU, 0.0, self.g(k + ".b"))
-                P("bn_bwd_maxpool", layer=k, x=self.z[i], dv=dpool.view(B, Nb, co), idx=self.pool_idx,
-                  g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
-                  invstd=self.saved[k + ".bn.invstd"], dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"),
-                  db=self.g(k + ".bn.b"))
+                if P is not None:
+                    P("bn_bwd_maxpool", layer=k, x=self.z[i], dv=dpool.view(B, Nb, co), idx=self.pool_idx,
+                      g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
+                      invstd=self.saved[k + ".bn.invstd"], dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"),
+                      db=self.g(k + ".bn.b"))
             else:
                 hb.bn_bwd(B, Nb, co, L, dt, self.z[i], cs, da, cs, self.master(k + ".bn.g"), self.master(k + ".bn.b"),
                           self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"], dz, cs, self.g(k + ".bn.g"),
                           self.g(k + ".bn.b"), hb.ACT_RELU, 0.0, self.g(k + ".b"))
-                P("bn_bwd", layer=k, layout="conv", x=self.z[i], dy=da.view(Nb, B * co, L),
-                  g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
-                  invstd=self.saved[k + ".bn.invstd"], dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"),
-                  db=self.g(k + ".bn.b"))
-            dxin = None if i == 0 else self.dbuf[cur][:Nb * B * ci * L]
+                if P is not None:
+                    P("bn_bwd", layer=k, layout="conv", x=self.z[i], dy=da.view(Nb, B * co, L),
+                      g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"],
+                      invstd=self.saved[k + ".bn.invstd"], dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"),
+                      db=self.g(k + ".bn.b"))
+            dxin = None if i == 0 else self._cut(self.dbuf[cur], Nb * B * ci * L)
             # data gradient and weight gradient as two calls: one GEMM launch each (plus the weight
             # gradient's split-K reduction), so a caller can time them separately
             if i > 0:
@@ -534,8 +569,9 @@ class FusedPointNetCls(ParamArena):
                                dxin, _cs(B, ci, L), None, None, self.ws)
             hb.conv1x1_bwd(B, Nb, ci, co, L, dt, xin, _cs(B, ci, L), None, dz, cs,
                            None, None, self.g(k + ".w"), None, self.ws)
-            P("conv1x1_bwd", layer=k, x=xin, w=self.w(k + ".w"), dy=dz.view(Nb, B * co, L),
-              dx=None if i == 0 else dxin.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"))
+            if P is not None:
+                P("conv1x1_bwd", layer=k, x=xin, w=self.w(k + ".w"), dy=dz.view(Nb, B * co, L),
+                  dx=None if i == 0 else dxin.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"))
             da = dxin
         return self.loss
 
@@ -617,26 +653,32 @@ class FusedMlp(ParamArena):
     def forward_backward(self, probe=None):
         """One forward + backward pass; ``probe(op, **tensors)`` as in FusedPointNetCls."""
         B, R, E, H, dt = self.B, self.R, self.E, self.H, self.dt
-        P = probe if probe is not None else (lambda op, **kw: None)
+        P = probe
         nb = self.spec.blocks
         for i in range(nb):
             k = f"blk{i}"
             x = self.x[i]
             hb.linear_fwd(B, R, E, H, dt, x, self.w(k + ".w1"), self.w(k + ".b1"), self.u[i])
-            P("linear_fwd", layer=k + ".1", x=x, w=self.w(k + ".w1"), b=self.w(k + ".b1"), y=self.u[i], act=0)
+            if P is not None:
+                P("linear_fwd", layer=k + ".1", x=x, w=self.w(k + ".w1"), b=self.w(k + ".b1"), y=self.u[i], act=0)
             hb.act_fwd(B * R * H, dt, self.u[i], self.h[i], hb.ACT_GELU)
-            P("act_fwd", layer=k, x=self.u[i], y=self.h[i], act=hb.ACT_GELU)
+            if P is not None:
+                P("act_fwd", layer=k, x=self.u[i], y=self.h[i], act=hb.ACT_GELU)
             hb.linear_fwd(B, R, H, E, dt, self.h[i], self.w(k + ".w2"), self.w(k + ".b2"), self.y)
-            P("linear_fwd", layer=k + ".2", x=self.h[i], w=self.w(k + ".w2"), b=self.w(k + ".b2"), y=self.y, act=0)
+            if P is not None:
+                P("linear_fwd", layer=k + ".2", x=self.h[i], w=self.w(k + ".w2"), b=self.w(k + ".b2"), y=self.y, act=0)
             hb.add(B * R * E, dt, x, self.y, self.s[i])
-            P("add", a=x, b=self.y, y=self.s[i])
+            if P is not None:
+                P("add", a=x, b=self.y, y=self.s[i])
             hb.layernorm_fwd(B, R, E, dt, self.s[i], self.master(k + ".ln.w"), self.master(k + ".ln.b"), self.LN_EPS,
                              self.ln_mean[i], self.ln_invstd[i], self.x[i + 1])
-            P("layernorm_fwd", layer=k, x=self.s[i], w=self.master(k + ".ln.w"), b=self.master(k + ".ln.b"),
-              y=self.x[i + 1], mean=self.ln_mean[i], invstd=self.ln_invstd[i])
+            if P is not None:
+                P("layernorm_fwd", layer=k, x=self.s[i], w=self.master(k + ".ln.w"), b=self.master(k + ".ln.b"),
+                  y=self.x[i + 1], mean=self.ln_mean[i], invstd=self.ln_invstd[i])
         d = self.dE[0]
         hb.mse(B, R * E, dt, self.x[nb], self.target, self.loss, d)
-        P("mse", pred=self.x[nb], target=self.target, loss=self.loss, d=d)
+        if P is not None:
+            P("mse", pred=self.x[nb], target=self.target, loss=self.loss, d=d)
         # A block's incoming gradient is the pair (ga, gb) whose sum it is: the LayerNorm backward adds
         # them on load (no stored sum) and also emits the column sums of its result, the second
         # Linear's bias gradient.  (Rows of E that are not whole 16-byte pieces: the separate calls.)
@@ -656,14 +698,16 @@ class FusedMlp(ParamArena):
                 hb.layernorm_bwd(B, R, E, dt, self.s[i], ga, self.master(k + ".ln.w"), self.ln_mean[i], self.ln_invstd[i],
                                  ds, self.g(k + ".ln.w"), self.g(k + ".ln.b"), self.ws)
                 hb.linear_bwd(B, R, H, E, dt, None, None, ds, None, None, self.g(k + ".b2"), None)
-            P("layernorm_bwd", layer=k, x=self.s[i], dy=ga, dy2=gb if fused_ln else None, w=self.master(k + ".ln.w"),
-              mean=self.ln_mean[i], invstd=self.ln_invstd[i], dx=ds, dw=self.g(k + ".ln.w"), db=self.g(k + ".ln.b"))
+            if P is not None:
+                P("layernorm_bwd", layer=k, x=self.s[i], dy=ga, dy2=gb if fused_ln else None, w=self.master(k + ".ln.w"),
+                  mean=self.ln_mean[i], invstd=self.ln_invstd[i], dx=ds, dw=self.g(k + ".ln.w"), db=self.g(k + ".ln.b"))
             # data gradient and weight gradient as separate calls (one kernel each), so a caller can
             # time them separately
             hb.linear_bwd(B, R, H, E, dt, None, self.w(k + ".w2"), ds, self.dH[0], None, None, None)
             hb.linear_bwd(B, R, H, E, dt, self.h[i], None, ds, None, self.g(k + ".w2"), None, self.ws)
-            P("linear_bwd", layer=k + ".2", x=self.h[i], w=self.w(k + ".w2"), dy=ds, dx=self.dH[0],
-              dw=self.g(k + ".w2"), db=self.g(k + ".b2"))
+            if P is not None:
+                P("linear_bwd", layer=k + ".2", x=self.h[i], w=self.w(k + ".w2"), dy=ds, dx=self.dH[0],
+                  dw=self.g(k + ".w2"), db=self.g(k + ".b2"))
             # GELU backward and the first Linear's bias gradient (column sums of its result) in one pass
             # (whole 16-byte pieces along H; otherwise the two separate calls)
             if H % epv == 0:
@@ -671,15 +715,17 @@ class FusedMlp(ParamArena):
             else:
                 hb.act_bwd(B * R * H, dt, self.u[i], self.dH[0], self.dH[1], hb.ACT_GELU)
                 hb.linear_bwd(B, R, E, H, dt, None, None, self.dH[1], None, None, self.g(k + ".b1"), None)
-            P("act_bwd", layer=k, x=self.u[i], dy=self.dH[0], dx=self.dH[1], act=hb.ACT_GELU)
+            if P is not None:
+                P("act_bwd", layer=k, x=self.u[i], dy=self.dH[0], dx=self.dH[1], act=hb.ACT_GELU)
             # nothing consumes the gradient of the array's input: the first block computes no data
             # gradient of its first Linear
             dxl = ga                                   # this block's incoming gradient is dead: reuse it
             if i > 0:
                 hb.linear_bwd(B, R, E, H, dt, None, self.w(k + ".w1"), self.dH[1], dxl, None, None, None)
             hb.linear_bwd(B, R, E, H, dt, self.x[i], None, self.dH[1], None, self.g(k + ".w1"), None, self.ws)
-            P("linear_bwd", layer=k + ".1", x=self.x[i], w=self.w(k + ".w1"), dy=self.dH[1], dx=dxl if i > 0 else None,
-              dw=self.g(k + ".w1"), db=self.g(k + ".b1"))
+            if P is not None:
+                P("linear_bwd", layer=k + ".1", x=self.x[i], w=self.w(k + ".w1"), dy=self.dH[1], dx=dxl if i > 0 else None,
+                  dw=self.g(k + ".w1"), db=self.g(k + ".b1"))
             if gb is not None:
                 free.append(gb)
             ga, gb = ds, dxl                           # the next block down receives ds + dxl
@@ -697,10 +743,10 @@ class _Arena(ParamArena):
         self.grad2 = torch.zeros_like(self.grad)      # second pass of a step that sums two passes
 
     def g2(self, name):
-        return self._seg(self.grad2, name)
+        return self._segment("grad2", self.grad2, name)
 
 
-class FusedDcgan:
+class FusedDcgan(_Views):
     """B generator/discriminator pairs trained as one job: every Conv2d / ConvTranspose2d is one
     grouped implicit GEMM with groups = B, BatchNorm keeps per-model statistics, one Adam launch
     per network updates all B models (per-model lr).  Activations are ``[Nb, B*C, H, W]``."""
@@ -782,20 +828,23 @@ class FusedDcgan:
             # ConvTranspose2d forward = the data-gradient form of the grouped convolution
             hb.conv2d_grouped_bwd(B, Nb, co, ci, ho, ho, 4, 4, st, p, dt, None, self.G.w(k + ".w"), x,
                                   self.g_pre[i], None, None, self.ws)
-            self._P("convT2d_fwd", layer=k, x=x, w=self.G.w(k + ".w"), y=self.g_pre[i], geo=(ci, co, st, p))
+            if self.probe is not None:
+                self._P("convT2d_fwd", layer=k, x=x, w=self.G.w(k + ".w"), y=self.g_pre[i], geo=(ci, co, st, p))
             if i < n - 1:
                 cs = _cs(B, co, ho * ho)
                 hb.bn_fwd(B, Nb, co, ho * ho, dt, self.g_pre[i], cs, self.G.master(k + ".bn.g"),
                           self.G.master(k + ".bn.b"), self.BN_EPS, self.BN_MOMENTUM, self.running[k + ".bn.rm"],
                           self.running[k + ".bn.rv"], self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"],
                           self.g_act[i], cs, hb.ACT_RELU)
-                self._P("bn_fwd", layer=k, x=self.g_pre[i], g=self.G.master(k + ".bn.g"), b=self.G.master(k + ".bn.b"),
-                        y=self.g_act[i], mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
-                        act=hb.ACT_RELU)
+                if self.probe is not None:
+                    self._P("bn_fwd", layer=k, x=self.g_pre[i], g=self.G.master(k + ".bn.g"), b=self.G.master(k + ".bn.b"),
+                            y=self.g_act[i], mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
+                            act=hb.ACT_RELU)
             else:
                 pre = self.g_pre[i].clone() if self.probe is not None else None
                 hb.bias_act_nchw(Nb, B * co, ho * ho, dt, self.g_pre[i], None, hb.ACT_TANH)
-                self._P("act_fwd", layer=k, x=pre, y=self.g_pre[i], act=hb.ACT_TANH)
+                if self.probe is not None:
+                    self._P("act_fwd", layer=k, x=pre, y=self.g_pre[i], act=hb.ACT_TANH)
             x = self.g_act[i]
         return self.fake
 
@@ -808,30 +857,34 @@ class FusedDcgan:
             k = f"g{i}"
             ho = (hin - 1) * st - 2 * p + 4
             cnt = Nb * B * co * ho * ho
-            dpre = self._other(d)[:cnt]
+            dpre = self._cut(self._other(d), cnt)
             if i == n - 1:
                 hb.act_bwd(cnt, dt, self.fake, d, dpre, hb.ACT_TANH, 0.0, 1)
-                self._P("act_bwd_from_output", layer=k, y=self.fake, dy=d[:cnt], dx=dpre, act=hb.ACT_TANH)
+                if self.probe is not None:
+                    self._P("act_bwd_from_output", layer=k, y=self.fake, dy=d[:cnt], dx=dpre, act=hb.ACT_TANH)
             else:
                 cs = _cs(B, co, ho * ho)
                 hb.bn_bwd(B, Nb, co, ho * ho, dt, self.g_pre[i], cs, d, cs, self.G.master(k + ".bn.g"),
                           self.G.master(k + ".bn.b"), self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"],
                           dpre, cs, self.G.g(k + ".bn.g"), self.G.g(k + ".bn.b"), hb.ACT_RELU, 0.0)
-                self._P("bn_bwd", layer=k, x=self.g_pre[i], dy=d[:cnt], g=self.G.master(k + ".bn.g"),
-                        b=self.G.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
-                        dx=dpre, dg=self.G.g(k + ".bn.g"), db=self.G.g(k + ".bn.b"), act=hb.ACT_RELU)
+                if self.probe is not None:
+                    self._P("bn_bwd", layer=k, x=self.g_pre[i], dy=d[:cnt], g=self.G.master(k + ".bn.g"),
+                            b=self.G.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
+                            dx=dpre, dg=self.G.g(k + ".bn.g"), db=self.G.g(k + ".bn.b"), act=hb.ACT_RELU)
             xin = self.z if i == 0 else self.g_act[i - 1]
             # ConvTranspose2d weight gradient = the convolution's with input and output gradient exchanged
             hb.conv2d_grouped_bwd(B, Nb, co, ci, ho, ho, 4, 4, st, p, dt, dpre, None, xin, None,
                                   self.G.g(k + ".w"), None, self.ws)
-            self._P("convT2d_dw", layer=k, x=xin, w=self.G.w(k + ".w"), dy=dpre, dw=self.G.g(k + ".w"), geo=(ci, co, st, p),
-                    hw=(hin, ho))
+            if self.probe is not None:
+                self._P("convT2d_dw", layer=k, x=xin, w=self.G.w(k + ".w"), dy=dpre, dw=self.G.g(k + ".w"), geo=(ci, co, st, p),
+                        hw=(hin, ho))
             if i > 0:
-                dx = self._other(dpre)[:Nb * B * ci * hin * hin]      # the incoming gradient's buffer: it is dead
+                dx = self._cut(self._other(dpre), Nb * B * ci * hin * hin)      # the incoming gradient's buffer: it is dead
                 # ConvTranspose2d data gradient = the convolution's forward
                 hb.conv2d_grouped_fwd(B, Nb, co, ci, ho, ho, 4, 4, st, p, dt, dpre, self.G.w(k + ".w"), None, dx,
                                       workspace=self.ws)
-                self._P("convT2d_dx", layer=k, x=xin, w=self.G.w(k + ".w"), dy=dpre, dx=dx, geo=(ci, co, st, p), hw=(hin, ho))
+                if self.probe is not None:
+                    self._P("convT2d_dx", layer=k, x=xin, w=self.G.w(k + ".w"), dy=dpre, dx=dx, geo=(ci, co, st, p), hw=(hin, ho))
                 d = dx
 
     def _other(self, t):
@@ -849,20 +902,23 @@ class FusedDcgan:
             if i == 0:
                 hb.conv2d_grouped_fwd(B, Nb, ci, co, hin, hin, 4, 4, st, p, dt, x, self.D.w(k + ".w"), None,
                                       self.d_pre[i], hb.ACT_LEAKY, self.SLOPE, workspace=self.ws)
-                self._P("conv2d_fwd", layer=k, x=x, w=self.D.w(k + ".w"), y=self.d_pre[i], geo=(ci, co, st, p), act=hb.ACT_LEAKY)
+                if self.probe is not None:
+                    self._P("conv2d_fwd", layer=k, x=x, w=self.D.w(k + ".w"), y=self.d_pre[i], geo=(ci, co, st, p), act=hb.ACT_LEAKY)
             else:
                 hb.conv2d_grouped_fwd(B, Nb, ci, co, hin, hin, 4, 4, st, p, dt, x, self.D.w(k + ".w"), None,
                                       self.d_pre[i], workspace=self.ws)
-                self._P("conv2d_fwd", layer=k, x=x, w=self.D.w(k + ".w"), y=self.d_pre[i], geo=(ci, co, st, p), act=hb.ACT_NONE)
+                if self.probe is not None:
+                    self._P("conv2d_fwd", layer=k, x=x, w=self.D.w(k + ".w"), y=self.d_pre[i], geo=(ci, co, st, p), act=hb.ACT_NONE)
                 if i < n - 1:
                     cs = _cs(B, co, ho * ho)
                     hb.bn_fwd(B, Nb, co, ho * ho, dt, self.d_pre[i], cs, self.D.master(k + ".bn.g"),
                               self.D.master(k + ".bn.b"), self.BN_EPS, self.BN_MOMENTUM, self.running[k + ".bn.rm"],
                               self.running[k + ".bn.rv"], self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"],
                               self.d_act[i], cs, hb.ACT_LEAKY, self.SLOPE)
-                    self._P("bn_fwd", layer=k, x=self.d_pre[i], g=self.D.master(k + ".bn.g"), b=self.D.master(k + ".bn.b"),
-                            y=self.d_act[i], mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
-                            act=hb.ACT_LEAKY)
+                    if self.probe is not None:
+                        self._P("bn_fwd", layer=k, x=self.d_pre[i], g=self.D.master(k + ".bn.g"), b=self.D.master(k + ".bn.b"),
+                                y=self.d_act[i], mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
+                                act=hb.ACT_LEAKY)
             x = self.d_act[i]
         return self.logits
 
@@ -879,10 +935,11 @@ class FusedDcgan:
             if i == n - 1:
                 dpre = d
             else:
-                dpre = self._other(d)[:cnt]
+                dpre = self._cut(self._other(d), cnt)
                 if i == 0:
                     hb.act_bwd(cnt, dt, self.d_act[0], d, dpre, hb.ACT_LEAKY, self.SLOPE, 1)
-                    self._P("act_bwd_from_output", layer=k, y=self.d_act[0], dy=d[:cnt], dx=dpre, act=hb.ACT_LEAKY)
+                    if self.probe is not None:
+                        self._P("act_bwd_from_output", layer=k, y=self.d_act[0], dy=d[:cnt], dx=dpre, act=hb.ACT_LEAKY)
                 else:
                     cs = _cs(B, co, ho * ho)
                     # without weight gradients the BatchNorm parameter gradients go to the spare buffer
@@ -890,27 +947,31 @@ class FusedDcgan:
                     hb.bn_bwd(B, Nb, co, ho * ho, dt, self.d_pre[i], cs, d, cs, self.D.master(k + ".bn.g"),
                               self.D.master(k + ".bn.b"), self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"],
                               dpre, cs, tgt(k + ".bn.g"), tgt(k + ".bn.b"), hb.ACT_LEAKY, self.SLOPE)
-                    self._P("bn_bwd", layer=k, x=self.d_pre[i], dy=d[:cnt], g=self.D.master(k + ".bn.g"),
-                            b=self.D.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
-                            dx=dpre, dg=tgt(k + ".bn.g"), db=tgt(k + ".bn.b"), act=hb.ACT_LEAKY)
+                    if self.probe is not None:
+                        self._P("bn_bwd", layer=k, x=self.d_pre[i], dy=d[:cnt], g=self.D.master(k + ".bn.g"),
+                                b=self.D.master(k + ".bn.b"), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"],
+                                dx=dpre, dg=tgt(k + ".bn.g"), db=tgt(k + ".bn.b"), act=hb.ACT_LEAKY)
             xin = self._d_in if i == 0 else self.d_act[i - 1]
             need_dx = i > 0 or want_dx
             if want_dw:
                 hb.conv2d_grouped_bwd(B, Nb, ci, co, hin, hin, 4, 4, st, p, dt, xin, None, dpre, None,
                                       grad_of(k + ".w"), None, self.ws)
-                self._P("conv2d_dw", layer=k, x=xin, w=self.D.w(k + ".w"), dy=dpre, dw=grad_of(k + ".w"), geo=(ci, co, st, p),
-                        hw=(hin, ho))
+                if self.probe is not None:
+                    self._P("conv2d_dw", layer=k, x=xin, w=self.D.w(k + ".w"), dy=dpre, dw=grad_of(k + ".w"), geo=(ci, co, st, p),
+                            hw=(hin, ho))
             if need_dx:
-                dx = self._other(dpre)[:Nb * B * ci * hin * hin]
+                dx = self._cut(self._other(dpre), Nb * B * ci * hin * hin)
                 hb.conv2d_grouped_bwd(B, Nb, ci, co, hin, hin, 4, 4, st, p, dt, None, self.D.w(k + ".w"), dpre, dx,
                                       None, None, self.ws)
-                self._P("conv2d_dx", layer=k, x=xin, w=self.D.w(k + ".w"), dy=dpre, dx=dx, geo=(ci, co, st, p), hw=(hin, ho))
+                if self.probe is not None:
+                    self._P("conv2d_dx", layer=k, x=xin, w=self.D.w(k + ".w"), dy=dpre, dx=dx, geo=(ci, co, st, p), hw=(hin, ho))
                 d = dx
         return d
 
     def _bce(self, targets, loss):
         hb.bce_logits_strided(self.B, self.Nb, self.dt, self.logits, targets, loss, self.dlogits, 1, self.B)
-        self._P("bce", logits=self.logits, targets=targets, loss=loss, d=self.dlogits)
+        if self.probe is not None:
+            self._P("bce", logits=self.logits, targets=targets, loss=loss, d=self.dlogits)
 
     # ------------------------------------------------------------------ one iteration
     def d_step(self):
@@ -923,7 +984,8 @@ class FusedDcgan:
         self.d_backward(self.D.g2)
         g1 = self.D.grad.clone() if self.probe is not None else None
         hb.add(self.D.grad.numel(), hb.F32, self.D.grad, self.D.grad2, self.D.grad)
-        self._P("grad_add", a=g1, b=self.D.grad2, y=self.D.grad)
+        if self.probe is not None:
+            self._P("grad_add", a=g1, b=self.D.grad2, y=self.D.grad)
 
     def g_step_backward(self):
         """Generator loss BCE(D(fake), 1) through the current discriminator, back to G's parameters."""
@@ -1045,12 +1107,13 @@ class FusedPointNetSeg(ParamArena):
         """Channel slice i of a concatenation buffer: (tensor whose data pointer is the slice's first
         element, for the ABI; the same slice as a [Nb, B, C, L] view, for tests)."""
         o, c = self.off[i], self.spec.conv[i + 1]
-        return buf.view(-1)[o * self.L:], buf.view(self.Nb, self.B, self.Cp, self.L)[:, :, o:o + c, :]
+        return self._view((id(buf), "slice", i), buf, lambda: (buf.view(-1)[o * self.L:],
+                                                               buf.view(self.Nb, self.B, self.Cp, self.L)[:, :, o:o + c, :]))
 
     def forward_backward(self, probe=None):
         s, B, Nb, L, dt = self.spec, self.B, self.Nb, self.L, self.dt
         eps, mom = self.BN_EPS, self.BN_MOMENTUM
-        P = probe if probe is not None else (lambda op, **kw: None)
+        P = probe
         cst, Cp, Cg, C4, H = self.cat_strides, self.Cp, self.Cg, self.C4, s.head
         bn = lambda k: (self.master(k + ".bn.g"), self.master(k + ".bn.b"))
         st = lambda k: (self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"])
@@ -1063,15 +1126,19 @@ class FusedPointNetSeg(ParamArena):
             hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, x, xs, self.w(k + ".w"), self.w(k + ".b"), *bn(k), eps, mom,
                               self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], *st(k), self.z[i], _cs(B, co, L),
                               a, cst, hb.ACT_RELU, 0.0, self.ws)
-            P("conv1x1_fwd", layer=k, x=xv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
-            P("bn_fwd", layer=k, x=self.z[i], g=bn(k)[0], b=bn(k)[1], y=av, mean=st(k)[0], invstd=st(k)[1])
+            if P is not None:
+                P("conv1x1_fwd", layer=k, x=xv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
+            if P is not None:
+                P("bn_fwd", layer=k, x=self.z[i], g=bn(k)[0], b=bn(k)[1], y=av, mean=st(k)[0], invstd=st(k)[1])
             x, xs, xv, ci = a, cst, av, co
         hb.maxpool_points(B, Nb, C4, L, dt, x, cst, self.gfeat, self.pool_idx, self.gvs)
-        P("maxpool_points", x=xv, v=self.gfeat[:, :, :C4], idx=self.pool_idx[:, :, :C4])
+        if P is not None:
+            P("maxpool_points", x=xv, v=self.gfeat[:, :, :C4], idx=self.pool_idx[:, :, :C4])
         # ---- head: first layer = per-point block over the concatenation + once-per-sample block
         # the tiled block's product (with the layer's bias) once per sample ...
         hb.linear_fwd_ws(B, Nb, Cg, H[1], dt, self.gfeat, self.w("head0.wg"), self.w("head0.b"), self.hg, workspace=self.ws)
-        P("linear_fwd", layer="head0.wg", x=self.gfeat, w=self.w("head0.wg"), b=self.w("head0.b"), y=self.hg)
+        if P is not None:
+            P("linear_fwd", layer="head0.wg", x=self.gfeat, w=self.w("head0.wg"), b=self.w("head0.b"), y=self.hg)
         h, hs, hv, ci = self.cat, cst, self.cat, Cp
         for i in range(self.nh):
             co, k = H[i + 1], f"head{i}"
@@ -1079,27 +1146,32 @@ class FusedPointNetSeg(ParamArena):
             if i == 0:      # ... enters the convolution over the per-point block as its per-sample bias: one store
                 hb.conv1x1_fwd_sample_bias(B, Nb, ci, co, L, dt, h, hs, self.w(k + ".w"), self.hg, (Nb * co, co, 1),
                                            self.zh[i], cs)
-                P("conv1x1_fwd_sample_bias", layer=k, x=hv, w=self.w(k + ".w"), s=self.hg, y=self.zh[i])
+                if P is not None:
+                    P("conv1x1_fwd_sample_bias", layer=k, x=hv, w=self.w(k + ".w"), s=self.hg, y=self.zh[i])
             elif i < self.nh - 1:
                 hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, h, hs, self.w(k + ".w"), self.w(k + ".b"), *bn(k), eps, mom,
                                   self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], *st(k), self.zh[i], cs,
                                   self.ah[i], cs, hb.ACT_RELU, 0.0, self.ws)
-                P("conv1x1_fwd", layer=k, x=hv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.zh[i])
+                if P is not None:
+                    P("conv1x1_fwd", layer=k, x=hv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.zh[i])
             else:
                 hb.conv1x1_fwd(B, Nb, ci, co, L, dt, h, hs, self.w(k + ".w"), self.w(k + ".b"), self.zh[i], cs)
-                P("conv1x1_fwd", layer=k, x=hv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.zh[i])
+                if P is not None:
+                    P("conv1x1_fwd", layer=k, x=hv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.zh[i])
             if i == self.nh - 1:
                 break
             if i == 0:
                 hb.bn_fwd(B, Nb, co, L, dt, self.zh[i], cs, *bn(k), eps, mom, self.running[k + ".bn.rm"],
                           self.running[k + ".bn.rv"], *st(k), self.ah[i], cs, hb.ACT_RELU)
-            P("bn_fwd", layer=k, x=self.zh[i], g=bn(k)[0], b=bn(k)[1], y=self.ah[i], mean=st(k)[0], invstd=st(k)[1])
+            if P is not None:
+                P("bn_fwd", layer=k, x=self.zh[i], g=bn(k)[0], b=bn(k)[1], y=self.ah[i], mean=st(k)[0], invstd=st(k)[1])
             h, hs, hv, ci = self.ah[i], cs, self.ah[i], co
         K = H[-1]
         logits = self.zh[-1]
-        d = self.dbuf[0][:Nb * B * K * L]
+        d = self._cut(self.dbuf[0], Nb * B * K * L)
         hb.softmax_xent_points(B, Nb, K, L, dt, logits, _cs(B, K, L), self.labels, self.loss, d, _cs(B, K, L), self.ws)
-        P("softmax_xent_points", logits=logits, labels=self.labels, loss=self.loss, d=d.view(Nb, B * K, L))
+        if P is not None:
+            P("softmax_xent_points", logits=logits, labels=self.labels, loss=self.loss, d=d.view(Nb, B * K, L))
 
         # ---- backward: head
         cur = 0
@@ -1107,26 +1179,30 @@ class FusedPointNetSeg(ParamArena):
             ci, co, k = (Cp if i == 0 else H[i]), H[i + 1], f"head{i}"
             cs = _cs(B, co, L)
             if i < self.nh - 1:
-                dz = self.dbuf[cur ^ 1][:Nb * B * co * L]
+                dz = self._cut(self.dbuf[cur ^ 1], Nb * B * co * L)
                 hb.bn_bwd(B, Nb, co, L, dt, self.zh[i], cs, d, cs, *bn(k), *st(k), dz, cs, self.g(k + ".bn.g"),
                           self.g(k + ".bn.b"), hb.ACT_RELU, 0.0, self.g(k + ".b"))
-                P("bn_bwd", layer=k, x=self.zh[i], dy=d.view(Nb, B * co, L), g=bn(k)[0], b=bn(k)[1], mean=st(k)[0],
-                  invstd=st(k)[1], dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"), db=self.g(k + ".bn.b"))
+                if P is not None:
+                    P("bn_bwd", layer=k, x=self.zh[i], dy=d.view(Nb, B * co, L), g=bn(k)[0], b=bn(k)[1], mean=st(k)[0],
+                      invstd=st(k)[1], dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"), db=self.g(k + ".bn.b"))
                 d, cur = dz, cur ^ 1
             hin, hs = (self.cat, cst) if i == 0 else (self.ah[i - 1], _cs(B, ci, L))
-            dx, dxs = (self.dcat, cst) if i == 0 else (self.dbuf[cur ^ 1][:Nb * B * ci * L], _cs(B, ci, L))
+            dx, dxs = (self.dcat, cst) if i == 0 else (self._cut(self.dbuf[cur ^ 1], Nb * B * ci * L), _cs(B, ci, L))
             hb.conv1x1_bwd(B, Nb, ci, co, L, dt, None, None, self.w(k + ".w"), d, cs, dx, dxs, None, None, self.ws)
             own_db = self.g(k + ".b") if i == self.nh - 1 else None      # else from the BatchNorm backward
             hb.conv1x1_bwd(B, Nb, ci, co, L, dt, hin, hs, None, d, cs, None, None, self.g(k + ".w"), own_db, self.ws)
-            P("conv1x1_bwd", layer=k, x=hin, w=self.w(k + ".w"), dy=d.view(Nb, B * co, L),
-              dx=dx.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"))
+            if P is not None:
+                P("conv1x1_bwd", layer=k, x=hin, w=self.w(k + ".w"), dy=d.view(Nb, B * co, L),
+                  dx=dx.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"))
             if i == 0:
                 hb.sum_points(B, Nb, co, L, dt, d, cs, self.dhg, (Nb * co, co, 1))
-                P("sum_points", x=d.view(Nb, B * co, L), s=self.dhg)
+                if P is not None:
+                    P("sum_points", x=d.view(Nb, B * co, L), s=self.dhg)
                 hb.linear_bwd(B, Nb, Cg, co, dt, self.gfeat, self.w("head0.wg"), self.dhg, self.dgfeat,
                               self.g("head0.wg"), None, self.ws)
-                P("linear_bwd", layer="head0.wg", x=self.gfeat, w=self.w("head0.wg"), dy=self.dhg, dx=self.dgfeat,
-                  dw=self.g("head0.wg"))
+                if P is not None:
+                    P("linear_bwd", layer="head0.wg", x=self.gfeat, w=self.w("head0.wg"), dy=self.dhg, dx=self.dgfeat,
+                      dw=self.g("head0.wg"))
             else:
                 d, cur = dx, cur ^ 1
 
@@ -1139,43 +1215,48 @@ class FusedPointNetSeg(ParamArena):
             if i == self.nconv - 1:
                 before = slv.clone() if probe is not None else None
                 hb.maxpool_points_bwd_add(B, Nb, co, L, dt, self.dgfeat, self.pool_idx, self.gvs, sl, cst)
-                P("maxpool_points_bwd_add", dx0=before, dv=self.dgfeat[:, :, :C4], idx=self.pool_idx[:, :, :C4], dx=slv)
+                if P is not None:
+                    P("maxpool_points_bwd_add", dx0=before, dv=self.dgfeat[:, :, :C4], idx=self.pool_idx[:, :, :C4], dx=slv)
                 da, das, dav = sl, cst, slv
             else:
-                dsum = self.dbuf[2][:Nb * B * co * L]
+                dsum = self._cut(self.dbuf[2], Nb * B * co * L)
                 hb.add_strided(B, Nb, co, L, dt, dnext, cs, sl, cst, dsum, cs)
-                P("add_strided", a=dnext.view(Nb, B * co, L), b=slv, y=dsum.view(Nb, B * co, L))
+                if P is not None:
+                    P("add_strided", a=dnext.view(Nb, B * co, L), b=slv, y=dsum.view(Nb, B * co, L))
                 da, das, dav = dsum, cs, dsum.view(Nb, B * co, L)
             if self.one_pass[i]:
                 # BatchNorm backward + convolution backward in one call (dz stays on chip)
                 if i > 0:
                     xin, xs, xinv = self._slice(self.cat, i - 1)[0], cst, self._slice(self.cat, i - 1)[1]
-                    dnext = self.dbuf[1][:Nb * B * ci * L]
+                    dnext = self._cut(self.dbuf[1], Nb * B * ci * L)
                 else:
                     xin, xs, xinv, dnext = self.points, _cs(B, 3, L), self.points, None
                 hb.conv1x1_bn_bwd(B, Nb, ci, co, L, dt, xin, xs, self.w(k + ".w"), self.z[i], cs, da, das, *bn(k), *st(k),
                                   dnext, None if i == 0 else _cs(B, ci, L), self.g(k + ".w"), self.g(k + ".b"),
                                   self.g(k + ".bn.g"), self.g(k + ".bn.b"), hb.ACT_RELU, 0.0, self.ws)
-                P("conv1x1_bn_bwd", layer=k, x=xinv, w=self.w(k + ".w"), z=self.z[i], dy=dav, g=bn(k)[0], bt=bn(k)[1],
-                  mean=st(k)[0], invstd=st(k)[1], dx=None if i == 0 else dnext.view(Nb, B * ci, L), dw=self.g(k + ".w"),
-                  db=self.g(k + ".b"), dg=self.g(k + ".bn.g"), dbt=self.g(k + ".bn.b"))
+                if P is not None:
+                    P("conv1x1_bn_bwd", layer=k, x=xinv, w=self.w(k + ".w"), z=self.z[i], dy=dav, g=bn(k)[0], bt=bn(k)[1],
+                      mean=st(k)[0], invstd=st(k)[1], dx=None if i == 0 else dnext.view(Nb, B * ci, L), dw=self.g(k + ".w"),
+                      db=self.g(k + ".b"), dg=self.g(k + ".bn.g"), dbt=self.g(k + ".bn.b"))
                 continue
-            dz = self.dbuf[0][:Nb * B * co * L]
+            dz = self._cut(self.dbuf[0], Nb * B * co * L)
             hb.bn_bwd(B, Nb, co, L, dt, self.z[i], cs, da, das, *bn(k), *st(k), dz, cs, self.g(k + ".bn.g"),
                       self.g(k + ".bn.b"), hb.ACT_RELU, 0.0, self.g(k + ".b"))
-            P("bn_bwd", layer=k, x=self.z[i], dy=dav, g=bn(k)[0], b=bn(k)[1], mean=st(k)[0], invstd=st(k)[1],
-              dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"), db=self.g(k + ".bn.b"))
+            if P is not None:
+                P("bn_bwd", layer=k, x=self.z[i], dy=dav, g=bn(k)[0], b=bn(k)[1], mean=st(k)[0], invstd=st(k)[1],
+                  dx=dz.view(Nb, B * co, L), dg=self.g(k + ".bn.g"), db=self.g(k + ".bn.b"))
             if i > 0:
                 xin, xs = self._slice(self.cat, i - 1)[0], cst
                 xinv = self._slice(self.cat, i - 1)[1]
-                dnext = self.dbuf[1][:Nb * B * ci * L]
+                dnext = self._cut(self.dbuf[1], Nb * B * ci * L)
                 hb.conv1x1_bwd(B, Nb, ci, co, L, dt, None, None, self.w(k + ".w"), dz, cs, dnext, _cs(B, ci, L),
                                None, None, self.ws)
             else:
                 xin, xs, xinv, dnext = self.points, _cs(B, 3, L), self.points, None
             hb.conv1x1_bwd(B, Nb, ci, co, L, dt, xin, xs, None, dz, cs, None, None, self.g(k + ".w"), None, self.ws)
-            P("conv1x1_bwd", layer=k, x=xinv, w=self.w(k + ".w"), dy=dz.view(Nb, B * co, L),
-              dx=None if i == 0 else dnext.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"))
+            if P is not None:
+                P("conv1x1_bwd", layer=k, x=xinv, w=self.w(k + ".w"), dy=dz.view(Nb, B * co, L),
+                  dx=None if i == 0 else dnext.view(Nb, B * ci, L), dw=self.g(k + ".w"), db=self.g(k + ".b"))
         return self.loss
 
 
@@ -1228,43 +1309,56 @@ class FusedTransformerLM(ParamArena):
 
     def _lin_bwd(self, P, name, M, Fx, Fy, x, dy, dx):
         hb.linear_bwd(self.B, M, Fx, Fy, self.dt, x, self.w(name + ".w"), dy, dx, self.g(name + ".w"), self.g(name + ".b"), self.ws)
-        P("linear_bwd", layer=name, x=x, w=self.w(name + ".w"), dy=dy, dx=dx, dw=self.g(name + ".w"), db=self.g(name + ".b"))
+        if P is not None:
+            P("linear_bwd", layer=name, x=x, w=self.w(name + ".w"), dy=dy, dx=dx, dw=self.g(name + ".w"), db=self.g(name + ".b"))
 
     def forward_backward(self, probe=None):
         B, R, E, F, V, N, S, Hh, dt = self.B, self.R, self.E, self.F, self.V, self.N, self.S, self.Hh, self.dt
-        P = probe if probe is not None else (lambda op, **kw: None)
+        P = probe
         nl = self.spec.layers
         hb.embedding_fwd(B, R, V, E, dt, self.w("emb"), self.tokens, self.scale, self.pos, S, self.x[0])
-        P("embedding_fwd", table=self.w("emb"), idx=self.tokens, pos=self.pos, y=self.x[0])
+        if P is not None:
+            P("embedding_fwd", table=self.w("emb"), idx=self.tokens, pos=self.pos, y=self.x[0])
         for i in range(nl):
             k, x = f"l{i}", self.x[i]
             mu1, inv1, mu2, inv2 = self.stats[i]
             hb.linear_fwd(B, R, E, 3 * E, dt, x, self.w(k + ".in.w"), self.w(k + ".in.b"), self.qkv[i])
-            P("linear_fwd", layer=k + ".in", x=x, w=self.w(k + ".in.w"), b=self.w(k + ".in.b"), y=self.qkv[i], act=0)
+            if P is not None:
+                P("linear_fwd", layer=k + ".in", x=x, w=self.w(k + ".in.w"), b=self.w(k + ".in.b"), y=self.qkv[i], act=0)
             hb.attention_fwd(B, N, S, E, Hh, dt, self.qkv[i], self.p[i], self.ctx[i], 1)
-            P("attention_fwd", qkv=self.qkv[i], p=self.p[i], ctx=self.ctx[i])
+            if P is not None:
+                P("attention_fwd", qkv=self.qkv[i], p=self.p[i], ctx=self.ctx[i])
             hb.linear_fwd(B, R, E, E, dt, self.ctx[i], self.w(k + ".out.w"), self.w(k + ".out.b"), self.tmpE)
-            P("linear_fwd", layer=k + ".out", x=self.ctx[i], w=self.w(k + ".out.w"), b=self.w(k + ".out.b"), y=self.tmpE, act=0)
+            if P is not None:
+                P("linear_fwd", layer=k + ".out", x=self.ctx[i], w=self.w(k + ".out.w"), b=self.w(k + ".out.b"), y=self.tmpE, act=0)
             hb.add(B * R * E, dt, x, self.tmpE, self.s1[i])
-            P("add", a=x, b=self.tmpE, y=self.s1[i])
+            if P is not None:
+                P("add", a=x, b=self.tmpE, y=self.s1[i])
             hb.layernorm_fwd(B, R, E, dt, self.s1[i], self.master(k + ".ln1.w"), self.master(k + ".ln1.b"), self.LN_EPS,
                              mu1, inv1, self.x1[i])
-            P("layernorm_fwd", layer=k + ".ln1", x=self.s1[i], w=self.master(k + ".ln1.w"), b=self.master(k + ".ln1.b"),
-              y=self.x1[i], mean=mu1, invstd=inv1)
+            if P is not None:
+                P("layernorm_fwd", layer=k + ".ln1", x=self.s1[i], w=self.master(k + ".ln1.w"), b=self.master(k + ".ln1.b"),
+                  y=self.x1[i], mean=mu1, invstd=inv1)
             hb.linear_fwd(B, R, E, F, dt, self.x1[i], self.w(k + ".ff1.w"), self.w(k + ".ff1.b"), self.h[i], hb.ACT_RELU)
-            P("linear_fwd", layer=k + ".ff1", x=self.x1[i], w=self.w(k + ".ff1.w"), b=self.w(k + ".ff1.b"), y=self.h[i], act=1)
+            if P is not None:
+                P("linear_fwd", layer=k + ".ff1", x=self.x1[i], w=self.w(k + ".ff1.w"), b=self.w(k + ".ff1.b"), y=self.h[i], act=1)
             hb.linear_fwd(B, R, F, E, dt, self.h[i], self.w(k + ".ff2.w"), self.w(k + ".ff2.b"), self.tmpE)
-            P("linear_fwd", layer=k + ".ff2", x=self.h[i], w=self.w(k + ".ff2.w"), b=self.w(k + ".ff2.b"), y=self.tmpE, act=0)
+            if P is not None:
+                P("linear_fwd", layer=k + ".ff2", x=self.h[i], w=self.w(k + ".ff2.w"), b=self.w(k + ".ff2.b"), y=self.tmpE, act=0)
             hb.add(B * R * E, dt, self.x1[i], self.tmpE, self.s2[i])
-            P("add", a=self.x1[i], b=self.tmpE, y=self.s2[i])
+            if P is not None:
+                P("add", a=self.x1[i], b=self.tmpE, y=self.s2[i])
             hb.layernorm_fwd(B, R, E, dt, self.s2[i], self.master(k + ".ln2.w"), self.master(k + ".ln2.b"), self.LN_EPS,
                              mu2, inv2, self.x[i + 1])
-            P("layernorm_fwd", layer=k + ".ln2", x=self.s2[i], w=self.master(k + ".ln2.w"), b=self.master(k + ".ln2.b"),
-              y=self.x[i + 1], mean=mu2, invstd=inv2)
+            if P is not None:
+                P("layernorm_fwd", layer=k + ".ln2", x=self.s2[i], w=self.master(k + ".ln2.w"), b=self.master(k + ".ln2.b"),
+                  y=self.x[i + 1], mean=mu2, invstd=inv2)
         hb.linear_fwd(B, R, E, V, dt, self.x[nl], self.w("dec.w"), self.w("dec.b"), self.logits)
-        P("linear_fwd", layer="dec", x=self.x[nl], w=self.w("dec.w"), b=self.w("dec.b"), y=self.logits, act=0)
+        if P is not None:
+            P("linear_fwd", layer="dec", x=self.x[nl], w=self.w("dec.w"), b=self.w("dec.b"), y=self.logits, act=0)
         hb.softmax_xent_rows(B, R, V, dt, self.logits, self.targets, self.loss, self.dlogits, self.ws)
-        P("softmax_xent", logits=self.logits, labels=self.targets, loss=self.loss, d=self.dlogits)
+        if P is not None:
+            P("softmax_xent", logits=self.logits, labels=self.targets, loss=self.loss, d=self.dlogits)
         # ---- backward
         d = self.dE[0]
         self._lin_bwd(P, "dec", R, E, V, self.x[nl], self.dlogits, d)
@@ -1274,32 +1368,39 @@ class FusedTransformerLM(ParamArena):
             ds2, t1, t2 = self.dE[1], self.dE[2], self.dE[3]
             hb.layernorm_bwd(B, R, E, dt, self.s2[i], d, self.master(k + ".ln2.w"), mu2, inv2, ds2,
                              self.g(k + ".ln2.w"), self.g(k + ".ln2.b"), self.ws)
-            P("layernorm_bwd", layer=k + ".ln2", x=self.s2[i], dy=d, w=self.master(k + ".ln2.w"), mean=mu2, invstd=inv2,
-              dx=ds2, dw=self.g(k + ".ln2.w"), db=self.g(k + ".ln2.b"))
+            if P is not None:
+                P("layernorm_bwd", layer=k + ".ln2", x=self.s2[i], dy=d, w=self.master(k + ".ln2.w"), mean=mu2, invstd=inv2,
+                  dx=ds2, dw=self.g(k + ".ln2.w"), db=self.g(k + ".ln2.b"))
             self._lin_bwd(P, k + ".ff2", R, F, E, self.h[i], ds2, self.dF[0])
             hb.act_bwd(B * R * F, dt, self.h[i], self.dF[0], self.dF[1], hb.ACT_RELU, 0.0, 1)
-            P("relu_bwd_from_output", y=self.h[i], dy=self.dF[0], dx=self.dF[1])
+            if P is not None:
+                P("relu_bwd_from_output", y=self.h[i], dy=self.dF[0], dx=self.dF[1])
             self._lin_bwd(P, k + ".ff1", R, E, F, self.x1[i], self.dF[1], t1)
             hb.add(B * R * E, dt, ds2, t1, t2)
-            P("add", a=ds2, b=t1, y=t2)
+            if P is not None:
+                P("add", a=ds2, b=t1, y=t2)
             ds1 = self.dE[1]                                   # ds2 is consumed
             hb.layernorm_bwd(B, R, E, dt, self.s1[i], t2, self.master(k + ".ln1.w"), mu1, inv1, ds1,
                              self.g(k + ".ln1.w"), self.g(k + ".ln1.b"), self.ws)
-            P("layernorm_bwd", layer=k + ".ln1", x=self.s1[i], dy=t2, w=self.master(k + ".ln1.w"), mean=mu1, invstd=inv1,
-              dx=ds1, dw=self.g(k + ".ln1.w"), db=self.g(k + ".ln1.b"))
+            if P is not None:
+                P("layernorm_bwd", layer=k + ".ln1", x=self.s1[i], dy=t2, w=self.master(k + ".ln1.w"), mean=mu1, invstd=inv1,
+                  dx=ds1, dw=self.g(k + ".ln1.w"), db=self.g(k + ".ln1.b"))
             self._lin_bwd(P, k + ".out", R, E, E, self.ctx[i], ds1, t1)            # t1 = dctx
             hb.attention_bwd(B, N, S, E, Hh, dt, self.qkv[i], self.p[i], t1, self.dqkv, self.ws)
-            P("attention_bwd", qkv=self.qkv[i], p=self.p[i], dctx=t1, dqkv=self.dqkv)
+            if P is not None:
+                P("attention_bwd", qkv=self.qkv[i], p=self.p[i], dctx=t1, dqkv=self.dqkv)
             self._lin_bwd(P, k + ".in", R, E, 3 * E, self.x[i], self.dqkv, t2)
             hb.add(B * R * E, dt, ds1, t2, self.dE[0])
-            P("add", a=ds1, b=t2, y=self.dE[0])
+            if P is not None:
+                P("add", a=ds1, b=t2, y=self.dE[0])
             d = self.dE[0]
         hb.embedding_bwd(B, R, V, E, dt, d, self.tokens, self.scale, self.g("emb"))
-        P("embedding_bwd", dy=d, idx=self.tokens, dtable=self.g("emb"))
+        if P is not None:
+            P("embedding_bwd", dy=d, idx=self.tokens, dtable=self.g("emb"))
         return self.loss
 
 
-class _PointChain:
+class _PointChain(_Views):
     """One chain of a point-cloud model inside a ParamArena: per-point layers (k=1 convolution,
     BatchNorm, ReLU) named ``{prefix}conv{conv_base+i}``, then, if ``fc`` is given, the max over
     points and the fully connected layers ``{prefix}fc{i}`` (hidden ones with BatchNorm and ReLU,
@@ -1433,10 +1534,10 @@ class _PointChain:
             if not last:
                 n = B * Nb * fy
                 if i == self.nfc - 2 and self.dropout_p > 0:
-                    nd = self.fd[cur ^ 1][:n]
+                    nd = self._cut(self.fd[cur ^ 1], n)
                     hb.dropout(n, dt, d, self.drop_mask, self.dropout_p, nd)
                     d, cur = nd, cur ^ 1
-                nd = self.fd[cur ^ 1][:n]
+                nd = self._cut(self.fd[cur ^ 1], n)
                 if self.fc_bn:
                     ls = (Nb * fy, fy, 1, 1)
                     hb.bn_bwd(B, Nb, fy, 1, dt, self.fz[i], ls, d, ls, A.master(k + ".bn.g"), A.master(k + ".bn.b"),
@@ -1451,7 +1552,7 @@ class _PointChain:
                 hin = self.fdrop
             else:
                 hin = self.fh[i - 1]
-            nd = self.fd[cur ^ 1][:B * Nb * fx]
+            nd = self._cut(self.fd[cur ^ 1], B * Nb * fx)
             own_db = A.g(k + ".b") if (last or not self.fc_bn) else None
             hb.linear_bwd(B, Nb, fx, fy, dt, hin, A.w(k + ".w"), d, nd, A.g(k + ".w"), own_db, ws)
             d, cur = nd, cur ^ 1
@@ -1466,7 +1567,7 @@ class _PointChain:
             bn = (A.master(k + ".bn.g"), A.master(k + ".bn.b"), A.saved[k + ".bn.mean"], A.saved[k + ".bn.invstd"])
             if tail and self.fused_tail:
                 # the operator always writes dX: give it a buffer even when nobody reads it
-                dxo = self.dbuf[cur][:Nb * B * ci * L]
+                dxo = self._cut(self.dbuf[cur], Nb * B * ci * L)
                 hb.conv1x1_bn_maxpool_bwd(B, Nb, ci, co, L, dt, xin, xs, A.w(k + ".w"), A.w(k + ".b"), None, None, self.zhit,
                                           self.moments, da, self.pool_idx, (Nb * co, co, 1), *bn, dxo, xs, A.g(k + ".w"),
                                           A.g(k + ".b"), A.g(k + ".bn.g"), A.g(k + ".bn.b"), hb.ACT_RELU, 0.0, ws)
@@ -1474,7 +1575,7 @@ class _PointChain:
                 continue
             if not tail and self.one_pass[i]:
                 # BatchNorm backward + convolution backward in one call; its dX must not share da's buffer
-                dxin = self.dbuf[cur][:Nb * B * ci * L] if need_dx else None
+                dxin = self._cut(self.dbuf[cur], Nb * B * ci * L) if need_dx else None
                 out = (dxin, xs if need_dx else None, A.g(k + ".w"), A.g(k + ".b"), A.g(k + ".bn.g"), A.g(k + ".bn.b"),
                        hb.ACT_RELU, 0.0, ws, None, self.bn_sums[i])
                 if self.prenorm[i]:
@@ -1487,8 +1588,8 @@ class _PointChain:
                     hb.conv1x1_bn_bwd(B, Nb, ci, co, L, dt, xin, xs, A.w(k + ".w"), self.z[i], cs, da, cs, *bn, *out)
                 da, cur = dxin, cur ^ 1
                 continue
-            dz = self.dbuf[cur][:Nb * B * co * L]
-            dxin = self.dbuf[cur ^ 1][:Nb * B * ci * L] if need_dx else None       # over da, which the BatchNorm has consumed
+            dz = self._cut(self.dbuf[cur], Nb * B * co * L)
+            dxin = self._cut(self.dbuf[cur ^ 1], Nb * B * ci * L) if need_dx else None       # over da, which the BatchNorm has consumed
             if tail:
                 hb.bn_bwd_maxpool(B, Nb, co, L, dt, self.z[i], cs, da, self.pool_idx, (Nb * co, co, 1), *bn, dz, cs,
                                   A.g(k + ".bn.g"), A.g(k + ".bn.b"), hb.ACT_RELU, 0.0, A.g(k + ".b"))

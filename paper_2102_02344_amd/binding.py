@@ -9,8 +9,11 @@ is missing the import fails.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional, Sequence
+
+import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libhfta.so")
@@ -147,14 +150,27 @@ def _ptr(t) -> Optional[int]:
 def _strides(s: Optional[Sequence[int]], n: int = 4):
     if s is None:
         return None
+    return _strides_of(tuple(s), n)
+
+
+@functools.lru_cache(maxsize=4096)
+def _strides_of(s: tuple, n: int):
+    """The host array a call reads its strides from (the library only reads it)."""
     assert len(s) == n, (s, n)
     return (C.c_int64 * n)(*[int(v) for v in s])
 
 
+def _current_stream() -> int:
+    """Raw handle of torch's current stream (without building a Stream object where torch offers that)."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and torch.cuda.is_initialized():
+        return raw(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        return _current_stream() or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
