@@ -196,22 +196,24 @@ int hfta_conv1x1_bwd(int B, int Nb, int Ci, int Co, int L, int dtype,
  * hfta_conv1x1_fwd (may be NULL when dX is NULL); gamma, beta, save_mean, save_invstd: [B][Co] fp32
  * as hfta_bn_fwd left them.  dX == NULL skips the data gradient (a network's first layer); dX must
  * not overlap X, Z or dY (it is written while other slices of those are still being read).
- * bf16 layers with Ci <= 128, Co <= 128, L % 4 == 0, 8-byte aligned X, Z, dY (and dX) and strides
- * that are multiples of 4 elements run as one
+ * bf16 layers with Ci <= 128, Co <= 128 and L >= 4 (rows of any length and alignment) run as one
  * reduction kernel (dgamma, dbeta and per-channel constants) plus ONE streaming kernel that forms
  * dZ per 128-point slice in registers and feeds it to both products from LDS: dZ never goes to
  * device memory.  The workspace (hfta_conv1x1_bn_bwd_workspace_bytes, 256-byte aligned) then holds
  * the constants and the per-workgroup fp32 partials of dW and dbias, added in a fixed order
  * (bit-reproducible).  Every other shape or dtype runs the two single operators with dZ in the
- * workspace (the query returns that larger size for them).  A shape the streaming kernel takes
- * whose pointers or strides break its alignment rules needs the larger workspace as well:
- * HFTA_EWORKSPACE if it is not there.  Nothing is allocated.
- * hfta_conv1x1_bn_bwd_one_pass returns 1 for the shapes and dtype of the one-kernel form, else 0 (a
- * caller that already owns a dZ-sized buffer may prefer the two single operators for the others).
+ * workspace (the query returns that larger size for them).  Nothing is allocated.
+ * hfta_conv1x1_bn_bwd_one_pass returns 1 for the shapes and dtype of the one-kernel form with
+ * L % 4 == 0, else 0 (a caller that already owns a dZ-sized buffer may prefer the two single operators
+ * for the others).  Rows with L % 4 != 0 take the one-kernel form when the workspace holds
+ * hfta_conv1x1_bn_bwd_stream_workspace_bytes (> 0 for every shape that form takes, whatever L; 0
+ * otherwise) and the two operators when it does not; hfta_conv1x1_bn_bwd_workspace_bytes is
+ * enough for both.
  * sums (optional, [B][Co][2] fp32): the two reductions {sum g, sum g xhat} of this block, as the
  * backward call of the block that consumed Y left them (in_sums of hfta_conv1x1_bn_prenorm_bwd);
  * the one-kernel form then skips its reduction pass over dY and Z (dgamma, dbeta and dZ come from
  * these sums; equal to the pass's own up to the fp32 summation order).  Other forms ignore it. */
+size_t hfta_conv1x1_bn_bwd_stream_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
 int hfta_conv1x1_bn_bwd_one_pass(int B, int Nb, int Ci, int Co, int L, int dtype);
 size_t hfta_conv1x1_bn_bwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
 int hfta_conv1x1_bn_bwd(int B, int Nb, int Ci, int Co, int L, int dtype,
@@ -232,9 +234,8 @@ int hfta_conv1x1_bn_bwd(int B, int Nb, int Ci, int Co, int L, int dtype,
  * call dX is the gradient with respect to X, what the previous block's backward takes as its dY).
  * Results are bit-identical to storing X and calling the plain pair.  The previous block is run
  * with Y == NULL.  Only the shapes both streaming kernels take: bf16, Ci % 8 == 0, Ci <= 128,
- * 64 <= Co <= 128, L % 4 == 0 (hfta_conv1x1_bn_prenorm_supported returns 1), 8-byte aligned
- * tensors with strides that are multiples of 4 elements; anything else is HFTA_EUNSUPPORTED with
- * nothing launched (store the activated tensor and use the plain pair).  Workspaces:
+ * 64 <= Co <= 128, L >= 4 (hfta_conv1x1_bn_prenorm_supported returns 1); rows may have any length
+ * and alignment.  Anything else is HFTA_EUNSUPPORTED with nothing launched (store the activated tensor and use the plain pair).  Workspaces:
  * hfta_conv1x1_bn_fwd_workspace_bytes and hfta_conv1x1_bn_bwd_workspace_bytes, required here
  * (HFTA_EWORKSPACE).  Y may be NULL in the forward call, dX in the backward call.
  * The backward call can hand the previous block's BatchNorm backward its two reductions: with
@@ -436,11 +437,16 @@ int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype,
  * dbeta.  BatchNorm's backward is a per-channel affine map of z plus Nb spikes, so dX and dW reduce
  * to the Gram matrix of X, a Ci -> Ci product with the spikes added in, and gathers at the argmax.
  *
- * EUNSUPPORTED unless bf16, Ci <= 128, Ci % 8 == 0, Co <= 1024, L % 4 == 0 and L < 2^21, 8-byte
- * aligned X rows; EWORKSPACE below the *_workspace_bytes value (workspace 256-byte aligned; the
- * workspace-size functions return 0 for unsupported shapes).
+ * Rows with L % 4 != 0: V is formed from z at the maximum rounded to bf16 (the values of the chain of
+ * stored operators); other rows normalise the fp32 product.  zhit is the fp32 product either way.
+ * EUNSUPPORTED unless bf16, Ci <= 128, Ci % 8 == 0, Co <= 1024, 4 <= L < 2^21, and rows of X and dX
+ * that do not overlap (stride_c >= L); rows may have any alignment.  EWORKSPACE below the needed
+ * size (workspace 256-byte aligned).  hfta_conv1x1_bn_maxpool_workspace_bytes is that size for either
+ * direction and every supported shape (0: unsupported); the per-direction queries answer for
+ * L % 4 == 0 and return 0 for other L.
  * ---------------------------------------------------------------------- */
 size_t hfta_conv1x1_bn_maxpool_saved_floats(int B, int Ci, int Co);
+size_t hfta_conv1x1_bn_maxpool_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
 size_t hfta_conv1x1_bn_maxpool_fwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
 int hfta_conv1x1_bn_maxpool_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,
                                 const void* X, const int64_t xs[4], const void* W, const void* bias,

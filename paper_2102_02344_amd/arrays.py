@@ -28,11 +28,21 @@ def _cs(B, C, L):
     return (C * L, B * C * L, L, 1)
 
 
+def _whole_pieces(L):
+    """Rows of whole four-point pieces.  On other rows the transform array's chains and the segmentation
+    array keep the single operators, whose sums run over single points in order: what stands behind them (a
+    matrix per cloud from normalised differences between clouds; a softmax per point) turns a last-bit
+    difference of a statistic into percents (running estimates behind the transforms: 0.03-0.09 after three
+    steps), and a model should not train differently from one release to the next.  The classification
+    array, which amplifies ten times less, takes the streaming operators on every row."""
+    return L % 4 == 0
+
+
 def _bn_bwd_one_pass(B, Nb, ci, co, L, dt):
     """True when ``conv1x1_bn_bwd`` runs this layer as one streaming kernel (dz never stored).  Layers it
     would run as the two single operators are called as such here, with dz in one of the array's
     gradient buffers instead of a workspace of that size."""
-    return hb.conv1x1_bn_bwd_one_pass(B, Nb, ci, co, L, dt)
+    return hb.conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, ci, co, L, dt) > 0
 
 
 class _Views:
@@ -232,9 +242,8 @@ class FusedPointNetCls(ParamArena):
         self.fused_tail = False
         if fused_tail and self.nconv >= 2:
             geo = (B, Nb, spec.conv[-2], spec.conv[-1], L, self.dt)
-            self.fused_tail_ws = max(hb.conv1x1_bn_maxpool_fwd_workspace_bytes(*geo),
-                                     hb.conv1x1_bn_maxpool_bwd_workspace_bytes(*geo))
-            self.fused_tail = hb.conv1x1_bn_maxpool_fwd_workspace_bytes(*geo) > 0
+            self.fused_tail_ws = hb.conv1x1_bn_maxpool_workspace_bytes(*geo)
+            self.fused_tail = self.fused_tail_ws > 0
         nz = self.nconv - 1 if self.fused_tail else self.nconv
         self.z = [torch.empty(Nb, B * c, L, **act) for c in spec.conv[1:1 + nz]]
         # prenorm[i]: layer i takes layer i-1's stored pre-activation and normalises it on load (forward and
@@ -246,7 +255,7 @@ class FusedPointNetCls(ParamArena):
                 self.prenorm[i] = hb.conv1x1_bn_prenorm_supported(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt)
         # ... unless the tail is the one-operator form: its first kernel normalises on load and writes the activated
         # tensor out on the way (tail_x), so that layer skips its own normalisation pass over the tensor
-        self.tail_prenorm = bool(tail_prenorm) and self.fused_tail and not self.unfused and self.nconv >= 2
+        self.tail_prenorm = bool(tail_prenorm) and self.fused_tail and L % 4 == 0 and not self.unfused and self.nconv >= 2
         self.tail_x = None
         if self.tail_prenorm:
             self.prenorm[self.nconv - 1] = True
@@ -285,7 +294,7 @@ class FusedPointNetCls(ParamArena):
                 if i in self.unfused:
                     ws = max(ws, hb.conv1x1_bn_bwd_workspace_bytes(1, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt))
                 elif self.one_pass[i]:
-                    ws = max(ws, hb.conv1x1_bn_bwd_workspace_bytes(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt))
+                    ws = max(ws, hb.conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt))
         for i in range(self.nfc):
             ws = max(ws, hb.linear_bwd_workspace_bytes(B, Nb, spec.fc[i], spec.fc[i + 1], self.dt),
                      hb.linear_fwd_workspace_bytes(B, Nb, spec.fc[i], spec.fc[i + 1], self.dt))
@@ -1073,12 +1082,12 @@ class FusedPointNetSeg(ParamArena):
         self.loss = torch.empty(B, **f32)
         ws = max(4, hb.softmax_xent_points_workspace_bytes(B, Nb, L), hb.linear_bwd_workspace_bytes(B, Nb, Cg, H[1], self.dt),
                  hb.linear_fwd_workspace_bytes(B, Nb, Cg, H[1], self.dt))
-        self.one_pass = [_bn_bwd_one_pass(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt) for i in range(self.nconv)]
+        self.one_pass = [_whole_pieces(L) and _bn_bwd_one_pass(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt) for i in range(self.nconv)]
         for i in range(self.nconv):
             ws = max(ws, hb.conv1x1_bwd_workspace_bytes(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt),
                      hb.conv1x1_bn_fwd_workspace_bytes(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt))
             if self.one_pass[i]:
-                ws = max(ws, hb.conv1x1_bn_bwd_workspace_bytes(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt))
+                ws = max(ws, hb.conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt))
         for i in range(self.nh):
             ws = max(ws, hb.conv1x1_bwd_workspace_bytes(B, Nb, Cp if i == 0 else H[i], H[i + 1], L, self.dt),
                      hb.conv1x1_bn_fwd_workspace_bytes(B, Nb, Cp if i == 0 else H[i], H[i + 1], L, self.dt))
@@ -1125,7 +1134,7 @@ class FusedPointNetSeg(ParamArena):
             # convolution + BatchNorm + ReLU in one call (z is read once, for the normalisation)
             hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, x, xs, self.w(k + ".w"), self.w(k + ".b"), *bn(k), eps, mom,
                               self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], *st(k), self.z[i], _cs(B, co, L),
-                              a, cst, hb.ACT_RELU, 0.0, self.ws)
+                              a, cst, hb.ACT_RELU, 0.0, self.ws if _whole_pieces(L) else None)
             if P is not None:
                 P("conv1x1_fwd", layer=k, x=xv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
             if P is not None:
@@ -1151,7 +1160,7 @@ class FusedPointNetSeg(ParamArena):
             elif i < self.nh - 1:
                 hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, h, hs, self.w(k + ".w"), self.w(k + ".b"), *bn(k), eps, mom,
                                   self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], *st(k), self.zh[i], cs,
-                                  self.ah[i], cs, hb.ACT_RELU, 0.0, self.ws)
+                                  self.ah[i], cs, hb.ACT_RELU, 0.0, self.ws if _whole_pieces(L) else None)
                 if P is not None:
                     P("conv1x1_fwd", layer=k, x=hv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.zh[i])
             else:
@@ -1423,9 +1432,9 @@ class _PointChain(_Views):
         if self.head and self.nconv >= 2:
             geo = (B, Nb, self.conv[-2], self.conv[-1], L, dt)
             wt = A.w(f"{prefix}conv{conv_base + self.nconv - 1}.w")     # the one-operator tail wants 16-byte aligned weights
-            self.fused_tail = hb.conv1x1_bn_maxpool_fwd_workspace_bytes(*geo) > 0 and wt.data_ptr() % 16 == 0
+            self.fused_tail = _whole_pieces(L) and hb.conv1x1_bn_maxpool_workspace_bytes(*geo) > 0 and wt.data_ptr() % 16 == 0
             if self.fused_tail:
-                ws = max(ws, hb.conv1x1_bn_maxpool_fwd_workspace_bytes(*geo), hb.conv1x1_bn_maxpool_bwd_workspace_bytes(*geo))
+                ws = max(ws, hb.conv1x1_bn_maxpool_workspace_bytes(*geo))
         nz = self.nconv - 1 if self.fused_tail else self.nconv
         self.z = [torch.empty(Nb, B * c, L, **act) for c in self.conv[1:1 + nz]]
         na = self.nconv if not self.head else self.nconv - 1            # a chain without a head keeps its last activation
@@ -1433,12 +1442,12 @@ class _PointChain(_Views):
         # (the layer in front of the tail keeps its output: the tail operator reads it)
         self.prenorm = [False] * self.nconv
         for i in range(1, na):
-            self.prenorm[i] = hb.conv1x1_bn_prenorm_supported(B, Nb, self.conv[i], self.conv[i + 1], L, dt)
+            self.prenorm[i] = _whole_pieces(L) and hb.conv1x1_bn_prenorm_supported(B, Nb, self.conv[i], self.conv[i + 1], L, dt)
         self.a = [None if (i + 1 < na and self.prenorm[i + 1]) else torch.empty(Nb, B * c, L, **act)
                   for i, c in enumerate(self.conv[1:1 + na])]
         cmax = max(self.conv)
         self.dbuf = [torch.empty(Nb * B * cmax * L, **act) for _ in range(2)]
-        self.one_pass = [_bn_bwd_one_pass(B, Nb, self.conv[i], self.conv[i + 1], L, dt) for i in range(self.nconv)]
+        self.one_pass = [_whole_pieces(L) and _bn_bwd_one_pass(B, Nb, self.conv[i], self.conv[i + 1], L, dt) for i in range(self.nconv)]
         # bn_sums[i]: layer i's two BatchNorm-backward reductions, left by layer i+1's backward call
         self.bn_sums = [None] * self.nconv
         for i in range(1, self.nconv):
@@ -1449,7 +1458,7 @@ class _PointChain(_Views):
             ws = max(ws, hb.conv1x1_bwd_workspace_bytes(B, Nb, self.conv[i], self.conv[i + 1], L, dt),
                      hb.conv1x1_bn_fwd_workspace_bytes(B, Nb, self.conv[i], self.conv[i + 1], L, dt))
             if self.one_pass[i]:
-                ws = max(ws, hb.conv1x1_bn_bwd_workspace_bytes(B, Nb, self.conv[i], self.conv[i + 1], L, dt))
+                ws = max(ws, hb.conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, self.conv[i], self.conv[i + 1], L, dt))
         if self.head:
             Cp = self.conv[-1]
             self.pooled = torch.empty(B, Nb, Cp, **act)
@@ -1496,7 +1505,7 @@ class _PointChain(_Views):
                                               _cs(B, co, L), y, ys, hb.ACT_RELU, 0.0, ws)
                 else:
                     hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), A.w(k + ".w"), A.w(k + ".b"), *self._bn(k),
-                                      self.z[i], _cs(B, co, L), y, ys, hb.ACT_RELU, 0.0, ws)
+                                      self.z[i], _cs(B, co, L), y, ys, hb.ACT_RELU, 0.0, ws if _whole_pieces(L) else None)
                 x, ci = y, co
                 continue
             hb.conv1x1_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), A.w(k + ".w"), A.w(k + ".b"), self.z[i], _cs(B, co, L))

@@ -57,6 +57,8 @@ _SIGS = {
     "hfta_conv1x1_bn_fwd": (_i, [_i, _i, _i, _i, _i, _i, _p, _s4, _p, _p, _p, _p, _f, _f, _p, _p, _p, _p, _p, _s4, _p, _s4,
                                  _i, _f, _p, _sz, _p]),
     "hfta_conv1x1_bn_bwd_one_pass": (_i, [_i, _i, _i, _i, _i, _i]),
+    "hfta_conv1x1_bn_bwd_stream_workspace_bytes": (_sz, [_i, _i, _i, _i, _i, _i]),
+    "hfta_conv1x1_bn_maxpool_workspace_bytes": (_sz, [_i] * 6),
     "hfta_conv1x1_bn_bwd_workspace_bytes": (_sz, [_i, _i, _i, _i, _i, _i]),
     "hfta_conv1x1_bn_bwd": (_i, [_i, _i, _i, _i, _i, _i, _p, _s4, _p, _p, _s4, _p, _s4, _p, _p, _p, _p, _p, _s4, _p, _p, _p, _p,
                                  _p, _i, _f, _p, _sz, _p]),
@@ -250,6 +252,11 @@ def conv1x1_bn_bwd_one_pass(B, Nb, Ci, Co, L, dtype) -> bool:
     return bool(_lib.hfta_conv1x1_bn_bwd_one_pass(B, Nb, Ci, Co, L, dtype))
 
 
+def conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, Ci, Co, L, dtype) -> int:
+    """Workspace of the one-kernel form (rows of any length), 0 where it does not take the shape."""
+    return _lib.hfta_conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, Ci, Co, L, dtype)
+
+
 def conv1x1_bn_bwd_workspace_bytes(B, Nb, Ci, Co, L, dtype) -> int:
     return _lib.hfta_conv1x1_bn_bwd_workspace_bytes(B, Nb, Ci, Co, L, dtype)
 
@@ -421,6 +428,11 @@ def conv1x1_bn_maxpool_prenorm_bwd(B, Nb, Ci, Co, L, dtype, Xpre, xs, in_gamma, 
 
 def conv1x1_bn_maxpool_saved_floats(B, Ci, Co):
     return _lib.hfta_conv1x1_bn_maxpool_saved_floats(B, Ci, Co)
+
+
+def conv1x1_bn_maxpool_workspace_bytes(B, Nb, Ci, Co, L, dtype) -> int:
+    """Workspace of either direction of the one-operator tail (rows of any length), 0 where unsupported."""
+    return _lib.hfta_conv1x1_bn_maxpool_workspace_bytes(B, Nb, Ci, Co, L, dtype)
 
 
 def conv1x1_bn_maxpool_fwd_workspace_bytes(B, Nb, Ci, Co, L, dtype):

@@ -30,6 +30,7 @@ struct BnFwdArgs {
 
 template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT) void bn_fwd_conv_kernel(BnFwdArgs p) {
+  constexpr int UN = bn_unroll(VEC);
   __shared__ float sh[NT / 64][2];
   const int c = blockIdx.x, b = blockIdx.y;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
@@ -38,18 +39,18 @@ __global__ __launch_bounds__(NT) void bn_fwd_conv_kernel(BnFwdArgs p) {
   const float shift = Elem<T>::load(x);
   float s1 = 0.f, s2 = 0.f;
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
-    // BN_UNROLL pieces per trip, their loads issued together (a piece past the end re-reads the
+    // UN pieces per trip, their loads issued together (a piece past the end re-reads the
     // channel's first piece and is not used): the bytes in flight per thread set the bandwidth
-    float v[BN_UNROLL][VEC];
-    bool ok[BN_UNROLL];
+    float v[UN][VEC];
+    bool ok[UN];
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u) {
+    for (int u = 0; u < UN; ++u) {
       ok[u] = w.n < p.Nb;
       load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
       w.step();
     }
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u)
+    for (int u = 0; u < UN; ++u)
       if (ok[u]) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) { const float d = v[u][e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
@@ -75,16 +76,16 @@ __global__ __launch_bounds__(NT) void bn_fwd_conv_kernel(BnFwdArgs p) {
   }
   if (!p.Y) return;                      // statistics only: a consumer normalises on load
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
-    float v[BN_UNROLL][VEC];
-    int n[BN_UNROLL], ch[BN_UNROLL];
+    float v[UN][VEC];
+    int n[UN], ch[UN];
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u) {
+    for (int u = 0; u < UN; ++u) {
       n[u] = w.n; ch[u] = w.ch;
       load_vec<T, VEC>(n[u] < p.Nb ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
       w.step();
     }
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u)
+    for (int u = 0; u < UN; ++u)
       if (n[u] < p.Nb) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[u][e] = apply_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope);
@@ -97,12 +98,12 @@ __global__ __launch_bounds__(NT) void bn_fwd_conv_kernel(BnFwdArgs p) {
 
 // Normalisation with given statistics (the forward kernel's second pass alone): what a consumer that
 // normalises on load computes, written out.
-template <typename T, int VEC, int NT>
+template <typename T, int VEC, int NT, bool RAG>
 __global__ __launch_bounds__(NT) void bn_apply_conv_kernel(BnFwdArgs p) {
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   T* y = reinterpret_cast<T*>(p.Y) + b * p.ysb + c * p.ysc;
-  const int chunks = p.L / VEC;
+  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
   const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
     float v[BN_UNROLL][VEC];
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(NT) void bn_apply_conv_kernel(BnFwdArgs p) {
 #pragma unroll
     for (int u = 0; u < BN_UNROLL; ++u) {
       n[u] = w.n; ch[u] = w.ch;
-      load_vec<T, VEC>(n[u] < p.Nb ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
+      load_piece<T, VEC, RAG>(n[u] < p.Nb ? x + n[u] * p.xsn : x, n[u] < p.Nb ? ch[u] : 0, p.L, v[u]);
       w.step();
     }
 #pragma unroll
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(NT) void bn_apply_conv_kernel(BnFwdArgs p) {
       if (n[u] < p.Nb) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[u][e] = apply_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope);
-        store_vec<T, VEC>(y + n[u] * p.ysn + ch[u] * VEC, v[u]);
+        store_piece<T, VEC, RAG>(y + n[u] * p.ysn, ch[u], p.L, v[u]);
       }
   }
 }
@@ -230,6 +231,7 @@ struct BnBwdArgs {
 
 template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT) void bn_bwd_conv_kernel(BnBwdArgs p) {
+  constexpr int UN = bn_unroll(VEC);
   __shared__ float sh[NT / 64][2];
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
@@ -239,17 +241,17 @@ __global__ __launch_bounds__(NT) void bn_bwd_conv_kernel(BnBwdArgs p) {
   const int chunks = p.L / VEC;
   float s1 = 0.f, s2 = 0.f;
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
-    float v[BN_UNROLL][VEC], d[BN_UNROLL][VEC];
-    bool ok[BN_UNROLL];
+    float v[UN][VEC], d[UN][VEC];
+    bool ok[UN];
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u) {
+    for (int u = 0; u < UN; ++u) {
       ok[u] = w.n < p.Nb;
       load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
       load_vec<T, VEC>(ok[u] ? dy + w.n * p.dysn + w.ch * VEC : dy, d[u]);
       w.step();
     }
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u)
+    for (int u = 0; u < UN; ++u)
       if (ok[u]) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
@@ -266,10 +268,10 @@ __global__ __launch_bounds__(NT) void bn_bwd_conv_kernel(BnBwdArgs p) {
   const float mb = s1 / m, mg = s2 / m, sc = g * invstd;
   float s3 = 0.f;
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
-    float v[BN_UNROLL][VEC], d[BN_UNROLL][VEC];
-    int n[BN_UNROLL], ch[BN_UNROLL];
+    float v[UN][VEC], d[UN][VEC];
+    int n[UN], ch[UN];
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u) {
+    for (int u = 0; u < UN; ++u) {
       n[u] = w.n; ch[u] = w.ch;
       const bool ok = n[u] < p.Nb;
       load_vec<T, VEC>(ok ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(NT) void bn_bwd_conv_kernel(BnBwdArgs p) {
       w.step();
     }
 #pragma unroll
-    for (int u = 0; u < BN_UNROLL; ++u)
+    for (int u = 0; u < UN; ++u)
       if (n[u] < p.Nb) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
@@ -299,14 +301,14 @@ __global__ __launch_bounds__(NT) void bn_bwd_conv_kernel(BnBwdArgs p) {
 // The reduction half of the backward pass alone: dbeta, dgamma, and per channel the eight constants
 // a consumer needs to form dX = sc * (g - mb - xhat * mg) by itself while it streams x and dY:
 // coef[k] = {mean, invstd, gamma, beta, mb, mg, sc, 0}.  Nothing of size [Nb, C, L] is written.
-template <typename T, int VEC, int NT>
+template <typename T, int VEC, int NT, bool RAG>
 __global__ __launch_bounds__(NT) void bn_bwd_conv_coef_kernel(BnBwdArgs p, float* __restrict__ coef) {
   __shared__ float sh[NT / 64][2];
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   const T* dy = reinterpret_cast<const T*>(p.dY) + b * p.dysb + c * p.dysc;
   const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
-  const int chunks = p.L / VEC;
+  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
   float s1 = 0.f, s2 = 0.f;
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
     float v[BN_UNROLL][VEC], d[BN_UNROLL][VEC];
@@ -314,8 +316,8 @@ __global__ __launch_bounds__(NT) void bn_bwd_conv_coef_kernel(BnBwdArgs p, float
 #pragma unroll
     for (int u = 0; u < BN_UNROLL; ++u) {
       ok[u] = w.n < p.Nb;
-      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
-      load_vec<T, VEC>(ok[u] ? dy + w.n * p.dysn + w.ch * VEC : dy, d[u]);
+      load_piece<T, VEC, RAG>(ok[u] ? x + w.n * p.xsn : x, ok[u] ? w.ch : 0, p.L, v[u]);
+      load_piece<T, VEC, RAG>(ok[u] ? dy + w.n * p.dysn : dy, ok[u] ? w.ch : 0, p.L, d[u]);   // past a row's end dY is zero: adds nothing
       w.step();
     }
 #pragma unroll
@@ -412,20 +414,20 @@ struct BnEvalArgs {
   float eps, slope;
 };
 
-template <typename T, int VEC, int NT>
+template <typename T, int VEC, int NT, bool RAG>
 __global__ __launch_bounds__(NT) void bn_eval_conv_kernel(BnEvalArgs p) {
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   T* y = reinterpret_cast<T*>(p.Y) + b * p.ysb + c * p.ysc;
   const float mean = p.running_mean[k];
   const float scale = p.gamma[k] * (1.0f / sqrtf(p.running_var[k] + p.eps)), bt = p.beta[k];
-  const int chunks = p.L / VEC;
+  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
   for (RowWalk w(chunks, NT); w.n < p.Nb; w.step()) {
     float v[VEC];
-    load_vec<T, VEC>(x + w.n * p.xsn + w.ch * VEC, v);
+    load_piece<T, VEC, RAG>(x + w.n * p.xsn, w.ch, p.L, v);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) v[e] = apply_act(fmaf(scale, v[e] - mean, bt), p.act, p.slope);
-    store_vec<T, VEC>(y + w.n * p.ysn + w.ch * VEC, v);
+    store_piece<T, VEC, RAG>(y + w.n * p.ysn, w.ch, p.L, v);
   }
 }
 
@@ -470,10 +472,13 @@ int bn_fwd_from_partials(int B, int Nb, int C, int L, int dtype, const void* X, 
   const dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype) && vec_ok(Y, ys, L, dtype);
   const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-  if (v4) { if (big) hipLaunchKernelGGL((bn_apply_conv_kernel<bf16_raw, 4, 1024>), grid, dim3(1024), 0, st, a);
-            else hipLaunchKernelGGL((bn_apply_conv_kernel<bf16_raw, 4, 256>), grid, dim3(256), 0, st, a); }
-  else { if (big) hipLaunchKernelGGL((bn_apply_conv_kernel<bf16_raw, 1, 1024>), grid, dim3(1024), 0, st, a);
-         else hipLaunchKernelGGL((bn_apply_conv_kernel<bf16_raw, 1, 256>), grid, dim3(256), 0, st, a); }
+#define HFTA_BN_NORM(T, V, R) \
+  do { if (big) hipLaunchKernelGGL((bn_apply_conv_kernel<T, V, 1024, R>), grid, dim3(1024), 0, st, a); \
+       else hipLaunchKernelGGL((bn_apply_conv_kernel<T, V, 256, R>), grid, dim3(256), 0, st, a); } while (0)
+  if (v4) HFTA_BN_NORM(bf16_raw, 4, false);
+  else if (L >= 4) HFTA_BN_NORM(bf16_raw, 4, true);
+  else HFTA_BN_NORM(bf16_raw, 1, false);
+#undef HFTA_BN_NORM
   return launch_status();
 }
 
@@ -508,11 +513,10 @@ int bn_bwd_coef(int B, int Nb, int C, int L, int dtype, const void* X, const int
   const dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype) && vec_ok(dY, dys, L, dtype);
   const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_BN_COEF(T, V) \
-  do { if (big) hipLaunchKernelGGL((bn_bwd_conv_coef_kernel<T, V, 1024>), grid, dim3(1024), 0, st, a, coef); \
-       else hipLaunchKernelGGL((bn_bwd_conv_coef_kernel<T, V, 256>), grid, dim3(256), 0, st, a, coef); } while (0)
-  if (dtype == HFTA_BF16) { if (v4) HFTA_BN_COEF(bf16_raw, 4); else HFTA_BN_COEF(bf16_raw, 1); }
-  else { if (v4) HFTA_BN_COEF(float, 4); else HFTA_BN_COEF(float, 1); }
+#define HFTA_BN_COEF(T, V, R) \
+  do { if (big) hipLaunchKernelGGL((bn_bwd_conv_coef_kernel<T, V, 1024, R>), grid, dim3(1024), 0, st, a, coef); \
+       else hipLaunchKernelGGL((bn_bwd_conv_coef_kernel<T, V, 256, R>), grid, dim3(256), 0, st, a, coef); } while (0)
+  HFTA_BN_BY_ROWS(HFTA_BN_COEF);
 #undef HFTA_BN_COEF
   return launch_status();
 }
@@ -576,11 +580,10 @@ int hfta_bn_apply_fwd(int B, int Nb, int C, int L, int dtype, const void* X, con
   const dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype) && vec_ok(Y, ys, L, dtype);
   const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_BN_APPLY(T, V) \
-  do { if (big) hipLaunchKernelGGL((bn_apply_conv_kernel<T, V, 1024>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_apply_conv_kernel<T, V, 256>), grid, dim3(256), 0, st, a); } while (0)
-  if (dtype == HFTA_BF16) { if (v4) HFTA_BN_APPLY(bf16_raw, 4); else HFTA_BN_APPLY(bf16_raw, 1); }
-  else { if (v4) HFTA_BN_APPLY(float, 4); else HFTA_BN_APPLY(float, 1); }
+#define HFTA_BN_APPLY(T, V, R) \
+  do { if (big) hipLaunchKernelGGL((bn_apply_conv_kernel<T, V, 1024, R>), grid, dim3(1024), 0, st, a); \
+       else hipLaunchKernelGGL((bn_apply_conv_kernel<T, V, 256, R>), grid, dim3(256), 0, st, a); } while (0)
+  HFTA_BN_BY_ROWS(HFTA_BN_APPLY);
 #undef HFTA_BN_APPLY
   return launch_status();
 }
@@ -608,11 +611,10 @@ int hfta_bn_eval_fwd(int B, int Nb, int C, int L, int dtype, const void* X, cons
   dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype) && vec_ok(Y, ys, L, dtype);
   const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_BN_EVAL(T, V) \
-  do { if (big) hipLaunchKernelGGL((bn_eval_conv_kernel<T, V, 1024>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_eval_conv_kernel<T, V, 256>), grid, dim3(256), 0, st, a); } while (0)
-  if (dtype == HFTA_BF16) { if (v4) HFTA_BN_EVAL(bf16_raw, 4); else HFTA_BN_EVAL(bf16_raw, 1); }
-  else { if (v4) HFTA_BN_EVAL(float, 4); else HFTA_BN_EVAL(float, 1); }
+#define HFTA_BN_EVAL(T, V, R) \
+  do { if (big) hipLaunchKernelGGL((bn_eval_conv_kernel<T, V, 1024, R>), grid, dim3(1024), 0, st, a); \
+       else hipLaunchKernelGGL((bn_eval_conv_kernel<T, V, 256, R>), grid, dim3(256), 0, st, a); } while (0)
+  HFTA_BN_BY_ROWS(HFTA_BN_EVAL);
 #undef HFTA_BN_EVAL
   return launch_status();
 }

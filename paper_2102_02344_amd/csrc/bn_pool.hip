@@ -29,7 +29,7 @@ struct BnPoolFwdArgs {
 
 template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
-  constexpr int NW = NT / 64;
+  constexpr int NW = NT / 64, UN = bn_unroll(VEC);
   __shared__ float sh[NW][2];
   const int c = blockIdx.x, b = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -39,12 +39,21 @@ __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
   float s1 = 0.f, s2 = 0.f;
   // same element -> thread assignment and reduction order as the stand-alone BatchNorm forward,
   // so the statistics (and with them every activated value) come out bit-identical
-  for (RowWalk w(chunks, NT); w.n < p.Nb; w.step()) {
-    const int n = w.n, ch = w.ch;
-    float v[VEC];
-    load_vec<T, VEC>(x + n * p.xsn + ch * VEC, v);
+  for (RowWalk w(chunks, NT); w.n < p.Nb;) {
+    float v[UN][VEC];
+    bool ok[UN];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) { const float d = v[e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
+    for (int u = 0; u < UN; ++u) {
+      ok[u] = w.n < p.Nb;
+      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
+      w.step();
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (ok[u]) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { const float d = v[u][e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
+      }
   }
   block_sum2<NW>(s1, s2, sh);
   const float m = (float)p.Nb * (float)p.L;
@@ -68,14 +77,21 @@ __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
     const T* row = x + n * p.xsn;
     float best = -INFINITY;
     int bi = 0x7fffffff;
-    for (int ch = lane; ch < chunks; ch += 64) {
-      float v[VEC];
-      load_vec<T, VEC>(row + ch * VEC, v);
+    for (int c0 = lane; c0 < chunks; c0 += 64 * UN) {
+      float v[UN][VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        // the activated value exactly as hfta_bn_fwd would have stored it
-        const float y = Elem<T>::to_f32(Elem<T>::from_f32(apply_act(fmaf(g, (v[e] - mean) * invstd, bt), p.act, p.slope)));
-        if (y > best || bi == 0x7fffffff) { best = y; bi = ch * VEC + e; }
+      for (int u = 0; u < UN; ++u) load_vec<T, VEC>(row + min(c0 + 64 * u, chunks - 1) * VEC, v[u]);
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int ch = c0 + 64 * u;
+        if (ch < chunks) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            // the activated value exactly as hfta_bn_fwd would have stored it
+            const float y = Elem<T>::to_f32(Elem<T>::from_f32(apply_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope)));
+            if (y > best || bi == 0x7fffffff) { best = y; bi = ch * VEC + e; }
+          }
+        }
       }
     }
 #pragma unroll
@@ -103,7 +119,7 @@ struct BnPoolBwdArgs {
 
 template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
-  constexpr int NW = NT / 64;
+  constexpr int NW = NT / 64, UN = bn_unroll(VEC);
   __shared__ float sh[NW][2];
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -132,18 +148,25 @@ __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
     T* drow = dx + n * p.dxsn;
     const int hit = min(max(ix[n * p.vsn], 0), p.L - 1);
     const float gv = Elem<T>::load(dv + n * p.vsn);
-    for (int ch = lane; ch < chunks; ch += 64) {
-      float v[VEC];
-      load_vec<T, VEC>(row + ch * VEC, v);
+    for (int c0 = lane; c0 < chunks; c0 += 64 * UN) {
+      float v[UN][VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const float xh = (v[e] - mean) * invstd;
-        float gr = 0.f;
-        if (ch * VEC + e == hit) gr = gv * act_grad(fmaf(g, xh, bt), p.act, p.slope);
-        v[e] = sc * (gr - mb - xh * mg);
-        s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[e]));
+      for (int u = 0; u < UN; ++u) load_vec<T, VEC>(row + min(c0 + 64 * u, chunks - 1) * VEC, v[u]);
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int ch = c0 + 64 * u;
+        if (ch < chunks) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            const float xh = (v[u][e] - mean) * invstd;
+            float gr = 0.f;
+            if (ch * VEC + e == hit) gr = gv * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+            v[u][e] = sc * (gr - mb - xh * mg);
+            s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[u][e]));
+          }
+          store_vec<T, VEC>(drow + ch * VEC, v[u]);
+        }
       }
-      store_vec<T, VEC>(drow + ch * VEC, v);
     }
   }
   if (p.dx_sum) {

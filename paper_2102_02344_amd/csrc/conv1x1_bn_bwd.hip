@@ -195,23 +195,24 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
     const __amdgpu_buffer_rsrc_t rz = pf_rsrc(p.Z + b * p.z_g0 + n * p.z_g1, p.z_extent);
     const __amdgpu_buffer_rsrc_t rx = pf_rsrc(p.X + b * p.x_g0 + n * p.x_g1, p.x_extent);
     const int c = l0 + ng * 4;
-    const bool cok = live && c + 4 <= p.L;
+    const bool cok = live && c < p.L;
+    const uint32_t cb = (uint32_t)row_piece_at(c, p.L) * 2u;
 #pragma unroll
     for (int i = 0; i < BPT; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int k = (sh + 2 * i) * 32 + 4 * kq + j;
         const bool ok = cok && k < p.Co;
-        const pf_u32x2 vd = __builtin_amdgcn_raw_buffer_load_b64(rd, (int)(ok ? (uint32_t)k * dy_ldb + (uint32_t)c * 2u : PF_OOB), 0, 0);
-        const pf_u32x2 vz = __builtin_amdgcn_raw_buffer_load_b64(rz, (int)(ok ? (uint32_t)k * z_ldb + (uint32_t)c * 2u : PF_OOB), 0, 0);
+        const pf_u32x2 vd = __builtin_amdgcn_raw_buffer_load_b64(rd, (int)(ok ? (uint32_t)k * dy_ldb + cb : PF_OOB), 0, 0);
+        const pf_u32x2 vz = __builtin_amdgcn_raw_buffer_load_b64(rz, (int)(ok ? (uint32_t)k * z_ldb + cb : PF_OOB), 0, 0);
         g.d[i][j] = make_uint2(vd.x, vd.y);
         g.z[i][j] = make_uint2(vz.x, vz.y);
       }
 #pragma unroll
     for (int i = 0; i < XPT; ++i) {
       const int id = t + CBB_THREADS * i, row = id >> 5, cx = l0 + (id & 31) * 4;
-      const bool ok = live && row < p.Ci && cx + 4 <= p.L;
-      const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)row * x_ldb + (uint32_t)cx * 2u : PF_OOB), 0, 0);
+      const bool ok = live && row < p.Ci && cx < p.L;
+      const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)row * x_ldb + (uint32_t)row_piece_at(cx, p.L) * 2u : PF_OOB), 0, 0);
       g.x[i] = make_uint2(v.x, v.y);
     }
   };
@@ -243,7 +244,19 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
       const int u = u0 + d;
       const bool live = u < uend;
       const int n = live ? u / p.slices : 0, l0 = live ? (u - n * p.slices) * 128 : p.slices * 128;
-      const bool cok = l0 + ng * 4 + 4 <= p.L;
+      const int left = p.L - (l0 + ng * 4);      // of this thread's four points, how many exist
+      if ((p.L & 3) && live && l0 + 128 > p.L) { // the sample's last slice, and its last piece is a partial one
+        const int c = l0 + ng * 4, cx = l0 + (t & 31) * 4;
+#pragma unroll
+        for (int i = 0; i < BPT; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            q[d].d[i][j] = row_piece_place(q[d].d[i][j], c, p.L);
+            q[d].z[i][j] = row_piece_place(q[d].z[i][j], c, p.L);
+          }
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) q[d].x[i] = row_piece_place(q[d].x[i], cx, p.L);
+      }
       // ---- dz of this slice, rounded, into both LDS tiles; x into its tile ----
 #pragma unroll
       for (int i = 0; i < BPT; ++i) {
@@ -262,7 +275,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
             const float xh = (zz[e] - c0.x) * c0.y;
             const float gr = dd[e] * (fmaf(c0.z, xh, c0.w) > 0.f ? 1.f : act_neg);
             const float v = c1.z * (gr - c1.x - xh * c1.y);
-            dz[j][e] = cok ? v : 0.f;        // points past the sample's end add nothing to dW and dbias
+            dz[j][e] = e < left ? v : 0.f;        // points past the sample's end add nothing to dW and dbias
           }
           uint2 o;
           o.x = pack_bf16x2(dz[j][0], dz[j][1]);
@@ -286,7 +299,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
         uint2 xv = q[d].x[i];
         if (K::SUMS && sums_on) *reinterpret_cast<uint2*>(zraw + id * 8) = xv;
         if (xin) {
-          xv = in_norm_apply4(xv, xc[id >> 5], l0 + (id & 31) * 4 + 4 <= p.L, p.in_act, p.in_slope);
+          xv = in_norm_apply4(xv, xc[id >> 5], p.L - (l0 + (id & 31) * 4), p.in_act, p.in_slope);
         }
         *reinterpret_cast<uint2*>(xN + (id >> 5) * PN + (id & 31) * 8) = xv;
       }
@@ -340,8 +353,8 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
         for (int i = 0; i < XPT; ++i) {
           const int id = t + CBB_THREADS * i, row = id >> 5, c = l0 + (id & 31) * 4;
           const uint2 v = *reinterpret_cast<const uint2*>(stg + row * PS + (id & 31) * 8);
-          const bool okp = row < p.Ci && c + 4 <= p.L;
-          if (okp) *reinterpret_cast<uint2*>(dXb + (int64_t)row * p.dx_ld + c) = v;
+          const bool okp = row < p.Ci && c < p.L;        // (past the end dX and x are zero: nothing for the sums)
+          if (okp) row_piece_store(dXb + (int64_t)row * p.dx_ld, v, c, p.L);
           if (K::SUMS && sums_on) {
             const uint2 zr = *reinterpret_cast<const uint2*>(zraw + id * 8);
             const float4 ic = xc[row];       // mean, invstd, gamma, beta of the input block
@@ -462,7 +475,7 @@ int cbb_point_halves(int Ci, int Co) { return (Ci <= 64 && Co <= 64) ? 2 : 1; } 
 bool conv1x1_bn_bwd_stream_sums(int Ci) { return Ci <= 64; }
 
 bool conv1x1_bn_bwd_streams(int B, int Ci, int Co, int L, int dtype) {
-  return dtype == HFTA_BF16 && Ci <= 128 && Co <= 128 && L % 4 == 0 && B <= 65535;
+  return dtype == HFTA_BF16 && Ci <= 128 && Co <= 128 && L >= 4 && B <= 65535;
 }
 
 size_t conv1x1_bn_bwd_stream_bytes(int B, int Nb, int Ci, int Co, int L) {
@@ -479,9 +492,8 @@ int conv1x1_bn_bwd_stream(int B, int Nb, int Ci, int Co, int L, const void* X, c
                           const float* in_mean, const float* in_invstd, int in_act, float in_slope, const float* sums,
                           float* in_sums) {
   auto al = [](const void* q, size_t a) { return (reinterpret_cast<uintptr_t>(q) % a) == 0; };
-  auto s4 = [](const int64_t* s) { return s[0] % 4 == 0 && s[1] % 4 == 0 && s[2] % 4 == 0 && s[2] > 0 && s[3] == 1; };
-  if (!al(X, 8) || !al(Z, 8) || !al(dY, 8) || !s4(xs) || !s4(zs) || !s4(dys) || !al(workspace, 16)) return HFTA_EUNSUPPORTED;
-  if (dX && (!s4(dxs) || !al(dX, 8))) return HFTA_EUNSUPPORTED;
+  auto rows = [](const int64_t* s) { return s[2] > 0 && s[3] == 1; };
+  if (!rows(xs) || !rows(zs) || !rows(dys) || !al(workspace, 16) || (dX && !rows(dxs))) return HFTA_EUNSUPPORTED;
   if (in_gamma && (!in_beta || !in_mean || !in_invstd ||
                    (in_act != HFTA_ACT_NONE && in_act != HFTA_ACT_RELU && in_act != HFTA_ACT_LEAKY)))
     return HFTA_EUNSUPPORTED;

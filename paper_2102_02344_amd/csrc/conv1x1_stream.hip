@@ -100,17 +100,23 @@ __global__ __launch_bounds__(GEMM_THREADS, ONE ? 4 : 1) void conv1x1_stream_kern
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int k = s * 32 + 4 * kq + j;
-        const bool ok = k < p.Ci && c + 4 <= p.L;
-        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)k * ldb + (uint32_t)c * 2u : PF_OOB), 0, 0);
+        const bool ok = k < p.Ci && c < p.L;
+        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)k * ldb + (uint32_t)row_piece_at(c, p.L) * 2u : PF_OOB), 0, 0);
         q[s][j] = make_uint2(v.x, v.y);
       }
-    if (XF) {
-      const float4* ic = reinterpret_cast<const float4*>(smem + SMEM);
-      const bool cok = c + 4 <= p.L;       // points past the sample's end stay zero (the statistics epilogue counts on it)
+    if ((p.L & 3) && l0 + 128 > p.L) {   // the sample's last slice, and its last piece is a partial one
 #pragma unroll
       for (int s = 0; s < SUB; ++s)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) q[s][j] = in_norm_apply4(q[s][j], ic[s * 32 + 4 * kq + j], cok, p.in_act, p.in_slope);
+        for (int j = 0; j < 4; ++j) q[s][j] = row_piece_place(q[s][j], c, p.L);
+    }
+    if (XF) {
+      const float4* ic = reinterpret_cast<const float4*>(smem + SMEM);
+      const int left = p.L - c;            // points past the sample's end stay zero (the statistics epilogue counts on it)
+#pragma unroll
+      for (int s = 0; s < SUB; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[s][j] = in_norm_apply4(q[s][j], ic[s * 32 + 4 * kq + j], left, p.in_act, p.in_slope);
     }
 #pragma unroll
     for (int s = 0; s < SUB; ++s) {
@@ -219,13 +225,13 @@ int conv1x1_stream_fwd(int B, int Nb, int Ci, int Co, int L, const void* X, cons
                        float* stat_part, const float* in_gamma, const float* in_beta, const float* in_mean,
                        const float* in_invstd, int in_act, float in_slope) {
   auto al = [](const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; };
-  if (Ci > 256 || Ci % 8 != 0 || Co < 64 || L % 4 != 0) return HFTA_EUNSUPPORTED;
+  if (Ci > 256 || Ci % 8 != 0 || Co < 64 || L < 4) return HFTA_EUNSUPPORTED;
   if (Ci > 128 && Co < STREAM_WIDE_MIN_CO) return HFTA_EUNSUPPORTED;
   if (act == HFTA_ACT_TANH || act == HFTA_ACT_GELU || (stat_part && act != HFTA_ACT_NONE)) return HFTA_EUNSUPPORTED;
   if (in_gamma && (Ci > 128 || !in_beta || !in_mean || !in_invstd ||
                    (in_act != HFTA_ACT_NONE && in_act != HFTA_ACT_RELU && in_act != HFTA_ACT_LEAKY)))
     return HFTA_EUNSUPPORTED;
-  if (!al(W, 16) || !al(X, 8) || xs[0] % 4 || xs[1] % 4 || xs[2] % 4 || xs[2] <= 0) return HFTA_EUNSUPPORTED;
+  if (!al(W, 16) || xs[2] <= 0) return HFTA_EUNSUPPORTED;
   const int64_t x_ext = ((int64_t)(Ci - 1) * xs[2] + L) * 2, w_ext = (int64_t)Co * Ci * 2;
   if (x_ext >= (int64_t)1 << 31 || w_ext >= (int64_t)1 << 31) return HFTA_EUNSUPPORTED;
   StreamArgs a;
@@ -235,11 +241,7 @@ int conv1x1_stream_fwd(int B, int Nb, int Ci, int Co, int L, const void* X, cons
   a.Ci = Ci; a.Co = Co; a.L = L; a.Nb = Nb;
   a.tiles_co = (Co + 127) / 128;
   a.act = act; a.slope = slope;
-  a.c_vec = 0;
-  for (int w = 16; w >= 8; w >>= 1) {
-    const int q = w / 2;
-    if (al(Y, w) && ys[0] % q == 0 && ys[1] % q == 0 && ys[2] % q == 0) { a.c_vec = w; break; }
-  }
+  a.c_vec = al(Y, 16) && ys[0] % 8 == 0 && ys[1] % 8 == 0 && ys[2] % 8 == 0 ? 16 : 8;   // 8-byte pieces at any row alignment
   a.w_extent = (uint32_t)w_ext; a.x_extent = (uint32_t)x_ext;
   a.stat_part = stat_part;
   a.in_gamma = in_gamma; a.in_beta = in_beta; a.in_mean = in_mean; a.in_invstd = in_invstd;

@@ -50,7 +50,6 @@ struct CbpArgs {
   uint32_t* skey;     // [B][Nb][Co]: argmax positions sorted by point, point << 10 | channel
   float* sval;        // [B][Nb][Co]: s in that order
   int* toff;          // [B][Nb][tiles + 1]: where each 128-point tile starts in the sorted order
-  int c_vec;
   uint32_t x_extent, g_extent;
 };
 
@@ -125,8 +124,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gram_kernel(GramArgs p) {
 #pragma unroll
     for (int h = 0; h < 16; ++h) {
       const int ci = row + 8 * h;
-      const bool ok = tile < t1 && ci < p.Ci && l + 4 <= p.L;
-      const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)ci * (uint32_t)(p.xsc * 2) + (uint32_t)l * 2u : PF_OOB), 0, 0);
+      const bool ok = tile < t1 && ci < p.Ci && l < p.L;
+      const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)ci * (uint32_t)(p.xsc * 2) + (uint32_t)row_piece_at(l, p.L) * 2u : PF_OOB), 0, 0);
       q[h] = make_uint2(v.x, v.y);
     }
   };
@@ -141,16 +140,19 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gram_kernel(GramArgs p) {
   load(t0);
   for (int tile = t0; tile < t1; ++tile) {
     unsigned char* buf = smem[(tile - t0) & 1];
-    if (xin) {
-      const int nn = tile / p.tiles_k;
-      const bool ok = (tile - nn * p.tiles_k) * GPTS + piece * 4 + 4 <= p.L;
+    const int nn = tile / p.tiles_k, l = (tile - nn * p.tiles_k) * GPTS + piece * 4;
+    if ((p.L & 3) && tile - nn * p.tiles_k == p.tiles_k - 1) {   // the sample's last tile, and its last piece is a partial one
 #pragma unroll
-      for (int h = 0; h < 16; ++h) q[h] = in_norm_apply4(q[h], icn[row + 8 * h], ok, p.in.act, p.in.slope);
-      if (p.Xact && ok) {                                  // every element of X passes through exactly one workgroup
-        bf16_raw* o = p.Xact + b * p.asb + nn * p.asn + (tile - nn * p.tiles_k) * GPTS + piece * 4;
+      for (int h = 0; h < 16; ++h) q[h] = row_piece_place(q[h], l, p.L);
+    }
+    if (xin) {
+#pragma unroll
+      for (int h = 0; h < 16; ++h) q[h] = in_norm_apply4(q[h], icn[row + 8 * h], p.L - l, p.in.act, p.in.slope);
+      if (p.Xact && l < p.L) {                             // every element of X passes through exactly one workgroup
+        bf16_raw* o = p.Xact + b * p.asb + nn * p.asn;
 #pragma unroll
         for (int h = 0; h < 16; ++h)
-          if (row + 8 * h < p.Ci) *reinterpret_cast<uint2*>(o + (row + 8 * h) * p.asc) = q[h];
+          if (row + 8 * h < p.Ci) row_piece_store(o + (row + 8 * h) * p.asc, q[h], l, p.L);
       }
     }
 #pragma unroll
@@ -378,10 +380,16 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int k = s * 32 + 4 * kq + j;
-        const bool ok = k < p.Ci && c + 4 <= p.L;
-        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)k * ldb + (uint32_t)c * 2u : PF_OOB), 0, 0);
+        const bool ok = k < p.Ci && c < p.L;
+        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)k * ldb + (uint32_t)row_piece_at(c, p.L) * 2u : PF_OOB), 0, 0);
         q[s][j] = make_uint2(v.x, v.y);
       }
+    if ((p.L & 3) && l0 + 128 > p.L) {   // the sample's last slice, and its last piece is a partial one
+#pragma unroll
+      for (int s = 0; s < SUB; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[s][j] = row_piece_place(q[s][j], c, p.L);
+    }
     if (p.in.gamma) {                    // X is a stored pre-activation: the block's activated output is formed here
       for (int k = t; k < KT; k += GEMM_THREADS)
         icn[k] = k < p.Ci ? in_norm_consts(p.in, (int64_t)b * p.Ci + k) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -389,7 +397,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
 #pragma unroll
       for (int s = 0; s < SUB; ++s)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) q[s][j] = in_norm_apply4(q[s][j], icn[s * 32 + 4 * kq + j], c + 4 <= p.L, p.in.act, p.in.slope);
+        for (int j = 0; j < 4; ++j) q[s][j] = in_norm_apply4(q[s][j], icn[s * 32 + 4 * kq + j], p.L - c, p.in.act, p.in.slope);
     }
     // the tile's hit list rides along with the tile loads
     const uint32_t key0 = t < nh ? skey[t] : 0u;
@@ -567,15 +575,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
       const int m = pass * 64 + rr, l = l0 + cp * 4;
       const float4 f = *reinterpret_cast<const float4*>(stage + rr * SP + cp * 4);
       if (m < p.Ci && l < p.L) {
-        bf16_raw* d = dXb + (int64_t)m * p.dxsc + l;
-        if (p.c_vec >= 8 && l + 4 <= p.L) {
-          *reinterpret_cast<uint2*>(d) = make_uint2(pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w));
-        } else {
-          const float e[4] = {f.x, f.y, f.z, f.w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (l + k < p.L) d[k] = f32_to_bf16(e[k]);
-        }
+        row_piece_store(dXb + (int64_t)m * p.dxsc, make_uint2(pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)), l, p.L);
       }
     }
     __syncthreads();
@@ -744,10 +744,16 @@ __global__ __launch_bounds__(GEMM_THREADS, FBP_OCC) void fbp_main_kernel(FbpArgs
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int k = s * 32 + 4 * kq + j;
-        const bool ok = k < p.Ci && c + 4 <= p.L;
-        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)k * ldb + (uint32_t)c * 2u : PF_OOB), 0, 0);
+        const bool ok = k < p.Ci && c < p.L;
+        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)k * ldb + (uint32_t)row_piece_at(c, p.L) * 2u : PF_OOB), 0, 0);
         q[s][j] = make_uint2(v.x, v.y);
       }
+    if ((p.L & 3) && l0 + 128 > p.L) {   // the sample's last slice, and its last piece is a partial one
+#pragma unroll
+      for (int s = 0; s < SUB; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[s][j] = row_piece_place(q[s][j], c, p.L);
+    }
     if (p.in.gamma) {                    // X is a stored pre-activation: the block's activated output is formed here
       for (int k = t; k < KT; k += GEMM_THREADS)
         icn[k] = k < p.Ci ? in_norm_consts(p.in, (int64_t)b * p.Ci + k) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -755,7 +761,7 @@ __global__ __launch_bounds__(GEMM_THREADS, FBP_OCC) void fbp_main_kernel(FbpArgs
 #pragma unroll
       for (int s = 0; s < SUB; ++s)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) q[s][j] = in_norm_apply4(q[s][j], icn[s * 32 + 4 * kq + j], c + 4 <= p.L, p.in.act, p.in.slope);
+        for (int j = 0; j < 4; ++j) q[s][j] = in_norm_apply4(q[s][j], icn[s * 32 + 4 * kq + j], p.L - c, p.in.act, p.in.slope);
     }
 #pragma unroll
     for (int s = 0; s < SUB; ++s) {
@@ -954,6 +960,10 @@ __global__ __launch_bounds__(128) void fbp_stats_kernel(FbpArgs p) {
 }
 
 // ---- per (model, sample, channel): first maximum over the slices, then BatchNorm + activation ------
+// Rows with L % 4 != 0: the value is normalised from z rounded to the storage type, which gives the pooled values of the chain of
+// stored operators (rounding keeps the order, so the rounded maximum is the maximum of the rounded values).
+// That chain is what such rows ran through before this operator took them; a fully connected head behind the
+// pool normalises small differences between clouds, and a value one step off there is a percent two layers on.
 __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   const int c = blockIdx.x * 256 + threadIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (c >= p.Co) return;
@@ -971,7 +981,8 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   const float bias = p.bias ? bf16_to_f32(p.bias[k]) : 0.f;
   const float scale = g * p.save_invstd[k], mean = p.save_mean[k], beta = p.beta[k];
   float z = (g < 0.f ? -best : best) + bias;
-  float pre = fmaf(scale, z - mean, beta);
+  const bool round_z = p.L & 3;
+  float pre = fmaf(scale, (round_z ? bf16_to_f32(f32_to_bf16(z)) : z) - mean, beta);
   // Equal activated values: the maximum is taken over act(BatchNorm(z)), so where the activation
   // is flat (ReLU, or LeakyReLU with slope 0, at a maximum that is not positive) or the channel's
   // scale is zero, every point of the row holds the same value and the lowest index, 0, is the
@@ -988,7 +999,7 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
     }
     at = 0;
     z = acc + bias;
-    pre = fmaf(scale, z - mean, beta);
+    pre = fmaf(scale, (round_z ? bf16_to_f32(f32_to_bf16(z)) : z) - mean, beta);
     if ((p.act == HFTA_ACT_RELU || (p.act == HFTA_ACT_LEAKY && p.slope == 0.f)) && pre > 0.f) pre = 0.f;   // the row's maximum was not positive
   }
   const float y = apply_act(pre, p.act, p.slope);
@@ -1042,7 +1053,7 @@ CbpLayout cbp_layout(int B, int Nb, int Ci, int Co, int L) {
 
 bool cbp_supported(int B, int Nb, int Ci, int Co, int L, int dtype) {
   return dtype == HFTA_BF16 && B > 0 && Nb > 0 && Ci > 0 && Co > 0 && L > 0 && Ci <= 128 && Ci % 8 == 0 && Co <= 1024 &&
-         L % 4 == 0 && L < (1 << 21) && Nb <= 65535 && B <= 65535 && (int64_t)B * Nb <= 65535;
+         L >= 4 && L < (1 << 21) && Nb <= 65535 && B <= 65535 && (int64_t)B * Nb <= 65535;
 }
 
 }  // namespace
@@ -1050,7 +1061,7 @@ bool cbp_supported(int B, int Nb, int Ci, int Co, int L, int dtype) {
 extern "C" {
 
 size_t hfta_conv1x1_bn_maxpool_bwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype) {
-  if (!cbp_supported(B, Nb, Ci, Co, L, dtype)) return 0;
+  if (!cbp_supported(B, Nb, Ci, Co, L, dtype) || L % 4 != 0) return 0;
   return cbp_layout(B, Nb, Ci, Co, L).total;
 }
 
@@ -1067,7 +1078,7 @@ static int cbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
   if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || act == HFTA_ACT_LEAKY)) return HFTA_EUNSUPPORTED;
   if (!cbp_supported(B, Nb, Ci, Co, L, dtype) || xs[3] != 1 || (Z && zs[3] != 1) || dxs[3] != 1) return HFTA_EUNSUPPORTED;
   auto al = [](const void* q, size_t a) { return (reinterpret_cast<uintptr_t>(q) % a) == 0; };
-  if (!al(X, 8) || xs[0] % 4 || xs[1] % 4 || xs[2] % 4 || xs[2] <= 0 || !al(W, 4)) return HFTA_EUNSUPPORTED;
+  if (xs[2] < L || dxs[2] < L || !al(W, 4)) return HFTA_EUNSUPPORTED;   // rows must not overlap
   const int64_t x_ext = ((int64_t)(Ci - 1) * xs[2] + L) * 2;
   if (x_ext >= (int64_t)1 << 31) return HFTA_EUNSUPPORTED;
   const CbpLayout lay = cbp_layout(B, Nb, Ci, Co, L);
@@ -1089,7 +1100,6 @@ static int cbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
   a.s = (float*)(ws + lay.s); a.XX = (float*)(ws + lay.XX); a.SX = (float*)(ws + lay.SX);
   a.negG = (bf16_raw*)(ws + lay.negG); a.v = (float*)(ws + lay.v); a.xg = (bf16_raw*)(ws + lay.xg); a.SXpart = (float*)(ws + lay.SXpart);
   a.skey = (uint32_t*)(ws + lay.skey); a.sval = (float*)(ws + lay.sval); a.toff = (int*)(ws + lay.toff);
-  a.c_vec = (al(dX, 8) && dxs[0] % 4 == 0 && dxs[1] % 4 == 0 && dxs[2] % 4 == 0) ? 8 : 0;
   a.x_extent = (uint32_t)x_ext; a.g_extent = (uint32_t)((int64_t)Ci * Ci * 2);
 
   if (saved_moments) {           // XX, SX and T = W XX as the forward operator left them
@@ -1127,8 +1137,14 @@ size_t hfta_conv1x1_bn_maxpool_saved_floats(int B, int Ci, int Co) {
 }
 
 size_t hfta_conv1x1_bn_maxpool_fwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype) {
-  if (!cbp_supported(B, Nb, Ci, Co, L, dtype)) return 0;
+  if (!cbp_supported(B, Nb, Ci, Co, L, dtype) || L % 4 != 0) return 0;
   return fbp_layout(B, Nb, Ci, Co, L, true).total;
+}
+
+size_t hfta_conv1x1_bn_maxpool_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype) {
+  if (!cbp_supported(B, Nb, Ci, Co, L, dtype)) return 0;
+  const size_t f = fbp_layout(B, Nb, Ci, Co, L, true).total, g = cbp_layout(B, Nb, Ci, Co, L).total;
+  return f > g ? f : g;
 }
 
 static int fbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* X, const int64_t xs[4],
@@ -1145,7 +1161,7 @@ static int fbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
   if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || (act == HFTA_ACT_LEAKY && act_slope >= 0.f))) return HFTA_EUNSUPPORTED;
   if (!cbp_supported(B, Nb, Ci, Co, L, dtype) || xs[3] != 1) return HFTA_EUNSUPPORTED;
   auto al = [](const void* q, size_t a) { return (reinterpret_cast<uintptr_t>(q) % a) == 0; };
-  if (!al(X, 8) || xs[0] % 4 || xs[1] % 4 || xs[2] % 4 || xs[2] <= 0 || !al(W, 16)) return HFTA_EUNSUPPORTED;
+  if (xs[2] < L || !al(W, 16)) return HFTA_EUNSUPPORTED;   // rows must not overlap
   const int64_t x_ext = ((int64_t)(Ci - 1) * xs[2] + L) * 2, w_ext = (int64_t)Co * Ci * 2;
   if (x_ext >= (int64_t)1 << 31 || w_ext >= (int64_t)1 << 31) return HFTA_EUNSUPPORTED;
   const int64_t xa_ext = Xact ? ((int64_t)(Ci - 1) * xas[2] + L) * 2 : 0;

@@ -345,10 +345,11 @@ __device__ __forceinline__ void store_rows(const unsigned char* lds, OutT* Cb, i
     for (int it = 0; it < RP / RPI; ++it) {
       const int m = mbase + r0 + it * RPI;
       typedef typename std::conditional<VB == 16, uint4, uint2>::type V;
+      typedef uint32_t DV __attribute__((ext_vector_type(VB / 4), aligned(ES)));   // rows of any alignment
       const V v = *reinterpret_cast<const V*>(src + it * RPI * PITCH);
       OutT* d = dst + (int64_t)it * RPI * c_ld;
       if (INTERIOR || (m < M && n + EPV <= N)) {
-        *reinterpret_cast<V*>(d) = v;
+        *reinterpret_cast<DV*>(d) = *reinterpret_cast<const DV*>(&v);
       } else if (m < M && n < N) {
         const OutT* e = reinterpret_cast<const OutT*>(&v);
 #pragma unroll

@@ -10,7 +10,7 @@
 // Rows / columns beyond the matrix, k beyond K and k-tiles beyond the end of the loop are all
 // expressed that way, so the steady-state loop issues PF-1 tiles ahead with no branches.
 //
-// Eligibility (checked by the host): bf16 operands, every 8-byte (16-byte when V16) piece of an
+// Eligibility (checked by the host; ANY lifts all but the last): bf16 operands, every 8-byte (16-byte when V16) piece of an
 // operand either wholly inside or wholly outside the matrix, each operand slice below 2 GiB.
 #pragma once
 #include "gemm.h"
@@ -62,7 +62,7 @@ template <bool V16> struct PfOperand<true, V16> {   // k-contiguous: rows t/4 an
       }
     }
   }
-  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t) { store_kc(tile, q, t); }
+  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t, int = 0, int = 0) { store_kc(tile, q, t); }
 };
 
 // m/n-contiguous operand: kept in its natural layout in LDS ([32 k][128 n], 320-byte rows = the k-major
@@ -97,13 +97,94 @@ template <bool N16> struct PfOperandNt {
       }
     }
   }
-  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t) {
+  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t, int = 0, int = 0) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       *reinterpret_cast<uint4*>(tile + ((t >> 4) + 16 * h) * PF_NPITCH + (t & 15) * 16) = q[h];
   }
 };
 template <bool V16> struct PfOperand<false, V16> : PfOperandNt<V16> {};   // for this operand kind V16 means N16
+
+// Rows of any length and alignment (a point cloud with an odd number of points, a vocabulary of odd size): the
+// same tiles from 8-byte pieces at element alignment.  The piece that straddles the end of the contiguous
+// dimension is read from where its last four elements start and moved into place on its way into LDS, what
+// lies past the end being zero; only the last k-tile (k-contiguous) or the last column tile (m/n-contiguous)
+// has such a piece.  Needs at least four elements along the contiguous dimension.
+__device__ __forceinline__ uint2 pf_place(uint2 q, int sh) {
+  const uint64_t w = ((uint64_t)q.y << 32 | q.x) >> (16 * sh);
+  return make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+}
+__device__ __forceinline__ int pf_shift(int i, int n) { return i < n ? i - min(i, n - 4) : 0; }
+template <bool KC> struct PfOperandAny;
+template <> struct PfOperandAny<true> {
+  typedef uint4 Regs[2];
+  uint32_t off[2];
+  int kg;
+  __device__ __forceinline__ void init(int row0, int rows, int64_t ld, int t) {
+    kg = (t & 3) * 8;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = row0 + (t >> 2) + 64 * h;
+      off[h] = r < rows ? (uint32_t)((int64_t)r * ld * 2) : PF_OOB;
+    }
+  }
+  __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
+    const int k = k0 + kg;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const pf_u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(k < K ? off[h] + (uint32_t)min(k, K - 4) * 2u : PF_OOB), 0, 0);
+      const pf_u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(k + 4 < K ? off[h] + (uint32_t)min(k + 4, K - 4) * 2u : PF_OOB), 0, 0);
+      q[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+  }
+  __device__ __forceinline__ void store(unsigned char* tile, Regs& q, int t, int k0, int K) const {
+    if (k0 + GemmT<bf16_raw>::BK > K) {
+      const int s0 = pf_shift(k0 + kg, K), s1 = pf_shift(k0 + kg + 4, K);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint2 lo = pf_place(make_uint2(q[h].x, q[h].y), s0), hi = pf_place(make_uint2(q[h].z, q[h].w), s1);
+        q[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+    }
+    store_kc(tile, q, t);
+  }
+};
+template <> struct PfOperandAny<false> {
+  typedef uint4 Regs[2];
+  uint32_t off0, off1, ldb;
+  int s0, s1;
+  bool tail;
+  __device__ __forceinline__ void init(int col0, int cols, int64_t ld, int t) {
+    ldb = (uint32_t)(ld * 2);
+    const int c = col0 + (t & 15) * 8, kr = t >> 4;
+    off0 = c < cols ? (uint32_t)kr * ldb + (uint32_t)min(c, cols - 4) * 2u : PF_OOB;
+    off1 = c + 4 < cols ? (uint32_t)kr * ldb + (uint32_t)min(c + 4, cols - 4) * 2u : PF_OOB;
+    s0 = pf_shift(c, cols);
+    s1 = pf_shift(c + 4, cols);
+    tail = col0 + 128 > cols;
+  }
+  __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
+    const int kr = (int)(threadIdx.x >> 4);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bool ok = k0 + kr + 16 * h < K;
+      const uint32_t kb = (uint32_t)(k0 + 16 * h) * ldb;
+      const pf_u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(ok && off0 != PF_OOB ? off0 + kb : PF_OOB), 0, 0);
+      const pf_u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(ok && off1 != PF_OOB ? off1 + kb : PF_OOB), 0, 0);
+      q[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+  }
+  __device__ __forceinline__ void store(unsigned char* tile, Regs& q, int t, int, int) const {
+    if (tail) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint2 lo = pf_place(make_uint2(q[h].x, q[h].y), s0), hi = pf_place(make_uint2(q[h].z, q[h].w), s1);
+        q[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+    }
+    PfOperandNt<true>::store(tile, q, t);
+  }
+};
 
 // Fragment for the 32 rows (columns of a natural-layout tile) from `base`, k-step s of the 32-deep tile:
 // lane l holds row base + l%32 and k = 16s + 8(l/32) + 0..7.  Transpose read: in every group of 16
@@ -143,7 +224,7 @@ __device__ __forceinline__ void pf_mma_tile(f32x16_t (&acc)[2][2], const unsigne
   }
 }
 
-template <bool A_KC, bool B_KC, typename OutT, bool V16, int PF, bool N16 = false>
+template <bool A_KC, bool B_KC, typename OutT, bool V16, int PF, bool N16 = false, bool ANY = false>
 // three workgroups per compute unit: the register budget this asks for (<= 168) makes the compiler keep
 // the accumulators in ordinary registers (120-137 in all), 40 KB of LDS each; four spill
 __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_pf_kernel(GemmArgs p) {
@@ -182,12 +263,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_pf_kernel(GemmArgs p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  PfOperand<A_KC, A_KC ? V16 : N16> oa;
-  PfOperand<B_KC, B_KC ? V16 : N16> ob;
+  typedef typename std::conditional<ANY, PfOperandAny<A_KC>, PfOperand<A_KC, A_KC ? V16 : N16>>::type OpA;
+  typedef typename std::conditional<ANY, PfOperandAny<B_KC>, PfOperand<B_KC, B_KC ? V16 : N16>>::type OpB;
+  OpA oa;
+  OpB ob;
   oa.init(m0, p.M, p.a_ld, t);
   ob.init(n0, p.N, p.b_ld, t);
-  typename PfOperand<A_KC, A_KC ? V16 : N16>::Regs ra[PF];
-  typename PfOperand<B_KC, B_KC ? V16 : N16>::Regs rb[PF];
+  typename OpA::Regs ra[PF];
+  typename OpB::Regs rb[PF];
+  auto k_of = [&](int tt) { return ANY ? (tt % p.tiles_per_seg) * BK : 0; };   // only a straddling piece needs it
 
   auto issue = [&](int set, int tt) {
     const bool live = tt < t_end;
@@ -202,8 +286,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_pf_kernel(GemmArgs p) {
   if (t_begin < t_end) {
 #pragma unroll
     for (int d = 0; d < PF; ++d) issue(d, t_begin + d);
-    oa.store(smem[0][0], ra[0], t);
-    ob.store(smem[0][1], rb[0], t);
+    oa.store(smem[0][0], ra[0], t, k_of(t_begin), p.K);
+    ob.store(smem[0][1], rb[0], t, k_of(t_begin), p.K);
     __syncthreads();
     int buf = 0;
     bool done = false;
@@ -214,8 +298,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_pf_kernel(GemmArgs p) {
         issue(d, cur + PF);                // set d is free again; beyond the end: zeros, no traffic
         pf_mma_tile<A_KC, B_KC>(acc, smem[buf][0], smem[buf][1], wm, wn, lane);
         if (cur + 1 >= t_end) { done = true; break; }
-        oa.store(smem[buf ^ 1][0], ra[(d + 1) % PF], t);
-        ob.store(smem[buf ^ 1][1], rb[(d + 1) % PF], t);
+        oa.store(smem[buf ^ 1][0], ra[(d + 1) % PF], t, k_of(cur + 1), p.K);
+        ob.store(smem[buf ^ 1][1], rb[(d + 1) % PF], t, k_of(cur + 1), p.K);
         __syncthreads();
         buf ^= 1;
       }
@@ -236,5 +320,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_pf_kernel(GemmArgs p) {
 }
 
 int gemm_pf_launch(const GemmDesc& d, const GemmArgs& a, bool v16, bool n16, dim3 grid, hipStream_t st);
+int gemm_any_launch(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st);   // operands of any alignment
 
 }  // namespace hfta

@@ -31,4 +31,20 @@ int gemm_pf_launch(const GemmDesc& d, const GemmArgs& a, bool v16, bool n16, dim
   return launch_status();
 }
 
+template <bool A_KC, bool B_KC>
+static void launch_any(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st) {
+  if (d.out_f32 || d.splits > 1)
+    hipLaunchKernelGGL((gemm_pf_kernel<A_KC, B_KC, float, false, PF_DEPTH, false, true>), grid, dim3(GEMM_THREADS), 0, st, a);
+  else
+    hipLaunchKernelGGL((gemm_pf_kernel<A_KC, B_KC, bf16_raw, false, PF_DEPTH, false, true>), grid, dim3(GEMM_THREADS), 0, st, a);
+}
+
+int gemm_any_launch(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st) {
+  if (d.a_kc && !d.b_kc) launch_any<true, false>(d, a, grid, st);
+  else if (d.a_kc && d.b_kc) launch_any<true, true>(d, a, grid, st);
+  else if (!d.a_kc && !d.b_kc) launch_any<false, false>(d, a, grid, st);
+  else return HFTA_EUNSUPPORTED;
+  return launch_status();
+}
+
 }  // namespace hfta

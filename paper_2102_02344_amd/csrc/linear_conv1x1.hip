@@ -2,6 +2,7 @@
 // forward / data-gradient / weight-gradient forms onto the batched GEMM core,
 // plus the bias-gradient reductions.
 #include "gemm.h"
+#include "in_norm.h"
 #include <mutex>
 
 namespace hfta {
@@ -54,14 +55,15 @@ __global__ __launch_bounds__(256) void conv1x1_tinyk_kernel(TinyKArgs p) {
     bl[o] = p.bias ? bf16_to_f32(p.bias[(int64_t)b * p.Co + o]) : 0.f;
   }
   __syncthreads();
-  const int l = (blockIdx.x * 256 + threadIdx.x) * 4;
+  int l = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (l >= p.L) return;
+  l = row_piece_at(l, p.L);                              // a row's last, partial piece: its last four points (some twice, same values)
   const bf16_raw* x = p.X + b * p.xsb + n * p.xsn + l;
   float xv[4][4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     uint2 raw = make_uint2(0u, 0u);
-    if (c < p.Ci) raw = *reinterpret_cast<const uint2*>(x + c * p.xsc);
+    if (c < p.Ci) { const row_piece_t v = *reinterpret_cast<const row_piece_t*>(x + c * p.xsc); raw = make_uint2(v[0], v[1]); }
     xv[c][0] = __uint_as_float(raw.x << 16); xv[c][1] = __uint_as_float(raw.x & 0xffff0000u);
     xv[c][2] = __uint_as_float(raw.y << 16); xv[c][3] = __uint_as_float(raw.y & 0xffff0000u);
   }
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(256) void conv1x1_tinyk_kernel(TinyKArgs p) {
     const float bo = bl[o];
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] = apply_act(acc[e] + bo, p.act, p.slope);
-    *reinterpret_cast<uint2*>(y + o * p.ysc) = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
+    *reinterpret_cast<row_piece_t*>(y + o * p.ysc) = row_piece_t{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])};
   }
 }
 
@@ -418,13 +420,10 @@ static int conv1x1_fwd_impl(int B, int Nb, int Ci, int Co, int L, int dtype, con
   if (rc != HFTA_OK) return rc;
   if (!X || !W || !Y || !xs || !ys || !valid_act(act)) return HFTA_EINVAL;
   if (xs[3] != 1 || ys[3] != 1) return HFTA_EUNSUPPORTED;
-  auto al8 = [](const void* q, const int64_t* st) {
-    return reinterpret_cast<uintptr_t>(q) % 8 == 0 && st[0] % 4 == 0 && st[1] % 4 == 0 && st[2] % 4 == 0;
-  };
-  if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && L % 4 == 0 && al8(X, xs) && al8(Y, ys) && Nb <= 65535 && B <= 65535) {
+  if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && (L % 4 == 0 || (stat_part && L >= 4)) && Nb <= 65535 && B <= 65535) {
     TinyKArgs a{(const bf16_raw*)X, (const bf16_raw*)W, (const bf16_raw*)bias, (bf16_raw*)Y, xs[0], xs[1], xs[2],
                 ys[0], ys[1], ys[2], Ci, Co, L, act, act_slope};
-    dim3 grid((unsigned)((L / 4 + 255) / 256), (unsigned)Nb, (unsigned)B);
+    dim3 grid((unsigned)(((L + 3) / 4 + 255) / 256), (unsigned)Nb, (unsigned)B);
     hipLaunchKernelGGL(conv1x1_tinyk_kernel, grid, dim3(256), 0, as_stream(stream), a);
     return launch_status();
   }
@@ -523,7 +522,7 @@ int hfta_conv1x1_bn_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, const v
 // ---- the same pair of calls with the input given as the previous block's stored pre-activation ----
 int hfta_conv1x1_bn_prenorm_supported(int B, int Nb, int Ci, int Co, int L, int dtype) {
   return check_conv1x1(B, Nb, Ci, Co, L, dtype) == HFTA_OK && dtype == HFTA_BF16 && Ci % 8 == 0 && Ci <= 128 && Co >= 64 &&
-                 Co <= 128 && L % 4 == 0 && hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype)
+                 Co <= 128 && hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype)
              ? 1 : 0;
 }
 
@@ -562,7 +561,7 @@ int hfta_conv1x1_bn_prenorm_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,
 // The data gradient of a narrow layer (Co <= 128, or Co <= 256 under at least 512 inputs) is a k=1 convolution of dY with the transposed
 // weights: it takes the streaming forward kernel once W^T [B][Ci][Co] has been written to the workspace.
 static bool dx_streams(int Ci, int Co, int L, int dtype) {
-  return dtype == HFTA_BF16 && Co % 8 == 0 && L % 4 == 0 && ((Co <= 128 && Ci >= 64) || (Co <= 256 && Ci >= 512));
+  return dtype == HFTA_BF16 && Co % 8 == 0 && L >= 4 && ((Co <= 128 && Ci >= 64) || (Co <= 256 && Ci >= 512));
 }
 static size_t wt_offset(size_t partial_bytes) { return (partial_bytes + 255) & ~(size_t)255; }
 
@@ -641,13 +640,20 @@ static size_t cbb_fallback_dz_bytes(int B, int Nb, int Co, int L, int dtype) {
 }
 
 int hfta_conv1x1_bn_bwd_one_pass(int B, int Nb, int Ci, int Co, int L, int dtype) {
-  return check_conv1x1(B, Nb, Ci, Co, L, dtype) == HFTA_OK && hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype) ? 1 : 0;
+  return check_conv1x1(B, Nb, Ci, Co, L, dtype) == HFTA_OK && L % 4 == 0 && hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype) ? 1 : 0;
+}
+
+size_t hfta_conv1x1_bn_bwd_stream_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype) {
+  if (check_conv1x1(B, Nb, Ci, Co, L, dtype) != HFTA_OK || !hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype)) return 0;
+  return hfta::conv1x1_bn_bwd_stream_bytes(B, Nb, Ci, Co, L);
 }
 
 size_t hfta_conv1x1_bn_bwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype) {
   if (check_conv1x1(B, Nb, Ci, Co, L, dtype) != HFTA_OK) return 0;
-  if (hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype)) return hfta::conv1x1_bn_bwd_stream_bytes(B, Nb, Ci, Co, L);
-  return cbb_fallback_dz_bytes(B, Nb, Co, L, dtype) + hfta_conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, dtype);
+  if (L % 4 == 0 && hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype)) return hfta::conv1x1_bn_bwd_stream_bytes(B, Nb, Ci, Co, L);
+  const size_t two = cbb_fallback_dz_bytes(B, Nb, Co, L, dtype) + hfta_conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, dtype);
+  const size_t one = hfta_conv1x1_bn_bwd_stream_workspace_bytes(B, Nb, Ci, Co, L, dtype);
+  return one > two ? one : two;
 }
 
 int hfta_conv1x1_bn_bwd(int B, int Nb, int Ci, int Co, int L, int dtype, const void* X, const int64_t xs[4],
@@ -663,7 +669,8 @@ int hfta_conv1x1_bn_bwd(int B, int Nb, int Ci, int Co, int L, int dtype, const v
   if (act != HFTA_ACT_NONE && act != HFTA_ACT_RELU && act != HFTA_ACT_LEAKY) return HFTA_EUNSUPPORTED;
   if (xs[3] != 1 || zs[3] != 1 || dys[3] != 1 || (dX && dxs[3] != 1)) return HFTA_EUNSUPPORTED;
   hipStream_t st = as_stream(stream);
-  if (hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype)) {
+  if (hfta::conv1x1_bn_bwd_streams(B, Ci, Co, L, dtype) &&
+      (L % 4 == 0 || (workspace && ws_bytes >= hfta::conv1x1_bn_bwd_stream_bytes(B, Nb, Ci, Co, L)))) {
     if (!workspace || ws_bytes < hfta::conv1x1_bn_bwd_stream_bytes(B, Nb, Ci, Co, L)) return HFTA_EWORKSPACE;
     rc = hfta::conv1x1_bn_bwd_stream(B, Nb, Ci, Co, L, X, xs, W, Z, zs, dY, dys, gamma, beta, save_mean, save_invstd,
                                      dX, dxs, dW, dbias, dgamma, dbeta, act, act_slope, workspace, st, nullptr, nullptr, nullptr,

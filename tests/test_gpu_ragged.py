@@ -1,0 +1,147 @@
+"""Rows of any length and alignment: the operator tests of the point-wise layers at row lengths that are
+no multiple of four points (the partial last piece one, two and three points long; just past a 128-point
+slice; a row shorter than one slice; the shortest row a piece fits), against the same oracle chains at
+the same tolerances.  L = 2501: several slices, every row start at another alignment."""
+import numpy as np
+import pytest
+import torch
+
+import hfta_inputs as hi
+import test_gpu_ops as ops
+import test_gpu_pointnet as pn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2102_02344_amd import binding
+    return binding
+
+
+class AnyLength:
+    """The binding with the workspace queries that answer for every row length."""
+
+    def __init__(self, hb):
+        self._hb = hb
+
+    def __getattr__(self, name):
+        if name in ("conv1x1_bn_maxpool_fwd_workspace_bytes", "conv1x1_bn_maxpool_bwd_workspace_bytes"):
+            name = "conv1x1_bn_maxpool_workspace_bytes"
+        return getattr(self._hb, name)
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L,act", [(2, 3, 64, 64, 2501, 1), (2, 2, 64, 128, 129, 2), (2, 2, 128, 128, 131, 1),
+                                              (2, 2, 3, 64, 130, 1), (2, 3, 24, 72, 7, 1), (2, 2, 8, 64, 5, 0), (2, 2, 3, 64, 4, 1)])
+def test_conv1x1_bn_forward_and_backward(hb, B, Nb, Ci, Co, L, act):
+    ops.test_conv1x1_bn_fwd(hb, "bf16", B, Nb, Ci, Co, L, act, True)
+    ops.test_conv1x1_bn_bwd(hb, "bf16", B, Nb, Ci, Co, L, act, True)
+    ops.test_conv1x1_bn_bwd(hb, "bf16", B, Nb, Ci, Co, L, act, False)
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L,act", [(2, 3, 64, 64, 2501, 1), (2, 2, 64, 128, 130, 1), (2, 2, 128, 128, 131, 2),
+                                              (2, 2, 40, 64, 127, 1)])
+def test_conv1x1_bn_prenorm(hb, B, Nb, Ci, Co, L, act):
+    ops.test_conv1x1_bn_prenorm(hb, B, Nb, Ci, Co, L, 1, act, True)
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L,act", [(2, 3, 128, 136, 261, 1), (2, 2, 64, 72, 131, 2), (2, 2, 16, 40, 130, 1),
+                                              (1, 2, 8, 1024, 7, 0)])
+def test_one_operator_tail(hb, B, Nb, Ci, Co, L, act):
+    ops.test_conv1x1_bn_maxpool_bwd_fused(AnyLength(hb), B, Nb, Ci, Co, L, act)
+    ops.test_conv1x1_bn_maxpool_fwd_bwd_one_operator(AnyLength(hb), B, Nb, Ci, Co, L, act)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Nb,C,L", [(3, 5, 1023), (2, 3, 9001), (4, 3, 6), (3, 4, 5), (2, 3, 3)])
+def test_batchnorm_rows(hb, dtype, Nb, C, L):
+    """Forward, backward, evaluation, and the pair with the max over points, on rows that are element-aligned
+    only, against float64 formulas at the storage tolerance (fp32: 2e-5 .. 3e-5 for the three rounded
+    factors of an output; sums against the magnitude of the summed terms)."""
+    B = 2
+    tdt = ops.TDT[dtype]
+    x = hi.snap(hi.normal(401, (Nb, B * C, L)) * 1.7 + 0.6, dtype)
+    dy = hi.normal(402, (Nb, B * C, L), dtype)
+    g = (hi.normal(403, (B * C,)) * 0.4 + 1.0).astype(np.float32)
+    bt = (hi.normal(404, (B * C,)) * 0.3).astype(np.float32)
+    # one element in front of the tensor: no row starts on a piece boundary by luck
+    def put(a):
+        buf = torch.zeros(a.size + 1, dtype=tdt, device="cuda")
+        buf[1:] = torch.from_numpy(a.reshape(-1)).to(tdt).cuda()
+        return buf[1:]
+    X, dY = put(x), put(dy)
+    Y, dX = put(np.zeros_like(x)), put(np.zeros_like(x))
+    G, Bt = ops.dev(g), ops.dev(bt)
+    st = ops.conv_strides(B, C, L)
+    SM, SI, dG, dB, S = (torch.empty(B * C, device="cuda") for _ in range(5))
+    hb.bn_fwd(B, Nb, C, L, ops.DT[dtype], X, st, G, Bt, 1e-5, 0.1, None, None, SM, SI, Y, st, hb.ACT_LEAKY, 0.2)
+    x64 = x.astype(np.float64)
+    mean, var = x64.mean(axis=(0, 2)), x64.var(axis=(0, 2))
+    inv = 1.0 / np.sqrt(var + 1e-5)
+    xh = (x64 - mean[None, :, None]) * inv[None, :, None]
+    pre = g[None, :, None] * xh + bt[None, :, None]
+    ry = np.where(pre > 0, pre, 0.2 * pre)
+    tol = ops.TOL[dtype]
+    ops.check(SM.cpu().numpy(), mean, 1e-5, "mean")
+    ops.check(SI.cpu().numpy(), inv, 1e-5, "invstd")
+    ops.check(Y.float().cpu().numpy().reshape(x.shape), ry, max(tol, 2e-5), "Y")
+    # backward: elements whose pre-activation is within fp32 rounding of the kink may take either branch
+    safe = np.abs(pre) > 1e-5
+    dyz = np.where(safe, dy, 0.0)
+    dY.copy_(torch.from_numpy(dyz.reshape(-1)).to(tdt).cuda())
+    hb.bn_bwd(B, Nb, C, L, ops.DT[dtype], X, st, dY, st, G, Bt, SM, SI, dX, st, dG, dB, hb.ACT_LEAKY, 0.2, S)
+    gr = dyz * np.where(pre > 0, 1.0, 0.2)
+    m = Nb * L
+    s1, s2 = gr.sum(axis=(0, 2)), (gr * xh).sum(axis=(0, 2))
+    rdx = (g * inv)[None, :, None] * (gr - s1[None, :, None] / m - xh * s2[None, :, None] / m)
+    mag = np.abs(gr).sum(axis=(0, 2)).max()
+    assert np.abs(dB.cpu().numpy() - s1).max() <= 2e-5 * mag and np.abs(dG.cpu().numpy() - s2).max() <= 1e-4 * mag
+    ops.check(dX.float().cpu().numpy().reshape(x.shape), rdx, max(tol, 3e-5), "dX")
+    dxs = dX.double().cpu().numpy().reshape(x.shape)
+    assert np.abs(S.cpu().numpy() - dxs.sum(axis=(0, 2))).max() <= 1e-5 * np.abs(dxs).sum(axis=(0, 2)).max()
+    # evaluation in place, and what the training forward with the pool finds
+    hb.bn_eval_fwd(B, Nb, C, L, ops.DT[dtype], X, st, G, Bt, ops.dev(mean.astype(np.float32)), ops.dev(var.astype(np.float32)),
+                   1e-5, X, st, hb.ACT_LEAKY, 0.2)
+    ops.check(X.float().cpu().numpy().reshape(x.shape), ry, max(tol, 2e-5), "eval in place")
+    X = put(x)
+    V = torch.empty(B, Nb, C, dtype=tdt, device="cuda")
+    I = torch.empty(B, Nb, C, dtype=torch.int32, device="cuda")
+    vs = (Nb * C, C, 1)
+    SM2, SI2 = torch.empty_like(SM), torch.empty_like(SI)
+    hb.bn_fwd_maxpool(B, Nb, C, L, ops.DT[dtype], X, st, G, Bt, 1e-5, 0.1, None, None, SM2, SI2, V, I, vs, hb.ACT_RELU)
+    hb.bn_fwd(B, Nb, C, L, ops.DT[dtype], X, st, G, Bt, 1e-5, 0.1, None, None, SM, SI, Y, st, hb.ACT_RELU)
+    yv = Y.float().view(Nb, B, C, L)
+    assert torch.equal(V.float(), yv.amax(dim=3).permute(1, 0, 2))
+    first = (yv == yv.amax(dim=3, keepdim=True)).int().argmax(dim=3).permute(1, 0, 2)
+    assert torch.equal(I.long(), first.long())
+    dV = torch.from_numpy(hi.normal(405, (B, Nb, C), dtype)).to(tdt).cuda()
+    hb.bn_bwd_maxpool(B, Nb, C, L, ops.DT[dtype], X, st, dV, I, vs, G, Bt, SM, SI, dX, st, dG, dB, hb.ACT_RELU, 0.0, S)
+    dense = torch.zeros(Nb, B, C, L, dtype=tdt, device="cuda")
+    dense.scatter_(3, I.long().permute(1, 0, 2).unsqueeze(3), dV.permute(1, 0, 2).unsqueeze(3))
+    dX2 = torch.empty_like(dX)
+    hb.bn_bwd(B, Nb, C, L, ops.DT[dtype], X, st, dense, st, G, Bt, SM, SI, dX2, st, dG, dB, hb.ACT_RELU, 0.0, S)
+    ops.check(dX.float().cpu().numpy(), dX2.float().cpu().numpy(), tol, "dX through the pool")
+
+
+@pytest.mark.parametrize("L", [501, 130])
+def test_classification_array(L):
+    """The assembled array on odd rows: every call of a step checked in place."""
+    from paper_2102_02344_amd.arrays import FusedPointNetCls
+    spec = hi.spec_c1(B=2, Nb=3, L=L)
+    arr = FusedPointNetCls(spec, hi.pointnet_cls_inputs(spec))
+    assert arr.fused_tail and all(arr.one_pass[:-1]) and any(arr.prenorm)
+    seen = []
+    arr.forward_backward(pn.in_place_probe(spec, seen))
+    assert seen.count("conv1x1_bn_bwd") == 4 and "conv1x1_bn_maxpool_bwd" in seen
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,M,Fx,Fy", [(2, 133, 37, 45), (3, 70, 129, 131), (2, 6, 5, 7), (2, 260, 66, 1839)])
+def test_matrix_products_linear(hb, dtype, B, M, Fx, Fy):
+    ops.test_linear_fwd_bwd(hb, dtype, B, M, Fx, Fy)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,Nb,Ci,Co,L", [(2, 2, 264, 136, 131), (2, 3, 70, 150, 257), (2, 2, 5, 12, 6), (2, 2, 130, 520, 1023)])
+def test_matrix_products_conv(hb, dtype, B, Nb, Ci, Co, L):
+    ops.test_conv1x1_fwd_bwd(hb, dtype, B, Nb, Ci, Co, L)
