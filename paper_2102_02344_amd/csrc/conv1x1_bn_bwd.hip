@@ -99,7 +99,9 @@ struct CbbCfg {
 };
 
 // (The launch bound is the register budget: 2 * CBB_THREADS threads per compute unit where two workgroups share one.)
-template <int CO, int CI, bool HAS_DX>
+// RAG: rows whose length is no multiple of four points (a straddling piece per row, see in_norm.h); kept apart
+// because its per-point checks cost the other rows 3 % (64 -> 64: 105.6 -> 109.4 us on 32 clouds of 2500 points, 8 models).
+template <int CO, int CI, bool HAS_DX, bool RAG>
 __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void cbb_kernel(CbbArgs p) {
   typedef CbbCfg<CO, CI, HAS_DX> K;
   constexpr int PT = K::PT, PN = K::PN, PS = K::PS, BPT = K::BPT, XPT = K::XPT, DEPTH = K::DEPTH;
@@ -196,7 +198,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
     const __amdgpu_buffer_rsrc_t rx = pf_rsrc(p.X + b * p.x_g0 + n * p.x_g1, p.x_extent);
     const int c = l0 + ng * 4;
     const bool cok = live && c < p.L;
-    const uint32_t cb = (uint32_t)row_piece_at(c, p.L) * 2u;
+    const uint32_t cb = (uint32_t)(RAG ? row_piece_at(c, p.L) : c) * 2u;
 #pragma unroll
     for (int i = 0; i < BPT; ++i)
 #pragma unroll
@@ -212,7 +214,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
     for (int i = 0; i < XPT; ++i) {
       const int id = t + CBB_THREADS * i, row = id >> 5, cx = l0 + (id & 31) * 4;
       const bool ok = live && row < p.Ci && cx < p.L;
-      const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)row * x_ldb + (uint32_t)row_piece_at(cx, p.L) * 2u : PF_OOB), 0, 0);
+      const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)(ok ? (uint32_t)row * x_ldb + (uint32_t)(RAG ? row_piece_at(cx, p.L) : cx) * 2u : PF_OOB), 0, 0);
       g.x[i] = make_uint2(v.x, v.y);
     }
   };
@@ -245,7 +247,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
       const bool live = u < uend;
       const int n = live ? u / p.slices : 0, l0 = live ? (u - n * p.slices) * 128 : p.slices * 128;
       const int left = p.L - (l0 + ng * 4);      // of this thread's four points, how many exist
-      if ((p.L & 3) && live && l0 + 128 > p.L) { // the sample's last slice, and its last piece is a partial one
+      if (RAG && live && l0 + 128 > p.L) { // the sample's last slice, and its last piece is a partial one
         const int c = l0 + ng * 4, cx = l0 + (t & 31) * 4;
 #pragma unroll
         for (int i = 0; i < BPT; ++i)
@@ -275,7 +277,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
             const float xh = (zz[e] - c0.x) * c0.y;
             const float gr = dd[e] * (fmaf(c0.z, xh, c0.w) > 0.f ? 1.f : act_neg);
             const float v = c1.z * (gr - c1.x - xh * c1.y);
-            dz[j][e] = e < left ? v : 0.f;        // points past the sample's end add nothing to dW and dbias
+            dz[j][e] = (RAG ? e : 0) < left ? v : 0.f;        // points past the sample's end add nothing to dW and dbias
           }
           uint2 o;
           o.x = pack_bf16x2(dz[j][0], dz[j][1]);
@@ -299,7 +301,7 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
         uint2 xv = q[d].x[i];
         if (K::SUMS && sums_on) *reinterpret_cast<uint2*>(zraw + id * 8) = xv;
         if (xin) {
-          xv = in_norm_apply4(xv, xc[id >> 5], p.L - (l0 + (id & 31) * 4), p.in_act, p.in_slope);
+          xv = in_norm_apply4<RAG>(xv, xc[id >> 5], p.L - (l0 + (id & 31) * 4), p.in_act, p.in_slope);
         }
         *reinterpret_cast<uint2*>(xN + (id >> 5) * PN + (id & 31) * 8) = xv;
       }
@@ -354,7 +356,10 @@ __global__ __launch_bounds__((CbbCfg<CO, CI, HAS_DX>::WGS * CBB_THREADS)) void c
           const int id = t + CBB_THREADS * i, row = id >> 5, c = l0 + (id & 31) * 4;
           const uint2 v = *reinterpret_cast<const uint2*>(stg + row * PS + (id & 31) * 8);
           const bool okp = row < p.Ci && c < p.L;        // (past the end dX and x are zero: nothing for the sums)
-          if (okp) row_piece_store(dXb + (int64_t)row * p.dx_ld, v, c, p.L);
+          if (okp) {
+            if (RAG) row_piece_store(dXb + (int64_t)row * p.dx_ld, v, c, p.L);
+            else *reinterpret_cast<row_piece_t*>(dXb + (int64_t)row * p.dx_ld + c) = row_piece_t{v.x, v.y};
+          }
           if (K::SUMS && sums_on) {
             const uint2 zr = *reinterpret_cast<const uint2*>(zraw + id * 8);
             const float4 ic = xc[row];       // mean, invstd, gamma, beta of the input block
@@ -527,8 +532,11 @@ int conv1x1_bn_bwd_stream(int B, int Nb, int Ci, int Co, int L, const void* X, c
   a.w_extent = (uint32_t)w_ext;
   const dim3 grid((unsigned)(B * a.G));
 #define HFTA_CBB(CO_, CI_) \
-  do { if (dX) hipLaunchKernelGGL((cbb_kernel<CO_, CI_, true>), grid, dim3(CBB_THREADS), 0, st, a); \
-       else hipLaunchKernelGGL((cbb_kernel<CO_, CI_, false>), grid, dim3(CBB_THREADS), 0, st, a); } while (0)
+  do { if (dX && rag) hipLaunchKernelGGL((cbb_kernel<CO_, CI_, true, true>), grid, dim3(CBB_THREADS), 0, st, a); \
+       else if (dX) hipLaunchKernelGGL((cbb_kernel<CO_, CI_, true, false>), grid, dim3(CBB_THREADS), 0, st, a); \
+       else if (rag) hipLaunchKernelGGL((cbb_kernel<CO_, CI_, false, true>), grid, dim3(CBB_THREADS), 0, st, a); \
+       else hipLaunchKernelGGL((cbb_kernel<CO_, CI_, false, false>), grid, dim3(CBB_THREADS), 0, st, a); } while (0)
+  const bool rag = L % 4 != 0;
   if (Co <= 64 && Ci <= 64) HFTA_CBB(64, 64);
   else if (Co <= 64) HFTA_CBB(64, 128);
   else if (Ci <= 64) HFTA_CBB(128, 64);

@@ -50,12 +50,14 @@ __device__ __forceinline__ void row_piece_store(bf16_raw* row, uint2 v, int c, i
   }
 }
 
-// left: how many of the four points exist (any larger number: all); points past the sample's end stay zero
+// left: how many of the four points exist (any larger number: all); points past the sample's end stay zero.
+// RAG == false: rows of whole pieces, all four exist or none
+template <bool RAG = true>
 __device__ __forceinline__ uint2 in_norm_apply4(uint2 q, const float4 cn, int left, int act, float slope) {
   float v[4] = {__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u), __uint_as_float(q.y << 16),
                 __uint_as_float(q.y & 0xffff0000u)};
 #pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = e < left ? in_norm_one(v[e], cn, act, slope) : 0.f;
+  for (int e = 0; e < 4; ++e) v[e] = (RAG ? e : 0) < left ? in_norm_one(v[e], cn, act, slope) : 0.f;
   return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
 }
 

@@ -37,8 +37,11 @@ namespace {
 // dbias of the fused Linear: column sums of dY[b] ([M][Fy]); 64 columns x 4 row slices per block.
 // Forward of a k=1 convolution with at most 4 input channels (the point coordinates): no matrix
 // instruction pays for K = 3.  A thread owns four consecutive points, keeps their Ci inputs in
-// registers and walks the output channels; consecutive lanes write consecutive 8-byte pieces of an
-// output row.  HBM-bound: Co rows written once.
+// registers and walks TK_CO of the output channels; consecutive lanes write consecutive 8-byte pieces of
+// an output row.  HBM-bound: Co rows written once.  The channels are split over workgroups (the inputs,
+// a twentieth of the output, are read again) because a single walk over 64 rows leaves a small batch on a
+// handful of compute units (64 channels: 8 x 32 x 2500 points 31 -> 25 us, 3 x 13 x 1023 points 26 -> 11 us).
+constexpr int TK_CO = 16;
 struct TinyKArgs {
   const bf16_raw* X; const bf16_raw* W; const bf16_raw* bias; bf16_raw* Y;
   int64_t xsb, xsn, xsc, ysb, ysn, ysc;
@@ -46,16 +49,17 @@ struct TinyKArgs {
   float slope;
 };
 __global__ __launch_bounds__(256) void conv1x1_tinyk_kernel(TinyKArgs p) {
-  __shared__ float wl[256][4];                           // Co <= 256 (host): weights of the model, then its bias
-  __shared__ float bl[256];
+  __shared__ float wl[TK_CO][4];                         // weights of this workgroup's channels, then their biases
+  __shared__ float bl[TK_CO];
   const int n = blockIdx.y, b = blockIdx.z;
-  for (int o = threadIdx.x; o < p.Co; o += 256) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) wl[o][c] = c < p.Ci ? bf16_to_f32(p.W[((int64_t)b * p.Co + o) * p.Ci + c]) : 0.f;
-    bl[o] = p.bias ? bf16_to_f32(p.bias[(int64_t)b * p.Co + o]) : 0.f;
+  const int groups = (p.Co + TK_CO - 1) / TK_CO, o0 = (blockIdx.x % groups) * TK_CO, co = min(TK_CO, p.Co - o0);
+  if (threadIdx.x < co * 4) {
+    const int o = o0 + (threadIdx.x >> 2), c = threadIdx.x & 3;
+    wl[threadIdx.x >> 2][c] = c < p.Ci ? bf16_to_f32(p.W[((int64_t)b * p.Co + o) * p.Ci + c]) : 0.f;
+    if (c == 0) bl[threadIdx.x >> 2] = p.bias ? bf16_to_f32(p.bias[(int64_t)b * p.Co + o]) : 0.f;
   }
   __syncthreads();
-  int l = (blockIdx.x * 256 + threadIdx.x) * 4;
+  int l = (blockIdx.x / groups * 256 + threadIdx.x) * 4;
   if (l >= p.L) return;
   l = row_piece_at(l, p.L);                              // a row's last, partial piece: its last four points (some twice, same values)
   const bf16_raw* x = p.X + b * p.xsb + n * p.xsn + l;
@@ -67,9 +71,9 @@ __global__ __launch_bounds__(256) void conv1x1_tinyk_kernel(TinyKArgs p) {
     xv[c][0] = __uint_as_float(raw.x << 16); xv[c][1] = __uint_as_float(raw.x & 0xffff0000u);
     xv[c][2] = __uint_as_float(raw.y << 16); xv[c][3] = __uint_as_float(raw.y & 0xffff0000u);
   }
-  bf16_raw* y = p.Y + b * p.ysb + n * p.ysn + l;
+  bf16_raw* y = p.Y + b * p.ysb + n * p.ysn + o0 * p.ysc + l;
 #pragma unroll 4
-  for (int o = 0; o < p.Co; ++o) {
+  for (int o = 0; o < co; ++o) {
     float acc[4];
     const float4 wo = *reinterpret_cast<const float4*>(wl[o]);
     const float wc[4] = {wo.x, wo.y, wo.z, wo.w};
@@ -423,7 +427,7 @@ static int conv1x1_fwd_impl(int B, int Nb, int Ci, int Co, int L, int dtype, con
   if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && (L % 4 == 0 || (stat_part && L >= 4)) && Nb <= 65535 && B <= 65535) {
     TinyKArgs a{(const bf16_raw*)X, (const bf16_raw*)W, (const bf16_raw*)bias, (bf16_raw*)Y, xs[0], xs[1], xs[2],
                 ys[0], ys[1], ys[2], Ci, Co, L, act, act_slope};
-    dim3 grid((unsigned)(((L + 3) / 4 + 255) / 256), (unsigned)Nb, (unsigned)B);
+    dim3 grid((unsigned)(((L + 3) / 4 + 255) / 256 * ((Co + TK_CO - 1) / TK_CO)), (unsigned)Nb, (unsigned)B);
     hipLaunchKernelGGL(conv1x1_tinyk_kernel, grid, dim3(256), 0, as_stream(stream), a);
     return launch_status();
   }
