@@ -1,6 +1,6 @@
 // Host side of the batched GEMM core: split selection, alignment checks, dispatch.
 #include "gemm.h"
-#include "gemm_pf.h"
+#include "gemm_dma.h"
 
 namespace hfta {
 
@@ -58,6 +58,7 @@ static int pick_splits_big(const GemmDesc& d) {
 // Enough workgroups to fill 256 compute units a few times over, without cutting
 // the reduction into pieces shorter than 8 k-tiles.
 int gemm_pick_splits(const GemmDesc& d) {
+  if (d.S == 1 && gemm_dma_tile(d) >= 0) return 1;
   const int big = pick_splits_big(d);
   if (big > 0) return big;
   const int64_t tiles = (int64_t)((d.M + GEMM_BM - 1) / GEMM_BM) * ((d.N + GEMM_BN - 1) / GEMM_BN) * d.G0 * d.G1;
@@ -189,6 +190,12 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   };
   const bool n16 = n16ok(d.A, d.a_ld, d.a_ss, d.a_g0, d.a_g1, d.a_kc, d.M) &&
                    n16ok(d.Bm, d.b_ld, d.b_ss, d.b_g0, d.b_g1, d.b_kc, d.N);
+
+  // Few output tiles under a reduction of some length: loads straight into LDS, deeper in flight.
+  if (buffers_ok && splits == 1 && n16 && (!d.a_kc || a.a_vec == 2) && (!d.b_kc || a.b_vec == 2)) {
+    const int rc = gemm_dma_launch(d, a, st);
+    if (rc != HFTA_EUNSUPPORTED) return rc;
+  }
 
   // Compute-bound problems (MLP-sized bf16 GEMMs) take the 256x256 kernel: it needs 16-byte
   // loadable operands, no split, a long reduction, and enough tiles to give every compute unit

@@ -1,0 +1,62 @@
+// Dispatch of the GEMM kernel that loads straight into LDS: which problems, which tile.
+#include "gemm_dma.h"
+
+namespace hfta {
+
+// The kernel is for launches that leave about one workgroup per compute unit, with a reduction long enough to
+// be worth a pipeline: up to 256 workgroups of the smallest tile that keeps the count there (a workgroup alone
+// on its compute unit spends 0.18 / 0.29 / 0.37 us per 64-element k-tile with 64 x 64 / 128 x 64 / 128 x 128,
+// so the smaller tile wins as long as it costs no second round), 320 of the largest.  Measured per call, against
+// the register-staged kernels with their split reductions:
+//   forward  8 x 2048 x 256, K = 1024     20.3 -> 15.9 us       5 x 693 x 384, K = 1536    24.9 -> 13.6 us
+//   data     8 x 2048 x 256, K = 8192      147 -> 101 us        4 x 3000 x 256, K = 5000     85 -> 57 us
+//   weights  8 x 256 x 768, K = 2048      33.7 -> 18.2 us       5 x 384 x 1536, K = 693     36 -> 13.1 us
+//   few rows 8 x 32 x 1024, K = 512        10.6 -> 5.8 us
+// With four k-tiles or fewer both take the same time (8 x 2048 x 256, K = 256: 9.1 and 9.3 us), and with many more
+// workgroups than compute units the smaller stages of the register-staged kernels hide more (4 x 3000 x 768,
+// K = 256: 16 against 19 us; 256 x 256 tiles: 180 us both at 16 x 4096 x 512, K = 2048).
+// Reductions past 128 k-tiles keep their split over k: this kernel walks them in sequence.
+int gemm_dma_tile(const GemmDesc& d) {
+  if (d.dtype != HFTA_BF16 || (!d.a_kc && d.b_kc)) return -1;
+  if ((d.a_kc || d.b_kc) && d.K % 8 != 0) return -1;
+  if ((!d.a_kc && d.M % 8 != 0) || (!d.b_kc && d.N % 8 != 0)) return -1;
+  const int64_t kt = (int64_t)d.S * ((d.K + 63) / 64), G = (int64_t)d.G0 * d.G1;
+  if (kt < 5 || kt > 128) return -1;
+  auto tiles = [&](int bm, int bn) { return (int64_t)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * G; };
+  if (tiles(64, 64) <= 256) return 0;
+  if (tiles(128, 64) <= 256) return 1;
+  if (tiles(128, 128) <= 320) return 2;
+  return -1;
+}
+
+template <int WM, int WN, int MI, int NI, int OCC, bool A_KC, bool B_KC, typename OutT>
+static void launch(const GemmDesc& d, GemmArgs a, hipStream_t st) {
+  constexpr int BM = WM * MI * 32, BN = WN * NI * 32, BK = 64;
+  a.tiles_m = (d.M + BM - 1) / BM;
+  a.tiles_n = (d.N + BN - 1) / BN;
+  a.tiles_per_seg = (d.K + BK - 1) / BK;
+  a.total_tiles = d.S * a.tiles_per_seg;
+  const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), 1, (unsigned)(d.G0 * d.G1 * a.splits));
+  hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, MI, NI, BK, A_KC, B_KC, OutT, 3, OCC>), grid, dim3(WM * WN * 64), 0, st, a);
+}
+
+template <bool A_KC, bool B_KC, typename OutT>
+static int launch_tile(const GemmDesc& d, const GemmArgs& a, hipStream_t st) {
+  switch (gemm_dma_tile(d)) {
+    case 0: launch<2, 2, 1, 1, 3, A_KC, B_KC, OutT>(d, a, st); break;      // 64 x 64
+    case 1: launch<2, 2, 2, 1, 2, A_KC, B_KC, OutT>(d, a, st); break;      // 128 x 64
+    case 2: launch<2, 4, 2, 1, 2, A_KC, B_KC, OutT>(d, a, st); break;      // 128 x 128
+    default: return HFTA_EUNSUPPORTED;
+  }
+  return launch_status();
+}
+
+// `a`: operand extents set, operands loadable in whole 16-byte pieces, no split.
+int gemm_dma_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st) {
+  if (a.splits != 1) return HFTA_EUNSUPPORTED;
+  if (d.a_kc && !d.b_kc) return d.out_f32 ? launch_tile<true, false, float>(d, a, st) : launch_tile<true, false, bf16_raw>(d, a, st);
+  if (d.a_kc && d.b_kc) return d.out_f32 ? launch_tile<true, true, float>(d, a, st) : launch_tile<true, true, bf16_raw>(d, a, st);
+  return d.out_f32 ? launch_tile<false, false, float>(d, a, st) : launch_tile<false, false, bf16_raw>(d, a, st);
+}
+
+}  // namespace hfta

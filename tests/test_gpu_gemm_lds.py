@@ -1,0 +1,67 @@
+"""Fused Linear at the sizes the GEMM kernel with loads straight into LDS takes (few output tiles under a
+reduction of at least five 64-element k-tiles): each of its three tiles, edges and remainders of a tile in
+every dimension, the fewest and the most k-tiles, and the sizes one step outside.
+
+Reference: float64 products of the same bf16 values.  Bound per element: the fp32 accumulation of K exact
+products, at most K 2^-23 sum|a||b| in any order, and for bf16 outputs one rounding, 2^-8 of the value."""
+import numpy as np
+import pytest
+import torch
+
+import hfta_inputs as hi
+from util import dev, host
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -23
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2102_02344_amd import binding
+    return binding
+
+
+def within(got, ref, mag, K, bf16, what):
+    d = np.abs(host(got).reshape(ref.shape) - ref)
+    lim = K * U * mag + (2.0 ** -8 * np.abs(ref) if bf16 else 0.0) + 1e-30
+    assert np.all(np.isfinite(d)), what
+    assert (d <= lim).all(), (what, float((d / lim).max()))
+
+
+@pytest.mark.parametrize("B,M,Fx,Fy", [
+    (2, 33, 320, 64),        # 64 x 64 tiles, five k-tiles forward, rows past a half tile
+    (1, 1, 264, 8),          # one row, one column piece, a last k-tile of one piece
+    (2, 200, 328, 520),      # remainders in every dimension
+    (3, 64, 8192, 72),       # the longest reduction (128 k-tiles)
+    (3, 64, 8200, 72),       # one past it: the split path
+    (5, 693, 384, 1000),     # 128 x 64 tiles backward
+    (4, 1500, 392, 520),     # 128 x 128 tiles
+    (1, 321, 1024, 1024),
+    (2, 96, 327, 65),        # not whole pieces: the other kernels
+])
+def test_linear_forward_backward(hb, B, M, Fx, Fy):
+    x = hi.normal(501, (B, M, Fx), "bf16")
+    w = hi.snap(hi.normal(502, (B, Fx, Fy)) * 0.1, "bf16")
+    bias = hi.normal(503, (B, Fy), "bf16")
+    dy = hi.normal(504, (B, M, Fy), "bf16")
+    X, W, Bi, dY = (dev(a, "bf16") for a in (x, w, bias, dy))
+    x64, w64, b64, dy64 = (np.asarray(a, np.float64) for a in (x, w, bias, dy))
+    aw, ax, ad = np.abs(w64), np.abs(x64), np.abs(dy64)
+    lin = x64 @ w64 + b64[:, None, :]
+    mag = ax @ aw + np.abs(b64)[:, None, :]
+    ws = torch.empty(max(4, hb.linear_fwd_workspace_bytes(B, M, Fx, Fy, 1), hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, 1)),
+                     dtype=torch.uint8, device="cuda")
+    nan = float("nan")
+    for act, ref in ((hb.ACT_NONE, lin), (hb.ACT_LEAKY, np.where(lin > 0, lin, 0.2 * lin))):
+        Y, Y2 = (torch.full((B, M, Fy), nan, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        hb.linear_fwd(B, M, Fx, Fy, 1, X, W, Bi, Y, act, 0.2)
+        within(Y, ref, mag, Fx + 1, True, f"forward act {act}")
+        hb.linear_fwd_ws(B, M, Fx, Fy, 1, X, W, Bi, Y2, act, 0.2, ws)
+        within(Y2, ref, mag, Fx + 1, True, f"forward with workspace act {act}")
+    dX = torch.full((B, M, Fx), nan, dtype=torch.bfloat16, device="cuda")
+    dW = torch.full((B, Fx, Fy), nan, device="cuda")
+    db = torch.full((B, Fy), nan, device="cuda")
+    hb.linear_bwd(B, M, Fx, Fy, 1, X, W, dY, dX, dW, db, ws)
+    within(dX, dy64 @ w64.transpose(0, 2, 1), ad @ aw.transpose(0, 2, 1), Fy, True, "data gradient")
+    within(dW, x64.transpose(0, 2, 1) @ dy64, ax.transpose(0, 2, 1) @ ad, M, False, "weight gradient")
+    within(db, dy64.sum(1), ad.sum(1), M, False, "bias gradient")
