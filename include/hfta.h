@@ -663,6 +663,9 @@ int hfta_dropout(int64_t count, int dtype, const void* X, const uint8_t* mask, f
 /* LayerNorm over the last dim E of X:[B][R][E] with per-model affine w,b: fp32 [B][E]. */
 int hfta_layernorm_fwd(int B, int R, int E, int dtype, const void* X, const float* w, const float* b,
                        float eps, float* save_mean, float* save_invstd, void* Y, void* stream);
+/* The residual form: S = X1 + X2 (rounded to the storage dtype, as hfta_add would store it), Y = LayerNorm(S). */
+int hfta_add_layernorm_fwd(int B, int R, int E, int dtype, const void* X1, const void* X2, void* S, const float* w,
+                           const float* b, float eps, float* save_mean, float* save_invstd, void* Y, void* stream);
 size_t hfta_layernorm_bwd_workspace_bytes(int B, int R, int E);
 int hfta_layernorm_bwd(int B, int R, int E, int dtype, const void* X, const void* dY, const float* w,
                        const float* save_mean, const float* save_invstd,

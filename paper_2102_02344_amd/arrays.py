@@ -676,12 +676,10 @@ class FusedMlp(ParamArena):
             hb.linear_fwd(B, R, H, E, dt, self.h[i], self.w(k + ".w2"), self.w(k + ".b2"), self.y)
             if P is not None:
                 P("linear_fwd", layer=k + ".2", x=self.h[i], w=self.w(k + ".w2"), b=self.w(k + ".b2"), y=self.y, act=0)
-            hb.add(B * R * E, dt, x, self.y, self.s[i])
+            hb.add_layernorm_fwd(B, R, E, dt, x, self.y, self.s[i], self.master(k + ".ln.w"), self.master(k + ".ln.b"),
+                                 self.LN_EPS, self.ln_mean[i], self.ln_invstd[i], self.x[i + 1])
             if P is not None:
                 P("add", a=x, b=self.y, y=self.s[i])
-            hb.layernorm_fwd(B, R, E, dt, self.s[i], self.master(k + ".ln.w"), self.master(k + ".ln.b"), self.LN_EPS,
-                             self.ln_mean[i], self.ln_invstd[i], self.x[i + 1])
-            if P is not None:
                 P("layernorm_fwd", layer=k, x=self.s[i], w=self.master(k + ".ln.w"), b=self.master(k + ".ln.b"),
                   y=self.x[i + 1], mean=self.ln_mean[i], invstd=self.ln_invstd[i])
         d = self.dE[0]
@@ -1310,16 +1308,36 @@ class FusedTransformerLM(ParamArena):
         self.dF = [torch.empty(B, R, F, **act) for _ in range(2)]
         self.dqkv = torch.empty(B, R, 3 * E, **act)
         self.loss = torch.empty(B, **f32)
-        ws = max(4, hb.layernorm_bwd_workspace_bytes(B, R, E), hb.attention_bwd_workspace_bytes(B, N, S, E, Hh, self.dt),
+        ws = max(4, hb.layernorm_bwd_sums_workspace_bytes(B, R, E), hb.attention_bwd_workspace_bytes(B, N, S, E, Hh, self.dt),
                  hb.softmax_xent_rows_workspace_bytes(B, R),
                  hb.linear_bwd_workspace_bytes(B, R, E, 3 * E, self.dt), hb.linear_bwd_workspace_bytes(B, R, E, F, self.dt),
                  hb.linear_bwd_workspace_bytes(B, R, F, E, self.dt), hb.linear_bwd_workspace_bytes(B, R, E, V, self.dt))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=self.dev)
 
-    def _lin_bwd(self, P, name, M, Fx, Fy, x, dy, dx):
-        hb.linear_bwd(self.B, M, Fx, Fy, self.dt, x, self.w(name + ".w"), dy, dx, self.g(name + ".w"), self.g(name + ".b"), self.ws)
+    def _lin_bwd(self, P, name, M, Fx, Fy, x, dy, dx, dbias=True):
+        """``dbias=False``: the bias gradient has been written already (by the LayerNorm backward that made dy)."""
+        hb.linear_bwd(self.B, M, Fx, Fy, self.dt, x, self.w(name + ".w"), dy, dx, self.g(name + ".w"),
+                      self.g(name + ".b") if dbias else None, self.ws)
         if P is not None:
             P("linear_bwd", layer=name, x=x, w=self.w(name + ".w"), dy=dy, dx=dx, dw=self.g(name + ".w"), db=self.g(name + ".b"))
+
+    def _ln_bwd(self, P, k, ln, lin, s, ga, gb, mean, invstd, dx):
+        """LayerNorm backward of the incoming gradient ga + gb (gb may be None), with the bias gradient of the Linear
+        whose output entered the residual sum where the one-call form takes the rows.  Returns whether it did."""
+        B, R, E, dt = self.B, self.R, self.E, self.dt
+        epv = 8 if dt == hb.BF16 else 4
+        fused = E % epv == 0 and E // epv <= 128
+        w, dw, db = self.master(f"{k}.{ln}.w"), self.g(f"{k}.{ln}.w"), self.g(f"{k}.{ln}.b")
+        if fused:
+            hb.layernorm_bwd_sums(B, R, E, dt, s, ga, gb, w, mean, invstd, dx, dw, db, self.g(f"{k}.{lin}.b"), self.ws)
+        else:
+            if gb is not None:
+                hb.add(B * R * E, dt, ga, gb, ga)
+            hb.layernorm_bwd(B, R, E, dt, s, ga, w, mean, invstd, dx, dw, db, self.ws)
+        if P is not None:
+            P("layernorm_bwd", layer=f"{k}.{ln}", x=s, dy=ga, dy2=gb if fused else None, w=w, mean=mean, invstd=invstd, dx=dx,
+              dw=dw, db=db)
+        return fused
 
     def forward_backward(self, probe=None):
         B, R, E, F, V, N, S, Hh, dt = self.B, self.R, self.E, self.F, self.V, self.N, self.S, self.Hh, self.dt
@@ -1340,12 +1358,10 @@ class FusedTransformerLM(ParamArena):
             hb.linear_fwd(B, R, E, E, dt, self.ctx[i], self.w(k + ".out.w"), self.w(k + ".out.b"), self.tmpE)
             if P is not None:
                 P("linear_fwd", layer=k + ".out", x=self.ctx[i], w=self.w(k + ".out.w"), b=self.w(k + ".out.b"), y=self.tmpE, act=0)
-            hb.add(B * R * E, dt, x, self.tmpE, self.s1[i])
+            hb.add_layernorm_fwd(B, R, E, dt, x, self.tmpE, self.s1[i], self.master(k + ".ln1.w"),
+                                 self.master(k + ".ln1.b"), self.LN_EPS, mu1, inv1, self.x1[i])
             if P is not None:
                 P("add", a=x, b=self.tmpE, y=self.s1[i])
-            hb.layernorm_fwd(B, R, E, dt, self.s1[i], self.master(k + ".ln1.w"), self.master(k + ".ln1.b"), self.LN_EPS,
-                             mu1, inv1, self.x1[i])
-            if P is not None:
                 P("layernorm_fwd", layer=k + ".ln1", x=self.s1[i], w=self.master(k + ".ln1.w"), b=self.master(k + ".ln1.b"),
                   y=self.x1[i], mean=mu1, invstd=inv1)
             hb.linear_fwd(B, R, E, F, dt, self.x1[i], self.w(k + ".ff1.w"), self.w(k + ".ff1.b"), self.h[i], hb.ACT_RELU)
@@ -1354,12 +1370,10 @@ class FusedTransformerLM(ParamArena):
             hb.linear_fwd(B, R, F, E, dt, self.h[i], self.w(k + ".ff2.w"), self.w(k + ".ff2.b"), self.tmpE)
             if P is not None:
                 P("linear_fwd", layer=k + ".ff2", x=self.h[i], w=self.w(k + ".ff2.w"), b=self.w(k + ".ff2.b"), y=self.tmpE, act=0)
-            hb.add(B * R * E, dt, self.x1[i], self.tmpE, self.s2[i])
+            hb.add_layernorm_fwd(B, R, E, dt, self.x1[i], self.tmpE, self.s2[i], self.master(k + ".ln2.w"),
+                                 self.master(k + ".ln2.b"), self.LN_EPS, mu2, inv2, self.x[i + 1])
             if P is not None:
                 P("add", a=self.x1[i], b=self.tmpE, y=self.s2[i])
-            hb.layernorm_fwd(B, R, E, dt, self.s2[i], self.master(k + ".ln2.w"), self.master(k + ".ln2.b"), self.LN_EPS,
-                             mu2, inv2, self.x[i + 1])
-            if P is not None:
                 P("layernorm_fwd", layer=k + ".ln2", x=self.s2[i], w=self.master(k + ".ln2.w"), b=self.master(k + ".ln2.b"),
                   y=self.x[i + 1], mean=mu2, invstd=inv2)
         hb.linear_fwd(B, R, E, V, dt, self.x[nl], self.w("dec.w"), self.w("dec.b"), self.logits)
@@ -1369,40 +1383,39 @@ class FusedTransformerLM(ParamArena):
         if P is not None:
             P("softmax_xent", logits=self.logits, labels=self.targets, loss=self.loss, d=self.dlogits)
         # ---- backward
-        d = self.dE[0]
-        self._lin_bwd(P, "dec", R, E, V, self.x[nl], self.dlogits, d)
+        # A block's incoming gradient is the pair (ga, gb) whose sum it is: the LayerNorm backward adds them on load.
+        ga, gb, free = self.dE[0], None, list(self.dE[1:])
+        self._lin_bwd(P, "dec", R, E, V, self.x[nl], self.dlogits, ga)
         for i in reversed(range(nl)):
             k = f"l{i}"
             mu1, inv1, mu2, inv2 = self.stats[i]
-            ds2, t1, t2 = self.dE[1], self.dE[2], self.dE[3]
-            hb.layernorm_bwd(B, R, E, dt, self.s2[i], d, self.master(k + ".ln2.w"), mu2, inv2, ds2,
-                             self.g(k + ".ln2.w"), self.g(k + ".ln2.b"), self.ws)
-            if P is not None:
-                P("layernorm_bwd", layer=k + ".ln2", x=self.s2[i], dy=d, w=self.master(k + ".ln2.w"), mean=mu2, invstd=inv2,
-                  dx=ds2, dw=self.g(k + ".ln2.w"), db=self.g(k + ".ln2.b"))
-            self._lin_bwd(P, k + ".ff2", R, F, E, self.h[i], ds2, self.dF[0])
+            ds2 = free.pop()
+            fused = self._ln_bwd(P, k, "ln2", "ff2", self.s2[i], ga, gb, mu2, inv2, ds2)
+            free += [t for t in (ga, gb) if t is not None]
+            self._lin_bwd(P, k + ".ff2", R, F, E, self.h[i], ds2, self.dF[0], not fused)
             hb.act_bwd(B * R * F, dt, self.h[i], self.dF[0], self.dF[1], hb.ACT_RELU, 0.0, 1)
             if P is not None:
                 P("relu_bwd_from_output", y=self.h[i], dy=self.dF[0], dx=self.dF[1])
-            self._lin_bwd(P, k + ".ff1", R, E, F, self.x1[i], self.dF[1], t1)
-            hb.add(B * R * E, dt, ds2, t1, t2)
+            dx1 = free.pop()
+            self._lin_bwd(P, k + ".ff1", R, E, F, self.x1[i], self.dF[1], dx1)
+            ds1 = free.pop()
+            fused = self._ln_bwd(P, k, "ln1", "out", self.s1[i], ds2, dx1, mu1, inv1, ds1)
+            free += [ds2, dx1]
+            dctx = free.pop()
+            self._lin_bwd(P, k + ".out", R, E, E, self.ctx[i], ds1, dctx, not fused)
+            hb.attention_bwd(B, N, S, E, Hh, dt, self.qkv[i], self.p[i], dctx, self.dqkv, self.ws)
             if P is not None:
-                P("add", a=ds2, b=t1, y=t2)
-            ds1 = self.dE[1]                                   # ds2 is consumed
-            hb.layernorm_bwd(B, R, E, dt, self.s1[i], t2, self.master(k + ".ln1.w"), mu1, inv1, ds1,
-                             self.g(k + ".ln1.w"), self.g(k + ".ln1.b"), self.ws)
+                P("attention_bwd", qkv=self.qkv[i], p=self.p[i], dctx=dctx, dqkv=self.dqkv)
+            dx = free.pop()
+            self._lin_bwd(P, k + ".in", R, E, 3 * E, self.x[i], self.dqkv, dx)
+            free.append(dctx)
+            ga, gb = ds1, dx
+        d = ga
+        if gb is not None:
+            d = free.pop()
+            hb.add(B * R * E, dt, ga, gb, d)
             if P is not None:
-                P("layernorm_bwd", layer=k + ".ln1", x=self.s1[i], dy=t2, w=self.master(k + ".ln1.w"), mean=mu1, invstd=inv1,
-                  dx=ds1, dw=self.g(k + ".ln1.w"), db=self.g(k + ".ln1.b"))
-            self._lin_bwd(P, k + ".out", R, E, E, self.ctx[i], ds1, t1)            # t1 = dctx
-            hb.attention_bwd(B, N, S, E, Hh, dt, self.qkv[i], self.p[i], t1, self.dqkv, self.ws)
-            if P is not None:
-                P("attention_bwd", qkv=self.qkv[i], p=self.p[i], dctx=t1, dqkv=self.dqkv)
-            self._lin_bwd(P, k + ".in", R, E, 3 * E, self.x[i], self.dqkv, t2)
-            hb.add(B * R * E, dt, ds1, t2, self.dE[0])
-            if P is not None:
-                P("add", a=ds1, b=t2, y=self.dE[0])
-            d = self.dE[0]
+                P("add", a=ga, b=gb, y=d)
         hb.embedding_bwd(B, R, V, E, dt, d, self.tokens, self.scale, self.g("emb"))
         if P is not None:
             P("embedding_bwd", dy=d, idx=self.tokens, dtable=self.g("emb"))

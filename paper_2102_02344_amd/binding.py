@@ -116,6 +116,7 @@ _SIGS = {
     "hfta_dropout": (_i, [_i64, _i, _p, _p, _f, _p, _p]),
     "hfta_add": (_i, [_i64, _i, _p, _p, _p, _p]),
     "hfta_layernorm_fwd": (_i, [_i, _i, _i, _i, _p, _p, _p, _f, _p, _p, _p, _p]),
+    "hfta_add_layernorm_fwd": (_i, [_i, _i, _i, _i, _p, _p, _p, _p, _p, _f, _p, _p, _p, _p]),
     "hfta_layernorm_bwd_workspace_bytes": (_sz, [_i, _i, _i]),
     "hfta_layernorm_bwd": (_i, [_i, _i, _i, _i, _p, _p, _p, _p, _p, _p, _p, _p, _p, _sz, _p]),
     "hfta_layernorm_bwd_sums_workspace_bytes": (_sz, [_i, _i, _i]),
@@ -506,6 +507,11 @@ def dropout(count, dtype, X, mask, p, Y, stream=None):
 def layernorm_fwd(B, R, E, dtype, X, w, b, eps, save_mean, save_invstd, Y, stream=None):
     _check(_lib.hfta_layernorm_fwd(B, R, E, dtype, _ptr(X), _ptr(w), _ptr(b), eps, _ptr(save_mean),
                                    _ptr(save_invstd), _ptr(Y), _stream(stream)), "hfta_layernorm_fwd")
+
+
+def add_layernorm_fwd(B, R, E, dtype, X1, X2, S, w, b, eps, save_mean, save_invstd, Y, stream=None):
+    _check(_lib.hfta_add_layernorm_fwd(B, R, E, dtype, _ptr(X1), _ptr(X2), _ptr(S), _ptr(w), _ptr(b), eps, _ptr(save_mean),
+                                       _ptr(save_invstd), _ptr(Y), _stream(stream)), "hfta_add_layernorm_fwd")
 
 
 def layernorm_bwd_workspace_bytes(B, R, E) -> int:

@@ -243,37 +243,55 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const T* __restrict_
   }
 }
 
-// np = 2: [dw | db] partial rows per block; np = 3: a third row, the column sums of the stored dX
-__global__ __launch_bounds__(256) void layernorm_bwd_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                                                  float* __restrict__ db, float* __restrict__ dxs, int E,
-                                                                  int nblk, int np) {
-  const int b = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= E) return;
-  float aw = 0.f, ab = 0.f, ax = 0.f;
-  for (int k = 0; k < nblk; ++k) {
-    const float* pw = part + (((int64_t)b * nblk + k) * np) * E;
-    aw += pw[e]; ab += pw[E + e];
-    if (np == 3) ax += pw[2 * E + e];
+// np = 2: [dw | db] partial rows per block; np = 3: a third row, the column sums of the stored dX.
+// 64 columns x 16 chains of blocks per workgroup (chain q takes blocks q, q + 16, ...), the chains added in
+// order.  One thread per column walking all blocks was a chain of dependent loads on a handful of workgroups:
+// 22 us for 64 blocks of 16 x 512 columns, 4.9 now.
+__global__ __launch_bounds__(1024) void layernorm_bwd_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw,
+                                                                   float* __restrict__ db, float* __restrict__ dxs, int E,
+                                                                   int nblk, int np) {
+  __shared__ float sh[16][64];
+  const int b = blockIdx.y, li = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + li;
+  const int row = blockIdx.z;                             // dw, db or the sums of dX
+  float s = 0.f;
+  if (e < E) {
+    const float* p = part + ((int64_t)b * nblk * np + row) * E + e;
+#pragma unroll 4
+    for (int k = q; k < nblk; k += 16) s += p[(int64_t)k * np * E];
   }
-  dw[(int64_t)b * E + e] = aw;
-  db[(int64_t)b * E + e] = ab;
-  if (np == 3) dxs[(int64_t)b * E + e] = ax;
+  sh[q][li] = s;
+  __syncthreads();
+  if (q == 0 && e < E) {
+    float t = sh[0][li];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) t += sh[k][li];
+    (row == 0 ? dw : row == 1 ? db : dxs)[(int64_t)b * E + e] = t;
+  }
 }
 
 // ---- LayerNorm, register-resident rows ----------------------------------------
-// One wavefront per row, a lane holds CH x 16 bytes of it (E <= CH * 64 * 16 / sizeof(T)), so the
-// row is read from memory once: statistics, normalisation (and in the backward the per-column
-// partial sums for dw, db) all work on registers.  Rows of a block are dealt round-robin to its
-// four wavefronts; column partials are combined wave 0..3 in order, so results are reproducible.
-template <typename T, int CH>
+// LPR lanes per row (a wavefront, or half of one for rows of at most 32 pieces), a lane holds CH x 16 bytes of
+// it, so the row is read from memory once: statistics, normalisation (and in the backward the per-column
+// partial sums for dw, db) all work on registers.  Rows of a block are dealt round-robin to its row slots;
+// column partials are combined in a fixed order, so results are reproducible.
+template <int LPR> __device__ __forceinline__ float row_sum(float v) {
+#pragma unroll
+  for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// ADD: the row is X + X2 rounded to the storage type, as if a separate element-wise sum had stored it; it is
+// stored to Sum (the residual sum, which the backward reads).  Against the two calls one read and one launch less.
+template <typename T, int CH, int LPR, bool ADD>
 __global__ __launch_bounds__(256) void layernorm_fwd_vec_kernel(const uint4* __restrict__ X, const float* __restrict__ w,
                                                                const float* __restrict__ bsh, float eps,
                                                                float* __restrict__ save_mean, float* __restrict__ save_invstd,
-                                                               uint4* __restrict__ Y, int R, int E, int64_t rows) {
-  constexpr int N = V16<T>::N;
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                               uint4* __restrict__ Y, int R, int E, int64_t rows,
+                                                               const uint4* __restrict__ X2, uint4* __restrict__ Sum) {
+  constexpr int N = V16<T>::N, SLOTS = 256 / LPR;
+  const int lane = threadIdx.x & (LPR - 1);
+  const int64_t row = (int64_t)blockIdx.x * SLOTS + threadIdx.x / LPR;
   if (row >= rows) return;
   const int b = (int)(row / R);
   const int vpr = E / N;                                  // 16-byte vectors per row
@@ -281,26 +299,35 @@ __global__ __launch_bounds__(256) void layernorm_fwd_vec_kernel(const uint4* __r
   float s = 0.f;
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int v = lane + 64 * c;
+    const int v = lane + LPR * c;
     if (v < vpr) {
       V16<T>::unpack(X[row * vpr + v], f[c]);
+      if (ADD) {
+        float f2[N];
+        V16<T>::unpack(X2[row * vpr + v], f2);
+#pragma unroll
+        for (int e = 0; e < N; ++e) f[c][e] += f2[e];
+        const uint4 st = V16<T>::pack(f[c]);
+        Sum[row * vpr + v] = st;
+        V16<T>::unpack(st, f[c]);
+      }
 #pragma unroll
       for (int e = 0; e < N; ++e) s += f[c][e];
     }
   }
-  const float mean = wave_sum(s) / (float)E;
+  const float mean = row_sum<LPR>(s) / (float)E;
   float q = 0.f;
 #pragma unroll
   for (int c = 0; c < CH; ++c)
-    if (lane + 64 * c < vpr) {
+    if (lane + LPR * c < vpr) {
 #pragma unroll
       for (int e = 0; e < N; ++e) { const float d = f[c][e] - mean; q = fmaf(d, d, q); }
     }
-  const float invstd = 1.0f / sqrtf(wave_sum(q) / (float)E + eps);
+  const float invstd = 1.0f / sqrtf(row_sum<LPR>(q) / (float)E + eps);
   if (lane == 0) { save_mean[row] = mean; save_invstd[row] = invstd; }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int v = lane + 64 * c;
+    const int v = lane + LPR * c;
     if (v < vpr) {
       const float* wp = w + (int64_t)b * E + v * N;
       const float* bp = bsh + (int64_t)b * E + v * N;
@@ -314,16 +341,16 @@ __global__ __launch_bounds__(256) void layernorm_fwd_vec_kernel(const uint4* __r
 // SUMS: the incoming gradient is dY + dY2 (rounded to the storage type, as if a separate element-wise
 // sum had stored it) when dY2 is given, and a third partial row carries the column sums of the
 // stored dX (the bias gradient of the Linear that produced X's residual branch).
-template <typename T, int CH, bool SUMS = false>
+template <typename T, int CH, int LPR, bool SUMS>
 __global__ __launch_bounds__(256) void layernorm_bwd_vec_kernel(const uint4* __restrict__ X, const uint4* __restrict__ dY,
                                                                const float* __restrict__ w, const float* __restrict__ save_mean,
                                                                const float* __restrict__ save_invstd, uint4* __restrict__ dX,
                                                                float* __restrict__ part, int R, int E, int rows_per_block,
-                                                               const uint4* __restrict__ dY2 = nullptr) {
-  constexpr int N = V16<T>::N;
+                                                               const uint4* __restrict__ dY2) {
+  constexpr int N = V16<T>::N, SLOTS = 256 / LPR;
   constexpr int NP = SUMS ? 3 : 2;
-  __shared__ float red[3][NP][CH * 64 * N];               // waves 1..3: [dw | db (| dx sums)] partials
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  __shared__ float red[SLOTS - 1][NP][CH * LPR * N];      // slots 1..: [dw | db (| dx sums)] partials
+  const int lane = threadIdx.x & (LPR - 1), slot = threadIdx.x / LPR;
   const int b = blockIdx.y;
   const int r_begin = blockIdx.x * rows_per_block;
   const int r_end = min(R, r_begin + rows_per_block);
@@ -333,19 +360,19 @@ __global__ __launch_bounds__(256) void layernorm_bwd_vec_kernel(const uint4* __r
   for (int c = 0; c < CH; ++c)
 #pragma unroll
     for (int e = 0; e < N; ++e) {
-      const int col = (lane + 64 * c) * N + e;
+      const int col = (lane + LPR * c) * N + e;
       wl[c][e] = col < E ? w[(int64_t)b * E + col] : 0.f;
       aw[c][e] = 0.f; ab[c][e] = 0.f;
       if (SUMS) ax[c][e] = 0.f;
     }
-  for (int r = r_begin + wv; r < r_end; r += 4) {
+  for (int r = r_begin + slot; r < r_end; r += SLOTS) {
     const int64_t row = (int64_t)b * R + r;
     const float mean = save_mean[row], invstd = save_invstd[row];
     float xh[CH][N], g[CH][N];
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-      const int v = lane + 64 * c;
+      const int v = lane + LPR * c;
       if (v < vpr) {
         float x[N], d[N];
         V16<T>::unpack(X[row * vpr + v], x);
@@ -366,11 +393,11 @@ __global__ __launch_bounds__(256) void layernorm_bwd_vec_kernel(const uint4* __r
         }
       }
     }
-    s1 = wave_sum(s1) / (float)E;
-    s2 = wave_sum(s2) / (float)E;
+    s1 = row_sum<LPR>(s1) / (float)E;
+    s2 = row_sum<LPR>(s2) / (float)E;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-      const int v = lane + 64 * c;
+      const int v = lane + LPR * c;
       if (v < vpr) {
         float o[N];
 #pragma unroll
@@ -385,28 +412,35 @@ __global__ __launch_bounds__(256) void layernorm_bwd_vec_kernel(const uint4* __r
       }
     }
   }
-  if (wv > 0) {
+  if (slot > 0) {
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
       for (int e = 0; e < N; ++e) {
-        red[wv - 1][0][(lane + 64 * c) * N + e] = aw[c][e];
-        red[wv - 1][1][(lane + 64 * c) * N + e] = ab[c][e];
-        if (SUMS) red[wv - 1][NP - 1][(lane + 64 * c) * N + e] = ax[c][e];
+        red[slot - 1][0][(lane + LPR * c) * N + e] = aw[c][e];
+        red[slot - 1][1][(lane + LPR * c) * N + e] = ab[c][e];
+        if (SUMS) red[slot - 1][NP - 1][(lane + LPR * c) * N + e] = ax[c][e];
       }
   }
   __syncthreads();
-  if (wv == 0) {
+  if (slot == 0) {
     float* pw = part + (((int64_t)b * gridDim.x + blockIdx.x) * NP) * E;
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
       for (int e = 0; e < N; ++e) {
-        const int col = (lane + 64 * c) * N + e;
+        const int col = (lane + LPR * c) * N + e;
         if (col < E) {
-          pw[col] = ((aw[c][e] + red[0][0][col]) + red[1][0][col]) + red[2][0][col];
-          pw[E + col] = ((ab[c][e] + red[0][1][col]) + red[1][1][col]) + red[2][1][col];
-          if (SUMS) pw[2 * E + col] = ((ax[c][e] + red[0][NP - 1][col]) + red[1][NP - 1][col]) + red[2][NP - 1][col];
+          float tw = aw[c][e], tb = ab[c][e], tx = SUMS ? ax[c][e] : 0.f;
+#pragma unroll
+          for (int k = 0; k < SLOTS - 1; ++k) {
+            tw += red[k][0][col];
+            tb += red[k][1][col];
+            if (SUMS) tx += red[k][NP - 1][col];
+          }
+          pw[col] = tw;
+          pw[E + col] = tb;
+          if (SUMS) pw[2 * E + col] = tx;
         }
       }
   }
@@ -672,6 +706,52 @@ static bool launch_pointwise_wide(int B, int64_t R, int dtype, const void* pred,
 
 }  // namespace
 
+// lanes per row of the register-resident kernels: half a wavefront where that holds a row in one 16-byte piece
+// per lane (a whole one would leave half its lanes idle), else a wavefront with one or two pieces per lane
+template <typename T, bool ADD>
+static void launch_ln_fwd(int R, int E, int64_t rows, const void* X, const void* X2, void* Sum, const float* w, const float* b,
+                          float eps, float* mean, float* invstd, void* Y, hipStream_t st) {
+  const int vpr = E / V16<T>::N;
+#define HFTA_LNF(CH, LPR) hipLaunchKernelGGL((layernorm_fwd_vec_kernel<T, CH, LPR, ADD>), \
+    dim3((unsigned)((rows + 256 / LPR - 1) / (256 / LPR))), dim3(256), 0, st, (const uint4*)X, w, b, eps, mean, invstd, \
+    (uint4*)Y, R, E, rows, (const uint4*)X2, (uint4*)Sum)
+  if (vpr <= 32) HFTA_LNF(1, 32);
+  else if (vpr <= 64) HFTA_LNF(1, 64);
+  else HFTA_LNF(2, 64);
+#undef HFTA_LNF
+}
+
+static bool ln_vec_rows(int E, int dtype) {
+  const int epv = 16 / (int)dtype_size(dtype);
+  return E % epv == 0 && E / epv <= 128;
+}
+
+// Workgroups per model of the backward: 16 rows each up to 128 workgroups (a function of R alone, so that a model's
+// result does not depend on how many it is trained with).  64 rows each left small arrays one workgroup per
+// compute unit: 8 x 2048 rows of 256 took 23.4 us, 12.5 now with a second gradient and the column sums besides.
+static int ln_blocks(int R) {
+  const int nb = (R + 15) / 16;
+  return nb > 128 ? 128 : nb;
+}
+
+template <typename T, bool SUMS>
+static void launch_ln_bwd(int R, int E, dim3 grid, const void* X, const void* dY, const void* dY2, const float* w,
+                          const float* mean, const float* invstd, void* dX, float* part, hipStream_t st) {
+  const int vpr = E / V16<T>::N, rpb = (R + (int)grid.x - 1) / (int)grid.x;
+#define HFTA_LNB(CH, LPR) hipLaunchKernelGGL((layernorm_bwd_vec_kernel<T, CH, LPR, SUMS>), grid, dim3(256), 0, st, (const uint4*)X, \
+    (const uint4*)dY, w, mean, invstd, (uint4*)dX, part, R, E, rpb, (const uint4*)dY2)
+  if (vpr <= 32) HFTA_LNB(1, 32);
+  else if (vpr <= 64) HFTA_LNB(1, 64);
+  else HFTA_LNB(2, 64);
+#undef HFTA_LNB
+}
+
+static int ln_bwd_reduce(int B, int E, int nblk, int np, const float* part, float* dw, float* db, float* dxs, hipStream_t st) {
+  hipLaunchKernelGGL(layernorm_bwd_reduce_kernel, dim3((unsigned)((E + 63) / 64), (unsigned)B, (unsigned)np), dim3(1024), 0, st,
+                     part, dw, db, dxs, E, nblk, np);
+  return launch_status();
+}
+
 extern "C" {
 
 const char* hfta_status_string(int status) {
@@ -826,32 +906,37 @@ int hfta_layernorm_fwd(int B, int R, int E, int dtype, const void* X, const floa
     return HFTA_EINVAL;
   const int64_t rows = (int64_t)B * R;
   if ((rows + 3) / 4 > 0x7fffffffLL) return HFTA_EINVAL;
-  dim3 grid((unsigned)((rows + 3) / 4));
-  const int epv = 16 / (int)dtype_size(dtype);
-  if (al16(X) && al16(Y) && E % epv == 0 && E / epv <= 128) {      // rows fit one or two 16-byte pieces per lane
-    hipStream_t st = as_stream(stream);
-    const bool one = E / epv <= 64;
-    if (dtype == HFTA_BF16) {
-      if (one) hipLaunchKernelGGL((layernorm_fwd_vec_kernel<bf16_raw, 1>), grid, dim3(256), 0, st, (const uint4*)X, w, b, eps, save_mean, save_invstd, (uint4*)Y, R, E, rows);
-      else hipLaunchKernelGGL((layernorm_fwd_vec_kernel<bf16_raw, 2>), grid, dim3(256), 0, st, (const uint4*)X, w, b, eps, save_mean, save_invstd, (uint4*)Y, R, E, rows);
-    } else {
-      if (one) hipLaunchKernelGGL((layernorm_fwd_vec_kernel<float, 1>), grid, dim3(256), 0, st, (const uint4*)X, w, b, eps, save_mean, save_invstd, (uint4*)Y, R, E, rows);
-      else hipLaunchKernelGGL((layernorm_fwd_vec_kernel<float, 2>), grid, dim3(256), 0, st, (const uint4*)X, w, b, eps, save_mean, save_invstd, (uint4*)Y, R, E, rows);
-    }
+  hipStream_t st = as_stream(stream);
+  if (al16(X) && al16(Y) && ln_vec_rows(E, dtype)) {
+    if (dtype == HFTA_BF16) launch_ln_fwd<bf16_raw, false>(R, E, rows, X, nullptr, nullptr, w, b, eps, save_mean, save_invstd, Y, st);
+    else launch_ln_fwd<float, false>(R, E, rows, X, nullptr, nullptr, w, b, eps, save_mean, save_invstd, Y, st);
     return launch_status();
   }
+  dim3 grid((unsigned)((rows + 3) / 4));
   if (dtype == HFTA_BF16)
-    hipLaunchKernelGGL(layernorm_fwd_kernel<bf16_raw>, grid, dim3(256), 0, as_stream(stream), (const bf16_raw*)X, w, b, eps,
+    hipLaunchKernelGGL(layernorm_fwd_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)X, w, b, eps,
                        save_mean, save_invstd, (bf16_raw*)Y, R, E, rows);
   else
-    hipLaunchKernelGGL(layernorm_fwd_kernel<float>, grid, dim3(256), 0, as_stream(stream), (const float*)X, w, b, eps,
+    hipLaunchKernelGGL(layernorm_fwd_kernel<float>, grid, dim3(256), 0, st, (const float*)X, w, b, eps,
                        save_mean, save_invstd, (float*)Y, R, E, rows);
   return launch_status();
 }
 
-static int ln_blocks(int R) {
-  int nb = (R + 63) / 64;
-  return nb > 256 ? 256 : nb;
+int hfta_add_layernorm_fwd(int B, int R, int E, int dtype, const void* X1, const void* X2, void* S, const float* w,
+                           const float* b, float eps, float* save_mean, float* save_invstd, void* Y, void* stream) {
+  if (B <= 0 || R <= 0 || E <= 0 || !valid_dtype(dtype) || !X1 || !X2 || !S || !w || !b || !save_mean || !save_invstd || !Y ||
+      !(eps >= 0.f))
+    return HFTA_EINVAL;
+  const int64_t rows = (int64_t)B * R;
+  if ((rows + 3) / 4 > 0x7fffffffLL) return HFTA_EINVAL;
+  if (!(al16(X1) && al16(X2) && al16(S) && al16(Y) && ln_vec_rows(E, dtype))) {
+    const int rc = hfta_add(rows * E, dtype, X1, X2, S, stream);
+    return rc != HFTA_OK ? rc : hfta_layernorm_fwd(B, R, E, dtype, S, w, b, eps, save_mean, save_invstd, Y, stream);
+  }
+  hipStream_t st = as_stream(stream);
+  if (dtype == HFTA_BF16) launch_ln_fwd<bf16_raw, true>(R, E, rows, X1, X2, S, w, b, eps, save_mean, save_invstd, Y, st);
+  else launch_ln_fwd<float, true>(R, E, rows, X1, X2, S, w, b, eps, save_mean, save_invstd, Y, st);
+  return launch_status();
 }
 
 size_t hfta_layernorm_bwd_workspace_bytes(int B, int R, int E) {
@@ -870,27 +955,18 @@ int hfta_layernorm_bwd(int B, int R, int E, int dtype, const void* X, const void
   const int rpb = (R + nblk - 1) / nblk;
   hipStream_t st = as_stream(stream);
   dim3 grid((unsigned)nblk, (unsigned)B);
-  const int epv = 16 / (int)dtype_size(dtype);
-  if (al16(X) && al16(dY) && al16(dX) && E % epv == 0 && E / epv <= 128) {
-    const bool one = E / epv <= 64;
-    float* part = (float*)workspace;
-    if (dtype == HFTA_BF16) {
-      if (one) hipLaunchKernelGGL((layernorm_bwd_vec_kernel<bf16_raw, 1>), grid, dim3(256), 0, st, (const uint4*)X, (const uint4*)dY, w, save_mean, save_invstd, (uint4*)dX, part, R, E, rpb);
-      else hipLaunchKernelGGL((layernorm_bwd_vec_kernel<bf16_raw, 2>), grid, dim3(256), 0, st, (const uint4*)X, (const uint4*)dY, w, save_mean, save_invstd, (uint4*)dX, part, R, E, rpb);
-    } else {
-      if (one) hipLaunchKernelGGL((layernorm_bwd_vec_kernel<float, 1>), grid, dim3(256), 0, st, (const uint4*)X, (const uint4*)dY, w, save_mean, save_invstd, (uint4*)dX, part, R, E, rpb);
-      else hipLaunchKernelGGL((layernorm_bwd_vec_kernel<float, 2>), grid, dim3(256), 0, st, (const uint4*)X, (const uint4*)dY, w, save_mean, save_invstd, (uint4*)dX, part, R, E, rpb);
-    }
+  float* part = (float*)workspace;
+  if (al16(X) && al16(dY) && al16(dX) && ln_vec_rows(E, dtype)) {
+    if (dtype == HFTA_BF16) launch_ln_bwd<bf16_raw, false>(R, E, grid, X, dY, nullptr, w, save_mean, save_invstd, dX, part, st);
+    else launch_ln_bwd<float, false>(R, E, grid, X, dY, nullptr, w, save_mean, save_invstd, dX, part, st);
   } else if (dtype == HFTA_BF16)
     hipLaunchKernelGGL(layernorm_bwd_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)X, (const bf16_raw*)dY, w,
-                       save_mean, save_invstd, (bf16_raw*)dX, (float*)workspace, R, E, rpb);
+                       save_mean, save_invstd, (bf16_raw*)dX, part, R, E, rpb);
   else
     hipLaunchKernelGGL(layernorm_bwd_kernel<float>, grid, dim3(256), 0, st, (const float*)X, (const float*)dY, w, save_mean,
-                       save_invstd, (float*)dX, (float*)workspace, R, E, rpb);
+                       save_invstd, (float*)dX, part, R, E, rpb);
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
-  hipLaunchKernelGGL(layernorm_bwd_reduce_kernel, dim3((unsigned)((E + 255) / 256), (unsigned)B), dim3(256), 0, st,
-                     (const float*)workspace, dw, db, (float*)nullptr, E, nblk, 2);
-  return launch_status();
+  return ln_bwd_reduce(B, E, nblk, 2, part, dw, db, nullptr, st);
 }
 
 size_t hfta_layernorm_bwd_sums_workspace_bytes(int B, int R, int E) {
@@ -906,23 +982,15 @@ int hfta_layernorm_bwd_sums(int B, int R, int E, int dtype, const void* X, const
     return HFTA_EINVAL;
   if (B > 65535) return HFTA_EUNSUPPORTED;
   if (!workspace || ws_bytes < hfta_layernorm_bwd_sums_workspace_bytes(B, R, E)) return HFTA_EWORKSPACE;
-  const int epv = 16 / (int)dtype_size(dtype);
-  if (!(al16(X) && al16(dY) && al16(dX) && (!dY2 || al16(dY2)) && E % epv == 0 && E / epv <= 128)) return HFTA_EUNSUPPORTED;
+  if (!(al16(X) && al16(dY) && al16(dX) && (!dY2 || al16(dY2)) && ln_vec_rows(E, dtype))) return HFTA_EUNSUPPORTED;
   const int nblk = ln_blocks(R);
-  const int rpb = (R + nblk - 1) / nblk;
   hipStream_t st = as_stream(stream);
   dim3 grid((unsigned)nblk, (unsigned)B);
-  const bool one = E / epv <= 64;
   float* part = (float*)workspace;
-#define HFTA_LNS(T, CHN) hipLaunchKernelGGL((layernorm_bwd_vec_kernel<T, CHN, true>), grid, dim3(256), 0, st, (const uint4*)X, \
-    (const uint4*)dY, w, save_mean, save_invstd, (uint4*)dX, part, R, E, rpb, (const uint4*)dY2)
-  if (dtype == HFTA_BF16) { if (one) HFTA_LNS(bf16_raw, 1); else HFTA_LNS(bf16_raw, 2); }
-  else { if (one) HFTA_LNS(float, 1); else HFTA_LNS(float, 2); }
-#undef HFTA_LNS
+  if (dtype == HFTA_BF16) launch_ln_bwd<bf16_raw, true>(R, E, grid, X, dY, dY2, w, save_mean, save_invstd, dX, part, st);
+  else launch_ln_bwd<float, true>(R, E, grid, X, dY, dY2, w, save_mean, save_invstd, dX, part, st);
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
-  hipLaunchKernelGGL(layernorm_bwd_reduce_kernel, dim3((unsigned)((E + 255) / 256), (unsigned)B), dim3(256), 0, st,
-                     (const float*)workspace, dw, db, dx_colsum, E, nblk, 3);
-  return launch_status();
+  return ln_bwd_reduce(B, E, nblk, 3, part, dw, db, dx_colsum, st);
 }
 
 int hfta_softmax_xent(int B, int R, int K, int dtype, const void* logits, const int32_t* labels, float* loss,
