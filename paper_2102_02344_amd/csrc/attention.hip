@@ -7,9 +7,15 @@
 // on the library's GEMM core: Q, K, V are column blocks of the packed projection output
 // [B][N][S][3E], addressed by leading dimension 3E and a per-head offset, so no head split or
 // transpose is ever materialised; the context is written straight into its [B][N][S][E] layout.
-// The softmax (scale and causal mask folded in) and its backward run in place on the score buffer,
+// (Most bf16 heads take the one-kernel form of attention_core.hip instead.)  The softmax (scale and causal mask folded in) and its backward run in place on the score buffer,
 // one wavefront per row.
 #include "gemm.h"
+
+namespace hfta {       // attention_core.hip: one kernel per direction for bf16 heads it takes
+bool attn_core_ok(int S, int E, int H, int dtype, const void* a, const void* b, const void* c);
+int attn_core_fwd(int BN, int S, int E, int H, const void* QKV, void* P, void* CTX, int causal, hipStream_t st);
+int attn_core_bwd(int BN, int S, int E, int H, const void* QKV, const void* P, const void* dCTX, void* dQKV, hipStream_t st);
+}  // namespace hfta
 
 using namespace hfta;
 
@@ -282,10 +288,11 @@ int hfta_attention_fwd(int B, int N, int S, int E, int H, int dtype, const void*
                        void* stream) {
   if (!valid_dtype(dtype) || !QKV || !P || !CTX) return HFTA_EINVAL;
   if (!attn_ok(B, N, S, E, H)) return B > 0 && N > 0 && S > 0 && E > 0 && H > 0 && E % H == 0 ? HFTA_EUNSUPPORTED : HFTA_EINVAL;
+  hipStream_t st = as_stream(stream);
+  if (attn_core_ok(S, E, H, dtype, QKV, CTX, nullptr)) return attn_core_fwd(B * N, S, E, H, QKV, P, CTX, causal, st);
   const int d = E / H;
   const size_t es = dtype_size(dtype);
   const unsigned char* q = reinterpret_cast<const unsigned char*>(QKV);
-  hipStream_t st = as_stream(stream);
   const int64_t tok = (int64_t)S * 3 * E, ss = (int64_t)S * S;
   // scores[i][j] = sum_c Q[i][c] K[j][c]
   GemmDesc g = head_desc(B, N, H, dtype);
@@ -322,11 +329,12 @@ int hfta_attention_bwd(int B, int N, int S, int E, int H, int dtype, const void*
   if (!valid_dtype(dtype) || !QKV || !P || !dCTX || !dQKV) return HFTA_EINVAL;
   if (!attn_ok(B, N, S, E, H)) return B > 0 && N > 0 && S > 0 && E > 0 && H > 0 && E % H == 0 ? HFTA_EUNSUPPORTED : HFTA_EINVAL;
   if (!workspace || ws_bytes < hfta_attention_bwd_workspace_bytes(B, N, S, E, H, dtype)) return HFTA_EWORKSPACE;
+  hipStream_t st = as_stream(stream);
+  if (attn_core_ok(S, E, H, dtype, QKV, dCTX, dQKV)) return attn_core_bwd(B * N, S, E, H, QKV, P, dCTX, dQKV, st);
   const int d = E / H;
   const size_t es = dtype_size(dtype);
   const unsigned char* q = reinterpret_cast<const unsigned char*>(QKV);
   unsigned char* dq = reinterpret_cast<unsigned char*>(dQKV);
-  hipStream_t st = as_stream(stream);
   const int64_t tok = (int64_t)S * 3 * E, ss = (int64_t)S * S, hs = (int64_t)H * ss;
   // dV[j][c] = sum_i P[i][j] dCTX[i][c]
   GemmDesc g = head_desc(B, N, H, dtype);
