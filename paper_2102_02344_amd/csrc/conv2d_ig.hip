@@ -20,7 +20,7 @@
 // bf16 only; output grids whose width and height are powers of two; see ig_*_supported.
 #include <mutex>
 #include <vector>
-#include "gemm_pf.h"
+#include "gemm_dma.h"
 
 namespace hfta {
 
@@ -62,6 +62,7 @@ struct IgArgs {
   int tap_step;                         // 1 (patch elements between the taps of a window row; see the column-tile build)
   int NI, TR, PR, PW, SP;               // samples per tile, grid rows per tile and sample, patch rows, row pitch, sample pitch (elements)
   int nchunk, chunk_el;                 // 16- or 8-byte pieces of patch rows per k-tile, elements per piece
+  int chp, plp;                         // plane kernels: bytes of a channel's rows in a plane, bytes between planes
   uint32_t x_bytes, a_bytes;            // extent of one model's slice of the view operand / of its weights
   IgGrid grid;                          // logical grid: x = tiles, y = class / k split, z = model
   int ksplit, kt_per_split;             // k range split over the grid's y (> 1: fp32 partial slices instead of Out)
@@ -92,6 +93,99 @@ __device__ __forceinline__ void ig_stage64(f32x16_t (&acc)[2][FN], unsigned char
         for (int e = 0; e < 4; ++e) x[e] = cheap_act(acc[i][j][4 * q + e] + bm, act, slope);
         *reinterpret_cast<uint2*>(lds + rl * IG_EPI_PITCH + nl * 2) = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
       }
+  }
+}
+
+// Epilogue of a TM x 128 tile: fp32 partial slices when k is split, else bias + activation and whole pieces of the
+// output rows (PAIR: the two classes of a row interleaved).  `smem` is free (behind a barrier).
+template <bool PAIR, int TM, int FN>
+__device__ __forceinline__ void ig_epilogue(const IgArgs& p, f32x16_t (&acc)[2][FN], unsigned char* smem, int b, int split,
+                                            int m0, int n0, int wm, int col0, const IgClass& cl0, int t, int lane) {
+  constexpr int NT = 256;
+  const int P = 1 << p.lgP;
+  if (p.ksplit > 1) {
+    // ---- split k: this workgroup's fp32 partial tile goes to its slice, indexed like the output;
+    // bias, activation and the conversion happen in ig_split_finish_kernel
+    float* lds_f = reinterpret_cast<float*>(smem);
+    float* ob = p.part + (int64_t)split * p.part_split + (int64_t)b * p.o_model;
+    constexpr int FP = 132;                               // floats per staged row
+#pragma unroll 1
+    for (int pass = 0; pass < TM / 64; ++pass) {
+      const int mp = m0 + 64 * pass;
+      if (wm == pass) {
+        const int ml = lane & 31, nq = (lane >> 5) * 4;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              *reinterpret_cast<float4*>(lds_f + (i * 32 + ml) * FP + col0 + j * 32 + 8 * q + nq) =
+                  make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int id = t; id < 64 * 32; id += NT) {
+        const int rr = id >> 5, pc = id & 31;
+        const int m = mp + rr;
+        if (!PAIR) {
+          const int n = n0 + pc * 4;
+          if (m >= p.M || n >= p.N) continue;
+          const int img = n >> p.lgP, pix = n & (P - 1);
+          *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + pix) =
+              *reinterpret_cast<const float4*>(lds_f + rr * FP + pc * 4);
+        } else {
+          const int n = n0 + pc * 2;                      // 2 pixels x 2 classes = 4 consecutive output elements
+          if (m >= p.M || n >= p.N) continue;
+          const int img = n >> p.lgP, y = (n & (P - 1)) >> p.lgWo, x = n & (p.Wo - 1);
+          const float2 e = *reinterpret_cast<const float2*>(lds_f + rr * FP + pc * 2);
+          const float2 o = *reinterpret_cast<const float2*>(lds_f + rr * FP + 64 + pc * 2);
+          *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + (int64_t)(y * p.oys + cl0.out_y0) * p.OW + x * p.oxs) =
+              make_float4(e.x, o.x, e.y, o.y);
+        }
+      }
+      if (pass + 1 < TM / 64) __syncthreads();
+    }
+    return;
+  }
+
+  // ---- epilogue: bias + activation, 64 rows at a time through an LDS staging tile, then whole
+  // 16-byte pieces of the output rows
+  unsigned char* lds = smem;
+  const bf16_raw* bias = p.bias ? p.bias + (int64_t)b * p.M : nullptr;
+  bf16_raw* ob = p.Out + (int64_t)b * p.o_model;
+#pragma unroll 1
+  for (int pass = 0; pass < TM / 64; ++pass) {
+    const int mp = m0 + 64 * pass;
+    if (wm == pass) ig_stage64<FN>(acc, lds, p.M, mp, bias, p.act, p.slope, lane, col0);
+    __syncthreads();
+    if (!PAIR) {
+      // 8 consecutive columns = 8 consecutive pixels of one sample: one 16-byte piece
+#pragma unroll
+      for (int id = t; id < 64 * 16; id += NT) {
+        const int rr = id >> 4, pc = id & 15;
+        const int m = mp + rr, n = n0 + pc * 8;
+        if (m >= p.M || n >= p.N) continue;
+        const int img = n >> p.lgP, pix = n & (P - 1);
+        *reinterpret_cast<uint4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + pix) =
+            *reinterpret_cast<const uint4*>(lds + rr * IG_EPI_PITCH + pc * 16);
+      }
+    } else {
+      // 4 consecutive pixels x 2 classes = 8 consecutive output elements
+#pragma unroll
+      for (int id = t; id < 64 * 16; id += NT) {
+        const int rr = id >> 4, pc = id & 15;
+        const int m = mp + rr, n = n0 + pc * 4;
+        if (m >= p.M || n >= p.N) continue;
+        const int img = n >> p.lgP, y = (n & (P - 1)) >> p.lgWo, x = n & (p.Wo - 1);
+        const uint2 e = *reinterpret_cast<const uint2*>(lds + rr * IG_EPI_PITCH + pc * 8);          // px = 0
+        const uint2 o = *reinterpret_cast<const uint2*>(lds + rr * IG_EPI_PITCH + 128 + pc * 8);    // px = 1
+        const uint4 v = make_uint4((e.x & 0xffffu) | (o.x << 16), (e.x >> 16) | (o.x & 0xffff0000u),
+                                   (e.y & 0xffffu) | (o.y << 16), (e.y >> 16) | (o.y & 0xffff0000u));
+        *reinterpret_cast<uint4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + (int64_t)(y * p.oys + cl0.out_y0) * p.OW + x * p.oxs) = v;
+      }
+    }
+    if (pass + 1 < TM / 64) __syncthreads();
   }
 }
 
@@ -341,90 +435,7 @@ __global__ __launch_bounds__(256) void conv_ig_fwd_kernel(IgArgs p) {
     __syncthreads();
   }
 
-  if (p.ksplit > 1) {
-    // ---- split k: this workgroup's fp32 partial tile goes to its slice, indexed like the output;
-    // bias, activation and the conversion happen in ig_split_finish_kernel
-    float* lds_f = reinterpret_cast<float*>(smem);
-    float* ob = p.part + (int64_t)split * p.part_split + (int64_t)b * p.o_model;
-    constexpr int FP = 132;                               // floats per staged row
-#pragma unroll 1
-    for (int pass = 0; pass < TM / 64; ++pass) {
-      const int mp = m0 + 64 * pass;
-      if (wm == pass) {
-        const int ml = lane & 31, nq = (lane >> 5) * 4;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              *reinterpret_cast<float4*>(lds_f + (i * 32 + ml) * FP + col0 + j * 32 + 8 * q + nq) =
-                  make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int id = t; id < 64 * 32; id += NT) {
-        const int rr = id >> 5, pc = id & 31;
-        const int m = mp + rr;
-        if (!PAIR) {
-          const int n = n0 + pc * 4;
-          if (m >= p.M || n >= p.N) continue;
-          const int img = n >> p.lgP, pix = n & (P - 1);
-          *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + pix) =
-              *reinterpret_cast<const float4*>(lds_f + rr * FP + pc * 4);
-        } else {
-          const int n = n0 + pc * 2;                      // 2 pixels x 2 classes = 4 consecutive output elements
-          if (m >= p.M || n >= p.N) continue;
-          const int img = n >> p.lgP, y = (n & (P - 1)) >> p.lgWo, x = n & (p.Wo - 1);
-          const float2 e = *reinterpret_cast<const float2*>(lds_f + rr * FP + pc * 2);
-          const float2 o = *reinterpret_cast<const float2*>(lds_f + rr * FP + 64 + pc * 2);
-          *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + (int64_t)(y * p.oys + cl0.out_y0) * p.OW + x * p.oxs) =
-              make_float4(e.x, o.x, e.y, o.y);
-        }
-      }
-      if (pass + 1 < TM / 64) __syncthreads();
-    }
-    return;
-  }
-
-  // ---- epilogue: bias + activation, 64 rows at a time through an LDS staging tile, then whole
-  // 16-byte pieces of the output rows
-  unsigned char* lds = smem;
-  const bf16_raw* bias = p.bias ? p.bias + (int64_t)b * p.M : nullptr;
-  bf16_raw* ob = p.Out + (int64_t)b * p.o_model;
-#pragma unroll 1
-  for (int pass = 0; pass < TM / 64; ++pass) {
-    const int mp = m0 + 64 * pass;
-    if (wm == pass) ig_stage64<FN>(acc, lds, p.M, mp, bias, p.act, p.slope, lane, col0);
-    __syncthreads();
-    if (!PAIR) {
-      // 8 consecutive columns = 8 consecutive pixels of one sample: one 16-byte piece
-#pragma unroll
-      for (int id = t; id < 64 * 16; id += NT) {
-        const int rr = id >> 4, pc = id & 15;
-        const int m = mp + rr, n = n0 + pc * 8;
-        if (m >= p.M || n >= p.N) continue;
-        const int img = n >> p.lgP, pix = n & (P - 1);
-        *reinterpret_cast<uint4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + pix) =
-            *reinterpret_cast<const uint4*>(lds + rr * IG_EPI_PITCH + pc * 16);
-      }
-    } else {
-      // 4 consecutive pixels x 2 classes = 8 consecutive output elements
-#pragma unroll
-      for (int id = t; id < 64 * 16; id += NT) {
-        const int rr = id >> 4, pc = id & 15;
-        const int m = mp + rr, n = n0 + pc * 4;
-        if (m >= p.M || n >= p.N) continue;
-        const int img = n >> p.lgP, y = (n & (P - 1)) >> p.lgWo, x = n & (p.Wo - 1);
-        const uint2 e = *reinterpret_cast<const uint2*>(lds + rr * IG_EPI_PITCH + pc * 8);          // px = 0
-        const uint2 o = *reinterpret_cast<const uint2*>(lds + rr * IG_EPI_PITCH + 128 + pc * 8);    // px = 1
-        const uint4 v = make_uint4((e.x & 0xffffu) | (o.x << 16), (e.x >> 16) | (o.x & 0xffff0000u),
-                                   (e.y & 0xffffu) | (o.y << 16), (e.y >> 16) | (o.y & 0xffff0000u));
-        *reinterpret_cast<uint4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + (int64_t)(y * p.oys + cl0.out_y0) * p.OW + x * p.oxs) = v;
-      }
-    }
-    if (pass + 1 < TM / 64) __syncthreads();
-  }
+  ig_epilogue<PAIR, TM, FN>(p, acc, smem, b, split, m0, n0, wm, col0, cl0, t, lane);
 }
 
 int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
@@ -703,7 +714,8 @@ __global__ __launch_bounds__(256) void ig_split_finish_kernel(const float* __res
 // workgroup and the reduction is long (the 8x8 layers: 320 tiles, 128 k-tiles: 101 -> 90 us).  With
 // 640 tiles and more, and for the class-pair data gradient, the split measured no gain or a loss.
 int ig_pick_ksplit(int64_t blocks, int ktiles, bool pair) {
-  if (pair || blocks >= 384 || ktiles < 64) return 1;
+  if (pair) return 1;
+  if (blocks >= 384 || ktiles < 64) return 1;
   return ktiles >= 128 ? 4 : 2;
 }
 
@@ -711,12 +723,15 @@ __global__ __launch_bounds__(256) void ig_split_reduce_kernel(const float4* __re
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= count4) return;
   float4 s = partial[i];
+#pragma unroll 8                          // a thread walks up to 64 slices: eight loads in flight, summed in order
   for (int k = 1; k < splits; ++k) {
     const float4 v = partial[(int64_t)k * count4 + i];
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
   out[i] = s;
 }
+
+#include "conv2d_planes.h"
 
 constexpr size_t IG_MAX_LDS = 96 * 1024;
 
@@ -857,10 +872,22 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   a.kt_per_split = (ktiles + a.ksplit - 1) / a.ksplit;
   a.part = reinterpret_cast<float*>(split_ws);
   a.part_split = (int64_t)Nb * a.o_img;
-  const size_t lds2 = ig_lds_bytes(a, 8, 0);
-  if (lds2 > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   dim3 grid((unsigned)(tiles_m * a.tiles_n), (unsigned)(2 * a.ksplit), (unsigned)B);
-  if (a.chunk_el == 8) {
+  const bool planes = dxp_geometry(a) && dxp_lds_bytes(a) <= IG_MAX_LDS;
+  const size_t lds2 = planes ? dxp_lds_bytes(a) : ig_lds_bytes(a, 8, 0);
+  if (lds2 > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
+  if (planes) {
+    const int kt = (Co + DXP_CH - 1) / DXP_CH;
+    a.kt_per_split = (kt + a.ksplit - 1) / a.ksplit;
+    const bool few = (int64_t)tiles_m * a.tiles_n * 2 * B < 256;
+    if (a.W == 4) {
+      if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, true, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<64, true, 1>, grid, 256, lds2, st, a);
+      else few ? ig_launch(conv_dx_planes_kernel<128, true, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<128, true, 1>, grid, 256, lds2, st, a);
+    } else {
+      if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<64, false, 1>, grid, 256, lds2, st, a);
+      else few ? ig_launch(conv_dx_planes_kernel<128, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds2, st, a);
+    }
+  } else if (a.chunk_el == 8) {
     if (tm == 64) ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 64, true>, grid, 256, lds2, st, a);
     else ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 128, true>, grid, 256, lds2, st, a);
   } else {
