@@ -56,6 +56,10 @@ struct GemmDesc {
   // when the kernel that writes them was launched (otherwise nothing touched stat_part).
   float* stat_part;
   bool* stat_done;
+  // Sums over k of B's columns, [G0][N] floats (the bias gradient that goes with a weight gradient), taken by kernels
+  // that hold B's tiles anyway; *bsum_done is set when the kernel launched writes them (otherwise nothing does).
+  float* bsum;
+  bool* bsum_done;
 };
 
 struct GemmArgs {
@@ -78,6 +82,7 @@ struct GemmArgs {
   int c_seg;
   int64_t c_seg_stride;
   float* stat_part;              // see GemmDesc
+  float* bsum;                   // see GemmDesc
 };
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;

@@ -129,6 +129,8 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   a.c_seg = d.c_seg; a.c_seg_stride = d.c_seg_stride;
   a.stat_part = d.stat_part;
   if (d.stat_done) *d.stat_done = false;
+  a.bsum = nullptr;                    // set by the launchers of kernels that take it
+  if (d.bsum_done) *d.bsum_done = false;
 
   // vector-load eligibility: every address the fast path forms must be aligned
   const int es = (int)dtype_size(d.dtype);

@@ -19,7 +19,7 @@
 // loads, the bias and the stores of neighbouring tiles overlapped; select-kind epilogues), which
 // the launcher takes whenever a launch has more tiles than compute units.
 #pragma once
-#include "gemm_pf.h"
+#include "gemm_dma.h"
 
 namespace hfta {
 
@@ -209,8 +209,9 @@ __device__ __forceinline__ bf16x8_t big_frag(const unsigned char* tile, int base
   return u.v;
 }
 
-// COLB: bias per column n (the fused Linear's), else per row m or none.
-template <bool A_KC, bool B_KC, typename OutT, bool V16, bool COLB, int ACT, bool N16 = false>
+// COLB: bias per column n (the fused Linear's), else per row m or none.  SUMS: the column sums of B besides (an
+// instantiation of its own: under a run-time flag the kernel without them took 154 us for 142).
+template <bool A_KC, bool B_KC, typename OutT, bool V16, bool COLB, int ACT, bool N16 = false, bool SUMS = false>
 __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[BIG_SMEM];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -268,8 +269,13 @@ __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
   ob.store(tileB(0), rb[0], t);
   __syncthreads();
   int buf = 0;
-  const int r = lane & 31, gsel = lane >> 5;
   bool done = false;
+  // column sums of B (GemmDesc::bsum) by the workgroups of the first row tile
+  static_assert(!SUMS || (!A_KC && !B_KC && sizeof(OutT) == 4 && N16), "column sums go with a weight gradient");
+  const bool sums = SUMS && m0 == 0;
+  float cs[SUMS ? 8 : 1];
+#pragma unroll
+  for (int e = 0; e < (SUMS ? 8 : 1); ++e) cs[e] = 0.f;
   for (int base = t_begin; !done; base += BIG_PF) {
 #pragma unroll
     for (int d = 0; d < BIG_PF; ++d) {
@@ -289,6 +295,9 @@ __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+        if constexpr (SUMS) {              // a quarter of the thread's four k-rows per k-step
+          if (sums) add_bf16x8(cs, *reinterpret_cast<const uint4*>(Bs + ((t >> 5) + 16 * s) * BIG_NPITCH + (t & 31) * 16));
+        }
       }
       if (cur + 1 >= t_end) { done = true; break; }
       oa.store(tileA(buf ^ 1), ra[(d + 1) % BIG_PF], t);
@@ -298,6 +307,12 @@ __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
     }
   }
   __syncthreads();
+  if constexpr (SUMS) {
+    if (sums) {
+      store_colsums<32, 16>(cs, reinterpret_cast<float*>(smem), p.bsum + (int64_t)g0 * p.N, n0, p.N, t);
+      __syncthreads();
+    }
+  }
 
   // epilogue: bias + activation in registers, staged through LDS in the output type in passes of
   // 128 rows (2-byte outputs) / 64 rows (4-byte outputs), then 16- or 8-byte row-major stores.

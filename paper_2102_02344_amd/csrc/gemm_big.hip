@@ -108,8 +108,15 @@ int gemm_big_launch(const GemmDesc& d, const GemmArgs& a0, bool v16, bool n16, d
     if (colb || !sel) return HFTA_EUNSUPPORTED;
     if (d.a_kc && !d.b_kc) launch_big<true, false, float, false, BIG_SEL>(a, n16, grid, st);
     else if (d.a_kc && d.b_kc) launch_big<true, true, float, false, BIG_SEL>(a, n16, grid, st);
-    else if (!d.a_kc && !d.b_kc) launch_big<false, false, float, false, BIG_SEL>(a, n16, grid, st);
-    else return HFTA_EUNSUPPORTED;
+    else if (!d.a_kc && !d.b_kc) {
+      if (n16 && a.splits == 1 && d.bsum && d.bsum_done) {
+        a.bsum = d.bsum;
+        hipLaunchKernelGGL((gemm_big_kernel<false, false, float, true, false, BIG_SEL, true, true>), grid, dim3(BIG_THREADS), 0, st, a);
+        *d.bsum_done = true;
+      } else {
+        launch_big<false, false, float, false, BIG_SEL>(a, n16, grid, st);
+      }
+    } else return HFTA_EUNSUPPORTED;
     return launch_status();
   }
   if (d.a_kc && !d.b_kc) {

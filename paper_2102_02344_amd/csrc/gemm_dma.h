@@ -161,6 +161,30 @@ __device__ __forceinline__ void dma_store_rows(const unsigned char* lds, OutT* C
   }
 }
 
+// Column sums of an operand tile (GemmDesc::bsum): eight bf16 columns onto a thread's fp32 sums, and the sums of the
+// ROWS threads of a column added in order through LDS.
+__device__ __forceinline__ void add_bf16x8(float (&s)[8], const uint4& q) {
+  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s[2 * i] += __uint_as_float(w[i] << 16);
+    s[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
+  }
+}
+template <int PPR, int ROWS>
+__device__ __forceinline__ void store_colsums(const float (&s)[8], float* lds, float* out, int n0, int N, int t) {
+  float* d = lds + (t / PPR) * (PPR * 8) + (t % PPR) * 8;
+  *reinterpret_cast<float4*>(d) = make_float4(s[0], s[1], s[2], s[3]);
+  *reinterpret_cast<float4*>(d + 4) = make_float4(s[4], s[5], s[6], s[7]);
+  __syncthreads();
+  if (t < PPR * 8 && n0 + t < N) {
+    float v = lds[t];
+#pragma unroll 8
+    for (int r = 1; r < ROWS; ++r) v += lds[r * (PPR * 8) + t];
+    out[n0 + t] = v;
+  }
+}
+
 // WM x WN waves, MI x NI matrix-instruction blocks each
 template <int WM, int WN, int MI, int NI, int BK, bool A_KC, bool B_KC, typename OutT, int ST, int OCC>
 __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p) {
@@ -234,6 +258,13 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
 
 #pragma unroll
   for (int d = 0; d < ST - 1; ++d) issue(aim(d), d, 0, PER);
+  // column sums of B, by the workgroups of the first row tile: 8 columns of every (threads / pieces)-th k-row a thread
+  constexpr bool SUMS = !A_KC && !B_KC && sizeof(OutT) == 4;
+  constexpr int SPPR = BN / 8, SROWS = WAVES * 64 / SPPR;
+  const bool sums = SUMS && p.bsum && m0 == 0;
+  float cs[SUMS ? 8 : 1];
+#pragma unroll
+  for (int e = 0; e < (SUMS ? 8 : 1); ++e) cs[e] = 0.f;
   bool done = false;
   for (int base = 0; !done; base += ST) {
 #pragma unroll
@@ -264,10 +295,25 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
           for (int j = 0; j < NI; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[s & 1][j], a[s & 1][i], acc[i][j], 0, 0, 0);
       }
+      if constexpr (SUMS) {
+        if (sums) {
+#pragma unroll
+          for (int r = t / SPPR; r < BK; r += SROWS) {
+            const uint4 q = *reinterpret_cast<const uint4*>(Bs + r * (BN * 2) + (((t % SPPR) ^ OpB::swz(r)) << 4));
+            add_bf16x8(cs, q);
+          }
+        }
+      }
       if (base + d + 1 >= kt) { done = true; break; }
     }
   }
   dma_wait_barrier<0>();                                   // nothing may land in the stages any more
+  if constexpr (SUMS) {
+    if (sums) {
+      store_colsums<SPPR, SROWS>(cs, reinterpret_cast<float*>(smem), p.bsum + (int64_t)g0 * p.N, n0, p.N, t);
+      __syncthreads();
+    }
+  }
 
   OutT* Cb = reinterpret_cast<OutT*>(p.C) + g0 * p.c_g0 + g1 * p.c_g1;
   const bf16_raw* bias = p.bias ? reinterpret_cast<const bf16_raw*>(p.bias) + g0 * p.bias_g0 + g1 * p.bias_g1 : nullptr;

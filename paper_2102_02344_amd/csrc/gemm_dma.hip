@@ -56,7 +56,12 @@ int gemm_dma_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st) {
   if (a.splits != 1) return HFTA_EUNSUPPORTED;
   if (d.a_kc && !d.b_kc) return d.out_f32 ? launch_tile<true, false, float>(d, a, st) : launch_tile<true, false, bf16_raw>(d, a, st);
   if (d.a_kc && d.b_kc) return d.out_f32 ? launch_tile<true, true, float>(d, a, st) : launch_tile<true, true, bf16_raw>(d, a, st);
-  return d.out_f32 ? launch_tile<false, false, float>(d, a, st) : launch_tile<false, false, bf16_raw>(d, a, st);
+  if (!d.out_f32) return launch_tile<false, false, bf16_raw>(d, a, st);
+  GemmArgs s = a;
+  s.bsum = d.bsum;
+  const int rc = launch_tile<false, false, float>(d, s, st);
+  if (rc == HFTA_OK && d.bsum && d.bsum_done) *d.bsum_done = true;
+  return rc;
 }
 
 }  // namespace hfta

@@ -384,11 +384,16 @@ int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype, const void* X, cons
     int rc = gemm_launch(d, st);
     if (rc != HFTA_OK) return rc;
   }
+  bool db_done = false;
   if (dW) {
+    // the weight gradient's kernel adds up dY's columns from the tiles it holds, where it is one that can: against a
+    // pass over dY of its own, 8 x 2048 x 8192 78 + 52 -> 91 us, 8 x 2048 x 1024 21 + 8.8 -> 22.9 us
+    dw.bsum = dbias;
+    dw.bsum_done = &db_done;
     int rc = gemm_launch(dw, st);
     if (rc != HFTA_OK) return rc;
   }
-  if (dbias) {
+  if (dbias && !db_done) {
     dim3 grid((unsigned)((Fy + 63) / 64), (unsigned)B);
     const int epv = 16 / (int)dtype_size(dtype);
     if (Fy % epv == 0 && (reinterpret_cast<uintptr_t>(dY) & 15) == 0 && M >= 64) {
