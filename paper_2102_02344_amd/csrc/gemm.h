@@ -268,6 +268,22 @@ __device__ __forceinline__ float epi_act(float x, int act, float slope) {
   return apply_act(x, act, slope);
 }
 
+// Four neighbouring column biases in one load (at element alignment; the last columns one by one).  One by one for
+// every row block they cost a small problem more than its k-loop: 8 x 2048 x 256, K = 256 25 -> 13 us.
+template <typename BiasT>
+__device__ __forceinline__ void col_bias4(float (&cb)[4], const BiasT* bias, int n, int N) {
+  if (n + 4 <= N) {
+    typedef uint32_t V __attribute__((ext_vector_type(sizeof(BiasT)), aligned(sizeof(BiasT))));
+    const V v = *reinterpret_cast<const V*>(bias + n);
+    const BiasT* e = reinterpret_cast<const BiasT*>(&v);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cb[k] = Elem<BiasT>::to_f32(e[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cb[k] = n + k < N ? Elem<BiasT>::load(bias + n + k) : 0.f;
+  }
+}
+
 // Phase 1 of the epilogue: accumulators (+ bias, activation) -> LDS staging tile in the output
 // type.  `pass` selects the 64-row half for 4-byte outputs (two passes), ignored for 2-byte
 // outputs (all 128 rows at once).  COLB: the bias is per column n (else per row m).  The caller
@@ -281,24 +297,27 @@ __device__ __forceinline__ void stage_pass(f32x16_t (&acc)[2][2], unsigned char*
   const int lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
   const int ml = lane & 31, nq = (lane >> 5) * 4;
   if (RP == 128 || wm == pass) {
+    float bm[2] = {0.f, 0.f};
+    if (!COLB && bias) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int rl = (RP == 128 ? wm * 64 : 0) + i * 32 + ml;
-      const int m = m0 + wm * 64 + i * 32 + ml;
-      float bm = 0.f;
-      if (!COLB && bias && m < M) bm = Elem<BiasT>::load(bias + m);
+      for (int i = 0; i < 2; ++i) {
+        const int m = m0 + wm * 64 + i * 32 + ml;
+        if (m < M) bm[i] = Elem<BiasT>::load(bias + m);
+      }
+    }
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int nl = wn * 64 + j * 32 + 8 * q + nq;
+      for (int q = 0; q < 4; ++q) {
+        const int nl = wn * 64 + j * 32 + 8 * q + nq;
+        float cb[4] = {0.f, 0.f, 0.f, 0.f};
+        if (COLB) col_bias4(cb, bias, n0 + nl, N);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int rl = (RP == 128 ? wm * 64 : 0) + i * 32 + ml;
           float x[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            x[e] = acc[i][j][4 * q + e] + bm;
-            if (COLB && n0 + nl + e < N) x[e] += Elem<BiasT>::load(bias + n0 + nl + e);
-            x[e] = epi_act<KIND>(x[e], act, slope);
-          }
+          for (int e = 0; e < 4; ++e) x[e] = epi_act<KIND>(acc[i][j][4 * q + e] + (COLB ? cb[e] : bm[i]), act, slope);
           unsigned char* dst = lds + rl * PITCH + nl * ES;
           if (ES == 2) {
             uint2 o;
@@ -309,7 +328,7 @@ __device__ __forceinline__ void stage_pass(f32x16_t (&acc)[2][2], unsigned char*
             *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
           }
         }
-    }
+      }
   }
 }
 
@@ -389,7 +408,9 @@ __device__ __forceinline__ void store_tile(f32x16_t (&acc)[2][2], unsigned char*
 #pragma unroll
   for (int pass = 0; pass < 128 / RP; ++pass) {
     if (full) {
-      if (colb) stage_pass<OutT, BiasT, EPI_ANY, true>(acc, lds, pass, M, N, m0, n0, bias, act, slope, t);
+      if (colb && act == HFTA_ACT_NONE) stage_pass<OutT, BiasT, EPI_NONE, true>(acc, lds, pass, M, N, m0, n0, bias, act, slope, t);
+      else if (colb && act == HFTA_ACT_RELU) stage_pass<OutT, BiasT, EPI_RELU, true>(acc, lds, pass, M, N, m0, n0, bias, act, slope, t);
+      else if (colb) stage_pass<OutT, BiasT, EPI_ANY, true>(acc, lds, pass, M, N, m0, n0, bias, act, slope, t);
       else stage_pass<OutT, BiasT, EPI_ANY, false>(acc, lds, pass, M, N, m0, n0, rb, act, slope, t);
     } else {
       stage_acc<OutT, BiasT>(acc, lds, pass, M, m0, rb, act, slope, t);

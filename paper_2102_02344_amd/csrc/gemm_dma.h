@@ -115,11 +115,7 @@ __device__ __forceinline__ void dma_stage(const f32x16_t (&acc)[MI][NI], unsigne
     for (int q = 0; q < 4; ++q) {
       const int nl = c0 + j * 32 + 8 * q + nq;
       float cb[4] = {0.f, 0.f, 0.f, 0.f};
-      if (COLB) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n0 + nl + e < N) cb[e] = bf16_to_f32(bias[n0 + nl + e]);
-      }
+      if (COLB) col_bias4(cb, bias, n0 + nl, N);
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         const int rl = r0 + i * 32 + ml;
@@ -327,6 +323,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
 #define DMA_STAGE(KIND, COLB) dma_stage<MI, NI, BN, OutT, KIND, COLB>(acc, smem, r0, c0, p.M, p.N, mp, n0, bias, p.act, p.slope, lane)
       if (sizeof(OutT) == 2 && (colb || p.act == HFTA_ACT_TANH || p.act == HFTA_ACT_GELU)) {
         if (colb && p.act == HFTA_ACT_NONE) DMA_STAGE(EPI_NONE, true);
+        else if (colb && p.act == HFTA_ACT_RELU) DMA_STAGE(EPI_RELU, true);
         else if (colb) DMA_STAGE(EPI_ANY, true);
         else DMA_STAGE(EPI_ANY, false);
       } else if (p.act == HFTA_ACT_RELU) DMA_STAGE(EPI_RELU, false);
