@@ -5,7 +5,7 @@
 // of the score-sized tensors only P moves: written once forward (the backward's input), read once backward.
 // Rounding is that of the batched form, which stores scores, P, dP and dS: each is rounded to bf16 once.
 // Per layer of 8 models x 32 x 64 tokens, 4 heads of 64: forward 44 -> 11.5 us, backward 61 -> 22 us;
-// 4 x 12 x 250 tokens: 58 -> 23 and 75 -> 46 us.  Bound by latency: a head is 16-row blocks of dependent
+// 4 x 12 x 250 tokens: 58 -> 23 and 75 -> 35 us.  Bound by latency: a head is 16-row blocks of dependent
 // products, reductions and exponentials, two to four wavefronts per SIMD.
 //
 // Matrix instruction 16 x 16 x 32: operands hold row (column) l%16 and k = 8(l/16) + 0..7, the result column l%16
@@ -44,22 +44,23 @@ __device__ __forceinline__ at_bf8 at_pair(uint2 a, uint2 b) {
   u.q = make_uint4(a.x, a.y, b.x, b.y);
   return u.v;
 }
-// rows tok0 .. of a [token][ld] tensor's 64-column slice, N 16-byte pieces per thread (32 N rows), through registers
+// rows tok0 .. of a [token][ld] tensor's 64-column slice, N 16-byte pieces per thread (N NT / 8 rows), through registers
 // into LDS; tokens past S and columns past d: zeros.  All loads are in flight before the first is stored.
-template <int N> struct AtRows {
+template <int N, int NT = 256> struct AtRows {
+  static constexpr int RP = NT / 8;                              // rows per pass
   uint4 v[N];
   __device__ __forceinline__ void load(const bf16_raw* src, int64_t ld, int tok0, int S, int d) {
     const int r = threadIdx.x >> 3, c = threadIdx.x & 7;
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       v[n] = make_uint4(0, 0, 0, 0);
-      if (tok0 + r + 32 * n < S && c * 8 < d) v[n] = *reinterpret_cast<const uint4*>(src + (int64_t)(tok0 + r + 32 * n) * ld + c * 8);
+      if (tok0 + r + RP * n < S && c * 8 < d) v[n] = *reinterpret_cast<const uint4*>(src + (int64_t)(tok0 + r + RP * n) * ld + c * 8);
     }
   }
   __device__ __forceinline__ void store(unsigned char* tile) const {
     const int r = threadIdx.x >> 3, c = threadIdx.x & 7;
 #pragma unroll
-    for (int n = 0; n < N; ++n) *reinterpret_cast<uint4*>(tile + (r + 32 * n) * AT_PITCH + c * 16) = v[n];
+    for (int n = 0; n < N; ++n) *reinterpret_cast<uint4*>(tile + (r + RP * n) * AT_PITCH + c * 16) = v[n];
   }
 };
 typedef uint32_t at_u2 __attribute__((ext_vector_type(2), aligned(2)));    // P rows start at any element
@@ -190,8 +191,11 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_raw* __restric
 // One workgroup per head, 64 queries at a time.  A wavefront takes 16 of them for dP, dS and dQ and leaves its P
 // and dS rows in LDS; after a barrier it takes key blocks wave, wave + 4, ... for dK and dV, which it accumulates in
 // registers over all queries.  P may come from any caller, so no block is skipped as masked.
-template <int NJ>
-__global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restrict__ QKV, const bf16_raw* __restrict__ P,
+// HV = 2: eight wavefronts, two per 16 queries with half the keys each (their halves of sum dP P meet in LDS) and half
+// the columns of dQ.  A head of more than 64 tokens fills a compute unit's LDS, so this is what hides its latencies:
+// 4 x 12 x 250 tokens 46 -> 35 us.
+template <int NJ, int HV>
+__global__ __launch_bounds__(256 * HV) void attn_bwd_kernel(const bf16_raw* __restrict__ QKV, const bf16_raw* __restrict__ P,
                                                        const bf16_raw* __restrict__ dCTX, bf16_raw* __restrict__ dQKV, int S, int E,
                                                        int H, int d, float scale) {
   constexpr int PP = NJ * 32 + 32;                               // bytes per row of the P and dS tiles
@@ -201,35 +205,38 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restric
   __shared__ __attribute__((aligned(16))) unsigned char sc[64 * AT_PITCH];
   __shared__ __attribute__((aligned(16))) unsigned char sp[64 * PP];
   __shared__ __attribute__((aligned(16))) unsigned char ss[64 * PP];
+  __shared__ float sdot[HV][64];
+  constexpr int NT = 256 * HV, HB = NJ / HV;                     // threads; key blocks per wavefront
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, li = lane & 15;
+  const int half = HV == 2 ? wave >> 2 : 0, qrow = (wave & 3) * 16 + li, j0 = half * HB;
   const int bn = blockIdx.x / H, h = blockIdx.x % H;
   const bf16_raw* q = QKV + (int64_t)bn * S * 3 * E + h * d;
   const bf16_raw* dc = dCTX + (int64_t)bn * S * E + h * d;
   bf16_raw* dq = dQKV + (int64_t)bn * S * 3 * E + h * d;
   const int nb = (S + 15) >> 4;
   // the next 64 queries' Q, dCTX and P rows, fetched while the last are multiplied
-  AtRows<2> rq, rc;
-  uint2 pn[NJ];
+  AtRows<2 / HV, NT> rq, rc;
+  uint2 pn[HB];
   auto fetch = [&](int i0) {
     rq.load(q, 3 * E, i0, S, d);
     rc.load(dc, E, i0, S, d);
     // (rows past S take the last row's P: their dCTX rows are zeros, so dP, dS and their part of dV are too)
-    const bf16_raw* prow = P + ((int64_t)blockIdx.x * S + min(i0 + wave * 16 + li, S - 1)) * S;
+    const bf16_raw* prow = P + ((int64_t)blockIdx.x * S + min(i0 + qrow, S - 1)) * S;
 #pragma unroll
-    for (int jb = 0; jb < NJ; ++jb) {
+    for (int jb = 0; jb < HB; ++jb) {
       pn[jb] = make_uint2(0, 0);
-      if (jb < nb) pn[jb] = at_load_p(prow, jb, g, S);
+      if (j0 + jb < nb) pn[jb] = at_load_p(prow, j0 + jb, g, S);
     }
   };
   {
-    AtRows<NJ / 2> k, v;
+    AtRows<NJ / 2 / HV, NT> k, v;
     k.load(q + E, 3 * E, 0, S, d);
     v.load(q + 2 * E, 3 * E, 0, S, d);
     fetch(0);
     k.store(sk);
     v.store(sv);
   }
-  constexpr int NW = NJ / 4;
+  constexpr int NW = NJ / (4 * HV);
   at_f4 dk[NW][4], dv[NW][4];
 #pragma unroll
   for (int n = 0; n < NW; ++n)
@@ -240,24 +247,24 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restric
     __syncthreads();                                             // the last group's tiles have been read
     rq.store(sq);
     rc.store(sc);
-    const int i = i0 + wave * 16 + li;
-    uint2 pk[NJ];
+    const int i = i0 + qrow;
+    uint2 pk[HB];
 #pragma unroll
-    for (int jb = 0; jb < NJ; ++jb) pk[jb] = pn[jb];
+    for (int jb = 0; jb < HB; ++jb) pk[jb] = pn[jb];
     __syncthreads();
     at_bf8 cf[2];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) cf[ks] = at_row_frag(sc, wave * 16, ks, lane);
-    at_f4 dp[NJ];
+    for (int ks = 0; ks < 2; ++ks) cf[ks] = at_row_frag(sc, (wave & 3) * 16, ks, lane);
+    at_f4 dp[HB];
     float dot = 0.f;
-    unsigned char* pt = sp + (wave * 16 + li) * PP + g * 8;
+    unsigned char* pt = sp + qrow * PP + j0 * 32 + g * 8;
 #pragma unroll
-    for (int jb = 0; jb < NJ; ++jb) {
+    for (int jb = 0; jb < HB; ++jb) {
       dp[jb] = at_f4{0.f, 0.f, 0.f, 0.f};
-      if (jb >= nb) continue;
+      if (j0 + jb >= nb) continue;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        dp[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_row_frag(sv, jb * 16, ks, lane), cf[ks], dp[jb], 0, 0, 0);
+        dp[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_row_frag(sv, (j0 + jb) * 16, ks, lane), cf[ks], dp[jb], 0, 0, 0);
       *reinterpret_cast<uint2*>(pt + jb * 32) = pk[jb];
       const float p[4] = {__uint_as_float(pk[jb].x << 16), __uint_as_float(pk[jb].x & 0xffff0000u),
                           __uint_as_float(pk[jb].y << 16), __uint_as_float(pk[jb].y & 0xffff0000u)};
@@ -268,10 +275,15 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restric
       }
     }
     dot = at_row_sum(dot);
-    unsigned char* st = ss + (wave * 16 + li) * PP + g * 8;
+    if (HV == 2) {
+      if (g == 0) sdot[half][qrow] = dot;
+      __syncthreads();
+      dot = sdot[0][qrow] + sdot[HV - 1][qrow];
+    }
+    unsigned char* st = ss + qrow * PP + j0 * 32 + g * 8;
 #pragma unroll
-    for (int jb = 0; jb < NJ; ++jb) {
-      if (jb >= nb) continue;
+    for (int jb = 0; jb < HB; ++jb) {
+      if (j0 + jb >= nb) continue;
       const float p[4] = {__uint_as_float(pk[jb].x << 16), __uint_as_float(pk[jb].x & 0xffff0000u),
                           __uint_as_float(pk[jb].y << 16), __uint_as_float(pk[jb].y & 0xffff0000u)};
       float x[4];
@@ -280,24 +292,35 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restric
       pk[jb] = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));       // dS from here on
       *reinterpret_cast<uint2*>(st + jb * 32) = pk[jb];
     }
-    at_f4 o[4];
+    // dQ: all keys, with HV = 2 from the dS rows in LDS (the other half's among them) and half the columns
+    if (HV == 2) __syncthreads();
+    constexpr int CB = 4 / HV;
+    at_f4 o[CB];
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) o[cb] = at_f4{0.f, 0.f, 0.f, 0.f};
+    for (int cb = 0; cb < CB; ++cb) o[cb] = at_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < NJ / 2; ++t) {
       if (2 * t >= nb) continue;
-      const at_bf8 sf = at_pair(pk[2 * t], pk[2 * t + 1]);
+      at_bf8 sf;
+      if constexpr (HV == 1) {
+        sf = at_pair(pk[2 * t], pk[2 * t + 1]);
+      } else {                                                   // (blocks past the last were never written)
+        const unsigned char* r = ss + qrow * PP + t * 64 + g * 8;
+        sf = at_pair(*reinterpret_cast<const uint2*>(r), 2 * t + 1 < nb ? *reinterpret_cast<const uint2*>(r + 32) : make_uint2(0, 0));
+      }
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-        o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_tr_frag<AT_PITCH>(sk, t * 32, cb * 16, lane), sf, o[cb], 0, 0, 0);
+      for (int cb = 0; cb < CB; ++cb)
+        o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_tr_frag<AT_PITCH>(sk, t * 32, (half * CB + cb) * 16, lane), sf, o[cb], 0, 0, 0);
     }
     if (i < S) {
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-        if (cb * 16 + 4 * g < d) at_store4(dq + (int64_t)i * 3 * E + cb * 16 + 4 * g, o[cb]);
+      for (int cb = 0; cb < CB; ++cb) {
+        const int c = (half * CB + cb) * 16 + 4 * g;
+        if (c < d) at_store4(dq + (int64_t)i * 3 * E + c, o[cb]);
+      }
     }
     if (i0 + 64 < S) fetch(i0 + 64);
-    __syncthreads();
+    if (HV == 1) __syncthreads();
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       if (i0 + 32 * kk >= S) continue;
@@ -309,7 +332,7 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restric
       }
 #pragma unroll
       for (int n = 0; n < NW; ++n) {
-        const int jb = n * 4 + wave;
+        const int jb = n * 4 * HV + wave;
         if (jb >= nb) continue;
         const at_bf8 pf = at_tr_frag<PP>(sp, kk * 32, jb * 16, lane), sf = at_tr_frag<PP>(ss, kk * 32, jb * 16, lane);
 #pragma unroll
@@ -322,7 +345,7 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const bf16_raw* __restric
   }
 #pragma unroll
   for (int n = 0; n < NW; ++n) {
-    const int j = (n * 4 + wave) * 16 + li;
+    const int j = (n * 4 * HV + wave) * 16 + li;
     if (j >= S) continue;
     bf16_raw* row = dq + (int64_t)j * 3 * E + 4 * g;
 #pragma unroll
@@ -360,11 +383,11 @@ int attn_core_fwd(int BN, int S, int E, int H, const void* QKV, void* P, void* C
 int attn_core_bwd(int BN, int S, int E, int H, const void* QKV, const void* P, const void* dCTX, void* dQKV, hipStream_t st) {
   const dim3 grid((unsigned)(BN * H));
   const float scale = 1.f / sqrtf((float)(E / H));
-#define HFTA_ATB(NJ) hipLaunchKernelGGL(attn_bwd_kernel<NJ>, grid, dim3(256), 0, st, (const bf16_raw*)QKV, (const bf16_raw*)P, \
-                                        (const bf16_raw*)dCTX, (bf16_raw*)dQKV, S, E, H, E / H, scale)
-  if (S <= 64) HFTA_ATB(4);
-  else if (S <= 128) HFTA_ATB(8);
-  else HFTA_ATB(16);
+#define HFTA_ATB(NJ, HV) hipLaunchKernelGGL((attn_bwd_kernel<NJ, HV>), grid, dim3(256 * HV), 0, st, (const bf16_raw*)QKV, \
+                                            (const bf16_raw*)P, (const bf16_raw*)dCTX, (bf16_raw*)dQKV, S, E, H, E / H, scale)
+  if (S <= 64) HFTA_ATB(4, 1);
+  else if (S <= 128) HFTA_ATB(8, 2);
+  else HFTA_ATB(16, 2);
 #undef HFTA_ATB
   return launch_status();
 }
