@@ -22,16 +22,24 @@ using namespace hfta;
 namespace {
 
 // ------------------------------------------------------------------ embedding
+constexpr int EMB_ROWS = 2;
 template <typename T>
 __global__ __launch_bounds__(256) void embedding_fwd_kernel(const T* __restrict__ table, const int32_t* __restrict__ idx,
                                                             const float* __restrict__ pos, T* __restrict__ out, int R,
                                                             int V, int E, int S, float scale) {
-  const int r = blockIdx.x, b = blockIdx.y;
-  const int v = min(max(idx[(int64_t)b * R + r], 0), V - 1);
-  const T* row = table + ((int64_t)b * V + v) * E;
-  T* o = out + ((int64_t)b * R + r) * E;
-  const float* pr = pos ? pos + (int64_t)(r % S) * E : nullptr;
-  for (int e = threadIdx.x; e < E; e += 256) Elem<T>::store(o + e, fmaf(scale, Elem<T>::load(row + e), pr ? pr[e] : 0.f));
+  // a wavefront per EMB_ROWS rows, a row's columns 64 at a time with four loads in flight; a workgroup per row of 256
+  // columns was 16384 workgroups of one element per thread: 8 x 2048 tokens 14.7 -> 9.3 us
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
+  for (int k = 0; k < EMB_ROWS; ++k) {
+    const int r = (blockIdx.x * 4 + (threadIdx.x >> 6)) * EMB_ROWS + k;
+    if (r >= R) return;
+    const int v = min(max(idx[(int64_t)b * R + r], 0), V - 1);
+    const T* row = table + ((int64_t)b * V + v) * E;
+    T* o = out + ((int64_t)b * R + r) * E;
+    const float* pr = pos ? pos + (int64_t)(r % S) * E : nullptr;
+#pragma unroll 4
+    for (int e = lane; e < E; e += 64) Elem<T>::store(o + e, fmaf(scale, Elem<T>::load(row + e), pr ? pr[e] : 0.f));
+  }
 }
 
 __global__ __launch_bounds__(256) void zero_f32_kernel(float* __restrict__ p, int64_t n) {
@@ -272,7 +280,7 @@ int hfta_embedding_fwd(int B, int R, int V, int E, int dtype, const void* table,
                        const float* pos, int S, void* out, void* stream) {
   if (B <= 0 || R <= 0 || V <= 0 || E <= 0 || !valid_dtype(dtype) || !table || !idx || !out || (pos && S <= 0)) return HFTA_EINVAL;
   if (B > 65535) return HFTA_EUNSUPPORTED;
-  dim3 grid((unsigned)R, (unsigned)B);
+  dim3 grid((unsigned)((R + 4 * EMB_ROWS - 1) / (4 * EMB_ROWS)), (unsigned)B);
   hipStream_t st = as_stream(stream);
   if (dtype == HFTA_BF16)
     hipLaunchKernelGGL(embedding_fwd_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)table, idx, pos, (bf16_raw*)out,
