@@ -47,18 +47,23 @@ def _bn_bwd_one_pass(B, Nb, ci, co, L, dt):
 
 class _Views:
     """Views of an object's own buffers, made once each: slicing a tensor costs as much host time as
-    marshalling a library call, and a step takes over a hundred of them."""
+    marshalling a library call, and a step takes over a hundred of them.  A view is made again when another
+    tensor took the buffer's place, and when the buffer itself was given other memory (``.data = ``, ``set_``)."""
 
     def _cut(self, buf: torch.Tensor, n: int) -> torch.Tensor:
         """``buf[:n]``."""
-        return self._view((id(buf), n), buf, lambda: buf[:n])
+        return self._view((id(buf), n), buf, buf.__getitem__, slice(n))
 
-    def _view(self, key, buf: torch.Tensor, make):
-        cache = self.__dict__.setdefault("_view_cache", {})
+    def _view(self, key, buf: torch.Tensor, make, *args):
+        try:
+            cache = self._view_cache
+        except AttributeError:
+            cache = self._view_cache = {}
         hit = cache.get(key)
-        if hit is None or hit[0] is not buf:                 # also when another tensor took the buffer's place
-            hit = cache[key] = (buf, make())
-        return hit[1]
+        at = buf.data_ptr()
+        if hit is None or hit[0] is not buf or hit[1] != at:
+            hit = cache[key] = (buf, at, make(*args))
+        return hit[2]
 
 
 class ParamArena(_Views):
@@ -125,7 +130,7 @@ class ParamArena(_Views):
         return self._segment("grad", self.grad, name)
 
     def _segment(self, kind: str, buf: torch.Tensor, name: str) -> torch.Tensor:
-        return self._view((kind, name), buf, lambda: self._seg(buf, name))
+        return self._view((kind, name), buf, self._seg, buf, name)
 
     def param_host(self, buf: torch.Tensor, name: str, b: int) -> np.ndarray:
         shp = dict(self.shapes)[name]
