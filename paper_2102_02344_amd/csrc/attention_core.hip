@@ -151,7 +151,9 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_raw* __restric
       if (jb >= nbl) continue;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        s[jb][v] = __expf(s[jb][v] - mx);                        // masked entries: exp(-inf)
+        // masked entries: exp(-inf).  (The native exponential loses a bit per doubling of its argument; it took
+        // 21.2 us where this takes 22.8, 4 x 12 x 250 tokens.)
+        s[jb][v] = expf(s[jb][v] - mx);
         se += s[jb][v];
       }
     }
