@@ -438,7 +438,8 @@ int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype,
  * to the Gram matrix of X, a Ci -> Ci product with the spikes added in, and gathers at the argmax.
  *
  * Rows with L % 4 != 0: V is formed from z at the maximum rounded to bf16 (the values of the chain of
- * stored operators); other rows normalise the fp32 product.  zhit is the fp32 product either way.
+ * stored operators), and the backward decides the activation's side from zhit rounded likewise; other rows
+ * use the fp32 product.  zhit is the fp32 product either way.
  * EUNSUPPORTED unless bf16, Ci <= 128, Ci % 8 == 0, Co <= 1024, 4 <= L < 2^21, and rows of X and dX
  * that do not overlap (stride_c >= L); rows may have any alignment.  EWORKSPACE below the needed
  * size (workspace 256-byte aligned).  hfta_conv1x1_bn_maxpool_workspace_bytes is that size for either

@@ -53,6 +53,9 @@ struct CbpArgs {
   uint32_t x_extent, g_extent;
 };
 
+// the z whose normalised value is pooled (see fbp_finish_kernel)
+__device__ __forceinline__ float pooled_z(float z, int L) { return L & 3 ? bf16_to_f32(f32_to_bf16(z)) : z; }
+
 // ---- per channel: dbeta, dgamma from the Nb argmax elements; coefficients ----------------
 __global__ __launch_bounds__(64) void cbp_coef_kernel(CbpArgs p) {
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.Co + c;
@@ -64,7 +67,9 @@ __global__ __launch_bounds__(64) void cbp_coef_kernel(CbpArgs p) {
     const float z = p.zhit ? p.zhit[((int64_t)b * p.Nb + n) * p.Co + c]
                            : bf16_to_f32(p.Z[b * p.zsb + n * p.zsn + c * p.zsc + hit]);
     const float xh = (z - mean) * invstd;
-    const float gr = bf16_to_f32(p.dV[b * p.vsb + n * p.vsn + c * p.vsc]) * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+    // the activation's side is the pooled value's
+    const float pre = fmaf(g, p.zhit ? (pooled_z(z, p.L) - mean) * invstd : xh, bt);
+    const float gr = bf16_to_f32(p.dV[b * p.vsb + n * p.vsn + c * p.vsc]) * act_grad(pre, p.act, p.slope);
     s1 += gr;
     s2 = fmaf(gr, xh, s2);
     p.s[((int64_t)b * p.Nb + n) * p.Co + c] = gr;          // scaled by a below
@@ -964,6 +969,7 @@ __global__ __launch_bounds__(128) void fbp_stats_kernel(FbpArgs p) {
 // stored operators (rounding keeps the order, so the rounded maximum is the maximum of the rounded values).
 // That chain is what such rows ran through before this operator took them; a fully connected head behind the
 // pool normalises small differences between clouds, and a value one step off there is a percent two layers on.
+// zhit keeps the fp32 product; the backward's mask is that of the value pooled here (pooled_z in both).
 __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   const int c = blockIdx.x * 256 + threadIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (c >= p.Co) return;
@@ -981,8 +987,7 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   const float bias = p.bias ? bf16_to_f32(p.bias[k]) : 0.f;
   const float scale = g * p.save_invstd[k], mean = p.save_mean[k], beta = p.beta[k];
   float z = (g < 0.f ? -best : best) + bias;
-  const bool round_z = p.L & 3;
-  float pre = fmaf(scale, (round_z ? bf16_to_f32(f32_to_bf16(z)) : z) - mean, beta);
+  float pre = fmaf(scale, pooled_z(z, p.L) - mean, beta);
   // Equal activated values: the maximum is taken over act(BatchNorm(z)), so where the activation
   // is flat (ReLU, or LeakyReLU with slope 0, at a maximum that is not positive) or the channel's
   // scale is zero, every point of the row holds the same value and the lowest index, 0, is the
@@ -999,7 +1004,7 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
     }
     at = 0;
     z = acc + bias;
-    pre = fmaf(scale, (round_z ? bf16_to_f32(f32_to_bf16(z)) : z) - mean, beta);
+    pre = fmaf(scale, pooled_z(z, p.L) - mean, beta);
     if ((p.act == HFTA_ACT_RELU || (p.act == HFTA_ACT_LEAKY && p.slope == 0.f)) && pre > 0.f) pre = 0.f;   // the row's maximum was not positive
   }
   const float y = apply_act(pre, p.act, p.slope);

@@ -9,6 +9,7 @@ import torch
 import hfta_inputs as hi
 import test_gpu_ops as ops
 import test_gpu_pointnet as pn
+from util import conv_strides, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -145,3 +146,38 @@ def test_matrix_products_linear(hb, dtype, B, M, Fx, Fy):
 @pytest.mark.parametrize("B,Nb,Ci,Co,L", [(2, 2, 264, 136, 131), (2, 3, 70, 150, 257), (2, 2, 5, 12, 6), (2, 2, 130, 520, 1023)])
 def test_matrix_products_conv(hb, dtype, B, Nb, Ci, Co, L):
     ops.test_conv1x1_fwd_bwd(hb, dtype, B, Nb, Ci, Co, L)
+
+
+@pytest.mark.parametrize("L", [131, 130, 132])
+def test_tail_backward_masks_what_the_forward_pooled(hb, L):
+    """A maximum whose fp32 value and bf16 rounding lie on different sides of the ReLU's kink (beta puts the kink
+    halfway between them; half the distance is at least 2^-13 of z, far above fp32's rounding of beta): whichever of the
+    two the forward pools, the backward has to see the same one, so a channel has a gradient exactly where V > 0."""
+    B, Nb, Ci, Co = 2, 1, 16, 1024
+    x = hi.normal(711, (Nb, B * Ci, L), "bf16")
+    w = hi.snap(hi.normal(712, (B, Co, Ci)) * 0.3, "bf16")
+    X, W = dev(x, "bf16"), dev(w, "bf16")
+    xs, vs = conv_strides(B, Ci, L), (Nb * Co, Co, 1)
+    f32 = lambda *s: torch.zeros(s, device="cuda")
+    gamma, beta, mean, invstd = f32(B, Co) + 1.0, f32(B, Co), f32(B, Co), f32(B, Co)
+    V, idx, zhit = torch.empty(B, Nb, Co, dtype=torch.bfloat16, device="cuda"), f32(B, Nb, Co).int(), f32(B, Nb, Co)
+    mom = f32(hb.conv1x1_bn_maxpool_saved_floats(B, Ci, Co))
+    ws = torch.empty(hb.conv1x1_bn_maxpool_workspace_bytes(B, Nb, Ci, Co, L, 1), dtype=torch.uint8, device="cuda")
+    fwd = lambda: hb.conv1x1_bn_maxpool_fwd(B, Nb, Ci, Co, L, 1, X, xs, W, None, gamma, beta, 1e-5, 0.1, None, None, mean, invstd,
+                                            V, idx, vs, zhit, mom, hb.ACT_RELU, 0.0, ws)
+    fwd()
+    z = torch.from_numpy(np.einsum("boc,bcl->bol", w.astype(np.float64), x.astype(np.float64).reshape(B, Ci, L)).max(-1))
+    zr = z.bfloat16().double()
+    kink = (z + zr) / 2
+    m, i = mean.cpu().double(), invstd.cpu().double()
+    beta.copy_((-(i * (kink - m))).float())
+    fwd()
+    dV, dX = torch.ones_like(V), torch.empty_like(X)
+    dW, dg, db = f32(B, Co, Ci), f32(B, Co), f32(B, Co)
+    hb.conv1x1_bn_maxpool_bwd(B, Nb, Ci, Co, L, 1, X, xs, W, None, None, None, zhit, mom, dV, idx, vs, gamma, beta, mean, invstd,
+                              dX, xs, dW, None, dg, db, hb.ACT_RELU, 0.0, ws)
+    sharp = (z - zr).abs() > 2.0 ** -12 * z.abs()
+    assert int((sharp & (zr > z)).sum()) > 100 and int((sharp & (zr < z)).sum()) > 100
+    pooled, seen = V.cpu()[:, 0] > 0, db.cpu() != 0
+    assert torch.equal(pooled[sharp], seen[sharp])
+    assert torch.equal(pooled[sharp], ((zr if L % 4 else z) > kink)[sharp])
