@@ -440,9 +440,9 @@ int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype,
  * Rows with L % 4 != 0: V is formed from z at the maximum rounded to bf16 (the values of the chain of
  * stored operators), and the backward decides the activation's side from zhit rounded likewise; other rows
  * use the fp32 product.  zhit is the fp32 product either way.
- * EUNSUPPORTED unless bf16, Ci <= 128, Ci % 8 == 0, Co <= 1024, 4 <= L < 2^21, and rows of X and dX
- * that do not overlap (stride_c >= L); rows may have any alignment.  EWORKSPACE below the needed
- * size (workspace 256-byte aligned).  hfta_conv1x1_bn_maxpool_workspace_bytes is that size for either
+ * EUNSUPPORTED unless bf16, Ci <= 128, Ci % 8 == 0, Co <= 1024, 4 <= L < 2^21 and stride_c of X positive,
+ * and for L % 4 != 0 unless stride_c >= L in X and dX (rows of X, which is only read, may overlap otherwise);
+ * rows may have any alignment.  EWORKSPACE below the needed size (workspace 256-byte aligned).  hfta_conv1x1_bn_maxpool_workspace_bytes is that size for either
  * direction and every supported shape (0: unsupported); the per-direction queries answer for
  * L % 4 == 0 and return 0 for other L.
  * ---------------------------------------------------------------------- */

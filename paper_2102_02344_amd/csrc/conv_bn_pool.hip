@@ -1083,7 +1083,8 @@ static int cbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
   if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || act == HFTA_ACT_LEAKY)) return HFTA_EUNSUPPORTED;
   if (!cbp_supported(B, Nb, Ci, Co, L, dtype) || xs[3] != 1 || (Z && zs[3] != 1) || dxs[3] != 1) return HFTA_EUNSUPPORTED;
   auto al = [](const void* q, size_t a) { return (reinterpret_cast<uintptr_t>(q) % a) == 0; };
-  if (xs[2] < L || dxs[2] < L || !al(W, 4)) return HFTA_EUNSUPPORTED;   // rows must not overlap
+  if (xs[2] <= 0 || !al(W, 4)) return HFTA_EUNSUPPORTED;
+  if (L % 4 != 0 && (xs[2] < L || dxs[2] < L)) return HFTA_EUNSUPPORTED;   // such rows: whole or with gaps behind them
   const int64_t x_ext = ((int64_t)(Ci - 1) * xs[2] + L) * 2;
   if (x_ext >= (int64_t)1 << 31) return HFTA_EUNSUPPORTED;
   const CbpLayout lay = cbp_layout(B, Nb, Ci, Co, L);
@@ -1166,7 +1167,7 @@ static int fbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
   if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || (act == HFTA_ACT_LEAKY && act_slope >= 0.f))) return HFTA_EUNSUPPORTED;
   if (!cbp_supported(B, Nb, Ci, Co, L, dtype) || xs[3] != 1) return HFTA_EUNSUPPORTED;
   auto al = [](const void* q, size_t a) { return (reinterpret_cast<uintptr_t>(q) % a) == 0; };
-  if (xs[2] < L || !al(W, 16)) return HFTA_EUNSUPPORTED;   // rows must not overlap
+  if (xs[2] <= 0 || (L % 4 != 0 && xs[2] < L) || !al(W, 16)) return HFTA_EUNSUPPORTED;
   const int64_t x_ext = ((int64_t)(Ci - 1) * xs[2] + L) * 2, w_ext = (int64_t)Co * Ci * 2;
   if (x_ext >= (int64_t)1 << 31 || w_ext >= (int64_t)1 << 31) return HFTA_EUNSUPPORTED;
   const int64_t xa_ext = Xact ? ((int64_t)(Ci - 1) * xas[2] + L) * 2 : 0;

@@ -181,3 +181,43 @@ def test_tail_backward_masks_what_the_forward_pooled(hb, L):
     pooled, seen = V.cpu()[:, 0] > 0, db.cpu() != 0
     assert torch.equal(pooled[sharp], seen[sharp])
     assert torch.equal(pooled[sharp], ((zr if L % 4 else z) > kink)[sharp])
+
+
+@pytest.mark.parametrize("L", [132, 131])
+def test_tail_row_strides(hb, L):
+    """Input rows that overlap (each channel the one before it four points on), rows with a gap behind them, and a data
+    gradient whose channels run backwards: the same bits as from a contiguous copy; with L % 4 != 0 only the gap."""
+    B, Nb, Ci, Co = 2, 2, 16, 72
+    W = dev(hi.snap(hi.normal(722, (B, Co, Ci)) * 0.3, "bf16"), "bf16")
+    dV = dev(hi.normal(723, (B, Nb, Co), "bf16"), "bf16")
+    base = dev(hi.normal(721, (2 * B * Nb * Ci * (L + 5),), "bf16"), "bf16")
+    f32 = lambda *s: torch.zeros(s, device="cuda")
+    gamma, beta, vs = f32(B, Co) + 1.0, f32(B, Co) + 0.1, (Nb * Co, Co, 1)
+    ws = torch.empty(hb.conv1x1_bn_maxpool_workspace_bytes(B, Nb, Ci, Co, L, 1), dtype=torch.uint8, device="cuda")
+
+    def run(X, xs, dx_buf, dx0, dxs):
+        mean, invstd, zhit, dW, dg, db = f32(B, Co), f32(B, Co), f32(B, Nb, Co), f32(B, Co, Ci), f32(B, Co), f32(B, Co)
+        V, idx = torch.empty(B, Nb, Co, dtype=torch.bfloat16, device="cuda"), f32(B, Nb, Co).int()
+        mom = f32(hb.conv1x1_bn_maxpool_saved_floats(B, Ci, Co))
+        hb.conv1x1_bn_maxpool_fwd(B, Nb, Ci, Co, L, 1, X, xs, W, None, gamma, beta, 1e-5, 0.1, None, None, mean, invstd, V, idx, vs,
+                                  zhit, mom, hb.ACT_RELU, 0.0, ws)
+        hb.conv1x1_bn_maxpool_bwd(B, Nb, Ci, Co, L, 1, X, xs, W, None, None, None, zhit, mom, dV, idx, vs, gamma, beta, mean, invstd,
+                                  dx_buf[dx0:], dxs, dW, None, dg, db, hb.ACT_RELU, 0.0, ws)
+        return V, idx, mean, invstd, dW, dg, db
+
+    plain = conv_strides(B, Ci, L)
+    whole = L % 4 == 0
+    for sc in (4, L + 5):
+        if sc < L and not whole:
+            with pytest.raises(hb.HftaError):
+                run(base, (Ci * (L + 5), B * Ci * (L + 5), sc, 1), base, 0, plain)
+            continue
+        xs = (Ci * (L + 5), B * Ci * (L + 5), sc, 1)
+        rows = base.as_strided((Nb, B, Ci, L), (xs[1], xs[0], sc, 1))
+        dx0 = torch.full((Nb, B, Ci, L), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ref = run(rows.contiguous(), plain, dx0.view(-1), 0, plain)
+        dx1 = torch.full_like(dx0, float("nan"))
+        got = run(base, xs, dx1.view(-1), (Ci - 1) * L if whole else 0, (plain[0], plain[1], -L if whole else L, 1))
+        for a, c in zip(ref, got):
+            assert torch.equal(a, c)
+        assert bool(torch.isfinite(dx0).all()) and torch.equal(dx0, dx1.flip(2) if whole else dx1)
