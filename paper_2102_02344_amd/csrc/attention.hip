@@ -22,13 +22,14 @@ using namespace hfta;
 namespace {
 
 // ------------------------------------------------------------------ embedding
-constexpr int EMB_ROWS = 2;
+// A wavefront per EMB_ROWS rows, four loads in flight: a workgroup per row of 256 columns was 16384 workgroups of one
+// element per thread (8 x 2048 tokens 14.7 -> 9.3 us).  Where that leaves fewer than two workgroups per compute unit the
+// columns are dealt over workgroups too, EMB_COLS at a time (16 rows of 2048 columns 9.7 -> 4.9 us).
+constexpr int EMB_ROWS = 2, EMB_COLS = 256;
 template <typename T>
 __global__ __launch_bounds__(256) void embedding_fwd_kernel(const T* __restrict__ table, const int32_t* __restrict__ idx,
                                                             const float* __restrict__ pos, T* __restrict__ out, int R,
-                                                            int V, int E, int S, float scale) {
-  // a wavefront per EMB_ROWS rows, a row's columns 64 at a time with four loads in flight; a workgroup per row of 256
-  // columns was 16384 workgroups of one element per thread: 8 x 2048 tokens 14.7 -> 9.3 us
+                                                            int V, int E, int S, int cols, float scale) {
   const int b = blockIdx.y, lane = threadIdx.x & 63;
   for (int k = 0; k < EMB_ROWS; ++k) {
     const int r = (blockIdx.x * 4 + (threadIdx.x >> 6)) * EMB_ROWS + k;
@@ -37,8 +38,9 @@ __global__ __launch_bounds__(256) void embedding_fwd_kernel(const T* __restrict_
     const T* row = table + ((int64_t)b * V + v) * E;
     T* o = out + ((int64_t)b * R + r) * E;
     const float* pr = pos ? pos + (int64_t)(r % S) * E : nullptr;
+    const int c_lo = blockIdx.z * cols, c_hi = min(E, c_lo + cols);
 #pragma unroll 4
-    for (int e = lane; e < E; e += 64) Elem<T>::store(o + e, fmaf(scale, Elem<T>::load(row + e), pr ? pr[e] : 0.f));
+    for (int e = c_lo + lane; e < c_hi; e += 64) Elem<T>::store(o + e, fmaf(scale, Elem<T>::load(row + e), pr ? pr[e] : 0.f));
   }
 }
 
@@ -48,65 +50,122 @@ __global__ __launch_bounds__(256) void zero_f32_kernel(float* __restrict__ p, in
   else for (int64_t k = i; k < n; ++k) p[k] = 0.f;
 }
 
-// A wavefront per token position p, EMB_POS positions one after the other: if p is the first position of its table
-// row, it walks the later ones with the same index in increasing order (ballots over 64 positions) and adds their
-// gradient rows in that order (no atomics, fixed order).  The model's indices are staged once per workgroup for
-// 4 EMB_POS positions; a workgroup per position staged them R times over and met four barriers for one or two
-// rows: 8 x 2048 tokens of 256 columns 40 -> 24 us, 4 x 3000 47 -> 25 us.
-constexpr int EMB_POS = 4;
+// The gradient rows of every position with the same index, added in increasing order (no atomics, fixed order) by
+// whoever holds the index' first position.  The model's indices are staged once per workgroup for 4 EMB_POS positions,
+// a wavefront each in turn (a workgroup per position staged them R times over and met four barriers for one or two
+// rows).  A wavefront searches 512 indices per step, keeps up to EMB_HITS positions in its lanes and has all their rows
+// in flight.  An index met more often (padding, the frequent words of a text) goes to the whole workgroup afterwards: a
+// position list in LDS, a column per thread, EMB_DEEP rows in flight.  Positions are dealt a grid apart, so that the
+// frequent indices, whose first positions come early, fall to different workgroups.
+// 8 x 2048 positions of 256 columns with the clearing of the 67 MB table: uniform indices 49 us as a workgroup per
+// position, 30 here; frequencies of text (1 / rank) 59 and 44; half the positions on one index 126 and 82.
+constexpr int EMB_POS = 4, EMB_HITS = 8, EMB_DEEP = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void embedding_bwd_kernel(const T* __restrict__ dY, const int32_t* __restrict__ idx,
-                                                            float* __restrict__ dtable, int R, int V, int E, float scale) {
-  extern __shared__ int32_t lidx[];                     // the model's R indices
+                                                            float* __restrict__ dtable, int R, int V, int E, int cols, float scale) {
+  extern __shared__ int32_t lidx[];                     // the model's R indices, then the list of matching positions
+  uint16_t* match = reinterpret_cast<uint16_t*>(lidx + R);      // (R < 65536: the host's limit)
+  __shared__ int often[4 * EMB_POS], n_often, wcnt[4];
   const int b = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int c_lo = blockIdx.z * cols, c_hi = min(E, c_lo + cols);
   const int32_t* ib = idx + (int64_t)b * R;
 #pragma unroll 4
   for (int q = t; q < R; q += 256) lidx[q] = min(max(ib[q], 0), V - 1);
+  if (t == 0) n_often = 0;
   __syncthreads();
   const T* dyb = dY + (int64_t)b * R * E;
   for (int k = 0; k < EMB_POS; ++k) {
-    const int p = (blockIdx.x * 4 + wave) * EMB_POS + k;
-    if (p >= R) return;
+    const int p = blockIdx.x + gridDim.x * (4 * k + wave);
+    if (p >= R) break;
     const int v = lidx[p];
     bool found = false;
-    for (int q0 = 0; q0 < p; q0 += 512)
+    for (int q0 = 0; q0 < p && !__any(found); q0 += 512)
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int q = q0 + 64 * u + lane;
         found |= lidx[min(q, R - 1)] == v && q < p;
       }
     if (__any(found)) continue;
-    float* dst = dtable + ((int64_t)b * V + v) * E;
-    for (int eb = 0; eb < E; eb += 256) {                // four columns per lane (every lane stays for the ballots)
-      const int e0 = eb + lane;
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int q0 = p; q0 < R; q0 += 512) {              // eight reads in flight, then the (few) hits in order
-        unsigned long long m[8], any = 0;
+    int n = 0, at = p;                                   // lane h: the h-th position with this index
+    for (int q0 = p; q0 < R && n <= EMB_HITS; q0 += 512) {
+      unsigned long long m[8], any = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int q = q0 + 64 * u + lane;
-          m[u] = __ballot(lidx[min(q, R - 1)] == v && q < R);
-          any |= m[u];
-        }
-        if (!any) continue;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          while (m[u]) {
-            const T* row = dyb + (int64_t)(q0 + 64 * u + __builtin_ctzll(m[u])) * E;
-            m[u] &= m[u] - 1;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-              if (e0 + 64 * c < E) acc[c] += Elem<T>::load(row + e0 + 64 * c);
-          }
+      for (int u = 0; u < 8; ++u) {
+        const int q = q0 + 64 * u + lane;
+        m[u] = __ballot(lidx[min(q, R - 1)] == v && q < R);
+        any |= m[u];
       }
+      if (!any) continue;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        while (m[u] && n <= EMB_HITS) {
+          const int q = q0 + 64 * u + __builtin_ctzll(m[u]);
+          m[u] &= m[u] - 1;
+          if (lane == n) at = q;
+          ++n;
+        }
+    }
+    if (n > EMB_HITS) {
+      if (lane == 0) often[atomicAdd(&n_often, 1)] = p;
+      continue;
+    }
+    float* dst = dtable + ((int64_t)b * V + v) * E;
+    for (int e0 = c_lo + lane; e0 < c_hi; e0 += 256) {   // four columns per lane
+      T x[EMB_HITS][4];
+#pragma unroll
+      for (int h = 0; h < EMB_HITS; ++h)
+        if (h < n) {
+          const T* row = dyb + (int64_t)__builtin_amdgcn_readlane(at, h) * E;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) x[h][c] = row[min(e0 + 64 * c, E - 1)];
+        }
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int h = 0; h < EMB_HITS; ++h)
+        if (h < n) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] += Elem<T>::to_f32(x[h][c]);
+        }
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        if (e0 + 64 * c < E) dst[e0 + 64 * c] = scale * acc[c];
+        if (e0 + 64 * c < c_hi) dst[e0 + 64 * c] = scale * acc[c];
+    }
+  }
+  __syncthreads();
+  for (int i = 0; i < n_often; ++i) {                    // (n_often changes no more: the same for the whole workgroup)
+    const int p = often[i], v = lidx[p];
+    const int len = (R - p + 255) / 256 * 64, q_lo = p + wave * len, q_hi = min(R, q_lo + len);      // a stretch per wavefront
+    int cnt = 0;
+    for (int q0 = q_lo; q0 < q_hi; q0 += 64) cnt += __popcll(__ballot(q0 + lane < q_hi && lidx[min(q0 + lane, R - 1)] == v));
+    if (lane == 0) wcnt[wave] = cnt;
+    __syncthreads();                                     // also: nobody reads the last index' list any more
+    const int total = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+    int base = 0;
+    for (int w = 0; w < wave; ++w) base += wcnt[w];
+    for (int q0 = q_lo; q0 < q_hi; q0 += 64) {
+      const bool hit = q0 + lane < q_hi && lidx[min(q0 + lane, R - 1)] == v;
+      const unsigned long long m = __ballot(hit);
+      if (hit) match[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(q0 + lane);
+      base += __popcll(m);
+    }
+    __syncthreads();
+    float* dst = dtable + ((int64_t)b * V + v) * E;
+    for (int e = c_lo + t; e < c_hi; e += 256) {
+      float acc = 0.f;
+      int h = 0;
+      for (; h + EMB_DEEP <= total; h += EMB_DEEP) {
+        T x[EMB_DEEP];
+#pragma unroll
+        for (int u = 0; u < EMB_DEEP; ++u) x[u] = dyb[(int64_t)match[h + u] * E + e];
+#pragma unroll
+        for (int u = 0; u < EMB_DEEP; ++u) acc += Elem<T>::to_f32(x[u]);
+      }
+      for (; h < total; ++h) acc += Elem<T>::load(dyb + (int64_t)match[h] * E + e);
+      dst[e] = scale * acc;
     }
   }
 }
 
-// ------------------------------------------------------------------ softmax over score rows, in place
 // rows = (batch, head, i); entry j of row i takes part if !causal or j <= i
 template <typename T>
 __global__ __launch_bounds__(256) void softmax_rows_kernel(T* __restrict__ P, int64_t rows, int S, float scale, int causal) {
@@ -260,6 +319,15 @@ __global__ __launch_bounds__(256) void xent_rows_reduce_kernel(const float* __re
   if (threadIdx.x == 0) loss[blockIdx.x] = ((sh[0] + sh[1]) + (sh[2] + sh[3])) / (float)R;
 }
 
+// Columns per workgroup of the embedding kernels: all of a row, or, where that makes fewer than two workgroups per
+// compute unit, whole pieces of EMB_COLS (gradient of 16 positions of 2048 columns 35 -> 11 us, with the clearing).
+int emb_cols(int64_t blocks, int E) {
+  const int pieces = E / EMB_COLS + (E % EMB_COLS != 0);
+  int nz = blocks >= 512 ? 1 : (int)(512 / blocks);
+  if (nz > pieces) nz = pieces;
+  return nz == 1 ? E : (pieces + nz - 1) / nz * EMB_COLS;
+}
+
 GemmDesc head_desc(int B, int N, int H, int dtype) {
   GemmDesc d{};
   d.S = 1; d.G0 = B * N; d.G1 = H;
@@ -280,30 +348,32 @@ int hfta_embedding_fwd(int B, int R, int V, int E, int dtype, const void* table,
                        const float* pos, int S, void* out, void* stream) {
   if (B <= 0 || R <= 0 || V <= 0 || E <= 0 || !valid_dtype(dtype) || !table || !idx || !out || (pos && S <= 0)) return HFTA_EINVAL;
   if (B > 65535) return HFTA_EUNSUPPORTED;
-  dim3 grid((unsigned)((R + 4 * EMB_ROWS - 1) / (4 * EMB_ROWS)), (unsigned)B);
+  const int nblk = R / (4 * EMB_ROWS) + (R % (4 * EMB_ROWS) != 0), cols = emb_cols((int64_t)nblk * B, E);
+  dim3 grid((unsigned)nblk, (unsigned)B, (unsigned)((E + cols - 1) / cols));
   hipStream_t st = as_stream(stream);
   if (dtype == HFTA_BF16)
     hipLaunchKernelGGL(embedding_fwd_kernel<bf16_raw>, grid, dim3(256), 0, st, (const bf16_raw*)table, idx, pos, (bf16_raw*)out,
-                       R, V, E, pos ? S : 1, scale);
+                       R, V, E, pos ? S : 1, cols, scale);
   else
     hipLaunchKernelGGL(embedding_fwd_kernel<float>, grid, dim3(256), 0, st, (const float*)table, idx, pos, (float*)out, R, V, E,
-                       pos ? S : 1, scale);
+                       pos ? S : 1, cols, scale);
   return launch_status();
 }
 
 int hfta_embedding_bwd(int B, int R, int V, int E, int dtype, const void* dY, const int32_t* idx, float scale,
                        float* dtable, void* stream) {
   if (B <= 0 || R <= 0 || V <= 0 || E <= 0 || !valid_dtype(dtype) || !dY || !idx || !dtable) return HFTA_EINVAL;
-  if (B > 65535 || (size_t)R * 8 > 60 * 1024) return HFTA_EUNSUPPORTED;      // the model's indices are staged in LDS
+  if (B > 65535 || (size_t)R * 8 > 60 * 1024) return HFTA_EUNSUPPORTED;      // the model's indices and a match list are staged in LDS
   hipStream_t st = as_stream(stream);
   const int64_t n = (int64_t)B * V * E;
   hipLaunchKernelGGL(zero_f32_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, dtable, n);
-  dim3 grid((unsigned)((R + 4 * EMB_POS - 1) / (4 * EMB_POS)), (unsigned)B);
-  const size_t shm = (size_t)R * 4;
+  const int nblk = (R + 4 * EMB_POS - 1) / (4 * EMB_POS), cols = emb_cols((int64_t)nblk * B, E);
+  dim3 grid((unsigned)nblk, (unsigned)B, (unsigned)((E + cols - 1) / cols));
+  const size_t shm = (size_t)R * 6;
   if (dtype == HFTA_BF16)
-    hipLaunchKernelGGL(embedding_bwd_kernel<bf16_raw>, grid, dim3(256), shm, st, (const bf16_raw*)dY, idx, dtable, R, V, E, scale);
+    hipLaunchKernelGGL(embedding_bwd_kernel<bf16_raw>, grid, dim3(256), shm, st, (const bf16_raw*)dY, idx, dtable, R, V, E, cols, scale);
   else
-    hipLaunchKernelGGL(embedding_bwd_kernel<float>, grid, dim3(256), shm, st, (const float*)dY, idx, dtable, R, V, E, scale);
+    hipLaunchKernelGGL(embedding_bwd_kernel<float>, grid, dim3(256), shm, st, (const float*)dY, idx, dtable, R, V, E, cols, scale);
   return launch_status();
 }
 
