@@ -1033,7 +1033,7 @@ int hfta_conv2d_grouped_bwd(int B, int Nb, int Ci, int Co, int H, int W, int kh,
       if (rc != HFTA_OK) return rc;
       GemmDesc d = lowered_dw_desc(B, Co, L, dtype);
       d.A = dyp; d.Bm = colb; d.C = dW;
-      d.splits = gemm_pick_splits(d);
+      d.splits = gemm_splits(d);
       d.partial = part;
       rc = gemm_launch(d, st);
       if (rc != HFTA_OK) return rc;

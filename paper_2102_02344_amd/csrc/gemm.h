@@ -511,7 +511,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs p) {
   store_tile<OutT, T, sizeof(T) == sizeof(OutT)>(acc, &smem[0][0][0], Cb, p.c_ld, p.M, p.N, m0, n0, bias, p.bias_mode, p.act, p.slope, p.c_vec, t, p.c_seg, p.c_seg_stride);
 }
 
-int gemm_pick_splits(const GemmDesc& d);
+int gemm_pick_splits(const GemmDesc& d);         // from the shape alone (workspace sizes): never fewer than gemm_splits
+int gemm_splits(const GemmDesc& d);              // with the operands known
 size_t gemm_partial_bytes(const GemmDesc& d, int splits);
 int gemm_launch(const GemmDesc& d, hipStream_t stream);
 

@@ -57,8 +57,8 @@ static int pick_splits_big(const GemmDesc& d) {
 
 // Enough workgroups to fill 256 compute units a few times over, without cutting
 // the reduction into pieces shorter than 8 k-tiles.
+// From the shape alone: what a workspace is sized for.
 int gemm_pick_splits(const GemmDesc& d) {
-  if (d.S == 1 && gemm_dma_tile(d) >= 0) return 1;
   const int big = pick_splits_big(d);
   if (big > 0) return big;
   const int64_t tiles = (int64_t)((d.M + GEMM_BM - 1) / GEMM_BM) * ((d.N + GEMM_BN - 1) / GEMM_BN) * d.G0 * d.G1;
@@ -70,6 +70,26 @@ int gemm_pick_splits(const GemmDesc& d) {
   if (want > 256) want = 256;
   return want < 1 ? 1 : (int)want;
 }
+
+// Whether an unsplit launch of d takes the kernel that loads straight into LDS: its shapes, whole aligned 16-byte pieces,
+// operand slices that fit a buffer.
+static bool loads_to_lds(const GemmDesc& d) {
+  if (gemm_dma_tile(d) < 0) return false;
+  auto pieces = [](const void* p, int64_t ld, int64_t ss, int64_t s0, int64_t s1) {
+    return aligned_to(p, 16) && ld > 0 && ld % 8 == 0 && ss % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
+  };
+  auto fits = [](bool kc, int64_t rows, int64_t K, int64_t ld) {
+    return ((kc ? (rows - 1) * ld + K : (K - 1) * ld + rows) * 2) < (int64_t)1 << 31;
+  };
+  return pieces(d.A, d.a_ld, d.a_ss, d.a_g0, d.a_g1) && pieces(d.Bm, d.b_ld, d.b_ss, d.b_g0, d.b_g1) &&
+         fits(d.a_kc, d.M, d.K, d.a_ld) && fits(d.b_kc, d.N, d.K, d.b_ld);
+}
+
+// With the operands known: unsplit where that kernel takes them, else the split that the workspace was sized for.  (On
+// operands it does not take, few tiles under a long reduction need the split: weight and bias gradient on 8-byte aligned
+// rows, 1 x 512 x 512, K = 4096 154 us, 176 unsplit.  More tiles and a shorter one would do without: 5 x 384 x 1536,
+// K = 693 79 and 64.)
+int gemm_splits(const GemmDesc& d) { return d.S == 1 && loads_to_lds(d) ? 1 : gemm_pick_splits(d); }
 
 size_t gemm_partial_bytes(const GemmDesc& d, int splits) {
   if (splits <= 1) return 0;
@@ -194,7 +214,7 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
                    n16ok(d.Bm, d.b_ld, d.b_ss, d.b_g0, d.b_g1, d.b_kc, d.N);
 
   // Few output tiles under a reduction of some length: loads straight into LDS, deeper in flight.
-  if (buffers_ok && splits == 1 && n16 && (!d.a_kc || a.a_vec == 2) && (!d.b_kc || a.b_vec == 2)) {
+  if (splits == 1 && loads_to_lds(d)) {
     const int rc = gemm_dma_launch(d, a, st);
     if (rc != HFTA_EUNSUPPORTED) return rc;
   }

@@ -369,7 +369,7 @@ int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype, const void* X, cons
   hipStream_t st = as_stream(stream);
   GemmDesc dw = linear_dw_desc(B, M, Fx, Fy, dtype, X, dY, dW);
   if (dW) {
-    dw.splits = gemm_pick_splits(dw);
+    dw.splits = gemm_splits(dw);
     const size_t need = gemm_partial_bytes(dw, dw.splits);
     if (need > 0 && (!workspace || ws_bytes < need)) return HFTA_EWORKSPACE;
     dw.partial = reinterpret_cast<float*>(workspace);
@@ -594,7 +594,7 @@ int hfta_conv1x1_bwd(int B, int Nb, int Ci, int Co, int L, int dtype, const void
   GemmDesc dw{};
   if (dW) {
     dw = conv_dw_desc(B, Nb, Ci, Co, L, dtype, X, xs, dY, dys, dW);
-    dw.splits = gemm_pick_splits(dw);
+    dw.splits = gemm_splits(dw);
     const size_t need = gemm_partial_bytes(dw, dw.splits);
     if (need > 0 && (!workspace || ws_bytes < need)) return HFTA_EWORKSPACE;
     dw.partial = reinterpret_cast<float*>(workspace);

@@ -65,3 +65,27 @@ def test_linear_forward_backward(hb, B, M, Fx, Fy):
     within(dX, dy64 @ w64.transpose(0, 2, 1), ad @ aw.transpose(0, 2, 1), Fy, True, "data gradient")
     within(dW, x64.transpose(0, 2, 1) @ dy64, ax.transpose(0, 2, 1) @ ad, M, False, "weight gradient")
     within(db, dy64.sum(1), ad.sum(1), M, False, "bias gradient")
+
+
+@pytest.mark.parametrize("B,M,Fx,Fy", [(5, 693, 384, 1536), (1, 4096, 512, 512)])
+@pytest.mark.parametrize("off", [0, 4, 1])
+def test_weight_gradient_by_alignment(hb, B, M, Fx, Fy, off):
+    """Operands that start on 16 bytes take the kernel unsplit and need no workspace; the same shape 8 or 2 bytes further
+    on, which it does not take, is split over the workspace that the query asks for."""
+    def place(seed, shape):
+        n = int(np.prod(shape))
+        return hi.normal(seed, shape, "bf16"), torch.empty(n + 8, dtype=torch.bfloat16, device="cuda")[off:off + n].view(shape)
+    (x, X), (dy, dY) = place(511, (B, M, Fx)), place(512, (B, M, Fy))
+    X.copy_(dev(x, "bf16"))
+    dY.copy_(dev(dy, "bf16"))
+    ws = torch.full((hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, 1),), 0xff, dtype=torch.uint8, device="cuda")
+    assert ws.numel() >= 2 * B * Fx * Fy * 4
+    dW, db = torch.full((B, Fx, Fy), float("nan"), device="cuda"), torch.full((B, Fy), float("nan"), device="cuda")
+    hb.linear_bwd(B, M, Fx, Fy, 1, X, None, dY, None, dW, db, None if off == 0 else ws)
+    x64, dy64 = np.asarray(x, np.float64), np.asarray(dy, np.float64)
+    within(dW, x64.transpose(0, 2, 1) @ dy64, np.abs(x64).transpose(0, 2, 1) @ np.abs(dy64), M, False, "weight gradient")
+    within(db, dy64.sum(1), np.abs(dy64).sum(1), M, False, "bias gradient")
+    assert bool((ws != 0xff).any()) == (off != 0)
+    if off:
+        with pytest.raises(hb.HftaError):
+            hb.linear_bwd(B, M, Fx, Fy, 1, X, None, dY, None, dW, db, None)
