@@ -273,9 +273,11 @@ __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
   // column sums of B (GemmDesc::bsum) by the workgroups of the first row tile
   static_assert(!SUMS || (!A_KC && !B_KC && sizeof(OutT) == 4 && N16), "column sums go with a weight gradient");
   const bool sums = SUMS && m0 == 0;
-  float cs[SUMS ? 8 : 1];
+  float cs[SUMS ? 4 : 1][8];
 #pragma unroll
-  for (int e = 0; e < (SUMS ? 8 : 1); ++e) cs[e] = 0.f;
+  for (int k = 0; k < (SUMS ? 4 : 1); ++k)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[k][e] = 0.f;
   for (int base = t_begin; !done; base += BIG_PF) {
 #pragma unroll
     for (int d = 0; d < BIG_PF; ++d) {
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
           for (int j = 0; j < 2; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
         if constexpr (SUMS) {              // a quarter of the thread's four k-rows per k-step
-          if (sums) add_bf16x8(cs, *reinterpret_cast<const uint4*>(Bs + ((t >> 5) + 16 * s) * BIG_NPITCH + (t & 31) * 16));
+          if (sums) add_bf16x8(cs[s], *reinterpret_cast<const uint4*>(Bs + ((t >> 5) + 16 * s) * BIG_NPITCH + (t & 31) * 16));
         }
       }
       if (cur + 1 >= t_end) { done = true; break; }
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(BIG_THREADS) void gemm_big_kernel(GemmArgs p) {
   __syncthreads();
   if constexpr (SUMS) {
     if (sums) {
-      store_colsums<32, 16>(cs, reinterpret_cast<float*>(smem), p.bsum + (int64_t)g0 * p.N, n0, p.N, t);
+      store_colsums<32, 4>(cs, reinterpret_cast<float*>(smem), p.bsum + (int64_t)g0 * p.N, n0, p.N, t);
       __syncthreads();
     }
   }

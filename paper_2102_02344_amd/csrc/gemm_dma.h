@@ -157,8 +157,11 @@ __device__ __forceinline__ void dma_store_rows(const unsigned char* lds, OutT* C
   }
 }
 
-// Column sums of an operand tile (GemmDesc::bsum): eight bf16 columns onto a thread's fp32 sums, and the sums of the
-// ROWS threads of a column added in order through LDS.
+// Column sums of an operand tile (GemmDesc::bsum), in the order of the stand-alone column sum (colsum_vec_kernel): row r
+// belongs to chain r % 64, a chain adds its rows in order, the chains are added in order.  So a bias gradient does not
+// depend on which kernel took the weight gradient, and with it on the number of models.  A tile is 64 rows: a thread keeps
+// eight columns of its rows of a tile, each a chain of its own.
+constexpr int SUM_CHAINS = 64;
 __device__ __forceinline__ void add_bf16x8(float (&s)[8], const uint4& q) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -167,16 +170,20 @@ __device__ __forceinline__ void add_bf16x8(float (&s)[8], const uint4& q) {
     s[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
   }
 }
-template <int PPR, int ROWS>
-__device__ __forceinline__ void store_colsums(const float (&s)[8], float* lds, float* out, int n0, int N, int t) {
-  float* d = lds + (t / PPR) * (PPR * 8) + (t % PPR) * 8;
-  *reinterpret_cast<float4*>(d) = make_float4(s[0], s[1], s[2], s[3]);
-  *reinterpret_cast<float4*>(d + 4) = make_float4(s[4], s[5], s[6], s[7]);
+// PPR eight-column pieces per row; thread t holds chains t / PPR + k * (SUM_CHAINS / C), k < C, of piece t % PPR
+template <int PPR, int C>
+__device__ __forceinline__ void store_colsums(const float (&s)[C][8], float* lds, float* out, int n0, int N, int t) {
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    float* d = lds + (t / PPR + k * (SUM_CHAINS / C)) * (PPR * 8) + (t % PPR) * 8;
+    *reinterpret_cast<float4*>(d) = make_float4(s[k][0], s[k][1], s[k][2], s[k][3]);
+    *reinterpret_cast<float4*>(d + 4) = make_float4(s[k][4], s[k][5], s[k][6], s[k][7]);
+  }
   __syncthreads();
   if (t < PPR * 8 && n0 + t < N) {
-    float v = lds[t];
-#pragma unroll 8
-    for (int r = 1; r < ROWS; ++r) v += lds[r * (PPR * 8) + t];
+    float v = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < SUM_CHAINS; ++r) v += lds[r * (PPR * 8) + t];
     out[n0 + t] = v;
   }
 }
@@ -256,11 +263,14 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
   for (int d = 0; d < ST - 1; ++d) issue(aim(d), d, 0, PER);
   // column sums of B, by the workgroups of the first row tile: 8 columns of every (threads / pieces)-th k-row a thread
   constexpr bool SUMS = !A_KC && !B_KC && sizeof(OutT) == 4;
-  constexpr int SPPR = BN / 8, SROWS = WAVES * 64 / SPPR;
+  constexpr int SPPR = BN / 8, SROWS = WAVES * 64 / SPPR, SC = SUMS ? SUM_CHAINS / SROWS : 1;
+  static_assert(!SUMS || (BK == SUM_CHAINS && SUM_CHAINS * BN * 4 <= SMEM), "a tile's rows are the chains");
   const bool sums = SUMS && p.bsum && m0 == 0;
-  float cs[SUMS ? 8 : 1];
+  float cs[SC][8];
 #pragma unroll
-  for (int e = 0; e < (SUMS ? 8 : 1); ++e) cs[e] = 0.f;
+  for (int k = 0; k < SC; ++k)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[k][e] = 0.f;
   bool done = false;
   for (int base = 0; !done; base += ST) {
 #pragma unroll
@@ -294,9 +304,9 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
       if constexpr (SUMS) {
         if (sums) {
 #pragma unroll
-          for (int r = t / SPPR; r < BK; r += SROWS) {
-            const uint4 q = *reinterpret_cast<const uint4*>(Bs + r * (BN * 2) + (((t % SPPR) ^ OpB::swz(r)) << 4));
-            add_bf16x8(cs, q);
+          for (int k = 0; k < SC; ++k) {
+            const int r = t / SPPR + k * SROWS;
+            add_bf16x8(cs[k], *reinterpret_cast<const uint4*>(Bs + r * (BN * 2) + (((t % SPPR) ^ OpB::swz(r)) << 4)));
           }
         }
       }
@@ -306,7 +316,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
   dma_wait_barrier<0>();                                   // nothing may land in the stages any more
   if constexpr (SUMS) {
     if (sums) {
-      store_colsums<SPPR, SROWS>(cs, reinterpret_cast<float*>(smem), p.bsum + (int64_t)g0 * p.N, n0, p.N, t);
+      store_colsums<SPPR, SC>(cs, reinterpret_cast<float*>(smem), p.bsum + (int64_t)g0 * p.N, n0, p.N, t);
       __syncthreads();
     }
   }

@@ -122,7 +122,8 @@ __global__ __launch_bounds__(256) void colsum_kernel(const T* __restrict__ dY, f
 
 // The same with 16-byte loads: 1024 threads = 16 column groups (one 16-byte piece of a row each,
 // so a row's pieces are contiguous) x 64 row lanes; row lanes are summed through LDS in a fixed
-// order.  Needs Fy a multiple of the piece and 16-byte aligned rows.
+// order (the order that the weight gradients' kernels keep too, see store_colsums in gemm_dma.h).
+// Needs Fy a multiple of the piece and 16-byte aligned rows.
 template <typename T>
 __global__ __launch_bounds__(1024) void colsum_vec_kernel(const uint4* __restrict__ dY, float* __restrict__ out,
                                                          int M, int Fy) {
@@ -386,8 +387,8 @@ int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype, const void* X, cons
   }
   bool db_done = false;
   if (dW) {
-    // the weight gradient's kernel adds up dY's columns from the tiles it holds, where it is one that can: against a
-    // pass over dY of its own, 8 x 2048 x 8192 78 + 52 -> 91 us, 8 x 2048 x 1024 21 + 8.8 -> 22.9 us
+    // The weight gradient's kernel adds up dY's columns from the tiles it holds, where it is one that can, in the order of
+    // the pass below (the same bits either way).  Both gradients, 8 x 2048 x 256 -> 8192: 131 us with the pass, 115 without.
     dw.bsum = dbias;
     dw.bsum_done = &db_done;
     int rc = gemm_launch(dw, st);

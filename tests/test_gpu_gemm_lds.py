@@ -89,3 +89,30 @@ def test_weight_gradient_by_alignment(hb, B, M, Fx, Fy, off):
     if off:
         with pytest.raises(hb.HftaError):
             hb.linear_bwd(B, M, Fx, Fy, 1, X, None, dY, None, dW, db, None)
+
+
+@pytest.mark.parametrize("M,Fx,Fy,models", [
+    (300, 64, 72, (1, 3)),           # 64 x 64 tiles
+    (693, 384, 1000, (1, 5)),        # 64 x 64 for one model, 128 x 64 for five
+    (1501, 392, 520, (1, 4)),        # 64 x 64 and 128 x 128
+    (600, 512, 2048, (1, 2, 12)),    # ... and the 256 x 256 kernel
+    (2048, 256, 8192, (2, 8)),
+])
+def test_bias_gradient_is_one_sum(hb, M, Fx, Fy, models):
+    """A model's bias gradient has the same bits however many models it is trained with and whether or not the weight
+    gradient is asked for: rows r, r + 64, r + 128, .. are added in order, then the 64 sums in order."""
+    B = max(models)
+    x, dy = dev(hi.normal(521, (B, M, Fx), "bf16"), "bf16"), dev(hi.normal(522, (B, M, Fy), "bf16"), "bf16")
+    chains = torch.zeros(B, 64, Fy)
+    rows = dy.float().cpu()
+    for r in range(M):
+        chains[:, r % 64] += rows[:, r]
+    ref = torch.zeros(B, Fy)
+    for k in range(64):
+        ref += chains[:, k]
+    for n in models:
+        ws = torch.empty(max(4, hb.linear_bwd_workspace_bytes(n, M, Fx, Fy, 1)), dtype=torch.uint8, device="cuda")
+        for dW in (None, torch.empty(n, Fx, Fy, device="cuda")):
+            db = torch.full((n, Fy), float("nan"), device="cuda")
+            hb.linear_bwd(n, M, Fx, Fy, 1, None if dW is None else x, None, dy, None, dW, db, ws)
+            assert torch.equal(db.cpu(), ref[:n]), (n, dW is None)
