@@ -726,12 +726,14 @@ static bool ln_vec_rows(int E, int dtype) {
   return E % epv == 0 && E / epv <= 128;
 }
 
-// Workgroups per model of the backward: 16 rows each up to 128 workgroups (a function of R alone, so that a model's
-// result does not depend on how many it is trained with).  64 rows each left small arrays one workgroup per
-// compute unit: 8 x 2048 rows of 256 took 23.4 us, 12.5 now with a second gradient and the column sums besides.
+// Workgroups per model of the backward (a function of R alone, so that a model's result does not depend on how many it
+// is trained with): 16 rows each up to 128 workgroups, 64 each up to 256, one per compute unit for one model alone.
+// 64 rows each throughout left small arrays one workgroup per compute unit: 8 x 2048 rows of 256 took 23.4 us, 12.5 now
+// with a second gradient and the column sums besides.  128 at most left one model half of them:
+// 65536 x 512 134 -> 73 us, 16384 x 500 (plain rows) 199 -> 103, 16 models x 16384 x 512 182 -> 170.
 static int ln_blocks(int R) {
-  const int nb = (R + 15) / 16;
-  return nb > 128 ? 128 : nb;
+  const int few = (R + 15) / 16, many = (R + 63) / 64;
+  return few <= 128 ? few : many <= 128 ? 128 : many <= 256 ? many : 256;
 }
 
 template <typename T, bool SUMS>

@@ -282,3 +282,10 @@ def test_validation_of_the_wider_entry_points(lib):
     assert raw.hfta_point_transform_fwd(1, 2, 64, 64, 8, 1, one, bad_l, one, one, s4, None) == lib.EUNSUPPORTED
     assert raw.hfta_point_transform_fwd(300, 300, 64, 64, 8, 1, one, s4, one, one, s4, None) == lib.EUNSUPPORTED
     assert raw.hfta_point_transform_bwd(1, 2, 64, 64, 8, 1, one, s4, one, None, s4, one, s4, one, None) == lib.EINVAL
+
+
+def test_layernorm_backward_workgroups(lib):
+    """The partial sums of the LayerNorm backward, [dw | db] per workgroup: 16 rows a workgroup up to 128, 64 up to 256."""
+    for R, blocks in ((1, 1), (16, 1), (17, 2), (2048, 128), (8192, 128), (8193, 129), (16383, 256), (16384, 256), (70000, 256)):
+        assert lib.layernorm_bwd_workspace_bytes(3, R, 40) == 3 * blocks * 2 * 40 * 4, R
+        assert lib.layernorm_bwd_sums_workspace_bytes(3, R, 40) == 3 * blocks * 3 * 40 * 4, R

@@ -24,3 +24,24 @@ def test_add_layernorm_is_add_then_layernorm(dtype, B, R, E):
     hb.add_layernorm_fwd(B, R, E, DT[dtype], x1, x2, s1, w, b, 1e-5, m1, i1, y1)
     for a, c in ((s0, s1), (y0, y1), (m0, m1), (i0, i1)):
         assert torch.equal(a, c) and bool(torch.isfinite(a).all())
+
+
+@pytest.mark.parametrize("R", [8191, 8193, 16385, 20011])
+@pytest.mark.parametrize("E", [64, 66])
+def test_backward_of_many_rows(R, E):
+    """Column sums over more rows than 128 workgroups of 16 hold (register-resident and plain rows), at counts that leave
+    the last workgroup short: against float64 of the same values.  R terms of at most 4 roundings each on the way in, added
+    in chains: a term's error is below (4 + R / 128) 2^-24 of it in any of the orders."""
+    from paper_2102_02344_amd import binding as hb
+    B = 1
+    x, dy = dev(hi.normal(611, (B, R, E))), dev(hi.normal(612, (B, R, E)))
+    w, b = dev(hi.normal(613, (B, E)).astype("float32")), dev(hi.normal(614, (B, E)).astype("float32"))
+    mean, inv, y, dx = (torch.empty(s, device="cuda") for s in ((R,), (R,), (B, R, E), (B, R, E)))
+    hb.layernorm_fwd(B, R, E, 0, x, w, b, 1e-5, mean, inv, y)
+    dw, db = torch.full((B, E), float("nan"), device="cuda"), torch.full((B, E), float("nan"), device="cuda")
+    ws = torch.empty(hb.layernorm_bwd_workspace_bytes(B, R, E), dtype=torch.uint8, device="cuda")
+    hb.layernorm_bwd(B, R, E, 0, x, dy, w, mean, inv, dx, dw, db, ws)
+    xh = (x.double()[0] - mean.double()[:, None]) * inv.double()[:, None]
+    for got, term in ((dw, dy.double()[0] * xh), (db, dy.double()[0])):
+        lim = (4 + R / 128) * 2.0 ** -24 * term.abs().sum(0)
+        assert bool(((got[0].double() - term.sum(0)).abs() <= lim).all())
