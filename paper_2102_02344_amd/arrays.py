@@ -38,6 +38,12 @@ def _whole_pieces(L):
     return L % 4 == 0
 
 
+def _on_16_bytes(w):
+    """Weights as the one-operator tail and the layers that normalise their input on load read them.  A segment of the
+    arena starts where the one before it ends, so layers with odd channel counts move those behind them off it."""
+    return w.data_ptr() % 16 == 0
+
+
 def _bn_bwd_one_pass(B, Nb, ci, co, L, dt):
     """True when ``conv1x1_bn_bwd`` runs this layer as one streaming kernel (dz never stored).  Layers it
     would run as the two single operators are called as such here, with dz in one of the array's
@@ -248,7 +254,7 @@ class FusedPointNetCls(ParamArena):
         if fused_tail and self.nconv >= 2:
             geo = (B, Nb, spec.conv[-2], spec.conv[-1], L, self.dt)
             self.fused_tail_ws = hb.conv1x1_bn_maxpool_workspace_bytes(*geo)
-            self.fused_tail = self.fused_tail_ws > 0
+            self.fused_tail = self.fused_tail_ws > 0 and _on_16_bytes(self.w(f"conv{self.nconv - 1}.w"))
         nz = self.nconv - 1 if self.fused_tail else self.nconv
         self.z = [torch.empty(Nb, B * c, L, **act) for c in spec.conv[1:1 + nz]]
         # prenorm[i]: layer i takes layer i-1's stored pre-activation and normalises it on load (forward and
@@ -257,7 +263,8 @@ class FusedPointNetCls(ParamArena):
         self.prenorm = [False] * self.nconv
         if not self.unfused:
             for i in range(1, self.nconv - 1):
-                self.prenorm[i] = hb.conv1x1_bn_prenorm_supported(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt)
+                self.prenorm[i] = hb.conv1x1_bn_prenorm_supported(B, Nb, spec.conv[i], spec.conv[i + 1], L, self.dt) and \
+                    _on_16_bytes(self.w(f"conv{i}.w"))
         # ... unless the tail is the one-operator form: its first kernel normalises on load and writes the activated
         # tensor out on the way (tail_x), so that layer skips its own normalisation pass over the tensor
         self.tail_prenorm = bool(tail_prenorm) and self.fused_tail and L % 4 == 0 and not self.unfused and self.nconv >= 2
@@ -1449,8 +1456,8 @@ class _PointChain(_Views):
         ws = 4
         if self.head and self.nconv >= 2:
             geo = (B, Nb, self.conv[-2], self.conv[-1], L, dt)
-            wt = A.w(f"{prefix}conv{conv_base + self.nconv - 1}.w")     # the one-operator tail wants 16-byte aligned weights
-            self.fused_tail = _whole_pieces(L) and hb.conv1x1_bn_maxpool_workspace_bytes(*geo) > 0 and wt.data_ptr() % 16 == 0
+            self.fused_tail = _whole_pieces(L) and hb.conv1x1_bn_maxpool_workspace_bytes(*geo) > 0 and \
+                _on_16_bytes(A.w(f"{prefix}conv{conv_base + self.nconv - 1}.w"))
             if self.fused_tail:
                 ws = max(ws, hb.conv1x1_bn_maxpool_workspace_bytes(*geo))
         nz = self.nconv - 1 if self.fused_tail else self.nconv
@@ -1460,7 +1467,8 @@ class _PointChain(_Views):
         # (the layer in front of the tail keeps its output: the tail operator reads it)
         self.prenorm = [False] * self.nconv
         for i in range(1, na):
-            self.prenorm[i] = _whole_pieces(L) and hb.conv1x1_bn_prenorm_supported(B, Nb, self.conv[i], self.conv[i + 1], L, dt)
+            self.prenorm[i] = _whole_pieces(L) and hb.conv1x1_bn_prenorm_supported(B, Nb, self.conv[i], self.conv[i + 1], L, dt) and \
+                _on_16_bytes(A.w(f"{prefix}conv{conv_base + i}.w"))
         self.a = [None if (i + 1 < na and self.prenorm[i + 1]) else torch.empty(Nb, B * c, L, **act)
                   for i, c in enumerate(self.conv[1:1 + na])]
         cmax = max(self.conv)

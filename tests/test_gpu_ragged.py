@@ -221,3 +221,17 @@ def test_tail_row_strides(hb, L):
         for a, c in zip(ref, got):
             assert torch.equal(a, c)
         assert bool(torch.isfinite(dx0).all()) and torch.equal(dx0, dx1.flip(2) if whole else dx1)
+
+
+@pytest.mark.parametrize("L", [131, 130, 132])
+def test_classification_array_with_weights_off_16_bytes(L):
+    """Ten channels in the first layer leave every later layer's weights 8 bytes off: the operators that want them on 16
+    are not chosen, and every call of a step is right in place."""
+    import dataclasses
+
+    from paper_2102_02344_amd.arrays import FusedPointNetCls
+    spec = dataclasses.replace(hi.spec_c1(B=1, Nb=3, L=L), conv=(3, 10, 16, 64, 64, 72), fc=(72, 24, 16))
+    arr = FusedPointNetCls(spec, hi.pointnet_cls_inputs(spec))
+    assert all(arr.w(f"conv{i}.w").data_ptr() % 16 == 8 for i in range(2, 5))
+    assert not arr.fused_tail and not any(arr.prenorm)
+    arr.forward_backward(pn.in_place_probe(spec, []))
