@@ -165,6 +165,16 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_raw* __restric
       pk[jb] = make_uint2(0, 0);
       if (jb < nbl) pk[jb] = make_uint2(pack_bf16x2(s[jb][0] * inv, s[jb][1] * inv), pack_bf16x2(s[jb][2] * inv, s[jb][3] * inv));
     }
+    if (__any(inv != inv)) {                                     // a row that holds a NaN or an infinity: its masked entries stay zero
+#pragma unroll
+      for (int jb = 0; jb < NJ; ++jb) {
+        if (jb != nbl - 1) continue;                             // (the only block with masked entries)
+        float x[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = jb * 16 + v < lim ? s[jb][v] * inv : 0.f;
+        pk[jb] = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+      }
+    }
     if (i < S) {
 #pragma unroll
       for (int jb = 0; jb < NJ; ++jb)

@@ -49,3 +49,25 @@ def test_probabilities_far_below_the_maximum(hb, causal):
     assert int((seen & (p < 1e-12)).sum()) > 10000
     assert bool(((got >= lo) & (got <= hi))[seen].all())
     assert bool((got[p == 0] == 0).all())
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("S", [20, 70, 200])
+@pytest.mark.parametrize("what", ["query nan", "query inf", "key nan", "key inf"])
+def test_values_that_are_not_finite(hb, what, S, causal):
+    """A NaN or an infinity in one query or key reaches the probabilities that the batched products give it (which the
+    same call takes with its output 8 bytes off): the row's own, none behind the causal mask, and no other row's."""
+    B, N, E, H, at = 1, 2, 48, 2, S // 2 + 3
+    g = torch.Generator().manual_seed(13)
+    qkv = torch.randn(B, N, S, 3 * E, generator=g).bfloat16()
+    qkv[0, 1, at, (0 if what.startswith("query") else E) + 5] = float(what.split()[1])
+    qkv = qkv.cuda()
+    P = [torch.full((B, N, H, S, S), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    for p, off in zip(P, (0, 4)):
+        ctx = torch.empty(B * N * S * E + 8, dtype=torch.bfloat16, device="cuda")[off:]
+        hb.attention_fwd(B, N, S, E, H, 1, qkv, p, ctx, causal)
+    a, b = (p.cpu().float() for p in P)
+    assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a == 0, b == 0)
+    assert bool(a.isnan().any()) and not bool(a[:, 0].isnan().any())
+    ok = ~a.isnan()
+    assert bool(((a - b).abs() <= 2.0 ** -7 * b.abs())[ok].all())
