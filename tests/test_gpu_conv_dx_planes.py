@@ -1,10 +1,15 @@
 """Data gradient of the 4x4 / stride 2 convolution at the image sizes its plane kernel treats differently (rows of
 one, two and eight 16-byte pieces, four-pixel rows in whole images, images smaller and larger than a tile), at
-ragged samples and channels, and below and above one workgroup per compute unit.  Same reference and tolerance
-as the operator's other sizes."""
+ragged samples and channels, below one workgroup per compute unit (two k-tiles of weights in registers) and above
+(one), with tiles of 64 and of 128 rows; and of four-pixel rows in images taller than a tile, which the gathering
+kernel keeps.  Same reference and tolerance as the operator's other sizes."""
+import numpy as np
 import pytest
 
+import hfta_inputs as hi
 import test_gpu_ops as ops
+from oracle import array as oa
+from util import TOL, check, dev, host
 
 pytestmark = pytest.mark.gpu
 
@@ -17,6 +22,20 @@ def hb():
 
 @pytest.mark.parametrize("B,Nb,Ci,Co,H", [
     (1, 1, 32, 2, 8), (2, 5, 40, 50, 8), (2, 7, 130, 34, 8), (1, 3, 72, 18, 16), (1, 2, 33, 66, 32), (1, 1, 32, 20, 64),
-    (1, 1, 96, 16, 128), (5, 30, 260, 36, 8)])
+    (1, 1, 96, 16, 128), (5, 30, 260, 36, 8),
+    # workgroups: rows / 128 (or 64) x samples' pixels / 64 x 2 x models = 288, 288, 260, 270
+    (6, 30, 260, 36, 8), (16, 33, 40, 18, 8), (5, 13, 130, 34, 16), (9, 15, 50, 20, 16)])
 def test_data_gradient(hb, B, Nb, Ci, Co, H):
     ops.test_conv2d_grouped(hb, "bf16", B, Nb, Ci, Co, H, 4, 2, 1, "implicit")
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co", [(2, 3, 40, 18), (1, 2, 130, 6)])
+def test_data_gradient_of_tall_images(hb, B, Nb, Ci, Co):
+    H, W = 64, 8
+    x = hi.normal(101, (Nb, B * Ci, H, W), "bf16")
+    w = hi.normal(102, (B * Co, Ci, 4, 4), "bf16", 1.0 / np.sqrt(Ci * 16))
+    dy = hi.normal(104, (Nb, B * Co, H // 2, W // 2), "bf16")
+    dX = ops.empty(x.shape, "bf16")
+    _, ws = ops.conv_workspaces(hb, "implicit", (B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1))
+    hb.conv2d_grouped_bwd(B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1, dev(x, "bf16"), dev(w, "bf16"), dev(dy, "bf16"), dX, None, None, ws)
+    check(host(dX), oa.conv2d_bwd(B, x, w, dy, 2, 1)[0], TOL["bf16"], "dX")
