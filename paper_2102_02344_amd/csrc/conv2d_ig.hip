@@ -96,14 +96,14 @@ __device__ __forceinline__ void ig_stage64(f32x16_t (&acc)[2][FN], unsigned char
   }
 }
 
-// Epilogue of a TM x 128 tile: fp32 partial slices when k is split, else bias + activation and whole pieces of the
-// output rows (PAIR: the two classes of a row interleaved).  `smem` is free (behind a barrier).
+// Epilogue of a TM x 128 tile: fp32 partial slices when k is split (not with PAIR), else bias + activation and whole
+// pieces of the output rows (PAIR: the two classes of a row interleaved).  `smem` is free (behind a barrier).
 template <bool PAIR, int TM, int FN>
 __device__ __forceinline__ void ig_epilogue(const IgArgs& p, f32x16_t (&acc)[2][FN], unsigned char* smem, int b, int split,
                                             int m0, int n0, int wm, int col0, const IgClass& cl0, int t, int lane) {
   constexpr int NT = 256;
   const int P = 1 << p.lgP;
-  if (p.ksplit > 1) {
+  if (!PAIR && p.ksplit > 1) {
     // ---- split k: this workgroup's fp32 partial tile goes to its slice, indexed like the output;
     // bias, activation and the conversion happen in ig_split_finish_kernel
     float* lds_f = reinterpret_cast<float*>(smem);
@@ -128,21 +128,11 @@ __device__ __forceinline__ void ig_epilogue(const IgArgs& p, f32x16_t (&acc)[2][
       for (int id = t; id < 64 * 32; id += NT) {
         const int rr = id >> 5, pc = id & 31;
         const int m = mp + rr;
-        if (!PAIR) {
-          const int n = n0 + pc * 4;
-          if (m >= p.M || n >= p.N) continue;
-          const int img = n >> p.lgP, pix = n & (P - 1);
-          *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + pix) =
-              *reinterpret_cast<const float4*>(lds_f + rr * FP + pc * 4);
-        } else {
-          const int n = n0 + pc * 2;                      // 2 pixels x 2 classes = 4 consecutive output elements
-          if (m >= p.M || n >= p.N) continue;
-          const int img = n >> p.lgP, y = (n & (P - 1)) >> p.lgWo, x = n & (p.Wo - 1);
-          const float2 e = *reinterpret_cast<const float2*>(lds_f + rr * FP + pc * 2);
-          const float2 o = *reinterpret_cast<const float2*>(lds_f + rr * FP + 64 + pc * 2);
-          *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + (int64_t)(y * p.oys + cl0.out_y0) * p.OW + x * p.oxs) =
-              make_float4(e.x, o.x, e.y, o.y);
-        }
+        const int n = n0 + pc * 4;
+        if (m >= p.M || n >= p.N) continue;
+        const int img = n >> p.lgP, pix = n & (P - 1);
+        *reinterpret_cast<float4*>(ob + (int64_t)img * p.o_img + (int64_t)m * p.o_m + pix) =
+            *reinterpret_cast<const float4*>(lds_f + rr * FP + pc * 4);
       }
       if (pass + 1 < TM / 64) __syncthreads();
     }
@@ -235,9 +225,9 @@ __global__ __launch_bounds__(256) void conv_ig_fwd_kernel(IgArgs p) {
   ig_block(p.grid, bx, by, b);
   const int tile_m = bx / p.tiles_n, tile_n = bx % p.tiles_n;
   const int m0 = tile_m * TM, n0 = tile_n * COLS;
-  // grid y: PAIR py + 2 * (k split), else the k split
-  const int py2 = PAIR ? 2 * (by & 1) : 0;
-  const int split = PAIR ? by >> 1 : by;
+  // grid y: py with PAIR, else the k split
+  const int py2 = PAIR ? 2 * by : 0;
+  const int split = PAIR ? 0 : by;
   const IgClass cl0 = p.cls[py2];
   const int P = 1 << p.lgP;
   const int img0 = n0 >> p.lgP;                          // first sample of the tile
@@ -713,8 +703,7 @@ __global__ __launch_bounds__(256) void ig_split_finish_kernel(const float* __res
 // k split of the forward kernel: taken when the tiles alone leave most compute units with a single
 // workgroup and the reduction is long (the 8x8 layers: 320 tiles, 128 k-tiles: 101 -> 90 us).  With
 // 640 tiles and more, and for the class-pair data gradient, the split measured no gain or a loss.
-int ig_pick_ksplit(int64_t blocks, int ktiles, bool pair) {
-  if (pair) return 1;
+int ig_pick_ksplit(int64_t blocks, int ktiles) {
   if (blocks >= 384 || ktiles < 64) return 1;
   return ktiles >= 128 ? 4 : 2;
 }
@@ -753,7 +742,7 @@ size_t conv_ig_fwd_split_bytes(int B, int Nb, int Ci, int Co, int H, int W) {
   const int Ho = H / 2, Wo = W / 2, tm = Co <= 64 ? 64 : 128;
   if (Ho <= 0 || Wo <= 0) return 0;
   const int64_t blocks = (int64_t)((Co + tm - 1) / tm) * (((int64_t)Nb * Ho * Wo + 127) / 128) * B;
-  const int ks = ig_pick_ksplit(blocks, (Ci * 16 + 31) / 32, false);
+  const int ks = ig_pick_ksplit(blocks, (Ci * 16 + 31) / 32);
   return ks > 1 ? (size_t)ks * Nb * B * Co * Ho * Wo * sizeof(float) : 0;
 }
 
@@ -788,7 +777,7 @@ int conv_ig_forward(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw,
   if ((int64_t)tiles_m * a.tiles_n > 0x7fffffff || B > 65535) return HFTA_EUNSUPPORTED;
   const int ktiles = (a.K + 31) / 32;
   const size_t need = conv_ig_fwd_split_bytes(B, Nb, Ci, Co, H, W);
-  a.ksplit = (need && ws && ws_bytes >= need && reinterpret_cast<uintptr_t>(ws) % 16 == 0) ? ig_pick_ksplit((int64_t)tiles_m * a.tiles_n * B, ktiles, false) : 1;
+  a.ksplit = (need && ws && ws_bytes >= need && reinterpret_cast<uintptr_t>(ws) % 16 == 0) ? ig_pick_ksplit((int64_t)tiles_m * a.tiles_n * B, ktiles) : 1;
   a.kt_per_split = (ktiles + a.ksplit - 1) / a.ksplit;
   a.part = reinterpret_cast<float*>(ws);
   a.part_split = (int64_t)Nb * a.o_img;
@@ -826,17 +815,8 @@ bool conv_ig_dx_supported(int Nb, int Ci, int Co, int H, int W, int kh, int kw, 
   return true;
 }
 
-// fp32 partial slices the data gradient wants for its k split (0: no split)
-size_t conv_ig_dx_split_bytes(int B, int Nb, int Ci, int Co, int H, int W) {
-  const int Hq = H / 2, Wq = W / 2, tm = Ci <= 64 ? 64 : 128;
-  if (Hq <= 0 || Wq <= 0) return 0;
-  const int64_t blocks = (int64_t)((Ci + tm - 1) / tm) * (((int64_t)Nb * Hq * Wq + 63) / 64) * 2 * B;
-  const int ks = ig_pick_ksplit(blocks, (Co * 4 + 31) / 32, true);
-  return ks > 1 ? (size_t)ks * Nb * B * Ci * H * W * sizeof(float) : 0;
-}
-
 int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int stride, int pad, const void* Wt,
-               const void* dY, void* dX, void* pack, void* split_ws, hipStream_t st) {
+               const void* dY, void* dX, void* pack, hipStream_t st) {
   if (!conv_ig_dx_supported(Nb, Ci, Co, H, W, kh, kw, stride, pad)) return HFTA_EUNSUPPORTED;
   if (reinterpret_cast<uintptr_t>(dY) % 16 || reinterpret_cast<uintptr_t>(Wt) % 16 || reinterpret_cast<uintptr_t>(dX) % 16 ||
       reinterpret_cast<uintptr_t>(pack) % 16 || B > 65535)
@@ -868,17 +848,11 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   const int64_t count = (int64_t)B * 4 * cls_el / 8;                   // 16-byte fragment pieces
   hipLaunchKernelGGL(ig_pack_class_w_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, (const bf16_raw*)Wt,
                      (bf16_raw*)pack, Ci, Co, tm, tiles_m, ktiles, count);
-  a.ksplit = (split_ws && reinterpret_cast<uintptr_t>(split_ws) % 16 == 0) ? ig_pick_ksplit((int64_t)tiles_m * a.tiles_n * 2 * B, ktiles, true) : 1;
-  a.kt_per_split = (ktiles + a.ksplit - 1) / a.ksplit;
-  a.part = reinterpret_cast<float*>(split_ws);
-  a.part_split = (int64_t)Nb * a.o_img;
-  dim3 grid((unsigned)(tiles_m * a.tiles_n), (unsigned)(2 * a.ksplit), (unsigned)B);
-  const bool planes = dxp_geometry(a) && dxp_lds_bytes(a) <= IG_MAX_LDS;
-  const size_t lds2 = planes ? dxp_lds_bytes(a) : ig_lds_bytes(a, 8, 0);
-  if (lds2 > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
-  if (planes) {
-    const int kt = (Co + DXP_CH - 1) / DXP_CH;
-    a.kt_per_split = (kt + a.ksplit - 1) / a.ksplit;
+  a.ksplit = 1;
+  a.kt_per_split = ktiles;
+  dim3 grid((unsigned)(tiles_m * a.tiles_n), 2u, (unsigned)B);
+  if (dxp_geometry(a)) {
+    const size_t lds2 = dxp_lds_bytes(a);
     const bool few = (int64_t)tiles_m * a.tiles_n * 2 * B < 256;
     if (a.W == 4) {
       if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, true, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<64, true, 1>, grid, 256, lds2, st, a);
@@ -887,18 +861,9 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
       if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<64, false, 1>, grid, 256, lds2, st, a);
       else few ? ig_launch(conv_dx_planes_kernel<128, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds2, st, a);
     }
-  } else if (a.chunk_el == 8) {
-    if (tm == 64) ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 64, true>, grid, 256, lds2, st, a);
-    else ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 128, true>, grid, 256, lds2, st, a);
   } else {
-    if (tm == 64) ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 64, false>, grid, 256, lds2, st, a);
-    else ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 128, false>, grid, 256, lds2, st, a);
-  }
-  if (a.ksplit > 1) {
-    if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
-    const int64_t count8 = a.part_split / 8;
-    hipLaunchKernelGGL(ig_split_finish_kernel, dim3((unsigned)((count8 + 255) / 256)), dim3(256), 0, st, (const float*)a.part,
-                       a.Out, (const bf16_raw*)nullptr, count8, a.part_split, a.ksplit, a.o_m, B * Ci, HFTA_ACT_NONE, 0.f);
+    if (tm == 64) ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 64, false>, grid, 256, lds, st, a);
+    else ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 128, false>, grid, 256, lds, st, a);
   }
   return launch_status();
 }

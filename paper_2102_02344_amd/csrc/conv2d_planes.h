@@ -30,10 +30,10 @@ __global__ __launch_bounds__(256, 2) void conv_dx_planes_kernel(IgArgs p) {
   ig_block(p.grid, bx, by, b);
   const int tile_m = bx / p.tiles_n, tile_n = bx % p.tiles_n;
   const int m0 = tile_m * TM, n0 = tile_n * 64;
-  const int py = by & 1, split = by >> 1;
+  const int py = by;
   const int P = 1 << p.lgP, HW = p.H * p.W;
   const int img0 = n0 >> p.lgP, y0 = (n0 & (P - 1)) >> p.lgWo;
-  const int kt0 = split * p.kt_per_split, kt1 = min((p.Cx + DXP_CH - 1) / DXP_CH, kt0 + p.kt_per_split);
+  const int kt1 = (p.Cx + DXP_CH - 1) / DXP_CH;
   const int img_el = p.PR * p.W;                          // elements of an image's rows in a plane
   const int wm = TM == 128 ? wave >> 1 : 0;
   const int col0 = TM == 128 ? (wave & 1) * 64 : wave * 32, px = col0 >> 6;
@@ -130,14 +130,14 @@ __global__ __launch_bounds__(256, 2) void conv_dx_planes_kernel(IgArgs p) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  fetch(kt0, 0);
-  fetch(kt0 + 1, 1);
+  fetch(0, 0);
+  fetch(1, 1);
 #pragma unroll
   for (int d = 0; d < AD; ++d)
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) load_a(d, kt0 + d, i, s);
+      for (int i = 0; i < 2; ++i) load_a(d, d, i, s);
   if (W4) {                                                // the row above or below the image is never written
     for (int i = t; i < 2 * buf_bytes / 16; i += 256) reinterpret_cast<uint4*>(planes)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void conv_dx_planes_kernel(IgArgs p) {
   raw_read(0);
   plane_write(0);
   bool done = false;
-  for (int base = kt0; !done; base += 2) {
+  for (int base = 0; !done; base += 2) {
 #pragma unroll
     for (int buf = 0; buf < 2; ++buf) {
       const int kt = base + buf, set = buf % AD;
@@ -181,10 +181,11 @@ __global__ __launch_bounds__(256, 2) void conv_dx_planes_kernel(IgArgs p) {
     }
   }
   dma_wait_barrier<0>();
-  ig_epilogue<true, TM, FN>(p, acc, smem, b, split, m0, n0, wm, col0, p.cls[2 * py], t, lane);
+  ig_epilogue<true, TM, FN>(p, acc, smem, b, 0, m0, n0, wm, col0, p.cls[2 * py], t, lane);
 }
 
-// Plane geometry of a data gradient's tiles; false where the kernel does not apply.
+// Plane geometry of a data gradient's tiles; false for images of four-pixel rows taller than a tile, which the gathering
+// kernel keeps.  (Rows of 8 to 64 pixels have 144 to 256 pieces a tile and at most 34 KB of planes.)
 bool dxp_geometry(IgArgs& a) {
   const int P = a.Ho * a.Wo;
   const bool w4 = a.W == 4;
@@ -200,6 +201,6 @@ bool dxp_geometry(IgArgs& a) {
 }
 size_t dxp_lds_bytes(const IgArgs& a) {
   const size_t k_loop = 2 * (size_t)DXP_RAW + 2 * (size_t)3 * a.plp;
-  const size_t staging = a.ksplit > 1 ? 64 * (size_t)132 * 4 : 64 * (size_t)IG_EPI_PITCH;
+  const size_t staging = 64 * (size_t)IG_EPI_PITCH;
   return k_loop > staging ? k_loop : staging;
 }
