@@ -2,13 +2,15 @@
 """Benchmark of the fused training array on one MI355X.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--repeats R] [--workload all|c0|c1|c2|c3|c4|c1t|t0] [--skip-serial] [--skip-cpu]
+                    [--report FILE]
 
 A step is one forward + backward + Adam pass of the whole fused array over one
 synthetic batch that is already resident in HBM.  Prints ONE JSON line:
 fused samples/s summed over the B models (`value`), the same B models run one
 after another through the library with B = 1 (`serial_b1`), the roofline of the
 kernel that dominates the step (timed live with HIP events on the launch stream)
-and the CPU oracle timed on a bounded sample (`cpu_baseline`).
+and the CPU oracle timed on a bounded sample (`cpu_baseline`).  With --report the complete record
+(per-kernel times, the other workloads' legs, the operator table) goes to FILE.
 """
 from __future__ import annotations
 
@@ -690,6 +692,16 @@ def run_workload(name, args, torch, arrays, binding):
     }
 
 
+def brief_line(out):
+    """The record's one line on stdout, short enough for a reader that keeps the last few kilobytes: without the
+    per-kernel times and the operator table, and of the workloads behind the headline their results."""
+    line = {k: v for k, v in out.items() if k not in ("kernels", "kernels_note", "operators", "operators_note", "workloads")}
+    if "workloads" in out:
+        line["workloads"] = {n: {"config": w["config"]["workload"], "value": w["value"], "ms_per_step": w["ms_per_step"],
+                                 "dtype": w["dtype"]} for n, w in out["workloads"].items()}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -698,13 +710,16 @@ def main():
     ap.add_argument("--repeats", type=int, default=3, help="timed regions of --steps steps each; mean / min / max are reported")
     ap.add_argument("--workload", default="all", choices=["all", "c0", "c1", "c1t", "c2", "c3", "c4", "t0"],
                     help="all (default): config 1 as the headline line plus a `workloads` block with configs 0, 2, 3, 4 "
-                         "and the operator table; a name: that workload alone")
+                         "(and, in the --report, the operator table); a name: that workload alone")
     ap.add_argument("--unfused", type=int, default=0,
                     help="config 1 only: run the first K per-point layers (and their share of Adam) model by model "
                          "(partial fusion); the headline line is K = 0")
     ap.add_argument("--skip-serial", action="store_true")
     ap.add_argument("--skip-cpu", action="store_true")
     ap.add_argument("--skip-ops", action="store_true", help="leave the operator table out of the default run")
+    ap.add_argument("--report", default=None,
+                    help="also write the complete record here: every workload's per-kernel times, repeats and serial and "
+                         "CPU legs, and the operator table (the line on stdout holds the headline workload and the others' results)")
     ap.add_argument("--ops-report", default=None,
                     help="also write the operator table (GEMMs at config 4 shapes, conv2d at config 3 shapes) as JSON here")
     ap.add_argument("--copy-ref", action="store_true",
@@ -757,7 +772,10 @@ def main():
             out["operators"] = ops
             out["operators_note"] = ("entry points timed alone with HIP events (120 warm-up + 100 launches): fused Linear at "
                                      "config 4 shapes, grouped conv2d at config 3 shapes, against the dense bf16 MFMA peak")
-    print(json.dumps(out))
+    if args.report:
+        with open(args.report, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(brief_line(out)))
 
 
 if __name__ == "__main__":
