@@ -157,7 +157,9 @@ int hfta_conv1x1_fwd_sample_bias(int B, int Nb, int Ci, int Co, int L, int dtype
  * statistics.  With a workspace of hfta_conv1x1_bn_fwd_workspace_bytes (8-byte aligned) and a bf16
  * layer that the streaming convolution kernel takes, the convolution's epilogue leaves per-slice
  * sums there and Z is read once (for the normalisation) instead of twice; otherwise the two
- * operators run one after the other (no workspace needed).  Y == NULL: only Z and the statistics
+ * operators run one after the other (no workspace needed).  A bf16 layer of at most four input channels on
+ * rows with L % 4 != 0 takes its vector kernel only with that workspace; without it Z is what
+ * hfta_conv1x1_fwd stores.  Y == NULL: only Z and the statistics
  * are produced (a consumer that normalises Z on load follows, see hfta_conv1x1_bn_prenorm_fwd). */
 size_t hfta_conv1x1_bn_fwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
 int hfta_conv1x1_bn_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,

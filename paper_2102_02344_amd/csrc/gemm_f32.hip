@@ -1,7 +1,8 @@
 // fp32 form of the batched GEMM core (same descriptor, same operand kinds as gemm.h).
 //
-// Bound: the fp32 matrix instruction (157 TFLOP/s nominal; a large library product reaches 154 on this
-// card).  One 32x32x2 instruction takes 64 cycles, so LDS and the vector ALU have room and what a k-tile
+// The limit is the fp32 matrix instruction (157 TFLOP/s nominal; a library product of 8192 x 8192 x 8192 reaches 154 on
+// this card); the short reductions it mostly gets (K = 64 and 128) run at 80-120, the rest being a tile's first loads and
+// its epilogue.  One 32x32x2 instruction takes 64 cycles, so LDS and the vector ALU have room and what a k-tile
 // must not do is wait for memory.  Hence: two k-tiles in flight in registers behind the one being
 // multiplied, every load a raw buffer load without control flow (out of range = zeros, see gemm_pf.h);
 // 16-byte pieces whatever the row pitch (a multi-dword access needs 4-byte alignment only, and an fp32 row

@@ -430,6 +430,8 @@ static int conv1x1_fwd_impl(int B, int Nb, int Ci, int Co, int L, int dtype, con
   if (rc != HFTA_OK) return rc;
   if (!X || !W || !Y || !xs || !ys || !valid_act(act)) return HFTA_EINVAL;
   if (xs[3] != 1 || ys[3] != 1) return HFTA_EUNSUPPORTED;
+  // Rows of other lengths take this kernel only in the block form (the caller's statistics workspace): a caller without one
+  // asked for the single operators, whose products keep the matrix kernels' rounding.
   if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && (L % 4 == 0 || (stat_part && L >= 4)) && Nb <= 65535 && B <= 65535) {
     TinyKArgs a{(const bf16_raw*)X, (const bf16_raw*)W, (const bf16_raw*)bias, (bf16_raw*)Y, xs[0], xs[1], xs[2],
                 ys[0], ys[1], ys[2], Ci, Co, L, act, act_slope};

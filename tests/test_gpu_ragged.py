@@ -235,3 +235,47 @@ def test_classification_array_with_weights_off_16_bytes(L):
     assert all(arr.w(f"conv{i}.w").data_ptr() % 16 == 8 for i in range(2, 5))
     assert not arr.fused_tail and not any(arr.prenorm)
     arr.forward_backward(pn.in_place_probe(spec, []))
+
+
+@pytest.mark.parametrize("Ci,Co,L", [(3, 64, 131), (64, 64, 131), (64, 128, 260), (40, 72, 129), (264, 136, 131), (128, 64, 6)])
+def test_padded_rows_on_odd_addresses(hb, Ci, Co, L):
+    """Rows with a gap behind them, from a base that is only 2-byte aligned, give the bits that packed rows on an odd base
+    give (the same kernels: neither is aligned) and leave the gaps alone: the k=1 convolution and its gradients, with and
+    without the BatchNorm in the same call, the activation, and on-load normalisation where the shape has it."""
+    B, Nb, pad = 2, 3, 3
+    f32 = lambda *s: torch.zeros(s, device="cuda")
+    W, bias = dev(hi.snap(hi.normal(741, (B, Co, Ci)) * 0.2, "bf16"), "bf16"), dev(hi.normal(742, (B, Co), "bf16"), "bf16")
+    gamma, beta = dev((1 + 0.2 * hi.normal(743, (B, Co))).astype(np.float32)), dev(hi.normal(744, (B, Co)).astype(np.float32))
+    x, dy = hi.normal(745, (Nb, B * Ci, L), "bf16"), hi.normal(746, (Nb, B * Co, L), "bf16")
+
+    def run(gap):
+        p = L + gap
+        st = lambda C: (C * p, B * C * p, p, 1)
+
+        def rows(C, values=None):
+            buf = torch.full((1 + Nb * B * C * p,), 7.0, dtype=torch.bfloat16, device="cuda")
+            view = buf[1:].view(Nb, B * C, p)
+            if values is not None:
+                view[:, :, :L] = dev(values, "bf16")
+            outs.append((buf, view))
+            return buf[1:]
+
+        outs = []
+        X, dY = rows(Ci, x), rows(Co, dy)
+        Z, Y, Z2, dX, dX2 = rows(Co), rows(Co), rows(Co), rows(Ci), rows(Ci)
+        ws = torch.empty(max(hb.conv1x1_bn_fwd_workspace_bytes(B, Nb, Ci, Co, L, 1), hb.conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, 1),
+                             hb.conv1x1_bn_bwd_workspace_bytes(B, Nb, Ci, Co, L, 1)), dtype=torch.uint8, device="cuda")
+        mean, invstd, rm, rv = f32(B * Co), f32(B * Co), f32(B * Co), f32(B * Co)
+        hb.conv1x1_fwd(B, Nb, Ci, Co, L, 1, X, st(Ci), W, bias, Z2, st(Co), hb.ACT_RELU)
+        hb.conv1x1_bn_fwd(B, Nb, Ci, Co, L, 1, X, st(Ci), W, bias, gamma, beta, 1e-5, 0.1, rm, rv, mean, invstd, Z, st(Co), Y, st(Co),
+                          hb.ACT_RELU, 0.0, ws)
+        dW, db, dW2, db2, dg, dbt = f32(B, Co, Ci), f32(B, Co), f32(B, Co, Ci), f32(B, Co), f32(B, Co), f32(B, Co)
+        hb.conv1x1_bwd(B, Nb, Ci, Co, L, 1, X, st(Ci), W, dY, st(Co), dX, st(Ci), dW, db, ws)
+        hb.conv1x1_bn_bwd(B, Nb, Ci, Co, L, 1, X, st(Ci), W, Z, st(Co), dY, st(Co), gamma, beta, mean, invstd, dX2, st(Ci), dW2, db2,
+                          dg, dbt, hb.ACT_RELU, 0.0, ws)
+        for buf, view in outs:
+            assert float(buf[0]) == 7.0 and bool((view[:, :, L:] == 7.0).all())
+        return [v[:, :, :L].clone() for _, v in outs] + [mean, invstd, rm, rv, dW, db, dW2, db2, dg, dbt]
+
+    for a, c in zip(run(0), run(pad)):
+        assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, c)
