@@ -93,7 +93,7 @@ def kernel_label(name, a):
         return f"{name}_{lay}_kernel"
     if name == "conv1x1_bn_fwd":
         B, Nb, Ci, Co, L, dt = a[:6]
-        if dt == 1 and Ci % 8 == 0 and L % 4 == 0 and ((Ci <= 128 and Co >= 64) or (Ci <= 256 and Co >= 512)):
+        if dt == 1 and Ci % 8 == 0 and L >= 4 and ((Ci <= 128 and Co >= 64) or (Ci <= 256 and Co >= 512)):
             return "conv1x1_bn_fwd: conv1x1_stream_kernel(+statistics) + bn_stats_part_kernel (+ bn_apply_conv_kernel)"
         return "conv1x1_bn_fwd: conv1x1 kernel (batched GEMM, + statistics in its 256x256 form; K <= 4: vector kernel) + BatchNorm kernels"
     if name == "conv1x1_bn_prenorm_fwd":     # the same kernels as the plain call, the input normalised on load
@@ -102,33 +102,33 @@ def kernel_label(name, a):
         return "conv1x1_bn_bwd: bn_bwd_conv_coef_kernel or bn_bwd_coef_sums_kernel + cbb_kernel + cbb_reduce_kernel"
     if name == "conv1x1_bn_bwd":
         B, Nb, Ci, Co, L, dt = a[:6]
-        if dt == 1 and Ci <= 128 and Co <= 128 and L % 4 == 0:
+        if dt == 1 and Ci <= 128 and Co <= 128 and L >= 4:
             return "conv1x1_bn_bwd: bn_bwd_conv_coef_kernel or bn_bwd_coef_sums_kernel + cbb_kernel + cbb_reduce_kernel"
         return "conv1x1_bn_bwd: bn_bwd_conv_kernel + conv1x1 backward kernels"
     if name == "conv1x1_fwd":
         B, Nb, Ci, Co, L, dt = a[:6]
         if dt == 1 and Ci <= 4 and L % 4 == 0:
             return "conv1x1_tinyk_kernel"
-        if dt == 1 and Ci % 8 == 0 and L % 4 == 0 and ((Ci <= 128 and Co >= 64) or (Ci <= 256 and Co >= 512)):
+        if dt == 1 and Ci % 8 == 0 and L >= 4 and ((Ci <= 128 and Co >= 64) or (Ci <= 256 and Co >= 512)):
             return "conv1x1_stream_kernel"
         if dt == 1 and big_gemm(B * Nb, Co, L, Ci):
             return big_name(B * Nb, Co, L) + "(fwd)"
-        return "gemm_pf_kernel(fwd)" if dt == 1 else "gemm_kernel(fwd)"
+        return small_gemm(dt) + "(fwd)"
     if name == "linear_fwd_ws" and a[1] <= 64:
-        return ("gemm_pf_kernel" if a[4] == 1 else "gemm_kernel") + "(fwd, split)+splitk_bias_act_kernel"
+        return ("gemm_pf_kernel" if a[4] == 1 else "gemm_f32_kernel") + "(fwd, split)+splitk_bias_act_kernel"
     if name in ("linear_fwd", "linear_fwd_ws"):
         if a[4] == 1 and big_gemm(a[0], a[1], a[3], a[2]):
             return big_name(a[0], a[1], a[3]) + "(fwd)"
-        return "gemm_pf_kernel(fwd)" if a[4] == 1 else "gemm_kernel(fwd)"
+        return small_gemm(a[4]) + "(fwd)"
     if name == "linear_bwd":           # the MLP array asks for dX, dW and dbias in separate calls
         B, M, Fx, Fy, dt = a[:5]
         if a[8] is not None and a[9] is not None:      # one call for everything (the Transformer array)
-            return "linear_bwd: gemm(dX) + gemm(dW) + splitk_reduce_kernel + colsum_kernel"
+            return "linear_bwd: gemm(dX) + gemm(dW, with dY's column sums where its kernel takes them)"
         if a[8] is not None:
-            return (big_name(B, M, Fx) if dt == 1 and big_gemm(B, M, Fx, Fy) else "gemm_pf_kernel") + "(dX)"
+            return (big_name(B, M, Fx) if dt == 1 and big_gemm(B, M, Fx, Fy) else small_gemm(dt)) + "(dX)"
         if a[9] is not None:
             sp = big_splits(B, Fx, Fy, M) if dt == 1 else 0
-            return (big_name(B, Fx, Fy, sp) if sp else "gemm_pf_kernel") + "(dW)"
+            return (big_name(B, Fx, Fy, sp) if sp else small_gemm(dt)) + "(dW)"
         return "colsum_kernel"
     if name == "layernorm_bwd_sums":
         return "layernorm_bwd_kernel"
@@ -137,6 +137,9 @@ def kernel_label(name, a):
     if name in ("act_fwd", "act_bwd", "act_bwd_colsum", "add", "layernorm_fwd", "layernorm_bwd", "bias_act_nchw"):
         return name + "_kernel"
     if name in ("attention_fwd", "attention_bwd"):
+        S, E, H, dt = a[2:6]
+        if dt == 1 and E // H % 8 == 0 and E // H <= 64 and S <= 256:
+            return "attn_%s_kernel" % name[-3:]
         return name + ": batched head GEMMs + softmax_rows kernel"
     if name in ("embedding_fwd", "embedding_bwd", "softmax_xent"):
         return name + "_kernel"
@@ -165,7 +168,7 @@ def kernel_label(name, a):
                 return small % "dx"
             if dt == 1 and (kh, kw, stride, pad) == (4, 4, 2, 1) and Ci <= 4:
                 return "conv_dx_fewc_kernel"
-            return ("ig_pack_class_w_kernel + conv_ig_fwd_kernel<2,2,1,pair>" if ig and Ci >= 32
+            return ("ig_pack_class_w_kernel + conv_dx_planes_kernel" if ig and Ci >= 32
                     else "conv2d dX: pack_dy_kernel + gemm + col2im_lds_kernel")
         if full:
             return small % "dw"
@@ -173,9 +176,9 @@ def kernel_label(name, a):
                 else "conv2d dW: pack_dy_kernel + im2col_lds_kernel + gemm")
     if name == "conv1x1_bwd":          # called with either dX or dW requested, never both
         B, Nb, Ci, Co, L, dt = a[:6]
-        k = "gemm_pf_kernel" if dt == 1 else "gemm_kernel"
+        k = small_gemm(dt)
         if a[11] is not None:
-            if (dt == 1 and Co % 8 == 0 and L % 4 == 0 and a[15] is not None
+            if (dt == 1 and Co % 8 == 0 and L >= 4 and a[15] is not None
                     and ((Co <= 128 and Ci >= 64) or (Co <= 256 and Ci >= 512))):
                 return "conv1x1_stream_kernel(dX)"
             return (big_name(B * Nb, Ci, L) if dt == 1 and big_gemm(B * Nb, Ci, L, Co) else k) + "(dX)"
@@ -192,6 +195,11 @@ def kernel_label(name, a):
         return "conv1x1_bn_maxpool_bwd: cbp_dx_kernel + 5 small" + ("" if saved is not None else " + gram_kernel")
     return {"maxpool_points": "maxpool_fwd_kernel", "maxpool_points_bwd": "maxpool_bwd_kernel",
             "adam_step_multi": "adam_multi_kernel"}[name]
+
+
+def small_gemm(dt):
+    """What products below the 256x256-tile kernel's sizes run in (bf16: by tiles and length, see gemm_dma.hip)."""
+    return "gemm_pf_kernel or gemm_dma_kernel" if dt == 1 else "gemm_f32_kernel"
 
 
 def big_gemm(G, M, N, K):
