@@ -9,7 +9,6 @@ is missing the import fails.
 from __future__ import annotations
 
 import ctypes as C
-import functools
 import os
 from typing import Optional, Sequence
 
@@ -150,17 +149,25 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+_stride_arrays = {}
+
+
 def _strides(s: Optional[Sequence[int]], n: int = 4):
+    """The host array a call reads its strides from (the library only reads it), kept for tuples of plain ints: anything
+    else (a list, numbers that could change in place) is converted on every call."""
     if s is None:
         return None
-    return _strides_of(tuple(s), n)
-
-
-@functools.lru_cache(maxsize=4096)
-def _strides_of(s: tuple, n: int):
-    """The host array a call reads its strides from (the library only reads it)."""
+    try:
+        return _stride_arrays[s, n]
+    except (KeyError, TypeError):
+        pass
     assert len(s) == n, (s, n)
-    return (C.c_int64 * n)(*[int(v) for v in s])
+    a = (C.c_int64 * n)(*[int(v) for v in s])
+    if type(s) is tuple and all(type(v) is int for v in s):
+        if len(_stride_arrays) >= 4096:
+            _stride_arrays.clear()
+        _stride_arrays[s, n] = a
+    return a
 
 
 def _current_stream() -> int:

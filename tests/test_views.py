@@ -3,6 +3,7 @@ took a buffer's place, and after the buffer itself was given other memory."""
 import torch
 
 from paper_2102_02344_amd import arrays
+from paper_2102_02344_amd import binding as hb
 
 
 def _arena():
@@ -34,3 +35,13 @@ def test_cuts_follow_their_buffer():
     assert a._cut(buf, 5).tolist() == list(range(5)) and a._cut(buf, 5) is a._cut(buf, 5)
     buf.data = torch.full((16,), 4.0)
     assert a._cut(buf, 5).data_ptr() == buf.data_ptr() and a._cut(buf, 5).tolist() == [4.0] * 5
+
+
+def test_strides_are_read_on_every_call():
+    """Numbers that can change in place are not remembered by the object that holds them."""
+    step = torch.tensor(7)
+    s = (step, step, torch.tensor(3), torch.tensor(1))
+    assert list(hb._strides(s)) == [7, 7, 3, 1]
+    step.fill_(9)
+    assert list(hb._strides(s)) == [9, 9, 3, 1] and list(hb._strides([1, 2, 3], 3)) == [1, 2, 3]
+    assert hb._strides((4, 3, 2, 1)) is hb._strides((4, 3, 2, 1)) and hb._strides(None) is None
