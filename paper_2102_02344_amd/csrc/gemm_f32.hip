@@ -1,26 +1,40 @@
 // fp32 form of the batched GEMM core (same descriptor, same operand kinds as gemm.h).
 //
-// The limit is the fp32 matrix instruction (157 TFLOP/s nominal; a library product of 8192 x 8192 x 8192 reaches 154 on
-// this card); the short reductions it mostly gets (K = 64 and 128) run at 80-120, the rest being a tile's first loads and
-// its epilogue.  One 32x32x2 instruction takes 64 cycles, so LDS and the vector ALU have room and what a k-tile
-// must not do is wait for memory.  Hence: two k-tiles in flight in registers behind the one being
-// multiplied, every load a raw buffer load without control flow (out of range = zeros, see gemm_pf.h);
-// 16-byte pieces whatever the row pitch (a multi-dword access needs 4-byte alignment only, and an fp32 row
-// has that), the piece that straddles a row's end read from where the row's last four elements start and
-// moved into place on its way into LDS.  An operand contiguous along m / n stays in its natural [k][n]
-// layout in LDS: a lane's fragment is one float, so 32 lanes read 32 neighbouring banks.
+// The fp32 matrix instruction reaches 154 TFLOP/s here (a library product of 8192 x 8192 x 8192); the bf16 one does
+// sixteen times the work per cycle, and an fp32 value IS the sum of three bf16 ones: h, the value rounded, m, the rest
+// rounded, l, what is left (8 + 8 + 8 bits).  Six of the nine products of two such sums are formed (hh, hm, mh, hl, mm,
+// lh; the others are below 2^-26 of the product), in fp32 accumulators, for 6/16 of the fp32 instruction's time.
+// The corrections have accumulators of their own: the bf16 instruction truncates its sum, and in one accumulator six
+// truncations per 16 k of a long weight gradient left a larger error (1.5e-6) than the fp32 instruction's roundings
+// (1.3e-6); in two it is 4.4e-7.  Measured for 128 -> 1024 channels on 4 x 32 x 2500 points, in the step: data gradient
+// 696 -> 520 us, weight gradient 693 -> 499, forward 815 -> 782 (four k-tiles a tile: bound by a tile's first loads and
+// its stores); relative errors against float64 5.7e-7 -> 1.9e-7, 1.3e-6 -> 4.4e-7, 2.0e-7 -> 6.5e-8.  On 2 x 4 x 256
+// points the data gradient's 64 workgroups take 27 us instead of 39.
+// A value is split once, on its way into LDS, whose tiles are three bf16 planes per operand.
 //
-// NB: matrix blocks per wavefront and dimension.  NB = 2 (128x128 tile): the throughput form.  NB = 1 (64x64
-// tile): four times the workgroups, a quarter of the matrix instructions per k-tile, for problems that would
-// leave compute units idle.  VEC = false: single-element loads, for operands with fewer than four elements
-// along their contiguous dimension.
+// The sum of three needs a finite value that is not tiny: an infinity or a NaN has no remainder, nor has what rounds up
+// to infinity, and below 2^-110 the last part falls under bf16's smallest numbers.  Both are noticed while splitting
+// (the remainder is NaN; a smallest magnitude is kept), and a workgroup that has seen one takes its tile again from the
+// start with fp32 matrix instructions (`exact_loop`).  Operands with fewer than four elements along their contiguous
+// dimension (VEC = 0, single-element loads) have that loop only.
+//
+// Every load is a raw buffer load without control flow (out of range = zeros, see gemm_pf.h), in 16-byte pieces whatever
+// the row pitch (a multi-dword access needs 4-byte alignment only, and an fp32 row has that).  VEC = 2: no piece straddles
+// a row's end, so the k-loop's body is one straight block.  VEC = 1: one that does is read from where the row's last four
+// elements start and moved into place on its way into LDS.
+//
+// NB: matrix blocks per wavefront and dimension.  NB = 2 (128x128 tile): the throughput form; its two sets of
+// accumulators leave two workgroups per compute unit, each with one k-tile in flight in registers and one in LDS (two of
+// 16 k each were 0-7 % slower: half a line of a k-contiguous row at a time).  NB = 1 (64x64 tile, two k-tiles each):
+// four times the workgroups, for problems that would leave compute units idle.
 #include "gemm_pf.h"
 
 namespace hfta {
 
 namespace {
 
-constexpr int F32_BK = GemmT<float>::BK;                   // 16 floats of k per tile
+constexpr int F32_BK = 32;                                 // floats of k per tile: a whole 128-byte line of a k-contiguous row
+constexpr int F32_TINY = (27 << 8) - 1;                     // 2 * bits - 1 of 2^-100 in bf16: smaller (but zero) is not split
 constexpr int F32_SMALL_TILES = 512;                       // fewer 128x128 tiles than this: 64x64 tiles
 typedef uint32_t pf_u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -39,28 +53,69 @@ __device__ __forceinline__ float ld_f1(__amdgpu_buffer_rsrc_t rs, uint32_t off) 
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
 }
 
-template <bool KC, int NB, bool VEC> struct F32Operand;
+// Four values as three planes of four bf16.  `chk` becomes NaN if one has no finite remainder; `low` holds the smallest
+// magnitude but zero (as 2 * bits - 1 of the first part: zero wraps to the largest).
+typedef unsigned short f32s_u16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 f32s_bf16x2 __attribute__((ext_vector_type(2)));
+struct SplitSeen {
+  float chk = 0.f;
+  f32s_u16x2 low = {0xffff, 0xffff};
+  __device__ __forceinline__ bool bad() const { return chk != chk || min(low.x, low.y) < F32_TINY; }
+};
+// the rounded pair; x and y become what it leaves (exact: a two-element dot product with -1 and 0)
+__device__ __forceinline__ uint32_t split_pair(float& x, float& y) {
+  const uint32_t w = pack_bf16x2(x, y);
+  const f32s_bf16x2 h = __builtin_bit_cast(f32s_bf16x2, w);
+  uint32_t cx, cy;
+  asm("s_mov_b32 %0, 0xbf80" : "=s"(cx));
+  asm("s_mov_b32 %0, 0xbf800000" : "=s"(cy));
+  x = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(f32s_bf16x2, cx), x, false);
+  y = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(f32s_bf16x2, cy), y, false);
+  return w;
+}
+__device__ __forceinline__ void split4(const float4& v, uint2 (&o)[3], SplitSeen& seen) {
+  float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    o[q].x = split_pair(e[0], e[1]);
+    o[q].y = split_pair(e[2], e[3]);
+  }
+  o[2].x = pack_bf16x2(e[0], e[1]);
+  o[2].y = pack_bf16x2(e[2], e[3]);
+  const f32s_bf16x2 ones = __builtin_bit_cast(f32s_bf16x2, 0x3f803f80u);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t h = i ? o[0].y : o[0].x, l = i ? o[2].y : o[2].x;
+    seen.low = __builtin_elementwise_min(seen.low, __builtin_bit_cast(f32s_u16x2, h) * (unsigned short)2 - (unsigned short)1);
+    seen.chk = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(f32s_bf16x2, l), ones, seen.chk, false);
+  }
+}
 
-// k-contiguous: LDS [row][16 k + 4 pad]; thread t stages 4-float group t%4 of rows t/4 (+ 64)
-template <int NB, bool VEC> struct F32Operand<true, NB, VEC> {
-  static constexpr int BYTES = 64 * NB * GEMM_PITCH;
-  typedef float4 Regs[NB];
-  uint32_t off[NB];
+template <bool KC, int NB, int VEC> struct F32Operand;
+
+// k-contiguous: thread t stages 4-float group t % PR of rows t / PR + h * RPI
+template <int NB, int VEC> struct F32Operand<true, NB, VEC> {
+  static constexpr int BK = F32_BK, PR = BK / 4, RPI = GEMM_THREADS / PR, H = 64 * NB / RPI;
+  static constexpr int PITCH = BK * 4 + 16;                // fp32 tile: [row][BK k + 4 pad]
+  static constexpr int BYTES = 64 * NB * PITCH;
+  static constexpr int PLANE = 64 * NB * BK * 2;           // bf16 plane: [row][BK k], 16-byte pieces permuted
+  typedef float4 Regs[H];
+  uint32_t off[H];
   int kg;
   __device__ __forceinline__ void init(int row0, int rows, int64_t ld, int t) {
-    kg = (t & 3) * 4;
+    kg = (t % PR) * 4;
 #pragma unroll
-    for (int h = 0; h < NB; ++h) {
-      const int r = row0 + (t >> 2) + 64 * h;
+    for (int h = 0; h < H; ++h) {
+      const int r = row0 + t / PR + RPI * h;
       off[h] = r < rows ? (uint32_t)((int64_t)r * ld * 4) : PF_OOB;
     }
   }
   __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
     const int k = k0 + kg;
 #pragma unroll
-    for (int h = 0; h < NB; ++h) {
+    for (int h = 0; h < H; ++h) {
       if (VEC) {
-        q[h] = ld_f4(rs, k < K ? off[h] + (uint32_t)min(k, K - 4) * 4u : PF_OOB);
+        q[h] = ld_f4(rs, k < K ? off[h] + (uint32_t)(VEC == 2 ? k : min(k, K - 4)) * 4u : PF_OOB);
       } else {
         float e[4];
 #pragma unroll
@@ -69,33 +124,53 @@ template <int NB, bool VEC> struct F32Operand<true, NB, VEC> {
       }
     }
   }
-  // tail: the k-tile reaches past K (the same for the whole workgroup)
-  __device__ __forceinline__ void store(unsigned char* tile, Regs& q, int t, int k0, int K) const {
-    if (VEC && k0 + F32_BK > K) {
+  // the k-tile reaches past K (the same for the whole workgroup)
+  __device__ __forceinline__ void place(Regs& q, int k0, int K) const {
+    if (VEC == 1 && k0 + BK > K) {
       const int k = k0 + kg, sh = k < K ? k - min(k, K - 4) : 0;
 #pragma unroll
-      for (int h = 0; h < NB; ++h) q[h] = shift_piece(q[h], sh);
+      for (int h = 0; h < H; ++h) q[h] = shift_piece(q[h], sh);
     }
+  }
+  __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t) const {
 #pragma unroll
-    for (int h = 0; h < NB; ++h) *reinterpret_cast<float4*>(tile + ((t >> 2) + 64 * h) * GEMM_PITCH + kg * 4) = q[h];
+    for (int h = 0; h < H; ++h) *reinterpret_cast<float4*>(tile + (t / PR + RPI * h) * PITCH + kg * 4) = q[h];
   }
   // the four k of step s for row base + lane%32: k = 8 s + 4 (lane/32) + j
   static __device__ __forceinline__ void frag(float (&f)[4], const unsigned char* tile, int base, int s, int lane) {
-    const float4 v = *reinterpret_cast<const float4*>(tile + (base + (lane & 31)) * GEMM_PITCH + (2 * s + (lane >> 5)) * 16);
+    const float4 v = *reinterpret_cast<const float4*>(tile + (base + (lane & 31)) * PITCH + (2 * s + (lane >> 5)) * 16);
     f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+  }
+  // 16-byte piece p of row r sits at p ^ swz(r): sixteen rows' pieces of one k cover the 64 banks once
+  static __device__ __forceinline__ int swz(int r) { return (r >> 2) & 3; }
+  __device__ __forceinline__ void store_split(unsigned char* tile, const Regs& q, int t, SplitSeen& seen) const {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      uint2 o[3];
+      split4(q[h], o, seen);
+      const int r = t / PR + RPI * h;
+      unsigned char* d = tile + r * (BK * 2) + (((kg >> 3) ^ swz(r)) << 4) + (kg & 4) * 2;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(d + i * PLANE) = o[i];
+    }
+  }
+  // bf16 fragment of plane `pl`: lane l holds row base + l%32 and k = 16 s + 8 (l/32) + 0..7
+  static __device__ __forceinline__ bf16x8_t frag16(const unsigned char* tile, int pl, int base, int s, int lane) {
+    const int r = base + (lane & 31);
+    return *reinterpret_cast<const bf16x8_t*>(tile + pl * PLANE + r * (BK * 2) + (((2 * s + (lane >> 5)) ^ swz(r)) << 4));
   }
 };
 
-// m/n-contiguous: LDS [16 k][64 NB columns + 8 pad]; k-rows four apart (the two lane halves of a fragment read)
-// are 32 banks apart.  NB = 2: thread t stages columns 4 (t % 32) .. of k-rows t/32 and t/32 + 8; NB = 1: columns
-// 4 (t % 16) .. of k-row t/16.
-template <int NB, bool VEC> struct F32Operand<false, NB, VEC> {
-  static constexpr int PITCH = (64 * NB + 8) * 4;          // 4 rows = 4 * 136 (or 72) dwords = 32 banks mod 64
-  static constexpr int BYTES = F32_BK * PITCH;
-  static constexpr int CG = 16 * NB, RS = GEMM_THREADS / CG;
-  typedef float4 Regs[NB];
+// m/n-contiguous: natural [k][column] layout; thread t stages columns 4 (t % CG) .. of k-rows t / CG + h * RS
+template <int NB, int VEC> struct F32Operand<false, NB, VEC> {
+  static constexpr int BK = F32_BK, COLS = 64 * NB;
+  static constexpr int PITCH = (COLS + 8) * 4;             // fp32 tile: k-rows four apart are 32 banks apart
+  static constexpr int BYTES = BK * PITCH;
+  static constexpr int PLANE = BK * COLS * 2;              // bf16 plane: [k][column], 16-byte pieces permuted
+  static constexpr int CG = COLS / 4, RS = GEMM_THREADS / CG, H = BK / RS;
+  typedef float4 Regs[H];
   uint32_t ldb;
-  uint32_t coff;                                           // byte offset of the piece's column, or PF_OOB
+  uint32_t coff;                                           // byte offset of the piece in k-row kr, or PF_OOB
   int kr, sh;
   __device__ __forceinline__ void init(int col0, int cols, int64_t ld, int t) {
     ldb = (uint32_t)(ld * 4);
@@ -103,39 +178,67 @@ template <int NB, bool VEC> struct F32Operand<false, NB, VEC> {
     const int c = col0 + (t % CG) * 4;
     if (VEC) {
       const int cc = min(c, cols - 4);
-      coff = c < cols ? (uint32_t)cc * 4u : PF_OOB;
+      coff = c < cols ? (uint32_t)kr * ldb + (uint32_t)cc * 4u : PF_OOB;
       sh = c < cols ? c - cc : 0;
     } else {
-      coff = (uint32_t)c * 4u;
+      coff = (uint32_t)kr * ldb + (uint32_t)c * 4u;
       sh = cols - c;                                       // elements of the piece that exist (may exceed four)
     }
   }
   __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
 #pragma unroll
-    for (int h = 0; h < NB; ++h) {
-      const int k = k0 + kr + RS * h;
+    for (int h = 0; h < H; ++h) {
+      const bool in = k0 + kr + RS * h < K;
+      const uint32_t o = coff + (uint32_t)(k0 + RS * h) * ldb;             // slices are below 2 GiB
       if (VEC) {
-        q[h] = ld_f4(rs, k < K && coff != PF_OOB ? (uint32_t)k * ldb + coff : PF_OOB);
+        q[h] = ld_f4(rs, in && coff != PF_OOB ? o : PF_OOB);
       } else {
         float e[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = ld_f1(rs, k < K && i < sh ? (uint32_t)k * ldb + coff + 4u * i : PF_OOB);
+        for (int i = 0; i < 4; ++i) e[i] = ld_f1(rs, in && i < sh ? o + 4u * i : PF_OOB);
         q[h] = make_float4(e[0], e[1], e[2], e[3]);
       }
     }
   }
-  __device__ __forceinline__ void store(unsigned char* tile, Regs& q, int t, int, int) const {
-    if (VEC && __any(sh != 0)) {
+  __device__ __forceinline__ void place(Regs& q, int, int) const {
+    if (VEC == 1 && __any(sh != 0)) {
 #pragma unroll
-      for (int h = 0; h < NB; ++h) q[h] = shift_piece(q[h], sh);
+      for (int h = 0; h < H; ++h) q[h] = shift_piece(q[h], sh);
     }
+  }
+  __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t) const {
 #pragma unroll
-    for (int h = 0; h < NB; ++h) *reinterpret_cast<float4*>(tile + (kr + RS * h) * PITCH + (t % CG) * 16) = q[h];
+    for (int h = 0; h < H; ++h) *reinterpret_cast<float4*>(tile + (kr + RS * h) * PITCH + (t % CG) * 16) = q[h];
   }
   static __device__ __forceinline__ void frag(float (&f)[4], const unsigned char* tile, int base, int s, int lane) {
     const unsigned char* a = tile + (8 * s + 4 * (lane >> 5)) * PITCH + (base + (lane & 31)) * 4;
 #pragma unroll
     for (int j = 0; j < 4; ++j) f[j] = *reinterpret_cast<const float*>(a + j * PITCH);
+  }
+  // piece p of k-row k sits at p ^ swz(k): the four k-rows of a transpose read cover the 64 banks once
+  static __device__ __forceinline__ int swz(int k) { return NB == 2 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; }
+  __device__ __forceinline__ void store_split(unsigned char* tile, const Regs& q, int t, SplitSeen& seen) const {
+    const int c4 = t % CG;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      uint2 o[3];
+      split4(q[h], o, seen);
+      const int k = kr + RS * h;
+      unsigned char* d = tile + k * (COLS * 2) + (((c4 >> 1) ^ swz(k)) << 4) + (c4 & 1) * 8;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(d + i * PLANE) = o[i];
+    }
+  }
+  // through the LDS transpose read (see gemm_pf.h)
+  static __device__ __forceinline__ bf16x8_t frag16(const unsigned char* tile, int pl, int base, int s, int lane) {
+    const int r16 = lane & 15, k = 8 * (lane >> 5) + (r16 >> 2);           // + 16 s: the same position pattern
+    const int piece = (base >> 3) + 2 * ((lane >> 4) & 1) + ((r16 & 3) >> 1);
+    const unsigned char* a0 = tile + pl * PLANE + (16 * s + k) * (COLS * 2) + ((piece ^ swz(k)) << 4) + (r16 & 1) * 8;
+    typedef __attribute__((address_space(3))) pf_v4s* lds_v4s;
+    union { pf_v4s h[2]; bf16x8_t v; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(a0));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(a0 + 4 * (COLS * 2)));
+    return u.v;
   }
 };
 
@@ -145,14 +248,14 @@ constexpr int f32_smem_bytes(int tiles) {
   return tiles > epi ? tiles : epi;
 }
 
-template <bool A_KC, bool B_KC, int NB, bool VEC>
-__global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_f32_kernel(GemmArgs p) {
+template <bool A_KC, bool B_KC, int NB, int VEC, bool SPLIT>
+__global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f32_kernel(GemmArgs p) {
   typedef F32Operand<A_KC, NB, VEC> OA;
   typedef F32Operand<B_KC, NB, VEC> OB;
-  constexpr int T = 64 * NB, PF = 2;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[f32_smem_bytes<NB>(2 * (OA::BYTES + OB::BYTES))];
-  auto at = [&](int buf) { return smem + buf * OA::BYTES; };
-  auto bt = [&](int buf) { return smem + 2 * OA::BYTES + buf * OB::BYTES; };
+  constexpr int T = 64 * NB, BK = F32_BK;
+  constexpr int PF = NB == 2 && SPLIT ? 1 : 2;             // k-tiles in flight in registers = LDS buffers
+  constexpr int EXACT = PF * (OA::BYTES + OB::BYTES), PLANES = SPLIT ? PF * 3 * (OA::PLANE + OB::PLANE) : 0;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[f32_smem_bytes<NB>(PLANES > EXACT ? PLANES : EXACT)];
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -175,13 +278,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_f32_kernel(GemmArgs p) {
   const int t_begin = (int)((int64_t)p.total_tiles * split / p.splits);
   const int t_end = (int)((int64_t)p.total_tiles * (split + 1) / p.splits);
 
-  f32x16_t acc[NB][NB];
+  f32x16_t acc[NB][NB], low[NB][NB];
+  auto clear = [&]() {
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
+  };
 
   OA oa;
   OB ob;
@@ -189,55 +294,126 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_f32_kernel(GemmArgs p) {
   ob.init(n0, p.N, p.b_ld, t);
   typename OA::Regs ra[PF];
   typename OB::Regs rb[PF];
-  auto k_of = [&](int tt) { return (tt % p.tiles_per_seg) * F32_BK; };
-  auto issue = [&](int set, int tt) {
-    const bool live = tt < t_end;
-    const int Ke = live ? p.K : 0;                         // a dead tile has no valid k: nothing is requested
-    const int tc = live ? tt : t_begin;
-    const int seg = tc / p.tiles_per_seg;
-    const int k0 = (tc - seg * p.tiles_per_seg) * F32_BK;
-    oa.load(ra[set], pf_rsrc(Ab + seg * p.a_ss, p.a_extent), k0, Ke);
-    ob.load(rb[set], pf_rsrc(Bb + seg * p.b_ss, p.b_extent), k0, Ke);
+  // the loader's k-tile: segment base and k0, stepped without a division; past the end nothing is requested
+  const float *la, *lb;
+  int lk, lt;
+  auto aim = [&](int tt) {
+    const int seg = tt / p.tiles_per_seg;
+    la = Ab + seg * p.a_ss;
+    lb = Bb + seg * p.b_ss;
+    lk = (tt - seg * p.tiles_per_seg) * BK;
+    lt = tt;
   };
-
-  if (t_begin < t_end) {
+  auto issue = [&](int set) {
+    const int Ke = lt < t_end ? p.K : 0;
+    oa.load(ra[set], pf_rsrc(la, p.a_extent), lk, Ke);
+    ob.load(rb[set], pf_rsrc(lb, p.b_extent), lk, Ke);
+    lk += BK;
+    const bool wrap = lk >= p.K;
+    la += wrap ? p.a_ss : 0;
+    lb += wrap ? p.b_ss : 0;
+    lk = wrap ? 0 : lk;
+    ++lt;
+  };
+  // the reduction over [t_begin, t_end): `park` puts a register set into an LDS buffer, `multiply` takes a buffer
+  auto reduce = [&](auto park, auto multiply) {
+    clear();
+    if (t_begin >= t_end) return;
+    int sk = (t_begin % p.tiles_per_seg) * BK;             // k0 of the tile about to be parked
+    auto stage = [&](int buf, int set) {
+      oa.place(ra[set], sk, p.K);
+      ob.place(rb[set], sk, p.K);
+      sk = sk + BK >= p.K ? 0 : sk + BK;
+      park(buf, set);
+    };
+    aim(t_begin);
 #pragma unroll
-    for (int d = 0; d < PF; ++d) issue(d, t_begin + d);
-    oa.store(at(0), ra[0], t, k_of(t_begin), p.K);
-    ob.store(bt(0), rb[0], t, k_of(t_begin), p.K);
-    __syncthreads();
-    int buf = 0;
-    bool done = false;
-    for (int base = t_begin; !done; base += PF) {
-#pragma unroll
-      for (int d = 0; d < PF; ++d) {
-        const int cur = base + d;
-        issue(d, cur + PF);
-        const unsigned char* As = at(buf);
-        const unsigned char* Bs = bt(buf);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          float a[NB][4], b[NB][4];
-#pragma unroll
-          for (int i = 0; i < NB; ++i) {
-            OA::frag(a[i], As, wm * 32 * NB + i * 32, s, lane);
-            OB::frag(b[i], Bs, wn * 32 * NB + i * 32, s, lane);
-          }
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-              for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][k], a[i][k], acc[i][j], 0, 0, 0);
-        }
-        if (cur + 1 >= t_end) { done = true; break; }
-        oa.store(at(buf ^ 1), ra[(d + 1) % PF], t, k_of(cur + 1), p.K);
-        ob.store(bt(buf ^ 1), rb[(d + 1) % PF], t, k_of(cur + 1), p.K);
+    for (int d = 0; d < PF; ++d) issue(d);
+    if constexpr (PF == 1) {
+      for (int cur = t_begin; cur < t_end; ++cur) {
+        if (cur != t_begin) __syncthreads();
+        stage(0, 0);
         __syncthreads();
-        buf ^= 1;
+        issue(0);
+        multiply(0);
+      }
+    } else {
+      stage(0, 0);
+      __syncthreads();
+      for (int cur = t_begin;; cur += 2) {
+        bool done = false;
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+          issue(d);
+          multiply(d);
+          stage(d ^ 1, d ^ 1);                             // past the end: zeros that nobody reads
+          __syncthreads();
+          if (cur + d + 1 >= t_end) { done = true; break; }
+        }
+        if (done) break;
       }
     }
     __syncthreads();
+  };
+  auto exact_loop = [&]() {
+    auto at = [&](int buf) { return smem + buf * OA::BYTES; };
+    auto bt = [&](int buf) { return smem + PF * OA::BYTES + buf * OB::BYTES; };
+    reduce([&](int buf, int set) { oa.store(at(buf), ra[set], t); ob.store(bt(buf), rb[set], t); },
+           [&](int buf) {
+#pragma unroll
+             for (int s = 0; s < BK / 8; ++s) {
+               float a[NB][4], b[NB][4];
+#pragma unroll
+               for (int i = 0; i < NB; ++i) {
+                 OA::frag(a[i], at(buf), wm * 32 * NB + i * 32, s, lane);
+                 OB::frag(b[i], bt(buf), wn * 32 * NB + i * 32, s, lane);
+               }
+#pragma unroll
+               for (int k = 0; k < 4; ++k)
+#pragma unroll
+                 for (int i = 0; i < NB; ++i)
+#pragma unroll
+                   for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][k], a[i][k], acc[i][j], 0, 0, 0);
+             }
+           });
+  };
+  if constexpr (SPLIT) {
+    SplitSeen seen;
+    auto at = [&](int buf) { return smem + buf * 3 * OA::PLANE; };
+    auto bt = [&](int buf) { return smem + PF * 3 * OA::PLANE + buf * 3 * OB::PLANE; };
+    reduce([&](int buf, int set) { oa.store_split(at(buf), ra[set], t, seen); ob.store_split(bt(buf), rb[set], t, seen); },
+           [&](int buf) {
+#pragma unroll
+             for (int s = 0; s < BK / 16; ++s) {
+               bf16x8_t a[3][NB], b[3][NB];
+#pragma unroll
+               for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+                 for (int i = 0; i < NB; ++i) {
+                   a[pl][i] = OA::frag16(at(buf), pl, wm * 32 * NB + i * 32, s, lane);
+                   b[2 - pl][i] = OB::frag16(bt(buf), 2 - pl, wn * 32 * NB + i * 32, s, lane);
+                 }
+               constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+               for (int q = 0; q < 6; ++q)
+#pragma unroll
+                 for (int i = 0; i < NB; ++i)
+#pragma unroll
+                   for (int j = 0; j < NB; ++j) {
+                     f32x16_t& c = q < 5 ? low[i][j] : acc[i][j];
+                     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[PB[q]][j], a[PA[q]][i], c, 0, 0, 0);
+                   }
+             }
+           });
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
+    if (__syncthreads_or(seen.bad())) exact_loop();
+  } else {
+    exact_loop();
   }
 
   // ---- epilogue: 64 rows at a time through LDS, 16-byte pieces of whole row segments out ----
@@ -298,11 +474,11 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_f32_kernel(GemmArgs p) {
   }
 }
 
-template <int NB, bool VEC>
+template <int NB, int VEC, bool SPLIT>
 int f32_layout(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st) {
-  if (d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, false, NB, VEC>), grid, dim3(GEMM_THREADS), 0, st, a);
-  else if (d.a_kc && d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, true, NB, VEC>), grid, dim3(GEMM_THREADS), 0, st, a);
-  else if (!d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<false, false, NB, VEC>), grid, dim3(GEMM_THREADS), 0, st, a);
+  if (d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, false, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
+  else if (d.a_kc && d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, true, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
+  else if (!d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<false, false, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
   else return HFTA_EUNSUPPORTED;
   return launch_status();
 }
@@ -323,10 +499,17 @@ int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
   const int T = small ? 64 : 128;
   a.tiles_m = (d.M + T - 1) / T;
   a.tiles_n = (d.N + T - 1) / T;
+  a.tiles_per_seg = (d.K + F32_BK - 1) / F32_BK;
+  a.total_tiles = d.S * a.tiles_per_seg;
   dim3 grid((unsigned)(a.tiles_m * a.tiles_n), 1, (unsigned)(G * a.splits));
   const bool vec = d.K >= 4 && (d.a_kc || d.M >= 4) && (d.b_kc || d.N >= 4);
-  if (small) return vec ? f32_layout<1, true>(d, a, grid, st) : f32_layout<1, false>(d, a, grid, st);
-  return vec ? f32_layout<2, true>(d, a, grid, st) : f32_layout<2, false>(d, a, grid, st);
+  const bool whole = vec && (d.a_kc ? d.K : d.M) % 4 == 0 && (d.b_kc ? d.K : d.N) % 4 == 0;   // no piece straddles a row's end
+  // Small tiles under at most 64 k are bound by their tensors and better off with the fp32 instruction's four
+  // workgroups per compute unit than with the split's three (64 -> 64 on 4 x 32 x 2500 points: 45 us, split 53).
+  if (small && (int64_t)d.K * d.S <= 64)
+    return whole ? f32_layout<1, 2, false>(d, a, grid, st) : vec ? f32_layout<1, 1, false>(d, a, grid, st) : f32_layout<1, 0, false>(d, a, grid, st);
+  if (small) return whole ? f32_layout<1, 2, true>(d, a, grid, st) : vec ? f32_layout<1, 1, true>(d, a, grid, st) : f32_layout<1, 0, false>(d, a, grid, st);
+  return whole ? f32_layout<2, 2, true>(d, a, grid, st) : vec ? f32_layout<2, 1, true>(d, a, grid, st) : f32_layout<2, 0, false>(d, a, grid, st);
 }
 
 }  // namespace hfta
