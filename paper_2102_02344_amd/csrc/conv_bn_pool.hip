@@ -57,36 +57,56 @@ struct CbpArgs {
 __device__ __forceinline__ float pooled_z(float z, int L) { return L & 3 ? bf16_to_f32(f32_to_bf16(z)) : z; }
 
 // ---- per channel: dbeta, dgamma from the Nb argmax elements; coefficients ----------------
-__global__ __launch_bounds__(64) void cbp_coef_kernel(CbpArgs p) {
-  const int c = blockIdx.x, b = blockIdx.y, k = b * p.Co + c;
-  const int lane = threadIdx.x;
-  const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
-  float s1 = 0.f, s2 = 0.f;
-  for (int n = lane; n < p.Nb; n += 64) {
-    const int hit = min(max(p.idx[b * p.vsb + n * p.vsn + c * p.vsc], 0), p.L - 1);
-    const float z = p.zhit ? p.zhit[((int64_t)b * p.Nb + n) * p.Co + c]
-                           : bf16_to_f32(p.Z[b * p.zsb + n * p.zsn + c * p.zsc + hit]);
-    const float xh = (z - mean) * invstd;
-    // the activation's side is the pooled value's
-    const float pre = fmaf(g, p.zhit ? (pooled_z(z, p.L) - mean) * invstd : xh, bt);
-    const float gr = bf16_to_f32(p.dV[b * p.vsb + n * p.vsn + c * p.vsc]) * act_grad(pre, p.act, p.slope);
-    s1 += gr;
-    s2 = fmaf(gr, xh, s2);
-    p.s[((int64_t)b * p.Nb + n) * p.Co + c] = gr;          // scaled by a below
-  }
-  s1 = wave_sum(s1);
-  s2 = wave_sum(s2);
+// Lanes are 64 neighbouring channels (of the [.., Co] rows whole cache lines), the eight wavefronts take every eighth
+// sample; a channel per workgroup with the samples across its lanes took 13 us on 8 x 32 x 1024 for 7 now.
+constexpr int COEF_WAVES = 8;   // and eight samples a thread: 64, the lanes of the sums' order
+__global__ __launch_bounds__(COEF_WAVES * 64) void cbp_coef_kernel(CbpArgs p) {
+  __shared__ float red[COEF_WAVES][2][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = blockIdx.x * 64 + lane, b = blockIdx.y, k = b * p.Co + c;
+  const bool live = c < p.Co;
+  float mean = 0.f, invstd = 0.f, g = 0.f, bt = 0.f;
+  if (live) { mean = p.save_mean[k]; invstd = p.save_invstd[k]; g = p.gamma[k]; bt = p.beta[k]; }
   const float a = g * invstd;
-  const float m = (float)p.Nb * (float)p.L;
-  const float bias = p.bias ? bf16_to_f32(p.bias[k]) : 0.f;
-  for (int n = lane; n < p.Nb; n += 64) p.s[((int64_t)b * p.Nb + n) * p.Co + c] *= a;
-  if (lane == 0) {
-    p.dbeta[k] = s1;
-    p.dgamma[k] = s2;
+  // Sums over n as a wavefront with the samples across its lanes forms them: n mod 64, then pairs 32, 16, 8, 4, 2, 1 apart.
+  float s1[8], s2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) s1[i] = s2[i] = 0.f;
+  if (live) {
+    for (int n0 = wave; n0 < p.Nb; n0 += 64)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = n0 + 8 * i;
+      if (n >= p.Nb) continue;
+      const int64_t v = b * p.vsb + n * p.vsn + c * p.vsc;
+      float z;
+      if (p.zhit) z = p.zhit[((int64_t)b * p.Nb + n) * p.Co + c];
+      else z = bf16_to_f32(p.Z[b * p.zsb + n * p.zsn + c * p.zsc + min(max(p.idx[v], 0), p.L - 1)]);
+      const float xh = (z - mean) * invstd;
+      // the activation's side is the pooled value's
+      const float pre = fmaf(g, p.zhit ? (pooled_z(z, p.L) - mean) * invstd : xh, bt);
+      const float gr = bf16_to_f32(p.dV[v]) * act_grad(pre, p.act, p.slope);
+      s1[i] += gr;
+      s2[i] = fmaf(gr, xh, s2[i]);
+      p.s[((int64_t)b * p.Nb + n) * p.Co + c] = gr * a;
+    }
+  }
+  auto tree = [](const float (&v)[8]) { return ((v[0] + v[4]) + (v[2] + v[6])) + ((v[1] + v[5]) + (v[3] + v[7])); };
+  red[wave][0][lane] = tree(s1);
+  red[wave][1][lane] = tree(s2);
+  __syncthreads();
+  if (wave == 0 && live) {
+#pragma unroll
+    for (int w = 0; w < COEF_WAVES; ++w) { s1[w] = red[w][0][lane]; s2[w] = red[w][1][lane]; }
+    const float sb = tree(s1), sg = tree(s2);
+    const float m = (float)p.Nb * (float)p.L;
+    const float bias = p.bias ? bf16_to_f32(p.bias[k]) : 0.f;
+    p.dbeta[k] = sb;
+    p.dgamma[k] = sg;
     if (p.dbias) p.dbias[k] = 0.f;                          // a bias in front of a BatchNorm: gradient exactly zero
-    p.chan[k] = CbpChan{a, s1, s2, invstd, mean, bias};
-    p.p1[k] = a * invstd * s2 / m;
-    p.p0[k] = a * (s1 + invstd * s2 * (bias - mean)) / m;
+    p.chan[k] = CbpChan{a, sb, sg, invstd, mean, bias};
+    p.p1[k] = a * invstd * sg / m;
+    p.p0[k] = a * (sb + invstd * sg * (bias - mean)) / m;
   }
 }
 
@@ -179,7 +199,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gram_kernel(GramArgs p) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[j], a[i], acc[i][j], 0, 0, 0);
     }
   }
-  // acc[i][j][4q+e]: column (from the first operand) wn*64 + j*32 + 8q + 4*gsel + e, row (second operand) wm*64 + i*32 + r
+  // acc[i][j][4q+e]: column (from the first operand) wn*64 + j*32 + 8q + 4*gsel + e, row (second operand) wm*64 + i*32 + r.
+  // The matrix is symmetric, element by element the same sum in the same order, so it goes out transposed: 32 lanes write
+  // one 128-byte row segment (in rows, every lane a cache line of its own: 57 us instead of 46 for the whole kernel on
+  // 8 x 32 x 2500 points, 25 instead of 11 on 3 x 13 x 1023).
   float* out = p.partial + ((int64_t)chunk * gridDim.y + b) * p.Ci * p.Ci;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -189,7 +212,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gram_kernel(GramArgs p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int cj = wn * 64 + j * 32 + 8 * (v >> 2) + 4 * gsel + (v & 3);
-        if (ci < p.Ci && cj < p.Ci) out[(int64_t)ci * p.Ci + cj] = acc[i][j][v];
+        if (ci < p.Ci && cj < p.Ci) out[(int64_t)cj * p.Ci + ci] = acc[i][j][v];
       }
   }
 }
@@ -200,7 +223,8 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const float* __restric
   if (i >= count) return;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;          // four interleaved sums, then (0+1)+(2+3): a fixed order
   int k = 0;
-  for (; k + 4 <= chunks; k += 4) {
+#pragma unroll 4
+  for (; k + 4 <= chunks; k += 4) {                      // sixteen loads in flight
     s0 += partial[(int64_t)k * count + i];
     s1 += partial[(int64_t)(k + 1) * count + i];
     s2 += partial[(int64_t)(k + 2) * count + i];
@@ -231,53 +255,57 @@ int gram_launch(int B, int Nb, int Ci, int L, const void* X, const int64_t xs[4]
   return launch_status();
 }
 
-// ---- argmax positions of one (model, sample) sorted by point, ties in channel order ------------
-// key = point << 10 | channel (Co <= 1024, L < 2^21: checked on the host); bitonic sort in LDS.
+// ---- two things that only wait for the coefficients, in one launch (15 us each on their own, few workgroups both;
+// ---- together 17 on 8 x 32 x 1024): the sorted argmax positions, and G
+constexpr int PREP_WAVES = 16, PREP_THREADS = PREP_WAVES * 64;
+struct GwShared { float red[PREP_WAVES][16][64]; float vred[PREP_WAVES][32]; };
+
+// Argmax positions of one (model, sample) sorted by point, ties in channel order: key = point << 10 | channel (Co <= 1024,
+// L < 2^21: checked on the host); bitonic, a key per thread, exchanged by shuffles inside a wavefront and through LDS
+// across (10 of the 55 exchanges, where a barrier each took 15 us).
 // toff[tile] = first sorted position whose point lies in 128-point tile `tile` or later.
-__global__ __launch_bounds__(512) void cbp_sort_kernel(CbpArgs p, int P, int tiles) {
-  __shared__ uint32_t key[1024];
-  const int n = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
-  for (int c = t; c < P; c += 512) {
-    uint32_t k = 0xffffffffu;
-    if (c < p.Co) {
-      const int hit = min(max(p.idx[b * p.vsb + n * p.vsn + c * p.vsc], 0), p.L - 1);
-      k = ((uint32_t)hit << 10) | (uint32_t)c;
-    }
-    key[c] = k;
+__device__ void sort_hits(const CbpArgs& p, uint32_t (&sh)[2][PREP_THREADS], int P, int tiles, int n, int b) {
+  const int t = threadIdx.x;
+  uint32_t key = 0xffffffffu;
+  if (t < p.Co) {
+    const int hit = min(max(p.idx[b * p.vsb + n * p.vsn + t * p.vsc], 0), p.L - 1);
+    key = ((uint32_t)hit << 10) | (uint32_t)t;
   }
+  int buf = 0;
   for (int k = 2; k <= P; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
-      __syncthreads();
-      for (int i = t; i < P / 2; i += 512) {
-        const int lo = 2 * (i & ~(j - 1)) + (i & (j - 1)), hi = lo + j;
-        const uint32_t x = key[lo], y = key[hi];
-        if ((x > y) == ((lo & k) == 0)) { key[lo] = y; key[hi] = x; }
+      uint32_t o;
+      if (j < 64) {
+        o = (uint32_t)__shfl_xor((int)key, j, 64);
+      } else {                                               // the other buffer was last read before the last barrier
+        sh[buf][t] = key;
+        __syncthreads();
+        o = sh[buf][t ^ j];
+        buf ^= 1;
       }
+      key = ((t & j) == 0) == ((t & k) == 0) ? min(key, o) : max(key, o);
     }
+  sh[buf][t] = key;
   __syncthreads();
   const int64_t base = ((int64_t)b * p.Nb + n) * p.Co;
-  for (int c = t; c < p.Co; c += 512) {
-    const uint32_t k = key[c];
-    p.skey[base + c] = k;
-    p.sval[base + c] = p.s[base + (k & 1023u)];
+  if (t < p.Co) {
+    p.skey[base + t] = key;
+    p.sval[base + t] = p.s[base + (key & 1023u)];
   }
   int* toff = p.toff + ((int64_t)b * p.Nb + n) * (tiles + 1);
-  for (int k = t; k <= p.Co; k += 512) {
-    const int cur = k < p.Co ? (int)(key[k] >> 17) : tiles;
-    const int prev = k > 0 ? (int)(key[k - 1] >> 17) : -1;
+  for (int k = t; k <= p.Co; k += PREP_THREADS) {
+    const int cur = k < p.Co ? (int)(sh[buf][k] >> 17) : tiles;
+    const int prev = k > 0 ? (int)(sh[buf][k - 1] >> 17) : -1;
     for (int tl = prev + 1; tl <= cur; ++tl) toff[tl] = k;
   }
 }
 
-// ---- G = sum_c p1[c] W[c,:]^T W[c,:] (stored negated, bf16) and v = sum_c p0[c] W[c,:] --------
-// One workgroup per 32 x 32 tile of G and model, fp32 matrix instructions (the operands are exact
-// in fp32); the eight wavefronts take an eighth of the channels each and are added in order.
-constexpr int GW_WAVES = 8;
-__global__ __launch_bounds__(GW_WAVES * 64) void cbp_gram_w_kernel(CbpArgs p) {
-  __shared__ float red[GW_WAVES][16][64];
-  __shared__ float vred[GW_WAVES][32];
+// G = sum_c p1[c] W[c,:]^T W[c,:] (stored negated, bf16) and v = sum_c p0[c] W[c,:]: one workgroup per 32 x 32 tile of G
+// and model, fp32 matrix instructions (the operands are exact in fp32); the wavefronts take a share of the channels each
+// and are added in order.
+__device__ void gram_w(const CbpArgs& p, GwShared& sh, int tile, int b) {
   const int T = (p.Ci + 31) / 32;
-  const int ti = blockIdx.x / T, tj = blockIdx.x % T, b = blockIdx.y;
+  const int ti = tile / T, tj = tile % T;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int i = lane & 31, kh = lane >> 5;
   const int ca = ti * 32 + i, cb = tj * 32 + i;
@@ -286,7 +314,7 @@ __global__ __launch_bounds__(GW_WAVES * 64) void cbp_gram_w_kernel(CbpArgs p) {
   const bf16_raw* Wc = p.W + (int64_t)b * p.Co * p.Ci + min(cb, p.Ci - 1);
   const float* P1 = p.p1 + b * p.Co;
   const float* P0 = p.p0 + b * p.Co;
-  const int per = ((p.Co + 2 * GW_WAVES - 1) / (2 * GW_WAVES)) * 2;      // channels per wavefront, even
+  const int per = ((p.Co + 2 * PREP_WAVES - 1) / (2 * PREP_WAVES)) * 2;  // channels per wavefront, even
   const int c_lo = wave * per, c_hi = min(p.Co, c_lo + per);
   f32x16_t acc;
 #pragma unroll
@@ -312,24 +340,32 @@ __global__ __launch_bounds__(GW_WAVES * 64) void cbp_gram_w_kernel(CbpArgs p) {
   }
   vacc += __shfl_xor(vacc, 32, 64);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
-  if (lane < 32) vred[wave][lane] = vacc;
+  for (int v = 0; v < 16; ++v) sh.red[wave][v][lane] = acc[v];
+  if (lane < 32) sh.vred[wave][lane] = vacc;
   __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 16 * 64 / (GW_WAVES * 64); ++r) {
-    const int o = t + GW_WAVES * 64 * r, v = o >> 6, ln = o & 63;
+  static_assert(PREP_THREADS == 16 * 64, "one element of the tile per thread");
+  {
+    const int v = t >> 6;
     float g = 0.f;
 #pragma unroll
-    for (int w = 0; w < GW_WAVES; ++w) g += red[w][v][ln];
-    const int ci = ti * 32 + 8 * (v >> 2) + 4 * (ln >> 5) + (v & 3), cj = tj * 32 + (ln & 31);
+    for (int w = 0; w < PREP_WAVES; ++w) g += sh.red[w][v][lane];
+    const int ci = ti * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), cj = tj * 32 + (lane & 31);
     if (ci < p.Ci && cj < p.Ci) p.negG[((int64_t)b * p.Ci + ci) * p.Ci + cj] = f32_to_bf16(-g);
   }
   if (tj == 0 && t < 32 && ti * 32 + t < p.Ci) {
     float vs = 0.f;
 #pragma unroll
-    for (int w = 0; w < GW_WAVES; ++w) vs += vred[w][t];
+    for (int w = 0; w < PREP_WAVES; ++w) vs += sh.vred[w][t];
     p.v[(int64_t)b * p.Ci + ti * 32 + t] = vs;
   }
+}
+
+// workgroups 0 .. B * Nb - 1: sort_hits; then (tiles of G) * B: gram_w
+__global__ __launch_bounds__(PREP_THREADS) void cbp_prep_kernel(CbpArgs p, int P, int tiles) {
+  __shared__ union { uint32_t key[2][PREP_THREADS]; GwShared g; } sh;
+  const int id = (int)blockIdx.x - p.B * p.Nb;
+  if (id < 0) sort_hits(p, sh.key, P, tiles, (int)blockIdx.x % p.Nb, (int)blockIdx.x / p.Nb);
+  else gram_w(p, sh.g, id / p.B, id % p.B);
 }
 
 // ---- dX tile = -(G x) - v + argmax columns.  Also emits, for the weight gradient, the input
@@ -910,46 +946,71 @@ __global__ __launch_bounds__(GEMM_THREADS, FBP_OCC) void fbp_main_kernel(FbpArgs
 }
 
 // ---- statistics from the moments; T = W XX kept for the backward operator --------------------------
-__global__ __launch_bounds__(128) void fbp_stats_kernel(FbpArgs p) {
-  constexpr int CB = 8;
-  __shared__ double wrow[CB][128];                       // widened once: the loop below is bound by fp64 issue
-  __shared__ double red[2][CB][2];
-  const int c0 = blockIdx.x * CB, b = blockIdx.y, cj = threadIdx.x;
-  for (int e = cj; e < CB * p.Ci; e += 128) {
-    const int cc = e / p.Ci, k = e - cc * p.Ci;
-    wrow[cc][k] = c0 + cc < p.Co ? (double)bf16_to_f32(p.W[((int64_t)b * p.Co + c0 + cc) * p.Ci + k]) : 0.0;
-  }
-  __syncthreads();
-  const bool live = cj < p.Ci;
-  const float* XXb = p.XX + (int64_t)b * p.Ci * p.Ci;
-  double T[CB];
+// fp64 matrix instructions (16x16x4): lane (q, i) = (lane / 16, lane % 16) holds A[i][q], B[q][i] and, in register r,
+// D[4 r + q][i].  A workgroup takes 16 channels, a wavefront 32 input channels; the k of lane quarter q are q Ci/4 ..,
+// so that a lane's weights are contiguous.  (fp64 vector arithmetic out of LDS took 23.5 us on 8 x 1024 x 128 for 16.)
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256) void fbp_stats_kernel(FbpArgs p) {
+  __shared__ double red[4][16][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, q = lane >> 4;
+  const int c0 = blockIdx.x * 16, b = blockIdx.y, kq = p.Ci / 4;       // Ci is a multiple of 8: kq is even
+  const bf16_raw* Wb = p.W + (int64_t)b * p.Co * p.Ci;
+  const uint32_t* wk = reinterpret_cast<const uint32_t*>(Wb + (int64_t)min(c0 + i, p.Co - 1) * p.Ci + q * kq);
+  double quad[4], s1[4];
 #pragma unroll
-  for (int e = 0; e < CB; ++e) T[e] = 0.0;
-  if (live) {
-#pragma unroll 16
-    for (int ci = 0; ci < p.Ci; ++ci) {                  // a chain of loads: sixteen in flight
-      const double x = (double)XXb[(int64_t)ci * p.Ci + cj];
+  for (int r = 0; r < 4; ++r) quad[r] = s1[r] = 0.0;
+  if (wave * 32 < p.Ci) {
+    int cj[2];
+    const float* xk[2];
+    f64x4_t acc[2];
 #pragma unroll
-      for (int e = 0; e < CB; ++e) T[e] = fma(wrow[e][ci], x, T[e]);
+    for (int u = 0; u < 2; ++u) {
+      cj[u] = wave * 32 + u * 16 + i;
+      xk[u] = p.XX + (int64_t)b * p.Ci * p.Ci + (int64_t)(q * kq) * p.Ci + min(cj[u], p.Ci - 1);
+      acc[u] = f64x4_t{0.0, 0.0, 0.0, 0.0};
     }
+#pragma unroll 8
+    for (int s = 0; s < kq; s += 2) {
+      const uint32_t w = wk[s >> 1];
+      const double lo = (double)__uint_as_float(w << 16), hi = (double)__uint_as_float(w & 0xffff0000u);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(lo, (double)xk[u][(int64_t)s * p.Ci], acc[u], 0, 0, 0);
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(hi, (double)xk[u][(int64_t)(s + 1) * p.Ci], acc[u], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (cj[u] < p.Ci) {
+        const double sxj = (double)p.SX[(int64_t)b * p.Ci + cj[u]];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = c0 + 4 * r + q;
+          if (c < p.Co) {
+            const double w = (double)bf16_to_f32(Wb[(int64_t)c * p.Ci + cj[u]]);
+            p.T[((int64_t)b * p.Co + c) * p.Ci + cj[u]] = (float)acc[u][r];
+            quad[r] = fma(acc[u][r], w, quad[r]);            // terms of W_c XX W_c^T and of W_c SX
+            s1[r] = fma(w, sxj, s1[r]);
+          }
+        }
+      }
   }
-  const double sxj = live ? (double)p.SX[(int64_t)b * p.Ci + cj] : 0.0;
 #pragma unroll
-  for (int e = 0; e < CB; ++e) {
-    if (live && c0 + e < p.Co) p.T[((int64_t)b * p.Co + c0 + e) * p.Ci + cj] = (float)T[e];
-    const double w = live ? wrow[e][cj] : 0.0;
-    double q = T[e] * w, s1 = w * sxj;                   // terms of W_c XX W_c^T and of W_c SX
+  for (int r = 0; r < 4; ++r) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { q += __shfl_xor(q, o, 64); s1 += __shfl_xor(s1, o, 64); }
-    if ((cj & 63) == 0) { red[cj >> 6][e][0] = q; red[cj >> 6][e][1] = s1; }
+    for (int o = 8; o > 0; o >>= 1) { quad[r] += __shfl_xor(quad[r], o, 64); s1[r] += __shfl_xor(s1[r], o, 64); }
+    if (i == 0) { red[wave][4 * r + q][0] = quad[r]; red[wave][4 * r + q][1] = s1[r]; }
   }
   __syncthreads();
-  if (cj < CB && c0 + cj < p.Co) {
-    const int k = b * p.Co + c0 + cj;
+  const int cl = threadIdx.x;
+  if (cl < 16 && c0 + cl < p.Co) {
+    const int k = b * p.Co + c0 + cl;
     const double m = (double)p.Nb * (double)p.L;
-    const double quad = red[0][cj][0] + red[1][cj][0], ws = red[0][cj][1] + red[1][cj][1];
+    double qs = 0.0, ws = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { qs += red[w][cl][0]; ws += red[w][cl][1]; }
     const double mz = ws / m;                            // mean of W x (the bias shifts the mean only)
-    double var = quad / m - mz * mz;
+    double var = qs / m - mz * mz;
     var = var < 0.0 ? 0.0 : var;
     const float mean = (float)(mz + (p.bias ? (double)bf16_to_f32(p.bias[k]) : 0.0));
     const float varf = (float)var;
@@ -1114,19 +1175,18 @@ static int cbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
     a.Tin = a.SX + (size_t)B * Ci;
     a.SXpart = nullptr;
   }
-  hipLaunchKernelGGL(cbp_coef_kernel, dim3((unsigned)Co, (unsigned)B), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(cbp_coef_kernel, dim3((unsigned)((Co + 63) / 64), (unsigned)B), dim3(COEF_WAVES * 64), 0, st, a);
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
   if (!saved_moments) {          // Gram matrix of the layer input: XX[b] = sum_{n,l} x x^T
     const int rc = gram_launch(B, Nb, Ci, L, X, xs, a.XX, (float*)(ws + lay.part), a.x_extent, in, nullptr, nullptr, st);
     if (rc != HFTA_OK) return rc;
   }
   const int T32 = (Ci + 31) / 32;
-  hipLaunchKernelGGL(cbp_gram_w_kernel, dim3((unsigned)(T32 * T32), (unsigned)B), dim3(GW_WAVES * 64), 0, st, a);
-  if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
   dim3 grid((unsigned)((L + 127) / 128), 1, (unsigned)(B * Nb));
   int P = 2;
   while (P < Co) P <<= 1;
-  hipLaunchKernelGGL(cbp_sort_kernel, dim3((unsigned)Nb, (unsigned)B), dim3(512), 0, st, a, P, (int)grid.x);
+  hipLaunchKernelGGL(cbp_prep_kernel, dim3((unsigned)(B * Nb + T32 * T32 * B)), dim3(PREP_THREADS), 0, st, a, P, (int)grid.x);
+  if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
   if (Ci <= 64) hipLaunchKernelGGL(cbp_dx_kernel<64>, grid, dim3(GEMM_THREADS), 0, st, a);
   else hipLaunchKernelGGL(cbp_dx_kernel<128>, grid, dim3(GEMM_THREADS), 0, st, a);
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
@@ -1204,7 +1264,7 @@ static int fbp_run(int B, int Nb, int Ci, int Co, int L, int dtype, const void* 
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
   hipLaunchKernelGGL(cbp_sx_kernel, dim3((unsigned)((Ci + 15) / 16), (unsigned)B), dim3(1024), 0, st, a.SXpart, a.SX, Ci,
                      Nb * (int)grid.x * 2);
-  hipLaunchKernelGGL(fbp_stats_kernel, dim3((unsigned)((Co + 7) / 8), (unsigned)B), dim3(128), 0, st, a);
+  hipLaunchKernelGGL(fbp_stats_kernel, dim3((unsigned)((Co + 15) / 16), (unsigned)B), dim3(256), 0, st, a);
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
   hipLaunchKernelGGL(fbp_finish_kernel, dim3((unsigned)((Co + 255) / 256), (unsigned)Nb, (unsigned)B), dim3(256), 0, st, a,
                      (int)grid.x);
