@@ -370,20 +370,26 @@ __global__ __launch_bounds__(PREP_THREADS) void cbp_prep_kernel(CbpArgs p, int P
 
 // ---- dX tile = -(G x) - v + argmax columns.  Also emits, for the weight gradient, the input
 // ---- column x[:, idx] of every argmax that falls in the tile and the tile's row sums of x. ----
+// The argmax columns are a product too: sum over the tile's hits k of W[c_k, :] s_k at column q_k, i.e. W_hits^T S with
+// S[k][q] = s_k at q = q_k and zero elsewhere.  S is built in registers, a compare per hit and lane, from s as the exact
+// sum of three bf16 values; the hits are sorted by column, so sixteen of them touch one or two of a tile's four column
+// blocks and the others are skipped.  (One lane per output row walking its hits one after the other, with a
+// read-add-write of the staged tile per column, took 171 us on 8 x 32 x 2500 x 128 for 110, and 52 for 19 on
+// 3 x 13 x 1023, where a tile has 128 hits instead of 51.)
 template <int KT>
 __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
   constexpr int PITCH = KT * 2 + 16;
   constexpr int TILE = 128 * PITCH;
-  constexpr int STAGE = 64 * EPI_PITCH4;                 // fp32 staging of 64 rows
-  constexpr int GREG = TILE > STAGE ? TILE : STAGE;
   constexpr int SUB = KT / 32;
-  constexpr int WP = KT * 2;                             // pitch of a staged W row
-  constexpr int HC = TILE / WP;                          // W rows that fit where the X tile was
-  constexpr int PRE = 16;                                // W rows per wavefront fetched ahead into registers
-  __shared__ __attribute__((aligned(16))) unsigned char smem[TILE + GREG];
-  __shared__ unsigned short hit_c[1024];               // this tile's argmax hits (Co <= 1024 on the host):
-  __shared__ unsigned char hit_q[1024];                // channel, column inside the tile, gradient value;
-  __shared__ float hit_s[1024];                        // sorted by column, channel order inside a column
+  constexpr int PPR = KT / 8, RPL = 64 / PPR;            // 16-byte pieces per W row, rows per wavefront load
+  constexpr int HC = 128;                                // W rows staged at a time, where the X tile was
+  constexpr int PRE = HC / 4 / RPL;                      // loads per wavefront: fetched ahead into registers
+  constexpr int OP = 128 * 2 + 8;                        // output staging pitch, where -G was
+  static_assert(HC * KT * 2 <= TILE && KT * OP <= TILE, "W rows and staged output must fit the tiles");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * TILE];
+  __shared__ unsigned short hit_c[1024];               // this tile's argmax hits (Co <= 1024 on the host), sorted by
+  __shared__ __attribute__((aligned(16))) unsigned char hit_q[1024];      // column, channel order inside a column:
+  __shared__ __attribute__((aligned(16))) bf16_raw hit_s[3][1024];        // channel, column, value in three parts
   __shared__ float sxs[256];
   __shared__ float4 icn[KT];                           // the input block's BatchNorm constants, if X is a pre-activation
   unsigned char* Xs = smem;
@@ -456,13 +462,19 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
       for (int i = 0; i < 4; ++i)
         *reinterpret_cast<uint2*>(Xs + (ng * 4 + i) * PITCH + s * 64 + kq * 8) = o[i];
     }
-    if (t < nh) {
-      hit_c[t] = (unsigned short)(key0 & 1023u); hit_q[t] = (unsigned char)((int)(key0 >> 10) - l0); hit_s[t] = sv0;
-    }
-    for (int i = t + GEMM_THREADS; i < nh; i += GEMM_THREADS) {
-      const uint32_t k = skey[i];
-      hit_c[i] = (unsigned short)(k & 1023u); hit_q[i] = (unsigned char)((int)(k >> 10) - l0); hit_s[i] = sval[i];
-    }
+    auto park_hit = [&](int i, uint32_t k, float sv) {       // past the list: a column no lane has
+      hit_c[i] = (unsigned short)(k & 1023u);
+      hit_q[i] = i < nh ? (unsigned char)((int)(k >> 10) - l0) : (unsigned char)255;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const bf16_raw h = f32_to_bf16(sv);
+        hit_s[q][i] = h;
+        sv -= bf16_to_f32(h);
+      }
+    };
+    const int nh16 = (nh + 15) & ~15;
+    if (t < nh16) park_hit(t, key0, sv0);
+    for (int i = t + GEMM_THREADS; i < nh16; i += GEMM_THREADS) park_hit(i, i < nh ? skey[i] : 0u, i < nh ? sval[i] : 0.f);
   }
   {  // -G rows (k-contiguous)
     const int wr = t >> 2, wg = (t & 3) * 8;
@@ -478,14 +490,20 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
   }
   __syncthreads();
 
-  // W rows of the first hits: fetched now, parked in LDS once the X tile is dead
-  uint32_t wpre[PRE];
+  // W rows of hits kc .. kc+127: fetched into registers, parked in LDS once the X tile is dead; rows past the list and
+  // columns past Ci are zeros
+  const __amdgpu_buffer_rsrc_t rwh = pf_rsrc(Wb, (uint32_t)((int64_t)p.Co * p.Ci * 2));
+  const int wpc = lane % PPR, wrl = lane / PPR;
+  pf_u32x4 wpre[PRE];
+  auto fetch_rows = [&](int kc) {
 #pragma unroll
-  for (int r = 0; r < PRE; ++r) {
-    const int i = wave + 4 * r;
-    wpre[r] = 0u;
-    if (i < nh && 2 * lane < p.Ci) wpre[r] = reinterpret_cast<const uint32_t*>(Wb + (int64_t)hit_c[i] * p.Ci)[lane];
-  }
+    for (int r = 0; r < PRE; ++r) {
+      const int i = kc + (wave * PRE + r) * RPL + wrl;
+      const bool ok = i < nh && wpc * 8 < p.Ci;
+      wpre[r] = __builtin_amdgcn_raw_buffer_load_b128(rwh, (int)(ok ? ((uint32_t)hit_c[min(i, 1023)] * (uint32_t)p.Ci + (uint32_t)wpc * 8u) * 2u : PF_OOB), 0, 0);
+    }
+  };
+  fetch_rows(0);
 
   f32x16_t acc[2][2];
 #pragma unroll
@@ -510,7 +528,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bb[j], a[i], acc[i][j], 0, 0, 0);
   }
 
-  {  // this tile's part of sum_l x: thread (ci, half) adds 64 points in order
+  if (p.SXpart) {  // this tile's part of sum_l x: thread (ci, half) adds 64 points in order
     const int ci = t & 127, half = t >> 7;
     float sx = 0.f;
     if (ci < KT) {
@@ -521,105 +539,101 @@ __global__ __launch_bounds__(GEMM_THREADS) void cbp_dx_kernel(CbpArgs p) {
     sxs[t] = sx;
   }
   // input columns at the argmax points, for the weight gradient's gather term
-#pragma unroll 4
-  for (int h = wave; h < nh; h += 4) {
-    const uint32_t* xrow = reinterpret_cast<const uint32_t*>(Xs + hit_q[h] * PITCH);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(p.xg + ((int64_t)bz * p.Co + hit_c[h]) * p.Ci);
-    if (2 * lane < p.Ci) dst[lane] = xrow[lane];
-  }
+#pragma unroll 2
+  for (int h = wave * RPL + wrl; h < nh; h += 4 * RPL)
+    if (wpc * 8 < p.Ci)
+      *reinterpret_cast<uint4*>(p.xg + ((int64_t)bz * p.Co + hit_c[h]) * p.Ci + wpc * 8) =
+          *reinterpret_cast<const uint4*>(Xs + hit_q[h] * PITCH + wpc * 16);
   __syncthreads();                                       // both tiles are dead from here on
 
   if (p.SXpart && t < 128 && t < p.Ci) p.SXpart[((int64_t)bz * gridDim.x + bx) * p.Ci + t] = sxs[t] + sxs[t + 128];
-  bf16_raw* dXb = p.dX + b * p.dxsb + n * p.dxsn;
-  float* stage = reinterpret_cast<float*>(Gs);
+
+  // ---- acc += W_hits^T S, 128 hits at a time.  W row k of the chunk: 16-byte piece pc at pc ^ wswz(k), so that the four
+  // ---- k-rows of a transpose read cover the 64 banks once.
   unsigned char* Wh = Xs;
-  constexpr int SP = EPI_PITCH4 / 4;                     // staging pitch in floats
-  const int ml = lane & 31, nq = (lane >> 5) * 4;
-
-  // W rows kc .. kc+kn of the hit list into LDS (row i of the chunk at Wh + i * WP); lanes past Ci write zeros
-  auto load_rows = [&](int kc, int kn, int first) {
-    for (int i = wave + 4 * first; i < kn; i += 4) {
-      uint32_t w = 0u;
-      if (2 * lane < p.Ci) w = reinterpret_cast<const uint32_t*>(Wb + (int64_t)hit_c[kc + i] * p.Ci)[lane];
-      if (4 * lane < WP) *reinterpret_cast<uint32_t*>(Wh + i * WP + lane * 4) = w;
-    }
-  };
-#pragma unroll
-  for (int r2 = 0; r2 < PRE; ++r2) {
-    const int i = wave + 4 * r2;
-    if (i < nh && i < HC && 4 * lane < WP) *reinterpret_cast<uint32_t*>(Wh + i * WP + lane * 4) = wpre[r2];
-  }
-  load_rows(0, min(nh, HC), PRE);
-  int resident = 0;                                      // first hit of the chunk that sits in Wh
-
-  // ---- two passes of 64 output rows: stage fp32 (dense part), add the columns, store as bf16
+  auto wswz = [](int k) { return KT == 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; };
 #pragma unroll 1
-  for (int pass = 0; pass < 2; ++pass) {
-    if (wm == pass) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int rl = i * 32 + ml;
-        const int m = pass * 64 + rl;
-        const float vm = m < p.Ci ? p.v[(int64_t)b * p.Ci + m] : 0.f;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int nl = wn * 64 + j * 32 + 8 * q + nq;
-            *reinterpret_cast<float4*>(stage + rl * SP + nl) =
-                make_float4(acc[i][j][4 * q] - vm, acc[i][j][4 * q + 1] - vm, acc[i][j][4 * q + 2] - vm,
-                            acc[i][j][4 * q + 3] - vm);
-          }
-      }
+  for (int kc = 0; kc < nh; kc += HC) {
+    if (kc > 0) {
+      fetch_rows(kc);
+      __syncthreads();                                   // the chunk before has been read
     }
-    __syncthreads();                                     // staged rows and W rows in place
-    if (pass * 64 < p.Ci) {
-#pragma unroll 1
-      for (int kc = 0; kc < nh; kc += HC) {
-        const int kn = min(HC, nh - kc);
-        if (kc != resident) {
-          load_rows(kc, kn, 0);
-          resident = kc;
-          __syncthreads();
-        }
-        // the wavefronts split the chunk at column boundaries; one lane per output row walks its
-        // share in order: a column's hits in channel order, then one update of the staged cell
-        int ka = kc + (kn * wave) / 4, ke = kc + (kn * (wave + 1)) / 4;
-        while (ka > kc && ka < kc + kn && hit_q[ka] == hit_q[ka - 1]) ++ka;
-        while (ke > kc && ke < kc + kn && hit_q[ke] == hit_q[ke - 1]) ++ke;
-        const unsigned char* wcol = Wh + (pass * 64 + lane) * 2 - kc * WP;
-        if (ka < ke) {
-          int col = hit_q[ka];
-          float val = 0.f;
-#pragma unroll 4
-          for (int k = ka; k < ke; ++k) {                // the loads of several hits are in flight together
-            const int q = hit_q[k];
-            const float sv = hit_s[k];
-            const float w = bf16_to_f32(*reinterpret_cast<const bf16_raw*>(wcol + k * WP));
-            if (q != col) {
-              stage[lane * SP + col] += val;
-              val = 0.f;
-              col = q;
-            }
-            val = fmaf(sv, w, val);
-          }
-          stage[lane * SP + col] += val;
-        }
-        __syncthreads();
-      }
-    }
-    // 64 rows x 128 columns out as bf16: 4-column (8-byte) pieces, consecutive lanes on consecutive pieces
 #pragma unroll
-    for (int it = 0; it < 64 * 32 / GEMM_THREADS; ++it) {
-      const int id = t + GEMM_THREADS * it;
-      const int rr = id >> 5, cp = id & 31;
-      const int m = pass * 64 + rr, l = l0 + cp * 4;
-      const float4 f = *reinterpret_cast<const float4*>(stage + rr * SP + cp * 4);
-      if (m < p.Ci && l < p.L) {
-        row_piece_store(dXb + (int64_t)m * p.dxsc, make_uint2(pack_bf16x2(f.x, f.y), pack_bf16x2(f.z, f.w)), l, p.L);
-      }
+    for (int r2 = 0; r2 < PRE; ++r2) {
+      const int i = (wave * PRE + r2) * RPL + wrl;
+      *reinterpret_cast<pf_u32x4*>(Wh + i * (KT * 2) + ((wpc ^ wswz(i)) << 4)) = wpre[r2];
     }
     __syncthreads();
+    const int ksteps = (min(HC, nh - kc) + 15) >> 4;
+#pragma unroll 1
+    for (int s = 0; s < ksteps; ++s) {
+      const int k0 = kc + 16 * s;
+      const int qlo = __builtin_amdgcn_readfirstlane((int)hit_q[k0]);
+      const int qhi = __builtin_amdgcn_readfirstlane((int)hit_q[min(k0 + 15, nh - 1)]);
+      if (qhi < wn * 64 || qlo >= wn * 64 + 64) continue;
+      bf16x8_t a[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (KT == 64 && wm == 1) break;
+        const int r16 = lane & 15, k = 8 * (lane >> 5) + (r16 >> 2);
+        const int piece = ((wm * 64 + i * 32) >> 3) + 2 * ((lane >> 4) & 1) + ((r16 & 3) >> 1);
+        const unsigned char* a0 = Wh + (16 * s + k) * (KT * 2) + ((piece ^ wswz(k)) << 4) + (r16 & 1) * 8;
+        typedef __attribute__((address_space(3))) pf_v4s* lds_v4s;
+        union { pf_v4s h[2]; bf16x8_t v; } u;
+        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(a0));
+        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(a0 + 4 * (KT * 2)));
+        a[i] = u.v;
+      }
+      if (KT == 64 && wm == 1) continue;                 // no output rows
+      const uint2 qb = *reinterpret_cast<const uint2*>(hit_q + k0 + 8 * gsel);
+      uint4 part[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) part[q] = *reinterpret_cast<const uint4*>(&hit_s[q][k0 + 8 * gsel]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int cb = wn * 64 + j * 32;
+        if (qhi < cb || qlo >= cb + 32) continue;
+        uint32_t mask[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t w = (e & 2 ? qb.y : qb.x) >> (16 * (e & 1));
+          mask[e] = ((int)(w & 0xffu) == cb + r ? 0xffffu : 0u) | ((int)((w >> 8) & 0xffu) == cb + r ? 0xffff0000u : 0u);
+        }
+#pragma unroll
+        for (int q = 2; q >= 0; --q) {
+          union { uint4 w; bf16x8_t v; } sfr;
+          sfr.w = make_uint4(part[q].x & mask[0], part[q].y & mask[1], part[q].z & mask[2], part[q].w & mask[3]);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sfr.v, a[i], acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  }
+
+  // ---- minus v, rounded, staged where -G was; whole row segments out
+  bf16_raw* dXb = p.dX + b * p.dxsb + n * p.dxsn;
+  const int ml = lane & 31, nq = (lane >> 5) * 4;
+  if (wm * 64 < KT) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int m = wm * 64 + i * 32 + ml;
+      const float vm = m < p.Ci ? p.v[(int64_t)b * p.Ci + m] : 0.f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<uint2*>(Gs + m * OP + (wn * 64 + j * 32 + 8 * q + nq) * 2) =
+              make_uint2(pack_bf16x2(acc[i][j][4 * q] - vm, acc[i][j][4 * q + 1] - vm),
+                         pack_bf16x2(acc[i][j][4 * q + 2] - vm, acc[i][j][4 * q + 3] - vm));
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < KT * 32 / GEMM_THREADS; ++it) {  // 4-column (8-byte) pieces, consecutive lanes on consecutive pieces
+    const int id = t + GEMM_THREADS * it;
+    const int m = id >> 5, cp = id & 31, l = l0 + cp * 4;
+    const uint2 v = *reinterpret_cast<const uint2*>(Gs + m * OP + cp * 8);
+    if (m < p.Ci && l < p.L) row_piece_store(dXb + (int64_t)m * p.dxsc, v, l, p.L);
   }
 }
 
