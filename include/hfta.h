@@ -402,6 +402,22 @@ int hfta_bn_fwd_maxpool(int B, int Nb, int C, int L, int dtype,
                         float eps, float momentum, float* running_mean, float* running_var,
                         float* save_mean, float* save_invstd,
                         void* V, int32_t* idx, const int64_t vs[3], int act, float act_slope, void* stream);
+/* Fused Conv1d k=1, BatchNorm, activation and point max-pool with the convolution's output kept (the backward's input):
+ *   Z = W X + bias (stored),  V = max_l act(BN(Z)), idx = where;  and, if Y is not NULL, Y = act(BN(Z)) (stored).
+ * Arguments as in hfta_conv1x1_bn_fwd and hfta_maxpool_points.  With Y the results are those of hfta_conv1x1_bn_fwd followed
+ * by hfta_maxpool_points.  Without Y they are those of hfta_conv1x1_fwd followed by hfta_bn_fwd_maxpool, up to the summation
+ * order of the statistics; in fp32, with a 16-byte aligned workspace of hfta_conv1x1_bn_pool_fwd_workspace_bytes, Z is not
+ * read back (its partial sums and row extremes are taken as it is produced), and among points whose values differ but round
+ * to the same maximum idx may be another than the lowest.  With a smaller or no workspace the operators run one after
+ * the other. */
+size_t hfta_conv1x1_bn_pool_fwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
+int hfta_conv1x1_bn_pool_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,
+                             const void* X, const int64_t xs[4], const void* W, const void* bias,
+                             const float* gamma, const float* beta, float eps, float momentum,
+                             float* running_mean, float* running_var, float* save_mean, float* save_invstd,
+                             void* Z, const int64_t zs[4], void* Y, const int64_t ys[4],
+                             void* V, int32_t* idx, const int64_t vs[3],
+                             int act, float act_slope, void* workspace, size_t ws_bytes, void* stream);
 int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype,
                         const void* X, const int64_t xs[4], const void* dV, const int32_t* idx,
                         const int64_t vs[3], const float* gamma, const float* beta,

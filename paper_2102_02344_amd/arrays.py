@@ -312,6 +312,7 @@ class FusedPointNetCls(ParamArena):
                      hb.linear_fwd_workspace_bytes(B, Nb, spec.fc[i], spec.fc[i + 1], self.dt))
         if not self.fused_tail:
             self.fused_tail_ws = 0
+            ws = max(ws, hb.conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, spec.conv[-2], spec.conv[-1], L, self.dt))
         ws = max(ws, self.fused_tail_ws)
         self.ws = torch.empty(ws, dtype=torch.uint8, device=self.dev)
 
@@ -400,24 +401,19 @@ class FusedPointNetCls(ParamArena):
                       y=self._act(i), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"])
                 x, ci = y, co
                 continue
-            hb.conv1x1_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"),
-                           self.z[i], _cs(B, co, L))
+            # last per-point layer: convolution, BatchNorm + ReLU + max over points in one call; the
+            # activated [Nb, B*C, L] tensor is never written
+            hb.conv1x1_bn_pool_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"),
+                                   self.master(k + ".bn.g"), self.master(k + ".bn.b"), eps, mom,
+                                   self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], self.saved[k + ".bn.mean"],
+                                   self.saved[k + ".bn.invstd"], self.z[i], _cs(B, co, L), None, None, self.pooled,
+                                   self.pool_idx, (Nb * co, co, 1), hb.ACT_RELU, 0.0, self.ws)
             if P is not None:
                 P("conv1x1_fwd", layer=k, x=x, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
-            if i == self.nconv - 1:
-                # last per-point layer: BatchNorm + ReLU + max over points in one operator; the
-                # activated [Nb, B*C, L] tensor is never written
-                vs = (Nb * co, co, 1)
-                hb.bn_fwd_maxpool(B, Nb, co, L, dt, self.z[i], _cs(B, co, L), self.master(k + ".bn.g"),
-                                  self.master(k + ".bn.b"), eps, mom, self.running[k + ".bn.rm"],
-                                  self.running[k + ".bn.rv"], self.saved[k + ".bn.mean"],
-                                  self.saved[k + ".bn.invstd"], self.pooled, self.pool_idx, vs, hb.ACT_RELU)
-                if P is not None:
-                    P("bn_fwd_maxpool", layer=k, x=self.z[i], g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"),
-                      v=self.pooled, idx=self.pool_idx, mean=self.saved[k + ".bn.mean"],
-                      invstd=self.saved[k + ".bn.invstd"])
-                ci = co
-                break
+                P("bn_fwd_maxpool", layer=k, x=self.z[i], g=self.master(k + ".bn.g"), b=self.master(k + ".bn.b"),
+                  v=self.pooled, idx=self.pool_idx, mean=self.saved[k + ".bn.mean"],
+                  invstd=self.saved[k + ".bn.invstd"])
+            ci = co
         Cp = ci
         # head
         h, fx = self.pooled, s.fc[0]
@@ -1141,16 +1137,20 @@ class FusedPointNetSeg(ParamArena):
         for i in range(self.nconv):
             co, k = s.conv[i + 1], f"conv{i}"
             a, av = self._slice(self.cat, i)
-            # convolution + BatchNorm + ReLU in one call (z is read once, for the normalisation)
-            hb.conv1x1_bn_fwd(B, Nb, ci, co, L, dt, x, xs, self.w(k + ".w"), self.w(k + ".b"), *bn(k), eps, mom,
-                              self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], *st(k), self.z[i], _cs(B, co, L),
-                              a, cst, hb.ACT_RELU, 0.0, self.ws if _whole_pieces(L) else None)
+            # convolution + BatchNorm + ReLU in one call (z is read once, for the normalisation); the last layer's
+            # maximum over the points is taken as its output is written
+            conv = (B, Nb, ci, co, L, dt, x, xs, self.w(k + ".w"), self.w(k + ".b"), *bn(k), eps, mom,
+                    self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], *st(k), self.z[i], _cs(B, co, L), a, cst)
+            ws = self.ws if _whole_pieces(L) else None
+            if i < self.nconv - 1:
+                hb.conv1x1_bn_fwd(*conv, hb.ACT_RELU, 0.0, ws)
+            else:
+                hb.conv1x1_bn_pool_fwd(*conv, self.gfeat, self.pool_idx, self.gvs, hb.ACT_RELU, 0.0, ws)
             if P is not None:
                 P("conv1x1_fwd", layer=k, x=xv, w=self.w(k + ".w"), b=self.w(k + ".b"), y=self.z[i])
             if P is not None:
                 P("bn_fwd", layer=k, x=self.z[i], g=bn(k)[0], b=bn(k)[1], y=av, mean=st(k)[0], invstd=st(k)[1])
             x, xs, xv, ci = a, cst, av, co
-        hb.maxpool_points(B, Nb, C4, L, dt, x, cst, self.gfeat, self.pool_idx, self.gvs)
         if P is not None:
             P("maxpool_points", x=xv, v=self.gfeat[:, :, :C4], idx=self.pool_idx[:, :, :C4])
         # ---- head: first layer = per-point block over the concatenation + once-per-sample block
@@ -1489,6 +1489,8 @@ class _PointChain(_Views):
             Cp = self.conv[-1]
             self.pooled = torch.empty(B, Nb, Cp, **act)
             self.pool_idx = torch.empty(B, Nb, Cp, dtype=torch.int32, device=A.dev)
+            if not self.fused_tail:
+                ws = max(ws, hb.conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, self.conv[-2], Cp, L, dt))
             if self.fused_tail:
                 self.zhit = torch.empty(B, Nb, Cp, **f32)
                 self.moments = torch.empty(hb.conv1x1_bn_maxpool_saved_floats(B, self.conv[-2], Cp), **f32)
@@ -1534,9 +1536,8 @@ class _PointChain(_Views):
                                       self.z[i], _cs(B, co, L), y, ys, hb.ACT_RELU, 0.0, ws if _whole_pieces(L) else None)
                 x, ci = y, co
                 continue
-            hb.conv1x1_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), A.w(k + ".w"), A.w(k + ".b"), self.z[i], _cs(B, co, L))
-            hb.bn_fwd_maxpool(B, Nb, co, L, dt, self.z[i], _cs(B, co, L), *self._bn(k), self.pooled, self.pool_idx,
-                              (Nb * co, co, 1), hb.ACT_RELU)
+            hb.conv1x1_bn_pool_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), A.w(k + ".w"), A.w(k + ".b"), *self._bn(k), self.z[i],
+                                   _cs(B, co, L), None, None, self.pooled, self.pool_idx, (Nb * co, co, 1), hb.ACT_RELU, 0.0, ws)
             break
         if not self.head:
             return x

@@ -79,6 +79,9 @@ _SIGS = {
     "hfta_bn_eval_fwd": (_i, [_i, _i, _i, _i, _i, _p, _s4, _p, _p, _p, _p, _f, _p, _s4, _i, _f, _p]),
     "hfta_bn_bwd": (_i, [_i, _i, _i, _i, _i, _p, _s4, _p, _s4, _p, _p, _p, _p, _p, _s4, _p, _p, _p, _i, _f, _p]),
     "hfta_bn_fwd_maxpool": (_i, [_i, _i, _i, _i, _i, _p, _s4, _p, _p, _f, _f, _p, _p, _p, _p, _p, _p, _s4, _i, _f, _p]),
+    "hfta_conv1x1_bn_pool_fwd_workspace_bytes": (_sz, [_i] * 6),
+    "hfta_conv1x1_bn_pool_fwd": (_i, [_i] * 6 + [_p, _s4, _p, _p, _p, _p, _f, _f, _p, _p, _p, _p, _p, _s4, _p, _s4, _p, _p, _s4,
+                                      _i, _f, _p, _sz, _p]),
     "hfta_bn_bwd_maxpool": (_i, [_i, _i, _i, _i, _i, _p, _s4, _p, _p, _s4, _p, _p, _p, _p, _p, _s4, _p, _p, _p, _i, _f, _p]),
     "hfta_conv1x1_bn_maxpool_bwd_workspace_bytes": (_sz, [_i] * 6),
     "hfta_conv1x1_bn_maxpool_bwd": (_i, [_i] * 6 + [_p] * 21 + [_i, _f, _p, _sz, _p]),
@@ -381,6 +384,20 @@ def bn_fwd_maxpool(B, Nb, C_, L, dtype, X, xs, gamma, beta, eps, momentum, runni
                                     momentum, _ptr(running_mean), _ptr(running_var), _ptr(save_mean),
                                     _ptr(save_invstd), _ptr(V), _ptr(idx), _strides(vs, 3), act, act_slope,
                                     _stream(stream)), "hfta_bn_fwd_maxpool")
+
+
+def conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, dtype) -> int:
+    return _lib.hfta_conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, dtype)
+
+
+def conv1x1_bn_pool_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, gamma, beta, eps, momentum, running_mean, running_var,
+                        save_mean, save_invstd, Z, zs, Y, ys, V, idx, vs, act=ACT_NONE, act_slope=0.0, workspace=None,
+                        stream=None):
+    wp, wb = _ws(workspace)
+    _check(_lib.hfta_conv1x1_bn_pool_fwd(B, Nb, Ci, Co, L, dtype, _ptr(X), _strides(xs), _ptr(W), _ptr(bias), _ptr(gamma),
+                                         _ptr(beta), eps, momentum, _ptr(running_mean), _ptr(running_var), _ptr(save_mean),
+                                         _ptr(save_invstd), _ptr(Z), _strides(zs), _ptr(Y), _strides(ys), _ptr(V), _ptr(idx),
+                                         _strides(vs, 3), act, act_slope, wp, wb, _stream(stream)), "hfta_conv1x1_bn_pool_fwd")
 
 
 def bn_bwd_maxpool(B, Nb, C_, L, dtype, X, xs, dV, idx, vs, gamma, beta, save_mean, save_invstd, dX, dxs, dgamma,

@@ -108,6 +108,123 @@ __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
   }
 }
 
+// Normalise, activate, store AND take each row's maximum of the stored values: the pass that writes the activated tensor
+// is the one that would be read again for the maximum (512 -> 2048 channels, 6 x 16 x 2500 points: 400 + 204 us apart,
+// 404 here).  A wavefront per row; the maximum as hfta_maxpool_points takes it, lowest index on ties.
+template <typename T>
+__global__ __launch_bounds__(256) void bn_apply_maxpool_kernel(BnPoolFwdArgs p, T* Y, int64_t ysb, int64_t ysn, int64_t ysc, int64_t rows) {
+  constexpr int U = 5;                                     // pieces in flight: a 2500-point row is two rounds
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  const int c = (int)(r % p.C);
+  const int64_t bn = r / p.C;
+  const int n = (int)(bn % p.Nb), b = (int)(bn / p.Nb), k = b * p.C + c;
+  const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + n * p.xsn + c * p.xsc;
+  T* y = Y + b * ysb + n * ysn + c * ysc;
+  const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
+  const int chunks = p.L / 4;
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+  for (int c0 = lane; c0 < chunks; c0 += 64 * U) {
+    float v[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_vec<T, 4>(x + min(c0 + 64 * u, chunks - 1) * 4, v[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ch = c0 + 64 * u;
+      if (ch < chunks) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[u][e] = Elem<T>::to_f32(Elem<T>::from_f32(apply_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope)));
+          if (v[u][e] > best || bi == 0x7fffffff) { best = v[u][e]; bi = ch * 4 + e; }
+        }
+        store_vec<T, 4>(y + ch * 4, v[u]);
+      }
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(best, o, 64);
+    const int oi = __shfl_xor(bi, o, 64);
+    if (oi != 0x7fffffff && (bi == 0x7fffffff || ov > best || (ov == best && oi < bi))) { best = ov; bi = oi; }
+  }
+  if (lane == 0) {
+    const int64_t o = b * p.vsb + n * p.vsn + c * p.vsc;
+    reinterpret_cast<T*>(p.V)[o] = Elem<T>::from_f32(best);
+    p.idx[o] = bi;
+  }
+}
+
+// Statistics and pooled values from what the fp32 convolution's epilogue left per (sample, column tile, channel): sum, sum
+// of squares about the tile's mean, extreme of z (largest, or smallest where gamma < 0) and where it is.  BatchNorm is
+// monotone in z per channel and the activations taken here do not decrease, so the extreme's normalised value is the row's
+// maximum; a row whose activated values are all equal (clipped, or gamma = 0) has its maximum at point 0.  The 1.3 GB of z
+// are not read (4 x 32 x 2500 points, 1024 channels: bn_fwd_maxpool_kernel 402 us, this 23 and the epilogue 122 more).
+// 16 channels a workgroup: 16 lanes read 256 contiguous bytes of a part, 64 parts in flight.
+constexpr int PP_C = 16, PP_P = 64;
+__global__ __launch_bounds__(PP_C * PP_P) void bn_pool_parts_kernel(BnPoolFwdArgs p, const float4* __restrict__ part, int tiles, int cols) {
+  __shared__ double red[PP_P][PP_C][2];
+  const int cl = threadIdx.x % PP_C, pl = threadIdx.x / PP_C;
+  const int c = blockIdx.x * PP_C + cl, b = blockIdx.y, k = b * p.C + c;
+  const bool live = c < p.C;
+  const float4* pp = part + (int64_t)b * p.Nb * tiles * p.C + (live ? c : 0);
+  const double full = 1.0 / cols, last = 1.0 / (p.L - (tiles - 1) * cols);
+  double s1 = 0.0, s2 = 0.0;
+#pragma unroll 4
+  for (int i = pl; i < p.Nb * tiles; i += PP_P) {
+    const float4 v = pp[(int64_t)i * p.C];
+    s1 += (double)v.x;
+    s2 += (double)v.y + (double)v.x * (double)v.x * ((i + 1) % tiles ? full : last);
+  }
+  red[pl][cl][0] = s1;
+  red[pl][cl][1] = s2;
+  __syncthreads();
+  for (int h = PP_P / 2; h > 0; h >>= 1) {
+    if (pl < h) {
+      red[pl][cl][0] += red[pl + h][cl][0];
+      red[pl][cl][1] += red[pl + h][cl][1];
+    }
+    __syncthreads();
+  }
+  if (!live) return;
+  const double m = (double)p.Nb * (double)p.L, mz = red[0][cl][0] / m;
+  double var = red[0][cl][1] / m - mz * mz;
+  var = var < 0.0 ? 0.0 : var;
+  const float mean = (float)mz, invstd = (float)(1.0 / sqrt(var + (double)p.eps));
+  const float g = p.gamma[k], bt = p.beta[k];
+  if (pl == 0) {
+    p.save_mean[k] = mean;
+    p.save_invstd[k] = invstd;
+    if (p.running_mean) {
+      const float unb = (float)(m > 1.0 ? var * (m / (m - 1.0)) : var);
+      p.running_mean[k] = (1.f - p.momentum) * p.running_mean[k] + p.momentum * mean;
+      p.running_var[k] = (1.f - p.momentum) * p.running_var[k] + p.momentum * unb;
+    }
+  }
+  const bool clips = p.act == HFTA_ACT_RELU || (p.act == HFTA_ACT_LEAKY && p.slope == 0.f);
+  for (int n = pl; n < p.Nb; n += PP_P) {
+    float best = -INFINITY;
+    int at = 0x7fffffff;
+#pragma unroll 4
+    for (int q = 0; q < tiles; ++q) {
+      const float4 v = pp[(int64_t)(n * tiles + q) * p.C];
+      if (v.z > best || at == 0x7fffffff) { best = v.z; at = __float_as_int(v.w); }
+    }
+    float pre = fmaf(g, ((g < 0.f ? -best : best) - mean) * invstd, bt);
+    const bool clipped = clips && !(pre > 0.f);
+    if (g == 0.f || clipped) {
+      at = 0;
+      const float z0 = reinterpret_cast<const float*>(p.X)[b * p.xsb + n * p.xsn + c * p.xsc];
+      pre = fmaf(g, (z0 - mean) * invstd, bt);
+      if (clipped && pre > 0.f) pre = 0.f;                 // the row's maximum was not positive
+    }
+    const int64_t o = b * p.vsb + n * p.vsn + c * p.vsc;
+    reinterpret_cast<float*>(p.V)[o] = apply_act(pre, p.act, p.slope);
+    p.idx[o] = at;
+  }
+}
+
 struct BnPoolBwdArgs {
   const void* X; const void* dV; const int32_t* idx; void* dX;
   const float* gamma; const float* beta; const float* save_mean; const float* save_invstd;
@@ -176,11 +293,73 @@ __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
   }
 }
 
+constexpr int POOL_MIN_COLS = 128;                         // narrowest column tile that comes with sums
+
 bool act_ok(int act) { return act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || act == HFTA_ACT_LEAKY; }
 
 }  // namespace
 
+namespace hfta {
+int conv1x1_fwd_pool_part(int B, int Nb, int Ci, int Co, int L, const void* X, const int64_t xs[4], const void* W, const void* bias,
+                          void* Z, const int64_t zs[4], const float* gamma, float4* part, int* cols, hipStream_t st);
+}
+
 extern "C" {
+
+size_t hfta_conv1x1_bn_pool_fwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype) {
+  if (B <= 0 || Nb <= 0 || Ci <= 0 || Co <= 0 || L <= 0 || !valid_dtype(dtype)) return 0;
+  if (dtype == HFTA_BF16) return hfta_conv1x1_bn_fwd_workspace_bytes(B, Nb, Ci, Co, L, dtype);
+  return (size_t)B * Nb * ((L + POOL_MIN_COLS - 1) / POOL_MIN_COLS) * Co * sizeof(float4);
+}
+
+int hfta_conv1x1_bn_pool_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, const void* X, const int64_t xs[4], const void* W,
+                             const void* bias, const float* gamma, const float* beta, float eps, float momentum,
+                             float* running_mean, float* running_var, float* save_mean, float* save_invstd, void* Z,
+                             const int64_t zs[4], void* Y, const int64_t ys[4], void* V, int32_t* idx, const int64_t vs[3], int act,
+                             float act_slope, void* workspace, size_t ws_bytes, void* stream) {
+  if (B <= 0 || Nb <= 0 || Ci <= 0 || Co <= 0 || L <= 0 || !valid_dtype(dtype) || !X || !xs || !W || !gamma || !beta ||
+      !save_mean || !save_invstd || !Z || !zs || (Y && !ys) || !V || !idx || !vs || !(eps >= 0.f))
+    return HFTA_EINVAL;
+  if ((running_mean == nullptr) != (running_var == nullptr)) return HFTA_EINVAL;
+  if (!act_ok(act) || xs[3] != 1 || zs[3] != 1 || (Y && ys[3] != 1) || B > 65535) return HFTA_EUNSUPPORTED;
+  hipStream_t st = as_stream(stream);
+  BnPoolFwdArgs a{Z, V, idx, gamma, beta, running_mean, running_var, save_mean, save_invstd,
+                  zs[0], zs[1], zs[2], vs[0], vs[1], vs[2], Nb, Co, L, act, eps, momentum, act_slope};
+  if (Y) {                       // the activated tensor is wanted too: statistics, then one pass for both
+    int rc = hfta_conv1x1_bn_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, gamma, beta, eps, momentum, running_mean, running_var,
+                                 save_mean, save_invstd, Z, zs, nullptr, nullptr, act, act_slope, workspace, ws_bytes, stream);
+    if (rc != HFTA_OK) return rc;
+    if (bn_vec4_ok(Z, zs, L, dtype) && bn_vec4_ok(Y, ys, L, dtype)) {
+      const int64_t rows = (int64_t)B * Nb * Co;
+      const dim3 grid((unsigned)((rows + 3) / 4));
+      if (dtype == HFTA_BF16)
+        hipLaunchKernelGGL(bn_apply_maxpool_kernel<bf16_raw>, grid, dim3(256), 0, st, a, (bf16_raw*)Y, ys[0], ys[1], ys[2], rows);
+      else
+        hipLaunchKernelGGL(bn_apply_maxpool_kernel<float>, grid, dim3(256), 0, st, a, (float*)Y, ys[0], ys[1], ys[2], rows);
+      return launch_status();
+    }
+    rc = hfta_bn_apply_fwd(B, Nb, Co, L, dtype, Z, zs, gamma, beta, save_mean, save_invstd, Y, ys, act, act_slope, stream);
+    return rc != HFTA_OK ? rc : hfta_maxpool_points(B, Nb, Co, L, dtype, Y, ys, V, idx, vs, stream);
+  }
+  // fp32: statistics and maxima from the convolution's epilogue; needs an activation that does not decrease
+  if (dtype == HFTA_F32 && !(act == HFTA_ACT_LEAKY && !(act_slope >= 0.f)) && workspace &&
+      ws_bytes >= hfta_conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, dtype) && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 &&
+      (int64_t)B * Nb <= 65535) {
+    int cols = 0;
+    const int rc = conv1x1_fwd_pool_part(B, Nb, Ci, Co, L, X, xs, W, bias, Z, zs, gamma, (float4*)workspace, &cols, st);
+    if (rc != HFTA_OK) return rc;
+    if (cols > 0) {
+      hipLaunchKernelGGL(bn_pool_parts_kernel, dim3((unsigned)((Co + PP_C - 1) / PP_C), (unsigned)B), dim3(PP_C * PP_P), 0, st, a,
+                         (const float4*)workspace, (L + cols - 1) / cols, cols);
+      return launch_status();
+    }
+  } else {
+    const int rc = hfta_conv1x1_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, Z, zs, HFTA_ACT_NONE, 0.f, stream);
+    if (rc != HFTA_OK) return rc;
+  }
+  return hfta_bn_fwd_maxpool(B, Nb, Co, L, dtype, Z, zs, gamma, beta, eps, momentum, running_mean, running_var, save_mean,
+                             save_invstd, V, idx, vs, act, act_slope, stream);
+}
 
 int hfta_bn_fwd_maxpool(int B, int Nb, int C, int L, int dtype, const void* X, const int64_t xs[4], const float* gamma,
                         const float* beta, float eps, float momentum, float* running_mean, float* running_var,

@@ -60,6 +60,13 @@ struct GemmDesc {
   // that hold B's tiles anyway; *bsum_done is set when the kernel launched writes them (otherwise nothing does).
   float* bsum;
   bool* bsum_done;
+  // What a BatchNorm and a maximum over each row need from the output (fp32 k=1 convolution forward): per (group, column
+  // tile, row m) the sum over the tile's columns, the sum of squares about their mean, the largest value of
+  // sign(gamma[g0][m]) c and its first column, [G0*G1][tiles_n][M] x 16 bytes.  *pool_cols is the tile's width when the
+  // kernel launched writes them, 0 otherwise.
+  float4* pool_part;
+  const float* pool_gamma;
+  int* pool_cols;
 };
 
 struct GemmArgs {
@@ -83,6 +90,8 @@ struct GemmArgs {
   int64_t c_seg_stride;
   float* stat_part;              // see GemmDesc
   float* bsum;                   // see GemmDesc
+  float4* pool_part;             // see GemmDesc
+  const float* pool_gamma;
 };
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;

@@ -151,6 +151,9 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   if (d.stat_done) *d.stat_done = false;
   a.bsum = nullptr;                    // set by the launchers of kernels that take it
   if (d.bsum_done) *d.bsum_done = false;
+  a.pool_part = nullptr;
+  a.pool_gamma = nullptr;
+  if (d.pool_cols) *d.pool_cols = 0;
 
   // vector-load eligibility: every address the fast path forms must be aligned
   const int es = (int)dtype_size(d.dtype);

@@ -248,7 +248,9 @@ constexpr int f32_smem_bytes(int tiles) {
   return tiles > epi ? tiles : epi;
 }
 
-template <bool A_KC, bool B_KC, int NB, int VEC, bool SPLIT>
+// POOL: the epilogue also leaves what a BatchNorm and a maximum over each row need (GemmDesc::pool_part), from the staged
+// rows: four threads a row, one loop for sum and maximum, one for the squares about the mean.
+template <bool A_KC, bool B_KC, int NB, int VEC, bool SPLIT, bool POOL = false>
 __global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f32_kernel(GemmArgs p) {
   typedef F32Operand<A_KC, NB, VEC> OA;
   typedef F32Operand<B_KC, NB, VEC> OB;
@@ -470,12 +472,69 @@ __global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f
           if (n + k < p.N) Cb[(int64_t)m * c_ld + (part ? (int64_t)(n + k) : col_offset(n + k, p.c_seg, p.c_seg_stride))] = e[k];
       }
     }
+    if constexpr (POOL) {
+      constexpr int CW = T / 4;                            // columns per thread
+      const int rl = t >> 2, c0 = (t & 3) * CW, m = m0 + pass * 64 + rl;
+      const int cnt = min(max(p.N - n0 - c0, 0), CW), all = min(p.N - n0, T);
+      const float sgn = m < p.M && p.pool_gamma[(int64_t)g0 * p.M + m] < 0.f ? -1.f : 1.f;
+      const float* row = st + rl * SP + c0;
+      float v[CW];                                         // the thread's columns, once
+#pragma unroll
+      for (int c = 0; c < CW; c += 4) {
+        const float4 q = *reinterpret_cast<const float4*>(row + c);
+        v[c] = q.x; v[c + 1] = q.y; v[c + 2] = q.z; v[c + 3] = q.w;
+      }
+      const bool edge = n0 + T > p.N;                      // the row's last tile: columns past the end do not take part
+      float s4[4] = {0.f, 0.f, 0.f, 0.f}, best = -INFINITY;
+#pragma unroll
+      for (int c = 0; c < CW; ++c) s4[c & 3] += !edge || c < cnt ? v[c] : 0.f;
+      float sum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      sum += __shfl_xor(sum, 1, 64);
+      sum += __shfl_xor(sum, 2, 64);
+      const float mean = sum / (float)all;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s4[k] = 0.f;
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const float d = !edge || c < cnt ? v[c] - mean : 0.f;
+        s4[c & 3] = fmaf(d, d, s4[c & 3]);
+      }
+      float sq = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      sq += __shfl_xor(sq, 1, 64);
+      sq += __shfl_xor(sq, 2, 64);
+      // the maximum, then the first column that holds it (walked downwards)
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        v[c] = !edge || c < cnt ? v[c] * sgn : -INFINITY;
+        best = fmaxf(best, v[c]);
+      }
+      int at = 0;
+#pragma unroll
+      for (int c = CW - 1; c >= 0; --c) at = v[c] == best ? c : at;
+      at += n0 + c0;
+#pragma unroll
+      for (int o = 1; o < 4; o <<= 1) {
+        const float ob = __shfl_xor(best, o, 64);
+        const int oa = __shfl_xor(at, o, 64);
+        if (ob > best || (ob == best && oa < at)) { best = ob; at = oa; }
+      }
+      if ((t & 3) == 0 && m < p.M)
+        p.pool_part[((int64_t)g * p.tiles_n + tile_n) * p.M + m] = make_float4(sum, sq, best, __int_as_float(at));
+    }
     if (pass + 1 < NB) __syncthreads();
   }
 }
 
 template <int NB, int VEC, bool SPLIT>
 int f32_layout(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st) {
+  if constexpr (SPLIT && NB == 2) {
+    if (a.pool_part) {
+      hipLaunchKernelGGL((gemm_f32_kernel<true, false, NB, VEC, true, true>), grid, dim3(GEMM_THREADS), 0, st, a);
+      const int rc = launch_status();
+      if (rc == HFTA_OK) *d.pool_cols = 64 * NB;
+      return rc;
+    }
+  }
   if (d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, false, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
   else if (d.a_kc && d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, true, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
   else if (!d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<false, false, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
@@ -504,6 +563,11 @@ int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
   dim3 grid((unsigned)(a.tiles_m * a.tiles_n), 1, (unsigned)(G * a.splits));
   const bool vec = d.K >= 4 && (d.a_kc || d.M >= 4) && (d.b_kc || d.N >= 4);
   const bool whole = vec && (d.a_kc ? d.K : d.M) % 4 == 0 && (d.b_kc ? d.K : d.N) % 4 == 0;   // no piece straddles a row's end
+  // (64x64 tiles: a pass over so small an output costs less than the epilogue, 2 x 4 x 256 points 188.5 us a step, 191.8 with)
+  if (d.pool_part && d.pool_cols && vec && d.a_kc && !d.b_kc && a.splits == 1 && d.act == HFTA_ACT_NONE && d.c_seg <= 0 && !small) {
+    a.pool_part = d.pool_part;
+    a.pool_gamma = d.pool_gamma;
+  }
   // Small tiles under at most 64 k are bound by their tensors and better off with the fp32 instruction's four
   // workgroups per compute unit than with the split's three (64 -> 64 on 4 x 32 x 2500 points: 45 us, split 53).
   if (small && (int64_t)d.K * d.S <= 64)

@@ -455,6 +455,29 @@ static int conv1x1_fwd_impl(int B, int Nb, int Ci, int Co, int L, int dtype, con
   return gemm_launch(d, as_stream(stream));
 }
 
+}  // extern "C"
+
+namespace hfta {
+// The fp32 convolution with the partial sums and row maxima of GemmDesc::pool_part; *cols: the width of the column tiles
+// they belong to, 0 if the kernel that ran does not write them (the output is there either way).
+int conv1x1_fwd_pool_part(int B, int Nb, int Ci, int Co, int L, const void* X, const int64_t xs[4], const void* W, const void* bias,
+                          void* Z, const int64_t zs[4], const float* gamma, float4* part, int* cols, hipStream_t st) {
+  const int rc = check_conv1x1(B, Nb, Ci, Co, L, HFTA_F32);
+  if (rc != HFTA_OK) return rc;
+  GemmDesc d = base_desc(HFTA_F32);
+  d.A = W; d.Bm = X; d.C = Z;
+  d.M = Co; d.N = L; d.K = Ci; d.G0 = B; d.G1 = Nb;
+  d.a_kc = true; d.a_ld = Ci; d.a_g0 = (int64_t)Co * Ci; d.a_g1 = 0;
+  d.b_kc = false; d.b_ld = xs[2]; d.b_g0 = xs[0]; d.b_g1 = xs[1];
+  d.c_ld = zs[2]; d.c_g0 = zs[0]; d.c_g1 = zs[1];
+  d.bias = bias; d.bias_mode = 1; d.bias_g0 = Co; d.bias_g1 = 0;
+  d.pool_part = part; d.pool_gamma = gamma; d.pool_cols = cols;
+  return gemm_launch(d, st);
+}
+}  // namespace hfta
+
+extern "C" {
+
 int hfta_conv1x1_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, const void* X, const int64_t xs[4],
                      const void* W, const void* bias, void* Y, const int64_t ys[4], int act, float act_slope,
                      void* stream) {
