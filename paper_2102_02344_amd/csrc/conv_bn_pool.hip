@@ -1067,8 +1067,8 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   // is flat (ReLU, or LeakyReLU with slope 0, at a maximum that is not positive) or the channel's
   // scale is zero, every point of the row holds the same value and the lowest index, 0, is the
   // argmax.  z at point 0 is recomputed here (Ci products) since no slice kept it.
-  const bool flat = g == 0.f || ((p.act == HFTA_ACT_RELU || (p.act == HFTA_ACT_LEAKY && p.slope == 0.f)) && !(pre > 0.f));
-  if (flat && at != 0) {
+  const bool clipped = (p.act == HFTA_ACT_RELU || (p.act == HFTA_ACT_LEAKY && p.slope == 0.f)) && !(pre > 0.f);
+  if ((g == 0.f || clipped) && at != 0) {
     const bf16_raw* x0 = p.X + b * p.xsb + n * p.xsn;
     const bf16_raw* w = p.W + (int64_t)k * p.Ci;
     float acc = 0.f;
@@ -1080,7 +1080,7 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
     at = 0;
     z = acc + bias;
     pre = fmaf(scale, pooled_z(z, p.L) - mean, beta);
-    if ((p.act == HFTA_ACT_RELU || (p.act == HFTA_ACT_LEAKY && p.slope == 0.f)) && pre > 0.f) pre = 0.f;   // the row's maximum was not positive
+    if (clipped && pre > 0.f) pre = 0.f;                 // the row's maximum was not positive
   }
   const float y = apply_act(pre, p.act, p.slope);
   p.V[b * p.vsb + n * p.vsn + c * p.vsc] = f32_to_bf16(y);

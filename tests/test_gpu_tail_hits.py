@@ -61,3 +61,21 @@ def test_crowded_hits(hb, B, Nb, Ci, Co, L, kind):
     assert np.abs(host(dBt) - ref[4]).max() <= 2e-4 * max(np.abs(ref[4]).max(), sc * 1e-2)
     check(host(dX), ref[0], TOL["bf16"], "dX")
     check(host(dW).reshape(ref[1].shape), ref[1], 2e-4, "dW")
+
+
+@pytest.mark.parametrize("act", [0, 1, 2])
+def test_zero_scale_pools_the_shift(hb, act):
+    """gamma == 0: every point's activated value is act(beta), the first point's index; a positive beta is not clipped."""
+    B, Nb, Ci, Co, L = 1, 2, 16, 24, 300
+    X = dev(hi.snap(np.abs(hi.normal(351, (Nb, Ci, L))), "bf16"), "bf16")
+    W, bt = dev(hi.normal(352, (Co, Ci), "bf16"), "bf16"), hi.normal(353, (Co,)).astype(np.float32)
+    G, Bt = torch.zeros(Co, device="cuda"), dev(bt)
+    SM, SI, ZH = (torch.empty(n, device="cuda") for n in (Co, Co, Nb * Co))
+    V = torch.full((B, Nb, Co), float("nan"), dtype=torch.bfloat16, device="cuda")
+    I = torch.full((B, Nb, Co), -1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(hb.conv1x1_bn_maxpool_workspace_bytes(B, Nb, Ci, Co, L, DT["bf16"]), dtype=torch.uint8, device="cuda")
+    hb.conv1x1_bn_maxpool_fwd(B, Nb, Ci, Co, L, DT["bf16"], X, conv_strides(B, Ci, L), W, None, G, Bt, 1e-5, 0.1, None, None, SM, SI, V, I,
+                              (Nb * Co, Co, 1), ZH, None, act, 0.2, ws)
+    ref = bt if act == 0 else np.where(bt > 0, bt, (0.2 if act == 2 else 0.0) * bt)
+    assert (bt > 0).any() and int(I.abs().max()) == 0
+    assert torch.equal(V[0].cpu(), torch.from_numpy(ref.astype(np.float32)).bfloat16().expand(Nb, Co))
