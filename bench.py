@@ -162,7 +162,7 @@ def kernel_label(name, a):
         if name == "conv2d_grouped_fwd":       # sample-folded implicit GEMM, else the column-buffer lowering
             if full:
                 return small % "fwd"
-            return "conv_ig_fwd_kernel<4,4,2>" if ig else "conv2d fwd: im2col_lds_kernel + gemm"
+            return "conv_rows_fwd_kernel" if ig else "conv2d fwd: im2col_lds_kernel + gemm"
         if a[14] is not None:                  # dX and dW are asked for in separate calls
             if full:
                 return small % "dx"
@@ -172,7 +172,7 @@ def kernel_label(name, a):
                     else "conv2d dX: pack_dy_kernel + gemm + col2im_lds_kernel")
         if full:
             return small % "dw"
-        return ("conv_ig_dw_kernel + ig_split_reduce_kernel" if ig and Co >= 32 and W <= 64
+        return ("conv_rows_dw_kernel + ig_split_reduce_kernel" if ig and Co >= 32 and W <= 64
                 else "conv2d dW: pack_dy_kernel + im2col_lds_kernel + gemm")
     if name == "conv1x1_bwd":          # called with either dX or dW requested, never both
         B, Nb, Ci, Co, L, dt = a[:6]

@@ -2,12 +2,9 @@
 // of one model (fusion rules table, rows "Conv2d" and "ConvTranspose2d": one grouped operator with
 // G = B; here the model is grid.z and never mixes with the channels).
 //
-// No column buffer exists in memory.  Per 32-element k-tile a workgroup (128 x 128 output tile, four
-// wavefronts of 64 x 64) brings the raw input patch its 128 columns need -- whole image rows, 16-byte
-// loads -- into LDS, builds the k-contiguous column tile [128 columns][32 k] from it there (LDS reads
-// of single elements, 16-byte writes), and runs the matrix instructions of the batched GEMM core on
-// it; the weight tile is an ordinary k-contiguous operand.  Folding the sample index into the columns
-// keeps the tiles full for 8x8 and 4x4 images, where a GEMM per sample has 64 or 16 columns.
+// No column buffer exists in memory: a workgroup brings the raw image rows its output tile needs into LDS and the matrix
+// instructions' window operand is read straight from them (conv2d_rows.h, conv2d_planes.h).  Folding the sample index into the
+// columns keeps the tiles full for 8x8 and 4x4 images, where a GEMM per sample has 64 or 16 columns.
 //
 //   forward (and the data gradient of a transposed convolution):
 //       Y[o][(n, y, x)] = sum_{(c, ky, kx)} W[o][(c, ky, kx)] X[n][c][s y + ky - p][s x + kx - p]
@@ -15,7 +12,7 @@
 //       dX[c][(n, qy, qx)] = sum_{(o, jy, jx)} Wp[class][c][(o, jy, jx)] dY[n][o][qy + py - 1 + jy][qx + px - 1 + jx]
 //     a stride-1 correlation with a 2x2 window and the weights regrouped per class (the taps a class
 //     does not see are never multiplied); results land at (2 qy + py, 2 qx + px).
-//   weight gradient: conv_ig_dw_kernel below, dW[o][(c, ky, kx)] = sum_{(n, y, x)} dY[n][o][y][x] X[n][c][...].
+//   weight gradient: dW[o][(c, ky, kx)] = sum_{(n, y, x)} dY[n][o][y][x] X[n][c][...].
 //
 // bf16 only; output grids whose width and height are powers of two; see ig_*_supported.
 #include <mutex>
@@ -59,7 +56,7 @@ struct IgArgs {
   int M, K, N;                          // GEMM sizes per model: rows, reduction, columns = Nb * Ho * Wo
   int Ho, Wo, lgWo, lgP;                // logical output grid per sample (powers of two)
   int OW, oys, oxs;                     // output image width in memory, output step per grid step
-  int tap_step;                         // 1 (patch elements between the taps of a window row; see the column-tile build)
+  int tap_step;                         // gathering kernel: 1 (patch elements between the taps of a window row)
   int NI, TR, PR, PW, SP;               // samples per tile, grid rows per tile and sample, patch rows, row pitch, sample pitch (elements)
   int nchunk, chunk_el;                 // 16- or 8-byte pieces of patch rows per k-tile, elements per piece
   int chp, plp;                         // plane kernels: bytes of a channel's rows in a plane, bytes between planes
@@ -179,69 +176,55 @@ __device__ __forceinline__ void ig_epilogue(const IgArgs& p, f32x16_t (&acc)[2][
   }
 }
 
+// Data gradient with a gathered column tile, for images of four-pixel rows taller than a tile (conv2d_planes.h has the others).
 // Four wavefronts; each computes 64 rows x 64 columns of a TM = 128 row tile, or 64 rows x 32 columns
-// of a TM = 64 row tile (layers with at most 64 output rows).
-// PAIR (data gradient): the tile's 128 columns are 64 pixels of the parity class px = 0 followed by
-// the same 64 pixels of px = 1 (the grid's y = py); the weight tile holds both classes' rows, a
-// wavefront works on the class its columns belong to, and the epilogue interleaves the two classes
-// into whole 16-byte pieces of the output rows.
+// of a TM = 64 row tile (layers with at most 64 output rows).  The tile's 128 columns are 64 pixels of the parity class px = 0
+// followed by the same 64 pixels of px = 1 (the grid's y = py); a wavefront works on the class its columns belong to, and the
+// epilogue interleaves the two classes into whole 16-byte pieces of the output rows.
 //
-// Weight tile, column tile and patch are double-buffered and there is one barrier per k-tile.  In
-// iteration kt a thread
+// Column tile and patch are double-buffered and there is one barrier per k-tile.  In iteration kt a thread
 //   issues the LDS reads that gather its part of column tile kt+1 from patch kt+1,
-//   parks the weights of k-tile kt+1 and the patch of k-tile kt+2 (registers -> LDS),
-//   issues the loads of the weights of kt+2 and of the patch of kt+3,
+//   parks the patch of k-tile kt+2 (registers -> LDS) and issues the loads of the patch of kt+3,
 //   runs the matrix instructions on k-tile kt (the gather's reads return meanwhile),
+//   issues the loads of the weights of kt+2 (fragments, see below),
 //   writes its part of column tile kt+1, and meets the others at the barrier.
 // Every load is a raw buffer load whose offset is inside the model's slice or the fixed out-of-range
 // value (the hardware returns zeros): no load sits under control flow, so the compiler's wait
 // counters let the loads of later k-tiles stay in flight across iterations.  Nothing in the loop
 // depends on the k-tile index: loads past the last k-tile are out of range, and what is parked or
 // built from them lands in buffers nobody reads any more.
-template <int KH, int KW, int S, bool PAIR, int TM, bool CH8>
-__global__ __launch_bounds__(256) void conv_ig_fwd_kernel(IgArgs p) {
+template <int TM>
+__global__ __launch_bounds__(256) void conv_ig_gather_kernel(IgArgs p) {
   static_assert(TM == 128 || TM == 64, "row tiles of 128 or 64");
-  constexpr int TK = KH * KW, CPT = 32 / TK;             // taps per channel, channels per k-tile
+  constexpr int KW = 2, TK = 4, CPT = 8;                 // taps per window row, per channel; channels per k-tile
   constexpr int NT = 256;
-  constexpr int AROWS = TM;                              // rows of the weight tile (PAIR: none, see below)
-  constexpr int NA = AROWS * 4 / NT;                     // 16-byte weight pieces per thread
-  // Weights as matrix-instruction fragments straight from memory: only where they are stored in
-  // fragment order (PAIR).  From the forward's row-major weights a wavefront's fragment load touches
-  // 32 rows of 64 bytes, and the kernel measured 1.3-1.5x slower than with the LDS tile.
-  constexpr bool AFRAG = PAIR;
-  constexpr int A_BYTES = AFRAG ? 0 : AROWS * GEMM_PITCH;
   constexpr int KPT = 16;                                // k per thread of the column tile
-  constexpr int COLS = PAIR ? 64 : 128;                  // pixel columns per tile
+  constexpr int COLS = 64;                               // pixels per tile
   constexpr int FN = TM == 128 ? 2 : 1;                  // 32-column blocks per wavefront
-  constexpr int CH = CH8 ? 8 : 4;                        // elements per patch piece
+  constexpr int CH = 4;                                  // elements per patch piece
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  auto As = [&](int buf) { return smem + buf * A_BYTES; };
-  auto Cb = [&](int buf) { return smem + 2 * A_BYTES + buf * GEMM_TILE_BYTES; };
+  auto Cb = [&](int buf) { return smem + buf * GEMM_TILE_BYTES; };
   const int chan_el = p.NI * p.SP;
   const int patch_el = CPT * chan_el;
-  auto Pt = [&](int buf) { return reinterpret_cast<bf16_raw*>(smem + 2 * A_BYTES + 2 * GEMM_TILE_BYTES) + buf * patch_el; };
+  auto Pt = [&](int buf) { return reinterpret_cast<bf16_raw*>(smem + 2 * GEMM_TILE_BYTES) + buf * patch_el; };
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int bx, by, b;
   ig_block(p.grid, bx, by, b);
   const int tile_m = bx / p.tiles_n, tile_n = bx % p.tiles_n;
   const int m0 = tile_m * TM, n0 = tile_n * COLS;
-  // grid y: py with PAIR, else the k split
-  const int py2 = PAIR ? 2 * by : 0;
-  const int split = PAIR ? 0 : by;
+  const int py2 = 2 * by;                                // first class of the pair
   const IgClass cl0 = p.cls[py2];
   const int P = 1 << p.lgP;
   const int img0 = n0 >> p.lgP;                          // first sample of the tile
   const int y0 = (n0 & (P - 1)) >> p.lgWo;               // first grid row (tiles inside one sample)
   const int HW = p.H * p.W;
   const int rmin = cl0.oy;                               // first patch row's image row for grid row 0 (the same for both classes of a pair)
-  const int row_base = y0 * S + rmin;
+  const int row_base = y0 + rmin;
   const int ktiles = (p.K + 31) / 32;
-  const int kt0 = split * p.kt_per_split, kt1 = min(ktiles, kt0 + p.kt_per_split);
 
   // position of the wavefront's block of the tile
   const int wm = TM == 128 ? wave >> 1 : 0;
   const int col0 = TM == 128 ? (wave & 1) * 64 : wave * 32;
-  const int a_row0 = wm * 64;
 
   const __amdgpu_buffer_rsrc_t rx = pf_rsrc(p.X + (int64_t)b * p.x_model, p.x_bytes);
   const __amdgpu_buffer_rsrc_t rw = pf_rsrc(p.A + (int64_t)b * p.a_model, p.a_bytes);
@@ -271,81 +254,49 @@ __global__ __launch_bounds__(256) void conv_ig_fwd_kernel(IgArgs p) {
   const int bcol = t & 127, bhalf = t >> 7;
   int boff;                                               // patch element of tap (0, 0), first channel of this half
   {
-    const IgClass cl = PAIR ? p.cls[py2 + (bcol >> 6)] : cl0;
-    const int n = n0 + (PAIR ? (bcol & 63) : bcol);
+    const IgClass cl = p.cls[py2 + (bcol >> 6)];
+    const int n = n0 + (bcol & 63);
     const int il = (n >> p.lgP) - img0;
     const int y = (n & (P - 1)) >> p.lgWo, x = n & (p.Wo - 1);
-    boff = il * p.SP + ((y - y0) * S + (cl.oy - rmin)) * p.PW + x * S + cl.ox + IG_MARGIN;
+    boff = il * p.SP + (y - y0 + (cl.oy - rmin)) * p.PW + x + cl.ox + IG_MARGIN;
     boff += ((bhalf * KPT) / TK) * chan_el;
   }
-  // ---- weights.  Forward: rows ra + 64 h of the weight tile, 8 k at ga, through LDS.
-  // PAIR: the regrouped weights are stored in the order the matrix instructions consume them
+  // ---- weights: regrouped and stored in the order the matrix instructions consume them
   // ([class][row tile][k-tile][32-row block][k-step][lane][8 k], ig_pack_class_w_kernel), so a
   // wavefront loads its own fragments -- 64 rows of its class, four 16-byte loads per lane, each a
   // contiguous 1 KB per wavefront -- straight into registers: no LDS write, no LDS fragment read.
-  const int ga = t & 3, ra = t >> 2;
-  uint32_t wo[NA];
-  uint32_t fo = 0;                                        // PAIR: byte offset of this lane's first fragment of k-tile 0
-  if constexpr (PAIR) {
-    const int64_t tile_el = (int64_t)ktiles * TM * 32;    // one (class, row tile): every k-tile's TM x 32 block
-    fo = (uint32_t)((p.cls[py2 + (col0 >> 6)].a_off + (int64_t)tile_m * tile_el) * 2) + (uint32_t)((wm * 4 * 64 + lane) * 16);
-#pragma unroll
-    for (int h = 0; h < NA; ++h) wo[h] = PF_OOB;
-  } else {
-#pragma unroll
-    for (int h = 0; h < NA; ++h) {
-      const int r = ra + (NT / 4) * h;
-      const int m = m0 + r;
-      wo[h] = m < p.M ? (uint32_t)((cl0.a_off + (int64_t)m * p.K + ga * 8) * 2) : PF_OOB;
-    }
-  }
-  pf_u32x4 qa[NA], qp[2];
-  pf_u32x4 fa_cur[2][2], fa_nxt[2][2];                    // PAIR: fragments [32-row block][k-step] of this and the next k-tile
+  const int64_t tile_el = (int64_t)ktiles * TM * 32;      // one (class, row tile): every k-tile's TM x 32 block
+  // byte offset of this lane's first fragment of k-tile 0
+  const uint32_t fo = (uint32_t)((p.cls[py2 + (col0 >> 6)].a_off + (int64_t)tile_m * tile_el) * 2) + (uint32_t)((wm * 4 * 64 + lane) * 16);
+  pf_u32x2 qp[2];
+  pf_u32x4 fa_cur[2][2], fa_nxt[2][2];                    // fragments [32-row block][k-step] of this and the next k-tile
   auto issue_a = [&](int kt) {
-    if constexpr (PAIR) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-          fa_nxt[i][s2] = __builtin_amdgcn_raw_buffer_load_b128(
-              rw, (int)(kt < ktiles ? fo + (uint32_t)kt * (uint32_t)(TM * 64) + (uint32_t)((i * 2 + s2) * 1024) : PF_OOB), 0, 0);
-    } else {
-      const bool in_k = kt * 32 + ga * 8 + 8 <= p.K;
-#pragma unroll
-      for (int h = 0; h < NA; ++h)
-        qa[h] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)((in_k && wo[h] != PF_OOB) ? wo[h] + (uint32_t)kt * 64u : PF_OOB), 0, 0);
-    }
+      for (int s2 = 0; s2 < 2; ++s2)
+        fa_nxt[i][s2] = __builtin_amdgcn_raw_buffer_load_b128(
+            rw, (int)(kt < ktiles ? fo + (uint32_t)kt * (uint32_t)(TM * 64) + (uint32_t)((i * 2 + s2) * 1024) : PF_OOB), 0, 0);
   };
   auto issue_p = [&](int kt) {
     const int c0 = kt * CPT;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const uint32_t off = (c0 + pcl[i] < p.Cx && pxo[i] != PF_OOB) ? pxo[i] + (uint32_t)kt * px_step : PF_OOB;
-      if constexpr (CH8) {
-        qp[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
-      } else {
-        const pf_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)off, 0, 0);
-        qp[i].x = v.x; qp[i].y = v.y;
-      }
+      qp[i] = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)off, 0, 0);
     }
   };
-  auto park_a = [&](int buf) {
-    if constexpr (AFRAG) {
+  auto park_a = [&]() {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) fa_cur[i][s2] = fa_nxt[i][s2];
-    } else {
-#pragma unroll
-      for (int h = 0; h < NA; ++h) *reinterpret_cast<pf_u32x4*>(As(buf) + (ra + (NT / 4) * h) * GEMM_PITCH + ga * 16) = qa[h];
-    }
+      for (int s2 = 0; s2 < 2; ++s2) fa_cur[i][s2] = fa_nxt[i][s2];
   };
   auto park_p = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       if (pl[i] >= 0) {                                   // a store under a branch; the loads stay branch-free
-        if constexpr (CH8) *reinterpret_cast<pf_u32x4*>(Pt(buf) + pl[i]) = qp[i];
-        else *reinterpret_cast<uint2*>(Pt(buf) + pl[i]) = make_uint2(qp[i].x, qp[i].y);
+        *reinterpret_cast<uint2*>(Pt(buf) + pl[i]) = make_uint2(qp[i].x, qp[i].y);
       }
     }
   };
@@ -379,16 +330,12 @@ __global__ __launch_bounds__(256) void conv_ig_fwd_kernel(IgArgs p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   auto mma = [&](int buf) {
-    const unsigned char* Ab = As(buf) + (a_row0 + r) * GEMM_PITCH + gsel * 16;
     const unsigned char* Bb = Cb(buf) + (col0 + r) * GEMM_PITCH + gsel * 16;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       bf16x8_t a[2], bq[FN];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if constexpr (AFRAG) a[i] = __builtin_bit_cast(bf16x8_t, fa_cur[i][s]);
-        else a[i] = *reinterpret_cast<const bf16x8_t*>(Ab + i * 32 * GEMM_PITCH + s * 32);
-      }
+      for (int i = 0; i < 2; ++i) a[i] = __builtin_bit_cast(bf16x8_t, fa_cur[i][s]);
 #pragma unroll
       for (int j = 0; j < FN; ++j) bq[j] = *reinterpret_cast<const bf16x8_t*>(Bb + j * 32 * GEMM_PITCH + s * 32);
 #pragma unroll
@@ -398,34 +345,34 @@ __global__ __launch_bounds__(256) void conv_ig_fwd_kernel(IgArgs p) {
     }
   };
 
-  issue_a(kt0);
-  issue_p(kt0);
+  issue_a(0);
+  issue_p(0);
   // zero both patch buffers once: the margins stay zero
   for (int i = t; i < 2 * patch_el / 2; i += NT) reinterpret_cast<uint32_t*>(Pt(0))[i] = 0u;
   __syncthreads();
-  park_a(0);
+  park_a();
   park_p(0);
-  issue_a(kt0 + 1);
-  issue_p(kt0 + 1);
+  issue_a(1);
+  issue_p(1);
   __syncthreads();
   build_read(0);
   park_p(1);
-  issue_p(kt0 + 2);
+  issue_p(2);
   build_write(0);
   __syncthreads();
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int buf = (kt - kt0) & 1;
+  for (int kt = 0; kt < ktiles; ++kt) {
+    const int buf = kt & 1;
     build_read(buf ^ 1);                                  // gather of column tile kt + 1 (patch kt + 1 was parked an iteration ago)
-    if constexpr (!AFRAG) { park_a(buf ^ 1); issue_a(kt + 2); }  // weights kt + 1 -> LDS, kt + 2 requested
     park_p(buf);                                          // patch kt + 2
     issue_p(kt + 3);
     mma(buf);
-    if constexpr (AFRAG) { park_a(0); issue_a(kt + 2); }  // fragments kt + 1 become current, kt + 2 requested
+    park_a();                                             // fragments kt + 1 become current, kt + 2 requested
+    issue_a(kt + 2);
     build_write(buf ^ 1);
     __syncthreads();
   }
 
-  ig_epilogue<PAIR, TM, FN>(p, acc, smem, b, split, m0, n0, wm, col0, cl0, t, lane);
+  ig_epilogue<true, TM, FN>(p, acc, smem, b, 0, m0, n0, wm, col0, cl0, t, lane);
 }
 
 int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
@@ -495,9 +442,9 @@ bool ig_extents(IgArgs& a) {
   return true;
 }
 
-size_t ig_lds_bytes(const IgArgs& a, int cpt, int a_rows) {
-  const size_t k_loop = 2 * (size_t)a_rows * GEMM_PITCH + 2 * GEMM_TILE_BYTES + 2 * (size_t)cpt * a.NI * a.SP * 2;
-  const size_t staging = a.ksplit > 1 ? 64 * (size_t)132 * 4 : 64 * (size_t)IG_EPI_PITCH;
+size_t ig_lds_bytes(const IgArgs& a) {
+  const size_t k_loop = 2 * GEMM_TILE_BYTES + 2 * (size_t)8 * a.NI * a.SP * 2;
+  const size_t staging = 64 * (size_t)IG_EPI_PITCH;
   return k_loop > staging ? k_loop : staging;
 }
 
@@ -545,138 +492,7 @@ __global__ __launch_bounds__(256) void ig_pack_class_w_kernel(const bf16_raw* __
 }
 
 
-// ---- weight gradient ---------------------------------------------------------------------------
-//   dW[o][j = (c, ky, kx)] = sum over k = (n, y, x) of dY[n][o][y][x] X[n][c][2 y + ky - 1][2 x + kx - 1]
-// Rows are output channels (dY is k-contiguous inside a sample), columns the 128 taps of 8 input
-// channels, and a k-tile is 32 consecutive output pixels (of one sample, or of two 4x4 samples).
-// The column tile [128 j][32 k] is built from the patch of the 8 channels' input rows those pixels
-// touch.  The grid's y splits the k range; partial sums go to fp32 slices reduced afterwards.
-struct IgDwArgs {
-  const bf16_raw* X; const bf16_raw* dY; float* Out;
-  int64_t x_img, x_model, y_img, y_model;                // element strides: sample, model
-  int64_t o_model, o_split;                              // output strides: model, k split
-  int Nb, Ci, Co, H, W, Ho, Wo, lgWo, lgP;
-  int NI, PR, PW, SP, nchunk;                            // samples per k-tile, patch rows, row pitch, sample pitch (elements)
-  int tiles_n, kt_total, kt_per_split;
-  IgGrid grid;                                           // logical grid: x = tiles, y = k split, z = model
-  uint32_t x_bytes, y_bytes;                             // extents of one model's slices of X and dY
-};
-
-__global__ __launch_bounds__(256) void conv_ig_dw_kernel(IgDwArgs p) {
-  constexpr int NT = 256;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  auto As = [&](int buf) { return smem + buf * GEMM_TILE_BYTES; };
-  auto Cb = [&](int buf) { return smem + 2 * GEMM_TILE_BYTES + buf * GEMM_TILE_BYTES; };
-  bf16_raw* const Pt = reinterpret_cast<bf16_raw*>(smem + 4 * GEMM_TILE_BYTES);
-  const int chan_el = p.NI * p.SP, patch_el = 8 * chan_el;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  int bx, by, b;
-  ig_block(p.grid, bx, by, b);
-  const int tile_m = bx / p.tiles_n, tile_n = bx % p.tiles_n;
-  const int m0 = tile_m * 128, c0 = tile_n * 8;
-  const int P = 1 << p.lgP, HW = p.H * p.W;
-  const int kt_begin = by * p.kt_per_split;
-  const int kt_end = min(p.kt_total, kt_begin + p.kt_per_split);
-
-  for (int i = t; i < patch_el / 2; i += NT) reinterpret_cast<uint32_t*>(Pt)[i] = 0u;   // margins stay zero
-
-  // Raw buffer loads, in range or at the fixed out-of-range offset (zeros): no load under control flow.
-  const __amdgpu_buffer_rsrc_t rx = pf_rsrc(p.X + (int64_t)b * p.x_model, p.x_bytes);
-  const __amdgpu_buffer_rsrc_t ry = pf_rsrc(p.dY + (int64_t)b * p.y_model, p.y_bytes);
-  // this thread's patch piece: channel, sample, patch row and position in the row are fixed; the image row moves with the k-tile
-  int p_row = 0, p_il = 0, p_lds = -1;
-  uint32_t p_off = PF_OOB;                                // byte offset at sample 0, image row 0
-  if (t < p.nchunk) {
-    const int cpr = p.W / 8;
-    const int xc = t % cpr;
-    int r = t / cpr;
-    p_row = r % p.PR; r /= p.PR;
-    p_il = r % p.NI;
-    const int c_l = r / p.NI;
-    p_lds = (c_l * p.NI + p_il) * p.SP + p_row * p.PW + IG_MARGIN + xc * 8;
-    if (c0 + c_l < p.Ci) p_off = (uint32_t)(((int64_t)(c0 + c_l) * HW + xc * 8) * 2);
-  }
-  // this thread's part of the column tile: row j = t % 128, 16 consecutive k (pixels) as four groups of 4 in a row
-  const int bj = t & 127, bhalf = t >> 7;
-  int boff[4];
-  {
-    const int c_l = bj >> 4, ky = (bj >> 2) & 3, kx = bj & 3;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int kl = bhalf * 16 + 4 * g;
-      const int il = kl >> p.lgP, y_l = (kl & (P - 1)) >> p.lgWo, x = kl & (p.Wo - 1);
-      boff[g] = (c_l * p.NI + il) * p.SP + (2 * y_l + ky) * p.PW + 2 * x + kx - 1 + IG_MARGIN;
-    }
-  }
-  const int ga = t & 3, ra = t >> 2;
-  uint32_t a_off[2];                                      // byte offset of the row's pixel 0 in sample 0
-#pragma unroll
-  for (int h = 0; h < 2; ++h) a_off[h] = m0 + ra + 64 * h < p.Co ? (uint32_t)((int64_t)(m0 + ra + 64 * h) * P * 2) : PF_OOB;
-  pf_u32x4 qa[2], qp;
-  auto issue = [&](int kt) {
-    const int kk = kt * 32 + ga * 8;                      // global pixel index of this 16-byte piece
-    const int n = kk >> p.lgP, pix = kk & (P - 1);
-    const uint32_t ab = (uint32_t)n * (uint32_t)(p.y_img * 2) + (uint32_t)pix * 2u;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      qa[h] = __builtin_amdgcn_raw_buffer_load_b128(ry, (int)((n < p.Nb && a_off[h] != PF_OOB) ? a_off[h] + ab : PF_OOB), 0, 0);
-    const int kk0 = kt * 32;
-    const int img = (kk0 >> p.lgP) + p_il;
-    const int iy = 2 * ((kk0 & (P - 1)) >> p.lgWo) - 1 + p_row;
-    const bool ok = p_off != PF_OOB && img < p.Nb && iy >= 0 && iy < p.H;
-    qp = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? p_off + (uint32_t)img * (uint32_t)(p.x_img * 2) + (uint32_t)(iy * p.W * 2) : PF_OOB), 0, 0);
-  };
-  auto park = [&](int buf) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) *reinterpret_cast<pf_u32x4*>(As(buf) + (ra + 64 * h) * GEMM_PITCH + ga * 16) = qa[h];
-    if (p_lds >= 0) *reinterpret_cast<pf_u32x4*>(Pt + p_lds) = qp;
-  };
-  auto build = [&](int buf) {
-    uint32_t w[8];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const bf16_raw* src = Pt + boff[g];
-      const uint32_t v0 = src[0], v1 = src[2], v2 = src[4], v3 = src[6];
-      w[2 * g] = v0 | (v1 << 16);
-      w[2 * g + 1] = v2 | (v3 << 16);
-    }
-    unsigned char* dst = Cb(buf) + bj * GEMM_PITCH + bhalf * 32;
-    *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-    *reinterpret_cast<uint4*>(dst + 16) = make_uint4(w[4], w[5], w[6], w[7]);
-  };
-
-  f32x16_t acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  // nothing below depends on the k-tile index: tiles past the end of the split are loaded (or read as
-  // zeros past the batch) and parked where nobody reads them any more
-  issue(kt_begin);
-  __syncthreads();
-  park(0);
-  issue(kt_begin + 1);
-  __syncthreads();
-  build(0);
-  __syncthreads();
-  int buf = 0;
-  for (int kt = kt_begin; kt < kt_end; ++kt) {
-    park(buf ^ 1);
-    issue(kt + 2);
-    mma_tile<bf16_raw>(acc, As(buf), Cb(buf), wm, wn, lane);
-    __syncthreads();
-    build(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
-  }
-  const int N = p.Ci * 16;
-  float* ob = p.Out + (int64_t)by * p.o_split + (int64_t)b * p.o_model;
-  store_tile<float, float, false>(acc, smem, ob, N, p.Co, N, m0, c0 * 16, (const float*)nullptr, 0, HFTA_ACT_NONE, 0.f, 16, t);
-}
+#include "conv2d_rows.h"
 
 // out[i] = bf16(act(sum of the k splits' partials + bias of i's channel)); 8 consecutive elements per thread
 __global__ __launch_bounds__(256) void ig_split_finish_kernel(const float* __restrict__ part, bf16_raw* __restrict__ out,
@@ -701,7 +517,7 @@ __global__ __launch_bounds__(256) void ig_split_finish_kernel(const float* __res
 }
 
 // k split of the forward kernel: taken when the tiles alone leave most compute units with a single
-// workgroup and the reduction is long (the 8x8 layers: 320 tiles, 128 k-tiles: 101 -> 90 us).  With
+// workgroup and the reduction is long (the 8x8 layers: 320 tiles, 4096 k: 101 -> 90 us when it was measured).  With
 // 640 tiles and more, and for the class-pair data gradient, the split measured no gain or a loss.
 int ig_pick_ksplit(int64_t blocks, int ktiles) {
   if (blocks >= 384 || ktiles < 64) return 1;
@@ -763,28 +579,25 @@ int conv_ig_forward(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw,
   a.Nb = Nb; a.Cx = Ci; a.H = H; a.W = W;
   a.M = Co; a.K = Ci * 16; a.N = Nb * Ho * Wo;
   if (!ig_extents(a)) return HFTA_EUNSUPPORTED;
-  a.OW = Wo; a.oys = 1; a.oxs = 1; a.tap_step = 1;
-  ig_geometry(a, 4, 4, 2, Ho, Wo, W, 128, false);
+  a.OW = Wo; a.oys = 1; a.oxs = 1;
+  a.lgWo = ilog2(Wo); a.lgP = ilog2(Ho * Wo); a.Ho = Ho; a.Wo = Wo;
+  rows_fwd_geometry(a);
   const int tm = Co <= 64 ? 64 : 128;
-  a.nchunk = 2 * a.NI * a.PR * (W / a.chunk_el);
-  if (a.nchunk > 512) return HFTA_EUNSUPPORTED;
   a.tiles_n = (a.N + 127) / 128;
   a.act = act; a.slope = slope;
-  a.cls[0] = IgClass{-pad, -pad, 0, 0, 0};
-  const size_t lds = ig_lds_bytes(a, 2, tm);
-  if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   const int tiles_m = (Co + tm - 1) / tm;
   if ((int64_t)tiles_m * a.tiles_n > 0x7fffffff || B > 65535) return HFTA_EUNSUPPORTED;
-  const int ktiles = (a.K + 31) / 32;
   const size_t need = conv_ig_fwd_split_bytes(B, Nb, Ci, Co, H, W);
-  a.ksplit = (need && ws && ws_bytes >= need && reinterpret_cast<uintptr_t>(ws) % 16 == 0) ? ig_pick_ksplit((int64_t)tiles_m * a.tiles_n * B, ktiles) : 1;
-  a.kt_per_split = (ktiles + a.ksplit - 1) / a.ksplit;
+  a.ksplit = (need && ws && ws_bytes >= need && reinterpret_cast<uintptr_t>(ws) % 16 == 0)
+                 ? ig_pick_ksplit((int64_t)tiles_m * a.tiles_n * B, (a.K + 31) / 32) : 1;
+  a.kt_per_split = ((a.K + 63) / 64 + a.ksplit - 1) / a.ksplit;
   a.part = reinterpret_cast<float*>(ws);
   a.part_split = (int64_t)Nb * a.o_img;
-  const size_t lds2 = ig_lds_bytes(a, 2, tm);
+  const size_t lds = rows_fwd_lds_bytes(a, tm);
+  if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   dim3 grid((unsigned)(tiles_m * a.tiles_n), (unsigned)a.ksplit, (unsigned)B);
-  if (tm == 64) ig_launch(conv_ig_fwd_kernel<4, 4, 2, false, 64, true>, grid, 256, lds2, st, a);
-  else ig_launch(conv_ig_fwd_kernel<4, 4, 2, false, 128, true>, grid, 256, lds2, st, a);
+  if (tm == 64) ig_launch(conv_rows_fwd_kernel<64>, grid, 256, lds, st, a);
+  else ig_launch(conv_rows_fwd_kernel<128>, grid, 256, lds, st, a);
   if (a.ksplit > 1) {
     if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
     const int64_t count8 = a.part_split / 8;
@@ -842,7 +655,7 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
     const int py = cls >> 1, px = cls & 1;
     a.cls[cls] = IgClass{py - 1, px - 1, py, px, cls * cls_el};          // window rows qy + py - 1, qy + py
   }
-  const size_t lds = ig_lds_bytes(a, 8, 0);
+  const size_t lds = ig_lds_bytes(a);
   if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   if ((int64_t)tiles_m * a.tiles_n > 0x7fffffff) return HFTA_EUNSUPPORTED;
   const int64_t count = (int64_t)B * 4 * cls_el / 8;                   // 16-byte fragment pieces
@@ -862,8 +675,8 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
       else few ? ig_launch(conv_dx_planes_kernel<128, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds2, st, a);
     }
   } else {
-    if (tm == 64) ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 64, false>, grid, 256, lds, st, a);
-    else ig_launch(conv_ig_fwd_kernel<2, 2, 1, true, 128, false>, grid, 256, lds, st, a);
+    if (tm == 64) ig_launch(conv_ig_gather_kernel<64>, grid, 256, lds, st, a);
+    else ig_launch(conv_ig_gather_kernel<128>, grid, 256, lds, st, a);
   }
   return launch_status();
 }
@@ -886,7 +699,7 @@ int conv_ig_dw_splits(int B, int Nb, int Ci, int Co, int H, int W) {
   const int64_t kt_total = ((int64_t)Nb * (H / 2) * (W / 2) + 31) / 32;
   const int64_t tiles = (int64_t)((Co + 127) / 128) * ((Ci + 7) / 8) * B;
   if (tiles >= 512 || kt_total < 32) return 1;
-  // two workgroups per compute unit: more splits only add partial-slice traffic (measured 512 .. 1536)
+  // more splits only add partial-slice traffic (measured 512 .. 1536)
   int64_t want = (512 + tiles - 1) / tiles, cap = kt_total / 16;
   if (want > cap) want = cap;
   if (want > 64) want = 64;
@@ -905,36 +718,16 @@ int conv_ig_dw(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   a.x_img = (int64_t)B * Ci * H * W; a.x_model = (int64_t)Ci * H * W;
   a.y_img = (int64_t)B * Co * P; a.y_model = (int64_t)Co * P;
   a.o_model = (int64_t)Co * Ci * 16;
-  a.Nb = Nb; a.Ci = Ci; a.Co = Co; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo;
+  if (W % 8 != 0) return HFTA_EUNSUPPORTED;
+  a.Nb = Nb; a.Ci = Ci; a.Co = Co; a.H = H; a.W = W; a.Wo = Wo;
   a.lgWo = ilog2(Wo); a.lgP = ilog2(P);
-  a.NI = P >= 32 ? 1 : 2;
-  const int TR = P >= 32 ? 32 / Wo : Ho;
-  a.PR = (TR - 1) * 2 + 4;
-  {
-    // Row and sample pitch of the patch with the fewest LDS bank conflicts in the gather (32 banks of
-    // 4 bytes, 32 lanes per clock): the lanes of a half wavefront read the 16 taps of two channels.
-    int64_t best = -1;
-    for (int i = 0; i < 6; ++i)
-      for (int j = 0; j < 8; ++j) {
-        const int pw = W + 16 + 8 * i, sp = a.PR * pw + 8 * j;
-        int cost = 0;
-        for (int h = 0; h < 2; ++h) {
-          int words[32], nw = 0, per_bank[32] = {0}, worst = 0;
-          for (int l = 0; l < 32; ++l) {
-            const int bj = h * 32 + l, c_l = bj >> 4, ky = (bj >> 2) & 3, kx = bj & 3;
-            const int word = (c_l * a.NI * sp + ky * pw + kx + IG_MARGIN - 1) >> 1;
-            bool seen = false;
-            for (int q = 0; q < nw; ++q) seen = seen || words[q] == word;
-            if (!seen) { words[nw++] = word; worst = ++per_bank[word & 31] > worst ? per_bank[word & 31] : worst; }
-          }
-          cost += worst;
-        }
-        const int64_t key = (int64_t)cost * (1 << 20) + (int64_t)a.NI * sp;
-        if (best < 0 || key < best) { best = key; a.PW = pw; a.SP = sp; }
-      }
-  }
-  a.nchunk = 8 * a.NI * a.PR * (W / 8);
-  if (a.nchunk > 256 || W % 8 != 0) return HFTA_EUNSUPPORTED;
+  a.NI = P >= 32 ? 1 : 32 / P;
+  a.PR = 2 * (P >= 32 ? 32 / Wo : Ho) + 2;
+  a.nchunk = 8 * a.NI * a.PR * (W / 8);                  // at most 256, one per thread: 16 + NI Wo / 2 a channel, NI Wo <= 32
+  // the eight lanes that an LDS clock serves read eight taps of a channel (four planes of two rows, 16 bytes each): these
+  // pitches put them on different banks
+  a.plane_b = Wo * 2 + (Wo >= 16 ? 16 : 0);
+  a.row_b = 4 * a.plane_b;
   const int64_t xb = ((int64_t)(Nb - 1) * a.x_img + (int64_t)Ci * H * W) * 2, yb = ((int64_t)(Nb - 1) * a.y_img + (int64_t)Co * P) * 2;
   if (xb >= ((int64_t)1 << 31) || yb >= ((int64_t)1 << 31)) return HFTA_EUNSUPPORTED;
   a.x_bytes = (uint32_t)xb; a.y_bytes = (uint32_t)yb;
@@ -945,16 +738,19 @@ int conv_ig_dw(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   a.kt_per_split = (a.kt_total + splits - 1) / splits;
   a.o_split = (int64_t)B * a.o_model;
   a.Out = splits > 1 ? partial : dW;
-  const size_t k_loop = 4 * (size_t)GEMM_TILE_BYTES + (size_t)8 * a.NI * a.SP * 2;
+  const size_t k_loop = 2 * ((size_t)GEMM_TILE_BYTES + (size_t)8 * a.NI * a.PR * a.row_b);
   const size_t staging = 64 * (size_t)EPI_PITCH4;
   const size_t lds = k_loop > staging ? k_loop : staging;
   if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   const int tiles_m = (Co + 127) / 128;
-  if (lds > 48 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(conv_ig_dw_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)IG_MAX_LDS);
   a.grid = IgGrid{tiles_m * a.tiles_n, splits, B};
   if ((int64_t)a.grid.gx * splits * B > 0x7fffffff) return HFTA_EUNSUPPORTED;
-  hipLaunchKernelGGL(conv_ig_dw_kernel, dim3((unsigned)(a.grid.gx * splits * B)), dim3(256), lds, st, a);
+  auto launch = [&](auto kernel) {
+    if (lds > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)IG_MAX_LDS);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.grid.gx * splits * B)), dim3(256), lds, st, a);
+  };
+  if (Wo == 4) launch(conv_rows_dw_kernel<true>);
+  else launch(conv_rows_dw_kernel<false>);
   if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
   if (splits > 1) {
     const int64_t count4 = (int64_t)B * a.o_model / 4;

@@ -1,6 +1,6 @@
 // Data gradient of the 4x4 / stride 2 / pad 1 convolution from shifted row planes.
 //
-// Building the column tile element by element (conv_ig_fwd_kernel) costs a thread 16 two-byte LDS reads and two
+// Building the column tile element by element (conv_ig_gather_kernel) costs a thread 16 two-byte LDS reads and two
 // 16-byte writes per 32-element k-tile, as much LDS time as the matrix instructions' operands.  The transpose
 // read (see pf_frag) makes that tile unnecessary: each of its lanes addresses four neighbouring pixels of one
 // k-row by itself, so the k-rows of a matrix instruction can be the four taps of a channel's 2x2 window, each at
