@@ -152,6 +152,77 @@ __global__ __launch_bounds__(256) void adam_multi_kernel(AdamMultiArgs p) {
   }
 }
 
+// where element i of the arena lies: its model, and the end of that model's part of the segment
+__device__ __forceinline__ void adam_locate(const AdamMultiArgs& p, int64_t i, int& b, int64_t& end) {
+  int lo = 0, hi = p.nseg;                        // largest j with B * off[j] <= i
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if ((int64_t)p.B * p.off[mid] <= i) lo = mid; else hi = mid;
+  }
+  const int64_t n = p.off[lo + 1] - p.off[lo], base = (int64_t)p.B * p.off[lo];
+  const int64_t q = i - base;
+  b = q < 0x7fffffffLL && n < 0x7fffffffLL ? (int)((uint32_t)q / (uint32_t)n) : (int)(q / n);
+  end = base + (int64_t)(b + 1) * n;
+}
+
+// The same for arenas with segments of any length (9 biases, 50 classes): 16-byte accesses need the arrays' alignment alone.
+// A workgroup's elements mostly lie in one model's part of one segment: that is looked up once for the workgroup; only
+// workgroups with a boundary in them look up per thread, and only groups of four across a boundary per element.  HBM-bound:
+// 27.8 M parameters 340 (element-wise) -> 147 us, 15.1 M 190 -> 78.  Arenas of whole groups keep the kernel above: 268 M
+// parameters 1450 us there, 1477 here (1640 with the loads ahead of the lookup).
+template <typename G>
+__global__ __launch_bounds__(256, 8) void adam_multi_odd_kernel(AdamMultiArgs p) {
+  extern __shared__ float bc[];                   // [B][2]
+  const int64_t i0 = (int64_t)blockIdx.x * 1024, i = i0 + threadIdx.x * 4;
+  for (int b = threadIdx.x; b < p.B; b += 256) {
+    bc[2 * b] = (float)(1.0 / (1.0 - pow((double)p.beta1[b], (double)p.t)));
+    bc[2 * b + 1] = (float)(1.0 / (1.0 - pow((double)p.beta2[b], (double)p.t)));
+  }
+  __syncthreads();
+  if (i >= p.total) return;
+  auto params = [&](int b) {
+    AdamHp h;
+    h.lr = p.lr[b]; h.b1 = p.beta1[b]; h.b2 = p.beta2[b]; h.eps = p.eps[b]; h.wd = p.wd[b];
+    h.inv_bc1 = bc[2 * b]; h.inv_bc2 = bc[2 * b + 1];
+    return h;
+  };
+  int b;
+  int64_t end;
+  adam_locate(p, i0, b, end);
+  if (end < i0 + 1024) adam_locate(p, i, b, end);
+  const G* gr = reinterpret_cast<const G*>(p.grad);
+  if (i + 4 > end) {                              // across a boundary, or fewer than four at the arena's end
+    for (int64_t j = i; j < i + 4 && j < p.total; ++j) {
+      adam_locate(p, j, b, end);
+      float th = p.theta[j], m = p.m[j], v = p.v[j];
+      adam_one(th, Elem<G>::load(gr + j), m, v, params(b), p.decoupled);
+      p.theta[j] = th; p.m[j] = m; p.v[j] = v;
+      if (p.lowp) p.lowp[j] = f32_to_bf16(th);
+    }
+    return;
+  }
+  float4 th = *reinterpret_cast<float4*>(p.theta + i);
+  float4 m = *reinterpret_cast<float4*>(p.m + i);
+  float4 v = *reinterpret_cast<float4*>(p.v + i);
+  float g[4];
+  if (sizeof(G) == 4) {
+    *reinterpret_cast<float4*>(g) = *reinterpret_cast<const float4*>(gr + i);
+  } else {
+    const uint2 raw = *reinterpret_cast<const uint2*>(gr + i);
+    g[0] = __uint_as_float(raw.x << 16); g[1] = __uint_as_float(raw.x & 0xffff0000u);
+    g[2] = __uint_as_float(raw.y << 16); g[3] = __uint_as_float(raw.y & 0xffff0000u);
+  }
+  const AdamHp h = params(b);
+  adam_one(th.x, g[0], m.x, v.x, h, p.decoupled);
+  adam_one(th.y, g[1], m.y, v.y, h, p.decoupled);
+  adam_one(th.z, g[2], m.z, v.z, h, p.decoupled);
+  adam_one(th.w, g[3], m.w, v.w, h, p.decoupled);
+  *reinterpret_cast<float4*>(p.theta + i) = th;
+  *reinterpret_cast<float4*>(p.m + i) = m;
+  *reinterpret_cast<float4*>(p.v + i) = v;
+  if (p.lowp) *reinterpret_cast<uint2*>(p.lowp + i) = make_uint2(pack_bf16x2(th.x, th.y), pack_bf16x2(th.z, th.w));
+}
+
 }  // namespace
 
 extern "C" int hfta_adam_step_multi(int B, int nseg, const int64_t* seg_offsets, int grad_dtype, float* theta,
@@ -172,7 +243,7 @@ extern "C" int hfta_adam_step_multi(int B, int nseg, const int64_t* seg_offsets,
   }
   for (int j = nseg + 1; j <= HFTA_ADAM_MAX_SEGMENTS; ++j) a.off[j] = seg_offsets[nseg];
   auto al = [](const void* q, size_t k) { return reinterpret_cast<uintptr_t>(q) % k == 0; };
-  const bool v4 = all4 && al(theta, 16) && al(m, 16) && al(v, 16) && al(grad, grad_dtype == HFTA_BF16 ? 8 : 16) &&
+  const bool v4 = al(theta, 16) && al(m, 16) && al(v, 16) && al(grad, grad_dtype == HFTA_BF16 ? 8 : 16) &&
                   (!theta_lowp || al(theta_lowp, 8));
   a.theta = theta; a.grad = grad; a.m = m; a.v = v; a.lowp = (bf16_raw*)theta_lowp;
   a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.eps = eps; a.wd = weight_decay;
@@ -185,10 +256,12 @@ extern "C" int hfta_adam_step_multi(int B, int nseg, const int64_t* seg_offsets,
   hipStream_t st = as_stream(stream);
   dim3 grid((unsigned)blocks);
   if (grad_dtype == HFTA_BF16) {
-    if (v4) hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, true>), grid, dim3(256), shm, st, a);
+    if (v4 && !all4) hipLaunchKernelGGL(adam_multi_odd_kernel<bf16_raw>, grid, dim3(256), shm, st, a);
+    else if (v4) hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, true>), grid, dim3(256), shm, st, a);
     else hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, false>), grid, dim3(256), shm, st, a);
   } else {
-    if (v4) hipLaunchKernelGGL((adam_multi_kernel<float, true>), grid, dim3(256), shm, st, a);
+    if (v4 && !all4) hipLaunchKernelGGL(adam_multi_odd_kernel<float>, grid, dim3(256), shm, st, a);
+    else if (v4) hipLaunchKernelGGL((adam_multi_kernel<float, true>), grid, dim3(256), shm, st, a);
     else hipLaunchKernelGGL((adam_multi_kernel<float, false>), grid, dim3(256), shm, st, a);
   }
   return launch_status();
