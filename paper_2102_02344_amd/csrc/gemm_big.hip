@@ -58,7 +58,7 @@ static void launch_bigp(const GemmArgs& a, bool ident, bool v16, bool n16, dim3 
 
 static bool persistent_ok(const GemmDesc& d, const GemmArgs& a, bool v16, bool sel, dim3 grid, int blocks) {
   if (blocks < 8 || (int64_t)grid.x * grid.z <= blocks || !sel) return false;
-  if (!v16 && !(d.a_kc && d.b_kc)) return false;       // 8-byte k-contiguous loads: both operands only
+  if (!v16 && !(d.a_kc && d.b_kc)) return false;       // 8-byte aligned k-contiguous rows: both operands only
   const bool partial = a.splits > 1;
   const int oes = (d.out_f32 || partial) ? 4 : 2;
   const int vb = partial ? a.p_vec : a.c_vec;
@@ -68,10 +68,10 @@ static bool persistent_ok(const GemmDesc& d, const GemmArgs& a, bool v16, bool s
 }
 
 // `a` must carry tile counts for 256x256 tiles and 64-element k-tiles and operand extents.
-// `v16`: k-contiguous operands are loadable in 16-byte pieces; otherwise (rows only 8-byte aligned,
+// `v16`: k-contiguous operands have rows of whole aligned 16-byte pieces; otherwise (rows only 8-byte aligned,
 // e.g. 2500 points per sample) only the weight-gradient form (both operands k-contiguous, fp32
-// output) is built, on 8-byte loads.  `n16`: operands contiguous along m / n load in 16-byte pieces
-// (else 8-byte).  HFTA_EUNSUPPORTED: not a combination this kernel is built for.
+// output) is built.  `n16`: operands contiguous along m / n have whole aligned 16-byte pieces.
+// HFTA_EUNSUPPORTED: not a combination this kernel is built for.
 int gemm_big_launch(const GemmDesc& d, const GemmArgs& a0, bool v16, bool n16, dim3 grid, hipStream_t st) {
   GemmArgs a = a0;
   const bool colb = d.bias && d.bias_mode == 2;

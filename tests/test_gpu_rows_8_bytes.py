@@ -1,0 +1,51 @@
+"""k=1 convolutions whose rows are multiples of 8 bytes but not of 16 (an odd number of groups of four points), in sizes that the
+256x256 product kernels take: the last piece of a row has four of its eight elements.  Rows lie apart in memory with NaN
+between them, so that an element read past a row's end shows."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_ops import f32_tol
+from util import DT, TOL, check, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2102_02344_amd import binding
+    return binding
+
+
+def padded(gen, rows, L, pitch, scale=1.0):
+    t = torch.full((rows, pitch), float("nan"), dtype=torch.bfloat16)
+    t[:, :L] = torch.randn((rows, L), generator=gen) * scale
+    return t.cuda(), t[:, :L].double()
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L,pad", [(2, 40, 264, 516, 516, 4), (1, 33, 512, 776, 772, 8), (2, 24, 520, 260, 1028, 0)])
+def test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad):
+    print(f"rows of 8 bytes B={B} Nb={Nb} Ci={Ci} Co={Co} L={L} pad={pad}", flush=True)
+    gen = torch.Generator().manual_seed(7)
+    P, dt = L + pad, DT["bf16"]
+    strides = lambda C: (C * P, B * C * P, P, 1)
+    X, x = padded(gen, Nb * B * Ci, L, P)
+    dY, dy = padded(gen, Nb * B * Co, L, P)
+    W = (torch.randn((B, Co, Ci), generator=gen) / np.sqrt(Ci)).bfloat16()
+    bias = torch.randn((B, Co), generator=gen).bfloat16()
+    x, dy, w = x.view(Nb, B, Ci, L), dy.view(Nb, B, Co, L), W.double()
+    Wd, Bd = W.cuda(), bias.cuda()
+    ws = torch.empty(max(hb.conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, dt), 4), dtype=torch.uint8, device="cuda")
+
+    Y = torch.zeros((Nb, B, Co, P), dtype=torch.bfloat16, device="cuda")
+    hb.conv1x1_fwd(B, Nb, Ci, Co, L, dt, X, strides(Ci), Wd, Bd, Y, strides(Co))
+    check(host(Y[..., :L]), (torch.matmul(w, x) + bias.double()[:, :, None]).numpy(), TOL["bf16"], "Y")
+    assert not Y[..., L:].any()
+    dX = torch.zeros((Nb, B, Ci, P), dtype=torch.bfloat16, device="cuda")
+    hb.conv1x1_bwd(B, Nb, Ci, Co, L, dt, None, None, Wd, dY, strides(Co), dX, strides(Ci), None, None, ws)
+    check(host(dX[..., :L]), torch.matmul(w.transpose(1, 2).contiguous(), dy).numpy(), TOL["bf16"], "dX")
+    assert not dX[..., L:].any()
+    dW = torch.zeros((B, Co, Ci), dtype=torch.float32, device="cuda")
+    hb.conv1x1_bwd(B, Nb, Ci, Co, L, dt, X, strides(Ci), None, dY, strides(Co), None, None, dW, None, ws)
+    ref = sum(torch.matmul(dy[n], x[n].transpose(1, 2).contiguous()) for n in range(Nb))
+    check(host(dW), ref.numpy(), f32_tol("bf16"), "dW")
