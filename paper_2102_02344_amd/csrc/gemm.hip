@@ -246,7 +246,8 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   int rc;
   // bf16 problems whose operands can be fetched in whole 8/16-byte pieces take the deep-prefetch
   // kernel (branch-free buffer loads, several k-tiles in flight).
-  const bool pf = v16 || v8;
+  // Its 16-byte loads want eight elements in a row of an operand that is not made of whole aligned 16-byte pieces.
+  const bool pf = (v16 || v8) && (d.a_kc ? v16 || d.K >= 8 : d.M >= 8) && (d.b_kc ? v16 || d.K >= 8 : d.N >= 8);
   if (d.dtype == HFTA_F32) {
     rc = gemm_f32_launch(d, a, st);
     if (rc == HFTA_EUNSUPPORTED) rc = launch_layout<float>(d, a, grid, st);

@@ -104,24 +104,12 @@ __device__ __forceinline__ void big_store_rows(const unsigned char* smem, OutT* 
   }
 }
 
-// Rows whose length or alignment are multiples of 8 bytes only (2500 points) load in 16-byte pieces too: a multi-dword access
-// needs 4-byte alignment.  The piece that has four of its eight elements in the row is read four elements early, so that
-// nothing past the row is touched, and is moved into place on its way into LDS.  Against two 8-byte loads per piece (6 x 16 x
-// 2500 points): weight gradients of 512 -> 2048 and 2880 -> 256 channels 1280 -> 1112 us together, forwards 715 -> 687 and 407 -> 392,
-// data gradient 550 -> 520.
-struct BigHalves {
-  uint4 v[4];
-  bool half;
-  __device__ __forceinline__ uint4 operator[](int h) const { return half ? make_uint4(v[h].z, v[h].w, 0u, 0u) : v[h]; }
-};
-struct BigWhole {
-  uint4 v[4];
-  __device__ __forceinline__ uint4 operator[](int h) const { return v[h]; }
-};
-
+// Rows of 8-byte multiples load in 16-byte pieces too (RowHalves in gemm_pf.h).  Against two 8-byte loads per piece (6 x 16 x
+// 2500 points): weight gradients of 512 -> 2048 and 2880 -> 256 channels 1280 -> 1112 us together, forwards 715 -> 687 and
+// 407 -> 392, data gradient 550 -> 520.
 // k-contiguous operand: 256 rows x 8 chunks of 16 bytes per k-tile, 4 chunks per thread
 template <bool V16> struct BigOpKc {
-  typedef typename std::conditional<V16, BigWhole, BigHalves>::type Regs;
+  typedef typename std::conditional<V16, RowWhole<4>, RowHalves<4>>::type Regs;
   uint32_t off[4];
   int kg;
   __device__ __forceinline__ void init(int row0, int rows, int64_t ld, int t) {
@@ -160,7 +148,7 @@ template <bool V16> struct BigOpKc {
 constexpr int BIG_NPITCH = 256 * 2 + 64;
 static_assert(64 * BIG_NPITCH == BIG_TILE, "natural-layout tile must fit the k-major tile's bytes");
 template <bool N16> struct BigOpNt {
-  typedef typename std::conditional<N16, BigWhole, BigHalves>::type Regs;
+  typedef typename std::conditional<N16, RowWhole<4>, RowHalves<4>>::type Regs;
   uint32_t off;           // byte offset of the chunk in row k = t/32, or out of range
   uint32_t ldb;
   bool half;

@@ -26,12 +26,27 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pf_rsrc(const void* p, uint32_
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
+// 16-byte pieces of rows.  Rows whose length or alignment are multiples of 8 bytes only (2500 points) load them too: a
+// multi-dword access needs 4-byte alignment.  The piece that has four of its eight elements in the row is read four elements
+// early (rows hold at least eight), so that nothing past the row is touched, and is moved into place on its way into LDS.
+// Against two 8-byte loads (6 x 16 x 2500 points): weight gradients of 128 -> 512, 128 -> 256 and 64 -> 128 channels 155 ->
+// 135, 91 -> 82 and 30 -> 27 us, products with both operands along the points 83 -> 76, with one 55 -> 51.
+template <int H> struct RowHalves {
+  uint4 v[H];
+  bool half;
+  __device__ __forceinline__ uint4 operator[](int h) const { return half ? make_uint4(v[h].z, v[h].w, 0u, 0u) : v[h]; }
+};
+template <int H> struct RowWhole {
+  uint4 v[H];
+  __device__ __forceinline__ uint4 operator[](int h) const { return v[h]; }
+};
+
 // Per-thread addressing of one operand; q-sets (the staged data) are kept apart so that several
 // tiles can be in flight with one copy of the offsets.
 template <bool KC, bool V16> struct PfOperand;
 
 template <bool V16> struct PfOperand<true, V16> {   // k-contiguous: rows t/4 and t/4+64, 16-byte group t%4
-  typedef uint4 Regs[2];
+  typedef typename std::conditional<V16, RowWhole<2>, RowHalves<2>>::type Regs;
   uint32_t off[2];
   int kg;
   __device__ __forceinline__ void init(int row0, int rows, int64_t ld, int t) {
@@ -39,65 +54,58 @@ template <bool V16> struct PfOperand<true, V16> {   // k-contiguous: rows t/4 an
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int r = row0 + (t >> 2) + 64 * h;
-      off[h] = r < rows ? (uint32_t)((int64_t)r * ld * 2) + (uint32_t)kg * 2u : PF_OOB;
+      off[h] = r < rows ? (uint32_t)((int64_t)r * ld * 2) + (uint32_t)kg * 2u : PF_OOB + 8u;
     }
   }
   __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
     const int k = k0 + kg;
-    if (V16) {
-      const bool ok = k + 8 <= K;
+    const bool ok = k + (V16 ? 8 : 4) <= K;
+    uint32_t kb = (uint32_t)k0 * 2u;
+    if constexpr (!V16) {
+      q.half = ok && k + 8 > K;
+      kb -= q.half ? 8u : 0u;                              // rows out of range stay out of range
+    }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const pf_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(ok ? off[h] + (uint32_t)k0 * 2u : PF_OOB), 0, 0);
-        q[h] = make_uint4(v.x, v.y, v.z, v.w);
-      }
-    } else {
-      const bool ok0 = k + 4 <= K, ok1 = k + 8 <= K;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t o = off[h] + (uint32_t)k0 * 2u;
-        const pf_u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(ok0 ? o : PF_OOB), 0, 0);
-        const pf_u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(ok1 ? o + 8u : PF_OOB), 0, 0);
-        q[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      }
+    for (int h = 0; h < 2; ++h) {
+      const pf_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(ok ? off[h] + kb : PF_OOB), 0, 0);
+      q.v[h] = make_uint4(v.x, v.y, v.z, v.w);
     }
   }
-  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t, int = 0, int = 0) { store_kc(tile, q, t); }
+  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t, int = 0, int = 0) {
+    const uint4 p[2] = {q[0], q[1]};
+    store_kc(tile, p, t);
+  }
 };
 
 // m/n-contiguous operand: kept in its natural layout in LDS ([32 k][128 n], 320-byte rows = the k-major
 // tile's 10240 bytes) and transposed by the LDS transpose read on the way into the matrix-instruction
-// fragments.  A thread owns chunk t%16 (8 columns) of k-rows t/16 and t/16 + 16; N16: the chunk is one
-// 16-byte piece (row starts 16-byte aligned, columns a multiple of 8), else two 8-byte pieces.
+// fragments.  A thread owns chunk t%16 (8 columns) of k-rows t/16 and t/16 + 16; N16: row starts 16-byte
+// aligned, columns a multiple of 8.
 constexpr int PF_NPITCH = 128 * 2 + 64;
 static_assert(32 * PF_NPITCH == GEMM_TILE_BYTES, "natural-layout tile must fit the k-major tile's bytes");
 template <bool N16> struct PfOperandNt {
-  typedef uint4 Regs[2];
-  uint32_t off0, off1;
+  typedef typename std::conditional<N16, RowWhole<2>, RowHalves<2>>::type Regs;
+  uint32_t off;
   uint32_t ldb;
+  bool half;
   __device__ __forceinline__ void init(int col0, int cols, int64_t ld, int t) {
     ldb = (uint32_t)(ld * 2);
     const int c = col0 + (t & 15) * 8, kr = t >> 4;
-    off0 = c + 4 <= cols ? (uint32_t)kr * ldb + (uint32_t)c * 2u : PF_OOB;
-    off1 = c + 8 <= cols ? (uint32_t)kr * ldb + (uint32_t)c * 2u + 8u : PF_OOB;
+    half = !N16 && c + 4 <= cols && c + 8 > cols;
+    off = c + 8 <= cols || half ? (uint32_t)kr * ldb + (uint32_t)c * 2u - (half ? 8u : 0u) : PF_OOB;
   }
   __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
     const int kr = (int)(threadIdx.x >> 4);
+    if constexpr (!N16) q.half = half;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const bool ok = k0 + kr + 16 * h < K;
       const uint32_t kb = (uint32_t)(k0 + 16 * h) * ldb;
-      if (N16) {
-        const pf_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(ok && off1 != PF_OOB ? off0 + kb : PF_OOB), 0, 0);
-        q[h] = make_uint4(v.x, v.y, v.z, v.w);
-      } else {
-        const pf_u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(ok && off0 != PF_OOB ? off0 + kb : PF_OOB), 0, 0);
-        const pf_u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(ok && off1 != PF_OOB ? off1 + kb : PF_OOB), 0, 0);
-        q[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      }
+      const pf_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(ok && off != PF_OOB ? off + kb : PF_OOB), 0, 0);
+      q.v[h] = make_uint4(v.x, v.y, v.z, v.w);
     }
   }
-  static __device__ __forceinline__ void store(unsigned char* tile, const Regs& q, int t, int = 0, int = 0) {
+  template <typename R> static __device__ __forceinline__ void store(unsigned char* tile, const R& q, int t, int = 0, int = 0) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       *reinterpret_cast<uint4*>(tile + ((t >> 4) + 16 * h) * PF_NPITCH + (t & 15) * 16) = q[h];

@@ -49,3 +49,10 @@ def test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad):
     hb.conv1x1_bwd(B, Nb, Ci, Co, L, dt, X, strides(Ci), None, dY, strides(Co), None, None, dW, None, ws)
     ref = sum(torch.matmul(dy[n], x[n].transpose(1, 2).contiguous()) for n in range(Nb))
     check(host(dW), ref.numpy(), f32_tol("bf16"), "dW")
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L,pad", [(2, 5, 12, 20, 4, 4), (1, 3, 4, 36, 12, 0), (3, 7, 64, 132, 132, 4), (2, 3, 136, 4, 1028, 4),
+                                              (1, 9, 100, 260, 260, 8)])
+def test_forward_and_gradients_of_small_layers(hb, B, Nb, Ci, Co, L, pad):
+    """The same for the 128x128 kernel: fewer than eight elements in a row of an operand among them."""
+    test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad)
