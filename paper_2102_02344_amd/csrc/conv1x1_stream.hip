@@ -2,7 +2,7 @@
 // (fusion rules table, Conv1d row; the point-cloud models' 64 -> 64 ... 128 -> 1024 layers).
 //
 // Per model b and sample n:  Y[co][l] = sum_ci W[b][co][ci] * X[ci][l] + bias[b][co], with Ci <= 128
-// (<= 256 for layers at least 512 channels wide, e.g. the data gradient of a 2880 -> 256 layer):
+// (<= 256 for layers at least 512 channels wide):
 // the whole reduction fits one LDS tile, so a generic k-loop kernel spends its time in launch,
 // prologue and epilogue latencies, not in the matrix cores or in HBM.  Here one workgroup owns one
 // 128-point slice of one sample, keeps that X tile (transposed, [point][ci]) in LDS, and walks

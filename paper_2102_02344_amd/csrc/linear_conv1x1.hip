@@ -593,10 +593,15 @@ int hfta_conv1x1_bn_prenorm_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,
                                     save_mean, save_invstd, Y, ys, act, act_slope, part, Nb * ((L + 127) / 128), bias, st);
 }
 
-// The data gradient of a narrow layer (Co <= 128, or Co <= 256 under at least 512 inputs) is a k=1 convolution of dY with the transposed
-// weights: it takes the streaming forward kernel once W^T [B][Ci][Co] has been written to the workspace.
-static bool dx_streams(int Ci, int Co, int L, int dtype) {
-  return dtype == HFTA_BF16 && Co % 8 == 0 && L >= 4 && ((Co <= 128 && Ci >= 64) || (Co <= 256 && Ci >= 512));
+// The data gradient of a narrow layer (Co <= 128) is a k=1 convolution of dY with the transposed weights: it takes the streaming
+// forward kernel once W^T [B][Ci][Co] has been written to the workspace.  So does Co <= 256 under at least 512 inputs where rows
+// are not of whole 8-byte pieces and the points fill the chip three times over (2880 <- 256 channels on 6 x 16 x 1023 points
+// 378 us, 389 as a product); any other such layer is a product (2500 points: 744 -> 699 us; 1 x 2 x 2500 93 -> 21, a workgroup
+// per 128 points there; 8 x 32 x 2500 under 512 inputs 417 -> 301).
+static bool dx_streams(int B, int Nb, int Ci, int Co, int L, int dtype) {
+  if (dtype != HFTA_BF16 || Co % 8 != 0 || L < 4) return false;
+  if (Co <= 128) return Ci >= 64;
+  return Co <= 256 && Ci >= 512 && L % 4 != 0 && (int64_t)B * Nb * ((L + 127) / 128) >= 768;
 }
 static size_t wt_offset(size_t partial_bytes) { return (partial_bytes + 255) & ~(size_t)255; }
 
@@ -605,7 +610,7 @@ size_t hfta_conv1x1_bwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, in
   const int64_t unit[4] = {(int64_t)Ci * L, (int64_t)B * Ci * L, L, 1};
   GemmDesc d = conv_dw_desc(B, Nb, Ci, Co, L, dtype, nullptr, unit, nullptr, unit, nullptr);
   const size_t part = gemm_partial_bytes(d, gemm_pick_splits(d));
-  return dx_streams(Ci, Co, L, dtype) ? wt_offset(part) + (size_t)B * Ci * Co * 2 : part;
+  return dx_streams(B, Nb, Ci, Co, L, dtype) ? wt_offset(part) + (size_t)B * Ci * Co * 2 : part;
 }
 
 int hfta_conv1x1_bwd(int B, int Nb, int Ci, int Co, int L, int dtype, const void* X, const int64_t xs[4],
@@ -626,7 +631,7 @@ int hfta_conv1x1_bwd(int B, int Nb, int Ci, int Co, int L, int dtype, const void
     dw.partial = reinterpret_cast<float*>(workspace);
   }
   bool dx_done = false;
-  if (dX && dx_streams(Ci, Co, L, dtype) && workspace) {
+  if (dX && dx_streams(B, Nb, Ci, Co, L, dtype) && workspace) {
     const size_t off = wt_offset(dW ? gemm_partial_bytes(dw, dw.splits) : 0);
     const size_t bytes = (size_t)B * Ci * Co * 2;
     if (ws_bytes >= off + bytes && reinterpret_cast<uintptr_t>(workspace) % 256 == 0) {

@@ -56,3 +56,9 @@ def test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad):
 def test_forward_and_gradients_of_small_layers(hb, B, Nb, Ci, Co, L, pad):
     """The same for the 128x128 kernel: fewer than eight elements in a row of an operand among them."""
     test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad)
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L", [(1, 2, 520, 136, 516), (1, 2, 512, 256, 515), (8, 32, 512, 136, 261), (2, 24, 576, 256, 1032)])
+def test_wide_data_gradient(hb, B, Nb, Ci, Co, L):
+    """More than 128 output channels under at least 512 inputs: a product, or (261 points on 768 workgroups) streamed."""
+    test_forward_and_gradients(hb, B, Nb, Ci, Co, L, 0)
