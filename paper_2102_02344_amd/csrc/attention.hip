@@ -15,6 +15,8 @@ namespace hfta {       // attention_core.hip: one kernel per direction for bf16 
 bool attn_core_ok(int S, int E, int H, int dtype, const void* a, const void* b, const void* c);
 int attn_core_fwd(int BN, int S, int E, int H, const void* QKV, void* P, void* CTX, int causal, hipStream_t st);
 int attn_core_bwd(int BN, int S, int E, int H, const void* QKV, const void* P, const void* dCTX, void* dQKV, hipStream_t st);
+int conv1x1_tinyk(int B, int Nb, int Ci, int Co, int L, const void* X, const int64_t xs[4], const void* W, int64_t w_b, int64_t w_n,
+                  const void* bias, void* Y, const int64_t ys[4], int act, float act_slope, hipStream_t st);   // linear_conv1x1.hip
 }  // namespace hfta
 
 using namespace hfta;
@@ -512,6 +514,10 @@ int hfta_point_transform_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, co
                              const void* T, void* Y, const int64_t ys[4], void* stream) {
   if (B <= 0 || Nb <= 0 || Ci <= 0 || Co <= 0 || L <= 0 || !valid_dtype(dtype) || !X || !xs || !T || !Y || !ys) return HFTA_EINVAL;
   if (xs[3] != 1 || ys[3] != 1 || (int64_t)B * Nb > 65535) return HFTA_EUNSUPPORTED;
+  // Coordinates: no matrix instruction pays for K = 3, and weights of three elements in a row are fetched one by one.
+  if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && L >= 4)
+    return conv1x1_tinyk(B, Nb, Ci, Co, L, X, xs, T, (int64_t)Nb * Co * Ci, (int64_t)Co * Ci, nullptr, Y, ys, HFTA_ACT_NONE, 0.f,
+                         as_stream(stream));
   GemmDesc g = head_desc(B, 1, Nb, dtype);
   g.A = T; g.Bm = X; g.C = Y;
   g.M = Co; g.N = L; g.K = Ci;

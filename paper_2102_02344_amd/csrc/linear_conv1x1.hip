@@ -41,10 +41,13 @@ namespace {
 // an output row.  HBM-bound: Co rows written once.  The channels are split over workgroups (the inputs,
 // a twentieth of the output, are read again) because a single walk over 64 rows leaves a small batch on a
 // handful of compute units (64 channels: 8 x 32 x 2500 points 31 -> 25 us, 3 x 13 x 1023 points 26 -> 11 us).
+// With weights per sample (wsn) it is also the point transform of the coordinates: 3 -> 3 channels on 8 x 32 x 2500 points
+// 62 -> 5 us (against the element-wise product).
 constexpr int TK_CO = 16;
 struct TinyKArgs {
   const bf16_raw* X; const bf16_raw* W; const bf16_raw* bias; bf16_raw* Y;
   int64_t xsb, xsn, xsc, ysb, ysn, ysc;
+  int64_t wsb, wsn;                                      // weight strides: model, sample
   int Ci, Co, L, act;
   float slope;
 };
@@ -55,7 +58,7 @@ __global__ __launch_bounds__(256) void conv1x1_tinyk_kernel(TinyKArgs p) {
   const int groups = (p.Co + TK_CO - 1) / TK_CO, o0 = (blockIdx.x % groups) * TK_CO, co = min(TK_CO, p.Co - o0);
   if (threadIdx.x < co * 4) {
     const int o = o0 + (threadIdx.x >> 2), c = threadIdx.x & 3;
-    wl[threadIdx.x >> 2][c] = c < p.Ci ? bf16_to_f32(p.W[((int64_t)b * p.Co + o) * p.Ci + c]) : 0.f;
+    wl[threadIdx.x >> 2][c] = c < p.Ci ? bf16_to_f32(p.W[b * p.wsb + n * p.wsn + (int64_t)o * p.Ci + c]) : 0.f;
     if (c == 0) bl[threadIdx.x >> 2] = p.bias ? bf16_to_f32(p.bias[(int64_t)b * p.Co + o]) : 0.f;
   }
   __syncthreads();
@@ -276,6 +279,19 @@ float* static_scratch() {
 
 }  // namespace
 
+namespace hfta {
+// k=1 convolution of at most 4 bf16 input channels and 256 outputs over rows of at least 4 points; W[o][c] of model b and
+// sample n at b * w_b + n * w_n
+int conv1x1_tinyk(int B, int Nb, int Ci, int Co, int L, const void* X, const int64_t xs[4], const void* W, int64_t w_b, int64_t w_n,
+                  const void* bias, void* Y, const int64_t ys[4], int act, float act_slope, hipStream_t st) {
+  TinyKArgs a{(const bf16_raw*)X, (const bf16_raw*)W, (const bf16_raw*)bias, (bf16_raw*)Y, xs[0], xs[1], xs[2],
+              ys[0], ys[1], ys[2], w_b, w_n, Ci, Co, L, act, act_slope};
+  dim3 grid((unsigned)(((L + 3) / 4 + 255) / 256 * ((Co + TK_CO - 1) / TK_CO)), (unsigned)Nb, (unsigned)B);
+  hipLaunchKernelGGL(conv1x1_tinyk_kernel, grid, dim3(256), 0, st, a);
+  return launch_status();
+}
+}  // namespace hfta
+
 extern "C" {
 
 int hfta_linear_fwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* bias,
@@ -433,11 +449,7 @@ static int conv1x1_fwd_impl(int B, int Nb, int Ci, int Co, int L, int dtype, con
   // Rows of other lengths take this kernel only in the block form (the caller's statistics workspace): a caller without one
   // asked for the single operators, whose products keep the matrix kernels' rounding.
   if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && (L % 4 == 0 || (stat_part && L >= 4)) && Nb <= 65535 && B <= 65535) {
-    TinyKArgs a{(const bf16_raw*)X, (const bf16_raw*)W, (const bf16_raw*)bias, (bf16_raw*)Y, xs[0], xs[1], xs[2],
-                ys[0], ys[1], ys[2], Ci, Co, L, act, act_slope};
-    dim3 grid((unsigned)(((L + 3) / 4 + 255) / 256 * ((Co + TK_CO - 1) / TK_CO)), (unsigned)Nb, (unsigned)B);
-    hipLaunchKernelGGL(conv1x1_tinyk_kernel, grid, dim3(256), 0, as_stream(stream), a);
-    return launch_status();
+    return hfta::conv1x1_tinyk(B, Nb, Ci, Co, L, X, xs, W, (int64_t)Co * Ci, 0, bias, Y, ys, act, act_slope, as_stream(stream));
   }
   if (dtype == HFTA_BF16) {   // wide layer, few input channels: streaming kernel
     rc = hfta::conv1x1_stream_fwd(B, Nb, Ci, Co, L, X, xs, W, bias, Y, ys, act, act_slope, as_stream(stream));
