@@ -34,7 +34,7 @@ namespace hfta {
 namespace {
 
 constexpr int F32_BK = 32;                                 // floats of k per tile: a whole 128-byte line of a k-contiguous row
-constexpr int F32_TINY = (27 << 8) - 1;                     // 2 * bits - 1 of 2^-100 in bf16: smaller (but zero) is not split
+constexpr uint32_t F32_TINY = (27u << 24) - 1;             // 2 * bits - 1 of 2^-100: smaller (but zero) is not split
 constexpr int F32_SMALL_TILES = 512;                       // fewer 128x128 tiles than this: 64x64 tiles
 typedef uint32_t pf_u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -54,13 +54,13 @@ __device__ __forceinline__ float ld_f1(__amdgpu_buffer_rsrc_t rs, uint32_t off) 
 }
 
 // Four values as three planes of four bf16.  `chk` becomes NaN if one has no finite remainder; `low` holds the smallest
-// magnitude but zero (as 2 * bits - 1 of the first part: zero wraps to the largest).
-typedef unsigned short f32s_u16x2 __attribute__((ext_vector_type(2)));
+// magnitude but zero, as 2 * bits - 1 of the value itself: zero wraps to the largest, and what its first part rounds to
+// zero (below 2^-134) does not look like one.
 typedef __bf16 f32s_bf16x2 __attribute__((ext_vector_type(2)));
 struct SplitSeen {
   float chk = 0.f;
-  f32s_u16x2 low = {0xffff, 0xffff};
-  __device__ __forceinline__ bool bad() const { return chk != chk || min(low.x, low.y) < F32_TINY; }
+  uint32_t low = 0xffffffffu;
+  __device__ __forceinline__ bool bad() const { return chk != chk || low < F32_TINY; }
 };
 // the rounded pair; x and y become what it leaves (exact: a two-element dot product with -1 and 0)
 __device__ __forceinline__ uint32_t split_pair(float& x, float& y) {
@@ -76,6 +76,8 @@ __device__ __forceinline__ uint32_t split_pair(float& x, float& y) {
 __device__ __forceinline__ void split4(const float4& v, uint2 (&o)[3], SplitSeen& seen) {
   float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
+  for (int i = 0; i < 4; ++i) seen.low = min(seen.low, __float_as_uint(e[i]) * 2u - 1u);
+#pragma unroll
   for (int q = 0; q < 2; ++q) {
     o[q].x = split_pair(e[0], e[1]);
     o[q].y = split_pair(e[2], e[3]);
@@ -84,11 +86,8 @@ __device__ __forceinline__ void split4(const float4& v, uint2 (&o)[3], SplitSeen
   o[2].y = pack_bf16x2(e[2], e[3]);
   const f32s_bf16x2 ones = __builtin_bit_cast(f32s_bf16x2, 0x3f803f80u);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const uint32_t h = i ? o[0].y : o[0].x, l = i ? o[2].y : o[2].x;
-    seen.low = __builtin_elementwise_min(seen.low, __builtin_bit_cast(f32s_u16x2, h) * (unsigned short)2 - (unsigned short)1);
-    seen.chk = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(f32s_bf16x2, l), ones, seen.chk, false);
-  }
+  for (int i = 0; i < 2; ++i)
+    seen.chk = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(f32s_bf16x2, i ? o[2].y : o[2].x), ones, seen.chk, false);
 }
 
 template <bool KC, int NB, int VEC> struct F32Operand;

@@ -1,6 +1,6 @@
 """The fp32 products as sums of bf16 products (k=1 convolution, forward and both gradients): tiles of both sizes, pieces
-that straddle a row's end, and values that have no split -- infinities, NaN, magnitudes near the largest and below 2^-100,
-which go through the fp32 matrix instruction.
+that straddle a row's end, and values that have no split -- infinities, NaN, magnitudes near the largest and below 2^-100
+down to fp32's smallest, which go through the fp32 matrix instruction.
 
 Reference: float64 products of the same values.  Bound per element, in units of 2^-24 sum|a||b|: a matrix instruction adds
 sixteen products to its accumulator and rounds or truncates once (2 units per 16 k, as much again for the sums inside it),
@@ -68,7 +68,7 @@ def test_products(hb, B, Nb, Ci, Co, L):
 
 
 @pytest.mark.parametrize("B,Nb,Ci,Co,L", [(2, 16, 72, 132, 1028), (1, 2, 131, 67, 133)])
-@pytest.mark.parametrize("what", ["inf", "nan", "largest", "small", "tiny"])
+@pytest.mark.parametrize("what", ["inf", "nan", "largest", "small", "tiny", "subnormal", "subnormal among ordinary"])
 def test_values_without_a_split(hb, B, Nb, Ci, Co, L, what):
     r = np.random.default_rng(7)
     x, w, dy = (r.standard_normal(s).astype(np.float32) for s in ((Nb, B * Ci, L), (B * Co, Ci), (Nb, B * Co, L)))
@@ -84,12 +84,17 @@ def test_values_without_a_split(hb, B, Nb, Ci, Co, L, what):
     elif what == "small":                                      # tiny values among ordinary ones
         x[:, :, ::3] *= np.float32(2.0 ** -118)
         dy[:, :, ::3] *= np.float32(2.0 ** -118)
+    elif what.startswith("subnormal"):                         # below bf16's smallest: the first part rounds to zero
+        part = slice(None) if what == "subnormal" else slice(None, None, 3)
+        x[:, :, part] *= np.float32(2.0 ** -140)
+        dy[:, :, part] *= np.float32(2.0 ** -140)
+        w *= np.float32(2.0 ** 100)
     else:                                                      # and nothing else: results near fp32's smallest normal numbers
         x *= np.float32(2.0 ** -118)
         dy *= np.float32(2.0 ** -118)
     for n, got, ref, mag, K in run(hb, B, Nb, Ci, Co, L, x, w, dy):
-        if what == "tiny" and n == "dW":
-            continue                                           # 2^-236: below fp32
+        if what in ("tiny", "subnormal") and n == "dW":
+            continue                                           # 2^-236, 2^-280: below fp32
         if what == "largest" and n == "dW":
             assert not np.isnan(got).any()                     # products beyond fp32 may go either way at its edge
             continue
