@@ -514,8 +514,11 @@ int hfta_point_transform_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, co
                              const void* T, void* Y, const int64_t ys[4], void* stream) {
   if (B <= 0 || Nb <= 0 || Ci <= 0 || Co <= 0 || L <= 0 || !valid_dtype(dtype) || !X || !xs || !T || !Y || !ys) return HFTA_EINVAL;
   if (xs[3] != 1 || ys[3] != 1 || (int64_t)B * Nb > 65535) return HFTA_EUNSUPPORTED;
-  // Coordinates: no matrix instruction pays for K = 3, and weights of three elements in a row are fetched one by one.
-  if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && L >= 4)
+  // Coordinates: no matrix instruction pays for K = 3, and weights of three elements in a row are fetched one by one.  As for
+  // the k=1 convolution, rows that are not whole four-point pieces keep the matrix kernels' rounding (64 us for 5 on 8 x 32 x
+  // 2499): sums whose terms cancel round otherwise here, and what stands behind the transforms turns a last bit on such
+  // rows into percents.
+  if (dtype == HFTA_BF16 && Ci <= 4 && Co <= 256 && L % 4 == 0)
     return conv1x1_tinyk(B, Nb, Ci, Co, L, X, xs, T, (int64_t)Nb * Co * Ci, (int64_t)Co * Ci, nullptr, Y, ys, HFTA_ACT_NONE, 0.f,
                          as_stream(stream));
   GemmDesc g = head_desc(B, 1, Nb, dtype);
