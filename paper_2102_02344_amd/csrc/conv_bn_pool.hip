@@ -53,8 +53,10 @@ struct CbpArgs {
   uint32_t x_extent, g_extent;
 };
 
-// the z whose normalised value is pooled (see fbp_finish_kernel)
+// the z whose normalised value is pooled (see fbp_finish_kernel), and that value, a = gamma * invstd: one expression for the
+// forward's maximum and the backward's mask, which must not round to different sides of zero
 __device__ __forceinline__ float pooled_z(float z, int L) { return L & 3 ? bf16_to_f32(f32_to_bf16(z)) : z; }
+__device__ __forceinline__ float pooled_pre(float z, int L, float a, float mean, float beta) { return fmaf(a, pooled_z(z, L) - mean, beta); }
 
 // ---- per channel: dbeta, dgamma from the Nb argmax elements; coefficients ----------------
 // Lanes are 64 neighbouring channels (of the [.., Co] rows whole cache lines), the eight wavefronts take every eighth
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(COEF_WAVES * 64) void cbp_coef_kernel(CbpArgs p) {
       else z = bf16_to_f32(p.Z[b * p.zsb + n * p.zsn + c * p.zsc + min(max(p.idx[v], 0), p.L - 1)]);
       const float xh = (z - mean) * invstd;
       // the activation's side is the pooled value's
-      const float pre = fmaf(g, p.zhit ? (pooled_z(z, p.L) - mean) * invstd : xh, bt);
+      const float pre = p.zhit ? pooled_pre(z, p.L, a, mean, bt) : fmaf(g, xh, bt);
       const float gr = bf16_to_f32(p.dV[v]) * act_grad(pre, p.act, p.slope);
       s1[i] += gr;
       s2[i] = fmaf(gr, xh, s2[i]);
@@ -1044,7 +1046,7 @@ __global__ __launch_bounds__(256) void fbp_stats_kernel(FbpArgs p) {
 // stored operators (rounding keeps the order, so the rounded maximum is the maximum of the rounded values).
 // That chain is what such rows ran through before this operator took them; a fully connected head behind the
 // pool normalises small differences between clouds, and a value one step off there is a percent two layers on.
-// zhit keeps the fp32 product; the backward's mask is that of the value pooled here (pooled_z in both).
+// zhit keeps the fp32 product; the backward's mask is that of the value pooled here (pooled_pre in both).
 __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   const int c = blockIdx.x * 256 + threadIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (c >= p.Co) return;
@@ -1062,7 +1064,7 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
   const float bias = p.bias ? bf16_to_f32(p.bias[k]) : 0.f;
   const float scale = g * p.save_invstd[k], mean = p.save_mean[k], beta = p.beta[k];
   float z = (g < 0.f ? -best : best) + bias;
-  float pre = fmaf(scale, pooled_z(z, p.L) - mean, beta);
+  float pre = pooled_pre(z, p.L, scale, mean, beta);
   // Equal activated values: the maximum is taken over act(BatchNorm(z)), so where the activation
   // is flat (ReLU, or LeakyReLU with slope 0, at a maximum that is not positive) or the channel's
   // scale is zero, every point of the row holds the same value and the lowest index, 0, is the
@@ -1078,9 +1080,8 @@ __global__ __launch_bounds__(256) void fbp_finish_kernel(FbpArgs p, int tiles) {
       acc = fmaf(bf16_to_f32(w[ci]), xv, acc);
     }
     at = 0;
-    z = acc + bias;
-    pre = fmaf(scale, pooled_z(z, p.L) - mean, beta);
-    if (clipped && pre > 0.f) pre = 0.f;                 // the row's maximum was not positive
+    const float z0 = acc + bias, pre0 = pooled_pre(z0, p.L, scale, mean, beta);
+    if (!(clipped && pre0 > 0.f)) { z = z0; pre = pre0; }    // else the sum's order alone made it positive: z of the maximum stays
   }
   const float y = apply_act(pre, p.act, p.slope);
   p.V[b * p.vsb + n * p.vsn + c * p.vsc] = f32_to_bf16(y);

@@ -79,3 +79,48 @@ def test_zero_scale_pools_the_shift(hb, act):
     ref = bt if act == 0 else np.where(bt > 0, bt, (0.2 if act == 2 else 0.0) * bt)
     assert (bt > 0).any() and int(I.abs().max()) == 0
     assert torch.equal(V[0].cpu(), torch.from_numpy(ref.astype(np.float32)).bfloat16().expand(Nb, Co))
+
+
+@pytest.mark.parametrize("near", ["rounding of the value", "rounding of point 0"])
+@pytest.mark.parametrize("L", [516, 257])
+def test_mask_is_the_pooled_values(hb, L, near):
+    """Shifts that bring a sample's maximum within rounding of zero: gradient passes where, and only where, a positive value was
+    pooled, so with a gradient of one dbeta counts them.  "Point 0": its z is a last bit below the maximum's, and recomputed
+    in another order of the sum it may come out above."""
+    B, Nb, Ci, Co = 2, 3, 64, 512
+    x = hi.normal(361, (Nb, B, Ci, L))
+    if near == "rounding of point 0":
+        x[..., 1] *= 8.0
+        x[..., 2:] *= 0.0625
+        x[:, :, 0, 1] = 2.0 ** -10
+        x[..., 0] = x[..., 1]
+        x[:, :, 0, 0] = 0.0
+    x = hi.snap(x.reshape(Nb, B * Ci, L).astype(np.float32), "bf16")
+    w = hi.normal(362, (B * Co, Ci), "bf16", 1.0 / np.sqrt(Ci))
+    if near == "rounding of point 0":
+        w[:, 0] = 2.0 ** -10
+    g = np.abs(hi.normal(363, (B * Co,)) * 0.3 + 1.0).astype(np.float32) + np.float32(0.1)
+    X, W, G = dev(x, "bf16"), dev(w, "bf16"), dev(g)
+    SM, SI = torch.empty(B * Co, device="cuda"), torch.empty(B * Co, device="cuda")
+    V, I = torch.empty(B, Nb, Co, dtype=torch.bfloat16, device="cuda"), torch.empty(B, Nb, Co, dtype=torch.int32, device="cuda")
+    Z, M = torch.empty(B, Nb, Co, device="cuda"), torch.empty(hb.conv1x1_bn_maxpool_saved_floats(B, Ci, Co), device="cuda")
+    ws = torch.empty(hb.conv1x1_bn_maxpool_workspace_bytes(B, Nb, Ci, Co, L, DT["bf16"]), dtype=torch.uint8, device="cuda")
+    sx, vs = conv_strides(B, Ci, L), (Nb * Co, Co, 1)
+
+    def forward(beta, act):
+        hb.conv1x1_bn_maxpool_fwd(B, Nb, Ci, Co, L, DT["bf16"], X, sx, W, None, G, beta, 1e-5, 0.1, None, None, SM, SI, V, I, vs, Z, M,
+                                  act, 0.0, ws)
+
+    forward(torch.zeros(B * Co, device="cuda"), hb.ACT_NONE)
+    z, mean, invstd = Z[:, 0].reshape(-1).clone(), SM.clone(), SI.clone()
+    if L % 4:
+        z = z.bfloat16().float()
+    beta = -((G * invstd) * (z - mean))
+    ulps = torch.tensor([-1, 0, 0, 1], device="cuda", dtype=torch.int32).repeat(B * Co // 4)
+    beta = (beta.view(torch.int32) + ulps).view(torch.float32)
+    forward(beta, hb.ACT_RELU)
+    dX, dV = torch.empty_like(X), torch.ones_like(V)
+    dW, dG, dBt = (torch.empty(n, device="cuda") for n in (B * Co * Ci, B * Co, B * Co))
+    hb.conv1x1_bn_maxpool_bwd(B, Nb, Ci, Co, L, DT["bf16"], X, sx, W, None, None, None, Z, M, dV, I, vs, G, beta, SM, SI, dX, sx, dW,
+                              None, dG, dBt, hb.ACT_RELU, 0.0, ws)
+    assert torch.equal(dBt.view(B, Co), (V.float() > 0).float().sum(1))
