@@ -15,15 +15,13 @@
 //   weight gradient: dW[o][(c, ky, kx)] = sum_{(n, y, x)} dY[n][o][y][x] X[n][c][...].
 //
 // bf16 only; output grids whose width and height are powers of two; see ig_*_supported.
-#include <mutex>
-#include <vector>
 #include "gemm_dma.h"
 
 namespace hfta {
 
 namespace {
 
-constexpr int IG_MARGIN = 8;            // zero columns left of a patch row (keeps the data 16-byte aligned)
+constexpr int IG_MARGIN = 8;            // gathering kernel: zero columns left of a patch row
 
 // Workgroups are dispatched to the 8 XCDs (each with its own L2) round-robin by their linear id.
 // The kernels are launched on a 1-D grid and turn the id into a logical (x, y, z) block such that
@@ -58,7 +56,7 @@ struct IgArgs {
   int OW, oys, oxs;                     // output image width in memory, output step per grid step
   int tap_step;                         // gathering kernel: 1 (patch elements between the taps of a window row)
   int NI, TR, PR, PW, SP;               // samples per tile, grid rows per tile and sample, patch rows, row pitch, sample pitch (elements)
-  int nchunk, chunk_el;                 // 16- or 8-byte pieces of patch rows per k-tile, elements per piece
+  int nchunk;                           // 16- or (gathering kernel) 8-byte pieces of patch rows per k-tile
   int chp, plp;                         // plane kernels: bytes of a channel's rows in a plane, bytes between planes
   uint32_t x_bytes, a_bytes;            // extent of one model's slice of the view operand / of its weights
   IgGrid grid;                          // logical grid: x = tiles, y = class / k split, z = model
@@ -378,59 +376,22 @@ __global__ __launch_bounds__(256) void conv_ig_gather_kernel(IgArgs p) {
 int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
-// patch geometry shared by the host-side checks and the launch
-// Patch geometry.  The gather reads 2-byte elements: the LDS serves 32 lanes per clock from 32
-// banks of 4 bytes (lanes on the same word are served together; measured: 2 clocks for a
-// conflict-free 64-lane read, 2n for an n-way conflict), and the 32 lanes of a half wavefront are 32
-// consecutive columns, i.e. several image rows (and samples) of small images.  With the natural row
-// pitch the four rows of an 8x8 layer that a half wavefront touches fall on the same banks (4-way,
-// 8 clocks per read).  Row pitch and sample pitch are therefore searched (multiples of 8 elements,
-// so that 16-byte pieces stay aligned) for the fewest conflicts over all taps of a window row.
-// (The search is a pure function of the layer geometry; its results are memoised, a call costs the
-// host ~100 us otherwise.)
-struct IgPitchKey { int KW, S, Ho, Wo, W, cols, pair, PW, SP; };
-std::mutex ig_pitch_mutex;
-std::vector<IgPitchKey> ig_pitch_cache;
-
-bool ig_geometry(IgArgs& a, int KW, int KH, int S, int Ho, int Wo, int W, int cols, bool pair) {
-  a.Ho = Ho; a.Wo = Wo; a.lgWo = ilog2(Wo); a.lgP = ilog2(Ho * Wo);
+// Pixels of a data gradient's tile (64 of each class), the rows of dY they need.
+void dx_geometry(IgArgs& a, int Ho, int Wo) {
   const int P = Ho * Wo;
-  if (P >= cols) { a.NI = 1; a.TR = cols / Wo; } else { a.NI = cols / P; a.TR = Ho; }
-  a.PR = (a.TR - 1) * S + KH;
-  a.chunk_el = W % 8 == 0 ? 8 : 4;
-  const int pw0 = W % 8 == 0 ? W + 16 : W + 12;
-  {
-    std::lock_guard<std::mutex> lock(ig_pitch_mutex);
-    for (const IgPitchKey& k : ig_pitch_cache)
-      if (k.KW == KW && k.S == S && k.Ho == Ho && k.Wo == Wo && k.W == W && k.cols == cols && k.pair == (int)pair) {
-        a.PW = k.PW; a.SP = k.SP;
-        return true;
-      }
-  }
-  const int floor_cost = (pair ? 2 : 1) * KW * (cols / 32);   // one pass per half wavefront and tap
-  int64_t best = -1;
-  for (int i = 0; i < 6 && best / (1 << 20) != floor_cost; ++i)
-    for (int j = 0; j < 8 && best / (1 << 20) != floor_cost; ++j) {
-      const int pw = pw0 + 8 * i, sp = a.PR * pw + 8 * j;
-      int cost = 0;
-      for (int cls = 0; cls < (pair ? 2 : 1); ++cls)
-        for (int tx = 0; tx < KW; ++tx)
-          for (int h = 0; h < cols; h += 32) {            // one half wavefront's columns
-            int words[32], nw = 0, per_bank[32] = {0}, worst = 0;
-            for (int l = 0; l < 32; ++l) {
-              const int n = h + l, il = n >> a.lgP, y = (n & (P - 1)) >> a.lgWo, x = n & (Wo - 1);
-              const int word = (il * sp + y * S * pw + x * S + (pair ? cls - 1 : -1) + IG_MARGIN + tx) >> 1;
-              bool seen = false;
-              for (int q = 0; q < nw; ++q) seen = seen || words[q] == word;
-              if (!seen) { words[nw++] = word; worst = ++per_bank[word & 31] > worst ? per_bank[word & 31] : worst; }
-            }
-            cost += worst;
-          }
-      const int64_t key = (int64_t)cost * (1 << 20) + (int64_t)a.NI * sp;   // fewest conflicts first, then the smallest patch
-      if (best < 0 || key < best) { best = key; a.PW = pw; a.SP = sp; }
-    }
-  std::lock_guard<std::mutex> lock(ig_pitch_mutex);
-  if (ig_pitch_cache.size() < 256) ig_pitch_cache.push_back(IgPitchKey{KW, S, Ho, Wo, W, cols, (int)pair, a.PW, a.SP});
+  a.Ho = Ho; a.Wo = Wo; a.lgWo = ilog2(Wo); a.lgP = ilog2(P);
+  if (P >= 64) { a.NI = 1; a.TR = 64 / Wo; } else { a.NI = 64 / P; a.TR = Ho; }
+  a.PR = a.TR + 1;
+}
+
+// What the gathering kernel is built for: images of four-pixel rows taller than a tile.  The gather reads 2-byte elements and
+// the 32 lanes of a half wavefront are eight rows' pixels: at a row pitch of 12 words no two of the rows share a bank (at the
+// natural 8 every fourth does).
+bool gather_geometry(IgArgs& a) {
+  if (a.W != 4 || a.NI != 1) return false;
+  a.PW = 24;
+  a.SP = a.PR * a.PW;
+  a.nchunk = 8 * a.PR;                                    // pieces: a row of each of eight channels
   return true;
 }
 
@@ -646,16 +607,16 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   a.M = Ci; a.K = Co * 4; a.N = Nb * Hq * Wq;
   if (!ig_extents(a)) return HFTA_EUNSUPPORTED;
   a.OW = W; a.oys = 2; a.oxs = 2; a.tap_step = 1;
-  ig_geometry(a, 2, 2, 1, Hq, Wq, Wq, 64, true);
-  a.nchunk = 8 * a.NI * a.PR * (Wq / a.chunk_el);
-  if (a.nchunk > 512) return HFTA_EUNSUPPORTED;
+  dx_geometry(a, Hq, Wq);
+  const bool planes = dxp_geometry(a);
+  if (!planes && !gather_geometry(a)) return HFTA_EUNSUPPORTED;
   a.tiles_n = (a.N + 63) / 64;
   a.act = HFTA_ACT_NONE; a.slope = 0.f;
   for (int cls = 0; cls < 4; ++cls) {
     const int py = cls >> 1, px = cls & 1;
     a.cls[cls] = IgClass{py - 1, px - 1, py, px, cls * cls_el};          // window rows qy + py - 1, qy + py
   }
-  const size_t lds = ig_lds_bytes(a);
+  const size_t lds = planes ? dxp_lds_bytes(a) : ig_lds_bytes(a);
   if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   if ((int64_t)tiles_m * a.tiles_n > 0x7fffffff) return HFTA_EUNSUPPORTED;
   const int64_t count = (int64_t)B * 4 * cls_el / 8;                   // 16-byte fragment pieces
@@ -664,15 +625,14 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   a.ksplit = 1;
   a.kt_per_split = ktiles;
   dim3 grid((unsigned)(tiles_m * a.tiles_n), 2u, (unsigned)B);
-  if (dxp_geometry(a)) {
-    const size_t lds2 = dxp_lds_bytes(a);
+  if (planes) {
     const bool few = (int64_t)tiles_m * a.tiles_n * 2 * B < 256;
     if (a.W == 4) {
-      if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, true, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<64, true, 1>, grid, 256, lds2, st, a);
-      else few ? ig_launch(conv_dx_planes_kernel<128, true, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<128, true, 1>, grid, 256, lds2, st, a);
+      if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, true, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<64, true, 1>, grid, 256, lds, st, a);
+      else few ? ig_launch(conv_dx_planes_kernel<128, true, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<128, true, 1>, grid, 256, lds, st, a);
     } else {
-      if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<64, false, 1>, grid, 256, lds2, st, a);
-      else few ? ig_launch(conv_dx_planes_kernel<128, false, 2>, grid, 256, lds2, st, a) : ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds2, st, a);
+      if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, false, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<64, false, 1>, grid, 256, lds, st, a);
+      else few ? ig_launch(conv_dx_planes_kernel<128, false, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds, st, a);
     }
   } else {
     if (tm == 64) ig_launch(conv_ig_gather_kernel<64>, grid, 256, lds, st, a);
