@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void bn_apply_maxpool_kernel(BnPoolFwdArgs p, 
 // Statistics and pooled values from what the fp32 convolution's epilogue left per (sample, column tile, channel): sum, sum
 // of squares about the tile's mean, extreme of z (largest, or smallest where gamma < 0) and where it is.  BatchNorm is
 // monotone in z per channel and the activations taken here do not decrease, so the extreme's normalised value is the row's
-// maximum; a row whose activated values are all equal (clipped, or gamma = 0) has its maximum at point 0.  The 1.3 GB of z
+// maximum; a row whose activated values are all equal (clipped, or gamma = 0) or no numbers has its maximum at point 0.  The 1.3 GB of z
 // are not read (4 x 32 x 2500 points, 1024 channels: bn_fwd_maxpool_kernel 402 us, this 23 and the epilogue 122 more).
 // 16 channels a workgroup: 16 lanes read 256 contiguous bytes of a part, 64 parts in flight.
 constexpr int PP_C = 16, PP_P = 64;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(PP_C * PP_P) void bn_pool_parts_kernel(BnPoolFwdArg
     }
     float pre = fmaf(g, ((g < 0.f ? -best : best) - mean) * invstd, bt);
     const bool clipped = clips && !(pre > 0.f);
-    if (g == 0.f || clipped) {
+    if (g == 0.f || clipped || pre != pre) {
       at = 0;
       const float z0 = reinterpret_cast<const float*>(p.X)[b * p.xsb + n * p.xsn + c * p.xsc];
       pre = fmaf(g, (z0 - mean) * invstd, bt);

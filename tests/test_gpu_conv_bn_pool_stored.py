@@ -105,3 +105,31 @@ def test_pooled_only_f32(hb, dims, act, slope, with_ws):
     assert np.all(np.take_along_axis(y, idx.astype(np.int64), axis=2)[:, :, 0] >= y.max(axis=2) - lim)
     flat = (y.max(axis=2) == y.min(axis=2))
     assert np.all(idx[:, :, 0][flat] == 0)
+
+
+@pytest.mark.parametrize("act,slope", [(0, 0.0), (1, 0.0), (2, 0.2)])
+@pytest.mark.parametrize("dims", [(4, 16, 72, 260, 1028), (4, 16, 70, 260, 1030), (1, 2, 8, 65, 65)])
+def test_channels_that_are_not_numbers_f32(hb, dims, act, slope):
+    """NaN and infinities in z (from weights, so in some channels only; from one point, so in all of a model): values and
+    indices of those channels are the two operators' own, the others stay finite."""
+    B, Nb, Ci, Co, L = dims
+    ins = setup(*dims, "f32")
+    nan, inf = float("nan"), float("inf")
+    ins[1][3, 1], ins[1][10, 2], ins[1][11, 2] = nan, inf, -inf
+    if B > 1:
+        ins[0][Nb // 2, Ci + 5, L - 1] = nan
+        ins[0][1, 2 * Ci + 6, 7] = inf
+    ws = torch.empty(hb.conv1x1_bn_pool_fwd_workspace_bytes(*dims, 0), dtype=torch.uint8, device="cuda")
+    a, b = outputs(B, Nb, Co, L, "f32", False), outputs(B, Nb, Co, L, "f32", False)
+    call(hb, dims, "f32", ins, a, act, slope, ws)
+    X, W, Bi, G, Bt = ins
+    ys = conv_strides(B, Co, L)
+    hb.conv1x1_fwd(B, Nb, Ci, Co, L, 0, X, conv_strides(B, Ci, L), W, Bi, b["Z"], ys)
+    hb.bn_fwd_maxpool(B, Nb, Co, L, 0, b["Z"], ys, G, Bt, 1e-5, 0.1, b["rm"], b["rv"], b["mean"], b["invstd"], b["V"], b["idx"],
+                      (Nb * Co, Co, 1), act, slope)
+    bad = ~torch.isfinite(b["mean"])
+    assert bad.any() and not bad.all() and torch.equal(bad, ~torch.isfinite(a["mean"]))
+    bad = bad.view(B, 1, Co).expand(B, Nb, Co)
+    assert torch.equal(a["idx"][bad], b["idx"][bad])
+    assert torch.equal(torch.nan_to_num(a["V"][bad], 7.0), torch.nan_to_num(b["V"][bad], 7.0))
+    assert torch.isfinite(a["V"][~bad]).all()
