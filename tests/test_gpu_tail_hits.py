@@ -85,20 +85,22 @@ def test_zero_scale_pools_the_shift(hb, act):
 @pytest.mark.parametrize("L", [516, 257])
 def test_mask_is_the_pooled_values(hb, L, near):
     """Shifts that bring a sample's maximum within rounding of zero: gradient passes where, and only where, a positive value was
-    pooled, so with a gradient of one dbeta counts them.  "Point 0": its z is a last bit below the maximum's, and recomputed
-    in another order of the sum it may come out above."""
+    pooled, so with a gradient of one dbeta counts them.  "Point 0": its z is 2^-16 below the maximum's, and recomputed one
+    product after the other through partial sums of about 64 it comes out above in some channels."""
     B, Nb, Ci, Co = 2, 3, 64, 512
     x = hi.normal(361, (Nb, B, Ci, L))
     if near == "rounding of point 0":
         x[..., 1] *= 8.0
         x[..., 2:] *= 0.0625
-        x[:, :, 0, 1] = 2.0 ** -10
+        x[:, :, 1, 1], x[:, :, Ci - 1, 1] = 512.0, -512.0
+        x[:, :, 0, 1] = 2.0 ** -6
         x[..., 0] = x[..., 1]
         x[:, :, 0, 0] = 0.0
     x = hi.snap(x.reshape(Nb, B * Ci, L).astype(np.float32), "bf16")
     w = hi.normal(362, (B * Co, Ci), "bf16", 1.0 / np.sqrt(Ci))
     if near == "rounding of point 0":
         w[:, 0] = 2.0 ** -10
+        w[:, Ci - 1] = w[:, 1]
     g = np.abs(hi.normal(363, (B * Co,)) * 0.3 + 1.0).astype(np.float32) + np.float32(0.1)
     X, W, G = dev(x, "bf16"), dev(w, "bf16"), dev(g)
     SM, SI = torch.empty(B * Co, device="cuda"), torch.empty(B * Co, device="cuda")
