@@ -179,7 +179,7 @@ def kernel_label(name, a):
         k = small_gemm(dt)
         if a[11] is not None:
             if dt == 1 and Co % 8 == 0 and L >= 4 and a[15] is not None and (
-                    Ci >= 64 if Co <= 128 else Co <= 256 and Ci >= 512 and L % 4 and B * Nb * ((L + 127) // 128) >= 768):
+                    Ci >= 64 if Co <= 128 else 192 < Co <= 256 and Ci >= 1280 and L % 4 and B * Nb * ((L + 127) // 128) >= 768):
                 return "conv1x1_stream_kernel(dX)"
             return (big_name(B * Nb, Ci, L) if dt == 1 and big_gemm(B * Nb, Ci, L, Co) else k) + "(dX)"
         sp = big_splits(B, Co, Ci, L, Nb) if dt == 1 else 0

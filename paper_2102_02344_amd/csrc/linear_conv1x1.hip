@@ -606,14 +606,19 @@ int hfta_conv1x1_bn_prenorm_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,
 }
 
 // The data gradient of a narrow layer (Co <= 128) is a k=1 convolution of dY with the transposed weights: it takes the streaming
-// forward kernel once W^T [B][Ci][Co] has been written to the workspace.  So does Co <= 256 under at least 512 inputs where rows
-// are not of whole 8-byte pieces and the points fill the chip three times over (2880 <- 256 channels on 6 x 16 x 1023 points
-// 378 us, 389 as a product); any other such layer is a product (2500 points: 744 -> 699 us; 1 x 2 x 2500 93 -> 21, a workgroup
-// per 128 points there; 8 x 32 x 2500 under 512 inputs 417 -> 301).
+// forward kernel once W^T [B][Ci][Co] has been written to the workspace.  A layer of up to 256 channels is a product: the
+// 256-deep streaming kernel has one workgroup per 128 points (2880 <- 256 channels, 1 x 2 x 2500 points: 93 -> 21 us; 6 x 16 x
+// 2500 744 -> 699; 512 <- 256 on 8 x 32 x 2500 417 -> 301).  It stays for wide layers on rows that are not of whole 8-byte
+// pieces, where the product loads at element alignment, from three workgroups per compute unit.  Both sides there, stream and
+// product in us, at 6 x 16 x 1023 (768 workgroups), 12 x 16 x 777 (1344), 8 x 32 x 1023 (2048) and 6 x 16 x 2499 (1920):
+//   2880 <- 256: 351 366, 568 588, 872 961, 753 904     2880 <- 224: 347 348, 565 557, 874 913, 747 858
+//   1280 <- 256: 163 166, 269 264, 406 427, 350 400     2880 <- 200: 344 345, 568 549, 884 904, 757 849
+// and outside the rule 1024 <- 256: 135 113 (768), 332 341 (2048); 2880 <- 192: 341 329, 852 864; 1024 <- 192: 125 93, 326 300;
+// 512 <- 256: 76 58, 190 180; below 768 workgroups 2880 <- 256: 300 276 (576), 210 189 (384), 118 78 (192).
 static bool dx_streams(int B, int Nb, int Ci, int Co, int L, int dtype) {
   if (dtype != HFTA_BF16 || Co % 8 != 0 || L < 4) return false;
   if (Co <= 128) return Ci >= 64;
-  return Co <= 256 && Ci >= 512 && L % 4 != 0 && (int64_t)B * Nb * ((L + 127) / 128) >= 768;
+  return Co > 192 && Co <= 256 && Ci >= 1280 && L % 4 != 0 && (int64_t)B * Nb * ((L + 127) / 128) >= 768;
 }
 static size_t wt_offset(size_t partial_bytes) { return (partial_bytes + 255) & ~(size_t)255; }
 

@@ -60,5 +60,27 @@ def test_forward_and_gradients_of_small_layers(hb, B, Nb, Ci, Co, L, pad):
 
 @pytest.mark.parametrize("B,Nb,Ci,Co,L", [(1, 2, 520, 136, 516), (1, 2, 512, 256, 515), (8, 32, 512, 136, 261), (2, 24, 576, 256, 1032)])
 def test_wide_data_gradient(hb, B, Nb, Ci, Co, L):
-    """More than 128 output channels under at least 512 inputs: a product, or (261 points on 768 workgroups) streamed."""
+    """More than 128 output channels under at least 512 inputs: products."""
     test_forward_and_gradients(hb, B, Nb, Ci, Co, L, 0)
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L", [(8, 32, 1280, 200, 261), (8, 32, 1280, 192, 261), (8, 32, 1272, 256, 261), (8, 31, 1280, 256, 261),
+                                          (4, 64, 1288, 256, 263)])
+def test_wide_data_gradient_either_way(hb, B, Nb, Ci, Co, L):
+    """Both sides of the rule that streams such gradients (more than 192 channels, 1280 inputs, 768 workgroups, odd rows): with
+    its workspace and without, where there is no room for the transposed weights, the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Ci)
+    W = (torch.randn(B, Co, Ci, generator=g, device="cuda") / 16).bfloat16()
+    dY = torch.randn(Nb, B, Co, L, generator=g, device="cuda").bfloat16()
+    strides = lambda C: (C * L, B * C * L, L, 1)
+    n = hb.conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, hb.BF16)
+    out = []
+    for ws in (torch.empty(max(n, 256), dtype=torch.uint8, device="cuda"), None):
+        dX = torch.full((Nb, B, Ci, L), float("nan"), dtype=torch.bfloat16, device="cuda")
+        hb.conv1x1_bwd(B, Nb, Ci, Co, L, hb.BF16, None, None, W, dY, strides(Co), dX, strides(Ci), None, None, ws)
+        out.append(dX)
+    assert torch.equal(*out)
+    wt = W[0].float().t().contiguous()
+    ref = wt @ dY[0, 0].float()
+    assert float((out[0][0, 0].float() - ref).norm() / ref.norm()) <= 2.0 ** -8            # one rounding to bf16
