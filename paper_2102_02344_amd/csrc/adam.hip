@@ -169,7 +169,10 @@ __device__ __forceinline__ void adam_locate(const AdamMultiArgs& p, int64_t i, i
 // A workgroup's elements mostly lie in one model's part of one segment: that is looked up once for the workgroup; only
 // workgroups with a boundary in them look up per thread, and only groups of four across a boundary per element.  HBM-bound:
 // 27.8 M parameters 340 (element-wise) -> 147 us, 15.1 M 190 -> 78.  Arenas of whole groups keep the kernel above: 268 M
-// parameters 1450 us there, 1477 here (1640 with the loads ahead of the lookup).
+// parameters 1450 us there, 1477 here (1640 with the loads ahead of the lookup).  Small arenas are bound by the chain of two
+// lookups and keep it too, element by element: 4 and 30 segments, element-wise and here in us, 50 k parameters 6.5 7.5 and
+// 8.1 10.7, 400 k 7.2 8.5 and 8.4 10.8, 800 k 10.8 9.5 and 12.2 12.1, 1.5 M 16.2 11.4 and 18.4 14.4.
+constexpr int64_t ADAM_ODD_MIN = 3 << 18;
 template <typename G>
 __global__ __launch_bounds__(256, 8) void adam_multi_odd_kernel(AdamMultiArgs p) {
   extern __shared__ float bc[];                   // [B][2]
@@ -243,24 +246,25 @@ extern "C" int hfta_adam_step_multi(int B, int nseg, const int64_t* seg_offsets,
   }
   for (int j = nseg + 1; j <= HFTA_ADAM_MAX_SEGMENTS; ++j) a.off[j] = seg_offsets[nseg];
   auto al = [](const void* q, size_t k) { return reinterpret_cast<uintptr_t>(q) % k == 0; };
-  const bool v4 = al(theta, 16) && al(m, 16) && al(v, 16) && al(grad, grad_dtype == HFTA_BF16 ? 8 : 16) &&
+  const bool aligned = al(theta, 16) && al(m, 16) && al(v, 16) && al(grad, grad_dtype == HFTA_BF16 ? 8 : 16) &&
                   (!theta_lowp || al(theta_lowp, 8));
   a.theta = theta; a.grad = grad; a.m = m; a.v = v; a.lowp = (bf16_raw*)theta_lowp;
   a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.eps = eps; a.wd = weight_decay;
   a.total = (int64_t)B * seg_offsets[nseg];
   a.B = B; a.nseg = nseg; a.t = step_t; a.decoupled = decoupled_wd ? 1 : 0;
-  const int64_t per_block = v4 ? 1024 : 256;
+  const bool v4 = aligned && all4, odd = aligned && !all4 && a.total >= ADAM_ODD_MIN;
+  const int64_t per_block = v4 || odd ? 1024 : 256;
   const int64_t blocks = (a.total + per_block - 1) / per_block;
   if (blocks > 0x7fffffffLL) return HFTA_EINVAL;
   const size_t shm = (size_t)B * 2 * sizeof(float);
   hipStream_t st = as_stream(stream);
   dim3 grid((unsigned)blocks);
   if (grad_dtype == HFTA_BF16) {
-    if (v4 && !all4) hipLaunchKernelGGL(adam_multi_odd_kernel<bf16_raw>, grid, dim3(256), shm, st, a);
+    if (odd) hipLaunchKernelGGL(adam_multi_odd_kernel<bf16_raw>, grid, dim3(256), shm, st, a);
     else if (v4) hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, true>), grid, dim3(256), shm, st, a);
     else hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, false>), grid, dim3(256), shm, st, a);
   } else {
-    if (v4 && !all4) hipLaunchKernelGGL(adam_multi_odd_kernel<float>, grid, dim3(256), shm, st, a);
+    if (odd) hipLaunchKernelGGL(adam_multi_odd_kernel<float>, grid, dim3(256), shm, st, a);
     else if (v4) hipLaunchKernelGGL((adam_multi_kernel<float, true>), grid, dim3(256), shm, st, a);
     else hipLaunchKernelGGL((adam_multi_kernel<float, false>), grid, dim3(256), shm, st, a);
   }

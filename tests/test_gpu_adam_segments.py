@@ -41,3 +41,11 @@ def test_segments_of_any_length(B, sizes, shift, gdtype):
         check(host(M_)[s], a[2].reshape(-1), 1e-5, f"m {j}")
         check(host(V_)[s], a[3].reshape(-1), 1e-5, f"v {j}")
     assert torch.equal(LP, TH.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("gdtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,sizes", [(3, (9, 262144, 50, 977, 1)), (5, (2, 157283, 1, 1)), (2, (4096, 393215, 30)), (256, (3073,)),
+                                     (3, (262144 - 4, 1, 3)), (3, (262144 - 8, 1, 6))])
+def test_large_arenas_of_odd_segments(B, sizes, gdtype):
+    """The same from 786432 elements on, where they are taken in groups of four; the last two lie on either side."""
+    test_segments_of_any_length(B, sizes, 0, gdtype)
