@@ -326,10 +326,19 @@ int hfta_conv1x1_bn_pool_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, co
   BnPoolFwdArgs a{Z, V, idx, gamma, beta, running_mean, running_var, save_mean, save_invstd,
                   zs[0], zs[1], zs[2], vs[0], vs[1], vs[2], Nb, Co, L, act, eps, momentum, act_slope};
   if (Y) {                       // the activated tensor is wanted too: statistics, then one pass for both
+    const bool pieces = bn_vec4_ok(Z, zs, L, dtype) && bn_vec4_ok(Y, ys, L, dtype);
+    // Rows of partial pieces take that in two passes, and small ones are better off with one launch less, BatchNorm's own kernel
+    // and the maximum: that, and here, in us: 64 channels on 2 x 4 x 129 points 13.8 15.4, 128 on 2 x 8 x 257 17.0 18.1, 256 on
+    // 1 x 16 x 333 29.8 28.4, 2048 on 1 x 2 x 333 33.1 33.5, on 6 x 4 x 513 170 151, on 6 x 16 x 2499 3298 2654.
+    if (!pieces && (int64_t)B * Nb * Co * L < (int64_t)1 << 20) {
+      const int rc = hfta_conv1x1_bn_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, gamma, beta, eps, momentum, running_mean, running_var,
+                                         save_mean, save_invstd, Z, zs, Y, ys, act, act_slope, workspace, ws_bytes, stream);
+      return rc != HFTA_OK ? rc : hfta_maxpool_points(B, Nb, Co, L, dtype, Y, ys, V, idx, vs, stream);
+    }
     int rc = hfta_conv1x1_bn_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, gamma, beta, eps, momentum, running_mean, running_var,
                                  save_mean, save_invstd, Z, zs, nullptr, nullptr, act, act_slope, workspace, ws_bytes, stream);
     if (rc != HFTA_OK) return rc;
-    if (bn_vec4_ok(Z, zs, L, dtype) && bn_vec4_ok(Y, ys, L, dtype)) {
+    if (pieces) {
       const int64_t rows = (int64_t)B * Nb * Co;
       const dim3 grid((unsigned)((rows + 3) / 4));
       if (dtype == HFTA_BF16)

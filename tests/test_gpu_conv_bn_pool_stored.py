@@ -53,7 +53,7 @@ def call(hb, dims, dtype, ins, o, act, slope, ws):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("dims", [(2, 3, 64, 130, 1300), (1, 2, 136, 520, 260), (2, 2, 16, 24, 131), (1, 1, 8, 9, 3)])
+@pytest.mark.parametrize("dims", [(2, 3, 64, 130, 1300), (1, 2, 136, 520, 260), (2, 2, 16, 24, 131), (1, 1, 8, 9, 3), (2, 8, 64, 130, 510), (1, 16, 72, 256, 333)])
 def test_stored(hb, dtype, dims):
     B, Nb, Ci, Co, L = dims
     ins = setup(*dims, dtype)
