@@ -33,7 +33,8 @@ namespace hfta {
 
 namespace {
 
-constexpr int F32_BK = 32;                                 // floats of k per tile: a whole 128-byte line of a k-contiguous row
+// floats of k per tile: of the split a whole 128-byte line of a k-contiguous row; of the fp32 instruction half of one
+constexpr int f32_bk(bool split) { return split ? 32 : 16; }
 constexpr uint32_t F32_TINY = (27u << 24) - 1;             // 2 * bits - 1 of 2^-100: smaller (but zero) is not split
 constexpr int F32_SMALL_TILES = 512;                       // fewer 128x128 tiles than this: 64x64 tiles
 typedef uint32_t pf_u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -90,11 +91,11 @@ __device__ __forceinline__ void split4(const float4& v, uint2 (&o)[3], SplitSeen
     seen.chk = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(f32s_bf16x2, i ? o[2].y : o[2].x), ones, seen.chk, false);
 }
 
-template <bool KC, int NB, int VEC> struct F32Operand;
+template <bool KC, int NB, int VEC, int BK> struct F32Operand;
 
 // k-contiguous: thread t stages 4-float group t % PR of rows t / PR + h * RPI
-template <int NB, int VEC> struct F32Operand<true, NB, VEC> {
-  static constexpr int BK = F32_BK, PR = BK / 4, RPI = GEMM_THREADS / PR, H = 64 * NB / RPI;
+template <int NB, int VEC, int BK> struct F32Operand<true, NB, VEC, BK> {
+  static constexpr int PR = BK / 4, RPI = GEMM_THREADS / PR, H = 64 * NB / RPI;
   static constexpr int PITCH = BK * 4 + 16;                // fp32 tile: [row][BK k + 4 pad]
   static constexpr int BYTES = 64 * NB * PITCH;
   static constexpr int PLANE = 64 * NB * BK * 2;           // bf16 plane: [row][BK k], 16-byte pieces permuted
@@ -161,8 +162,8 @@ template <int NB, int VEC> struct F32Operand<true, NB, VEC> {
 };
 
 // m/n-contiguous: natural [k][column] layout; thread t stages columns 4 (t % CG) .. of k-rows t / CG + h * RS
-template <int NB, int VEC> struct F32Operand<false, NB, VEC> {
-  static constexpr int BK = F32_BK, COLS = 64 * NB;
+template <int NB, int VEC, int BK> struct F32Operand<false, NB, VEC, BK> {
+  static constexpr int COLS = 64 * NB;
   static constexpr int PITCH = (COLS + 8) * 4;             // fp32 tile: k-rows four apart are 32 banks apart
   static constexpr int BYTES = BK * PITCH;
   static constexpr int PLANE = BK * COLS * 2;              // bf16 plane: [k][column], 16-byte pieces permuted
@@ -251,9 +252,9 @@ constexpr int f32_smem_bytes(int tiles) {
 // rows: four threads a row, one loop for sum and maximum, one for the squares about the mean.
 template <bool A_KC, bool B_KC, int NB, int VEC, bool SPLIT, bool POOL = false>
 __global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f32_kernel(GemmArgs p) {
-  typedef F32Operand<A_KC, NB, VEC> OA;
-  typedef F32Operand<B_KC, NB, VEC> OB;
-  constexpr int T = 64 * NB, BK = F32_BK;
+  constexpr int T = 64 * NB, BK = f32_bk(SPLIT);
+  typedef F32Operand<A_KC, NB, VEC, BK> OA;
+  typedef F32Operand<B_KC, NB, VEC, BK> OB;
   constexpr int PF = NB == 2 && SPLIT ? 1 : 2;             // k-tiles in flight in registers = LDS buffers
   constexpr int EXACT = PF * (OA::BYTES + OB::BYTES), PLANES = SPLIT ? PF * 3 * (OA::PLANE + OB::PLANE) : 0;
   __shared__ __attribute__((aligned(16))) unsigned char smem[f32_smem_bytes<NB>(PLANES > EXACT ? PLANES : EXACT)];
@@ -557,9 +558,6 @@ int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
   const int T = small ? 64 : 128;
   a.tiles_m = (d.M + T - 1) / T;
   a.tiles_n = (d.N + T - 1) / T;
-  a.tiles_per_seg = (d.K + F32_BK - 1) / F32_BK;
-  a.total_tiles = d.S * a.tiles_per_seg;
-  dim3 grid((unsigned)(a.tiles_m * a.tiles_n), 1, (unsigned)(G * a.splits));
   const bool vec = d.K >= 4 && (d.a_kc || d.M >= 4) && (d.b_kc || d.N >= 4);
   const bool whole = vec && (d.a_kc ? d.K : d.M) % 4 == 0 && (d.b_kc ? d.K : d.N) % 4 == 0;   // no piece straddles a row's end
   // (64x64 tiles: a pass over so small an output costs less than the epilogue, 2 x 4 x 256 points 188.5 us a step, 191.8 with)
@@ -567,12 +565,29 @@ int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
     a.pool_part = d.pool_part;
     a.pool_gamma = d.pool_gamma;
   }
-  // Small tiles under at most 64 k are bound by their tensors and better off with the fp32 instruction's four
-  // workgroups per compute unit than with the split's three (64 -> 64 on 4 x 32 x 2500 points: 45 us, split 53).
-  if (small && (int64_t)d.K * d.S <= 64)
-    return whole ? f32_layout<1, 2, false>(d, a, grid, st) : vec ? f32_layout<1, 1, false>(d, a, grid, st) : f32_layout<1, 0, false>(d, a, grid, st);
-  if (small) return whole ? f32_layout<1, 2, true>(d, a, grid, st) : vec ? f32_layout<1, 1, true>(d, a, grid, st) : f32_layout<1, 0, false>(d, a, grid, st);
-  return whole ? f32_layout<2, 2, true>(d, a, grid, st) : vec ? f32_layout<2, 1, true>(d, a, grid, st) : f32_layout<2, 0, false>(d, a, grid, st);
+  // The fp32 instruction, with its shorter k-tiles, takes
+  //   single elements, loaded one by one whether they exist or not: forward of 3 -> 64 channels on 4 x 32 x 2500 points 25 us, 36
+  //     with 32-k tiles;
+  //   small tiles under at most 64 k a workgroup, which are bound by their tensors and better off with its four workgroups per
+  //     compute unit than with the split's three (64 -> 64 on 4 x 32 x 2500: 45 us, split 53), and under up to 136 k where pieces
+  //     straddle rows' ends (weight gradient of 64 -> 64 on 1 x 8 x 333 10.4 us, split 11.6, on 1 x 2 x 257 9.4, 10.0; forward of
+  //     70 -> 90 on 3 x 13 x 1023 15.9, 17.6);
+  //   rows (of a reduction over samples: their parts) that leave half of their last 32-k tile empty, while that tile is the
+  //     first, in small tiles also the second (forward of 8 -> 128 and 16 -> 256 on 4 x 32 x 2500 37 us, split 46, and 86, 106;
+  //     weight gradient of 64 -> 128 on 2 x 16 x 12, 4 x 64 x 7 and 2 x 64 x 48 points 9.9, 11.6, 10.5, 14.3 and 11.1, 12.0).
+  const int64_t k_wg = ((int64_t)d.K * d.S + a.splits - 1) / a.splits;
+  const bool exact = !vec || (small && k_wg <= (whole ? 64 : 136)) ||
+                     (d.K <= (small ? 48 : 16) && (d.K - 1) % 32 < 16 && !a.pool_part);
+  const int BK = f32_bk(!exact);
+  a.tiles_per_seg = (d.K + BK - 1) / BK;
+  a.total_tiles = d.S * a.tiles_per_seg;
+  dim3 grid((unsigned)(a.tiles_m * a.tiles_n), 1, (unsigned)(G * a.splits));
+  if (exact) {
+    if (small) return whole ? f32_layout<1, 2, false>(d, a, grid, st) : vec ? f32_layout<1, 1, false>(d, a, grid, st) : f32_layout<1, 0, false>(d, a, grid, st);
+    return whole ? f32_layout<2, 2, false>(d, a, grid, st) : vec ? f32_layout<2, 1, false>(d, a, grid, st) : f32_layout<2, 0, false>(d, a, grid, st);
+  }
+  if (small) return whole ? f32_layout<1, 2, true>(d, a, grid, st) : f32_layout<1, 1, true>(d, a, grid, st);
+  return whole ? f32_layout<2, 2, true>(d, a, grid, st) : f32_layout<2, 1, true>(d, a, grid, st);
 }
 
 }  // namespace hfta

@@ -58,6 +58,11 @@ def check(name, got, ref, mag, K, units=None):
     (1, 1, 65, 33, 4),           # one k past two tiles; a row of one piece
     (2, 2, 64, 64, 100),         # a reduction the fp32 instruction keeps
     (1, 2, 3, 70, 130),          # too few elements for a piece
+    (1, 3, 201, 150, 333),       # straddling pieces in small tiles, enough k a workgroup for the split
+    (1, 40, 22, 26, 1029),       # the same for the weight gradient
+    (2, 20, 16, 130, 1500),      # 128 x 128 tiles of at most 16 k: the fp32 instruction's
+    (2, 20, 14, 130, 1501),      # and with pieces that straddle
+    (2, 5, 40, 48, 44),          # small tiles whose second k-tile is half empty
 ])
 def test_products(hb, B, Nb, Ci, Co, L):
     r = np.random.default_rng(L)
@@ -99,3 +104,23 @@ def test_values_without_a_split(hb, B, Nb, Ci, Co, L, what):
             assert not np.isnan(got).any()                     # products beyond fp32 may go either way at its edge
             continue
         check(n, got, ref, mag, K, max(K, 8))                  # the fp32 instruction's bound
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L", [(1, 2, 128, 256, 256), (1, 1, 4096, 256, 256), (8, 2, 1024, 1024, 2500)])
+def test_sums_of_one_sign(hb, B, Nb, Ci, Co, L):
+    """Positive values throughout: partial sums grow with k, and an accumulation that rounds one way would be off by K / 16 half
+    units.  One rounding to nearest per 16 k of partial sums up to the result, taken as independent, is 2^-24 sqrt(K / 16) at
+    most in the 2-norm, and one unit more for the rest.  (The last weight gradient is one sum of 5000 products.)"""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Ci)
+    X, W, dY = (torch.rand(s, generator=g, device="cuda") for s in ((Nb, B, Ci, L), (B, Co, Ci), (Nb, B, Co, L)))
+    Y, dX, dW = torch.empty_like(dY), torch.empty_like(X), torch.empty_like(W)
+    ws = torch.empty(hb.conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, 0) + 256, dtype=torch.uint8, device="cuda")
+    xs, ys = conv_strides(B, Ci, L), conv_strides(B, Co, L)
+    hb.conv1x1_fwd(B, Nb, Ci, Co, L, 0, X, xs, W, None, Y, ys)
+    hb.conv1x1_bwd(B, Nb, Ci, Co, L, 0, X, xs, W, dY, ys, dX, xs, dW, None, workspace=ws)
+    x, w, d = X[:, B - 1].double(), W[B - 1].double(), dY[:, B - 1].double()
+    ref_w = sum(d[n] @ x[n].t().contiguous() for n in range(Nb))
+    for got, ref, K in ((Y[0, B - 1], w @ x[0], Ci), (dX[0, B - 1], w.t().contiguous() @ d[0], Co), (dW[B - 1], ref_w, Nb * L)):
+        err = float((got.double() - ref).norm() / ref.norm())
+        assert err <= U * (1 + (K / 16) ** 0.5), (K, err)
