@@ -39,6 +39,7 @@ class Tracer:
                      "adam_step_multi", "linear_fwd", "linear_fwd_ws", "linear_bwd", "bn_fwd_maxpool", "bn_bwd_maxpool",
                      "act_fwd", "act_bwd", "act_bwd_colsum", "add", "layernorm_fwd", "add_layernorm_fwd", "layernorm_bwd", "layernorm_bwd_sums",
                      "conv2d_grouped_fwd", "conv2d_grouped_bwd", "bias_act_nchw", "conv1x1_bn_maxpool_fwd",
+                     "conv1x1_bn_pool_fwd", "conv1x1_fwd_sample_bias", "maxpool_points_bwd_add",
                      "add_sample_bias", "sum_points", "add_strided", "softmax_xent_points",
                      "attention_fwd", "attention_bwd", "embedding_fwd", "embedding_bwd", "softmax_xent", "softmax_xent_rows",
                      "point_transform_fwd", "point_transform_bwd",
@@ -96,6 +97,15 @@ def kernel_label(name, a):
         if dt == 1 and Ci % 8 == 0 and L >= 4 and ((Ci <= 128 and Co >= 64) or (Ci <= 256 and Co >= 512)):
             return "conv1x1_bn_fwd: conv1x1_stream_kernel(+statistics) + bn_stats_part_kernel (+ bn_apply_conv_kernel)"
         return "conv1x1_bn_fwd: conv1x1 kernel (batched GEMM, + statistics in its 256x256 form; K <= 4: vector kernel) + BatchNorm kernels"
+    if name == "conv1x1_bn_pool_fwd":
+        B, Nb, Ci, Co, L, dt = a[:6]
+        if a[20] is not None and L % 4 == 0:      # the activated tensor is stored too
+            return "conv1x1_bn_pool_fwd: conv1x1 kernel + statistics kernel + bn_apply_maxpool_kernel"
+        if a[20] is not None:
+            return "conv1x1_bn_pool_fwd: conv1x1 kernel + BatchNorm kernels + maxpool_fwd_kernel"
+        if dt == 0 and ((Co + 127) // 128) * ((L + 127) // 128) * B * Nb >= 512 and min(Co, L) > 64:
+            return "conv1x1_bn_pool_fwd: gemm_f32_kernel(+sums and maxima) + bn_pool_parts_kernel"
+        return "conv1x1_bn_pool_fwd: conv1x1 kernel + bn_fwd_maxpool_kernel"
     if name == "conv1x1_bn_prenorm_fwd":     # the same kernels as the plain call, the input normalised on load
         return "conv1x1_bn_fwd: conv1x1_stream_kernel(+statistics) + bn_stats_part_kernel (+ bn_apply_conv_kernel)"
     if name == "conv1x1_bn_prenorm_bwd":
@@ -105,6 +115,9 @@ def kernel_label(name, a):
         if dt == 1 and Ci <= 128 and Co <= 128 and L >= 4:
             return "conv1x1_bn_bwd: bn_bwd_conv_coef_kernel or bn_bwd_coef_sums_kernel + cbb_kernel + cbb_reduce_kernel"
         return "conv1x1_bn_bwd: bn_bwd_conv_kernel + conv1x1 backward kernels"
+    if name == "conv1x1_fwd_sample_bias":
+        B, Nb, Ci, Co, L, dt = a[:6]
+        return (big_name(B * Nb, Co, L) if dt == 1 and big_gemm(B * Nb, Co, L, Ci) else small_gemm(dt)) + "(fwd, a bias per sample)"
     if name == "conv1x1_fwd":
         B, Nb, Ci, Co, L, dt = a[:6]
         if dt == 1 and Ci <= 4 and L % 4 == 0:
@@ -145,6 +158,8 @@ def kernel_label(name, a):
         return name + "_kernel"
     if name == "softmax_xent_rows":
         return "xent_rows_kernel"
+    if name == "point_transform_fwd" and a[5] == 1 and a[2] <= 4 and a[3] <= 256 and a[4] % 4 == 0:
+        return "conv1x1_tinyk_kernel(weights per cloud)"
     if name in ("point_transform_fwd", "point_transform_bwd"):
         return name + ": batched GEMM per (model, cloud)"
     if name in ("add_sample_bias", "add_strided"):
@@ -193,8 +208,10 @@ def kernel_label(name, a):
     if name in ("conv1x1_bn_maxpool_bwd", "conv1x1_bn_maxpool_prenorm_bwd"):
         saved = a[13] if name == "conv1x1_bn_maxpool_bwd" else a[17]
         return "conv1x1_bn_maxpool_bwd: cbp_dx_kernel + 5 small" + ("" if saved is not None else " + gram_kernel")
+    if name == "adam_step_multi":
+        return "adam_multi_odd_kernel" if any(o % 4 for o in a[1]) and a[0] * a[1][-1] >= 3 << 18 else "adam_multi_kernel"
     return {"maxpool_points": "maxpool_fwd_kernel", "maxpool_points_bwd": "maxpool_bwd_kernel",
-            "adam_step_multi": "adam_multi_kernel"}[name]
+            "maxpool_points_bwd_add": "maxpool_bwd_add_kernel"}[name]
 
 
 def small_gemm(dt):
@@ -243,7 +260,7 @@ def algorithmic_flops(name, a):
             return 0.0
         both = name == "linear_bwd" and a[8] is not None and a[9] is not None
         return (4.0 if both else 2.0) * B * M * Fx * Fy
-    if name in ("conv1x1_fwd", "conv1x1_bwd", "conv1x1_bn_fwd"):
+    if name in ("conv1x1_fwd", "conv1x1_bwd", "conv1x1_bn_fwd", "conv1x1_bn_pool_fwd", "conv1x1_fwd_sample_bias"):
         B, Nb, Ci, Co, L = a[:5]
         return 2.0 * B * Nb * Ci * Co * L
     if name in ("conv1x1_bn_bwd", "conv1x1_bn_prenorm_bwd"):       # weight gradient, and the data gradient if asked for
@@ -287,6 +304,16 @@ def algorithmic_bytes(name, a):
     if name == "conv1x1_fwd":
         B, Nb, Ci, Co, L, dt = a[:6]
         return (B * Nb * (Ci + Co) * L + B * Co * (Ci + 1)) * _es(dt)
+    if name == "conv1x1_fwd_sample_bias":          # x, W and a bias per sample in, y out
+        B, Nb, Ci, Co, L, dt = a[:6]
+        return (B * Nb * ((Ci + Co) * L + Co) + B * Co * Ci) * _es(dt)
+    if name == "conv1x1_bn_pool_fwd":      # x and W in, z out, z in and y out if y is asked for; the pooled values and where they are
+        B, Nb, Ci, Co, L, dt = a[:6]
+        return ((B * Nb * (Ci + (3 if a[20] is not None else 1) * Co) * L + B * Co * (Ci + 1)) * _es(dt)
+                + B * Nb * Co * (_es(dt) + 4))
+    if name == "maxpool_points_bwd_add":   # pooled gradient and index in, one element per row read and written
+        B, Nb, C, L, dt = a[:5]
+        return B * Nb * C * (3 * _es(dt) + 4)
     if name in ("conv1x1_bn_fwd", "conv1x1_bn_prenorm_fwd"):       # x and W in, z out; z in, y out (if y is asked for)
         B, Nb, Ci, Co, L, dt = a[:6]
         y = a[20] if name == "conv1x1_bn_fwd" else a[26]
