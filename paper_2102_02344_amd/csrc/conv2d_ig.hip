@@ -477,9 +477,10 @@ __global__ __launch_bounds__(256) void ig_split_finish_kernel(const float* __res
   *reinterpret_cast<uint4*>(out + i) = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
 }
 
-// k split of the forward kernel: taken when the tiles alone leave most compute units with a single
-// workgroup and the reduction is long (the 8x8 layers: 320 tiles, 4096 k: 101 -> 90 us when it was measured).  With
-// 640 tiles and more, and for the class-pair data gradient, the split measured no gain or a loss.
+// k split of the forward kernel: taken when the tiles alone leave most compute units with a single workgroup and the
+// reduction is long.  512 <- 256 channels at 8x8, unsplit and split in us: 36 tiles 53 21, 96 53 30, 192 53 47, 320 67 71 (the
+// bound predates the present kernel; it stays, since another split is another order of the sums).  With 640 tiles and more, and
+// for the class-pair data gradient, the split measured no gain or a loss.
 int ig_pick_ksplit(int64_t blocks, int ktiles) {
   if (blocks >= 384 || ktiles < 64) return 1;
   return ktiles >= 128 ? 4 : 2;

@@ -10,7 +10,9 @@
 //   weight gradient: the 8 k of a fragment are neighbouring output pixels of one tap (ky, kx), i.e. every other pixel of an
 //     image row.  Rows are kept as four planes, plane kx holding the pixels 2x + kx - 1: one aligned 16-byte read (two of
 //     8 bytes where a row has four output pixels); a piece of 8 pixels is written four times, 8 bytes each.
-// Order and operands of the matrix instructions are those of the gathering kernels (k ascending), so results keep their bits.
+// Order and operands of the matrix instructions are those of the gathering kernels (k ascending), so results keep their bits
+// where k is not split.  A split cuts at multiples of 64 k instead of 32, elsewhere than before unless the channels are a
+// multiple of four times the splits.
 // 10 models x 64 images, forward: 256 <- 128 channels at 8x8 80 -> 58 us, 128 <- 64 at 16x16 and 512 <- 256 at 4x4 (split over
 // k) 85 -> 72 on average, 64 <- 3 40 -> 36; weight gradients of the same layers 75 -> 68, 88 -> 81,
 // 70 -> 64 and 46 -> 38 (with k-tiles of 64 and two workgroups per compute unit 73, 83, 67 and 46).  3 models x 20 images:

@@ -4,9 +4,10 @@
 // sixteen times the work per cycle, and an fp32 value IS the sum of three bf16 ones: h, the value rounded, m, the rest
 // rounded, l, what is left (8 + 8 + 8 bits).  Six of the nine products of two such sums are formed (hh, hm, mh, hl, mm,
 // lh; the others are below 2^-26 of the product), in fp32 accumulators, for 6/16 of the fp32 instruction's time.
-// The corrections have accumulators of their own: the bf16 instruction truncates its sum, and in one accumulator six
-// truncations per 16 k of a long weight gradient left a larger error (1.5e-6) than the fp32 instruction's roundings
-// (1.3e-6); in two it is 4.4e-7.  Measured for 128 -> 1024 channels on 4 x 32 x 2500 points, in the step: data gradient
+// The corrections have accumulators of their own: the bf16 instruction rounds its sum (to nearest: sums of positive values
+// are off by 3.0e-7 at K = 4096 and 1.7e-6 at 80000, their signed mean by 5e-9 and 6e-7, where the fp32 instruction, which
+// rounds every two k, leaves 8.5e-7 and 4.7e-6, 5e-9 and 1.7e-6), and in one accumulator six roundings per 16 k of a long weight gradient left a
+// larger error (1.5e-6) than the fp32 instruction's (1.3e-6); in two it is 4.4e-7.  Measured for 128 -> 1024 channels on 4 x 32 x 2500 points, in the step: data gradient
 // 696 -> 520 us, weight gradient 693 -> 499, forward 815 -> 782 (four k-tiles a tile: bound by a tile's first loads and
 // its stores); relative errors against float64 5.7e-7 -> 1.9e-7, 1.3e-6 -> 4.4e-7, 2.0e-7 -> 6.5e-8.  On 2 x 4 x 256
 // points the data gradient's 64 workgroups take 27 us instead of 39.
@@ -15,7 +16,8 @@
 // The sum of three needs a finite value that is not tiny: an infinity or a NaN has no remainder, nor has what rounds up
 // to infinity, and below 2^-110 the last part falls under bf16's smallest numbers.  Both are noticed while splitting
 // (the remainder is NaN; a smallest magnitude is kept), and a workgroup that has seen one takes its tile again from the
-// start with fp32 matrix instructions (`exact_loop`).  Operands with fewer than four elements along their contiguous
+// start with fp32 matrix instructions (`exact_loop`): one value between 0 and 2^-100 in every tile of the layer above makes it
+// 1287 us forward, 1198 and 1197 backward, where the fp32 instruction alone took 803, 688 and 704.  Operands with fewer than four elements along their contiguous
 // dimension (VEC = 0, single-element loads) have that loop only.
 //
 // Every load is a raw buffer load without control flow (out of range = zeros, see gemm_pf.h), in 16-byte pieces whatever
