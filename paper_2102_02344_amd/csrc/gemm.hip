@@ -246,10 +246,7 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   int rc;
   // bf16 problems whose operands can be fetched in whole 8/16-byte pieces take the deep-prefetch
   // kernel (branch-free buffer loads, several k-tiles in flight).
-  // Its 16-byte loads want eight elements in a row of an operand that is not made of whole aligned 16-byte pieces; rows of
-  // four go to the element-aligned kernel, which is 0-15 % slower on them (136 -> 256 channels on 8 x 256 x 4 points 41.4 us
-  // with two 8-byte loads, 47.4 now; Linear 4 x 4096 x 256 -> 4 8.2, 9.3; 12 -> 4 channels on 8 x 32 x 2500 29.3, 32.6).
-  const bool pf = (v16 || v8) && (d.a_kc ? v16 || d.K >= 8 : d.M >= 8) && (d.b_kc ? v16 || d.K >= 8 : d.N >= 8);
+  const bool pf = v16 || v8;
   if (d.dtype == HFTA_F32) {
     rc = gemm_f32_launch(d, a, st);
     if (rc == HFTA_EUNSUPPORTED) rc = launch_layout<float>(d, a, grid, st);

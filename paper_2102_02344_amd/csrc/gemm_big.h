@@ -125,7 +125,7 @@ template <bool V16> struct BigOpKc {
     const bool ok = k + (V16 ? 8 : 4) <= K;
     uint32_t kb = (uint32_t)k0 * 2u;
     if constexpr (!V16) {
-      q.half = ok && k + 8 > K;
+      q.half = q.early = ok && k + 8 > K;
       kb -= q.half ? 8u : 0u;                              // K is at least 256: rows out of range stay out of range
     }
 #pragma unroll
@@ -160,7 +160,7 @@ template <bool N16> struct BigOpNt {
   }
   __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
     const int kr = (int)(threadIdx.x >> 5);
-    if constexpr (!N16) q.half = half;
+    if constexpr (!N16) q.half = q.early = half;
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       const bool ok = k0 + kr + 16 * h < K;

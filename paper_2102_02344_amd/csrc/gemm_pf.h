@@ -28,13 +28,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pf_rsrc(const void* p, uint32_
 
 // 16-byte pieces of rows.  Rows whose length or alignment are multiples of 8 bytes only (2500 points) load them too: a
 // multi-dword access needs 4-byte alignment.  The piece that has four of its eight elements in the row is read four elements
-// early (rows hold at least eight), so that nothing past the row is touched, and is moved into place on its way into LDS.
+// early, so that nothing past the row is touched, and is moved into place on its way into LDS.  (A row of four elements has
+// nothing before it: it is read in place, and what comes from behind it, out of range after the slice's last row, is dropped;
+// on the element-aligned kernel 136 -> 256 channels on 8 x 256 x 4 points took 47.4 us forward for 38.9.)
 // Against two 8-byte loads (6 x 16 x 2500 points): weight gradients of 128 -> 512, 128 -> 256 and 64 -> 128 channels 155 ->
 // 135, 91 -> 82 and 30 -> 27 us, products with both operands along the points 83 -> 76, with one 55 -> 51.
 template <int H> struct RowHalves {
   uint4 v[H];
-  bool half;
-  __device__ __forceinline__ uint4 operator[](int h) const { return half ? make_uint4(v[h].z, v[h].w, 0u, 0u) : v[h]; }
+  bool half, early;                                        // four elements only; read four early
+  __device__ __forceinline__ uint4 operator[](int h) const {
+    return make_uint4(early ? v[h].z : v[h].x, early ? v[h].w : v[h].y, half ? 0u : v[h].z, half ? 0u : v[h].w);
+  }
 };
 template <int H> struct RowWhole {
   uint4 v[H];
@@ -63,7 +67,8 @@ template <bool V16> struct PfOperand<true, V16> {   // k-contiguous: rows t/4 an
     uint32_t kb = (uint32_t)k0 * 2u;
     if constexpr (!V16) {
       q.half = ok && k + 8 > K;
-      kb -= q.half ? 8u : 0u;                              // rows out of range stay out of range
+      q.early = q.half && k > 0;
+      kb -= q.early ? 8u : 0u;                             // rows out of range stay out of range
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -87,16 +92,17 @@ template <bool N16> struct PfOperandNt {
   typedef typename std::conditional<N16, RowWhole<2>, RowHalves<2>>::type Regs;
   uint32_t off;
   uint32_t ldb;
-  bool half;
+  bool half, early;
   __device__ __forceinline__ void init(int col0, int cols, int64_t ld, int t) {
     ldb = (uint32_t)(ld * 2);
     const int c = col0 + (t & 15) * 8, kr = t >> 4;
     half = !N16 && c + 4 <= cols && c + 8 > cols;
-    off = c + 8 <= cols || half ? (uint32_t)kr * ldb + (uint32_t)c * 2u - (half ? 8u : 0u) : PF_OOB;
+    early = half && c > 0;
+    off = c + 8 <= cols || half ? (uint32_t)kr * ldb + (uint32_t)c * 2u - (early ? 8u : 0u) : PF_OOB;
   }
   __device__ __forceinline__ void load(Regs& q, __amdgpu_buffer_rsrc_t rs, int k0, int K) const {
     const int kr = (int)(threadIdx.x >> 4);
-    if constexpr (!N16) q.half = half;
+    if constexpr (!N16) { q.half = half; q.early = early; }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const bool ok = k0 + kr + 16 * h < K;

@@ -52,9 +52,10 @@ def test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad):
 
 
 @pytest.mark.parametrize("B,Nb,Ci,Co,L,pad", [(2, 5, 12, 20, 4, 4), (1, 3, 4, 36, 12, 0), (3, 7, 64, 132, 132, 4), (2, 3, 136, 4, 1028, 4),
-                                              (1, 9, 100, 260, 260, 8)])
+                                              (1, 9, 100, 260, 260, 8), (1, 2, 4, 4, 4, 0), (2, 9, 4, 20, 4, 12), (2, 40, 136, 132, 4, 4)])
 def test_forward_and_gradients_of_small_layers(hb, B, Nb, Ci, Co, L, pad):
-    """The same for the 128x128 kernel: fewer than eight elements in a row of an operand among them."""
+    """The same for the 128x128 kernel, with four elements in a row of an operand among them: those are read in place, with
+    what follows them (NaN here, or past the slice's end) dropped."""
     test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad)
 
 
