@@ -209,7 +209,9 @@ def kernel_label(name, a):
         saved = a[13] if name == "conv1x1_bn_maxpool_bwd" else a[17]
         return "conv1x1_bn_maxpool_bwd: cbp_dx_kernel + 5 small" + ("" if saved is not None else " + gram_kernel")
     if name == "adam_step_multi":
-        return "adam_multi_odd_kernel" if any(o % 4 for o in a[1]) and a[0] * a[1][-1] >= 3 << 18 else "adam_multi_kernel"
+        B, off = a[0], a[1]
+        fours = B * off[-1] >= (14 << 16) + (0 if B > 128 else min(768 * B * (len(off) - 1), 18 << 16))
+        return "adam_multi_odd_kernel" if fours and any(o % 4 for o in off) else "adam_multi_kernel"
     return {"maxpool_points": "maxpool_fwd_kernel", "maxpool_points_bwd": "maxpool_bwd_kernel",
             "maxpool_points_bwd_add": "maxpool_bwd_add_kernel"}[name]
 

@@ -7,6 +7,7 @@
 // through LDS.  Each thread updates four consecutive parameters with 16-byte
 // accesses.  HBM-bound: reads theta, g, m, v and writes theta, m, v (+ the bf16
 // copy the GEMMs read).
+#include <algorithm>
 #include "common.h"
 
 using namespace hfta;
@@ -170,9 +171,15 @@ __device__ __forceinline__ void adam_locate(const AdamMultiArgs& p, int64_t i, i
 // workgroups with a boundary in them look up per thread, and only groups of four across a boundary per element.  HBM-bound:
 // 27.8 M parameters 340 (element-wise) -> 147 us, 15.1 M 190 -> 78.  Arenas of whole groups keep the kernel above: 268 M
 // parameters 1450 us there, 1477 here (1640 with the loads ahead of the lookup).  Small arenas are bound by the chain of two
-// lookups and keep it too, element by element: 4 and 30 segments, element-wise and here in us, 50 k parameters 6.5 7.5 and
-// 8.1 10.7, 400 k 7.2 8.5 and 8.4 10.8, 800 k 10.8 9.5 and 12.2 12.1, 1.5 M 16.2 11.4 and 18.4 14.4.
-constexpr int64_t ADAM_ODD_MIN = 3 << 18;
+// lookups, of many parts (a model's share of a segment) by their boundaries, and keep the kernel above too, element by element.
+// Element-wise and here, in us: parts of similar length, 1 part, 600 k parameters 8.5 7.2, 64 parts 600 k 9.7 9.9, 1.0 M 13.1
+// 11.3, 240 parts 800 k 12.4 13.4, 1.2 M 15.8 14.9, 960 parts 1.0 M 14.7 17.2, 1.3 M 16.8 17.3, 2.0 M 23.6 18.5, 9600 parts
+// 1.3 M 18.5 21.2, 2.0 M 25.2 24.6; lengths over all magnitudes, 36 parts 727 k 10.7 12.3, 63 parts 914 k 12.7 14.4, 156 parts
+// 1.0 M 13.7 14.8.  More than 128 models cost the element-wise kernel's workgroups their bias corrections: 256 models, 30
+// segments 700 k 15.6 15.9, 1.0 M 20.5 17.8.
+int64_t adam_odd_min(int B, int nseg) {
+  return (14 << 16) + (B > 128 ? 0 : std::min((int64_t)B * nseg * 768, (int64_t)18 << 16));
+}
 template <typename G>
 __global__ __launch_bounds__(256, 8) void adam_multi_odd_kernel(AdamMultiArgs p) {
   extern __shared__ float bc[];                   // [B][2]
@@ -252,7 +259,7 @@ extern "C" int hfta_adam_step_multi(int B, int nseg, const int64_t* seg_offsets,
   a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.eps = eps; a.wd = weight_decay;
   a.total = (int64_t)B * seg_offsets[nseg];
   a.B = B; a.nseg = nseg; a.t = step_t; a.decoupled = decoupled_wd ? 1 : 0;
-  const bool v4 = aligned && all4, odd = aligned && !all4 && a.total >= ADAM_ODD_MIN;
+  const bool v4 = aligned && all4, odd = aligned && !all4 && a.total >= adam_odd_min(B, nseg);
   const int64_t per_block = v4 || odd ? 1024 : 256;
   const int64_t blocks = (a.total + per_block - 1) / per_block;
   if (blocks > 0x7fffffffLL) return HFTA_EINVAL;

@@ -44,8 +44,9 @@ def test_segments_of_any_length(B, sizes, shift, gdtype):
 
 
 @pytest.mark.parametrize("gdtype", ["f32", "bf16"])
-@pytest.mark.parametrize("B,sizes", [(3, (9, 262144, 50, 977, 1)), (5, (2, 157283, 1, 1)), (2, (4096, 393215, 30)), (256, (3073,)),
-                                     (3, (262144 - 4, 1, 3)), (3, (262144 - 8, 1, 6))])
+@pytest.mark.parametrize("B,sizes", [(3, (9, 320000, 50, 977, 1)), (5, (2, 187283, 1, 1)), (2, (4096, 463215, 30)), (256, (3585,)),
+                                     (3, (308130, 1, 8)), (3, (308130, 1, 7)), (40, (31, 33000, 2, 3))])
 def test_large_arenas_of_odd_segments(B, sizes, gdtype):
-    """The same from 786432 elements on, where they are taken in groups of four; the last two lie on either side."""
+    """The same in arenas large enough to be taken in groups of four (from 917504 elements and 768 more per part on, of more
+    than 128 models from 917504); the two of 308130 lie on either side."""
     test_segments_of_any_length(B, sizes, 0, gdtype)
