@@ -23,6 +23,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 int gemm_f32_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st);
+int gemm_ring_launch(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st);
 int gemm_big_launch(const GemmDesc& d, const GemmArgs& a, bool v16, bool n16, dim3 grid, hipStream_t st);
 
 static inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -235,7 +236,9 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
       b.tiles_per_seg = (d.K + 63) / 64;
       b.total_tiles = d.S * b.tiles_per_seg;
       dim3 grid((unsigned)(b.tiles_m * b.tiles_n), 1, (unsigned)(G * splits));
-      const int rc = gemm_big_launch(d, b, v16 || !(d.a_kc || d.b_kc), n16, grid, st);
+      int rc = HFTA_EUNSUPPORTED;
+      if ((v16 || !(d.a_kc || d.b_kc)) && n16 && !(d.bsum && d.bsum_done && splits == 1)) rc = gemm_ring_launch(d, b, grid, st);
+      if (rc == HFTA_EUNSUPPORTED) rc = gemm_big_launch(d, b, v16 || !(d.a_kc || d.b_kc), n16, grid, st);
       if (rc == HFTA_OK && splits > 1 && !d.keep_partials) return reduce_partials(d, G, splits, st);
       if (rc != HFTA_EUNSUPPORTED) return rc;
     }

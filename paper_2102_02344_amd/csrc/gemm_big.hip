@@ -16,7 +16,7 @@ static void launch_big(const GemmArgs& a, bool n16, dim3 grid, hipStream_t st) {
 // Persistent form: as many workgroups as compute units (a multiple of 8, one per XCD slot), each
 // walking several output tiles.  Taken when a launch has more tiles than that, the epilogue is the
 // select kind, every operand loads in 16-byte pieces, and output rows take whole 16-byte stores.
-static int persistent_blocks() {
+int persistent_blocks() {
   static const int n = [] {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)

@@ -1,0 +1,40 @@
+"""The 256x256 products on a ring of LDS slots, at the sizes where the ring, the tile walk and the epilogue can go wrong: a second
+round of workgroups, one column past a tile, k that ends inside a k-tile, the shortest reduction, split reductions, output
+rows of 8-byte alignment, batches that do not divide among the XCDs."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_ops import f32_tol
+from util import DT, TOL, check, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2102_02344_amd import binding
+    return binding
+
+
+@pytest.mark.parametrize("B,M,Fx,Fy,relu", [(50, 300, 264, 520, True), (65, 257, 256, 776, False), (200, 448, 520, 192, False),
+                                            (97, 320, 260, 256, False), (33, 768, 256, 520, True), (4, 4104, 512, 264, False)])
+def test_linear(hb, B, M, Fx, Fy, relu):
+    print(f"ring products B={B} M={M} Fx={Fx} Fy={Fy}", flush=True)
+    gen = torch.Generator().manual_seed(11)
+    dt = DT["bf16"]
+    r = lambda *s: torch.randn(s, generator=gen).bfloat16()
+    X, W, b, dY = r(B, M, Fx), (r(B, Fx, Fy).float() / np.sqrt(Fx)).bfloat16(), r(B, Fy), r(B, M, Fy)
+    Xd, Wd, bd, dYd = X.cuda(), W.cuda(), b.cuda(), dY.cuda()
+    x, w, dy = X.double(), W.double(), dY.double()
+    ws = torch.empty(max(hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, dt), 4), dtype=torch.uint8, device="cuda")
+    Y = torch.full((B, M, Fy), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hb.linear_fwd(B, M, Fx, Fy, dt, Xd, Wd, bd, Y, act=hb.ACT_RELU if relu else hb.ACT_NONE)
+    y = torch.matmul(x, w) + b.double()[:, None, :]
+    check(host(Y), (y.clamp(min=0) if relu else y).numpy(), TOL["bf16"], "Y")
+    dX = torch.full((B, M, Fx), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hb.linear_bwd(B, M, Fx, Fy, dt, None, Wd, dYd, dX, None, None, ws)
+    check(host(dX), torch.matmul(dy, w.transpose(1, 2).contiguous()).numpy(), TOL["bf16"], "dX")
+    dW = torch.full((B, Fx, Fy), float("nan"), device="cuda")
+    hb.linear_bwd(B, M, Fx, Fy, dt, Xd, None, dYd, None, dW, None, ws)
+    check(host(dW), torch.matmul(x.transpose(1, 2).contiguous(), dy).numpy(), f32_tol("bf16"), "dW")
