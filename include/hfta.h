@@ -425,6 +425,25 @@ int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype,
                         void* dX, const int64_t dxs[4], float* dgamma, float* dbeta, float* dx_sum,
                         int act, float act_slope, void* stream);
 
+/* The same layer in fp32 as a pair of calls between which the convolution's [Nb][B*Co][L] output is not stored.
+ * Forward: V, idx, the statistics and the running estimates are those of hfta_conv1x1_bn_pool_fwd without Y, bit for bit where the
+ * maximum is not clipped; zhit fp32 [B][Nb][Co] = the convolution's output at idx (for a row that a ReLU clips as a whole, whose
+ * gradient is zero, at any of its points).  Backward: dX, dW, dgamma, dbeta as hfta_bn_bwd_maxpool followed by hfta_conv1x1_bwd
+ * give them, up to fp32 rounding; dbias (or NULL) exactly zero.  act: NONE, RELU, or LEAKY with slope >= 0.
+ * hfta_conv1x1_bn_maxpool_f32_workspace_bytes: what either direction needs (256-byte aligned), 0 for shapes the pair is not built
+ * for (64 < Ci <= 128 in multiples of four, 64 < Co <= 1024, 128 <= L < 2^21, at least 512 tiles of 128 points). */
+size_t hfta_conv1x1_bn_maxpool_f32_workspace_bytes(int B, int Nb, int Ci, int Co, int L);
+int hfta_conv1x1_bn_maxpool_f32_fwd(int B, int Nb, int Ci, int Co, int L, const float* X, const int64_t xs[4], const float* W,
+                                    const float* bias, const float* gamma, const float* beta, float eps, float momentum,
+                                    float* running_mean, float* running_var, float* save_mean, float* save_invstd, float* V,
+                                    int32_t* idx, const int64_t vs[3], float* zhit, int act, float act_slope, void* workspace,
+                                    size_t ws_bytes, void* stream);
+int hfta_conv1x1_bn_maxpool_f32_bwd(int B, int Nb, int Ci, int Co, int L, const float* X, const int64_t xs[4], const float* W,
+                                    const float* bias, const float* zhit, const float* dV, const int32_t* idx, const int64_t vs[3],
+                                    const float* gamma, const float* beta, const float* save_mean, const float* save_invstd,
+                                    float* dX, const int64_t dxs[4], float* dW, float* dbias, float* dgamma, float* dbeta, int act,
+                                    float act_slope, void* workspace, size_t ws_bytes, void* stream);
+
 /* ------------------------------------------------------------------------
  * The last per-point layer of a point-cloud model as ONE operator, forward and backward
  * (fusion rules table rows "Conv1d" and "BatchNorm1d", the element-wise rows, then the max over

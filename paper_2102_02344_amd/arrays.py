@@ -255,7 +255,13 @@ class FusedPointNetCls(ParamArena):
             geo = (B, Nb, spec.conv[-2], spec.conv[-1], L, self.dt)
             self.fused_tail_ws = hb.conv1x1_bn_maxpool_workspace_bytes(*geo)
             self.fused_tail = self.fused_tail_ws > 0 and _on_16_bytes(self.w(f"conv{self.nconv - 1}.w"))
-        nz = self.nconv - 1 if self.fused_tail else self.nconv
+        # In fp32 the same pair of calls without the layer's output in memory; a step that shows a probe every operator's
+        # tensors stores it, in buffers made for that.
+        self.tail_f32_ws = 0
+        if fused_tail and not self.fused_tail and self.dt == hb.F32 and self.nconv >= 2 and \
+                self.w(f"conv{self.nconv - 1}.w").data_ptr() % 8 == 0:
+            self.tail_f32_ws = hb.conv1x1_bn_maxpool_f32_workspace_bytes(B, Nb, spec.conv[-2], spec.conv[-1], L)
+        nz = self.nconv - 1 if self.fused_tail or self.tail_f32_ws else self.nconv
         self.z = [torch.empty(Nb, B * c, L, **act) for c in spec.conv[1:1 + nz]]
         # prenorm[i]: layer i takes layer i-1's stored pre-activation and normalises it on load (forward and
         # backward), so the activated tensor a[i-1] between the two is never stored.  The layer in front of the
@@ -280,8 +286,9 @@ class FusedPointNetCls(ParamArena):
         Cp = spec.conv[-1]
         self.pooled = torch.empty(B, Nb, Cp, **act)
         self.pool_idx = torch.empty(B, Nb, Cp, dtype=torch.int32, device=self.dev)
-        if self.fused_tail:
+        if self.fused_tail or self.tail_f32_ws:
             self.zhit = torch.empty(B, Nb, Cp, **f32)
+        if self.fused_tail:
             self.tail_moments = torch.empty(hb.conv1x1_bn_maxpool_saved_floats(B, spec.conv[-2], Cp), **f32)
         self.fz = [torch.empty(B, Nb, f, **act) for f in spec.fc[1:]]
         self.fh = [torch.empty(B, Nb, f, **act) for f in spec.fc[1:-1]]
@@ -313,7 +320,7 @@ class FusedPointNetCls(ParamArena):
         if not self.fused_tail:
             self.fused_tail_ws = 0
             ws = max(ws, hb.conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, spec.conv[-2], spec.conv[-1], L, self.dt))
-        ws = max(ws, self.fused_tail_ws)
+        ws = max(ws, self.fused_tail_ws, self.tail_f32_ws)
         self.ws = torch.empty(ws, dtype=torch.uint8, device=self.dev)
 
         # ---- inputs -----------------------------------------------------------------
@@ -339,6 +346,14 @@ class FusedPointNetCls(ParamArena):
                         self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"], t, cs, hb.ACT_RELU)
         return t
 
+    def _store_tail(self):
+        """Buffers for the last per-point layer's output and its gradient, in a step that stores them all the same."""
+        s, B, Nb, L = self.spec, self.B, self.Nb, self.L
+        if len(self.z) < self.nconv:
+            act = dict(dtype=self.tdt, device=self.dev)
+            self.z.append(torch.empty(Nb, B * s.conv[-1], L, **act))
+            self.dbuf = [torch.empty(Nb * B * max(s.conv[1:]) * L, **act) for _ in range(2)]
+
     def forward_backward(self, probe=None):
         """One forward + backward pass.  ``probe(op, **tensors)``, if given, is called after
         every library call with the tensors that call read and wrote (tests use it to check
@@ -346,6 +361,9 @@ class FusedPointNetCls(ParamArena):
         s, B, Nb, L, dt = self.spec, self.B, self.Nb, self.L, self.dt
         eps, mom = self.BN_EPS, self.BN_MOMENTUM
         P = probe
+        tail_f32 = self.tail_f32_ws > 0 and P is None
+        if self.tail_f32_ws > 0 and P is not None:
+            self._store_tail()
         # per-point MLP
         x, ci = self.points, s.conv[0]
         for i in range(self.nconv):
@@ -401,6 +419,14 @@ class FusedPointNetCls(ParamArena):
                       y=self._act(i), mean=self.saved[k + ".bn.mean"], invstd=self.saved[k + ".bn.invstd"])
                 x, ci = y, co
                 continue
+            if tail_f32:
+                hb.conv1x1_bn_maxpool_f32_fwd(B, Nb, ci, co, L, x, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"),
+                                              self.master(k + ".bn.g"), self.master(k + ".bn.b"), eps, mom,
+                                              self.running[k + ".bn.rm"], self.running[k + ".bn.rv"], self.saved[k + ".bn.mean"],
+                                              self.saved[k + ".bn.invstd"], self.pooled, self.pool_idx, (Nb * co, co, 1),
+                                              self.zhit, hb.ACT_RELU, 0.0, self.ws)
+                ci = co
+                break
             # last per-point layer: convolution, BatchNorm + ReLU + max over points in one call; the
             # activated [Nb, B*C, L] tensor is never written
             hb.conv1x1_bn_pool_fwd(B, Nb, ci, co, L, dt, x, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"),
@@ -529,6 +555,14 @@ class FusedPointNetCls(ParamArena):
                 da = dxin
                 continue
             xin = self.points if i == 0 else self.a[i - 1]
+            if i == self.nconv - 1 and tail_f32:
+                da = self._cut(self.dbuf[cur], Nb * B * ci * L)
+                hb.conv1x1_bn_maxpool_f32_bwd(B, Nb, ci, co, L, xin, _cs(B, ci, L), self.w(k + ".w"), self.w(k + ".b"), self.zhit,
+                                              dpool, self.pool_idx, (Nb * co, co, 1), self.master(k + ".bn.g"),
+                                              self.master(k + ".bn.b"), self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"],
+                                              da, _cs(B, ci, L), self.g(k + ".w"), self.g(k + ".b"), self.g(k + ".bn.g"),
+                                              self.g(k + ".bn.b"), hb.ACT_RELU, 0.0, self.ws)
+                continue
             if i < self.nconv - 1 and (i in self.unfused or self.one_pass[i]):
                 # BatchNorm backward + convolution backward in one call: dz stays on chip.  The data
                 # gradient goes to the other buffer (dY is still being read while it is written).

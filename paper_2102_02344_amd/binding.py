@@ -83,6 +83,9 @@ _SIGS = {
     "hfta_conv1x1_bn_pool_fwd": (_i, [_i] * 6 + [_p, _s4, _p, _p, _p, _p, _f, _f, _p, _p, _p, _p, _p, _s4, _p, _s4, _p, _p, _s4,
                                       _i, _f, _p, _sz, _p]),
     "hfta_bn_bwd_maxpool": (_i, [_i, _i, _i, _i, _i, _p, _s4, _p, _p, _s4, _p, _p, _p, _p, _p, _s4, _p, _p, _p, _i, _f, _p]),
+    "hfta_conv1x1_bn_maxpool_f32_workspace_bytes": (_sz, [_i] * 5),
+    "hfta_conv1x1_bn_maxpool_f32_fwd": (_i, [_i] * 5 + [_p, _s4, _p, _p, _p, _p, _f, _f] + [_p] * 6 + [_s4, _p, _i, _f, _p, _sz, _p]),
+    "hfta_conv1x1_bn_maxpool_f32_bwd": (_i, [_i] * 5 + [_p, _s4] + [_p] * 5 + [_s4] + [_p] * 5 + [_s4] + [_p] * 4 + [_i, _f, _p, _sz, _p]),
     "hfta_conv1x1_bn_maxpool_bwd_workspace_bytes": (_sz, [_i] * 6),
     "hfta_conv1x1_bn_maxpool_bwd": (_i, [_i] * 6 + [_p] * 21 + [_i, _f, _p, _sz, _p]),
     "hfta_conv1x1_bn_maxpool_prenorm_fwd": (_i, [_i] * 6 + [_p] * 6 + [_i, _f] + [_p] * 4 + [_f, _f] + [_p] * 9 + [_i, _f, _p, _s4, _p, _sz, _p]),
@@ -406,6 +409,29 @@ def bn_bwd_maxpool(B, Nb, C_, L, dtype, X, xs, dV, idx, vs, gamma, beta, save_me
                                     _strides(vs, 3), _ptr(gamma), _ptr(beta), _ptr(save_mean), _ptr(save_invstd),
                                     _ptr(dX), _strides(dxs), _ptr(dgamma), _ptr(dbeta), _ptr(dx_sum), act,
                                     act_slope, _stream(stream)), "hfta_bn_bwd_maxpool")
+
+
+def conv1x1_bn_maxpool_f32_workspace_bytes(B, Nb, Ci, Co, L) -> int:
+    return _lib.hfta_conv1x1_bn_maxpool_f32_workspace_bytes(B, Nb, Ci, Co, L)
+
+
+def conv1x1_bn_maxpool_f32_fwd(B, Nb, Ci, Co, L, X, xs, W, bias, gamma, beta, eps, momentum, running_mean, running_var, save_mean,
+                               save_invstd, V, idx, vs, zhit, act=ACT_NONE, act_slope=0.0, workspace=None, stream=None):
+    wp, wb = _ws(workspace)
+    _check(_lib.hfta_conv1x1_bn_maxpool_f32_fwd(B, Nb, Ci, Co, L, _ptr(X), _strides(xs), _ptr(W), _ptr(bias), _ptr(gamma), _ptr(beta),
+                                                eps, momentum, _ptr(running_mean), _ptr(running_var), _ptr(save_mean),
+                                                _ptr(save_invstd), _ptr(V), _ptr(idx), _strides(vs, 3), _ptr(zhit), act, act_slope,
+                                                wp, wb, _stream(stream)), "hfta_conv1x1_bn_maxpool_f32_fwd")
+
+
+def conv1x1_bn_maxpool_f32_bwd(B, Nb, Ci, Co, L, X, xs, W, bias, zhit, dV, idx, vs, gamma, beta, save_mean, save_invstd, dX, dxs, dW,
+                               dbias, dgamma, dbeta, act=ACT_NONE, act_slope=0.0, workspace=None, stream=None):
+    wp, wb = _ws(workspace)
+    _check(_lib.hfta_conv1x1_bn_maxpool_f32_bwd(B, Nb, Ci, Co, L, _ptr(X), _strides(xs), _ptr(W), _ptr(bias), _ptr(zhit), _ptr(dV),
+                                                _ptr(idx), _strides(vs, 3), _ptr(gamma), _ptr(beta), _ptr(save_mean),
+                                                _ptr(save_invstd), _ptr(dX), _strides(dxs), _ptr(dW), _ptr(dbias), _ptr(dgamma),
+                                                _ptr(dbeta), act, act_slope, wp, wb, _stream(stream)),
+           "hfta_conv1x1_bn_maxpool_f32_bwd")
 
 
 def conv1x1_bn_maxpool_bwd_workspace_bytes(B, Nb, Ci, Co, L, dtype) -> int:

@@ -162,8 +162,12 @@ __global__ __launch_bounds__(256) void bn_apply_maxpool_kernel(BnPoolFwdArgs p, 
 // maximum; a row whose activated values are all equal (clipped, or gamma = 0) or no numbers has its maximum at point 0.  The 1.3 GB of z
 // are not read (4 x 32 x 2500 points, 1024 channels: bn_fwd_maxpool_kernel 402 us, this 23 and the epilogue 122 more).
 // 16 channels a workgroup: 16 lanes read 256 contiguous bytes of a part, 64 parts in flight.
+// p.X == nullptr: z was not stored.  Then z at point 0, where it is asked for, is the product again, from `at0`; and the z that
+// was pooled goes to at0.zhit, [B][Nb][C], for the backward.
+struct PoolAt0 { const float* x; const float* w; const float* bias; int64_t xsb, xsn, xsc; int Ci; float* zhit; };
 constexpr int PP_C = 16, PP_P = 64;
-__global__ __launch_bounds__(PP_C * PP_P) void bn_pool_parts_kernel(BnPoolFwdArgs p, const float4* __restrict__ part, int tiles, int cols) {
+__global__ __launch_bounds__(PP_C * PP_P) void bn_pool_parts_kernel(BnPoolFwdArgs p, const float4* __restrict__ part, int tiles, int cols,
+                                                                    PoolAt0 at0) {
   __shared__ double red[PP_P][PP_C][2];
   const int cl = threadIdx.x % PP_C, pl = threadIdx.x / PP_C;
   const int c = blockIdx.x * PP_C + cl, b = blockIdx.y, k = b * p.C + c;
@@ -211,14 +215,27 @@ __global__ __launch_bounds__(PP_C * PP_P) void bn_pool_parts_kernel(BnPoolFwdArg
       const float4 v = pp[(int64_t)(n * tiles + q) * p.C];
       if (v.z > best || at == 0x7fffffff) { best = v.z; at = __float_as_int(v.w); }
     }
-    float pre = fmaf(g, ((g < 0.f ? -best : best) - mean) * invstd, bt);
+    float z = g < 0.f ? -best : best;
+    float pre = fmaf(g, (z - mean) * invstd, bt);
     const bool clipped = clips && !(pre > 0.f);
     if (g == 0.f || clipped || pre != pre) {
       at = 0;
-      const float z0 = reinterpret_cast<const float*>(p.X)[b * p.xsb + n * p.xsn + c * p.xsc];
-      pre = fmaf(g, (z0 - mean) * invstd, bt);
-      if (clipped && pre > 0.f) pre = 0.f;                 // the row's maximum was not positive
+      if (p.X) {
+        z = reinterpret_cast<const float*>(p.X)[b * p.xsb + n * p.xsn + c * p.xsc];
+        pre = fmaf(g, (z - mean) * invstd, bt);
+        if (clipped && pre > 0.f) pre = 0.f;               // the row's maximum was not positive
+      } else if (clipped && pre == pre) {
+        pre = 0.f;                                         // its gradient is zero: any z of the row will do for the backward
+      } else {
+        const float* x = at0.x + b * at0.xsb + n * at0.xsn;
+        const float* w = at0.w + (int64_t)k * at0.Ci;
+        z = at0.bias ? at0.bias[k] : 0.f;
+        for (int i = 0; i < at0.Ci; ++i) z = fmaf(w[i], x[i * at0.xsc], z);
+        pre = fmaf(g, (z - mean) * invstd, bt);
+        if (clipped && pre > 0.f) pre = 0.f;
+      }
     }
+    if (at0.zhit) at0.zhit[((int64_t)b * p.Nb + n) * p.C + c] = z;
     const int64_t o = b * p.vsb + n * p.vsn + c * p.vsc;
     reinterpret_cast<float*>(p.V)[o] = apply_act(pre, p.act, p.slope);
     p.idx[o] = at;
@@ -359,7 +376,7 @@ int hfta_conv1x1_bn_pool_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, co
     if (rc != HFTA_OK) return rc;
     if (cols > 0) {
       hipLaunchKernelGGL(bn_pool_parts_kernel, dim3((unsigned)((Co + PP_C - 1) / PP_C), (unsigned)B), dim3(PP_C * PP_P), 0, st, a,
-                         (const float4*)workspace, (L + cols - 1) / cols, cols);
+                         (const float4*)workspace, (L + cols - 1) / cols, cols, PoolAt0{});
       return launch_status();
     }
   } else {
@@ -368,6 +385,36 @@ int hfta_conv1x1_bn_pool_fwd(int B, int Nb, int Ci, int Co, int L, int dtype, co
   }
   return hfta_bn_fwd_maxpool(B, Nb, Co, L, dtype, Z, zs, gamma, beta, eps, momentum, running_mean, running_var, save_mean,
                              save_invstd, V, idx, vs, act, act_slope, stream);
+}
+
+// The same in fp32 without Z (backward: conv_pool_f32.hip)
+int hfta_conv1x1_bn_maxpool_f32_fwd(int B, int Nb, int Ci, int Co, int L, const float* X, const int64_t xs[4], const float* W,
+                                    const float* bias, const float* gamma, const float* beta, float eps, float momentum,
+                                    float* running_mean, float* running_var, float* save_mean, float* save_invstd, float* V,
+                                    int32_t* idx, const int64_t vs[3], float* zhit, int act, float act_slope, void* workspace,
+                                    size_t ws_bytes, void* stream) {
+  if (B <= 0 || Nb <= 0 || Ci <= 0 || Co <= 0 || L <= 0 || !X || !xs || !W || !gamma || !beta || !save_mean || !save_invstd || !V ||
+      !idx || !vs || !zhit || !(eps >= 0.f))
+    return HFTA_EINVAL;
+  if ((running_mean == nullptr) != (running_var == nullptr)) return HFTA_EINVAL;
+  if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || (act == HFTA_ACT_LEAKY && act_slope >= 0.f))) return HFTA_EUNSUPPORTED;
+  const size_t need = hfta_conv1x1_bn_maxpool_f32_workspace_bytes(B, Nb, Ci, Co, L);
+  if (xs[3] != 1 || need == 0) return HFTA_EUNSUPPORTED;
+  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 != 0 ||
+      ws_bytes < need)
+    return HFTA_EWORKSPACE;
+  hipStream_t st = as_stream(stream);
+  BnPoolFwdArgs a{nullptr, V, idx, gamma, beta, running_mean, running_var, save_mean, save_invstd,
+                  0, 0, 0, vs[0], vs[1], vs[2], Nb, Co, L, act, eps, momentum, act_slope};
+  const int64_t zs[4] = {(int64_t)Co * L, (int64_t)B * Co * L, L, 1};
+  int cols = 0;
+  const int rc = conv1x1_fwd_pool_part(B, Nb, Ci, Co, L, X, xs, W, bias, nullptr, zs, gamma, (float4*)workspace, &cols, st);
+  if (rc != HFTA_OK) return rc;
+  if (cols <= 0) return HFTA_EUNSUPPORTED;
+  hipLaunchKernelGGL(bn_pool_parts_kernel, dim3((unsigned)((Co + PP_C - 1) / PP_C), (unsigned)B), dim3(PP_C * PP_P), 0, st, a,
+                     (const float4*)workspace, (L + cols - 1) / cols, cols,
+                     PoolAt0{X, W, bias, xs[0], xs[1], xs[2], Ci, zhit});
+  return launch_status();
 }
 
 int hfta_bn_fwd_maxpool(int B, int Nb, int C, int L, int dtype, const void* X, const int64_t xs[4], const float* gamma,

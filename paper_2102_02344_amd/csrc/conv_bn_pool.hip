@@ -18,6 +18,7 @@
 #include "gemm_pf.h"
 #include "bn_common.h"
 #include "in_norm.h"
+#include "hit_sort.h"
 
 using namespace hfta;
 
@@ -260,47 +261,8 @@ int gram_launch(int B, int Nb, int Ci, int L, const void* X, const int64_t xs[4]
 // ---- two things that only wait for the coefficients, in one launch (15 us each on their own, few workgroups both;
 // ---- together 17 on 8 x 32 x 1024): the sorted argmax positions, and G
 constexpr int PREP_WAVES = 16, PREP_THREADS = PREP_WAVES * 64;
+static_assert(PREP_THREADS == HIT_THREADS, "a key per thread");
 struct GwShared { float red[PREP_WAVES][16][64]; float vred[PREP_WAVES][32]; };
-
-// Argmax positions of one (model, sample) sorted by point, ties in channel order: key = point << 10 | channel (Co <= 1024,
-// L < 2^21: checked on the host); bitonic, a key per thread, exchanged by shuffles inside a wavefront and through LDS
-// across (10 of the 55 exchanges, where a barrier each took 15 us).
-// toff[tile] = first sorted position whose point lies in 128-point tile `tile` or later.
-__device__ void sort_hits(const CbpArgs& p, uint32_t (&sh)[2][PREP_THREADS], int P, int tiles, int n, int b) {
-  const int t = threadIdx.x;
-  uint32_t key = 0xffffffffu;
-  if (t < p.Co) {
-    const int hit = min(max(p.idx[b * p.vsb + n * p.vsn + t * p.vsc], 0), p.L - 1);
-    key = ((uint32_t)hit << 10) | (uint32_t)t;
-  }
-  int buf = 0;
-  for (int k = 2; k <= P; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      uint32_t o;
-      if (j < 64) {
-        o = (uint32_t)__shfl_xor((int)key, j, 64);
-      } else {                                               // the other buffer was last read before the last barrier
-        sh[buf][t] = key;
-        __syncthreads();
-        o = sh[buf][t ^ j];
-        buf ^= 1;
-      }
-      key = ((t & j) == 0) == ((t & k) == 0) ? min(key, o) : max(key, o);
-    }
-  sh[buf][t] = key;
-  __syncthreads();
-  const int64_t base = ((int64_t)b * p.Nb + n) * p.Co;
-  if (t < p.Co) {
-    p.skey[base + t] = key;
-    p.sval[base + t] = p.s[base + (key & 1023u)];
-  }
-  int* toff = p.toff + ((int64_t)b * p.Nb + n) * (tiles + 1);
-  for (int k = t; k <= p.Co; k += PREP_THREADS) {
-    const int cur = k < p.Co ? (int)(sh[buf][k] >> 17) : tiles;
-    const int prev = k > 0 ? (int)(sh[buf][k - 1] >> 17) : -1;
-    for (int tl = prev + 1; tl <= cur; ++tl) toff[tl] = k;
-  }
-}
 
 // G = sum_c p1[c] W[c,:]^T W[c,:] (stored negated, bf16) and v = sum_c p0[c] W[c,:]: one workgroup per 32 x 32 tile of G
 // and model, fp32 matrix instructions (the operands are exact in fp32); the wavefronts take a share of the channels each
@@ -366,8 +328,12 @@ __device__ void gram_w(const CbpArgs& p, GwShared& sh, int tile, int b) {
 __global__ __launch_bounds__(PREP_THREADS) void cbp_prep_kernel(CbpArgs p, int P, int tiles) {
   __shared__ union { uint32_t key[2][PREP_THREADS]; GwShared g; } sh;
   const int id = (int)blockIdx.x - p.B * p.Nb;
-  if (id < 0) sort_hits(p, sh.key, P, tiles, (int)blockIdx.x % p.Nb, (int)blockIdx.x / p.Nb);
-  else gram_w(p, sh.g, id / p.B, id % p.B);
+  if (id < 0) {
+    const int n = (int)blockIdx.x % p.Nb, b = (int)blockIdx.x / p.Nb;
+    const int64_t row = (int64_t)b * p.Nb + n;
+    sort_hits(p.idx + b * p.vsb + n * p.vsn, p.vsc, p.s + row * p.Co, p.skey + row * p.Co, p.sval + row * p.Co, p.toff + row * (tiles + 1),
+              p.Co, p.L, sh.key, P, tiles);
+  } else gram_w(p, sh.g, id / p.B, id % p.B);
 }
 
 // ---- dX tile = -(G x) - v + argmax columns.  Also emits, for the weight gradient, the input

@@ -66,7 +66,15 @@ struct GemmDesc {
   // kernel launched writes them, 0 otherwise.
   float4* pool_part;
   const float* pool_gamma;
-  int* pool_cols;
+  int* pool_cols;                  // (C may then be nullptr: the output is not stored)
+  // fp32 k=1 convolution forms: hit_val[g][h] times row c of hit_w[g0], [hit_co][M], is added to output column l of group g, for
+  // the hits h of the group in their order; hit_key[g][h] = l << 10 | c, sorted, [G0*G1][hit_co]; hit_off[g][t] = first hit in
+  // 128-column tile t or later, [G0*G1][tiles + 1].  128x128 tiles only.
+  const uint32_t* hit_key;
+  const float* hit_val;
+  const int* hit_off;
+  const float* hit_w;
+  int hit_co;
 };
 
 struct GemmArgs {
@@ -92,6 +100,11 @@ struct GemmArgs {
   float* bsum;                   // see GemmDesc
   float4* pool_part;             // see GemmDesc
   const float* pool_gamma;
+  const uint32_t* hit_key;       // see GemmDesc
+  const float* hit_val;
+  const int* hit_off;
+  const float* hit_w;
+  int hit_co;
 };
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;

@@ -155,6 +155,7 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   a.pool_part = nullptr;
   a.pool_gamma = nullptr;
   if (d.pool_cols) *d.pool_cols = 0;
+  a.hit_key = d.hit_key; a.hit_val = d.hit_val; a.hit_off = d.hit_off; a.hit_w = d.hit_w; a.hit_co = d.hit_co;
 
   // vector-load eligibility: every address the fast path forms must be aligned
   const int es = (int)dtype_size(d.dtype);
@@ -252,7 +253,7 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   const bool pf = v16 || v8;
   if (d.dtype == HFTA_F32) {
     rc = gemm_f32_launch(d, a, st);
-    if (rc == HFTA_EUNSUPPORTED) rc = launch_layout<float>(d, a, grid, st);
+    if (rc == HFTA_EUNSUPPORTED && !(d.pool_part && !d.C) && !d.hit_key) rc = launch_layout<float>(d, a, grid, st);
   } else if (pf) {
     rc = gemm_pf_launch(d, a, v16, n16, grid, st);
   } else if (buffers_ok && d.K >= 4 && (d.a_kc || d.M >= 4) && (d.b_kc || d.N >= 4)) {

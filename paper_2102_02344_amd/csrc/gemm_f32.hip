@@ -30,6 +30,7 @@
 // 16 k each were 0-7 % slower: half a line of a k-contiguous row at a time).  NB = 1 (64x64 tile, two k-tiles each):
 // four times the workgroups, for problems that would leave compute units idle.
 #include "gemm_pf.h"
+#include "f32_split.h"
 
 namespace hfta {
 
@@ -37,7 +38,6 @@ namespace {
 
 // floats of k per tile: of the split a whole 128-byte line of a k-contiguous row; of the fp32 instruction half of one
 constexpr int f32_bk(bool split) { return split ? 32 : 16; }
-constexpr uint32_t F32_TINY = (27u << 24) - 1;             // 2 * bits - 1 of 2^-100: smaller (but zero) is not split
 constexpr int F32_SMALL_TILES = 512;                       // fewer 128x128 tiles than this: 64x64 tiles
 typedef uint32_t pf_u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -54,43 +54,6 @@ __device__ __forceinline__ float4 ld_f4(__amdgpu_buffer_rsrc_t rs, uint32_t off)
 }
 __device__ __forceinline__ float ld_f1(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
-}
-
-// Four values as three planes of four bf16.  `chk` becomes NaN if one has no finite remainder; `low` holds the smallest
-// magnitude but zero, as 2 * bits - 1 of the value itself: zero wraps to the largest, and what its first part rounds to
-// zero (below 2^-134) does not look like one.
-typedef __bf16 f32s_bf16x2 __attribute__((ext_vector_type(2)));
-struct SplitSeen {
-  float chk = 0.f;
-  uint32_t low = 0xffffffffu;
-  __device__ __forceinline__ bool bad() const { return chk != chk || low < F32_TINY; }
-};
-// the rounded pair; x and y become what it leaves (exact: a two-element dot product with -1 and 0)
-__device__ __forceinline__ uint32_t split_pair(float& x, float& y) {
-  const uint32_t w = pack_bf16x2(x, y);
-  const f32s_bf16x2 h = __builtin_bit_cast(f32s_bf16x2, w);
-  uint32_t cx, cy;
-  asm("s_mov_b32 %0, 0xbf80" : "=s"(cx));
-  asm("s_mov_b32 %0, 0xbf800000" : "=s"(cy));
-  x = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(f32s_bf16x2, cx), x, false);
-  y = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(f32s_bf16x2, cy), y, false);
-  return w;
-}
-__device__ __forceinline__ void split4(const float4& v, uint2 (&o)[3], SplitSeen& seen) {
-  float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) seen.low = min(seen.low, __float_as_uint(e[i]) * 2u - 1u);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    o[q].x = split_pair(e[0], e[1]);
-    o[q].y = split_pair(e[2], e[3]);
-  }
-  o[2].x = pack_bf16x2(e[0], e[1]);
-  o[2].y = pack_bf16x2(e[2], e[3]);
-  const f32s_bf16x2 ones = __builtin_bit_cast(f32s_bf16x2, 0x3f803f80u);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    seen.chk = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(f32s_bf16x2, i ? o[2].y : o[2].x), ones, seen.chk, false);
 }
 
 template <bool KC, int NB, int VEC, int BK> struct F32Operand;
@@ -252,7 +215,9 @@ constexpr int f32_smem_bytes(int tiles) {
 
 // POOL: the epilogue also leaves what a BatchNorm and a maximum over each row need (GemmDesc::pool_part), from the staged
 // rows: four threads a row, one loop for sum and maximum, one for the squares about the mean.
-template <bool A_KC, bool B_KC, int NB, int VEC, bool SPLIT, bool POOL = false>
+// The output itself is stored only if there is a place for it (p.C).
+// HITS: columns of the output that get rows of another matrix added (GemmDesc::hit_key), while they are staged.
+template <bool A_KC, bool B_KC, int NB, int VEC, bool SPLIT, bool POOL = false, bool HITS = false>
 __global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f32_kernel(GemmArgs p) {
   constexpr int T = 64 * NB, BK = f32_bk(SPLIT);
   typedef F32Operand<A_KC, NB, VEC, BK> OA;
@@ -448,6 +413,43 @@ __global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f
       }
     }
     __syncthreads();
+    if constexpr (HITS) {
+      // A wavefront takes a quarter of the tile's columns, a lane a row: no two touch one element, and a column's hits are
+      // added in their order.
+      static_assert(NB == 2, "64 rows, four quarters of 32 columns");
+      const int* off = p.hit_off + (int64_t)g * (p.tiles_n + 1) + tile_n;
+      const int h1 = off[1], m = m0 + pass * 64 + lane;
+      const uint32_t* key = p.hit_key + (int64_t)g * p.hit_co;
+      const float* val = p.hit_val + (int64_t)g * p.hit_co;
+      const float* W = p.hit_w + (int64_t)g0 * p.hit_co * p.M + min(m, p.M - 1);
+      constexpr int U = 8;                                 // rows of W in flight
+      for (int h0 = off[0]; h0 < h1; h0 += 64) {
+        const uint32_t kl = h0 + lane < h1 ? key[h0 + lane] : 0xffffffffu;
+        const float vl = h0 + lane < h1 ? val[h0 + lane] : 0.f;
+        unsigned long long todo = __ballot((int)((kl >> 10) - (uint32_t)n0) >> 5 == wave);
+        while (todo) {
+          uint32_t ku[U];
+          float vu[U], wu[U];
+          const int cnt = min((int)__builtin_popcountll(todo), U);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int i = todo ? __builtin_ctzll(todo) : 0;
+            todo &= todo - 1;
+            ku[u] = (uint32_t)__builtin_amdgcn_readlane((int)kl, i);
+            vu[u] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(vl), i));
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) wu[u] = u < cnt ? W[(int64_t)(ku[u] & 1023u) * p.M] : 0.f;
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (u < cnt) {
+              float* d = st + lane * SP + (int)((ku[u] >> 10) - (uint32_t)n0);
+              *d = fmaf(vu[u], wu[u], *d);
+            }
+        }
+      }
+      __syncthreads();
+    }
     constexpr int PPR = T / 4, RPI = GEMM_THREADS / PPR;   // pieces per row, rows per iteration
     const int c = t % PPR, n = n0 + c * 4;
     float cb[4] = {0.f, 0.f, 0.f, 0.f};
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(GEMM_THREADS, NB == 2 && SPLIT ? 2 : 3) void gemm_f
       for (int e = 0; e < 4; ++e) cb[e] = n + e < p.N ? bias[n + e] : 0.f;
     }
 #pragma unroll 4
-    for (int it = 0; it < 64 / RPI; ++it) {
+    for (int it = 0; it < (POOL && !p.C ? 0 : 64 / RPI); ++it) {
       const int rl = t / PPR + it * RPI, m = m0 + pass * 64 + rl;
       const float4 v = *reinterpret_cast<const float4*>(st + rl * SP + c * 4);
       float e[4] = {v.x + cb[0], v.y + cb[1], v.z + cb[2], v.w + cb[3]};
@@ -536,6 +538,10 @@ int f32_layout(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st) 
       if (rc == HFTA_OK) *d.pool_cols = 64 * NB;
       return rc;
     }
+    if (d.hit_key) {
+      hipLaunchKernelGGL((gemm_f32_kernel<true, false, NB, VEC, true, false, true>), grid, dim3(GEMM_THREADS), 0, st, a);
+      return launch_status();
+    }
   }
   if (d.a_kc && !d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, false, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
   else if (d.a_kc && d.b_kc) hipLaunchKernelGGL((gemm_f32_kernel<true, true, NB, VEC, SPLIT>), grid, dim3(GEMM_THREADS), 0, st, a);
@@ -546,6 +552,11 @@ int f32_layout(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st) 
 
 }  // namespace
 
+// whether M x N outputs of G groups are taken in 128x128 tiles
+bool gemm_f32_big_tiles(int M, int N, int64_t G) {
+  return (int64_t)((M + 127) / 128) * ((N + 127) / 128) * G >= F32_SMALL_TILES && M > 64 && N > 64;
+}
+
 // HFTA_EUNSUPPORTED: an operand slice does not fit a buffer descriptor (nothing has been launched).
 int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
   GemmArgs a = base;
@@ -555,8 +566,7 @@ int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
   a.a_extent = (uint32_t)a_ext;
   a.b_extent = (uint32_t)b_ext;
   const int64_t G = (int64_t)d.G0 * d.G1;
-  const int64_t t128 = (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * G * a.splits;
-  const bool small = t128 < F32_SMALL_TILES || d.M <= 64 || d.N <= 64;
+  const bool small = !gemm_f32_big_tiles(d.M, d.N, G * a.splits);
   const int T = small ? 64 : 128;
   a.tiles_m = (d.M + T - 1) / T;
   a.tiles_n = (d.N + T - 1) / T;
@@ -580,6 +590,9 @@ int gemm_f32_launch(const GemmDesc& d, const GemmArgs& base, hipStream_t st) {
   const int64_t k_wg = ((int64_t)d.K * d.S + a.splits - 1) / a.splits;
   const bool exact = !vec || (small && k_wg <= (whole ? 64 : 136)) ||
                      (d.K <= (small ? 48 : 16) && (d.K - 1) % 32 < 16 && !a.pool_part);
+  // what only the 128x128 tiles of the split product do
+  if (d.pool_part && !d.C && (!a.pool_part || exact)) return HFTA_EUNSUPPORTED;
+  if (d.hit_key && (small || exact || a.splits != 1 || !d.a_kc || d.b_kc || d.c_seg > 0)) return HFTA_EUNSUPPORTED;
   const int BK = f32_bk(!exact);
   a.tiles_per_seg = (d.K + BK - 1) / BK;
   a.total_tiles = d.S * a.tiles_per_seg;

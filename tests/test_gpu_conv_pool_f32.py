@@ -1,0 +1,108 @@
+"""The fp32 pair that keeps the convolution's output out of memory: the forward against hfta_conv1x1_bn_pool_fwd, bit for bit,
+the backward against float64 and against the chain of stored operators."""
+import pytest
+import torch
+
+from util import conv_strides
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2102_02344_amd import binding
+    return binding
+
+
+def reference(X, W, bias, gam, bet, idx, dV, act, slope, eps=1e-5):
+    """dX, dW, dgamma, dbeta in float64; X [Nb, B, Ci, L]."""
+    Nb, B, Ci, L = X.shape
+    Co, out = W.shape[1], ([], [], [], [])
+    for b in range(B):
+        x, w = X[:, b].double(), W[b].double()
+        z = torch.matmul(w, x) + bias[b].double()[:, None]
+        mu, iv = z.mean((0, 2))[:, None], (z.var((0, 2), unbiased=False) + eps).rsqrt()[:, None]
+        xh = (z - mu) * iv
+        g, bt = gam[b].double()[:, None], bet[b].double()[:, None]
+        ix = idx[b].long().unsqueeze(-1)
+        hit = xh.gather(2, ix)
+        pre = hit * g + bt
+        gr = dV[b].double().unsqueeze(-1) * torch.where(pre > 0, 1.0, 1.0 if act == 0 else slope if act == 2 else 0.0)
+        dbt, dg, m = gr.sum((0, 2)), (gr * hit).sum((0, 2)), Nb * L
+        dz = g * iv * (torch.zeros_like(z).scatter_(2, ix, gr) - dbt[:, None] / m - xh * dg[:, None] / m)
+        out[0].append(torch.matmul(w.t().contiguous(), dz))
+        out[1].append(sum(torch.matmul(dz[n], x[n].t().contiguous()) for n in range(Nb)))
+        out[2].append(dg)
+        out[3].append(dbt)
+    return torch.stack(out[0], 1), torch.stack(out[1]), torch.stack(out[2]), torch.stack(out[3])
+
+
+@pytest.mark.parametrize("dims,act,slope,shift", [((3, 29, 128, 1024, 1023), 1, 0.0, 0.0), ((8, 64, 68, 70, 130), 1, 0.0, 2.0),
+                                                  ((2, 32, 96, 200, 1030), 2, 0.2, 0.0), ((1, 512, 128, 65, 128), 0, 0.0, 0.0),
+                                                  ((2, 32, 100, 513, 1028), 1, 0.0, 10.0)])
+def test_pair(hb, dims, act, slope, shift):
+    B, Nb, Ci, Co, L = dims
+    print(f"fp32 tail {dims} act={act} shift={shift}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X = torch.relu(r(Nb, B, Ci, L)) + shift
+    X[:, :, :, L // 2] *= 3.0                                # a point that many channels choose: more hits than a wavefront
+    W, bias, gam, bet, dV = r(B, Co, Ci) * (2.0 / Ci) ** 0.5, 0.1 * r(B, Co), 1.0 + 0.2 * r(B, Co), 0.3 * r(B, Co), r(B, Nb, Co)
+    gam[:, ::7] *= -1.0
+    gam[0, 3], bet[0, 3], bet[0, 5] = 0.0, 0.5, -50.0        # all points equal; all points clipped
+    xs, zs, vs = conv_strides(B, Ci, L), conv_strides(B, Co, L), (Nb * Co, Co, 1)
+    need = hb.conv1x1_bn_maxpool_f32_workspace_bytes(*dims)
+    assert need > 0
+    ws = torch.empty(max(need, hb.conv1x1_bwd_workspace_bytes(*dims, 0)), dtype=torch.uint8, device="cuda")
+    e = lambda *s: torch.full(s, float("nan"), device="cuda")
+    res = []
+    for stored in (True, False):
+        o = dict(mean=e(B * Co), invstd=e(B * Co), V=e(B, Nb, Co), idx=torch.full((B, Nb, Co), -1, dtype=torch.int32, device="cuda"),
+                 rm=torch.zeros(B * Co, device="cuda"), rv=torch.ones(B * Co, device="cuda"))
+        bn = (W, bias, gam, bet, 1e-5, 0.1, o["rm"], o["rv"], o["mean"], o["invstd"])
+        dX, dW, db, dg, dbt = e(Nb, B, Ci, L), e(B, Co, Ci), e(B, Co), e(B, Co), e(B, Co)
+        if stored:
+            Z, dZ = e(Nb, B * Co, L), e(Nb, B * Co, L)
+            hb.conv1x1_bn_pool_fwd(*dims, 0, X, xs, *bn, Z, zs, None, None, o["V"], o["idx"], vs, act, slope, ws)
+            hb.bn_bwd_maxpool(B, Nb, Co, L, 0, Z, zs, dV, o["idx"], vs, gam, bet, o["mean"], o["invstd"], dZ, zs, dg, dbt, act, slope, db)
+            hb.conv1x1_bwd(*dims, 0, X, xs, W, dZ, zs, dX, xs, dW, None, ws)
+            del Z, dZ
+        else:
+            zhit = e(B, Nb, Co)
+            hb.conv1x1_bn_maxpool_f32_fwd(*dims, X, xs, *bn, o["V"], o["idx"], vs, zhit, act, slope, ws)
+            hb.conv1x1_bn_maxpool_f32_bwd(*dims, X, xs, W, bias, zhit, dV, o["idx"], vs, gam, bet, o["mean"], o["invstd"], dX, xs, dW, db,
+                                          dg, dbt, act, slope, ws)
+            assert not db.any()
+        res.append((o, (dX, dW, dg, dbt)))
+    (a, ga), (b, gb) = res
+    same = torch.ones_like(a["V"], dtype=torch.bool)
+    same[0, :, 3] = False                                    # gamma = 0: z at point 0 by another order of the sum
+    for k in a:
+        assert torch.equal(a[k][same], b[k][same]) if k == "V" else torch.equal(a[k], b[k]), k
+    assert torch.allclose(a["V"], b["V"], rtol=1e-6, atol=0)
+    # Sums of K <= 1024 products of fp32 values rounded to 2^-24 each: sqrt(K) 2^-24 = 2e-6 of their norm; and no further off
+    # than the stored chain, whose rounding of 1e-7 in what cancels is the yardstick where the mean is large.
+    for name, q, s, t in zip(("dX", "dW", "dgamma", "dbeta"), reference(X, W, bias, gam, bet, a["idx"], dV, act, slope), ga, gb):
+        err = [((v.double() - q).norm() / q.norm()).item() for v in (s, t)]
+        print(name, err)
+        assert err[1] <= 2e-6 and err[1] <= 1.05 * err[0] + 2e-8, (name, err)
+
+
+def test_refuses_and_array_route(hb):
+    assert hb.conv1x1_bn_maxpool_f32_workspace_bytes(4, 32, 128, 1024, 2500) > 0
+    for dims in ((4, 32, 64, 1024, 2500), (4, 32, 132, 1024, 2500), (4, 32, 128, 1028, 2500), (1, 4, 128, 1024, 256), (4, 32, 126, 1024, 2500),
+                 (600, 1, 128, 128, 100)):
+        assert hb.conv1x1_bn_maxpool_f32_workspace_bytes(*dims) == 0
+    import hfta_inputs as hi
+    from paper_2102_02344_amd.arrays import FusedPointNetCls
+    spec = hi.spec_c1(B=2, Nb=16, L=2050, dtype="f32")
+    inp = hi.pointnet_cls_inputs(spec)
+    lean, stored = FusedPointNetCls(spec, inp), FusedPointNetCls(spec, inp, fused_tail=False)
+    assert lean.tail_f32_ws > 0 and stored.tail_f32_ws == 0
+    lean.forward_backward()
+    stored.forward_backward()
+    assert torch.equal(lean.pooled, stored.pooled) and torch.equal(lean.loss, stored.loss)
+    for name, _ in lean.shapes:
+        if name.startswith("fc") or name.endswith(("conv4.bn.g", "conv4.w")):
+            x, y = lean.g(name).double(), stored.g(name).double()
+            assert (x - y).norm() <= 4e-6 * y.norm() + 1e-12, name
