@@ -44,7 +44,8 @@ class Tracer:
                      "attention_fwd", "attention_bwd", "embedding_fwd", "embedding_bwd", "softmax_xent", "softmax_xent_rows",
                      "point_transform_fwd", "point_transform_bwd",
                      "conv1x1_bn_maxpool_bwd", "conv1x1_bn_fwd", "conv1x1_bn_bwd", "conv1x1_bn_prenorm_fwd",
-                     "conv1x1_bn_prenorm_bwd", "conv1x1_bn_maxpool_prenorm_fwd", "conv1x1_bn_maxpool_prenorm_bwd")
+                     "conv1x1_bn_prenorm_bwd", "conv1x1_bn_maxpool_prenorm_fwd", "conv1x1_bn_maxpool_prenorm_bwd",
+                     "conv1x1_bn_maxpool_f32_fwd", "conv1x1_bn_maxpool_f32_bwd")
 
     def __init__(self, hb, torch):
         self._hb, self._torch = hb, torch
@@ -89,6 +90,10 @@ def _es(dtype):
 
 def kernel_label(name, a):
     """Kernel symbol family an entry point launches (matches the rocprofv3 kernel names)."""
+    if name == "conv1x1_bn_maxpool_f32_fwd":
+        return "conv1x1_bn_maxpool_f32_fwd: gemm_f32_kernel(+sums and maxima, not stored) + bn_pool_parts_kernel"
+    if name == "conv1x1_bn_maxpool_f32_bwd":
+        return "conv1x1_bn_maxpool_f32_bwd: gemm_f32_kernel(+hits) + pool32_moments_kernel + 4 small"
     if name in ("bn_fwd", "bn_bwd"):
         lay = "linear" if a[3] == 1 else "conv"
         return f"{name}_{lay}_kernel"
@@ -256,6 +261,9 @@ def big_splits(G, M, N, K, S=1):
 
 
 def algorithmic_flops(name, a):
+    if name in ("conv1x1_bn_maxpool_f32_fwd", "conv1x1_bn_maxpool_f32_bwd"):      # the Ci -> Co product; the two Ci x Ci ones
+        B, Nb, Ci, Co, L = a[:5]
+        return 2.0 * B * Nb * Ci * (Co if name.endswith("fwd") else 2 * Ci) * L
     if name in ("linear_fwd", "linear_fwd_ws", "linear_bwd"):
         B, M, Fx, Fy = a[:4]
         if name == "linear_bwd" and a[8] is None and a[9] is None:
@@ -291,6 +299,10 @@ def algorithmic_flops(name, a):
 
 def algorithmic_bytes(name, a):
     """Bytes that must cross HBM once: every operand in once, every result out once."""
+    if name in ("conv1x1_bn_maxpool_f32_fwd", "conv1x1_bn_maxpool_f32_bwd"):      # x (backward: and dX), W (and dW), the pooled rows
+        B, Nb, Ci, Co, L = a[:5]
+        both = 1 if name.endswith("fwd") else 2
+        return 4 * (both * (B * Nb * Ci * L + B * Co * Ci) + 3 * B * Nb * Co)
     if name == "bn_fwd":
         B, Nb, C, L, dt = a[:5]
         return 2 * B * Nb * C * L * _es(dt)
