@@ -1,17 +1,18 @@
 // Fused BatchNorm (training mode) over the channels of all B models.
 //
-// Conv-family layout (stride_l == 1): one workgroup per channel (b, c).  It
-// streams the channel's Nb rows of L contiguous elements twice -- once for the
-// statistics, once to normalise -- and the second pass of a channel follows its
-// first immediately, so the re-read is served by L2 / Infinity Cache rather
-// than HBM for all but the largest channels.  Statistics use sums shifted by
-// the channel's first element, which keeps fp32 accurate when |mean| >> std.
+// Conv-family layout (stride_l == 1): one workgroup per channel (b, c), which needs the channel's Nb rows of L
+// contiguous elements twice -- for the sums, and to form the result.  The first H pieces of four elements per
+// thread stay in registers in between (held_pieces() below); what a channel has beyond that is read again,
+// from L2 / Infinity Cache for all but the largest channels.  Statistics use sums shifted by the channel's
+// first element, which keeps fp32 accurate when |mean| >> std.
 // Reductions: per-lane partials -> wave64 shuffle reduction -> 4-entry LDS.
 //
 // Linear layout (L == 1, stride_c == 1, the table's [N, B, C] case): one thread
 // per channel, coalesced across channels, two passes over the Nb samples.
-#include <stdlib.h>
+#include <type_traits>
 #include "bn_common.h"
+
+namespace hfta { int persistent_blocks(); }     // compute units
 
 using namespace hfta;
 
@@ -28,33 +29,102 @@ struct BnFwdArgs {
   float eps, momentum, slope;
 };
 
-template <typename T, int VEC, int NT>
-__global__ __launch_bounds__(NT) void bn_fwd_conv_kernel(BnFwdArgs p) {
-  constexpr int UN = bn_unroll(VEC);
+// What bounds these kernels is the memory system behind L2: two workgroups of a 160 KB channel pair on each of 32 units are
+// more than an XCD's 4 MB, so a second read travels the fabric again.  With the pieces in registers the forward moves two
+// tensors instead of three, the backward three instead of five.
+//
+// held_waves: wavefronts per SIMD for `words` held registers (1024 threads: 8 or 4; 8 take up to `most`).
+constexpr int held_waves(int words, int most, int nt) { return words <= most ? 8 : nt == 1024 || words > 56 ? 4 : 5; }
+
+// the words of a piece as they lie in memory; the one that straddles its row's end is moved into place by held_place
+// (element offsets from the channel's start in 32 bits: a scalar base and one register a load; held_rows_ok)
+template <typename T, bool RAG>
+__device__ __forceinline__ void held_load(const T* x, uint32_t row, int ch, int L, uint32_t (&w)[sizeof(T)]) {
+  typedef typename std::conditional<RAG, typename PieceAt<T>::type, uint32_t __attribute__((ext_vector_type(sizeof(T))))>::type V;
+  const uint32_t at = (row + (uint32_t)(RAG ? min(ch * 4, L - 4) : ch * 4)) * (uint32_t)sizeof(T);
+  const V raw = *reinterpret_cast<const V*>(reinterpret_cast<const char*>(x) + at);
+#pragma unroll
+  for (int i = 0; i < (int)sizeof(T); ++i) w[i] = raw[i];
+}
+template <typename T, bool RAG>
+__device__ __forceinline__ void held_place(uint32_t (&w)[sizeof(T)], int ch, int L) {
+  if (RAG) piece_shift(w, ch * 4 - min(ch * 4, L - 4));
+}
+template <typename T>
+__device__ __forceinline__ void held_values(const uint32_t (&w)[sizeof(T)], float (&v)[4]) {
+  if (sizeof(T) == 2) {
+    v[0] = __uint_as_float(w[0] << 16); v[1] = __uint_as_float(w[0] & 0xffff0000u);
+    v[2] = __uint_as_float(w[1] << 16); v[3] = __uint_as_float(w[1] & 0xffff0000u);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(w[e & (sizeof(T) - 1)]);
+  }
+}
+// The walk again from the start: what the last one computed along the way is not kept in registers.
+__device__ __forceinline__ RowWalk held_walk(const RowWalk& start) {
+  RowWalk w = start;
+  asm volatile("" : "+v"(w.n), "+v"(w.ch));
+  return w;
+}
+// keeps the words, not the values made from them, in registers
+template <int W> __device__ __forceinline__ void held_keep(uint32_t (&w)[W]) {
+#pragma unroll
+  for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
+}
+
+template <typename T, int VEC, int NT, bool RAG, int H>
+__global__ __launch_bounds__(NT, held_waves(H * (int)sizeof(T), NT == 1024 ? 40 : 20, NT)) void bn_fwd_conv_kernel(BnFwdArgs p, int per) {
+  constexpr int UN = H ? 2 : bn_unroll(VEC), W = sizeof(T);
+  static_assert(H == 0 || VEC == 4, "pieces are held whole");
   __shared__ float sh[NT / 64][2];
   const int c = blockIdx.x, b = blockIdx.y;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   T* y = reinterpret_cast<T*>(p.Y) + b * p.ysb + c * p.ysc;
-  const int chunks = p.L / VEC;
+  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
+  uint32_t held[H ? H : 1][W];
+  const RowWalk start(chunks, NT);
+  RowWalk rest = held_walk(start);                                  // where the pieces that are not held begin
+#pragma unroll
+  for (int u = 0; u < H; ++u) {
+    if (u % 4 == 0 && u >= per) break;                   // `per` pieces exist for some thread
+    const bool ok = rest.n < p.Nb;                       // a piece past the end re-reads the channel's first and is not used
+    held_load<T, RAG>(x, ok ? (uint32_t)rest.n * (uint32_t)p.xsn : 0u, ok ? rest.ch : 0, p.L, held[u]);
+    rest.step();
+  }
   const float shift = Elem<T>::load(x);
   float s1 = 0.f, s2 = 0.f;
-  for (RowWalk w(chunks, NT); w.n < p.Nb;) {
-    // UN pieces per trip, their loads issued together (a piece past the end re-reads the
-    // channel's first piece and is not used): the bytes in flight per thread set the bandwidth
+  auto add = [&](const float (&v)[VEC], int ch) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      if (!RAG || ch * VEC + e < p.L) { const float d = v[e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
+  };
+  if constexpr (H > 0) {
+    RowWalk w = held_walk(start);
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+      if (u % 4 == 0 && u >= per) break;
+      held_place<T, RAG>(held[u], w.n < p.Nb ? w.ch : 0, p.L);
+      float v[VEC];
+      held_values<T>(held[u], v);
+      if (w.n < p.Nb) add(v, w.ch);
+      held_keep(held[u]);
+      w.step();
+    }
+  }
+  for (RowWalk w = rest; w.n < p.Nb;) {
+    // UN pieces per trip, their loads issued together: the bytes in flight per thread set the bandwidth
     float v[UN][VEC];
+    int ch[UN];
     bool ok[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      ok[u] = w.n < p.Nb;
-      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
+      ok[u] = w.n < p.Nb; ch[u] = w.ch;
+      load_piece<T, VEC, RAG>(ok[u] ? x + w.n * p.xsn : x, ok[u] ? w.ch : 0, p.L, v[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      if (ok[u]) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) { const float d = v[u][e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
-      }
+      if (ok[u]) add(v[u], ch[u]);
   }
   block_sum2<NT / 64>(s1, s2, sh);
   const float m = (float)p.Nb * (float)p.L;
@@ -75,26 +145,36 @@ __global__ __launch_bounds__(NT) void bn_fwd_conv_kernel(BnFwdArgs p) {
     }
   }
   if (!p.Y) return;                      // statistics only: a consumer normalises on load
-  for (RowWalk w(chunks, NT); w.n < p.Nb;) {
+  auto write = [&](float (&v)[VEC], int n, int ch) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) v[e] = bn_act(fmaf(g, (v[e] - mean) * invstd, bt), p.act, p.slope);
+    store_piece<T, VEC, RAG>(y + n * p.ysn, ch, p.L, v);
+  };
+  if constexpr (H > 0) {
+    RowWalk w = held_walk(start);
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+      if (u % 4 == 0 && u >= per) break;
+      float v[VEC];
+      held_values<T>(held[u], v);
+      if (w.n < p.Nb) write(v, w.n, w.ch);
+      w.step();
+    }
+  }
+  for (RowWalk w = rest; w.n < p.Nb;) {
     float v[UN][VEC];
     int n[UN], ch[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       n[u] = w.n; ch[u] = w.ch;
-      load_vec<T, VEC>(n[u] < p.Nb ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
+      load_piece<T, VEC, RAG>(n[u] < p.Nb ? x + n[u] * p.xsn : x, n[u] < p.Nb ? ch[u] : 0, p.L, v[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      if (n[u] < p.Nb) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) v[u][e] = apply_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope);
-        store_vec<T, VEC>(y + n[u] * p.ysn + ch[u] * VEC, v[u]);
-      }
+      if (n[u] < p.Nb) write(v[u], n[u], ch[u]);
   }
 }
-
-
 
 // Normalisation with given statistics (the forward kernel's second pass alone): what a consumer that
 // normalises on load computes, written out.
@@ -118,7 +198,7 @@ __global__ __launch_bounds__(NT) void bn_apply_conv_kernel(BnFwdArgs p) {
     for (int u = 0; u < BN_UNROLL; ++u)
       if (n[u] < p.Nb) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[u][e] = apply_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope);
+        for (int e = 0; e < VEC; ++e) v[u][e] = bn_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope);
         store_piece<T, VEC, RAG>(y + n[u] * p.ysn, ch[u], p.L, v[u]);
       }
   }
@@ -216,7 +296,7 @@ __global__ __launch_bounds__(BNL_C * BNL_N) void bn_fwd_linear_kernel(BnFwdArgs 
   if (!live) return;
   for (int n = ty; n < p.Nb; n += BNL_N) {
     const float v = Elem<T>::load(x + n * p.xsn);
-    Elem<T>::store(y + n * p.ysn, apply_act(fmaf(g, (v - mean) * invstd, bt), p.act, p.slope));
+    Elem<T>::store(y + n * p.ysn, bn_act(fmaf(g, (v - mean) * invstd, bt), p.act, p.slope));
   }
 }
 
@@ -229,67 +309,143 @@ struct BnBwdArgs {
   float slope;
 };
 
-template <typename T, int VEC, int NT>
-__global__ __launch_bounds__(NT) void bn_bwd_conv_kernel(BnBwdArgs p) {
-  constexpr int UN = bn_unroll(VEC);
+// XL: the pieces of X wait in LDS and only those of dY in registers, so that two 1024-thread workgroups fit a compute unit
+// (80 KB and 64 registers each) and one loads while the other writes.
+template <typename T, int VEC, int NT, bool RAG, int H, bool XL>
+__global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20, NT)) void bn_bwd_conv_kernel(BnBwdArgs p, int per) {
+  constexpr int UN = H ? 2 : bn_unroll(VEC), W = sizeof(T), G = H > 4 ? (H + 1) / 2 : 4;    // G: pieces loaded at a time
+  static_assert(H == 0 || VEC == 4, "pieces are held whole");
   __shared__ float sh[NT / 64][2];
   const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   const T* dy = reinterpret_cast<const T*>(p.dY) + b * p.dysb + c * p.dysc;
   T* dx = reinterpret_cast<T*>(p.dX) + b * p.dxsb + c * p.dxsc;
+  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
+  typedef uint32_t Words __attribute__((ext_vector_type(W)));
+  constexpr int HL = XL ? H - 1 : 0;                     // pieces of X in LDS: the last one's place is left to the sums
+  __shared__ Words xl[XL ? HL : 1][XL ? NT : 1];
+  uint32_t hx[H ? H - HL : 1][W], hd[H ? H : 1][W];
+  const RowWalk start(chunks, NT);
   const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
-  const int chunks = p.L / VEC;
   float s1 = 0.f, s2 = 0.f;
-  for (RowWalk w(chunks, NT); w.n < p.Nb;) {
+  auto add = [&](const float (&v)[VEC], const float (&d)[VEC], int ch) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      if (!RAG || ch * VEC + e < p.L) {
+        const float xh = (v[e] - mean) * invstd;
+        const float gr = d[e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+        s1 += gr;
+        s2 = fmaf(gr, xh, s2);
+      }
+  };
+  RowWalk rest = held_walk(start);                       // where the pieces that are not held begin
+  if constexpr (H > 0) {
+#pragma unroll
+    for (int u0 = 0; u0 < H; u0 += G) {
+      if (u0 >= per) break;
+      uint32_t tx[G][W];
+      RowWalk w = rest;
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        if (u0 + i >= H) continue;
+        const bool ok = rest.n < p.Nb;                   // a piece past the end re-reads the channel's first and is not used
+        const int ch = ok ? rest.ch : 0;
+        held_load<T, RAG>(x, ok ? (uint32_t)rest.n * (uint32_t)p.xsn : 0u, ch, p.L, tx[i]);
+        held_load<T, RAG>(dy, ok ? (uint32_t)rest.n * (uint32_t)p.dysn : 0u, ch, p.L, hd[u0 + i]);
+        rest.step();
+      }
+      w = held_walk(w);
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        const int u = u0 + i;
+        if (u >= H) continue;
+        const int at = w.n < p.Nb ? w.ch : 0;
+        held_place<T, RAG>(tx[i], at, p.L);
+        held_place<T, RAG>(hd[u], at, p.L);
+        float v[VEC], d[VEC];
+        held_values<T>(tx[i], v);
+        held_values<T>(hd[u], d);
+        if (w.n < p.Nb) add(v, d, w.ch);
+        if (u < HL) {
+          Words q;
+#pragma unroll
+          for (int j = 0; j < W; ++j) q[j] = tx[i][j];
+          xl[u < HL ? u : 0][XL ? threadIdx.x : 0] = q;              // read by this thread alone
+        } else {
+#pragma unroll
+          for (int j = 0; j < W; ++j) hx[u < HL ? 0 : u - HL][j] = tx[i][j];
+          held_keep(hx[u < HL ? 0 : u - HL]);
+        }
+        held_keep(hd[u]);
+        w.step();
+      }
+    }
+  }
+  for (RowWalk w = rest; w.n < p.Nb;) {
     float v[UN][VEC], d[UN][VEC];
+    int ch[UN];
     bool ok[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      ok[u] = w.n < p.Nb;
-      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
-      load_vec<T, VEC>(ok[u] ? dy + w.n * p.dysn + w.ch * VEC : dy, d[u]);
+      ok[u] = w.n < p.Nb; ch[u] = w.ch;
+      load_piece<T, VEC, RAG>(ok[u] ? x + w.n * p.xsn : x, ok[u] ? w.ch : 0, p.L, v[u]);
+      load_piece<T, VEC, RAG>(ok[u] ? dy + w.n * p.dysn : dy, ok[u] ? w.ch : 0, p.L, d[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      if (ok[u]) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const float xh = (v[u][e] - mean) * invstd;
-          const float gr = d[u][e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
-          s1 += gr;
-          s2 = fmaf(gr, xh, s2);
-        }
-      }
+      if (ok[u]) add(v[u], d[u], ch[u]);
   }
   block_sum2<NT / 64>(s1, s2, sh);
   if (threadIdx.x == 0) { p.dbeta[k] = s1; p.dgamma[k] = s2; }
   const float m = (float)p.Nb * (float)p.L;
   const float mb = s1 / m, mg = s2 / m, sc = g * invstd;
   float s3 = 0.f;
-  for (RowWalk w(chunks, NT); w.n < p.Nb;) {
+  auto write = [&](float (&v)[VEC], const float (&d)[VEC], int n, int ch) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const float xh = (v[e] - mean) * invstd;
+      const float gr = d[e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+      v[e] = sc * (gr - mb - xh * mg);
+      if (!RAG || ch * VEC + e < p.L) s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[e]));     // the value as it is stored
+    }
+    store_piece<T, VEC, RAG>(dx + n * p.dxsn, ch, p.L, v);
+  };
+  if constexpr (H > 0) {
+    RowWalk w = held_walk(start);
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+      if (u % G == 0 && u >= per) break;
+      float v[VEC], d[VEC];
+      uint32_t tx[W];
+      if (u < HL) {
+        const Words q = xl[u < HL ? u : 0][XL ? threadIdx.x : 0];
+#pragma unroll
+        for (int j = 0; j < W; ++j) tx[j] = q[j];
+      } else {
+#pragma unroll
+        for (int j = 0; j < W; ++j) tx[j] = hx[u < HL ? 0 : u - HL][j];
+      }
+      held_values<T>(tx, v);
+      held_values<T>(hd[u], d);
+      if (w.n < p.Nb) write(v, d, w.n, w.ch);
+      w.step();
+    }
+  }
+  for (RowWalk w = rest; w.n < p.Nb;) {
     float v[UN][VEC], d[UN][VEC];
     int n[UN], ch[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       n[u] = w.n; ch[u] = w.ch;
       const bool ok = n[u] < p.Nb;
-      load_vec<T, VEC>(ok ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
-      load_vec<T, VEC>(ok ? dy + n[u] * p.dysn + ch[u] * VEC : dy, d[u]);
+      load_piece<T, VEC, RAG>(ok ? x + n[u] * p.xsn : x, ok ? ch[u] : 0, p.L, v[u]);
+      load_piece<T, VEC, RAG>(ok ? dy + n[u] * p.dysn : dy, ok ? ch[u] : 0, p.L, d[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      if (n[u] < p.Nb) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const float xh = (v[u][e] - mean) * invstd;
-          const float gr = d[u][e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
-          v[u][e] = sc * (gr - mb - xh * mg);
-          s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[u][e]));     // the value as it is stored
-        }
-        store_vec<T, VEC>(dx + n[u] * p.dxsn + ch[u] * VEC, v[u]);
-      }
+      if (n[u] < p.Nb) write(v[u], d[u], n[u], ch[u]);
   }
   if (p.dx_sum) {
     float dummy = 0.f;
@@ -398,6 +554,79 @@ __global__ __launch_bounds__(BNL_C * BNL_N) void bn_bwd_linear_kernel(BnBwdArgs 
   }
 }
 
+// Pieces of a channel per thread.
+int held_pieces(int Nb, int L, int nt) { return (int)(((int64_t)Nb * ((L + 3) / 4) + nt - 1) / nt); }
+
+// Byte offsets within a channel fit 32 bits.
+template <typename T> bool held_rows_ok(int Nb, int L, int64_t sn0, int64_t sn1) {
+  const int64_t limit = (int64_t)1 << 32, far = (sn0 > sn1 ? sn0 : sn1);
+  return sn0 >= 0 && sn1 >= 0 && far < limit / Nb && ((int64_t)(Nb - 1) * far + L) * (int64_t)sizeof(T) < limit;
+}
+
+// How many pieces a thread holds.  All of a channel if they fit with two 1024-thread workgroups per compute unit, else what
+// does: us with nothing held -> now, and what the other choice takes:
+//   forward   bf16 6 x 16 x 2500, 2048 channels 538 -> 446, 128 channels 31 -> 26 (rows of 2497: 118 -> 29, most of it from
+//             four-element pieces); 8 x 32 x 2500, 64 channels 39 -> 31; fp32 4 x 32 x 2500, 128 channels 81 -> 69 with 9 of
+//             20 held, 76 with all 20 and one workgroup per unit, which wins where all channels run at once: 64 channels
+//             38 -> 27, 34 with 9.
+//   backward  the same tensors: 741 -> 588 (777 with both operands in registers and one workgroup per unit), 50 -> 38
+//             (159 -> 41), 62 -> 54; fp32 62 -> 52 and 155 -> 126 with 10 of 20 held in registers, 56 and 137 with 5 in LDS,
+//             which wins where 5 are most of the channel (32 x 1023: 41 against 43).
+// Past 40 pieces too little of a channel is held to pay for the wavefronts (2 x 64 channels of 100 x 4096 bf16: forward
+// 77 us with nothing held, 95 with 20 of 100, backward 125 and 131).
+constexpr int HELD_MOST = 40;
+template <typename T, int NT, bool RAG>
+void launch_bn_fwd(const BnFwdArgs& a, dim3 grid, hipStream_t st) {
+  constexpr int HALF = sizeof(T) == 2 ? 20 : RAG ? 8 : 9, FULL = sizeof(T) == 2 ? HALF : RAG ? 17 : 20;
+  const int per = a.Y ? held_pieces(a.Nb, a.L, NT) : 0;            // statistics alone: read once
+#define HFTA_HELD(N) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 4, NT, RAG, N>), grid, dim3(NT), 0, st, a, per)
+  if (per == 0 || per > HELD_MOST || !held_rows_ok<T>(a.Nb, a.L, a.xsn, 0)) HFTA_HELD(0);
+  else if (per <= 4) HFTA_HELD(4);
+  else if (per <= HALF / 2) HFTA_HELD(HALF / 2);
+  else if (NT == 256 || per <= HALF || (int)(grid.x * grid.y) > persistent_blocks()) HFTA_HELD(HALF);
+  else HFTA_HELD((NT == 256 ? HALF : FULL));
+#undef HFTA_HELD
+}
+template <typename T, int NT, bool RAG>
+void launch_bn_bwd(const BnBwdArgs& a, dim3 grid, hipStream_t st) {
+  constexpr int W = (int)sizeof(T), REGS = RAG ? 9 : 10;
+  const int per = held_pieces(a.Nb, a.L, NT);
+#define HFTA_HELD(N, XL) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 4, NT, RAG, N, XL>), grid, dim3(NT), 0, st, a, per)
+  if (per > HELD_MOST || !held_rows_ok<T>(a.Nb, a.L, a.xsn, a.dysn)) HFTA_HELD(0, false);
+  else if constexpr (NT == 256) {
+    if (per <= 4) HFTA_HELD(4, false);
+    else if (per <= 20 / W) HFTA_HELD(20 / W, false);
+    else HFTA_HELD(32 / W, false);
+  } else if constexpr (W == 2) {
+    if (per <= 4) HFTA_HELD(4, false);
+    else HFTA_HELD(10, true);
+  } else {
+    if (per <= REGS) HFTA_HELD(5, true);
+    else HFTA_HELD(REGS, false);
+  }
+#undef HFTA_HELD
+}
+// The kernel of the row form: aligned four-element pieces (v4), pieces of rows of any length and alignment, or, for rows
+// shorter than one piece, single elements.
+template <typename T>
+void launch_bn_fwd_rows(const BnFwdArgs& a, int B, bool v4, hipStream_t st) {
+  const dim3 grid((unsigned)a.C, (unsigned)B);
+  const bool big = bn_wide_block((int64_t)a.Nb * a.L * (int64_t)sizeof(T));
+  if (v4) big ? launch_bn_fwd<T, 1024, false>(a, grid, st) : launch_bn_fwd<T, 256, false>(a, grid, st);
+  else if (a.L >= 4) big ? launch_bn_fwd<T, 1024, true>(a, grid, st) : launch_bn_fwd<T, 256, true>(a, grid, st);
+  else if (big) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 1024, false, 0>), grid, dim3(1024), 0, st, a, 0);
+  else hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 256, false, 0>), grid, dim3(256), 0, st, a, 0);
+}
+template <typename T>
+void launch_bn_bwd_rows(const BnBwdArgs& a, int B, bool v4, hipStream_t st) {
+  const dim3 grid((unsigned)a.C, (unsigned)B);
+  const bool big = bn_wide_block((int64_t)a.Nb * a.L * (int64_t)sizeof(T));
+  if (v4) big ? launch_bn_bwd<T, 1024, false>(a, grid, st) : launch_bn_bwd<T, 256, false>(a, grid, st);
+  else if (a.L >= 4) big ? launch_bn_bwd<T, 1024, true>(a, grid, st) : launch_bn_bwd<T, 256, true>(a, grid, st);
+  else if (big) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 1024, false, 0, false>), grid, dim3(1024), 0, st, a, 0);
+  else hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 256, false, 0, false>), grid, dim3(256), 0, st, a, 0);
+}
+
 bool vec_ok(const void* p, const int64_t* s, int L, int dtype) {
   const int es = (int)dtype_size(dtype);
   const size_t bytes = 4 * es;
@@ -426,7 +655,7 @@ __global__ __launch_bounds__(NT) void bn_eval_conv_kernel(BnEvalArgs p) {
     float v[VEC];
     load_piece<T, VEC, RAG>(x + w.n * p.xsn, w.ch, p.L, v);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) v[e] = apply_act(fmaf(scale, v[e] - mean, bt), p.act, p.slope);
+    for (int e = 0; e < VEC; ++e) v[e] = bn_act(fmaf(scale, v[e] - mean, bt), p.act, p.slope);
     store_piece<T, VEC, RAG>(y + w.n * p.ysn, w.ch, p.L, v);
   }
 }
@@ -442,7 +671,7 @@ __global__ __launch_bounds__(BNL_C * BNL_N) void bn_eval_linear_kernel(BnEvalArg
   const float mean = p.running_mean[k];
   const float scale = p.gamma[k] * (1.0f / sqrtf(p.running_var[k] + p.eps)), bt = p.beta[k];
   for (int n = ty; n < p.Nb; n += BNL_N)
-    Elem<T>::store(y + n * p.ysn, apply_act(fmaf(scale, Elem<T>::load(x + n * p.xsn) - mean, bt), p.act, p.slope));
+    Elem<T>::store(y + n * p.ysn, bn_act(fmaf(scale, Elem<T>::load(x + n * p.xsn) - mean, bt), p.act, p.slope));
 }
 
 int layout_kind(const int64_t* s, int L) {
@@ -490,15 +719,9 @@ int bn_stats_conv(int B, int Nb, int C, int L, int dtype, const void* X, const i
   if (B > 65535 || layout_kind(xs, L) != 1) return HFTA_EUNSUPPORTED;
   BnFwdArgs a{X, nullptr, gamma, beta, running_mean, running_var, save_mean, save_invstd,
               xs[0], xs[1], xs[2], 0, 0, 0, Nb, C, L, HFTA_ACT_NONE, eps, momentum, 0.f};
-  const dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype);
-  const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_BN_STATS(T, V) \
-  do { if (big) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, V, 1024>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_fwd_conv_kernel<T, V, 256>), grid, dim3(256), 0, st, a); } while (0)
-  if (dtype == HFTA_BF16) { if (v4) HFTA_BN_STATS(bf16_raw, 4); else HFTA_BN_STATS(bf16_raw, 1); }
-  else { if (v4) HFTA_BN_STATS(float, 4); else HFTA_BN_STATS(float, 1); }
-#undef HFTA_BN_STATS
+  if (dtype == HFTA_BF16) launch_bn_fwd_rows<bf16_raw>(a, B, v4, st);
+  else launch_bn_fwd_rows<float>(a, B, v4, st);
   return launch_status();
 }
 
@@ -554,15 +777,9 @@ int hfta_bn_fwd(int B, int Nb, int C, int L, int dtype, const void* X, const int
     else hipLaunchKernelGGL(bn_fwd_linear_kernel<float>, grid, dim3(BNL_C * BNL_N), 0, st, a);
     return launch_status();
   }
-  dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype) && vec_ok(Y, ys, L, dtype);
-  const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_BN_FWD(T, V) \
-  do { if (big) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, V, 1024>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_fwd_conv_kernel<T, V, 256>), grid, dim3(256), 0, st, a); } while (0)
-  if (dtype == HFTA_BF16) { if (v4) HFTA_BN_FWD(bf16_raw, 4); else HFTA_BN_FWD(bf16_raw, 1); }
-  else { if (v4) HFTA_BN_FWD(float, 4); else HFTA_BN_FWD(float, 1); }
-#undef HFTA_BN_FWD
+  if (dtype == HFTA_BF16) launch_bn_fwd_rows<bf16_raw>(a, B, v4, st);
+  else launch_bn_fwd_rows<float>(a, B, v4, st);
   return launch_status();
 }
 
@@ -640,15 +857,9 @@ int hfta_bn_bwd(int B, int Nb, int C, int L, int dtype, const void* X, const int
     else hipLaunchKernelGGL(bn_bwd_linear_kernel<float>, grid, dim3(BNL_C * BNL_N), 0, st, a);
     return launch_status();
   }
-  dim3 grid((unsigned)C, (unsigned)B);
   const bool v4 = vec_ok(X, xs, L, dtype) && vec_ok(dY, dys, L, dtype) && vec_ok(dX, dxs, L, dtype);
-  const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_BN_BWD(T, V) \
-  do { if (big) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, V, 1024>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_bwd_conv_kernel<T, V, 256>), grid, dim3(256), 0, st, a); } while (0)
-  if (dtype == HFTA_BF16) { if (v4) HFTA_BN_BWD(bf16_raw, 4); else HFTA_BN_BWD(bf16_raw, 1); }
-  else { if (v4) HFTA_BN_BWD(float, 4); else HFTA_BN_BWD(float, 1); }
-#undef HFTA_BN_BWD
+  if (dtype == HFTA_BF16) launch_bn_bwd_rows<bf16_raw>(a, B, v4, st);
+  else launch_bn_bwd_rows<float>(a, B, v4, st);
   return launch_status();
 }
 

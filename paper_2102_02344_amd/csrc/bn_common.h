@@ -97,12 +97,19 @@ __device__ __forceinline__ void block_sum2(float& a, float& b, float (*sh)[2]) {
   a = ra; b = rb;
 }
 
-__device__ __forceinline__ float act_grad(float pre, int act, float slope) {
-  if (act == HFTA_ACT_RELU) return pre > 0.f ? 1.f : 0.f;
-  if (act == HFTA_ACT_LEAKY) return pre > 0.f ? 1.f : slope;
-  return 1.f;
+// The activations a BatchNorm takes: none, ReLU, LeakyReLU.  What is uniform over the launch stays outside the element:
+// with the general apply_act a kernel carries tanh and erf for every element it unrolls (the forward kernel 13 KB of code,
+// 70 KB with 20 pieces unrolled, fetched anew by each launch) and takes a scalar branch around them.
+__device__ __forceinline__ float act_below(int act, float slope) {
+  return act == HFTA_ACT_RELU ? 0.f : act == HFTA_ACT_LEAKY ? slope : 1.f;
 }
-
+__device__ __forceinline__ float bn_act(float y, int act, float slope) {
+  const float lo = act_below(act, slope) * y;
+  return y > 0.f ? y : act == HFTA_ACT_RELU ? 0.f : lo;
+}
+__device__ __forceinline__ float act_grad(float pre, int act, float slope) {
+  return pre > 0.f ? 1.f : act_below(act, slope);
+}
 
 // Channels whose data is large get one 1024-thread workgroup each (instead of 256 threads):
 // 512 channels x 1024 threads fill the chip where 512 x 256 would leave it three quarters empty,
