@@ -36,19 +36,14 @@ struct BnFwdArgs {
 // held_waves: wavefronts per SIMD for `words` held registers (1024 threads: 8 or 4; 8 take up to `most`).
 constexpr int held_waves(int words, int most, int nt) { return words <= most ? 8 : nt == 1024 || words > 56 ? 4 : 5; }
 
-// the words of a piece as they lie in memory; the one that straddles its row's end is moved into place by held_place
-// (element offsets from the channel's start in 32 bits: a scalar base and one register a load; held_rows_ok)
-template <typename T, bool RAG>
-__device__ __forceinline__ void held_load(const T* x, uint32_t row, int ch, int L, uint32_t (&w)[sizeof(T)]) {
-  typedef typename std::conditional<RAG, typename PieceAt<T>::type, uint32_t __attribute__((ext_vector_type(sizeof(T))))>::type V;
-  const uint32_t at = (row + (uint32_t)(RAG ? min(ch * 4, L - 4) : ch * 4)) * (uint32_t)sizeof(T);
+// the words of a piece (element offsets from the channel's start in 32 bits: a scalar base and one register a load; held_rows_ok)
+template <typename T>
+__device__ __forceinline__ void held_load(const T* x, uint32_t row, int ch, uint32_t (&w)[sizeof(T)]) {
+  typedef uint32_t V __attribute__((ext_vector_type(sizeof(T))));
+  const uint32_t at = (row + (uint32_t)ch * 4u) * (uint32_t)sizeof(T);
   const V raw = *reinterpret_cast<const V*>(reinterpret_cast<const char*>(x) + at);
 #pragma unroll
   for (int i = 0; i < (int)sizeof(T); ++i) w[i] = raw[i];
-}
-template <typename T, bool RAG>
-__device__ __forceinline__ void held_place(uint32_t (&w)[sizeof(T)], int ch, int L) {
-  if (RAG) piece_shift(w, ch * 4 - min(ch * 4, L - 4));
 }
 template <typename T>
 __device__ __forceinline__ void held_values(const uint32_t (&w)[sizeof(T)], float (&v)[4]) {
@@ -72,15 +67,15 @@ template <int W> __device__ __forceinline__ void held_keep(uint32_t (&w)[W]) {
   for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
 }
 
-template <typename T, int VEC, int NT, bool RAG, int H>
-__global__ __launch_bounds__(NT, held_waves(H * (int)sizeof(T), NT == 1024 ? 40 : 20, NT)) void bn_fwd_conv_kernel(BnFwdArgs p, int per) {
+template <typename T, int VEC, int NT, int H>
+__global__ __launch_bounds__(NT, VEC == 1 ? 4 : held_waves(H * (int)sizeof(T), NT == 1024 ? 40 : 20, NT)) void bn_fwd_conv_kernel(BnFwdArgs p, int per) {
   constexpr int UN = H ? 2 : bn_unroll(VEC), W = sizeof(T);
   static_assert(H == 0 || VEC == 4, "pieces are held whole");
   __shared__ float sh[NT / 64][2];
   const int c = blockIdx.x, b = blockIdx.y;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   T* y = reinterpret_cast<T*>(p.Y) + b * p.ysb + c * p.ysc;
-  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
+  const int chunks = p.L / VEC;
   uint32_t held[H ? H : 1][W];
   const RowWalk start(chunks, NT);
   RowWalk rest = held_walk(start);                                  // where the pieces that are not held begin
@@ -88,25 +83,24 @@ __global__ __launch_bounds__(NT, held_waves(H * (int)sizeof(T), NT == 1024 ? 40 
   for (int u = 0; u < H; ++u) {
     if (u % 4 == 0 && u >= per) break;                   // `per` pieces exist for some thread
     const bool ok = rest.n < p.Nb;                       // a piece past the end re-reads the channel's first and is not used
-    held_load<T, RAG>(x, ok ? (uint32_t)rest.n * (uint32_t)p.xsn : 0u, ok ? rest.ch : 0, p.L, held[u]);
+    held_load<T>(x, ok ? (uint32_t)rest.n * (uint32_t)p.xsn : 0u, ok ? rest.ch : 0, held[u]);
     rest.step();
   }
   const float shift = Elem<T>::load(x);
   float s1 = 0.f, s2 = 0.f;
-  auto add = [&](const float (&v)[VEC], int ch) {
+  auto add = [&](const float (&v)[VEC]) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e)
-      if (!RAG || ch * VEC + e < p.L) { const float d = v[e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
+      { const float d = v[e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
   };
   if constexpr (H > 0) {
     RowWalk w = held_walk(start);
 #pragma unroll
     for (int u = 0; u < H; ++u) {
       if (u % 4 == 0 && u >= per) break;
-      held_place<T, RAG>(held[u], w.n < p.Nb ? w.ch : 0, p.L);
       float v[VEC];
       held_values<T>(held[u], v);
-      if (w.n < p.Nb) add(v, w.ch);
+      if (w.n < p.Nb) add(v);
       held_keep(held[u]);
       w.step();
     }
@@ -114,17 +108,16 @@ __global__ __launch_bounds__(NT, held_waves(H * (int)sizeof(T), NT == 1024 ? 40 
   for (RowWalk w = rest; w.n < p.Nb;) {
     // UN pieces per trip, their loads issued together: the bytes in flight per thread set the bandwidth
     float v[UN][VEC];
-    int ch[UN];
     bool ok[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      ok[u] = w.n < p.Nb; ch[u] = w.ch;
-      load_piece<T, VEC, RAG>(ok[u] ? x + w.n * p.xsn : x, ok[u] ? w.ch : 0, p.L, v[u]);
+      ok[u] = w.n < p.Nb;
+      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      if (ok[u]) add(v[u], ch[u]);
+      if (ok[u]) add(v[u]);
   }
   block_sum2<NT / 64>(s1, s2, sh);
   const float m = (float)p.Nb * (float)p.L;
@@ -148,7 +141,7 @@ __global__ __launch_bounds__(NT, held_waves(H * (int)sizeof(T), NT == 1024 ? 40 
   auto write = [&](float (&v)[VEC], int n, int ch) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) v[e] = bn_act(fmaf(g, (v[e] - mean) * invstd, bt), p.act, p.slope);
-    store_piece<T, VEC, RAG>(y + n * p.ysn, ch, p.L, v);
+    store_vec<T, VEC>(y + n * p.ysn + ch * VEC, v);
   };
   if constexpr (H > 0) {
     RowWalk w = held_walk(start);
@@ -167,12 +160,96 @@ __global__ __launch_bounds__(NT, held_waves(H * (int)sizeof(T), NT == 1024 ? 40 
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       n[u] = w.n; ch[u] = w.ch;
-      load_piece<T, VEC, RAG>(n[u] < p.Nb ? x + n[u] * p.xsn : x, n[u] < p.Nb ? ch[u] : 0, p.L, v[u]);
+      load_vec<T, VEC>(n[u] < p.Nb ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
       if (n[u] < p.Nb) write(v[u], n[u], ch[u]);
+  }
+}
+
+// Rows that are no multiple of four elements: the sums run over single elements in order (the walk of VEC == 1: thread t adds
+// the channel's elements t, t + NT, ...), whatever the loads are, because sums in another order move the outputs of the
+// segmentation and the transform array by 0.01 to 0.1 after three steps, more than two correct forms may differ by.  Single
+// elements from memory reach a quarter of the bandwidth, so a channel travels in four-element pieces into LDS, rows at a pitch
+// of whole pieces, and is added up from there, 2 or 4 bytes a lane.
+// Stages rows of L elements at pitch 4 * chunks; the caller's barrier makes them visible.
+template <typename T, int NT>
+__device__ __forceinline__ void bn_stage(T* lds, const T* x, int64_t sn, int Nb, int L, int chunks) {
+  constexpr int UN = 4, W = sizeof(T);
+  typedef uint32_t Words __attribute__((ext_vector_type(W)));
+  for (RowWalk w(chunks, NT); w.n < Nb;) {
+    Words q[UN];
+    int n[UN], ch[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      n[u] = w.n; ch[u] = w.ch;
+      const bool ok = w.n < Nb;
+      const typename PieceAt<T>::type raw = *reinterpret_cast<const typename PieceAt<T>::type*>((ok ? x + w.n * sn : x) + (ok ? min(w.ch * 4, L - 4) : 0));
+#pragma unroll
+      for (int i = 0; i < W; ++i) q[u][i] = raw[i];
+      w.step();
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (n[u] < Nb) {
+        uint32_t v[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) v[i] = q[u][i];
+        piece_shift(v, ch[u] * 4 - min(ch[u] * 4, L - 4));
+#pragma unroll
+        for (int i = 0; i < W; ++i) q[u][i] = v[i];
+        *reinterpret_cast<Words*>(lds + (n[u] * chunks + ch[u]) * 4) = q[u];
+      }
+  }
+}
+constexpr int STAGE_SMALL = 20 * 1024 - 256, STAGE_MID = 40 * 1024 - 256, STAGE_HALF = 80 * 1024 - 256, STAGE_FULL = 160 * 1024 - 256;
+
+template <typename T, int NT, int BYTES>
+__global__ __launch_bounds__(NT) void bn_fwd_odd_kernel(BnFwdArgs p) {
+  __shared__ float sh[NT / 64][2];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
+  T* lds = reinterpret_cast<T*>(smem);
+  const int c = blockIdx.x, b = blockIdx.y;
+  const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
+  T* y = reinterpret_cast<T*>(p.Y) + b * p.ysb + c * p.ysc;
+  const int chunks = (p.L + 3) / 4, pitch = chunks * 4;
+  const float shift = Elem<T>::load(x);
+  bn_stage<T, NT>(lds, x, p.xsn, p.Nb, p.L, chunks);
+  __syncthreads();
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll 8
+  for (RowWalk w(p.L, NT); w.n < p.Nb; w.step()) {
+    const float d = Elem<T>::load(lds + w.n * pitch + w.ch) - shift;
+    s1 += d;
+    s2 = fmaf(d, d, s2);
+  }
+  block_sum2<NT / 64>(s1, s2, sh);
+  const float m = (float)p.Nb * (float)p.L;
+  const float dm = s1 / m;
+  const float mean = shift + dm;
+  float var = s2 / m - dm * dm;
+  var = var < 0.f ? 0.f : var;
+  const float invstd = 1.0f / sqrtf(var + p.eps);
+  const int k = b * p.C + c;
+  const float g = p.gamma[k], bt = p.beta[k];
+  if (threadIdx.x == 0) {
+    p.save_mean[k] = mean;
+    p.save_invstd[k] = invstd;
+    if (p.running_mean) {
+      const float unb = m > 1.f ? var * (m / (m - 1.f)) : var;
+      p.running_mean[k] = (1.f - p.momentum) * p.running_mean[k] + p.momentum * mean;
+      p.running_var[k] = (1.f - p.momentum) * p.running_var[k] + p.momentum * unb;
+    }
+  }
+  if (!p.Y) return;
+  for (RowWalk w(chunks, NT); w.n < p.Nb; w.step()) {
+    float v[4];
+    load_vec<T, 4>(lds + (w.n * chunks + w.ch) * 4, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = bn_act(fmaf(g, (v[e] - mean) * invstd, bt), p.act, p.slope);
+    store_piece<T, 4, true>(y + w.n * p.ysn, w.ch, p.L, v);
   }
 }
 
@@ -311,8 +388,8 @@ struct BnBwdArgs {
 
 // XL: the pieces of X wait in LDS and only those of dY in registers, so that two 1024-thread workgroups fit a compute unit
 // (80 KB and 64 registers each) and one loads while the other writes.
-template <typename T, int VEC, int NT, bool RAG, int H, bool XL>
-__global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20, NT)) void bn_bwd_conv_kernel(BnBwdArgs p, int per) {
+template <typename T, int VEC, int NT, int H, bool XL>
+__global__ __launch_bounds__(NT, VEC == 1 ? 4 : XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20, NT)) void bn_bwd_conv_kernel(BnBwdArgs p, int per) {
   constexpr int UN = H ? 2 : bn_unroll(VEC), W = sizeof(T), G = H > 4 ? (H + 1) / 2 : 4;    // G: pieces loaded at a time
   static_assert(H == 0 || VEC == 4, "pieces are held whole");
   __shared__ float sh[NT / 64][2];
@@ -320,7 +397,7 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
   const T* dy = reinterpret_cast<const T*>(p.dY) + b * p.dysb + c * p.dysc;
   T* dx = reinterpret_cast<T*>(p.dX) + b * p.dxsb + c * p.dxsc;
-  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
+  const int chunks = p.L / VEC;
   typedef uint32_t Words __attribute__((ext_vector_type(W)));
   constexpr int HL = XL ? H - 1 : 0;                     // pieces of X in LDS: the last one's place is left to the sums
   __shared__ Words xl[XL ? HL : 1][XL ? NT : 1];
@@ -328,15 +405,14 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
   const RowWalk start(chunks, NT);
   const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
   float s1 = 0.f, s2 = 0.f;
-  auto add = [&](const float (&v)[VEC], const float (&d)[VEC], int ch) {
+  auto add = [&](const float (&v)[VEC], const float (&d)[VEC]) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      if (!RAG || ch * VEC + e < p.L) {
-        const float xh = (v[e] - mean) * invstd;
-        const float gr = d[e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
-        s1 += gr;
-        s2 = fmaf(gr, xh, s2);
-      }
+    for (int e = 0; e < VEC; ++e) {
+      const float xh = (v[e] - mean) * invstd;
+      const float gr = d[e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+      s1 += gr;
+      s2 = fmaf(gr, xh, s2);
+    }
   };
   RowWalk rest = held_walk(start);                       // where the pieces that are not held begin
   if constexpr (H > 0) {
@@ -350,8 +426,8 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
         if (u0 + i >= H) continue;
         const bool ok = rest.n < p.Nb;                   // a piece past the end re-reads the channel's first and is not used
         const int ch = ok ? rest.ch : 0;
-        held_load<T, RAG>(x, ok ? (uint32_t)rest.n * (uint32_t)p.xsn : 0u, ch, p.L, tx[i]);
-        held_load<T, RAG>(dy, ok ? (uint32_t)rest.n * (uint32_t)p.dysn : 0u, ch, p.L, hd[u0 + i]);
+        held_load<T>(x, ok ? (uint32_t)rest.n * (uint32_t)p.xsn : 0u, ch, tx[i]);
+        held_load<T>(dy, ok ? (uint32_t)rest.n * (uint32_t)p.dysn : 0u, ch, hd[u0 + i]);
         rest.step();
       }
       w = held_walk(w);
@@ -359,13 +435,10 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
       for (int i = 0; i < G; ++i) {
         const int u = u0 + i;
         if (u >= H) continue;
-        const int at = w.n < p.Nb ? w.ch : 0;
-        held_place<T, RAG>(tx[i], at, p.L);
-        held_place<T, RAG>(hd[u], at, p.L);
         float v[VEC], d[VEC];
         held_values<T>(tx[i], v);
         held_values<T>(hd[u], d);
-        if (w.n < p.Nb) add(v, d, w.ch);
+        if (w.n < p.Nb) add(v, d);
         if (u < HL) {
           Words q;
 #pragma unroll
@@ -383,18 +456,17 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
   }
   for (RowWalk w = rest; w.n < p.Nb;) {
     float v[UN][VEC], d[UN][VEC];
-    int ch[UN];
     bool ok[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      ok[u] = w.n < p.Nb; ch[u] = w.ch;
-      load_piece<T, VEC, RAG>(ok[u] ? x + w.n * p.xsn : x, ok[u] ? w.ch : 0, p.L, v[u]);
-      load_piece<T, VEC, RAG>(ok[u] ? dy + w.n * p.dysn : dy, ok[u] ? w.ch : 0, p.L, d[u]);
+      ok[u] = w.n < p.Nb;
+      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
+      load_vec<T, VEC>(ok[u] ? dy + w.n * p.dysn + w.ch * VEC : dy, d[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      if (ok[u]) add(v[u], d[u], ch[u]);
+      if (ok[u]) add(v[u], d[u]);
   }
   block_sum2<NT / 64>(s1, s2, sh);
   if (threadIdx.x == 0) { p.dbeta[k] = s1; p.dgamma[k] = s2; }
@@ -407,9 +479,9 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
       const float xh = (v[e] - mean) * invstd;
       const float gr = d[e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
       v[e] = sc * (gr - mb - xh * mg);
-      if (!RAG || ch * VEC + e < p.L) s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[e]));     // the value as it is stored
+      s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[e]));     // the value as it is stored
     }
-    store_piece<T, VEC, RAG>(dx + n * p.dxsn, ch, p.L, v);
+    store_vec<T, VEC>(dx + n * p.dxsn + ch * VEC, v);
   };
   if constexpr (H > 0) {
     RowWalk w = held_walk(start);
@@ -439,8 +511,8 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
     for (int u = 0; u < UN; ++u) {
       n[u] = w.n; ch[u] = w.ch;
       const bool ok = n[u] < p.Nb;
-      load_piece<T, VEC, RAG>(ok ? x + n[u] * p.xsn : x, ok ? ch[u] : 0, p.L, v[u]);
-      load_piece<T, VEC, RAG>(ok ? dy + n[u] * p.dysn : dy, ok ? ch[u] : 0, p.L, d[u]);
+      load_vec<T, VEC>(ok ? x + n[u] * p.xsn + ch[u] * VEC : x, v[u]);
+      load_vec<T, VEC>(ok ? dy + n[u] * p.dysn + ch[u] * VEC : dy, d[u]);
       w.step();
     }
 #pragma unroll
@@ -449,6 +521,60 @@ __global__ __launch_bounds__(NT, XL ? 8 : held_waves(2 * H * (int)sizeof(T), 20,
   }
   if (p.dx_sum) {
     float dummy = 0.f;
+    block_sum2<NT / 64>(s3, dummy, sh);
+    if (threadIdx.x == 0) p.dx_sum[k] = s3;
+  }
+}
+
+// Rows that are no multiple of four elements (see bn_fwd_odd_kernel): X and dY staged, the sums and that of the stored dX over
+// single elements in order.
+template <typename T, int NT, int BYTES>
+__global__ __launch_bounds__(NT) void bn_bwd_odd_kernel(BnBwdArgs p) {
+  __shared__ float sh[NT / 64][2];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
+  const int c = blockIdx.x, b = blockIdx.y, k = b * p.C + c;
+  const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
+  const T* dy = reinterpret_cast<const T*>(p.dY) + b * p.dysb + c * p.dysc;
+  T* dx = reinterpret_cast<T*>(p.dX) + b * p.dxsb + c * p.dxsc;
+  const int chunks = (p.L + 3) / 4, pitch = chunks * 4;
+  T* lx = reinterpret_cast<T*>(smem);
+  T* ld = lx + p.Nb * pitch;
+  bn_stage<T, NT>(lx, x, p.xsn, p.Nb, p.L, chunks);
+  bn_stage<T, NT>(ld, dy, p.dysn, p.Nb, p.L, chunks);
+  const float mean = p.save_mean[k], invstd = p.save_invstd[k], g = p.gamma[k], bt = p.beta[k];
+  __syncthreads();
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll 8
+  for (RowWalk w(p.L, NT); w.n < p.Nb; w.step()) {
+    const int at = w.n * pitch + w.ch;
+    const float xh = (Elem<T>::load(lx + at) - mean) * invstd;
+    const float gr = Elem<T>::load(ld + at) * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+    s1 += gr;
+    s2 = fmaf(gr, xh, s2);
+  }
+  block_sum2<NT / 64>(s1, s2, sh);
+  if (threadIdx.x == 0) { p.dbeta[k] = s1; p.dgamma[k] = s2; }
+  const float m = (float)p.Nb * (float)p.L;
+  const float mb = s1 / m, mg = s2 / m, sc = g * invstd;
+  for (RowWalk w(chunks, NT); w.n < p.Nb; w.step()) {
+    T* at = lx + (w.n * chunks + w.ch) * 4;
+    float v[4], d[4];
+    load_vec<T, 4>(at, v);
+    load_vec<T, 4>(ld + (w.n * chunks + w.ch) * 4, d);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float xh = (v[e] - mean) * invstd;
+      const float gr = d[e] * act_grad(fmaf(g, xh, bt), p.act, p.slope);
+      v[e] = sc * (gr - mb - xh * mg);
+    }
+    store_piece<T, 4, true>(dx + w.n * p.dxsn, w.ch, p.L, v);
+    if (p.dx_sum) store_vec<T, 4>(at, v);
+  }
+  if (p.dx_sum) {                        // uniform over the grid
+    __syncthreads();
+    float s3 = 0.f, dummy = 0.f;
+#pragma unroll 8
+    for (RowWalk w(p.L, NT); w.n < p.Nb; w.step()) s3 += Elem<T>::load(lx + w.n * pitch + w.ch);
     block_sum2<NT / 64>(s3, dummy, sh);
     if (threadIdx.x == 0) p.dx_sum[k] = s3;
   }
@@ -565,21 +691,20 @@ template <typename T> bool held_rows_ok(int Nb, int L, int64_t sn0, int64_t sn1)
 
 // How many pieces a thread holds.  All of a channel if they fit with two 1024-thread workgroups per compute unit, else what
 // does: us with nothing held -> now, and what the other choice takes:
-//   forward   bf16 6 x 16 x 2500, 2048 channels 538 -> 446, 128 channels 31 -> 26 (rows of 2497: 118 -> 29, most of it from
-//             four-element pieces); 8 x 32 x 2500, 64 channels 39 -> 31; fp32 4 x 32 x 2500, 128 channels 81 -> 69 with 9 of
+//   forward   bf16 6 x 16 x 2500, 2048 channels 538 -> 446, 128 channels 31 -> 26; 8 x 32 x 2500, 64 channels 39 -> 31; fp32 4 x 32 x 2500, 128 channels 81 -> 69 with 9 of
 //             20 held, 76 with all 20 and one workgroup per unit, which wins where all channels run at once: 64 channels
 //             38 -> 27, 34 with 9.
-//   backward  the same tensors: 741 -> 588 (777 with both operands in registers and one workgroup per unit), 50 -> 38
-//             (159 -> 41), 62 -> 54; fp32 62 -> 52 and 155 -> 126 with 10 of 20 held in registers, 56 and 137 with 5 in LDS,
-//             which wins where 5 are most of the channel (32 x 1023: 41 against 43).
+//   backward  the same tensors: 741 -> 588 (777 with both operands in registers and one workgroup per unit), 50 -> 38,
+//             62 -> 54; fp32 62 -> 52 and 155 -> 126 with 10 of 20 held in registers, 56 and 137 with 5 in LDS,
+//             which wins where 5 are most of the channel (32 x 1024: 41 against 43).
 // Past 40 pieces too little of a channel is held to pay for the wavefronts (2 x 64 channels of 100 x 4096 bf16: forward
 // 77 us with nothing held, 95 with 20 of 100, backward 125 and 131).
 constexpr int HELD_MOST = 40;
-template <typename T, int NT, bool RAG>
+template <typename T, int NT>
 void launch_bn_fwd(const BnFwdArgs& a, dim3 grid, hipStream_t st) {
-  constexpr int HALF = sizeof(T) == 2 ? 20 : RAG ? 8 : 9, FULL = sizeof(T) == 2 ? HALF : RAG ? 17 : 20;
+  constexpr int HALF = sizeof(T) == 2 ? 20 : 9, FULL = sizeof(T) == 2 ? HALF : 20;
   const int per = a.Y ? held_pieces(a.Nb, a.L, NT) : 0;            // statistics alone: read once
-#define HFTA_HELD(N) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 4, NT, RAG, N>), grid, dim3(NT), 0, st, a, per)
+#define HFTA_HELD(N) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 4, NT, N>), grid, dim3(NT), 0, st, a, per)
   if (per == 0 || per > HELD_MOST || !held_rows_ok<T>(a.Nb, a.L, a.xsn, 0)) HFTA_HELD(0);
   else if (per <= 4) HFTA_HELD(4);
   else if (per <= HALF / 2) HFTA_HELD(HALF / 2);
@@ -587,11 +712,11 @@ void launch_bn_fwd(const BnFwdArgs& a, dim3 grid, hipStream_t st) {
   else HFTA_HELD((NT == 256 ? HALF : FULL));
 #undef HFTA_HELD
 }
-template <typename T, int NT, bool RAG>
+template <typename T, int NT>
 void launch_bn_bwd(const BnBwdArgs& a, dim3 grid, hipStream_t st) {
-  constexpr int W = (int)sizeof(T), REGS = RAG ? 9 : 10;
+  constexpr int W = (int)sizeof(T), REGS = 10;
   const int per = held_pieces(a.Nb, a.L, NT);
-#define HFTA_HELD(N, XL) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 4, NT, RAG, N, XL>), grid, dim3(NT), 0, st, a, per)
+#define HFTA_HELD(N, XL) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 4, NT, N, XL>), grid, dim3(NT), 0, st, a, per)
   if (per > HELD_MOST || !held_rows_ok<T>(a.Nb, a.L, a.xsn, a.dysn)) HFTA_HELD(0, false);
   else if constexpr (NT == 256) {
     if (per <= 4) HFTA_HELD(4, false);
@@ -606,25 +731,49 @@ void launch_bn_bwd(const BnBwdArgs& a, dim3 grid, hipStream_t st) {
   }
 #undef HFTA_HELD
 }
-// The kernel of the row form: aligned four-element pieces (v4), pieces of rows of any length and alignment, or, for rows
-// shorter than one piece, single elements.
+// The kernel of the row form: aligned four-element pieces (v4); single elements in order, staged in LDS where the channel fits,
+// else from memory.  us with the element loads from memory -> staged: 6 x 16 x 2497 points bf16, 2048 channels forward 1766 -> 605,
+// backward 2435 -> 1294, 128 channels 116 -> 45 and 157 -> 87, 6 x 24 x 607, 128 channels 49 -> 24 and 69 -> 48.  Memory stays where
+// a thread has few elements (2 x 5 x 331 backward 9.5, staged 11.7) and for the fp32 backward, whose elements are a lane's four
+// bytes either way (3 x 13 x 1023, 128 channels 28.2, staged 29.0; the forward, which reads them twice, 21.4 -> 18.4).
+constexpr int ODD_MIN = 8;                               // elements per thread from which a channel is staged
 template <typename T>
 void launch_bn_fwd_rows(const BnFwdArgs& a, int B, bool v4, hipStream_t st) {
   const dim3 grid((unsigned)a.C, (unsigned)B);
+  const int64_t bytes = (int64_t)a.Nb * ((a.L + 3) / 4) * 4 * (int64_t)sizeof(T);      // staged
   const bool big = bn_wide_block((int64_t)a.Nb * a.L * (int64_t)sizeof(T));
-  if (v4) big ? launch_bn_fwd<T, 1024, false>(a, grid, st) : launch_bn_fwd<T, 256, false>(a, grid, st);
-  else if (a.L >= 4) big ? launch_bn_fwd<T, 1024, true>(a, grid, st) : launch_bn_fwd<T, 256, true>(a, grid, st);
-  else if (big) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 1024, false, 0>), grid, dim3(1024), 0, st, a, 0);
-  else hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 256, false, 0>), grid, dim3(256), 0, st, a, 0);
+  if (v4) big ? launch_bn_fwd<T, 1024>(a, grid, st) : launch_bn_fwd<T, 256>(a, grid, st);
+  else if (a.L >= 4 && bytes <= STAGE_FULL && (int64_t)a.Nb * a.L >= ODD_MIN * (big ? 1024 : 256)) {
+#define HFTA_ODD(NT, N) hipLaunchKernelGGL((bn_fwd_odd_kernel<T, NT, N>), grid, dim3(NT), 0, st, a)
+    // (rows of five elements take eight places: a small channel can need more than its 32 KB)
+    if (big && bytes <= STAGE_HALF) HFTA_ODD(1024, STAGE_HALF);
+    else if (big) HFTA_ODD(1024, STAGE_FULL);
+    else if (bytes <= STAGE_SMALL) HFTA_ODD(256, STAGE_SMALL);
+    else if (bytes <= STAGE_MID) HFTA_ODD(256, STAGE_MID);
+    else if (bytes <= STAGE_HALF) HFTA_ODD(256, STAGE_HALF);
+    else HFTA_ODD(256, STAGE_FULL);
+#undef HFTA_ODD
+  } else if (big) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 1024, 0>), grid, dim3(1024), 0, st, a, 0);
+  else hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 256, 0>), grid, dim3(256), 0, st, a, 0);
 }
 template <typename T>
 void launch_bn_bwd_rows(const BnBwdArgs& a, int B, bool v4, hipStream_t st) {
   const dim3 grid((unsigned)a.C, (unsigned)B);
+  const int64_t bytes = 2 * (int64_t)a.Nb * ((a.L + 3) / 4) * 4 * (int64_t)sizeof(T);      // staged
   const bool big = bn_wide_block((int64_t)a.Nb * a.L * (int64_t)sizeof(T));
-  if (v4) big ? launch_bn_bwd<T, 1024, false>(a, grid, st) : launch_bn_bwd<T, 256, false>(a, grid, st);
-  else if (a.L >= 4) big ? launch_bn_bwd<T, 1024, true>(a, grid, st) : launch_bn_bwd<T, 256, true>(a, grid, st);
-  else if (big) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 1024, false, 0, false>), grid, dim3(1024), 0, st, a, 0);
-  else hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 256, false, 0, false>), grid, dim3(256), 0, st, a, 0);
+  if (v4) big ? launch_bn_bwd<T, 1024>(a, grid, st) : launch_bn_bwd<T, 256>(a, grid, st);
+  else if (sizeof(T) == 2 && a.L >= 4 && bytes <= STAGE_FULL && (int64_t)a.Nb * a.L >= ODD_MIN * (big ? 1024 : 256)) {
+#define HFTA_ODD(NT, N) hipLaunchKernelGGL((bn_bwd_odd_kernel<T, NT, N>), grid, dim3(NT), 0, st, a)
+    // (rows of five elements take eight places: a small channel can need more than its 32 KB)
+    if (big && bytes <= STAGE_HALF) HFTA_ODD(1024, STAGE_HALF);
+    else if (big) HFTA_ODD(1024, STAGE_FULL);
+    else if (bytes <= STAGE_SMALL) HFTA_ODD(256, STAGE_SMALL);
+    else if (bytes <= STAGE_MID) HFTA_ODD(256, STAGE_MID);
+    else if (bytes <= STAGE_HALF) HFTA_ODD(256, STAGE_HALF);
+    else HFTA_ODD(256, STAGE_FULL);
+#undef HFTA_ODD
+  } else if (big) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 1024, 0, false>), grid, dim3(1024), 0, st, a, 0);
+  else hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 256, 0, false>), grid, dim3(256), 0, st, a, 0);
 }
 
 bool vec_ok(const void* p, const int64_t* s, int L, int dtype) {

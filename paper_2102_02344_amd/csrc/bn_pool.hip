@@ -27,34 +27,32 @@ struct BnPoolFwdArgs {
   float eps, momentum, slope;
 };
 
-template <typename T, int VEC, int NT, bool RAG>
+template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
   constexpr int NW = NT / 64, UN = bn_unroll(VEC);
   __shared__ float sh[NW][2];
   const int c = blockIdx.x, b = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const T* x = reinterpret_cast<const T*>(p.X) + b * p.xsb + c * p.xsc;
-  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
+  const int chunks = p.L / VEC;
   const float shift = Elem<T>::load(x);
   float s1 = 0.f, s2 = 0.f;
   // same element -> thread assignment and reduction order as the stand-alone BatchNorm forward,
   // so the statistics (and with them every activated value) come out bit-identical
   for (RowWalk w(chunks, NT); w.n < p.Nb;) {
     float v[UN][VEC];
-    int ch[UN];
     bool ok[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      ok[u] = w.n < p.Nb; ch[u] = w.ch;
-      load_piece<T, VEC, RAG>(ok[u] ? x + w.n * p.xsn : x, ok[u] ? w.ch : 0, p.L, v[u]);
+      ok[u] = w.n < p.Nb;
+      load_vec<T, VEC>(ok[u] ? x + w.n * p.xsn + w.ch * VEC : x, v[u]);
       w.step();
     }
 #pragma unroll
     for (int u = 0; u < UN; ++u)
       if (ok[u]) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          if (!RAG || ch[u] * VEC + e < p.L) { const float d = v[u][e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
+        for (int e = 0; e < VEC; ++e) { const float d = v[u][e] - shift; s1 += d; s2 = fmaf(d, d, s2); }
       }
   }
   block_sum2<NW>(s1, s2, sh);
@@ -82,7 +80,7 @@ __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
     for (int c0 = lane; c0 < chunks; c0 += 64 * UN) {
       float v[UN][VEC];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) load_piece<T, VEC, RAG>(row, min(c0 + 64 * u, chunks - 1), p.L, v[u]);
+      for (int u = 0; u < UN; ++u) load_vec<T, VEC>(row + min(c0 + 64 * u, chunks - 1) * VEC, v[u]);
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
         const int ch = c0 + 64 * u;
@@ -91,7 +89,7 @@ __global__ __launch_bounds__(NT) void bn_fwd_maxpool_kernel(BnPoolFwdArgs p) {
           for (int e = 0; e < VEC; ++e) {
             // the activated value exactly as hfta_bn_fwd would have stored it
             const float y = Elem<T>::to_f32(Elem<T>::from_f32(bn_act(fmaf(g, (v[u][e] - mean) * invstd, bt), p.act, p.slope)));
-            if ((!RAG || ch * VEC + e < p.L) && (y > best || bi == 0x7fffffff)) { best = y; bi = ch * VEC + e; }
+            if (y > best || bi == 0x7fffffff) { best = y; bi = ch * VEC + e; }
           }
         }
       }
@@ -253,7 +251,7 @@ struct BnPoolBwdArgs {
   float slope;
 };
 
-template <typename T, int VEC, int NT, bool RAG>
+template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
   constexpr int NW = NT / 64, UN = bn_unroll(VEC);
   __shared__ float sh[NW][2];
@@ -277,7 +275,7 @@ __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
   if (threadIdx.x == 0) { p.dbeta[k] = s1; p.dgamma[k] = s2; }
   const float m = (float)p.Nb * (float)p.L;
   const float mb = s1 / m, mg = s2 / m, sc = g * invstd;
-  const int chunks = RAG ? (p.L + VEC - 1) / VEC : p.L / VEC;
+  const int chunks = p.L / VEC;
   float s3 = 0.f;
   for (int n = wave; n < p.Nb; n += NW) {
     const T* row = x + n * p.xsn;
@@ -287,7 +285,7 @@ __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
     for (int c0 = lane; c0 < chunks; c0 += 64 * UN) {
       float v[UN][VEC];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) load_piece<T, VEC, RAG>(row, min(c0 + 64 * u, chunks - 1), p.L, v[u]);
+      for (int u = 0; u < UN; ++u) load_vec<T, VEC>(row + min(c0 + 64 * u, chunks - 1) * VEC, v[u]);
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
         const int ch = c0 + 64 * u;
@@ -298,9 +296,9 @@ __global__ __launch_bounds__(NT) void bn_bwd_maxpool_kernel(BnPoolBwdArgs p) {
             float gr = 0.f;
             if (ch * VEC + e == hit) gr = gv * act_grad(fmaf(g, xh, bt), p.act, p.slope);
             v[u][e] = sc * (gr - mb - xh * mg);
-            if (!RAG || ch * VEC + e < p.L) s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[u][e]));
+            s3 += Elem<T>::to_f32(Elem<T>::from_f32(v[u][e]));
           }
-          store_piece<T, VEC, RAG>(drow, ch, p.L, v[u]);
+          store_vec<T, VEC>(drow + ch * VEC, v[u]);
         }
       }
     }
@@ -434,10 +432,11 @@ int hfta_bn_fwd_maxpool(int B, int Nb, int C, int L, int dtype, const void* X, c
   hipStream_t st = as_stream(stream);
   const bool v4 = bn_vec4_ok(X, xs, L, dtype);
   const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_LAUNCH(T, V_, R) \
-  do { if (big) hipLaunchKernelGGL((bn_fwd_maxpool_kernel<T, V_, 1024, R>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_fwd_maxpool_kernel<T, V_, 256, R>), grid, dim3(256), 0, st, a); } while (0)
-  HFTA_BN_BY_ROWS(HFTA_LAUNCH);
+#define HFTA_LAUNCH(T, V_) \
+  do { if (big) hipLaunchKernelGGL((bn_fwd_maxpool_kernel<T, V_, 1024>), grid, dim3(1024), 0, st, a); \
+       else hipLaunchKernelGGL((bn_fwd_maxpool_kernel<T, V_, 256>), grid, dim3(256), 0, st, a); } while (0)
+  if (dtype == HFTA_BF16) { if (v4) HFTA_LAUNCH(bf16_raw, 4); else HFTA_LAUNCH(bf16_raw, 1); }
+  else { if (v4) HFTA_LAUNCH(float, 4); else HFTA_LAUNCH(float, 1); }
 #undef HFTA_LAUNCH
   return launch_status();
 }
@@ -456,10 +455,11 @@ int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype, const void* X, c
   hipStream_t st = as_stream(stream);
   const bool v4 = bn_vec4_ok(X, xs, L, dtype) && bn_vec4_ok(dX, dxs, L, dtype);
   const bool big = bn_wide_block((int64_t)Nb * L * dtype_size(dtype));
-#define HFTA_LAUNCH(T, V_, R) \
-  do { if (big) hipLaunchKernelGGL((bn_bwd_maxpool_kernel<T, V_, 1024, R>), grid, dim3(1024), 0, st, a); \
-       else hipLaunchKernelGGL((bn_bwd_maxpool_kernel<T, V_, 256, R>), grid, dim3(256), 0, st, a); } while (0)
-  HFTA_BN_BY_ROWS(HFTA_LAUNCH);
+#define HFTA_LAUNCH(T, V_) \
+  do { if (big) hipLaunchKernelGGL((bn_bwd_maxpool_kernel<T, V_, 1024>), grid, dim3(1024), 0, st, a); \
+       else hipLaunchKernelGGL((bn_bwd_maxpool_kernel<T, V_, 256>), grid, dim3(256), 0, st, a); } while (0)
+  if (dtype == HFTA_BF16) { if (v4) HFTA_LAUNCH(bf16_raw, 4); else HFTA_LAUNCH(bf16_raw, 1); }
+  else { if (v4) HFTA_LAUNCH(float, 4); else HFTA_LAUNCH(float, 1); }
 #undef HFTA_LAUNCH
   return launch_status();
 }

@@ -1,6 +1,6 @@
 """Training BatchNorm whose channels stay on chip between its passes, where the number of four-element pieces a thread holds
-changes kernel: one piece short of a full thread and one past it, rows of any length and alignment, channels that fit in part,
-in neither, and launches of more channels than compute units."""
+or the size staged for rows of other lengths changes kernel: one piece short of a full thread and one past it, channels that fit
+in part or not at all, launches of more channels than compute units, short rows whose places outnumber their elements."""
 import pytest
 import torch
 
@@ -16,9 +16,9 @@ def hb():
 
 
 # (Nb, L): pieces a thread has at 256 threads (channels below 32 KB) and at 1024
-BF16 = [(1, 2052), (4, 1028), (3, 1363), (5, 2049), (7, 2338), (4, 4096), (4, 4100), (10, 4096), (10, 4099), (17, 2411), (20, 4096),
-        (20, 4101), (40, 4096), (41, 4095)]
-F32 = [(1, 1024), (1, 4100), (3, 1363), (5, 1639), (2, 4096), (5, 4096), (5, 4099), (9, 4096), (9, 4099), (10, 4097), (17, 4095),
+BF16 = [(1, 5), (2, 6), (3200, 5), (1630, 6), (1, 2052), (4, 1028), (3, 1363), (5, 2049), (7, 2338), (4, 4096), (4, 4100), (10, 4096), (10, 4099), (17, 2411), (20, 4096),
+        (20, 4101), (40, 4096), (41, 4095), (10, 1021), (8, 2541), (16, 2549)]
+F32 = [(1, 5), (1600, 5), (850, 9), (1, 1024), (1, 4100), (3, 1363), (5, 1639), (2, 4096), (5, 4096), (5, 4099), (9, 4096), (9, 4099), (10, 4097), (17, 4095),
        (17, 4097), (20, 4096), (20, 4098), (41, 4097)]
 
 
