@@ -416,42 +416,48 @@ size_t ig_lds_bytes(const IgArgs& a) {
 // matrix instructions consume them:
 //   Wp[b][class][row tile][k-tile][32-row block][k-step (16 k)][lane][8 k],
 //   lane = 32 (k half) + row inside the block; rows past Ci and k past 4 Co are zeros.
-// One thread per 16-byte fragment piece: 8 k = the class's 2x2 taps of two output channels of one
-// input channel, read as two 32-byte windows; consecutive lanes read consecutive channels and
-// write consecutive pieces.
+// One thread per 16-byte fragment piece of all four classes: 8 k = a class's 2x2 taps of two output channels of one input
+// channel, and the 16 taps of the two are read once for the four.  A thread per class read them four times and found its place
+// with 64-bit divisions: 10 x 512 x 256 channels 24 -> 17 us, 3 models 8.4 -> 6.  Consecutive lanes read consecutive channels and write
+// consecutive pieces.  grid.y: the model.
 __global__ __launch_bounds__(256) void ig_pack_class_w_kernel(const bf16_raw* __restrict__ Wt, bf16_raw* __restrict__ Wp, int Ci,
-                                                              int Co, int tm, int tiles_m, int ktiles, int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= count) return;
-  const int lane = (int)(i & 63), s2 = (int)((i >> 6) & 1);
-  int64_t r = i >> 7;
-  const int rbs = tm / 32;
-  const int rb = (int)(r % rbs); r /= rbs;
-  const int kt = (int)(r % ktiles); r /= ktiles;
-  const int tile_m = (int)(r % tiles_m); r /= tiles_m;
-  const int cls = (int)(r & 3);
-  const int64_t b = r >> 2;
+                                                              int Co, int tm, int ktiles, uint32_t pieces) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;                // piece of one class of one model
+  if (i >= pieces) return;
+  const int64_t b = blockIdx.y;
+  const int lane = (int)(i & 63u), s2 = (int)((i >> 6) & 1u);
+  uint32_t r = i >> 7;
+  const uint32_t rbs = (uint32_t)tm >> 5;                            // 2 or 4
+  const int rb = (int)(r & (rbs - 1u));
+  r = rbs == 4 ? r >> 2 : r >> 1;
+  const int tile_m = (int)(r / (uint32_t)ktiles), kt = (int)(r - (uint32_t)tile_m * (uint32_t)ktiles);
   const int c = tile_m * tm + rb * 32 + (lane & 31);
   const int o0 = (kt * 32 + s2 * 16 + (lane >> 5) * 8) >> 2;       // two output channels: o0, o0 + 1
-  const int py = cls >> 1, px = cls & 1;
-  const int ry = (py + 1) & 1, rx = (px + 1) & 1;
-  uint32_t out[4] = {0u, 0u, 0u, 0u};
+  uint32_t w[2][4][2] = {};                                // rows ky = 0 .. 3; two taps per 32-bit word
   if (c < Ci) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       if (o0 + q < Co) {
         const uint4* src = reinterpret_cast<const uint4*>(Wt + ((b * Co + o0 + q) * Ci + c) * 16);
-        const uint4 lo = src[0], hi = src[1];              // rows ky = 0, 1 | 2, 3; two taps per 32-bit word
-        const uint32_t w[4][2] = {{lo.x, lo.y}, {lo.z, lo.w}, {hi.x, hi.y}, {hi.z, hi.w}};
-        auto tap = [&](int ky, int kx) { return (w[ky][kx >> 1] >> (16 * (kx & 1))) & 0xffffu; };
-        out[2 * q] = tap(ry + 2, rx + 2) | (tap(ry + 2, rx) << 16);      // (jy, jx) = (0, 0), (0, 1)
-        out[2 * q + 1] = tap(ry, rx + 2) | (tap(ry, rx) << 16);          // (1, 0), (1, 1)
+        const uint4 lo = src[0], hi = src[1];
+        w[q][0][0] = lo.x; w[q][0][1] = lo.y; w[q][1][0] = lo.z; w[q][1][1] = lo.w;
+        w[q][2][0] = hi.x; w[q][2][1] = hi.y; w[q][3][0] = hi.z; w[q][3][1] = hi.w;
       }
     }
   }
-  *reinterpret_cast<uint4*>(Wp + i * 8) = make_uint4(out[0], out[1], out[2], out[3]);
+#pragma unroll
+  for (int cls = 0; cls < 4; ++cls) {
+    const int ry = ((cls >> 1) + 1) & 1, rx = ((cls & 1) + 1) & 1;
+    uint32_t out[4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      auto tap = [&](int ky, int kx) { return (w[q][ky][kx >> 1] >> (16 * (kx & 1))) & 0xffffu; };
+      out[2 * q] = tap(ry + 2, rx + 2) | (tap(ry + 2, rx) << 16);      // (jy, jx) = (0, 0), (0, 1)
+      out[2 * q + 1] = tap(ry, rx + 2) | (tap(ry, rx) << 16);          // (1, 0), (1, 1)
+    }
+    *reinterpret_cast<uint4*>(Wp + ((b * 4 + cls) * (int64_t)pieces + i) * 8) = make_uint4(out[0], out[1], out[2], out[3]);
+  }
 }
-
 
 #include "conv2d_rows.h"
 
@@ -620,9 +626,10 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   const size_t lds = planes ? dxp_lds_bytes(a) : ig_lds_bytes(a);
   if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
   if ((int64_t)tiles_m * a.tiles_n > 0x7fffffff) return HFTA_EUNSUPPORTED;
-  const int64_t count = (int64_t)B * 4 * cls_el / 8;                   // 16-byte fragment pieces
-  hipLaunchKernelGGL(ig_pack_class_w_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, (const bf16_raw*)Wt,
-                     (bf16_raw*)pack, Ci, Co, tm, tiles_m, ktiles, count);
+  const int64_t pieces = cls_el / 8;                                   // 16-byte fragment pieces
+  if (pieces > 0x7fffffff) return HFTA_EUNSUPPORTED;
+  hipLaunchKernelGGL(ig_pack_class_w_kernel, dim3((unsigned)((pieces + 255) / 256), (unsigned)B), dim3(256), 0, st, (const bf16_raw*)Wt,
+                     (bf16_raw*)pack, Ci, Co, tm, ktiles, (uint32_t)pieces);
   a.ksplit = 1;
   a.kt_per_split = ktiles;
   dim3 grid((unsigned)(tiles_m * a.tiles_n), 2u, (unsigned)B);
