@@ -7,62 +7,93 @@
 //     S(0) = {(1,1), (3,0)},  S(1) = {(0,2), (2,1)}
 // One thread owns one q pixel: the 2x2 output block of every channel (4 Ci accumulators) against the
 // 3x3 neighbourhood of dY, 16 Ci multiply-adds per output channel o.  A workgroup covers 32 x 8 q
-// pixels; dY goes through LDS eight channels at a time (10 x 34 halo tile); the weights are the same
+// pixels; dY goes through LDS sixteen channels at a time (10 x 36 halo tile); the weights are the same
 // for every thread of a workgroup and are read with scalar loads (they occupy the scalar unit and
 // scalar registers, not LDS bandwidth or vector instructions).
-#include "common.h"
+//
+// The halo travels in pairs of columns (4 bytes) by buffer loads whose addresses are formed once: element by element, with the
+// places worked out for each eight channels anew, the staging cost more vector instructions than the multiply-adds, and a
+// launch of one workgroup per compute unit waited for eight round trips to memory instead of four, and for the scalar unit in
+// every channel (see the loop).  3 x 20 samples of 64 -> 3 channels at 64 x 64: 44 -> 30 us; 10 x 64 fill the chip and are bound by
+// LDS reads and multiply-adds, 117 us either way.  Rows of an odd number of q pixels, or not on 4 bytes, keep the elements.
+#include "gemm_pf.h"
 
 namespace hfta {
 
 namespace {
 
-constexpr int FC_TX = 32, FC_TY = 8, FC_OC = 8;            // q tile, channels of dY per LDS stage
-constexpr int FC_PW = FC_TX + 2 + 2;                       // halo row pitch (elements)
+constexpr int FC_TX = 32, FC_TY = 8;                       // q tile
+constexpr int FC_PW = FC_TX + 2 + 2;                       // halo row pitch (elements): columns -2 .. 33
 
 struct FewcArgs {
   const bf16_raw* Wt; const bf16_raw* dY; bf16_raw* dX;
   int B, Nb, Co, H, W, Hq, Wq, tiles_x;
 };
 
-template <int CI>
+template <int CI, bool PAIR>
 __global__ __launch_bounds__(256) void conv_dx_fewc_kernel(FewcArgs p) {
+  constexpr int FC_OC = PAIR ? 16 : 8;                     // channels of dY per LDS stage
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_raw* tile = reinterpret_cast<bf16_raw*>(smem);                           // [2][FC_OC][FC_TY + 2][FC_PW]
   const int t = threadIdx.x, tx = t & (FC_TX - 1), ty = t >> 5;
   const int qx0 = (blockIdx.x % p.tiles_x) * FC_TX, qy0 = (blockIdx.x / p.tiles_x) * FC_TY;
   const int n = blockIdx.y, b = blockIdx.z;
-  const int64_t P = (int64_t)p.Hq * p.Wq;
+  const int P = p.Hq * p.Wq;
   const bf16_raw* dy = p.dY + ((int64_t)n * p.B + b) * p.Co * P;
   const uint32_t* __restrict__ w2 = reinterpret_cast<const uint32_t*>(p.Wt + (int64_t)b * p.Co * CI * 16);   // pairs (kx, kx + 1)
 
   constexpr int TILE_EL = FC_OC * (FC_TY + 2) * FC_PW;
-  constexpr int PER_THREAD = (FC_OC * (FC_TY + 2) * (FC_TX + 2) + 255) / 256;
-  bf16_raw stage[PER_THREAD];
-  auto fetch = [&](int o0) {
+  constexpr int COLS = PAIR ? FC_PW / 2 : FC_TX + 2, UNITS = FC_OC * (FC_TY + 2) * COLS;      // pairs or elements per stage
+  constexpr int PER_THREAD = (UNITS + 255) / 256;
+  uint32_t stage[PER_THREAD], from[PER_THREAD], to[PER_THREAD];
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int e = t + 256 * i;
-      const int col = e % (FC_TX + 2), r = e / (FC_TX + 2);
-      const int row = r % (FC_TY + 2), oc = r / (FC_TY + 2);
-      const int y = qy0 - 1 + row, x = qx0 - 1 + col, o = o0 + oc;
-      const bool ok = oc < FC_OC && o < p.Co && y >= 0 && y < p.Hq && x >= 0 && x < p.Wq;
-      const bf16_raw v = dy[ok ? (int64_t)o * P + (int64_t)y * p.Wq + x : 0];     // always a valid address: no load under a branch
-      stage[i] = ok ? v : (bf16_raw)0;
-    }
+  for (int i = 0; i < PER_THREAD; ++i) {
+    const int e = t + 256 * i;
+    const int col = e % COLS, r = e / COLS;
+    const int row = r % (FC_TY + 2), oc = r / (FC_TY + 2);
+    const int y = qy0 - 1 + row, x = qx0 + (PAIR ? 2 * col - 2 : col - 1);
+    const bool ok = oc < FC_OC && y >= 0 && y < p.Hq && x >= 0 && x < p.Wq;
+    from[i] = ok ? ((uint32_t)oc * (uint32_t)P + (uint32_t)(y * p.Wq + x)) * 2u : PF_OOB;                 // out of range: zeros, no memory request
+    to[i] = (uint32_t)((oc * (FC_TY + 2) + row) * FC_PW + (PAIR ? 2 * col : col + 1));
+  }
+  const __amdgpu_buffer_rsrc_t rs = pf_rsrc(dy, (uint32_t)((int64_t)p.Co * P * 2));   // channels past the last: zeros too
+  auto fetch = [&](int o0) {
+    const uint32_t at = (uint32_t)o0 * (uint32_t)P * 2u;
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i)
+      stage[i] = PAIR ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(from[i] + at), 0, 0)
+                      : (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(from[i] + at), 0, 0);
   };
   auto park = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int e = t + 256 * i;
-      const int col = e % (FC_TX + 2), r = e / (FC_TX + 2);
-      const int row = r % (FC_TY + 2), oc = r / (FC_TY + 2);
-      if (oc < FC_OC) tile[buf * TILE_EL + (oc * (FC_TY + 2) + row) * FC_PW + col] = stage[i];
-    }
+    for (int i = 0; i < PER_THREAD; ++i)
+      if (UNITS % 256 == 0 || t + 256 * i < UNITS) {
+        if (PAIR) *reinterpret_cast<uint32_t*>(tile + buf * TILE_EL + to[i]) = stage[i];
+        else tile[buf * TILE_EL + to[i]] = (bf16_raw)stage[i];
+      }
   };
 
   float acc[CI][2][2];
 #pragma unroll
   for (int c = 0; c < CI; ++c) acc[c][0][0] = acc[c][0][1] = acc[c][1][0] = acc[c][1][1] = 0.f;
+
+  bf16_raw dn[3][3];
+  uint32_t wn[CI * 8];
+  // the three columns one by one: two neighbours in one 4-byte read are off four bytes in every other lane, which costs launches
+  // that fill the chip twice the time
+  int at[3] = {tx + 1, tx + 2, tx + 3};
+#pragma unroll
+  for (int s = 0; s < 3; ++s) asm("" : "+v"(at[s]));
+  auto issue = [&](int o0, int buf, int oc) {
+    const bf16_raw* tp = tile + buf * TILE_EL + (oc * (FC_TY + 2) + ty) * FC_PW;
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int s = 0; s < 3; ++s) dn[r][s] = tp[r * FC_PW + at[s]];
+    const uint32_t* wq = w2 + (size_t)(o0 + oc) * CI * 8;        // uniform address: scalar loads
+#pragma unroll
+    for (int k = 0; k < CI * 8; ++k) wn[k] = wq[k];
+  };
 
   fetch(0);
   park(0);
@@ -71,22 +102,28 @@ __global__ __launch_bounds__(256) void conv_dx_fewc_kernel(FewcArgs p) {
   for (int o0 = 0; o0 < p.Co; o0 += FC_OC) {
     const bool more = o0 + FC_OC < p.Co;
     if (more) fetch(o0 + FC_OC);
+    // the weights and the neighbourhood of an output channel are on their way while the one before is multiplied: a scalar
+    // load's round trip is longer than a channel's multiply-adds
+    const int last = min(FC_OC, p.Co - o0) - 1;
+    issue(o0, buf, 0);
 #pragma unroll 2
-    for (int oc = 0; oc < FC_OC; ++oc) {
-      if (o0 + oc >= p.Co) break;
-      const bf16_raw* tp = tile + buf * TILE_EL + (oc * (FC_TY + 2) + ty) * FC_PW + tx;
+    for (int oc = 0; oc <= last; ++oc) {
       float d[3][3];
+      uint32_t w[CI * 8];
 #pragma unroll
       for (int r = 0; r < 3; ++r)
 #pragma unroll
-        for (int s = 0; s < 3; ++s) d[r][s] = bf16_to_f32(tp[r * FC_PW + s]);
-      const uint32_t* wq = w2 + (size_t)(o0 + oc) * CI * 8;      // uniform address: scalar loads
+        for (int s = 0; s < 3; ++s) d[r][s] = bf16_to_f32(dn[r][s]);
+#pragma unroll
+      for (int k = 0; k < CI * 8; ++k) w[k] = wn[k];
+      issue(o0, buf, min(oc + 1, last));
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int c = 0; c < CI; ++c) {
         float4 k[4];                                            // rows ky = 0..3
 #pragma unroll
         for (int ky = 0; ky < 4; ++ky) {
-          const uint32_t lo = wq[c * 8 + ky * 2], hi = wq[c * 8 + ky * 2 + 1];
+          const uint32_t lo = w[c * 8 + ky * 2], hi = w[c * 8 + ky * 2 + 1];
           k[ky] = make_float4(__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16),
                               __uint_as_float(hi & 0xffff0000u));
         }
@@ -99,6 +136,7 @@ __global__ __launch_bounds__(256) void conv_dx_fewc_kernel(FewcArgs p) {
         HFTA_FC4(acc[c][1][1], k0.x, d[2][2], k0.z, d[2][1], k2.x, d[1][2], k2.z, d[1][1]);
 #undef HFTA_FC4
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
     if (more) park(buf ^ 1);
     __syncthreads();
@@ -118,16 +156,19 @@ __global__ __launch_bounds__(256) void conv_dx_fewc_kernel(FewcArgs p) {
 }  // namespace
 
 bool conv_dx_fewc_supported(int Nb, int B, int Ci, int Co, int H, int W, int kh, int kw, int stride, int pad) {
-  return kh == 4 && kw == 4 && stride == 2 && pad == 1 && Ci >= 1 && Ci <= 4 && H % 2 == 0 && W % 2 == 0 && Nb <= 65535 && B <= 65535;
+  return kh == 4 && kw == 4 && stride == 2 && pad == 1 && Ci >= 1 && Ci <= 4 && H % 2 == 0 && W % 2 == 0 && Nb <= 65535 && B <= 65535 &&
+         (int64_t)Co * (H / 2) * (W / 2) * 2 < ((int64_t)1 << 31);                       // a sample's dY: one buffer
 }
 
 int conv_dx_fewc(int B, int Nb, int Ci, int Co, int H, int W, const void* Wt, const void* dY, void* dX, hipStream_t st) {
   if (reinterpret_cast<uintptr_t>(dX) % 4 != 0 || reinterpret_cast<uintptr_t>(Wt) % 4 != 0) return HFTA_EUNSUPPORTED;
   FewcArgs a{(const bf16_raw*)Wt, (const bf16_raw*)dY, (bf16_raw*)dX, B, Nb, Co, H, W, H / 2, W / 2, (W / 2 + FC_TX - 1) / FC_TX};
-  const size_t lds = 2 * FC_OC * (FC_TY + 2) * FC_PW * 2;
+  const bool pair = a.Wq % 2 == 0 && reinterpret_cast<uintptr_t>(dY) % 4 == 0;
+  const size_t lds = 2 * (pair ? 16 : 8) * (FC_TY + 2) * FC_PW * 2;
   const dim3 grid((unsigned)(a.tiles_x * ((a.Hq + FC_TY - 1) / FC_TY)), (unsigned)Nb, (unsigned)B);
 #define HFTA_FEWC(C) \
-  hipLaunchKernelGGL(conv_dx_fewc_kernel<C>, grid, dim3(256), lds, st, a)
+  do { if (pair) hipLaunchKernelGGL((conv_dx_fewc_kernel<C, true>), grid, dim3(256), lds, st, a); \
+       else hipLaunchKernelGGL((conv_dx_fewc_kernel<C, false>), grid, dim3(256), lds, st, a); } while (0)
   switch (Ci) {
     case 1: HFTA_FEWC(1); break;
     case 2: HFTA_FEWC(2); break;

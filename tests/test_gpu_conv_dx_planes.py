@@ -39,3 +39,21 @@ def test_data_gradient_of_tall_images(hb, B, Nb, Ci, Co):
     _, ws = ops.conv_workspaces(hb, "implicit", (B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1))
     hb.conv2d_grouped_bwd(B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1, dev(x, "bf16"), dev(w, "bf16"), dev(dy, "bf16"), dX, None, None, ws)
     check(host(dX), oa.conv2d_bwd(B, x, w, dy, 2, 1)[0], TOL["bf16"], "dX")
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,H,W,shift", [
+    (2, 3, 3, 64, 64, 64, 0), (1, 2, 1, 5, 6, 10, 0), (2, 2, 4, 33, 18, 70, 0), (1, 3, 2, 16, 34, 2, 0), (2, 1, 3, 17, 20, 132, 0),
+    (1, 2, 3, 16, 64, 68, 1)])
+def test_data_gradient_of_few_channels(hb, B, Nb, Ci, Co, H, W, shift):
+    """Up to four input channels: output channels short of a stage, rows of one, an odd and an even number of gradient columns,
+    tiles that end past the image, and a gradient that starts off four bytes."""
+    x = hi.normal(111, (Nb, B * Ci, H, W), "bf16")
+    w = hi.normal(112, (B * Co, Ci, 4, 4), "bf16", 1.0 / np.sqrt(Ci * 16))
+    dy = hi.normal(114, (Nb, B * Co, H // 2, W // 2), "bf16")
+    dX = ops.empty(x.shape, "bf16")
+    _, ws = ops.conv_workspaces(hb, "implicit", (B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1))
+    flat = dev(dy, "bf16").reshape(-1)
+    dY = flat.new_empty(flat.numel() + shift)[shift:]
+    dY.copy_(flat)
+    hb.conv2d_grouped_bwd(B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1, dev(x, "bf16"), dev(w, "bf16"), dY.view(dy.shape), dX, None, None, ws)
+    check(host(dX), oa.conv2d_bwd(B, x, w, dy, 2, 1)[0], TOL["bf16"], "dX")
