@@ -21,6 +21,24 @@ struct AdamArgs {
   int t, decoupled;
 };
 
+// The state passes through once a step: non-temporal, so that it does not push what the next forward reads -- the bf16 weights
+// written here, the batch -- out of the Infinity Cache.  Steps, us: residual MLP 10514 -> 10415, its small sweep 612 -> 604, language
+// model 1286 -> 1266, transforms 3898 -> 3863, small GAN 1242 -> 1223, classification 1384 -> 1374.
+template <bool NT> __device__ __forceinline__ float4 adam_ld(const float* p) {
+  typedef float f4v __attribute__((ext_vector_type(4)));
+  const f4v* q = reinterpret_cast<const f4v*>(p);
+  const f4v v = NT ? __builtin_nontemporal_load(q) : *q;
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+template <bool NT> __device__ __forceinline__ void adam_st(float* p, float4 a) {
+  typedef float f4v __attribute__((ext_vector_type(4)));
+  const f4v v = {a.x, a.y, a.z, a.w};
+  if (NT) __builtin_nontemporal_store(v, reinterpret_cast<f4v*>(p));
+  else *reinterpret_cast<f4v*>(p) = v;
+}
+// from 1.5 M parameters, 18 MB in three arrays: 0.8 M lose by it (185.2 -> 186.7 us a step), 2.4 M gain (422.6 -> 418.6)
+constexpr int64_t ADAM_NT_MIN = (int64_t)3 << 19;
+
 struct AdamHp { float lr, b1, b2, eps, wd, inv_bc1, inv_bc2; };
 
 __device__ __forceinline__ void adam_one(float& th, float g, float& m, float& v, const AdamHp& h, int decoupled) {
@@ -96,7 +114,7 @@ struct AdamMultiArgs {
 
 // Parameter-major arena: thread -> flat index -> (segment, model).  The bias
 // corrections of all B models are formed once per workgroup in double.
-template <typename G, bool VEC4>
+template <typename G, bool VEC4, bool NT>
 __global__ __launch_bounds__(256) void adam_multi_kernel(AdamMultiArgs p) {
   extern __shared__ float bc[];                   // [B][2]
   for (int b = threadIdx.x; b < p.B; b += 256) {
@@ -120,12 +138,12 @@ __global__ __launch_bounds__(256) void adam_multi_kernel(AdamMultiArgs p) {
   h.inv_bc1 = bc[2 * b]; h.inv_bc2 = bc[2 * b + 1];
   const G* gr = reinterpret_cast<const G*>(p.grad);
   if (VEC4) {
-    float4 th = *reinterpret_cast<float4*>(p.theta + i);
-    float4 m = *reinterpret_cast<float4*>(p.m + i);
-    float4 v = *reinterpret_cast<float4*>(p.v + i);
+    float4 th = adam_ld<NT>(p.theta + i);
+    float4 m = adam_ld<NT>(p.m + i);
+    float4 v = adam_ld<NT>(p.v + i);
     float g[4];
     if (sizeof(G) == 4) {
-      *reinterpret_cast<float4*>(g) = *reinterpret_cast<const float4*>(gr + i);
+      *reinterpret_cast<float4*>(g) = adam_ld<NT>((const float*)(gr + i));
     } else {
       const uint2 raw = *reinterpret_cast<const uint2*>(gr + i);
       g[0] = __uint_as_float(raw.x << 16); g[1] = __uint_as_float(raw.x & 0xffff0000u);
@@ -135,9 +153,9 @@ __global__ __launch_bounds__(256) void adam_multi_kernel(AdamMultiArgs p) {
     adam_one(th.y, g[1], m.y, v.y, h, p.decoupled);
     adam_one(th.z, g[2], m.z, v.z, h, p.decoupled);
     adam_one(th.w, g[3], m.w, v.w, h, p.decoupled);
-    *reinterpret_cast<float4*>(p.theta + i) = th;
-    *reinterpret_cast<float4*>(p.m + i) = m;
-    *reinterpret_cast<float4*>(p.v + i) = v;
+    adam_st<NT>(p.theta + i, th);
+    adam_st<NT>(p.m + i, m);
+    adam_st<NT>(p.v + i, v);
     if (p.lowp) {
       uint2 o;
       o.x = pack_bf16x2(th.x, th.y);
@@ -180,7 +198,7 @@ __device__ __forceinline__ void adam_locate(const AdamMultiArgs& p, int64_t i, i
 int64_t adam_odd_min(int B, int nseg) {
   return (14 << 16) + (B > 128 ? 0 : std::min((int64_t)B * nseg * 768, (int64_t)18 << 16));
 }
-template <typename G>
+template <typename G, bool NT>
 __global__ __launch_bounds__(256, 8) void adam_multi_odd_kernel(AdamMultiArgs p) {
   extern __shared__ float bc[];                   // [B][2]
   const int64_t i0 = (int64_t)blockIdx.x * 1024, i = i0 + threadIdx.x * 4;
@@ -211,12 +229,12 @@ __global__ __launch_bounds__(256, 8) void adam_multi_odd_kernel(AdamMultiArgs p)
     }
     return;
   }
-  float4 th = *reinterpret_cast<float4*>(p.theta + i);
-  float4 m = *reinterpret_cast<float4*>(p.m + i);
-  float4 v = *reinterpret_cast<float4*>(p.v + i);
+  float4 th = adam_ld<NT>(p.theta + i);
+  float4 m = adam_ld<NT>(p.m + i);
+  float4 v = adam_ld<NT>(p.v + i);
   float g[4];
   if (sizeof(G) == 4) {
-    *reinterpret_cast<float4*>(g) = *reinterpret_cast<const float4*>(gr + i);
+    *reinterpret_cast<float4*>(g) = adam_ld<NT>((const float*)(gr + i));
   } else {
     const uint2 raw = *reinterpret_cast<const uint2*>(gr + i);
     g[0] = __uint_as_float(raw.x << 16); g[1] = __uint_as_float(raw.x & 0xffff0000u);
@@ -227,9 +245,9 @@ __global__ __launch_bounds__(256, 8) void adam_multi_odd_kernel(AdamMultiArgs p)
   adam_one(th.y, g[1], m.y, v.y, h, p.decoupled);
   adam_one(th.z, g[2], m.z, v.z, h, p.decoupled);
   adam_one(th.w, g[3], m.w, v.w, h, p.decoupled);
-  *reinterpret_cast<float4*>(p.theta + i) = th;
-  *reinterpret_cast<float4*>(p.m + i) = m;
-  *reinterpret_cast<float4*>(p.v + i) = v;
+  adam_st<NT>(p.theta + i, th);
+  adam_st<NT>(p.m + i, m);
+  adam_st<NT>(p.v + i, v);
   if (p.lowp) *reinterpret_cast<uint2*>(p.lowp + i) = make_uint2(pack_bf16x2(th.x, th.y), pack_bf16x2(th.z, th.w));
 }
 
@@ -266,15 +284,16 @@ extern "C" int hfta_adam_step_multi(int B, int nseg, const int64_t* seg_offsets,
   const size_t shm = (size_t)B * 2 * sizeof(float);
   hipStream_t st = as_stream(stream);
   dim3 grid((unsigned)blocks);
-  if (grad_dtype == HFTA_BF16) {
-    if (odd) hipLaunchKernelGGL(adam_multi_odd_kernel<bf16_raw>, grid, dim3(256), shm, st, a);
-    else if (v4) hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, true>), grid, dim3(256), shm, st, a);
-    else hipLaunchKernelGGL((adam_multi_kernel<bf16_raw, false>), grid, dim3(256), shm, st, a);
-  } else {
-    if (odd) hipLaunchKernelGGL(adam_multi_odd_kernel<float>, grid, dim3(256), shm, st, a);
-    else if (v4) hipLaunchKernelGGL((adam_multi_kernel<float, true>), grid, dim3(256), shm, st, a);
-    else hipLaunchKernelGGL((adam_multi_kernel<float, false>), grid, dim3(256), shm, st, a);
-  }
+  const bool nt = a.total >= ADAM_NT_MIN;
+#define HFTA_ADAM(K) hipLaunchKernelGGL((K), grid, dim3(256), shm, st, a)
+#define HFTA_ADAM_BY_SIZE(G) \
+  do { if (odd) { if (nt) HFTA_ADAM((adam_multi_odd_kernel<G, true>)); else HFTA_ADAM((adam_multi_odd_kernel<G, false>)); } \
+       else if (v4) { if (nt) HFTA_ADAM((adam_multi_kernel<G, true, true>)); else HFTA_ADAM((adam_multi_kernel<G, true, false>)); } \
+       else HFTA_ADAM((adam_multi_kernel<G, false, false>)); } while (0)
+  if (grad_dtype == HFTA_BF16) HFTA_ADAM_BY_SIZE(bf16_raw);
+  else HFTA_ADAM_BY_SIZE(float);
+#undef HFTA_ADAM_BY_SIZE
+#undef HFTA_ADAM
   return launch_status();
 }
 
