@@ -77,7 +77,8 @@ template <int N> __device__ __forceinline__ void ring_wait_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool A_KC, bool B_KC, typename OutT, bool COLB, int ACT, int VB>
+// LATE: every workgroup has one tile (vtotal <= gridDim.x).
+template <bool A_KC, bool B_KC, typename OutT, bool COLB, int ACT, int VB, bool LATE = false>
 __global__ __launch_bounds__(RING_THREADS, 2) void gemm_ring_kernel(GemmArgs p, int vgx, int vtotal) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[RING_SMEM];
   typedef DmaOp<256, RING_BK, A_KC, 8> OpA;
@@ -208,36 +209,51 @@ __global__ __launch_bounds__(RING_THREADS, 2) void gemm_ring_kernel(GemmArgs p, 
   bool after_stores = false;
   for (int lin = blockIdx.x;;) {
     const int T = cur.t_end - cur.t_begin;
-    const bf16_raw* bias = p.bias ? reinterpret_cast<const bf16_raw*>(p.bias) + cur.g0 * p.bias_g0 + cur.g1 * p.bias_g1 : nullptr;
-    // the bias is the accumulators' initial value; column biases come by scalar loads (the same 64 columns for all lanes)
-    if (COLB) {
-      typedef const __attribute__((address_space(4))) uint2* cptr;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = cur.n0 + wn * 64 + j * 32 + 8 * q;
-          uint32_t c[4] = {0u, 0u, 0u, 0u};              // N is a multiple of 4
-          if (n + 4 <= p.N) { const cptr s = (cptr)(uintptr_t)(bias + n); c[0] = s->x; c[1] = s->y; }
-          if (n + 8 <= p.N) { const cptr s = (cptr)(uintptr_t)(bias + n + 4); c[2] = s->x; c[3] = s->y; }
-          const uint32_t x = hi ? c[2] : c[0], y = hi ? c[3] : c[1];
-          const float v[4] = {__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16),
-                              __uint_as_float(y & 0xffff0000u)};
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = v[e];
-        }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = cur.m0 + wm * 128 + i * 32 + ml;
-        const float bm = bias && m < p.M ? bf16_to_f32(bias[m]) : 0.f;
+    // The bias is the accumulators' initial value where a workgroup walks several tiles and is added to the finished sums where it
+    // has one: the order of the kernel that each took the place of (gemm_bigp_kernel, gemm_big_kernel), whose bits these are.  (8 x 2048
+    // rows, 256 -> 1024, one tile each: 16.2 us, 16.5 with the bias first.)  Column biases come by scalar loads (the same 64 columns
+    // for all lanes).
+    auto take_bias = [&]() {
+      const bf16_raw* bias = p.bias ? reinterpret_cast<const bf16_raw*>(p.bias) + cur.g0 * p.bias_g0 + cur.g1 * p.bias_g1 : nullptr;
+      if (COLB) {
+        typedef const __attribute__((address_space(4))) uint2* cptr;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[i][j][v] = bm;
+          for (int q = 0; q < 4; ++q) {
+            const int n = cur.n0 + wn * 64 + j * 32 + 8 * q;
+            uint32_t c[4] = {0u, 0u, 0u, 0u};              // N is a multiple of 4
+            if (n + 4 <= p.N) { const cptr s = (cptr)(uintptr_t)(bias + n); c[0] = s->x; c[1] = s->y; }
+            if (n + 8 <= p.N) { const cptr s = (cptr)(uintptr_t)(bias + n + 4); c[2] = s->x; c[3] = s->y; }
+            const uint32_t x = hi ? c[2] : c[0], y = hi ? c[3] : c[1];
+            const float v[4] = {__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16),
+                                __uint_as_float(y & 0xffff0000u)};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = LATE ? acc[i][j][4 * q + e] + v[e] : v[e];
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int m = cur.m0 + wm * 128 + i * 32 + ml;
+          const float bm = bias && m < p.M ? bf16_to_f32(bias[m]) : 0.f;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = LATE ? acc[i][j][v] + bm : bm;
+        }
       }
+    };
+    if constexpr (LATE) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    } else {
+      take_bias();
     }
     __builtin_amdgcn_sched_barrier(0);
     for (int kt = 0;; ++kt) {
@@ -268,6 +284,7 @@ __global__ __launch_bounds__(RING_THREADS, 2) void gemm_ring_kernel(GemmArgs p, 
       sb = nb;
     }
     fetchB(2, 4);
+    if constexpr (LATE) take_bias();
     // Epilogue: slot sb, which the loader fills next after the barrier at the end, as staging.
     unsigned char* priv = smem + sb + wave * 4096;
     OutT* Cb = to_partial
@@ -324,7 +341,7 @@ __global__ __launch_bounds__(RING_THREADS, 2) void gemm_ring_kernel(GemmArgs p, 
       }
     }
     lin += gridDim.x;
-    if (lin >= vtotal) break;
+    if (LATE || lin >= vtotal) break;
     // every wavefront is through with the staging slot
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");

@@ -5,8 +5,17 @@ namespace hfta {
 
 template <bool A_KC, bool B_KC, typename OutT, bool COLB, int ACT, int VB>
 static void launch(const GemmArgs& a, dim3 grid, int blocks, hipStream_t st) {
+  const int tiles = (int)(grid.x * grid.z);
+  // the order in which a bias is added: see the kernel
+  if constexpr (A_KC && !B_KC && sizeof(OutT) == 2) {
+    if (a.bias && tiles <= blocks) {
+      hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, OutT, COLB, ACT, VB, true>), dim3((unsigned)blocks), dim3(RING_THREADS), 0, st, a,
+                         (int)grid.x, tiles);
+      return;
+    }
+  }
   hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, OutT, COLB, ACT, VB>), dim3((unsigned)blocks), dim3(RING_THREADS), 0, st, a, (int)grid.x,
-                     (int)(grid.x * grid.z));
+                     tiles);
 }
 
 template <bool A_KC, bool B_KC, bool COLB>
@@ -33,6 +42,7 @@ int gemm_ring_launch(const GemmDesc& d, const GemmArgs& a0, dim3 grid, hipStream
   if (f32 ? vb != 16 : vb != 16 && vb != 8) return HFTA_EUNSUPPORTED;
   if (d.N % (vb / (f32 ? 4 : 2)) != 0) return HFTA_EUNSUPPORTED;
   if (partial ? (int64_t)d.M * d.N * 4 >= (int64_t)1 << 31 : a0.c_extent == 0) return HFTA_EUNSUPPORTED;
+  if (d.bias && tiles <= blocks && (f32 || !d.a_kc || d.b_kc)) return HFTA_EUNSUPPORTED;      // forms that no bias comes with
   GemmArgs a = a0;
   a.slope = d.act == HFTA_ACT_NONE ? 1.f : d.act == HFTA_ACT_RELU ? 0.f : d.slope;
   const bool ident = d.act == HFTA_ACT_NONE;
