@@ -25,6 +25,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 int gemm_f32_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st);
 int gemm_ring_launch(const GemmDesc& d, const GemmArgs& a, dim3 grid, hipStream_t st);
 int gemm_big_launch(const GemmDesc& d, const GemmArgs& a, bool v16, bool n16, dim3 grid, hipStream_t st);
+int persistent_blocks();     // compute units, in whole XCD rounds
 
 static inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
@@ -238,7 +239,11 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
       b.total_tiles = d.S * b.tiles_per_seg;
       dim3 grid((unsigned)(b.tiles_m * b.tiles_n), 1, (unsigned)(G * splits));
       int rc = HFTA_EUNSUPPORTED;
-      if ((v16 || !(d.a_kc || d.b_kc)) && n16 && !(d.bsum && d.bsum_done && splits == 1)) rc = gemm_ring_launch(d, b, grid, st);
+      // BatchNorm's statistics come from the persistent register-staged kernel alone (gemm_big_launch), in the order of sums that
+      // rows of 8-byte pieces have too.  On the ring Z is read again for them: 6 x 16 samples, 512 -> 2048 channels on 2048 points
+      // 519 -> 566 us without the activated tensor, 6 x 16, 256 -> 256 54 -> 64; with it, which reads Z anyway, 825 -> 750 and 94 -> 92.
+      const bool stats = d.stat_part && d.stat_done && t256 * splits > persistent_blocks();
+      if ((v16 || !(d.a_kc || d.b_kc)) && n16 && !stats && !(d.bsum && d.bsum_done && splits == 1)) rc = gemm_ring_launch(d, b, grid, st);
       if (rc == HFTA_EUNSUPPORTED) rc = gemm_big_launch(d, b, v16 || !(d.a_kc || d.b_kc), n16, grid, st);
       if (rc == HFTA_OK && splits > 1 && !d.keep_partials) return reduce_partials(d, G, splits, st);
       if (rc != HFTA_EUNSUPPORTED) return rc;
