@@ -242,8 +242,12 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
       // BatchNorm's statistics come from the persistent register-staged kernel alone (gemm_big_launch), in the order of sums that
       // rows of 8-byte pieces have too.  On the ring Z is read again for them: 6 x 16 samples, 512 -> 2048 channels on 2048 points
       // 519 -> 566 us without the activated tensor, 6 x 16, 256 -> 256 54 -> 64; with it, which reads Z anyway, 825 -> 750 and 94 -> 92.
-      const bool stats = d.stat_part && d.stat_done && t256 * splits > persistent_blocks();
-      if ((v16 || !(d.a_kc || d.b_kc)) && n16 && !stats && !(d.bsum && d.bsum_done && splits == 1)) rc = gemm_ring_launch(d, b, grid, st);
+      const bool one_round = t256 * splits <= persistent_blocks();
+      const bool stats = d.stat_part && d.stat_done && !one_round;
+      // B's column sums come from the kernel with one tile per workgroup alone (gemm_big_launch); with more tiles the ring and a pass
+      // over B: 32 models, 4096 rows, 512 x 2048 weight and bias gradient 360 -> 327 us, 16 models, 2048 rows, 256 x 8192 247 -> 223.
+      const bool sums = d.bsum && d.bsum_done && splits == 1 && one_round;
+      if ((v16 || !(d.a_kc || d.b_kc)) && n16 && !stats && !sums) rc = gemm_ring_launch(d, b, grid, st);
       if (rc == HFTA_EUNSUPPORTED) rc = gemm_big_launch(d, b, v16 || !(d.a_kc || d.b_kc), n16, grid, st);
       if (rc == HFTA_OK && splits > 1 && !d.keep_partials) return reduce_partials(d, G, splits, st);
       if (rc != HFTA_EUNSUPPORTED) return rc;

@@ -54,3 +54,20 @@ def test_bias_after_the_sum(hb, B, M, Fx, Fy, relu):
     Y = torch.full((B, M, Fy), float("nan"), dtype=torch.bfloat16, device="cuda")
     hb.linear_fwd(B, M, Fx, Fy, DT["bf16"], X.cuda(), W.cuda(), b.cuda(), Y, act=hb.ACT_RELU if relu else hb.ACT_NONE)
     assert torch.equal(Y.cpu(), b[:, None, :].expand(B, M, Fy))
+
+
+@pytest.mark.parametrize("B,M,Fx,Fy", [(64, 300, 256, 1024), (65, 300, 256, 1024), (33, 520, 512, 1000)])
+def test_weight_and_bias_gradient(hb, B, M, Fx, Fy):
+    """Column sums of dY beside the weight gradient, on both sides of one tile per workgroup: the same dW bits without them."""
+    print(f"weight and bias gradient B={B} M={M} Fx={Fx} Fy={Fy}", flush=True)
+    gen = torch.Generator().manual_seed(3)
+    X, dY = torch.randn(B, M, Fx, generator=gen).bfloat16().cuda(), torch.randn(B, M, Fy, generator=gen).bfloat16().cuda()
+    ws = torch.empty(max(hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, DT["bf16"]), 4), dtype=torch.uint8, device="cuda")
+    dW, dW2 = (torch.full((B, Fx, Fy), float("nan"), device="cuda") for _ in range(2))
+    db = torch.full((B, Fy), float("nan"), device="cuda")
+    hb.linear_bwd(B, M, Fx, Fy, DT["bf16"], X, None, dY, None, dW, db, ws)
+    hb.linear_bwd(B, M, Fx, Fy, DT["bf16"], X, None, dY, None, dW2, None, ws)
+    assert torch.equal(dW, dW2)
+    x, dy = X.cpu().double(), dY.cpu().double()
+    check(host(dW), torch.matmul(x.transpose(1, 2).contiguous(), dy).numpy(), f32_tol("bf16"), "dW")
+    check(host(db), dy.sum(1).numpy(), f32_tol("bf16"), "db")
