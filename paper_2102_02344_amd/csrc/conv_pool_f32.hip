@@ -9,8 +9,8 @@
 // G, v, Cov(x) W_c and the channel sums are formed in double; G x is the fp32 product of gemm_f32.hip, with the hits added
 // while its output is staged; Cov(x) is a product of the same kind over the points.  Against the chain of stored operators the
 // 1024-channel tensors of a 128 -> 1024 layer (1.3 GB each on 4 x 32 x 2500 points) are neither written nor read.
-// On 4 x 32 x 2500 points, 128 -> 1024 channels: forward 902 -> 680 us (the product without its stores), backward 1595 -> 340
-// (moments 108, dX 145, the rest 85), the training step 3745 -> 2250; dX 2.2e-7 -> 5.7e-8 and dW 5.9e-7 -> 6.6e-8 off float64.
+// On 4 x 32 x 2500 points, 128 -> 1024 channels: forward 858 -> 598 us (the product without its stores), backward 1567 -> 314
+// (moments 107, dX 123, the rest 84); dX 2.2e-7 -> 5.7e-8 and dW 5.9e-7 -> 6.6e-8 off float64.
 // Bound: x read twice and dX written once; the hits, a chain of loads per tile, and the moments' phases take longer.
 #include "gemm_pf.h"
 #include "f32_split.h"
@@ -43,12 +43,12 @@ struct Pool32Args {
   uint32_t* skey; float* sval; int* toff;
   float* negG;        // [B][Ci][Ci]
   float* negv;        // [B][Ci]
-  float* XXpart;      // [chunks][B][Ci][Ci] sums of products about `ref`
-  float* SXpart;      // [chunks][B][Ci] sums about `ref`
-  float* ref;         // [B][Ci]
+  float* XXpart;      // [chunks][B][Ci][Ci] sums of products about the means of groups of 64 tiles and less
+  double* gm;         // [chunks * groups][B][Ci] those means
+  double* gn;         // [chunks * groups][B] a group's points
   double* cov;        // [B][Ci][Ci] Cov(x)
   double* ex;         // [B][Ci] E[x]
-  int chunks;
+  int chunks, groups; // groups: of a chunk, the last may be empty
   float* xg;          // [B][Nb][Co][Ci] the input at each hit
 };
 
@@ -159,17 +159,32 @@ __global__ __launch_bounds__(HIT_THREADS) void pool32_prep_kernel(Pool32Args p, 
 
 // ---- second moments of x, and the input at each hit, in one pass over x.  A workgroup takes a share of a model's 64-point
 // ---- tiles; each is loaded once (16-byte pieces, the next tile's in flight), parked as it is for the hits (a column of x is
-// ---- Ci cache lines in memory) and, about a reference near its mean, as three bf16 planes that are both operands of the
-// ---- product.  About the reference: XX / m - E[x]^2 would lose what a mean that is large against the spread has in digits
-// ---- (dW's error 8e-5 for 3e-5 of the stored operators at a mean of ten spreads).  The six products of two splits as in
-// ---- gemm_f32.hip.  4 x 32 x 2500 x 128: 108 us, 5.4 a tile, of which 1.9 are its bytes and 1.4 its matrix instructions: the phases
-// ---- of the one workgroup per compute unit (eight wavefronts, 210 registers) follow each other.  Two workgroups spill (136-317 us);
-// ---- a pass for the hits and the product over the points on the general kernel took 150. ----
+// ---- Ci cache lines in memory) and, about its own mean, as three bf16 planes that are both operands of the product.  The means of
+// ---- 64 tiles, or of what the share has left, about their own mean and times the root of their points, are one more tile.  So the
+// ---- sums never hold more than the points' own spread, whatever their order: XX / m - E[x]^2 loses what a mean that is large
+// ---- against the spread has in digits (dW's error 8e-5 for 3e-5 of the stored operators at a mean of ten spreads), and one
+// ---- reference for a model, its first 64 points, what the others lie off by (64 x 8 clouds padded in front with a point five
+// ---- spreads away: 7.5e-6 for 5.3e-7 of the stored operators, now 1.4e-7).  The six products of two splits as in gemm_f32.hip.
+// ---- 4 x 32 x 2500 x 128: 107 us (98 about one reference), of 5.3 a tile 1.9 are its bytes and 1.4 its matrix instructions: the
+// ---- phases of the one workgroup per compute unit (eight wavefronts, 216 registers) follow each other.  Two workgroups spill
+// ---- (136-317 us); a pass for the hits and the product over the points on the general kernel took 150. ----
 constexpr int MM_PTS = 64, MM_THREADS = 512, MM_WN = MM_THREADS / 128, MM_NJ = 4 / MM_WN, MM_ROWS = MM_THREADS / 16, MM_H = 128 / MM_ROWS, MM_PLANE = 128 * MM_PTS * 2;
 __device__ __forceinline__ int mm_swz(int r) { return (r ^ (r >> 3)) & 7; }
+// the sum over sixteen lanes, the same bits in each
+template <int N> __device__ __forceinline__ float mm_ror(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float mm_sum16(float v) {
+  v += mm_ror<8>(v);
+  v += mm_ror<4>(v);
+  v += mm_ror<2>(v);
+  return v + mm_ror<1>(v);
+}
+constexpr int MM_GROUP = MM_PTS, MM_PITCH = 129;           // means: tiles of a group, floats a tile
 __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Args p) {
   __shared__ __attribute__((aligned(16))) unsigned char planes[3 * MM_PLANE];
   __shared__ __attribute__((aligned(16))) float raw[128 * MM_PTS];     // 16-byte piece q of row r at q ^ (r & 15)
+  __shared__ float means[MM_GROUP * MM_PITCH], count[MM_GROUP];        // of a group's tiles
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave / MM_WN, wn = wave % MM_WN;   // 2 x 4 wavefronts, 64 x 32 each
   const int chunk = blockIdx.x, b = blockIdx.y;
   const int per = (p.L + MM_PTS - 1) / MM_PTS, total = p.Nb * per;
@@ -192,19 +207,6 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
     const int n = tile / per;
     fetch(xb + n * p.xsn, tile < t1 ? (tile - n * per) * MM_PTS + piece * 4 : p.L);
   };
-  // the reference: the mean of the model's first 64 points, the same in every workgroup
-  float ref[MM_H], sum[MM_H];
-  fetch(xb, piece * 4);
-#pragma unroll
-  for (int h = 0; h < MM_H; ++h) {
-    const int ci = row + MM_ROWS * h;
-    float s = (q[h].x + q[h].y) + (q[h].z + q[h].w);
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    ref[h] = s * (1.f / MM_PTS);
-    if (chunk == 0 && piece == 0 && ci < p.Ci) p.ref[b * p.Ci + ci] = ref[h];
-    sum[h] = 0.f;
-  }
   f32x16_t acc[2][MM_NJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -221,40 +223,27 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
   };
   load(t0);
   range(t0);
-  for (int tile = t0; tile < t1; ++tile) {
-    const int n = tile / per, l0 = (tile - n * per) * MM_PTS, have = p.L - (l0 + piece * 4);
-    __syncthreads();                                       // the last tile is read
+  auto park = [&](int r, const float4& c) {
     SplitSeen seen;                                        // (an infinity or a NaN reaches every result through the statistics)
+    uint2 o[3];
+    split4(c, o, seen);
+    unsigned char* d = planes + r * (MM_PTS * 2) + (((piece >> 1) ^ mm_swz(r)) << 4) + (piece & 1) * 8;
 #pragma unroll
-    for (int h = 0; h < MM_H; ++h) {
-      const int r = row + MM_ROWS * h;
-      *reinterpret_cast<float4*>(raw + r * MM_PTS + (piece ^ (r & 15)) * 4) = q[h];
-      float4 c = make_float4(q[h].x - ref[h], have > 1 ? q[h].y - ref[h] : 0.f, have > 2 ? q[h].z - ref[h] : 0.f, have > 3 ? q[h].w - ref[h] : 0.f);
-      if (have < 1 || r >= p.Ci) c = make_float4(0.f, 0.f, 0.f, 0.f);
-      sum[h] += (c.x + c.y) + (c.z + c.w);
-      uint2 o[3];
-      split4(c, o, seen);
-      unsigned char* d = planes + r * (MM_PTS * 2) + (((piece >> 1) ^ mm_swz(r)) << 4) + (piece & 1) * 8;
-#pragma unroll
-      for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(d + i * MM_PLANE) = o[i];
-    }
-    __syncthreads();
-    load(tile + 1);
-    const int64_t smp = (int64_t)b * p.Nb + n;
-    const int h_lo = hlo, h_hi = hhi;                      // this tile's range of hits, and the first of them
-    const uint32_t first = h_lo + lane < h_hi ? p.skey[smp * p.Co + h_lo + lane] : 0xffffffffu;
-    range(tile + 1);
-    auto frag = [&](int pl, int base, int s) {
-      const int r = base + (lane & 31);
-      return *reinterpret_cast<const bf16x8_t*>(planes + pl * MM_PLANE + r * (MM_PTS * 2) + (((2 * s + (lane >> 5)) ^ mm_swz(r)) << 4));
-    };
-    // one block after the other, the corrections' accumulators for one block and tile only: registers
+    for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(d + i * MM_PLANE) = o[i];
+  };
+  auto frag = [&](int pl, int r0, int s) {
+    const int r = r0 + (lane & 31);
+    return *reinterpret_cast<const bf16x8_t*>(planes + pl * MM_PLANE + r * (MM_PTS * 2) + (((2 * s + (lane >> 5)) ^ mm_swz(r)) << 4));
+  };
+  // one block after the other, a tile's accumulators for one block only: registers.  A tile's sums start from zero: one rounding a
+  // tile at the size of all.
+  auto products = [&]() {
 #pragma unroll
     for (int ij = 0; ij < 2 * MM_NJ; ++ij) {
       const int i = ij / MM_NJ, j = ij % MM_NJ;
-      f32x16_t low;
+      f32x16_t low, top;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) low[v] = 0.f;
+      for (int v = 0; v < 16; ++v) low[v] = top[v] = 0.f;
 #pragma unroll
       for (int s = 0; s < MM_PTS / 16; ++s) {
         bf16x8_t x[3], y[3];
@@ -266,25 +255,84 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
         constexpr int PA[5] = {2, 1, 0, 1, 0}, PB[5] = {0, 1, 2, 0, 1};
 #pragma unroll
         for (int k = 0; k < 5; ++k) low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[PB[k]], x[PA[k]], low, 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[0], x[0], acc[i][j], 0, 0, 0);
+        top = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[0], x[0], top, 0, 0, 0);
       }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] += low[v];
+      for (int v = 0; v < 16; ++v) acc[i][j][v] += top[v] + low[v];
     }
-    // this tile's hits: those of its 128-point tile whose point is in it, in turn over the wavefronts
-    for (int h0 = h_lo; h0 < h_hi; h0 += 64) {
-      const uint32_t kl = h0 == h_lo ? first : h0 + lane < h_hi ? p.skey[smp * p.Co + h0 + lane] : 0xffffffffu;
-      unsigned long long todo = __ballot((int)(kl >> 10) - l0 >= 0 && (int)(kl >> 10) - l0 < MM_PTS);
-      for (int k = 0; todo; ++k, todo &= todo - 1) {
-        if (k % (MM_THREADS / 64) != wave) continue;
-        const uint32_t key = (uint32_t)__builtin_amdgcn_readlane((int)kl, __builtin_ctzll(todo));
-        const int col = (int)(key >> 10) - l0;
-        float* out = p.xg + (smp * p.Co + (key & 1023u)) * p.Ci;
+  };
+  for (int tile = t0, group = 0; group < p.groups; ++group) {
+    const int g0 = tile, g1 = min(tile + MM_GROUP, t1);
+    for (; tile < g1; ++tile) {
+      const int n = tile / per, l0 = (tile - n * per) * MM_PTS, have = p.L - (l0 + piece * 4);
+      const float pts = (float)min(p.L - l0, MM_PTS), inv = __builtin_amdgcn_rcpf(pts);
+      __syncthreads();                                     // the last tile is read
 #pragma unroll
-        for (int r = lane; r < 128; r += 64)
-          if (r < p.Ci) out[r] = raw[r * MM_PTS + (((col >> 2) ^ (r & 15)) << 2) + (col & 3)];
+      for (int h = 0; h < MM_H; ++h) {
+        const int r = row + MM_ROWS * h;
+        *reinterpret_cast<float4*>(raw + r * MM_PTS + (piece ^ (r & 15)) * 4) = q[h];
+        // (what is out of range has been loaded as zeros; the mean but for its rounding, 2^-23 of it)
+        const float y = have > 1 ? q[h].y : 0.f, z = have > 2 ? q[h].z : 0.f, w = have > 3 ? q[h].w : 0.f;
+        const float ref = mm_sum16((q[h].x + y) + (z + w)) * inv;
+        if (piece == 0) means[(tile - g0) * MM_PITCH + r] = ref;
+        park(r, make_float4(have > 0 ? q[h].x - ref : 0.f, have > 1 ? y - ref : 0.f, have > 2 ? z - ref : 0.f, have > 3 ? w - ref : 0.f));
+      }
+      if (t == 0) count[tile - g0] = pts;
+      __syncthreads();
+      load(tile + 1);
+      const int64_t smp = (int64_t)b * p.Nb + n;
+      const int h_lo = hlo, h_hi = hhi;                    // this tile's range of hits, and the first of them
+      const uint32_t first = h_lo + lane < h_hi ? p.skey[smp * p.Co + h_lo + lane] : 0xffffffffu;
+      range(tile + 1);
+      products();
+      // this tile's hits: those of its 128-point tile whose point is in it, in turn over the wavefronts
+      for (int h0 = h_lo; h0 < h_hi; h0 += 64) {
+        const uint32_t kl = h0 == h_lo ? first : h0 + lane < h_hi ? p.skey[smp * p.Co + h0 + lane] : 0xffffffffu;
+        unsigned long long todo = __ballot((int)(kl >> 10) - l0 >= 0 && (int)(kl >> 10) - l0 < MM_PTS);
+        for (int k = 0; todo; ++k, todo &= todo - 1) {
+          if (k % (MM_THREADS / 64) != wave) continue;
+          const uint32_t key = (uint32_t)__builtin_amdgcn_readlane((int)kl, __builtin_ctzll(todo));
+          const int col = (int)(key >> 10) - l0;
+          float* out = p.xg + (smp * p.Co + (key & 1023u)) * p.Ci;
+#pragma unroll
+          for (int r = lane; r < 128; r += 64)
+            if (r < p.Ci) out[r] = raw[r * MM_PTS + (((col >> 2) ^ (r & 15)) << 2) + (col & 3)];
+        }
       }
     }
+    // the group's means as a tile
+    const int have = g1 - g0;                              // 0: a chunk of fewer groups
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(raw);          // [4][128]
+    float* mid = raw + 4 * 128 * 2;                        // [128]
+    const int i = t & 127, g = t >> 7;
+    double s = 0.0;
+    for (int k = g; k < have; k += MM_THREADS / 128) s = fma((double)count[k], (double)means[k * MM_PITCH + i], s);
+    red[g * 128 + i] = s;
+    __syncthreads();
+    if (g == 0) {
+      double points = 0.0;
+      for (int k = 0; k < have; ++k) points += (double)count[k];
+      s = have > 0 ? (((s + red[128 + i]) + red[256 + i]) + red[384 + i]) / points : 0.0;
+      const int64_t at = ((int64_t)chunk * p.groups + group) * p.B + b;
+      if (i < p.Ci) p.gm[at * p.Ci + i] = s;
+      if (i == 0) p.gn[at] = points;
+      mid[i] = (float)s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < MM_H; ++h) {
+      const int r = row + MM_ROWS * h;
+      float c[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = piece * 4 + e;
+        c[e] = k < have ? (means[k * MM_PITCH + r] - mid[r]) * sqrtf(count[k]) : 0.f;
+      }
+      park(r, make_float4(c[0], c[1], c[2], c[3]));
+    }
+    __syncthreads();
+    products();
   }
   float* XX = p.XXpart + ((int64_t)chunk * p.B + b) * p.Ci * p.Ci;
   // symmetric, element by element the same products in the same order up to the corrections': out as gram_kernel's
@@ -299,28 +347,38 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
         if (ci < p.Ci && cj < p.Ci) XX[(int64_t)cj * p.Ci + ci] = acc[i][j][v];
       }
   }
-#pragma unroll
-  for (int h = 0; h < MM_H; ++h) {
-    float s = sum[h];
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (piece == 0 && row + MM_ROWS * h < p.Ci) p.SXpart[((int64_t)chunk * p.B + b) * p.Ci + row + MM_ROWS * h] = s;
-  }
 }
 
-// ---- E[x] and Cov(x) from the workgroups' parts, in a fixed order: one input channel per workgroup, eight shares of the parts ----
-__global__ __launch_bounds__(1024) void pool32_cov_kernel(Pool32Args p) {
-  __shared__ double red[8][128], sx[8][128];
-  const int i = blockIdx.x, b = blockIdx.y, j = threadIdx.x & 127, g = threadIdx.x >> 7;
+// ---- E[x] and Cov(x) from the workgroups' parts, about the first's mean, in a fixed order: one input channel per workgroup, eight
+// ---- shares of the parts ----
+__global__ __launch_bounds__(1024, 8) void pool32_cov_kernel(Pool32Args p) {
+  constexpr int Q = 256;                                   // groups at a time
+  __shared__ double red[8][128], sx[8][128], wn[Q], wi[Q];
+  const int i = blockIdx.x, b = blockIdx.y, j = threadIdx.x & 127, g = threadIdx.x >> 7, jc = min(j, p.Ci - 1);
   const int64_t stride = (int64_t)p.B * p.Ci;
+  const double* gm = p.gm + (int64_t)b * p.Ci;
+  const double ri = gm[i], rj = gm[jc];
   double a = 0.0, s = 0.0;
-  if (j < p.Ci) {
-    const float* XX = p.XXpart + ((int64_t)b * p.Ci + i) * p.Ci + j;
-    const float* SX = p.SXpart + (int64_t)b * p.Ci + j;
-#pragma unroll 4
-    for (int q = g; q < p.chunks; q += 8) {
-      a += (double)XX[q * stride * p.Ci];
-      s += (double)SX[q * stride];
+  const float* XX = p.XXpart + ((int64_t)b * p.Ci + i) * p.Ci + jc;
+  for (int q0 = 0; q0 < p.chunks * p.groups; q0 += Q) {
+    const int qs = min(Q, p.chunks * p.groups - q0);
+    if (q0 > 0) __syncthreads();
+    if ((int)threadIdx.x < qs) {
+      const int64_t q = q0 + threadIdx.x;
+      const double n = p.gn[q * p.B + b];
+      wn[threadIdx.x] = n;
+      wi[threadIdx.x] = n * (gm[q * stride + i] - ri);
+    }
+    if (q0 == 0) {
+#pragma unroll 8
+      for (int q = g; q < p.chunks; q += 8) a += (double)XX[q * stride * p.Ci];
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int q = g; q < qs; q += 8) {
+      const double d = gm[(q0 + q) * stride + jc] - rj;
+      a = fma(wi[q], d, a);
+      s = fma(wn[q], d, s);
     }
   }
   red[g][j] = a;
@@ -334,7 +392,7 @@ __global__ __launch_bounds__(1024) void pool32_cov_kernel(Pool32Args p) {
   if (g != 0 || j >= p.Ci) return;
   const double m = (double)p.Nb * (double)p.L;
   p.cov[((int64_t)b * p.Ci + i) * p.Ci + j] = a / m - (sx[0][i] / m) * (s / m);
-  if (i == 0) p.ex[(int64_t)b * p.Ci + j] = (double)p.ref[b * p.Ci + j] + s / m;
+  if (i == 0) p.ex[(int64_t)b * p.Ci + j] = rj + s / m;
 }
 
 // ---- dW: a thread per (channel of eight, input channel) ----
@@ -381,8 +439,9 @@ size_t layout(Pool32Args& a, unsigned char* base) {
   const int total = a.Nb * ((a.L + MM_PTS - 1) / MM_PTS), want = (256 + a.B - 1) / a.B;   // a workgroup per compute unit
   a.chunks = want < total ? want : total;
   take(a.XXpart, a.chunks * B * Ci * Ci);
-  take(a.SXpart, a.chunks * B * Ci);
-  take(a.ref, B * Ci);
+  a.groups = ((total + a.chunks - 1) / a.chunks + MM_GROUP - 1) / MM_GROUP;
+  take(a.gm, (size_t)a.chunks * a.groups * B * Ci);
+  take(a.gn, (size_t)a.chunks * a.groups * B);
   take(a.cov, B * Ci * Ci);
   take(a.ex, B * Ci);
   take(a.xg, N * Co * Ci);

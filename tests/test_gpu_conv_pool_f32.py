@@ -37,19 +37,9 @@ def reference(X, W, bias, gam, bet, idx, dV, act, slope, eps=1e-5):
     return torch.stack(out[0], 1), torch.stack(out[1]), torch.stack(out[2]), torch.stack(out[3])
 
 
-@pytest.mark.parametrize("dims,act,slope,shift", [((3, 29, 128, 1024, 1023), 1, 0.0, 0.0), ((8, 64, 68, 70, 130), 1, 0.0, 2.0),
-                                                  ((2, 32, 96, 200, 1030), 2, 0.2, 0.0), ((1, 512, 128, 65, 128), 0, 0.0, 0.0),
-                                                  ((2, 32, 100, 513, 1028), 1, 0.0, 10.0)])
-def test_pair(hb, dims, act, slope, shift):
+def both_ways(hb, dims, X, W, bias, gam, bet, dV, act, slope):
+    """Forward results and (dX, dW, dgamma, dbeta) of the chain of stored operators and of the pair."""
     B, Nb, Ci, Co, L = dims
-    print(f"fp32 tail {dims} act={act} shift={shift}", flush=True)
-    gen = torch.Generator(device="cuda").manual_seed(5)
-    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
-    X = torch.relu(r(Nb, B, Ci, L)) + shift
-    X[:, :, :, L // 2] *= 3.0                                # a point that many channels choose: more hits than a wavefront
-    W, bias, gam, bet, dV = r(B, Co, Ci) * (2.0 / Ci) ** 0.5, 0.1 * r(B, Co), 1.0 + 0.2 * r(B, Co), 0.3 * r(B, Co), r(B, Nb, Co)
-    gam[:, ::7] *= -1.0
-    gam[0, 3], bet[0, 3], bet[0, 5] = 0.0, 0.5, -50.0        # all points equal; all points clipped
     xs, zs, vs = conv_strides(B, Ci, L), conv_strides(B, Co, L), (Nb * Co, Co, 1)
     need = hb.conv1x1_bn_maxpool_f32_workspace_bytes(*dims)
     assert need > 0
@@ -74,7 +64,23 @@ def test_pair(hb, dims, act, slope, shift):
                                           dg, dbt, act, slope, ws)
             assert not db.any()
         res.append((o, (dX, dW, dg, dbt)))
-    (a, ga), (b, gb) = res
+    return res
+
+
+@pytest.mark.parametrize("dims,act,slope,shift", [((3, 29, 128, 1024, 1023), 1, 0.0, 0.0), ((8, 64, 68, 70, 130), 1, 0.0, 2.0),
+                                                  ((2, 32, 96, 200, 1030), 2, 0.2, 0.0), ((1, 512, 128, 65, 128), 0, 0.0, 0.0),
+                                                  ((2, 32, 100, 513, 1028), 1, 0.0, 10.0)])
+def test_pair(hb, dims, act, slope, shift):
+    B, Nb, Ci, Co, L = dims
+    print(f"fp32 tail {dims} act={act} shift={shift}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X = torch.relu(r(Nb, B, Ci, L)) + shift
+    X[:, :, :, L // 2] *= 3.0                                # a point that many channels choose: more hits than a wavefront
+    W, bias, gam, bet, dV = r(B, Co, Ci) * (2.0 / Ci) ** 0.5, 0.1 * r(B, Co), 1.0 + 0.2 * r(B, Co), 0.3 * r(B, Co), r(B, Nb, Co)
+    gam[:, ::7] *= -1.0
+    gam[0, 3], bet[0, 3], bet[0, 5] = 0.0, 0.5, -50.0        # all points equal; all points clipped
+    (a, ga), (b, gb) = both_ways(hb, dims, X, W, bias, gam, bet, dV, act, slope)
     same = torch.ones_like(a["V"], dtype=torch.bool)
     same[0, :, 3] = False                                    # gamma = 0: z at point 0 by another order of the sum
     for k in a:
@@ -83,6 +89,40 @@ def test_pair(hb, dims, act, slope, shift):
     # Sums of K <= 1024 products of fp32 values rounded to 2^-24 each: sqrt(K) 2^-24 = 2e-6 of their norm; and no further off
     # than the stored chain, whose rounding of 1e-7 in what cancels is the yardstick where the mean is large.
     for name, q, s, t in zip(("dX", "dW", "dgamma", "dbeta"), reference(X, W, bias, gam, bet, a["idx"], dV, act, slope), ga, gb):
+        err = [((v.double() - q).norm() / q.norm()).item() for v in (s, t)]
+        print(name, err)
+        assert err[1] <= 2e-6 and err[1] <= 1.05 * err[0] + 2e-8, (name, err)
+
+
+def _padded(X):
+    """Every cloud's first 96 points are one and the same, five spreads from the others."""
+    X[:, :, :, :96] = X.mean((0, 3), keepdim=True) + 5.0 * X.std((0, 3), keepdim=True)
+
+
+def _front(X):
+    """The first cloud of each model lies three spreads from the others."""
+    X[0] += 3.0 * X.std((0, 3), keepdim=True)[0]
+
+
+def _ordered(X):
+    """Clouds sorted along a direction that all channels see."""
+    X += 2.0 * X[:, :, :1].sort(3).values
+
+
+@pytest.mark.parametrize("how", [_padded, _front, _ordered])
+@pytest.mark.parametrize("dims", [(2, 16, 128, 256, 2048), (3, 29, 68, 130, 1023), (64, 8, 68, 70, 2050), (64, 1, 72, 66, 16400)])
+def test_points_that_are_not_alike(hb, dims, how):
+    """dW of clouds whose points are not spread alike over their memory: no further off float64 than the stored chain is (see
+    test_pair)."""
+    print(f"fp32 tail {dims} {how.__name__}", flush=True)
+    B, Nb, Ci, Co, L = dims
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X = r(Nb, B, Ci, L)
+    how(X)
+    W, bias, gam, bet, dV = r(B, Co, Ci) * (2.0 / Ci) ** 0.5, 0.1 * r(B, Co), 1.0 + 0.2 * r(B, Co), 0.3 * r(B, Co), r(B, Nb, Co)
+    (a, ga), (_, gb) = both_ways(hb, dims, X, W, bias, gam, bet, dV, 1, 0.0)
+    for name, q, s, t in zip(("dX", "dW", "dgamma", "dbeta"), reference(X, W, bias, gam, bet, a["idx"], dV, 1, 0.0), ga, gb):
         err = [((v.double() - q).norm() / q.norm()).item() for v in (s, t)]
         print(name, err)
         assert err[1] <= 2e-6 and err[1] <= 1.05 * err[0] + 2e-8, (name, err)
