@@ -33,8 +33,9 @@ struct BnFwdArgs {
 // more than an XCD's 4 MB, so a second read travels the fabric again.  With the pieces in registers the forward moves two
 // tensors instead of three, the backward three instead of five.
 //
-// held_waves: wavefronts per SIMD for `words` held registers (1024 threads: 8 or 4; 8 take up to `most`).
-constexpr int held_waves(int words, int most, int nt) { return words <= most ? 8 : nt == 1024 || words > 56 ? 4 : 5; }
+// held_waves: wavefronts per SIMD for `words` held registers (1024 threads: 8 or 4; 8 take up to `most`; nothing held: what the
+// kernel comes to, 7 or 8).
+constexpr int held_waves(int words, int most, int nt) { return words == 0 ? 4 : words <= most ? 8 : nt == 1024 || words > 56 ? 4 : 5; }
 
 // the words of a piece (element offsets from the channel's start in 32 bits: a scalar base and one register a load; held_rows_ok)
 template <typename T>
@@ -691,14 +692,15 @@ template <typename T> bool held_rows_ok(int Nb, int L, int64_t sn0, int64_t sn1)
 
 // How many pieces a thread holds.  All of a channel if they fit with two 1024-thread workgroups per compute unit, else what
 // does: us with nothing held -> now, and what the other choice takes:
-//   forward   bf16 6 x 16 x 2500, 2048 channels 538 -> 446, 128 channels 31 -> 26; 8 x 32 x 2500, 64 channels 39 -> 31; fp32 4 x 32 x 2500, 128 channels 81 -> 69 with 9 of
+//   forward   bf16 6 x 16 x 2500, 2048 channels 538 -> 446, 128 channels 31 -> 26; 8 x 32 x 2500, 64 channels 39 -> 28; fp32 4 x 32 x 2500, 128 channels 81 -> 69 with 9 of
 //             20 held, 76 with all 20 and one workgroup per unit, which wins where all channels run at once: 64 channels
 //             38 -> 27, 34 with 9.
 //   backward  the same tensors: 741 -> 588 (777 with both operands in registers and one workgroup per unit), 50 -> 38,
 //             62 -> 54; fp32 62 -> 52 and 155 -> 126 with 10 of 20 held in registers, 56 and 137 with 5 in LDS,
 //             which wins where 5 are most of the channel (32 x 1024: 41 against 43).
 // Past 40 pieces too little of a channel is held to pay for the wavefronts (2 x 64 channels of 100 x 4096 bf16: forward
-// 77 us with nothing held, 95 with 20 of 100, backward 125 and 131).
+// 77 us with nothing held, 95 with 20 of 100, backward 125 and 131; elsewhere 61 and 108 with nothing held, 80 and 117 with
+// the general activation in the loop).
 constexpr int HELD_MOST = 40;
 template <typename T, int NT>
 void launch_bn_fwd(const BnFwdArgs& a, dim3 grid, hipStream_t st) {

@@ -93,6 +93,7 @@ __device__ __forceinline__ void block_sum2(float& a, float& b, float (*sh)[2]) {
   for (int i = 0; i < NW; i += 4) {          // fixed order, pairwise within groups of four waves
     ra += (sh[i][0] + sh[i + 1][0]) + (sh[i + 2][0] + sh[i + 3][0]);
     rb += (sh[i][1] + sh[i + 1][1]) + (sh[i + 2][1] + sh[i + 3][1]);
+    if (NW > 4) __builtin_amdgcn_sched_barrier(0);          // 8 registers at a time: all 32 at once made kernels that hold data spill
   }
   a = ra; b = rb;
 }
