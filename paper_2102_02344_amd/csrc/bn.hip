@@ -747,13 +747,11 @@ void launch_bn_fwd_rows(const BnFwdArgs& a, int B, bool v4, hipStream_t st) {
   if (v4) big ? launch_bn_fwd<T, 1024>(a, grid, st) : launch_bn_fwd<T, 256>(a, grid, st);
   else if (a.L >= 4 && bytes <= STAGE_FULL && (int64_t)a.Nb * a.L >= ODD_MIN * (big ? 1024 : 256)) {
 #define HFTA_ODD(NT, N) hipLaunchKernelGGL((bn_fwd_odd_kernel<T, NT, N>), grid, dim3(NT), 0, st, a)
-    // (rows of five elements take eight places: a small channel can need more than its 32 KB)
     if (big && bytes <= STAGE_HALF) HFTA_ODD(1024, STAGE_HALF);
     else if (big) HFTA_ODD(1024, STAGE_FULL);
     else if (bytes <= STAGE_SMALL) HFTA_ODD(256, STAGE_SMALL);
     else if (bytes <= STAGE_MID) HFTA_ODD(256, STAGE_MID);
-    else if (bytes <= STAGE_HALF) HFTA_ODD(256, STAGE_HALF);
-    else HFTA_ODD(256, STAGE_FULL);
+    else HFTA_ODD(256, STAGE_HALF);                      // 32 KB at most; rows of five elements take eight places: 52
 #undef HFTA_ODD
   } else if (big) hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 1024, 0>), grid, dim3(1024), 0, st, a, 0);
   else hipLaunchKernelGGL((bn_fwd_conv_kernel<T, 1, 256, 0>), grid, dim3(256), 0, st, a, 0);
@@ -763,18 +761,25 @@ void launch_bn_bwd_rows(const BnBwdArgs& a, int B, bool v4, hipStream_t st) {
   const dim3 grid((unsigned)a.C, (unsigned)B);
   const int64_t bytes = 2 * (int64_t)a.Nb * ((a.L + 3) / 4) * 4 * (int64_t)sizeof(T);      // staged
   const bool big = bn_wide_block((int64_t)a.Nb * a.L * (int64_t)sizeof(T));
-  if (v4) big ? launch_bn_bwd<T, 1024>(a, grid, st) : launch_bn_bwd<T, 256>(a, grid, st);
-  else if (sizeof(T) == 2 && a.L >= 4 && bytes <= STAGE_FULL && (int64_t)a.Nb * a.L >= ODD_MIN * (big ? 1024 : 256)) {
+  if (v4) {
+    big ? launch_bn_bwd<T, 1024>(a, grid, st) : launch_bn_bwd<T, 256>(a, grid, st);
+    return;
+  }
+  if constexpr (sizeof(T) == 2) {
+    if (a.L >= 4 && bytes <= STAGE_FULL && (int64_t)a.Nb * a.L >= ODD_MIN * (big ? 1024 : 256)) {
 #define HFTA_ODD(NT, N) hipLaunchKernelGGL((bn_bwd_odd_kernel<T, NT, N>), grid, dim3(NT), 0, st, a)
-    // (rows of five elements take eight places: a small channel can need more than its 32 KB)
-    if (big && bytes <= STAGE_HALF) HFTA_ODD(1024, STAGE_HALF);
-    else if (big) HFTA_ODD(1024, STAGE_FULL);
-    else if (bytes <= STAGE_SMALL) HFTA_ODD(256, STAGE_SMALL);
-    else if (bytes <= STAGE_MID) HFTA_ODD(256, STAGE_MID);
-    else if (bytes <= STAGE_HALF) HFTA_ODD(256, STAGE_HALF);
-    else HFTA_ODD(256, STAGE_FULL);
+      // (rows of five elements take eight places: a small channel can need more than its 2 x 32 KB)
+      if (big && bytes <= STAGE_HALF) HFTA_ODD(1024, STAGE_HALF);
+      else if (big) HFTA_ODD(1024, STAGE_FULL);
+      else if (bytes <= STAGE_SMALL) HFTA_ODD(256, STAGE_SMALL);
+      else if (bytes <= STAGE_MID) HFTA_ODD(256, STAGE_MID);
+      else if (bytes <= STAGE_HALF) HFTA_ODD(256, STAGE_HALF);
+      else HFTA_ODD(256, STAGE_FULL);
 #undef HFTA_ODD
-  } else if (big) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 1024, 0, false>), grid, dim3(1024), 0, st, a, 0);
+      return;
+    }
+  }
+  if (big) hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 1024, 0, false>), grid, dim3(1024), 0, st, a, 0);
   else hipLaunchKernelGGL((bn_bwd_conv_kernel<T, 1, 256, 0, false>), grid, dim3(256), 0, st, a, 0);
 }
 
