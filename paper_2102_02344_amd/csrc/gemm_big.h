@@ -1,4 +1,6 @@
-// Compute-bound variant of the batched GEMM core: 256x256 output tile per 512-thread workgroup.
+// Compute-bound variant of the batched GEMM core: 256x256 output tile per 512-thread workgroup, staged through registers.
+// Products whose operands have rows of whole 16-byte pieces take the LDS ring of gemm_ring.h first; here is what is
+// left: rows of 8-byte pieces (2500 points), BatchNorm's statistics and B's column sums in the epilogue, GELU and tanh.
 //
 // The 128x128 kernel in gemm.h reads 32 bytes of LDS per MFMA cycle and wave, which is the
 // whole LDS bandwidth of a compute unit, and moves 64 flop per byte it pulls from L2.  For the
@@ -17,7 +19,7 @@
 // Two kernels: gemm_big_kernel (one tile per workgroup; every epilogue kind) and, further down,
 // gemm_bigp_kernel (persistent: as many workgroups as compute units walk the tiles, with the
 // loads, the bias and the stores of neighbouring tiles overlapped; select-kind epilogues), which
-// the launcher takes whenever a launch has more tiles than compute units.
+// the launcher takes when a launch has more tiles than compute units.
 #pragma once
 #include "gemm_dma.h"
 

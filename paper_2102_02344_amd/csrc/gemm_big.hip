@@ -26,15 +26,15 @@ int persistent_blocks() {
   return n;
 }
 
+// Statistics epilogue: k=1 convolution forward
+template <bool N16>
+static void launch_stats(const GemmArgs& a, dim3 grid, int blocks, hipStream_t st) {
+  hipLaunchKernelGGL((gemm_bigp_kernel<true, false, bf16_raw, false, BIG_NONE, true, N16, true>), dim3((unsigned)blocks), dim3(BIG_THREADS), 0,
+                     st, a, (int)grid.x, (int)(grid.x * grid.z));
+}
+
 template <bool A_KC, bool B_KC, typename OutT, bool COLB, bool V16, bool N16>
-static void launch_bigp2(const GemmArgs& a, bool ident, dim3 grid, int blocks, hipStream_t st) {
-  if constexpr (A_KC && !B_KC && std::is_same<OutT, bf16_raw>::value && !COLB && V16) {
-    if (ident && a.stat_part) {          // k=1 convolution forward with the statistics epilogue
-      hipLaunchKernelGGL((gemm_bigp_kernel<A_KC, B_KC, OutT, COLB, BIG_NONE, V16, N16, true>), dim3((unsigned)blocks), dim3(BIG_THREADS), 0,
-                         st, a, (int)grid.x, (int)(grid.x * grid.z));
-      return;
-    }
-  }
+static void launch_bigp(const GemmArgs& a, bool ident, dim3 grid, int blocks, hipStream_t st) {
   if (ident)
     hipLaunchKernelGGL((gemm_bigp_kernel<A_KC, B_KC, OutT, COLB, BIG_NONE, V16, N16>), dim3((unsigned)blocks), dim3(BIG_THREADS), 0, st, a,
                        (int)grid.x, (int)(grid.x * grid.z));
@@ -43,16 +43,17 @@ static void launch_bigp2(const GemmArgs& a, bool ident, dim3 grid, int blocks, h
                        (int)grid.x, (int)(grid.x * grid.z));
 }
 
-// One load-width flag matters per operand pair: v16 for two k-contiguous operands, n16 otherwise
-// (a k-contiguous operand next to an m/n-contiguous one always loads 16-byte pieces here).
-template <bool A_KC, bool B_KC, typename OutT, bool COLB>
-static void launch_bigp(const GemmArgs& a, bool ident, bool v16, bool n16, dim3 grid, int blocks, hipStream_t st) {
+// fp32 output: rows in whole 16-byte pieces have gone to the ring, those in 8-byte pieces are left with operands of both widths.
+// One load-width flag matters per operand pair: v16 for two k-contiguous operands, n16 otherwise (a k-contiguous operand next
+// to an m/n-contiguous one always loads 16-byte pieces here).
+template <bool A_KC, bool B_KC>
+static void launch_bigp_f32(const GemmArgs& a, bool ident, bool v16, bool n16, dim3 grid, int blocks, hipStream_t st) {
   if constexpr (A_KC && B_KC) {
-    if (v16) launch_bigp2<A_KC, B_KC, OutT, COLB, true, false>(a, ident, grid, blocks, st);
-    else launch_bigp2<A_KC, B_KC, OutT, COLB, false, false>(a, ident, grid, blocks, st);
+    if (v16) launch_bigp<A_KC, B_KC, float, false, true, false>(a, ident, grid, blocks, st);
+    else launch_bigp<A_KC, B_KC, float, false, false, false>(a, ident, grid, blocks, st);
   } else {
-    if (n16) launch_bigp2<A_KC, B_KC, OutT, COLB, true, true>(a, ident, grid, blocks, st);
-    else launch_bigp2<A_KC, B_KC, OutT, COLB, true, false>(a, ident, grid, blocks, st);
+    if (n16) launch_bigp<A_KC, B_KC, float, false, true, true>(a, ident, grid, blocks, st);
+    else launch_bigp<A_KC, B_KC, float, false, true, false>(a, ident, grid, blocks, st);
   }
 }
 
@@ -84,19 +85,24 @@ int gemm_big_launch(const GemmDesc& d, const GemmArgs& a0, bool v16, bool n16, d
     const bool f32 = d.out_f32 || a.splits > 1;
     const bool ident = d.act == HFTA_ACT_NONE;
     if (f32 && !colb) {
-      if (d.a_kc && !d.b_kc) { launch_bigp<true, false, float, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
-      if (d.a_kc && d.b_kc) { launch_bigp<true, true, float, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
-      if (!d.a_kc && !d.b_kc) { launch_bigp<false, false, float, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
+      if (d.a_kc && !d.b_kc) { launch_bigp_f32<true, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
+      if (d.a_kc && d.b_kc) { launch_bigp_f32<true, true>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
+      if (!d.a_kc && !d.b_kc) { launch_bigp_f32<false, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
+    } else if (!f32 && d.a_kc && !d.b_kc && !colb && ident && a.stat_part && a.splits == 1 && d.stat_done) {
+      if (n16) launch_stats<true>(a, grid, blocks, st);
+      else launch_stats<false>(a, grid, blocks, st);
+      const int rc = launch_status();
+      *d.stat_done = rc == HFTA_OK;
+      return rc;
     } else if (!f32) {
-      if (d.a_kc && !d.b_kc) {
-        if (colb) launch_bigp<true, false, bf16_raw, true>(a, ident, v16, n16, grid, blocks, st);
-        else launch_bigp<true, false, bf16_raw, false>(a, ident, v16, n16, grid, blocks, st);
-        const int rc = launch_status();
-        if (rc == HFTA_OK && !colb && ident && a.stat_part && a.splits == 1 && d.stat_done) *d.stat_done = true;
-        return rc;
+      // 8-byte aligned operand rows: those in whole 16-byte pieces have gone to the ring
+      if (d.a_kc && !d.b_kc && !n16) {
+        if (colb) launch_bigp<true, false, bf16_raw, true, true, false>(a, ident, grid, blocks, st);
+        else launch_bigp<true, false, bf16_raw, false, true, false>(a, ident, grid, blocks, st);
+        return launch_status();
       }
-      if (!colb && d.a_kc && d.b_kc) { launch_bigp<true, true, bf16_raw, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
-      if (!colb && !d.a_kc && !d.b_kc) { launch_bigp<false, false, bf16_raw, false>(a, ident, v16, n16, grid, blocks, st); return launch_status(); }
+      if (!colb && d.a_kc && d.b_kc && !v16) { launch_bigp<true, true, bf16_raw, false, false, false>(a, ident, grid, blocks, st); return launch_status(); }
+      if (!colb && !d.a_kc && !d.b_kc && !n16) { launch_bigp<false, false, bf16_raw, false, true, false>(a, ident, grid, blocks, st); return launch_status(); }
     }
   }
   if (!v16) {

@@ -18,12 +18,10 @@ static void launch(const GemmArgs& a, dim3 grid, int blocks, hipStream_t st) {
                      tiles);
 }
 
-template <bool A_KC, bool B_KC, bool COLB>
-static void launch_bf16(const GemmArgs& a, bool ident, dim3 grid, int blocks, hipStream_t st) {
-  if (ident && a.c_vec == 16) launch<A_KC, B_KC, bf16_raw, COLB, BIG_NONE, 16>(a, grid, blocks, st);
-  else if (ident) launch<A_KC, B_KC, bf16_raw, COLB, BIG_NONE, 8>(a, grid, blocks, st);
-  else if (a.c_vec == 16) launch<A_KC, B_KC, bf16_raw, COLB, BIG_SEL, 16>(a, grid, blocks, st);
-  else launch<A_KC, B_KC, bf16_raw, COLB, BIG_SEL, 8>(a, grid, blocks, st);
+template <bool A_KC, bool B_KC, bool COLB, int ACT>
+static void launch_bf16(const GemmArgs& a, dim3 grid, int blocks, hipStream_t st) {
+  if (a.c_vec == 16) launch<A_KC, B_KC, bf16_raw, COLB, ACT, 16>(a, grid, blocks, st);
+  else launch<A_KC, B_KC, bf16_raw, COLB, ACT, 8>(a, grid, blocks, st);
 }
 
 // `a` carries tile counts for 256x256 tiles of 64-element k-tiles and operand extents; every operand loads in whole aligned
@@ -53,14 +51,16 @@ int gemm_ring_launch(const GemmDesc& d, const GemmArgs& a0, dim3 grid, hipStream
     else if (!d.a_kc && !d.b_kc) launch<false, false, float, false, BIG_NONE, 16>(a, grid, blocks, st);
     else return HFTA_EUNSUPPORTED;
   } else if (d.a_kc && !d.b_kc) {
-    if (colb) launch_bf16<true, false, true>(a, ident, grid, blocks, st);
-    else launch_bf16<true, false, false>(a, ident, grid, blocks, st);
+    if (colb && ident) launch_bf16<true, false, true, BIG_NONE>(a, grid, blocks, st);
+    else if (colb) launch_bf16<true, false, true, BIG_SEL>(a, grid, blocks, st);
+    else if (ident) launch_bf16<true, false, false, BIG_NONE>(a, grid, blocks, st);
+    else launch_bf16<true, false, false, BIG_SEL>(a, grid, blocks, st);
   } else if (colb || !ident) {
     return HFTA_EUNSUPPORTED;
   } else if (d.a_kc && d.b_kc) {
-    launch_bf16<true, true, false>(a, true, grid, blocks, st);
+    launch_bf16<true, true, false, BIG_NONE>(a, grid, blocks, st);
   } else if (!d.a_kc && !d.b_kc) {
-    launch_bf16<false, false, false>(a, true, grid, blocks, st);
+    launch_bf16<false, false, false, BIG_NONE>(a, grid, blocks, st);
   } else {
     return HFTA_EUNSUPPORTED;
   }
