@@ -56,13 +56,13 @@ __global__ __launch_bounds__(256) void conv_dx_fewc_kernel(FewcArgs p) {
     from[i] = ok ? ((uint32_t)oc * (uint32_t)P + (uint32_t)(y * p.Wq + x)) * 2u : PF_OOB;                 // out of range: zeros, no memory request
     to[i] = (uint32_t)((oc * (FC_TY + 2) + row) * FC_PW + (PAIR ? 2 * col : col + 1));
   }
-  const __amdgpu_buffer_rsrc_t rs = pf_rsrc(dy, (uint32_t)((int64_t)p.Co * P * 2));   // channels past the last: zeros too
+  // a buffer per stage; what is read for channels past the last is not used
   auto fetch = [&](int o0) {
-    const uint32_t at = (uint32_t)o0 * (uint32_t)P * 2u;
+    const __amdgpu_buffer_rsrc_t rs = pf_rsrc(dy + (int64_t)o0 * P, (uint32_t)min(FC_OC, p.Co - o0) * (uint32_t)P * 2u);
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i)
-      stage[i] = PAIR ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(from[i] + at), 0, 0)
-                      : (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(from[i] + at), 0, 0);
+      stage[i] = PAIR ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)from[i], 0, 0)
+                      : (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)from[i], 0, 0);
   };
   auto park = [&](int buf) {
 #pragma unroll
@@ -155,9 +155,10 @@ __global__ __launch_bounds__(256) void conv_dx_fewc_kernel(FewcArgs p) {
 
 }  // namespace
 
+// A stage of dY, sixteen channels or what there is, has to lie below 2 GiB: gradients of 2^26 pixels and more take the general path.
 bool conv_dx_fewc_supported(int Nb, int B, int Ci, int Co, int H, int W, int kh, int kw, int stride, int pad) {
   return kh == 4 && kw == 4 && stride == 2 && pad == 1 && Ci >= 1 && Ci <= 4 && H % 2 == 0 && W % 2 == 0 && Nb <= 65535 && B <= 65535 &&
-         (int64_t)Co * (H / 2) * (W / 2) * 2 < ((int64_t)1 << 31);                       // a sample's dY: one buffer
+         (int64_t)(Co < 16 ? Co : 16) * (H / 2) * (W / 2) * 2 < ((int64_t)1 << 31);
 }
 
 int conv_dx_fewc(int B, int Nb, int Ci, int Co, int H, int W, const void* Wt, const void* dY, void* dX, hipStream_t st) {

@@ -5,6 +5,7 @@ ragged samples and channels, below one workgroup per compute unit (two k-tiles o
 kernel keeps.  Same reference and tolerance as the operator's other sizes."""
 import numpy as np
 import pytest
+import torch
 
 import hfta_inputs as hi
 import test_gpu_ops as ops
@@ -57,3 +58,20 @@ def test_data_gradient_of_few_channels(hb, B, Nb, Ci, Co, H, W, shift):
     dY.copy_(flat)
     hb.conv2d_grouped_bwd(B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1, dev(x, "bf16"), dev(w, "bf16"), dY.view(dy.shape), dX, None, None, ws)
     check(host(dX), oa.conv2d_bwd(B, x, w, dy, 2, 1)[0], TOL["bf16"], "dX")
+
+
+def test_data_gradient_of_few_channels_of_a_large_image(hb):
+    """One sample whose gradient is 2 GiB: the last rows are, bit for bit, those of an image that has only these."""
+    Ci, Co, H, q = 3, 64, 8192, 34
+    print("few channels, 2 GiB of gradient", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    dY = torch.randn((Co, H // 2, H // 2), generator=gen, device="cuda", dtype=torch.bfloat16)
+    W = torch.randn((Co, Ci, 4, 4), generator=gen, device="cuda", dtype=torch.bfloat16)
+    dX = torch.full((Ci, H, H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    hb.conv2d_grouped_bwd(1, 1, Ci, Co, H, H, 4, 4, 2, 1, 1, dX, W, dY, dX, None, None, None)
+    rows = dY[:, -q:].contiguous()
+    part = torch.full((Ci, 2 * q, H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    hb.conv2d_grouped_bwd(1, 1, Ci, Co, 2 * q, H, 4, 4, 2, 1, 1, part, W, rows, part, None, None, None)
+    assert torch.equal(dX[:, 2 - 2 * q:], part[:, 2:])
+    x = torch.nn.functional.conv_transpose2d(rows[:, -4:, -4:].float().cpu()[None], W.float().cpu(), stride=2, padding=1)[0]
+    check(host(dX[:, -6:, -6:]), x[:, 2:, 2:].double().numpy(), TOL["bf16"], "corner")
