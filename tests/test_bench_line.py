@@ -4,6 +4,10 @@ import glob
 import json
 import os
 import re
+import shutil
+import subprocess
+
+import pytest
 
 import bench
 
@@ -55,3 +59,17 @@ def test_profiled_traffic_is_that_of_present_kernels():
         for key in json.load(open(path)):
             for kernel in re.findall(r"\w+_kernel\b", key):
                 assert kernel in csrc and (kernel in src or kernel[:-len("_kernel")] in bench.Tracer.SINGLE_KERNEL), (path, kernel)
+
+
+def test_profiled_kernels_are_in_the_library():
+    """The kernels that the tables under profiles/ name, template arguments and all, are those that the library holds."""
+    lib = os.path.join(bench.ROOT, "paper_2102_02344_amd", "libhfta.so")
+    if not os.path.exists(lib) or shutil.which("nm") is None:
+        pytest.skip("needs the built library and nm")
+    syms = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True).stdout
+    have = set(re.findall(r"__device_stub__(\w+_kernel(?:<[^()]*>)?)\(", syms))
+    named = set()
+    for path in glob.glob(os.path.join(bench.ROOT, "profiles", "*.md")):
+        # (rows of bench.py's entries go by families' names, without arguments)
+        named |= {n for n in re.findall(r"`(\w+_kernel(?:<[^`]*>)?)` (?:\||\()", open(path).read()) if "<" in n or "traffic" not in path}
+    assert len(named) > 80 and named <= have, sorted(named - have)
