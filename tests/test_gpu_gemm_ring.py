@@ -40,18 +40,20 @@ def test_linear(hb, B, M, Fx, Fy, relu):
     check(host(dW), torch.matmul(x.transpose(1, 2).contiguous(), dy).numpy(), f32_tol("bf16"), "dW")
 
 
-@pytest.mark.parametrize("B,M,Fx,Fy,relu", [(8, 2048, 256, 1024, True), (16, 768, 512, 1024, False), (12, 1024, 384, 1016, False), (4, 2048, 256, 2044, True)])
-def test_bias_after_the_sum(hb, B, M, Fx, Fy, relu):
+@pytest.mark.parametrize("B,M,Fx,Fy,relu,shift", [(8, 2048, 256, 1024, True, 0), (16, 768, 512, 1024, False, 0), (12, 1024, 384, 1016, False, 0),
+                                                  (4, 2048, 256, 2044, True, 0), (7, 2000, 256, 1016, True, 4), (13, 1024, 264, 1024, False, 4)])
+def test_bias_after_the_sum(hb, B, M, Fx, Fy, relu, shift):
     """One output tile per workgroup (192 to 256 tiles): the bias is added to the finished sum.  The partial sums pass through
-    2^27, where a bias of a few units added at the start would be rounded away, and return to zero: the output is the bias."""
-    print(f"bias after the sum B={B} M={M} Fx={Fx} Fy={Fy}", flush=True)
+    2^27, where a bias of a few units added at the start would be rounded away, and return to zero: the output is the bias.
+    `shift`: elements by which the output starts off 16 bytes."""
+    print(f"bias after the sum B={B} M={M} Fx={Fx} Fy={Fy} shift={shift}", flush=True)
     assert 192 <= B * ((M + 255) // 256) * ((Fy + 255) // 256) <= torch.cuda.get_device_properties(0).multi_processor_count
     gen = torch.Generator().manual_seed(7)
     X = torch.full((B, M, Fx), 1024.0, dtype=torch.bfloat16)
     W = torch.full((B, Fx, Fy), 1024.0, dtype=torch.bfloat16)
     W[:, Fx // 2:] = -1024.0
     b = torch.randint(1, 5, (B, Fy), generator=gen).bfloat16()
-    Y = torch.full((B, M, Fy), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Y = torch.full((B * M * Fy + shift,), float("nan"), dtype=torch.bfloat16, device="cuda")[shift:].view(B, M, Fy)
     hb.linear_fwd(B, M, Fx, Fy, DT["bf16"], X.cuda(), W.cuda(), b.cuda(), Y, act=hb.ACT_RELU if relu else hb.ACT_NONE)
     assert torch.equal(Y.cpu(), b[:, None, :].expand(B, M, Fy))
 
