@@ -166,7 +166,7 @@ __global__ __launch_bounds__(HIT_THREADS) void pool32_prep_kernel(Pool32Args p, 
 // ---- reference for a model, its first 64 points, what the others lie off by (64 x 8 clouds padded in front with a point five
 // ---- spreads away: 7.5e-6 for 5.3e-7 of the stored operators, now 1.4e-7).  The six products of two splits as in gemm_f32.hip.
 // ---- 4 x 32 x 2500 x 128: 107 us (98 about one reference), of 5.3 a tile 1.9 are its bytes and 1.4 its matrix instructions: the
-// ---- phases of the one workgroup per compute unit (eight wavefronts, 216 registers) follow each other.  Two workgroups spill
+// ---- phases of the one workgroup per compute unit (eight wavefronts, 248 registers) follow each other.  Two workgroups spill
 // ---- (136-317 us); a pass for the hits and the product over the points on the general kernel took 150. ----
 constexpr int MM_PTS = 64, MM_THREADS = 512, MM_WN = MM_THREADS / 128, MM_NJ = 4 / MM_WN, MM_ROWS = MM_THREADS / 16, MM_H = 128 / MM_ROWS, MM_PLANE = 128 * MM_PTS * 2;
 __device__ __forceinline__ int mm_swz(int r) { return (r ^ (r >> 3)) & 7; }
@@ -181,6 +181,9 @@ __device__ __forceinline__ float mm_sum16(float v) {
   return v + mm_ror<1>(v);
 }
 constexpr int MM_GROUP = MM_PTS, MM_PITCH = 129;           // means: tiles of a group, floats a tile
+// tiles added up before they join the others: on channels correlated at 0.99, 66 tiles to a workgroup, dW is 8.9e-7 off float64
+// (1.8e-6 without, the stored operators 1.0e-6), in the same time
+constexpr int MM_RUN = 8;
 __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Args p) {
   __shared__ __attribute__((aligned(16))) unsigned char planes[3 * MM_PLANE];
   __shared__ __attribute__((aligned(16))) float raw[128 * MM_PTS];     // 16-byte piece q of row r at q ^ (r & 15)
@@ -207,13 +210,21 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
     const int n = tile / per;
     fetch(xb + n * p.xsn, tile < t1 ? (tile - n * per) * MM_PTS + piece * 4 : p.L);
   };
-  f32x16_t acc[2][MM_NJ];
+  f32x16_t acc[2][MM_NJ], sum[2][MM_NJ];                   // of up to MM_RUN tiles, of all
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < MM_NJ; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = sum[i][j][v] = 0.f;
+  auto gather = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < MM_NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { sum[i][j][v] += acc[i][j][v]; acc[i][j][v] = 0.f; }
+  };
   int hlo, hhi;
   auto range = [&](int tile) {                             // of the hits of the 128-point tile that `tile` is half of
     const int tc = min(tile, t1 - 1), n = tc / per;
@@ -235,8 +246,8 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
     const int r = r0 + (lane & 31);
     return *reinterpret_cast<const bf16x8_t*>(planes + pl * MM_PLANE + r * (MM_PTS * 2) + (((2 * s + (lane >> 5)) ^ mm_swz(r)) << 4));
   };
-  // one block after the other, a tile's accumulators for one block only: registers.  A tile's sums start from zero: one rounding a
-  // tile at the size of all.
+  // one block after the other, a tile's accumulators for one block only: registers.  A tile's sums start from zero, and so do
+  // those of MM_RUN tiles: few roundings at the size of all.
   auto products = [&]() {
 #pragma unroll
     for (int ij = 0; ij < 2 * MM_NJ; ++ij) {
@@ -285,6 +296,7 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
       const uint32_t first = h_lo + lane < h_hi ? p.skey[smp * p.Co + h_lo + lane] : 0xffffffffu;
       range(tile + 1);
       products();
+      if ((tile - g0) % MM_RUN == MM_RUN - 1) gather();
       // this tile's hits: those of its 128-point tile whose point is in it, in turn over the wavefronts
       for (int h0 = h_lo; h0 < h_hi; h0 += 64) {
         const uint32_t kl = h0 == h_lo ? first : h0 + lane < h_hi ? p.skey[smp * p.Co + h0 + lane] : 0xffffffffu;
@@ -333,6 +345,7 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
     }
     __syncthreads();
     products();
+    gather();
   }
   float* XX = p.XXpart + ((int64_t)chunk * p.B + b) * p.Ci * p.Ci;
   // symmetric, element by element the same products in the same order up to the corrections': out as gram_kernel's
@@ -344,7 +357,7 @@ __global__ __launch_bounds__(MM_THREADS, 2) void pool32_moments_kernel(Pool32Arg
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int cj = (wn * MM_NJ + j) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (ci < p.Ci && cj < p.Ci) XX[(int64_t)cj * p.Ci + ci] = acc[i][j][v];
+        if (ci < p.Ci && cj < p.Ci) XX[(int64_t)cj * p.Ci + ci] = sum[i][j][v];
       }
   }
 }

@@ -109,7 +109,12 @@ def _ordered(X):
     X += 2.0 * X[:, :, :1].sort(3).values
 
 
-@pytest.mark.parametrize("how", [_padded, _front, _ordered])
+def _correlated(X):
+    """Channels that are pairwise correlated at 0.99."""
+    X.mul_(0.1).add_(0.99 ** 0.5 * torch.randn(X[:, :, :1].shape, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda"))
+
+
+@pytest.mark.parametrize("how", [_padded, _front, _ordered, _correlated])
 @pytest.mark.parametrize("dims", [(2, 16, 128, 256, 2048), (3, 29, 68, 130, 1023), (64, 8, 68, 70, 2050), (64, 1, 72, 66, 16400)])
 def test_points_that_are_not_alike(hb, dims, how):
     """dW of clouds whose points are not spread alike over their memory: no further off float64 than the stored chain is (see
