@@ -44,6 +44,21 @@ def _on_16_bytes(w):
     return w.data_ptr() % 16 == 0
 
 
+def _few_rows(A, i, fc, prefix, B, Nb, dt):
+    """Whether layer i of a fully connected head takes the calls that run a Linear together with what stands beside it
+    (BatchNorm, dropout or the loss; the same bits as the single operators)."""
+    return hb.linear_few_supported(B, Nb, fc[i], fc[i + 1], dt) and _on_16_bytes(A.w(f"{prefix}fc{i}.w"))
+
+
+def _few_bwd(A, i, fc, prefix, hin, fz, d, out, own_db, below, mask, p):
+    """One launch for layer i's Linear backward; ``below``: its data gradient goes on through the dropout (``mask``) and the
+    BatchNorm of layer i - 1 to the gradient of ``fz[i - 1]``."""
+    k, kb = f"{prefix}fc{i}", f"{prefix}fc{i - 1}"
+    bn = (fz[i - 1], A.master(kb + ".bn.g"), A.master(kb + ".bn.b"), A.saved[kb + ".bn.mean"], A.saved[kb + ".bn.invstd"],
+          hb.ACT_RELU, 0.0, mask, p, A.g(kb + ".bn.g"), A.g(kb + ".bn.b"), A.g(kb + ".b")) if below else ()
+    hb.linear_bwd_bn(A.B, A.Nb, fc[i], fc[i + 1], A.dt, hin, A.w(k + ".w"), d, out, A.g(k + ".w"), own_db, *bn)
+
+
 def _bn_bwd_one_pass(B, Nb, ci, co, L, dt):
     """True when ``conv1x1_bn_bwd`` runs this layer as one streaming kernel (dz never stored).  Layers it
     would run as the two single operators are called as such here, with dz in one of the array's
@@ -447,6 +462,19 @@ class FusedPointNetCls(ParamArena):
             fy = s.fc[i + 1]
             k = f"fc{i}"
             last = i == self.nfc - 1
+            if P is None and s.fc_bn and _few_rows(self, i, s.fc, "", B, Nb, dt):
+                if last and fy <= 32:
+                    d = self._cut(self.fd[0], B * Nb * fy)
+                    hb.linear_xent(B, Nb, fx, fy, dt, h, self.w(k + ".w"), self.w(k + ".b"), self.fz[i], self.labels, self.loss, d)
+                    break
+                if not last:
+                    drop = i == self.nfc - 2 and s.dropout_p > 0
+                    hb.linear_bn_fwd(B, Nb, fx, fy, dt, h, self.w(k + ".w"), self.w(k + ".b"), self.master(k + ".bn.g"),
+                                     self.master(k + ".bn.b"), eps, mom, self.running[k + ".bn.rm"], self.running[k + ".bn.rv"],
+                                     self.saved[k + ".bn.mean"], self.saved[k + ".bn.invstd"], self.fz[i], self.fh[i], hb.ACT_RELU,
+                                     0.0, self.drop_mask if drop else None, s.dropout_p if drop else 0.0, self.fdrop if drop else None)
+                    h, fx = self.fdrop if drop else self.fh[i], fy
+                    continue
             if last or s.fc_bn:
                 hb.linear_fwd_ws(B, Nb, fx, fy, dt, h, self.w(k + ".w"), self.w(k + ".b"), self.fz[i], workspace=self.ws)
                 if P is not None:
@@ -475,20 +503,22 @@ class FusedPointNetCls(ParamArena):
                         P("dropout", x=h, mask=self.drop_mask, y=self.fdrop)
                     h = self.fdrop
             fx = fy
-        logits = h
-        K = s.fc[-1]
-        d = self._cut(self.fd[0], B * Nb * K)
-        hb.softmax_xent(B, Nb, K, dt, logits, self.labels, self.loss, d)
-        if P is not None:
-            P("softmax_xent", logits=logits, labels=self.labels, loss=self.loss, d=d.view(B, Nb, K))
+        else:
+            logits = h
+            K = s.fc[-1]
+            d = self._cut(self.fd[0], B * Nb * K)
+            hb.softmax_xent(B, Nb, K, dt, logits, self.labels, self.loss, d)
+            if P is not None:
+                P("softmax_xent", logits=logits, labels=self.labels, loss=self.loss, d=d.view(B, Nb, K))
 
         # backward: head
         cur = 0
+        through = False          # the call before carried the gradient on through this layer's BatchNorm
         for i in reversed(range(self.nfc)):
             fx, fy = s.fc[i], s.fc[i + 1]
             k = f"fc{i}"
             last = i == self.nfc - 1
-            if not last:
+            if not last and not through:
                 n = B * Nb * fy
                 if i == self.nfc - 2 and s.dropout_p > 0:
                     nd = self._cut(self.fd[cur ^ 1], n)
@@ -521,6 +551,14 @@ class FusedPointNetCls(ParamArena):
             nd = self._cut(self.fd[cur ^ 1], B * Nb * fx)
             # a bias that feeds a BatchNorm gets its gradient from that BatchNorm's backward (dx_sum)
             own_db = self.g(k + ".b") if (last or not s.fc_bn) else None
+            through = False
+            if P is None and s.fc_bn and _few_rows(self, i, s.fc, "", B, Nb, dt):
+                through = i > 0
+                drop = through and last and s.dropout_p > 0
+                _few_bwd(self, i, s.fc, "", hin, self.fz, d, nd, own_db, through, self.drop_mask if drop else None,
+                         s.dropout_p if drop else 0.0)
+                d, cur = nd, cur ^ 1
+                continue
             hb.linear_bwd(B, Nb, fx, fy, dt, hin, self.w(k + ".w"), d, nd, self.g(k + ".w"), own_db, self.ws)
             if P is not None:
                 P("linear_bwd", layer=k, x=hin, w=self.w(k + ".w"), dy=d.view(B, Nb, fy), dx=nd.view(B, Nb, fx),
@@ -1542,8 +1580,9 @@ class _PointChain(_Views):
         return (A.master(k + ".bn.g"), A.master(k + ".bn.b"), A.BN_EPS, A.BN_MOMENTUM, A.running[k + ".bn.rm"],
                 A.running[k + ".bn.rv"], A.saved[k + ".bn.mean"], A.saved[k + ".bn.invstd"])
 
-    def fwd(self, x):
-        """x: [Nb, B*conv[0], L] contiguous.  Returns the last activation (no head) or the last Linear's output."""
+    def fwd(self, x, xent=None):
+        """x: [Nb, B*conv[0], L] contiguous.  Returns the last activation (no head) or the last Linear's output;
+        ``xent``: (labels, loss, dlogits) of the softmax cross-entropy of that output."""
         A = self.A
         B, Nb, L, dt, ws = A.B, A.Nb, A.L, A.dt, A.ws
         self.x_in = x
@@ -1579,9 +1618,22 @@ class _PointChain(_Views):
         for i in range(self.nfc):
             fx, fy, k = self.fc[i], self.fc[i + 1], f"{self.px}fc{i}"
             last = i == self.nfc - 1
+            if self.fc_bn and _few_rows(A, i, self.fc, self.px, B, Nb, dt):
+                if last and xent is not None and fy <= 32:
+                    hb.linear_xent(B, Nb, fx, fy, dt, h, A.w(k + ".w"), A.w(k + ".b"), self.fz[i], *xent)
+                    return self.fz[i]
+                if not last:
+                    drop = i == self.nfc - 2 and self.dropout_p > 0
+                    hb.linear_bn_fwd(B, Nb, fx, fy, dt, h, A.w(k + ".w"), A.w(k + ".b"), *self._bn(k), self.fz[i], self.fh[i],
+                                     hb.ACT_RELU, 0.0, self.drop_mask if drop else None, self.dropout_p if drop else 0.0,
+                                     self.fdrop if drop else None)
+                    h = self.fdrop if drop else self.fh[i]
+                    continue
             if last or self.fc_bn:
                 hb.linear_fwd_ws(B, Nb, fx, fy, dt, h, A.w(k + ".w"), A.w(k + ".b"), self.fz[i], workspace=ws)
                 if last:
+                    if xent is not None:
+                        hb.softmax_xent(B, Nb, fy, dt, self.fz[i], *xent)
                     return self.fz[i]
                 ls = (Nb * fy, fy, 1, 1)
                 hb.bn_fwd(B, Nb, fy, 1, dt, self.fz[i], ls, *self._bn(k), self.fh[i], ls, hb.ACT_RELU)
@@ -1598,10 +1650,11 @@ class _PointChain(_Views):
         A = self.A
         B, Nb, L, dt, ws = A.B, A.Nb, A.L, A.dt, A.ws
         cur = 0
+        through = False          # the call before carried the gradient on through this layer's BatchNorm
         for i in reversed(range(self.nfc)):
             fx, fy, k = self.fc[i], self.fc[i + 1], f"{self.px}fc{i}"
             last = i == self.nfc - 1
-            if not last:
+            if not last and not through:
                 n = B * Nb * fy
                 if i == self.nfc - 2 and self.dropout_p > 0:
                     nd = self._cut(self.fd[cur ^ 1], n)
@@ -1624,6 +1677,14 @@ class _PointChain(_Views):
                 hin = self.fh[i - 1]
             nd = self._cut(self.fd[cur ^ 1], B * Nb * fx)
             own_db = A.g(k + ".b") if (last or not self.fc_bn) else None
+            through = False
+            if self.fc_bn and _on_16_bytes(d) and _few_rows(A, i, self.fc, self.px, B, Nb, dt):
+                through = i > 0
+                drop = through and last and self.dropout_p > 0
+                _few_bwd(A, i, self.fc, self.px, hin, self.fz, d, nd, own_db, through, self.drop_mask if drop else None,
+                         self.dropout_p if drop else 0.0)
+                d, cur = nd, cur ^ 1
+                continue
             hb.linear_bwd(B, Nb, fx, fy, dt, hin, A.w(k + ".w"), d, nd, A.g(k + ".w"), own_db, ws)
             d, cur = nd, cur ^ 1
 
@@ -1751,8 +1812,7 @@ class FusedPointNetClsT(ParamArena):
         x = self.block0.fwd(x)
         if self.t_feat is not None:
             x = self._transform_fwd(self.t_feat, x)
-        logits = self.rest.fwd(x)
-        hb.softmax_xent(B, Nb, s.fc[-1], dt, logits, self.labels, self.loss, self.dlogits)
+        self.rest.fwd(x, (self.labels, self.loss, self.dlogits))
         d = self.rest.bwd(self.dlogits, True)
         if self.t_feat is not None:
             d = self._transform_bwd(self.t_feat, d, True)

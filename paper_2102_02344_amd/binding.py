@@ -50,6 +50,10 @@ _SIGS = {
     "hfta_linear_fwd_static": (_i, [_i, _i, _i, _i, _i, _p, _p, _p, _p, _i, _f, _p]),
     "hfta_linear_bwd_workspace_bytes": (_sz, [_i, _i, _i, _i, _i]),
     "hfta_linear_bwd": (_i, [_i, _i, _i, _i, _i, _p, _p, _p, _p, _p, _p, _p, _sz, _p]),
+    "hfta_linear_few_supported": (_i, [_i] * 5),
+    "hfta_linear_bn_fwd": (_i, [_i] * 5 + [_p] * 5 + [_f, _f] + [_p] * 6 + [_i, _f, _p, _f, _p, _p]),
+    "hfta_linear_xent": (_i, [_i] * 5 + [_p] * 8),
+    "hfta_linear_bwd_bn": (_i, [_i] * 5 + [_p] * 11 + [_i, _f, _p, _f] + [_p] * 4),
     "hfta_conv1x1_fwd": (_i, [_i, _i, _i, _i, _i, _i, _p, _s4, _p, _p, _p, _s4, _i, _f, _p]),
     "hfta_conv1x1_fwd_sample_bias": (_i, [_i, _i, _i, _i, _i, _i, _p, _s4, _p, _p, _s4, _p, _s4, _i, _f, _p]),
     "hfta_conv1x1_bn_fwd_workspace_bytes": (_sz, [_i, _i, _i, _i, _i, _i]),
@@ -236,6 +240,29 @@ def linear_bwd(B, M, Fx, Fy, dtype, X, W, dY, dX, dW, dbias, workspace=None, str
     wp, wb = _ws(workspace)
     _check(_lib.hfta_linear_bwd(B, M, Fx, Fy, dtype, _ptr(X), _ptr(W), _ptr(dY), _ptr(dX), _ptr(dW), _ptr(dbias),
                                 wp, wb, _stream(stream)), "hfta_linear_bwd")
+
+
+def linear_few_supported(B, M, Fx, Fy, dtype) -> bool:
+    return bool(_lib.hfta_linear_few_supported(B, M, Fx, Fy, dtype))
+
+
+def linear_bn_fwd(B, M, Fx, Fy, dtype, X, W, bias, gamma, beta, eps, momentum, running_mean, running_var, save_mean, save_invstd,
+                  Z, Y, act=ACT_NONE, act_slope=0.0, mask=None, p=0.0, Yd=None, stream=None):
+    _check(_lib.hfta_linear_bn_fwd(B, M, Fx, Fy, dtype, _ptr(X), _ptr(W), _ptr(bias), _ptr(gamma), _ptr(beta), eps, momentum,
+                                   _ptr(running_mean), _ptr(running_var), _ptr(save_mean), _ptr(save_invstd), _ptr(Z), _ptr(Y),
+                                   act, act_slope, _ptr(mask), p, _ptr(Yd), _stream(stream)), "hfta_linear_bn_fwd")
+
+
+def linear_xent(B, M, Fx, K, dtype, X, W, bias, logits, labels, loss, dlogits, stream=None):
+    _check(_lib.hfta_linear_xent(B, M, Fx, K, dtype, _ptr(X), _ptr(W), _ptr(bias), _ptr(logits), _ptr(labels), _ptr(loss),
+                                 _ptr(dlogits), _stream(stream)), "hfta_linear_xent")
+
+
+def linear_bwd_bn(B, M, Fx, Fy, dtype, X, W, dY, dX, dW, dbias, Z=None, gamma=None, beta=None, save_mean=None, save_invstd=None,
+                  act=ACT_NONE, act_slope=0.0, mask=None, p=0.0, dgamma=None, dbeta=None, dx_sum=None, stream=None):
+    _check(_lib.hfta_linear_bwd_bn(B, M, Fx, Fy, dtype, _ptr(X), _ptr(W), _ptr(dY), _ptr(dX), _ptr(dW), _ptr(dbias), _ptr(Z),
+                                   _ptr(gamma), _ptr(beta), _ptr(save_mean), _ptr(save_invstd), act, act_slope, _ptr(mask), p,
+                                   _ptr(dgamma), _ptr(dbeta), _ptr(dx_sum), _stream(stream)), "hfta_linear_bwd_bn")
 
 
 def conv1x1_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, Y, ys, act=ACT_NONE, act_slope=0.0, stream=None):

@@ -280,6 +280,8 @@ float* static_scratch() {
 }  // namespace
 
 namespace hfta {
+// the split of a few-row product, for the kernel that takes BatchNorm along (linear_few.hip)
+int linear_row_splits(int B, int M, int Fx, int Fy, int dtype) { return linear_fwd_splits(B, M, Fx, Fy, dtype); }
 // k=1 convolution of at most 4 bf16 input channels and 256 outputs over rows of at least 4 points; W[o][c] of model b and
 // sample n at b * w_b + n * w_n
 int conv1x1_tinyk(int B, int Nb, int Ci, int Co, int L, const void* X, const int64_t xs[4], const void* W, int64_t w_b, int64_t w_n,
