@@ -119,6 +119,8 @@ int hfta_linear_fwd_static(int B, int M, int Fx, int Fy, int dtype,
  *   dbias[b] = column sums of dY[b]  (fp32 [B][Fy]; NULL = skip)
  * Workspace: hfta_linear_bwd_workspace_bytes (split-K partials of dW). */
 size_t hfta_linear_bwd_workspace_bytes(int B, int M, int Fx, int Fy, int dtype);
+/* 1 where one call for dX and dW is one launch on 16-byte aligned operands (small products): the same bits as two calls, sooner. */
+int hfta_linear_bwd_pair_supported(int B, int M, int Fx, int Fy, int dtype);
 int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype,
                     const void* X, const void* W, const void* dY,
                     void* dX, float* dW, float* dbias,

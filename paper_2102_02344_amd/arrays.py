@@ -738,6 +738,8 @@ class FusedMlp(ParamArena):
                  hb.linear_bwd_workspace_bytes(B, R, E, H, self.dt),
                  hb.linear_bwd_workspace_bytes(B, R, H, E, self.dt))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=self.dev)
+        # both gradients of the first and of the second Linear of a block in one launch
+        self.one_launch = (hb.linear_bwd_pair_supported(B, R, E, H, self.dt), hb.linear_bwd_pair_supported(B, R, H, E, self.dt))
 
     def forward_backward(self, probe=None):
         """One forward + backward pass; ``probe(op, **tensors)`` as in FusedPointNetCls."""
@@ -789,9 +791,12 @@ class FusedMlp(ParamArena):
                 P("layernorm_bwd", layer=k, x=self.s[i], dy=ga, dy2=gb if fused_ln else None, w=self.master(k + ".ln.w"),
                   mean=self.ln_mean[i], invstd=self.ln_invstd[i], dx=ds, dw=self.g(k + ".ln.w"), db=self.g(k + ".ln.b"))
             # data gradient and weight gradient as separate calls (one kernel each), so a caller can
-            # time them separately
-            hb.linear_bwd(B, R, H, E, dt, None, self.w(k + ".w2"), ds, self.dH[0], None, None, None)
-            hb.linear_bwd(B, R, H, E, dt, self.h[i], None, ds, None, self.g(k + ".w2"), None, self.ws)
+            # time them separately, except where one call is one launch
+            if self.one_launch[1]:
+                hb.linear_bwd(B, R, H, E, dt, self.h[i], self.w(k + ".w2"), ds, self.dH[0], self.g(k + ".w2"), None, self.ws)
+            else:
+                hb.linear_bwd(B, R, H, E, dt, None, self.w(k + ".w2"), ds, self.dH[0], None, None, None)
+                hb.linear_bwd(B, R, H, E, dt, self.h[i], None, ds, None, self.g(k + ".w2"), None, self.ws)
             if P is not None:
                 P("linear_bwd", layer=k + ".2", x=self.h[i], w=self.w(k + ".w2"), dy=ds, dx=self.dH[0],
                   dw=self.g(k + ".w2"), db=self.g(k + ".b2"))
@@ -807,9 +812,12 @@ class FusedMlp(ParamArena):
             # nothing consumes the gradient of the array's input: the first block computes no data
             # gradient of its first Linear
             dxl = ga                                   # this block's incoming gradient is dead: reuse it
-            if i > 0:
-                hb.linear_bwd(B, R, E, H, dt, None, self.w(k + ".w1"), self.dH[1], dxl, None, None, None)
-            hb.linear_bwd(B, R, E, H, dt, self.x[i], None, self.dH[1], None, self.g(k + ".w1"), None, self.ws)
+            if i > 0 and self.one_launch[0]:
+                hb.linear_bwd(B, R, E, H, dt, self.x[i], self.w(k + ".w1"), self.dH[1], dxl, self.g(k + ".w1"), None, self.ws)
+            else:
+                if i > 0:
+                    hb.linear_bwd(B, R, E, H, dt, None, self.w(k + ".w1"), self.dH[1], dxl, None, None, None)
+                hb.linear_bwd(B, R, E, H, dt, self.x[i], None, self.dH[1], None, self.g(k + ".w1"), None, self.ws)
             if P is not None:
                 P("linear_bwd", layer=k + ".1", x=self.x[i], w=self.w(k + ".w1"), dy=self.dH[1], dx=dxl if i > 0 else None,
                   dw=self.g(k + ".w1"), db=self.g(k + ".b1"))

@@ -49,6 +49,7 @@ _SIGS = {
     "hfta_linear_fwd_static_max_bytes": (_sz, []),
     "hfta_linear_fwd_static": (_i, [_i, _i, _i, _i, _i, _p, _p, _p, _p, _i, _f, _p]),
     "hfta_linear_bwd_workspace_bytes": (_sz, [_i, _i, _i, _i, _i]),
+    "hfta_linear_bwd_pair_supported": (_i, [_i] * 5),
     "hfta_linear_bwd": (_i, [_i, _i, _i, _i, _i, _p, _p, _p, _p, _p, _p, _p, _sz, _p]),
     "hfta_linear_few_supported": (_i, [_i] * 5),
     "hfta_linear_bn_fwd": (_i, [_i] * 5 + [_p] * 5 + [_f, _f] + [_p] * 6 + [_i, _f, _p, _f, _p, _p]),
@@ -234,6 +235,10 @@ def linear_fwd_static(B, M, Fx, Fy, dtype, X, W, bias, Y, act=ACT_NONE, act_slop
 
 def linear_bwd_workspace_bytes(B, M, Fx, Fy, dtype) -> int:
     return _lib.hfta_linear_bwd_workspace_bytes(B, M, Fx, Fy, dtype)
+
+
+def linear_bwd_pair_supported(B, M, Fx, Fy, dtype) -> bool:
+    return bool(_lib.hfta_linear_bwd_pair_supported(B, M, Fx, Fy, dtype))
 
 
 def linear_bwd(B, M, Fx, Fy, dtype, X, W, dY, dX, dW, dbias, workspace=None, stream=None):

@@ -537,5 +537,7 @@ int gemm_pick_splits(const GemmDesc& d);         // from the shape alone (worksp
 int gemm_splits(const GemmDesc& d);              // with the operands known
 size_t gemm_partial_bytes(const GemmDesc& d, int splits);
 int gemm_launch(const GemmDesc& d, hipStream_t stream);
+// both gradients of a Linear in one launch (bf16); HFTA_EUNSUPPORTED: make the two launches
+int gemm_pair_launch(const GemmDesc& dw, const GemmDesc& dx, hipStream_t stream);
 
 }  // namespace hfta

@@ -73,19 +73,30 @@ int gemm_pick_splits(const GemmDesc& d) {
   return want < 1 ? 1 : (int)want;
 }
 
+// bytes from an operand slice's first to one past its last element
+static int64_t slice_bytes(bool kc, int64_t rows, int64_t K, int64_t ld, int es) {
+  return (kc ? (rows - 1) * ld + K : (K - 1) * ld + rows) * es;
+}
+// widest store (bytes) that every row start of an output of `es`-byte elements is aligned to
+static int store_bytes(int es, const void* p, int64_t ld, int64_t s0, int64_t s1) {
+  for (int w = 16; w >= 8; w >>= 1) {
+    const int q = w / es;
+    if (aligned_to(p, w) && ld % q == 0 && s0 % q == 0 && s1 % q == 0) return w;
+  }
+  return 0;
+}
+
 // Whether an unsplit launch of d takes the kernel that loads straight into LDS: its shapes, whole aligned 16-byte pieces,
 // operand slices that fit a buffer.
-static bool loads_to_lds(const GemmDesc& d) {
-  if (gemm_dma_tile(d) < 0) return false;
+static bool lds_operands(const GemmDesc& d) {
   auto pieces = [](const void* p, int64_t ld, int64_t ss, int64_t s0, int64_t s1) {
     return aligned_to(p, 16) && ld > 0 && ld % 8 == 0 && ss % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
   };
-  auto fits = [](bool kc, int64_t rows, int64_t K, int64_t ld) {
-    return ((kc ? (rows - 1) * ld + K : (K - 1) * ld + rows) * 2) < (int64_t)1 << 31;
-  };
+  auto fits = [](bool kc, int64_t rows, int64_t K, int64_t ld) { return slice_bytes(kc, rows, K, ld, 2) < (int64_t)1 << 31; };
   return pieces(d.A, d.a_ld, d.a_ss, d.a_g0, d.a_g1) && pieces(d.Bm, d.b_ld, d.b_ss, d.b_g0, d.b_g1) &&
          fits(d.a_kc, d.M, d.K, d.a_ld) && fits(d.b_kc, d.N, d.K, d.b_ld);
 }
+static bool loads_to_lds(const GemmDesc& d) { return gemm_dma_tile(d) >= 0 && lds_operands(d); }
 
 // With the operands known: unsplit where that kernel takes them, else the split that the workspace was sized for.  (On
 // operands it does not take, few tiles under a long reduction need the split: weight and bias gradient on 8-byte aligned
@@ -122,16 +133,8 @@ static int reduce_partials(const GemmDesc& d, int64_t G, int splits, hipStream_t
   return launch_status();
 }
 
-int gemm_launch(const GemmDesc& d, hipStream_t st) {
-  if (d.M <= 0 || d.N <= 0 || d.K <= 0 || d.S <= 0 || d.G0 <= 0 || d.G1 <= 0) return HFTA_EINVAL;
-  const int64_t G = (int64_t)d.G0 * d.G1;
-  const int splits = d.splits < 1 ? 1 : d.splits;
-  if (G * splits > 65535) return HFTA_EUNSUPPORTED;
-  if (splits > 1 && (!d.partial || !d.out_f32 || d.bias || d.act != HFTA_ACT_NONE)) return HFTA_EINVAL;
-  if (d.dtype == HFTA_BF16 && d.out_f32 &&
-      ((d.bias && d.bias_mode == 2) || d.act == HFTA_ACT_TANH || d.act == HFTA_ACT_GELU))
-    return HFTA_EUNSUPPORTED;
-
+// what follows from the descriptor without a look at alignment
+static GemmArgs plain_args(const GemmDesc& d, int splits) {
   GemmArgs a;
   a.A = d.A; a.Bm = d.Bm; a.C = d.C; a.bias = d.bias; a.partial = d.partial;
   a.a_ld = d.a_ld; a.a_ss = d.a_ss; a.a_g0 = d.a_g0; a.a_g1 = d.a_g1;
@@ -150,13 +153,40 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   a.a_extent = a.b_extent = 0;
   a.c_seg = d.c_seg; a.c_seg_stride = d.c_seg_stride;
   a.stat_part = d.stat_part;
-  if (d.stat_done) *d.stat_done = false;
   a.bsum = nullptr;                    // set by the launchers of kernels that take it
-  if (d.bsum_done) *d.bsum_done = false;
   a.pool_part = nullptr;
   a.pool_gamma = nullptr;
-  if (d.pool_cols) *d.pool_cols = 0;
   a.hit_key = d.hit_key; a.hit_val = d.hit_val; a.hit_off = d.hit_off; a.hit_w = d.hit_w; a.hit_co = d.hit_co;
+  return a;
+}
+
+// Data gradient dx and weight gradient dw of one Linear in one launch, bits as in two.  HFTA_EUNSUPPORTED: make the two launches.
+int gemm_pair_launch(const GemmDesc& dw, const GemmDesc& dx, hipStream_t st) {
+  if (dw.splits > 1 || !gemm_dma_pair_takes(dw, dx) || !lds_operands(dw) || !lds_operands(dx)) return HFTA_EUNSUPPORTED;
+  auto args = [](const GemmDesc& d) {
+    GemmArgs a = plain_args(d, 1);
+    a.a_extent = (uint32_t)slice_bytes(d.a_kc, d.M, d.K, d.a_ld, 2);
+    a.b_extent = (uint32_t)slice_bytes(d.b_kc, d.N, d.K, d.b_ld, 2);
+    a.c_vec = store_bytes(d.out_f32 ? 4 : 2, d.C, d.c_ld, d.c_g0, d.c_g1);
+    return a;
+  };
+  return gemm_dma_pair_launch(dw, args(dw), dx, args(dx), st);
+}
+
+int gemm_launch(const GemmDesc& d, hipStream_t st) {
+  if (d.M <= 0 || d.N <= 0 || d.K <= 0 || d.S <= 0 || d.G0 <= 0 || d.G1 <= 0) return HFTA_EINVAL;
+  const int64_t G = (int64_t)d.G0 * d.G1;
+  const int splits = d.splits < 1 ? 1 : d.splits;
+  if (G * splits > 65535) return HFTA_EUNSUPPORTED;
+  if (splits > 1 && (!d.partial || !d.out_f32 || d.bias || d.act != HFTA_ACT_NONE)) return HFTA_EINVAL;
+  if (d.dtype == HFTA_BF16 && d.out_f32 &&
+      ((d.bias && d.bias_mode == 2) || d.act == HFTA_ACT_TANH || d.act == HFTA_ACT_GELU))
+    return HFTA_EUNSUPPORTED;
+
+  GemmArgs a = plain_args(d, splits);
+  if (d.stat_done) *d.stat_done = false;
+  if (d.bsum_done) *d.bsum_done = false;
+  if (d.pool_cols) *d.pool_cols = 0;
 
   // vector-load eligibility: every address the fast path forms must be aligned
   const int es = (int)dtype_size(d.dtype);
@@ -173,24 +203,16 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
   a.b_vec = ok(d.Bm, d.b_ld, d.b_ss, d.b_g0, d.b_g1, d.b_kc);
   // widest store (bytes) every row start of C / of the partial buffer is aligned to
   const int oes = (d.out_f32 || splits > 1) ? 4 : es;
-  auto store_bytes = [&](const void* p, int64_t ld, int64_t s0, int64_t s1) {
-    for (int w = 16; w >= 8; w >>= 1) {
-      const int q = w / oes;
-      if (aligned_to(p, w) && ld % q == 0 && s0 % q == 0 && s1 % q == 0) return w;
-    }
-    return 0;
-  };
-  a.c_vec = store_bytes(d.C, d.c_ld, d.c_g0, d.c_g1);
+  a.c_vec = store_bytes(oes, d.C, d.c_ld, d.c_g0, d.c_g1);
   if (d.c_seg > 0) {                 // a store piece must not straddle two column segments
     if (splits > 1) return HFTA_EUNSUPPORTED;
     while (a.c_vec >= 8 && (d.c_seg % (a.c_vec / oes) != 0 || d.c_seg_stride % (a.c_vec / oes) != 0)) a.c_vec >>= 1;
     if (a.c_vec < 8) a.c_vec = 0;
   }
-  a.p_vec = splits > 1 ? store_bytes(d.partial, d.N, (int64_t)d.M * d.N, 0) : 0;
+  a.p_vec = splits > 1 ? store_bytes(oes, d.partial, d.N, (int64_t)d.M * d.N, 0) : 0;
 
   // operand slice extents for the buffer-load kernels
-  const int64_t a_ext = ((d.a_kc ? (int64_t)(d.M - 1) * d.a_ld + d.K : (int64_t)(d.K - 1) * d.a_ld + d.M)) * es;
-  const int64_t b_ext = ((d.b_kc ? (int64_t)(d.N - 1) * d.b_ld + d.K : (int64_t)(d.K - 1) * d.b_ld + d.N)) * es;
+  const int64_t a_ext = slice_bytes(d.a_kc, d.M, d.K, d.a_ld, es), b_ext = slice_bytes(d.b_kc, d.N, d.K, d.b_ld, es);
   const bool buffers_ok = d.dtype == HFTA_BF16 && a_ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31 &&
                           d.a_ld > 0 && d.b_ld > 0 && (d.a_kc || !d.b_kc);
   auto whole_pieces = [&](int vec, bool kc, int extent_mn, bool v16) {

@@ -188,34 +188,42 @@ __device__ __forceinline__ void store_colsums(const float (&s)[C][8], float* lds
   }
 }
 
-// WM x WN waves, MI x NI matrix-instruction blocks each
-template <int WM, int WN, int MI, int NI, int BK, bool A_KC, bool B_KC, typename OutT, int ST, int OCC>
-__global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p) {
-  constexpr int BM = WM * MI * 32, BN = WN * NI * 32, WAVES = WM * WN;
+// What one instantiation keeps in LDS: WM x WN waves, MI x NI matrix-instruction blocks each
+template <int WM, int WN, int MI, int NI, int BK, bool A_KC, bool B_KC, typename OutT, int ST> struct DmaTile {
+  static constexpr int BM = WM * MI * 32, BN = WN * NI * 32, WAVES = WM * WN;
   typedef DmaOp<BM, BK, A_KC, WAVES> OpA;
   typedef DmaOp<BN, BK, B_KC, WAVES> OpB;
-  constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+  static constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+  // rows staged per epilogue pass: as many whole wave rows as fit
+  static constexpr int ROWB = dma_pitch<BN, OutT>();
+  static constexpr int STAGES = ST * STAGE;
+  static constexpr int WPP = BM * ROWB <= STAGES + 4096 ? WM : WM / 2;   // wave rows per pass
+  static constexpr int RP = WPP * MI * 32;
+  static_assert(WPP >= 1 && RP * ROWB <= STAGES + 4096, "the staged output must fit");
+  static constexpr int SMEM = RP * ROWB > STAGES ? RP * ROWB : STAGES;
+};
+
+// workgroup `lin` of tiles_x x batches: a contiguous range of (batch, tile) per XCD, as in gemm_kernel
+__device__ __forceinline__ void dma_renumber(int lin, int tiles_x, int total, int& bx, int& bz) {
+  const int per = total >> 3;
+  const int l2 = lin < (per << 3) ? (lin & 7) * per + (lin >> 3) : lin;
+  bz = l2 / tiles_x;
+  bx = l2 - bz * tiles_x;
+}
+
+// Tile bx of batch bz
+template <int WM, int WN, int MI, int NI, int BK, bool A_KC, bool B_KC, typename OutT, int ST>
+__device__ __forceinline__ void gemm_dma_body(const GemmArgs& p, int bx, int bz, unsigned char* smem) {
+  typedef DmaTile<WM, WN, MI, NI, BK, A_KC, B_KC, OutT, ST> T;
+  constexpr int BM = T::BM, BN = T::BN, WAVES = T::WAVES;
+  typedef typename T::OpA OpA;
+  typedef typename T::OpB OpB;
+  constexpr int STAGE = T::STAGE, SMEM = T::STAGES;
   constexpr int PER = OpA::NC + OpB::NC, KS = BK / 16;
   constexpr int FLIGHT = (ST - 2) * PER;                  // loads of the tiles that stay in flight at a barrier
-  // rows staged per epilogue pass: as many whole wave rows as fit
-  constexpr int ROWB = dma_pitch<BN, OutT>();
-  constexpr int SMEM = ST * STAGE;
-  constexpr int WPP = BM * ROWB <= SMEM + 4096 ? WM : WM / 2;   // wave rows per pass
-  constexpr int RP = WPP * MI * 32;
-  static_assert(WPP >= 1 && RP * ROWB <= SMEM + 4096, "the staged output must fit");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[RP * ROWB > SMEM ? RP * ROWB : SMEM];
+  constexpr int WPP = T::WPP, RP = T::RP;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  int bx = blockIdx.x, bz = blockIdx.z;
-  {  // XCD-aware renumbering, as in gemm_kernel
-    const int total = gridDim.x * gridDim.z, per = total >> 3;
-    const int lin = blockIdx.x + gridDim.x * blockIdx.z;
-    if (lin < (per << 3)) {
-      const int l2 = (lin & 7) * per + (lin >> 3);
-      bz = l2 / gridDim.x;
-      bx = l2 - bz * gridDim.x;
-    }
-  }
   const int m0 = (bx % p.tiles_m) * BM, n0 = (bx / p.tiles_m) * BN;
   const int g0 = bz / p.G1, g1 = bz % p.G1;
   const bf16_raw* Ab = reinterpret_cast<const bf16_raw*>(p.A) + g0 * p.a_g0 + g1 * p.a_g1;
@@ -348,7 +356,36 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p)
   }
 }
 
+template <int WM, int WN, int MI, int NI, int BK, bool A_KC, bool B_KC, typename OutT, int ST, int OCC>
+__global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_dma_kernel(GemmArgs p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DmaTile<WM, WN, MI, NI, BK, A_KC, B_KC, OutT, ST>::SMEM];
+  int bx, bz;
+  dma_renumber(blockIdx.x + gridDim.x * blockIdx.z, gridDim.x, gridDim.x * gridDim.z, bx, bz);
+  gemm_dma_body<WM, WN, MI, NI, BK, A_KC, B_KC, OutT, ST>(p, bx, bz, smem);
+}
+
+// Both gradients of a Linear in one launch: workgroups below `first` (a multiple of 8, those past the tiles have nothing to do) take
+// the weight gradient X^T dY, the longer reduction, the others the data gradient dY W^T.  MW, MX: matrix-instruction blocks of 32 rows
+// per wavefront.
+struct GemmPair { GemmArgs dw, dx; int first, dw_x, dw_total, dx_x, dx_total; };
+template <int MW, int MX>
+__global__ __launch_bounds__(256, 2) void gemm_dma_pair_kernel(GemmPair p) {
+  constexpr int SW = DmaTile<2, 2, MW, 1, 64, false, false, float, 3>::SMEM, SX = DmaTile<2, 2, MX, 1, 64, true, true, bf16_raw, 3>::SMEM;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SW > SX ? SW : SX];
+  int bx, bz;
+  if ((int)blockIdx.x < p.first) {
+    if ((int)blockIdx.x >= p.dw_total) return;
+    dma_renumber(blockIdx.x, p.dw_x, p.dw_total, bx, bz);
+    gemm_dma_body<2, 2, MW, 1, 64, false, false, float, 3>(p.dw, bx, bz, smem);
+  } else {
+    dma_renumber((int)blockIdx.x - p.first, p.dx_x, p.dx_total, bx, bz);
+    gemm_dma_body<2, 2, MX, 1, 64, true, true, bf16_raw, 3>(p.dx, bx, bz, smem);
+  }
+}
+
 int gemm_dma_tile(const GemmDesc& d);      // rows x columns of the tile the kernel would take, as an index; -1: not for it
 int gemm_dma_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st);
+bool gemm_dma_pair_takes(const GemmDesc& dw, const GemmDesc& dx);      // from the shapes alone
+int gemm_dma_pair_launch(const GemmDesc& dw, const GemmArgs& aw, const GemmDesc& dx, const GemmArgs& ax, hipStream_t st);
 
 }  // namespace hfta

@@ -64,4 +64,52 @@ int gemm_dma_launch(const GemmDesc& d, const GemmArgs& a, hipStream_t st) {
   return rc;
 }
 
+template <int MW, int MX>
+static void launch_pair(GemmPair p, hipStream_t st) {
+  auto tiles = [](GemmArgs& a, int bm, int batches, int& x, int& total) {
+    a.tiles_m = (a.M + bm - 1) / bm;
+    a.tiles_n = (a.N + 63) / 64;
+    a.tiles_per_seg = (a.K + 63) / 64;
+    a.total_tiles = a.tiles_per_seg;
+    x = a.tiles_m * a.tiles_n;
+    total = x * batches;
+  };
+  tiles(p.dw, MW * 64, p.dw_total, p.dw_x, p.dw_total);
+  tiles(p.dx, MX * 64, p.dx_total, p.dx_x, p.dx_total);
+  p.first = (p.dw_total + 7) / 8 * 8;
+  hipLaunchKernelGGL((gemm_dma_pair_kernel<MW, MX>), dim3((unsigned)(p.first + p.dx_total)), dim3(256), 0, st, p);
+}
+
+static int64_t tiles64(const GemmDesc& d, int bm) { return (int64_t)((d.M + bm - 1) / bm) * ((d.N + 63) / 64) * d.G0; }
+
+// Two launches of a few hundred workgroups each are a wait of 4 us, two prologues and two tails that leave compute units idle; in one
+// launch the data gradient's tiles fill the places that the weight gradient's long chains leave, two or three workgroups to a compute
+// unit.  us, two launches -> one (256 -> 1024 etc. are Fx -> Fy):
+//   8 x 2048 rows, 256 -> 768 34.0 -> 24.5, 256 -> 1024 36.9 -> 28.4, 256 -> 256 25.8 -> 18.2   4 x 3000, 256 -> 1024 37.0 -> 26.7,
+//   1024 -> 256 36.2 -> 31.6   5 x 693, 384 -> 1536 25.4 -> 21.2   1 x 64, 256 -> 768 15.3 -> 6.7   8 x 3000, 256 -> 1000 56.9 -> 51.0
+// Up to 3 1/4 rounds of the 512 places and 24.8 GFLOP; more work is faster on larger tiles: 3 x 2048, 512 -> 2048 (25.8 GFLOP)
+// 43.8 -> 46.0, 4 x 2048, 256 -> 3000 (25.2) 51.6 -> 52.7, 16 x 693, 1024 -> 256 (1920 tiles) 26.3 -> 28.3, 8 x 2048, 1024 -> 256
+// (2304 tiles) 34.5 -> 35.2, 16 x 4096, 512 -> 2048 292 -> 496.  Reductions past 128 k-tiles of the weight gradient stay split.
+bool gemm_dma_pair_takes(const GemmDesc& dw, const GemmDesc& dx) {
+  return dw.dtype == HFTA_BF16 && dw.M % 8 == 0 && dw.N % 8 == 0 && dw.K >= 64 && dw.K <= 128 * 64 &&
+         tiles64(dw, 128) + tiles64(dx, 128) <= 1664 && 4.0 * dw.G0 * dw.K * dw.M * dw.N <= 24.8e9;
+}
+
+// The weight gradient's tile as for a launch of its own; data gradients of few tiles take the smaller one too (5 x 693, 384 -> 1536
+// 23.2 -> 21.2; with 512 tiles, 8 x 1024, 256 -> 1024, 17.0 -> 20.8).
+int gemm_dma_pair_launch(const GemmDesc& dw, const GemmArgs& aw, const GemmDesc& dx, const GemmArgs& ax, hipStream_t st) {
+  GemmPair p;
+  p.dw = aw; p.dx = ax;
+  p.dw.bsum = dw.bsum;
+  p.dw_total = dw.G0; p.dx_total = dx.G0;
+  const bool w64 = tiles64(dw, 64) <= 256, x64 = tiles64(dx, 64) <= 384;
+  if (w64 && x64) launch_pair<1, 1>(p, st);
+  else if (w64) launch_pair<1, 2>(p, st);
+  else if (x64) launch_pair<2, 1>(p, st);
+  else launch_pair<2, 2>(p, st);
+  const int rc = launch_status();
+  if (rc == HFTA_OK && dw.bsum && dw.bsum_done) *dw.bsum_done = true;
+  return rc;
+}
+
 }  // namespace hfta

@@ -1,7 +1,7 @@
 // Fused Linear and fused k=1 Conv1d: argument checking and mapping of the
 // forward / data-gradient / weight-gradient forms onto the batched GEMM core,
 // plus the bias-gradient reductions.
-#include "gemm.h"
+#include "gemm_dma.h"
 #include "in_norm.h"
 #include <mutex>
 
@@ -243,6 +243,16 @@ GemmDesc linear_dw_desc(int B, int M, int Fx, int Fy, int dtype, const void* X, 
   return d;
 }
 
+GemmDesc linear_dx_desc(int B, int M, int Fx, int Fy, int dtype, const void* dY, const void* W, void* dX) {
+  GemmDesc d = base_desc(dtype);
+  d.A = dY; d.Bm = W; d.C = dX;
+  d.M = M; d.N = Fx; d.K = Fy; d.G0 = B;
+  d.a_kc = true; d.a_ld = Fy; d.a_g0 = (int64_t)M * Fy;
+  d.b_kc = true; d.b_ld = Fy; d.b_g0 = (int64_t)Fx * Fy;      // B[k=fy][n=fx] = W[fx][fy]
+  d.c_ld = Fx; d.c_g0 = (int64_t)M * Fx;
+  return d;
+}
+
 GemmDesc conv_dw_desc(int B, int Nb, int Ci, int Co, int L, int dtype, const void* X, const int64_t* xs,
                       const void* dY, const int64_t* dys, float* dW) {
   GemmDesc d = base_desc(dtype);
@@ -380,6 +390,12 @@ size_t hfta_linear_bwd_workspace_bytes(int B, int M, int Fx, int Fy, int dtype) 
   return gemm_partial_bytes(d, gemm_pick_splits(d));
 }
 
+int hfta_linear_bwd_pair_supported(int B, int M, int Fx, int Fy, int dtype) {
+  if (B <= 0 || M <= 0 || Fx <= 0 || Fy <= 0 || dtype != HFTA_BF16) return 0;
+  return gemm_dma_pair_takes(linear_dw_desc(B, M, Fx, Fy, dtype, nullptr, nullptr, nullptr),
+                             linear_dx_desc(B, M, Fx, Fy, dtype, nullptr, nullptr, nullptr)) ? 1 : 0;
+}
+
 int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* dY,
                     void* dX, float* dW, float* dbias, void* workspace, size_t ws_bytes, void* stream) {
   if (B <= 0 || M <= 0 || Fx <= 0 || Fy <= 0 || !dY || !valid_dtype(dtype)) return HFTA_EINVAL;
@@ -393,25 +409,25 @@ int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype, const void* X, cons
     if (need > 0 && (!workspace || ws_bytes < need)) return HFTA_EWORKSPACE;
     dw.partial = reinterpret_cast<float*>(workspace);
   }
-  if (dX) {
-    GemmDesc d = base_desc(dtype);
-    d.A = dY; d.Bm = W; d.C = dX;
-    d.M = M; d.N = Fx; d.K = Fy; d.G0 = B;
-    d.a_kc = true; d.a_ld = Fy; d.a_g0 = (int64_t)M * Fy;
-    d.b_kc = true; d.b_ld = Fy; d.b_g0 = (int64_t)Fx * Fy;    // B[k=fy][n=fx] = W[fx][fy]
-    d.c_ld = Fx; d.c_g0 = (int64_t)M * Fx;
-    int rc = gemm_launch(d, st);
-    if (rc != HFTA_OK) return rc;
-  }
   bool db_done = false;
   if (dW) {
     // The weight gradient's kernel adds up dY's columns from the tiles it holds, where it is one that can, in the order of
     // the pass below (the same bits either way).  Both gradients, 8 x 2048 x 256 -> 8192: 131 us with the pass, 115 without.
     dw.bsum = dbias;
     dw.bsum_done = &db_done;
-    int rc = gemm_launch(dw, st);
-    if (rc != HFTA_OK) return rc;
   }
+  int rc = HFTA_EUNSUPPORTED;
+  if (dX) {
+    const GemmDesc d = linear_dx_desc(B, M, Fx, Fy, dtype, dY, W, dX);
+    if (dW) rc = gemm_pair_launch(dw, d, st);
+    if (rc == HFTA_EUNSUPPORTED) {
+      rc = gemm_launch(d, st);
+      if (rc == HFTA_OK && dW) rc = gemm_launch(dw, st);
+    }
+  } else if (dW) {
+    rc = gemm_launch(dw, st);
+  }
+  if ((dX || dW) && rc != HFTA_OK) return rc;
   if (dbias && !db_done) {
     dim3 grid((unsigned)((Fy + 63) / 64), (unsigned)B);
     const int epv = 16 / (int)dtype_size(dtype);
