@@ -36,7 +36,7 @@ class Tracer:
     sequence) are bracketed by HIP events on the stream they launch on (torch's current stream)."""
 
     SINGLE_KERNEL = ("conv1x1_fwd", "conv1x1_bwd", "bn_fwd", "bn_bwd", "maxpool_points", "maxpool_points_bwd",
-                     "adam_step_multi", "linear_fwd", "linear_fwd_ws", "linear_bwd", "linear_bn_fwd", "linear_xent", "linear_bwd_bn", "bn_fwd_maxpool", "bn_bwd_maxpool",
+                     "adam_step_multi", "linear_fwd", "linear_fwd_ws", "linear_bwd", "linear_bn_fwd", "linear_xent", "linear_bwd_bn", "linear_bwd_act", "bn_fwd_maxpool", "bn_bwd_maxpool",
                      "act_fwd", "act_bwd", "act_bwd_colsum", "add", "layernorm_fwd", "add_layernorm_fwd", "layernorm_bwd", "layernorm_bwd_sums",
                      "conv2d_grouped_fwd", "conv2d_grouped_bwd", "bias_act_nchw", "conv1x1_bn_maxpool_fwd",
                      "conv1x1_bn_pool_fwd", "conv1x1_fwd_sample_bias", "maxpool_points_bwd_add",
@@ -134,8 +134,8 @@ def kernel_label(name, a):
         return small_gemm(dt) + "(fwd)"
     if name == "linear_fwd_ws" and a[1] <= 64:
         return ("gemm_pf_kernel" if a[4] == 1 else "gemm_f32_kernel") + "(fwd, split)+splitk_bias_act_kernel"
-    if name in ("linear_bn_fwd", "linear_xent", "linear_bwd_bn"):
-        return "linear_few_%s_kernel" % ("bwd" if name == "linear_bwd_bn" else "fwd")
+    if name in ("linear_bn_fwd", "linear_xent", "linear_bwd_bn", "linear_bwd_act"):
+        return "linear_few_%s_kernel" % ("bwd" if name.startswith("linear_bwd") else "fwd")
     if name in ("linear_fwd", "linear_fwd_ws"):
         if a[4] == 1 and big_gemm(a[0], a[1], a[3], a[2]):
             return big_name(a[0], a[1], a[3], a[2:4]) + "(fwd)"
@@ -269,9 +269,9 @@ def algorithmic_flops(name, a):
     if name in ("conv1x1_bn_maxpool_f32_fwd", "conv1x1_bn_maxpool_f32_bwd"):      # the Ci -> Co product; the two Ci x Ci ones
         B, Nb, Ci, Co, L = a[:5]
         return 2.0 * B * Nb * Ci * (Co if name.endswith("fwd") else 2 * Ci) * L
-    if name in ("linear_fwd", "linear_fwd_ws", "linear_bwd", "linear_bn_fwd", "linear_xent", "linear_bwd_bn"):
+    if name in ("linear_fwd", "linear_fwd_ws", "linear_bwd", "linear_bn_fwd", "linear_xent", "linear_bwd_bn", "linear_bwd_act"):
         B, M, Fx, Fy = a[:4]
-        if name == "linear_bwd_bn":
+        if name in ("linear_bwd_bn", "linear_bwd_act"):
             return 4.0 * B * M * Fx * Fy
         if name == "linear_bwd" and a[8] is None and a[9] is None:
             return 0.0
@@ -350,7 +350,7 @@ def algorithmic_bytes(name, a):
         B, M, Fx, Fy, dt = a[:5]
         outs = 1 if name.startswith("linear_fwd") else 2 if name == "linear_xent" or a[20] is None else 3
         return B * (M * Fx + Fx * Fy + Fy + outs * M * Fy) * _es(dt)
-    if name == "linear_bwd_bn":                        # x, W, dy in, the input's pre-activation where a BatchNorm follows; dx, dW out
+    if name in ("linear_bwd_bn", "linear_bwd_act"):    # x, W, dy in, the input's pre-activation where a BatchNorm follows; dx, dW out
         B, M, Fx, Fy, dt = a[:5]
         return B * ((3 if len(a) > 11 and a[11] is not None else 2) * M * Fx + Fx * Fy + M * Fy) * _es(dt) + B * Fx * Fy * 4
     if name == "conv1x1_bwd":

@@ -127,14 +127,17 @@ int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype,
                     void* workspace, size_t ws_bytes, void* stream);
 
 /* The same Linear on few rows together with the operators that stand beside it in a fully connected head, each call ONE launch
- * that leaves the bits of the single operators (bf16, at most 32 rows, Fx and Fy multiples of 8, X, W and dY 16-byte aligned;
- * EUNSUPPORTED with nothing launched otherwise: make the single calls).  hfta_linear_few_supported: 1 where the two forward calls
- * take the shape (the backward call takes any such shape with bf16, M <= 32, Fx % 8 == Fy % 8 == 0).
+ * that leaves the bits of the single operators (at most 32 rows, Fx and Fy multiples of 8 in bf16 and of 4 in fp32, X, W and dY
+ * 16-byte aligned; EUNSUPPORTED with nothing launched otherwise: make the single calls).  hfta_linear_few_supported: 1 where the two
+ * forward calls take the shape (the backward calls take any such shape).
  *   hfta_linear_bn_fwd  = hfta_linear_fwd_ws (Z = X W + bias), hfta_bn_fwd over the rows (Y), and with a mask hfta_dropout (Yd).
  *   hfta_linear_xent    = hfta_linear_fwd_ws (logits), hfta_softmax_xent; K <= 32 classes.
  *   hfta_linear_bwd_bn  = hfta_linear_bwd (dW, dbias or NULL); Z == NULL: dX = dY W^T.  Otherwise Z is what the BatchNorm below
  *     normalised, and that gradient goes on through hfta_dropout (mask or NULL) and hfta_bn_bwd: dX, [B][M][Fx], is the gradient of
- *     Z, with dgamma, dbeta and, if not NULL, dx_sum.  dX may not alias X, dY or Z. */
+ *     Z, with dgamma, dbeta and, if not NULL, dx_sum.  dX may not alias X, dY or Z.
+ *   hfta_linear_bwd_act = the same with hfta_act_bwd from the output H [B][M][Fx] of the activation below instead of hfta_bn_bwd.
+ * (fp32: a data gradient over more than 64 columns that meets a value without a split into three bf16 parts takes the fp32
+ * instruction for 32 columns here, for a tile of the product there.) */
 int hfta_linear_few_supported(int B, int M, int Fx, int Fy, int dtype);
 int hfta_linear_bn_fwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* bias,
                        const float* gamma, const float* beta, float eps, float momentum, float* running_mean,
@@ -146,6 +149,9 @@ int hfta_linear_bwd_bn(int B, int M, int Fx, int Fy, int dtype, const void* X, c
                        float* dW, float* dbias, const void* Z, const float* gamma, const float* beta, const float* save_mean,
                        const float* save_invstd, int act, float act_slope, const uint8_t* mask, float p, float* dgamma,
                        float* dbeta, float* dx_sum, void* stream);
+int hfta_linear_bwd_act(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* dY, void* dX,
+                        float* dW, float* dbias, const void* H, int act, float act_slope, const uint8_t* mask, float p,
+                        void* stream);
 
 /* ------------------------------------------------------------------------
  * Fused Conv1d with kernel length 1 (row "Conv1d" -> grouped Conv1d, G = B).

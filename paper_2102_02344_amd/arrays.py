@@ -50,13 +50,18 @@ def _few_rows(A, i, fc, prefix, B, Nb, dt):
     return hb.linear_few_supported(B, Nb, fc[i], fc[i + 1], dt) and _on_16_bytes(A.w(f"{prefix}fc{i}.w"))
 
 
-def _few_bwd(A, i, fc, prefix, hin, fz, d, out, own_db, below, mask, p):
-    """One launch for layer i's Linear backward; ``below``: its data gradient goes on through the dropout (``mask``) and the
-    BatchNorm of layer i - 1 to the gradient of ``fz[i - 1]``."""
+def _few_bwd(A, i, fc, prefix, hin, fz, fh, bn, d, out, own_db, mask, p):
+    """One launch for layer i's Linear backward; for i > 0 its data gradient goes on through the dropout (``mask``) and the
+    BatchNorm (``bn``: to the gradient of ``fz[i - 1]``) or the ReLU of layer i - 1."""
     k, kb = f"{prefix}fc{i}", f"{prefix}fc{i - 1}"
-    bn = (fz[i - 1], A.master(kb + ".bn.g"), A.master(kb + ".bn.b"), A.saved[kb + ".bn.mean"], A.saved[kb + ".bn.invstd"],
-          hb.ACT_RELU, 0.0, mask, p, A.g(kb + ".bn.g"), A.g(kb + ".bn.b"), A.g(kb + ".b")) if below else ()
-    hb.linear_bwd_bn(A.B, A.Nb, fc[i], fc[i + 1], A.dt, hin, A.w(k + ".w"), d, out, A.g(k + ".w"), own_db, *bn)
+    args = (A.B, A.Nb, fc[i], fc[i + 1], A.dt, hin, A.w(k + ".w"), d, out, A.g(k + ".w"), own_db)
+    if i == 0:
+        hb.linear_bwd_bn(*args)
+    elif bn:
+        hb.linear_bwd_bn(*args, fz[i - 1], A.master(kb + ".bn.g"), A.master(kb + ".bn.b"), A.saved[kb + ".bn.mean"],
+                         A.saved[kb + ".bn.invstd"], hb.ACT_RELU, 0.0, mask, p, A.g(kb + ".bn.g"), A.g(kb + ".bn.b"), A.g(kb + ".b"))
+    else:
+        hb.linear_bwd_act(*args, fh[i - 1], hb.ACT_RELU, 0.0, mask, p)
 
 
 def _bn_bwd_one_pass(B, Nb, ci, co, L, dt):
@@ -462,7 +467,7 @@ class FusedPointNetCls(ParamArena):
             fy = s.fc[i + 1]
             k = f"fc{i}"
             last = i == self.nfc - 1
-            if P is None and s.fc_bn and _few_rows(self, i, s.fc, "", B, Nb, dt):
+            if P is None and (last or s.fc_bn) and _few_rows(self, i, s.fc, "", B, Nb, dt):
                 if last and fy <= 32:
                     d = self._cut(self.fd[0], B * Nb * fy)
                     hb.linear_xent(B, Nb, fx, fy, dt, h, self.w(k + ".w"), self.w(k + ".b"), self.fz[i], self.labels, self.loss, d)
@@ -552,10 +557,10 @@ class FusedPointNetCls(ParamArena):
             # a bias that feeds a BatchNorm gets its gradient from that BatchNorm's backward (dx_sum)
             own_db = self.g(k + ".b") if (last or not s.fc_bn) else None
             through = False
-            if P is None and s.fc_bn and _few_rows(self, i, s.fc, "", B, Nb, dt):
+            if P is None and _few_rows(self, i, s.fc, "", B, Nb, dt):
                 through = i > 0
                 drop = through and last and s.dropout_p > 0
-                _few_bwd(self, i, s.fc, "", hin, self.fz, d, nd, own_db, through, self.drop_mask if drop else None,
+                _few_bwd(self, i, s.fc, "", hin, self.fz, self.fh, s.fc_bn, d, nd, own_db, self.drop_mask if drop else None,
                          s.dropout_p if drop else 0.0)
                 d, cur = nd, cur ^ 1
                 continue
@@ -1626,7 +1631,7 @@ class _PointChain(_Views):
         for i in range(self.nfc):
             fx, fy, k = self.fc[i], self.fc[i + 1], f"{self.px}fc{i}"
             last = i == self.nfc - 1
-            if self.fc_bn and _few_rows(A, i, self.fc, self.px, B, Nb, dt):
+            if (last or self.fc_bn) and _few_rows(A, i, self.fc, self.px, B, Nb, dt):
                 if last and xent is not None and fy <= 32:
                     hb.linear_xent(B, Nb, fx, fy, dt, h, A.w(k + ".w"), A.w(k + ".b"), self.fz[i], *xent)
                     return self.fz[i]
@@ -1686,10 +1691,10 @@ class _PointChain(_Views):
             nd = self._cut(self.fd[cur ^ 1], B * Nb * fx)
             own_db = A.g(k + ".b") if (last or not self.fc_bn) else None
             through = False
-            if self.fc_bn and _on_16_bytes(d) and _few_rows(A, i, self.fc, self.px, B, Nb, dt):
+            if _on_16_bytes(d) and _few_rows(A, i, self.fc, self.px, B, Nb, dt):
                 through = i > 0
                 drop = through and last and self.dropout_p > 0
-                _few_bwd(A, i, self.fc, self.px, hin, self.fz, d, nd, own_db, through, self.drop_mask if drop else None,
+                _few_bwd(A, i, self.fc, self.px, hin, self.fz, self.fh, self.fc_bn, d, nd, own_db, self.drop_mask if drop else None,
                          self.dropout_p if drop else 0.0)
                 d, cur = nd, cur ^ 1
                 continue

@@ -54,6 +54,7 @@ _SIGS = {
     "hfta_linear_few_supported": (_i, [_i] * 5),
     "hfta_linear_bn_fwd": (_i, [_i] * 5 + [_p] * 5 + [_f, _f] + [_p] * 6 + [_i, _f, _p, _f, _p, _p]),
     "hfta_linear_xent": (_i, [_i] * 5 + [_p] * 8),
+    "hfta_linear_bwd_act": (_i, [_i] * 5 + [_p] * 7 + [_i, _f, _p, _f, _p]),
     "hfta_linear_bwd_bn": (_i, [_i] * 5 + [_p] * 11 + [_i, _f, _p, _f] + [_p] * 4),
     "hfta_conv1x1_fwd": (_i, [_i, _i, _i, _i, _i, _i, _p, _s4, _p, _p, _p, _s4, _i, _f, _p]),
     "hfta_conv1x1_fwd_sample_bias": (_i, [_i, _i, _i, _i, _i, _i, _p, _s4, _p, _p, _s4, _p, _s4, _i, _f, _p]),
@@ -268,6 +269,11 @@ def linear_bwd_bn(B, M, Fx, Fy, dtype, X, W, dY, dX, dW, dbias, Z=None, gamma=No
     _check(_lib.hfta_linear_bwd_bn(B, M, Fx, Fy, dtype, _ptr(X), _ptr(W), _ptr(dY), _ptr(dX), _ptr(dW), _ptr(dbias), _ptr(Z),
                                    _ptr(gamma), _ptr(beta), _ptr(save_mean), _ptr(save_invstd), act, act_slope, _ptr(mask), p,
                                    _ptr(dgamma), _ptr(dbeta), _ptr(dx_sum), _stream(stream)), "hfta_linear_bwd_bn")
+
+
+def linear_bwd_act(B, M, Fx, Fy, dtype, X, W, dY, dX, dW, dbias, H, act=ACT_NONE, act_slope=0.0, mask=None, p=0.0, stream=None):
+    _check(_lib.hfta_linear_bwd_act(B, M, Fx, Fy, dtype, _ptr(X), _ptr(W), _ptr(dY), _ptr(dX), _ptr(dW), _ptr(dbias), _ptr(H),
+                                    act, act_slope, _ptr(mask), p, _stream(stream)), "hfta_linear_bwd_act")
 
 
 def conv1x1_fwd(B, Nb, Ci, Co, L, dtype, X, xs, W, bias, Y, ys, act=ACT_NONE, act_slope=0.0, stream=None):

@@ -25,6 +25,9 @@ int conv1x1_bn_bwd_stream(int B, int Nb, int Ci, int Co, int L, const void* X, c
                           const float* in_mean = nullptr, const float* in_invstd = nullptr, int in_act = 0, float in_slope = 0.f,
                           const float* sums = nullptr, float* in_sums = nullptr);
 bool conv1x1_bn_bwd_stream_sums(int Ci);
+// a few-row product with its split reduction in one launch (linear_few.hip)
+int linear_few_fwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* bias, void* Y, int act, float slope,
+                   hipStream_t st);
 int bn_stats_conv(int B, int Nb, int C, int L, int dtype, const void* X, const int64_t xs[4], const float* gamma,
                   const float* beta, float eps, float momentum, float* running_mean, float* running_var,
                   float* save_mean, float* save_invstd, hipStream_t st);
@@ -360,6 +363,8 @@ int hfta_linear_fwd_ws(int B, int M, int Fx, int Fy, int dtype, const void* X, c
   if (!fits_i32((int64_t)M * Fx) || !fits_i32((int64_t)M * Fy) || !fits_i32((int64_t)Fx * Fy)) return HFTA_EINVAL;
   const size_t need = (size_t)splits * B * M * Fy * sizeof(float);
   if (!workspace || ws_bytes < need) return HFTA_EWORKSPACE;
+  const int rc = linear_few_fwd(B, M, Fx, Fy, dtype, X, W, bias, Y, act, act_slope, as_stream(stream));
+  if (rc != HFTA_EUNSUPPORTED) return rc;
   return linear_fwd_split(B, M, Fx, Fy, dtype, X, W, bias, Y, act, act_slope, splits,
                           reinterpret_cast<float*>(workspace), as_stream(stream));
 }

@@ -7,10 +7,11 @@ import torch
 from paper_2102_02344_amd import binding as hb
 
 DEV = "cuda"
+TDT = {hb.F32: torch.float32, hb.BF16: torch.bfloat16}
 
 
-def _rand(g, *shape, scale=1.0):
-    return ((torch.rand(shape, generator=g) * 2 - 1) * scale).to(torch.bfloat16).to(DEV)
+def _rand(g, dt, *shape, scale=1.0):
+    return ((torch.rand(shape, generator=g) * 2 - 1) * scale).to(TDT[dt]).to(DEV)
 
 
 def _f32(g, *shape):
@@ -18,94 +19,125 @@ def _f32(g, *shape):
 
 
 def _same(a, b, what):
-    assert torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a.view(torch.int16),
-                       b.view(torch.int32) if b.dtype == torch.float32 else b.view(torch.int16)), what
+    kind = torch.int32 if a.dtype == torch.float32 else torch.int16
+    assert torch.equal(a.view(kind), b.view(kind)), what
 
 
-SHAPES = [(1, 1, 8, 8), (2, 2, 96, 16), (3, 13, 1024, 512), (16, 16, 1216, 40), (5, 17, 72, 264), (8, 32, 512, 256), (40, 31, 136, 72)]
+BF16_SHAPES = [(1, 1, 8, 8), (2, 2, 96, 16), (3, 13, 1024, 512), (16, 16, 1216, 40), (5, 17, 72, 264), (8, 32, 512, 256), (40, 31, 136, 72)]
+F32_SHAPES = [(1, 1, 4, 4), (2, 4, 1024, 256), (2, 4, 256, 16), (4, 32, 1024, 512), (4, 32, 512, 256), (3, 13, 68, 68), (5, 17, 100, 260), (9, 31, 36, 300),
+              (1, 16, 64, 1028)]
+SHAPES = [(hb.BF16,) + s for s in BF16_SHAPES] + [(hb.F32,) + s for s in F32_SHAPES]
+
+
+def _linear(B, M, Fx, Fy, dt, x, w, bias, y, act=hb.ACT_NONE):
+    """The split product and the sum of its parts as two launches (the entry point without a workspace keeps them)."""
+    hb.linear_fwd_static(B, M, Fx, Fy, dt, x, w, bias, y, act)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,M,Fx,Fy", SHAPES)
+@pytest.mark.parametrize("dt,B,M,Fx,Fy", SHAPES)
 @pytest.mark.parametrize("drop", [False, True])
-def test_linear_batchnorm(B, M, Fx, Fy, drop):
+def test_linear_batchnorm(dt, B, M, Fx, Fy, drop):
     g = torch.Generator().manual_seed(B * 1000 + M)
-    assert hb.linear_few_supported(B, M, Fx, Fy, hb.BF16)
-    x, w, bias = _rand(g, B, M, Fx), _rand(g, B, Fx, Fy, scale=Fx ** -0.5), _rand(g, B, Fy)
+    assert hb.linear_few_supported(B, M, Fx, Fy, dt)
+    x, w, bias = _rand(g, dt, B, M, Fx), _rand(g, dt, B, Fx, Fy, scale=Fx ** -0.5), _rand(g, dt, B, Fy)
     gamma, beta = _f32(g, B, Fy), _f32(g, B, Fy) - 1.0
     mask = (torch.rand((B, M, Fy), generator=g) < 0.7).to(torch.uint8).to(DEV) if drop else None
     ls = (M * Fy, Fy, 1, 1)
+    T = dict(dtype=TDT[dt], device=DEV)
 
     def outputs():
-        o = dict(z=torch.empty(B, M, Fy), y=torch.empty(B, M, Fy), yd=torch.empty(B, M, Fy))
-        o = {k: v.to(torch.bfloat16).to(DEV) for k, v in o.items()}
-        return o, dict(rm=torch.full((B, Fy), 0.25, device=DEV), rv=torch.full((B, Fy), 1.5, device=DEV),
-                       mean=torch.empty(B, Fy, device=DEV), invstd=torch.empty(B, Fy, device=DEV))
+        return dict(z=torch.empty(B, M, Fy, **T), y=torch.empty(B, M, Fy, **T), yd=torch.empty(B, M, Fy, **T)), \
+            dict(rm=torch.full((B, Fy), 0.25, device=DEV), rv=torch.full((B, Fy), 1.5, device=DEV),
+                 mean=torch.empty(B, Fy, device=DEV), invstd=torch.empty(B, Fy, device=DEV))
 
     (o1, s1), (o2, s2) = outputs(), outputs()
-    ws = torch.empty(max(4, hb.linear_fwd_workspace_bytes(B, M, Fx, Fy, hb.BF16)), dtype=torch.uint8, device=DEV)
-    hb.linear_fwd_ws(B, M, Fx, Fy, hb.BF16, x, w, bias, o1["z"], workspace=ws)
-    hb.bn_fwd(B, M, Fy, 1, hb.BF16, o1["z"], ls, gamma, beta, 1e-5, 0.1, s1["rm"], s1["rv"], s1["mean"], s1["invstd"], o1["y"], ls,
+    _linear(B, M, Fx, Fy, dt, x, w, bias, o1["z"])
+    hb.bn_fwd(B, M, Fy, 1, dt, o1["z"], ls, gamma, beta, 1e-5, 0.1, s1["rm"], s1["rv"], s1["mean"], s1["invstd"], o1["y"], ls,
               hb.ACT_RELU)
     if drop:
-        hb.dropout(B * M * Fy, hb.BF16, o1["y"], mask, 0.3, o1["yd"])
-    hb.linear_bn_fwd(B, M, Fx, Fy, hb.BF16, x, w, bias, gamma, beta, 1e-5, 0.1, s2["rm"], s2["rv"], s2["mean"], s2["invstd"], o2["z"],
+        hb.dropout(B * M * Fy, dt, o1["y"], mask, 0.3, o1["yd"])
+    hb.linear_bn_fwd(B, M, Fx, Fy, dt, x, w, bias, gamma, beta, 1e-5, 0.1, s2["rm"], s2["rv"], s2["mean"], s2["invstd"], o2["z"],
                      o2["y"], hb.ACT_RELU, 0.0, mask, 0.3 if drop else 0.0, o2["yd"] if drop else None)
     for k in ("z", "y") + (("yd",) if drop else ()):
         _same(o1[k], o2[k], k)
     for k in s1:
         _same(s1[k], s2[k], k)
+    ws = torch.empty(max(4, hb.linear_fwd_workspace_bytes(B, M, Fx, Fy, dt)), dtype=torch.uint8, device=DEV)
+    for act in (hb.ACT_NONE, hb.ACT_RELU):
+        _linear(B, M, Fx, Fy, dt, x, w, bias, o1["y"], act)
+        hb.linear_fwd_ws(B, M, Fx, Fy, dt, x, w, bias, o2["y"], act, workspace=ws)
+        _same(o1["y"], o2["y"], ("forward", act))
 
-    # backward: this Linear's gradients, and on through a BatchNorm below it (of Fx channels)
-    dy, zb = _rand(g, B, M, Fy, scale=0.1), _rand(g, B, M, Fx)
+    # backward: this Linear's gradients, and on through a BatchNorm or a ReLU below it (of Fx channels)
+    dy, zb = _rand(g, dt, B, M, Fy, scale=0.1), _rand(g, dt, B, M, Fx)
     gb, bb = _f32(g, B, Fx), _f32(g, B, Fx) - 1.0
     mean, invstd = zb.float().mean(1).contiguous(), _f32(g, B, Fx)
     maskb = (torch.rand((B, M, Fx), generator=g) < 0.7).to(torch.uint8).to(DEV) if drop else None
     lx = (M * Fx, Fx, 1, 1)
-    wb = torch.empty(max(4, hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, hb.BF16)), dtype=torch.uint8, device=DEV)
-    bf = dict(dtype=torch.bfloat16, device=DEV)
-    dx, dd, dz = (torch.empty(B, M, Fx, **bf) for _ in range(3))
+    wb = torch.empty(max(4, hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, dt)), dtype=torch.uint8, device=DEV)
+    dx, dd, dz, da = (torch.empty(B, M, Fx, **T) for _ in range(4))
     dw, db = torch.empty(B, Fx, Fy, device=DEV), torch.empty(B, Fy, device=DEV)
     sums = [torch.empty(B, Fx, device=DEV) for _ in range(3)]
-    hb.linear_bwd(B, M, Fx, Fy, hb.BF16, x, w, dy, dx, dw, db, wb)
+    hb.linear_bwd(B, M, Fx, Fy, dt, x, w, dy, dx, dw, db, wb)
     if drop:
-        hb.dropout(B * M * Fx, hb.BF16, dx, maskb, 0.3, dd)
-    hb.bn_bwd(B, M, Fx, 1, hb.BF16, zb, lx, dd if drop else dx, lx, gb, bb, mean, invstd, dz, lx, sums[0], sums[1], hb.ACT_RELU, 0.0, sums[2])
-    dx2, dz2 = torch.empty(B, M, Fx, **bf), torch.empty(B, M, Fx, **bf)
+        hb.dropout(B * M * Fx, dt, dx, maskb, 0.3, dd)
+    hb.bn_bwd(B, M, Fx, 1, dt, zb, lx, dd if drop else dx, lx, gb, bb, mean, invstd, dz, lx, sums[0], sums[1], hb.ACT_RELU, 0.0, sums[2])
+    hb.act_bwd(B * M * Fx, dt, zb, dd if drop else dx, da, hb.ACT_RELU, 0.0, 1)
+    dx2, dz2, da2 = (torch.empty(B, M, Fx, **T) for _ in range(3))
     dw2, db2 = torch.empty_like(dw), torch.empty_like(db)
-    dw3 = torch.empty_like(dw)
+    dw3, dw4 = torch.empty_like(dw), torch.empty_like(dw)
     sums2 = [torch.empty(B, Fx, device=DEV) for _ in range(3)]
-    hb.linear_bwd_bn(B, M, Fx, Fy, hb.BF16, x, w, dy, dx2, dw2, db2)
-    hb.linear_bwd_bn(B, M, Fx, Fy, hb.BF16, x, w, dy, dz2, dw3, None, zb, gb, bb, mean, invstd, hb.ACT_RELU, 0.0, maskb,
-                     0.3 if drop else 0.0, *sums2)
-    for a, b, what in ((dx, dx2, "dX"), (dw, dw2, "dW"), (dw, dw3, "dW"), (db, db2, "dbias"), (dz, dz2, "dZ")):
+    p = 0.3 if drop else 0.0
+    hb.linear_bwd_bn(B, M, Fx, Fy, dt, x, w, dy, dx2, dw2, db2)
+    hb.linear_bwd_bn(B, M, Fx, Fy, dt, x, w, dy, dz2, dw3, None, zb, gb, bb, mean, invstd, hb.ACT_RELU, 0.0, maskb, p, *sums2)
+    hb.linear_bwd_act(B, M, Fx, Fy, dt, x, w, dy, da2, dw4, None, zb, hb.ACT_RELU, 0.0, maskb, p)
+    for a, b, what in ((dx, dx2, "dX"), (dw, dw2, "dW"), (dw, dw3, "dW"), (dw, dw4, "dW"), (db, db2, "dbias"), (dz, dz2, "dZ"),
+                       (da, da2, "through the ReLU")):
         _same(a, b, what)
     for a, b, what in zip(sums, sums2, ("dgamma", "dbeta", "sum of dZ")):
         _same(a, b, what)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,M,Fx,K", [(1, 1, 8, 8), (3, 13, 256, 16), (8, 32, 256, 16), (2, 17, 1000, 32)])
-def test_linear_cross_entropy(B, M, Fx, K):
+@pytest.mark.parametrize("dt,B,M,Fx,K", [(hb.BF16, 1, 1, 8, 8), (hb.BF16, 3, 13, 256, 16), (hb.BF16, 8, 32, 256, 16), (hb.BF16, 2, 17, 1000, 32),
+                                         (hb.F32, 2, 4, 256, 16), (hb.F32, 1, 1, 4, 4), (hb.F32, 3, 31, 100, 28)])
+def test_linear_cross_entropy(dt, B, M, Fx, K):
     g = torch.Generator().manual_seed(M)
-    x, w, bias = _rand(g, B, M, Fx), _rand(g, B, Fx, K, scale=3 * Fx ** -0.5), _rand(g, B, K)
+    x, w, bias = _rand(g, dt, B, M, Fx), _rand(g, dt, B, Fx, K, scale=3 * Fx ** -0.5), _rand(g, dt, B, K)
     labels = torch.randint(K, (B, M), generator=g, dtype=torch.int32).to(DEV)
-    bf = dict(dtype=torch.bfloat16, device=DEV)
-    z1, z2, d1, d2 = (torch.empty(B, M, K, **bf) for _ in range(4))
+    z1, z2, d1, d2 = (torch.empty(B, M, K, dtype=TDT[dt], device=DEV) for _ in range(4))
     l1, l2 = torch.empty(B, device=DEV), torch.empty(B, device=DEV)
-    ws = torch.empty(max(4, hb.linear_fwd_workspace_bytes(B, M, Fx, K, hb.BF16)), dtype=torch.uint8, device=DEV)
-    hb.linear_fwd_ws(B, M, Fx, K, hb.BF16, x, w, bias, z1, workspace=ws)
-    hb.softmax_xent(B, M, K, hb.BF16, z1, labels, l1, d1)
-    hb.linear_xent(B, M, Fx, K, hb.BF16, x, w, bias, z2, labels, l2, d2)
+    _linear(B, M, Fx, K, dt, x, w, bias, z1)
+    hb.softmax_xent(B, M, K, dt, z1, labels, l1, d1)
+    hb.linear_xent(B, M, Fx, K, dt, x, w, bias, z2, labels, l2, d2)
     for a, b, what in ((z1, z2, "logits"), (l1, l2, "loss"), (d1, d2, "dlogits")):
         _same(a, b, what)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e-38, 1e-42, -3.39e38])
+def test_values_without_a_split(value):
+    """Such a value in dY: the data gradient of every column takes the fp32 instruction, as the product's tile does."""
+    B, M, Fx, Fy = 2, 20, 96, 128
+    g = torch.Generator().manual_seed(7)
+    x, w, dy = _rand(g, hb.F32, B, M, Fx), _rand(g, hb.F32, B, Fx, Fy), _rand(g, hb.F32, B, M, Fy)
+    dy[1, 3, 100] = value
+    dx, dx2 = torch.empty(B, M, Fx, device=DEV), torch.empty(B, M, Fx, device=DEV)
+    dw, dw2 = torch.empty(B, Fx, Fy, device=DEV), torch.empty(B, Fx, Fy, device=DEV)
+    wb = torch.empty(max(4, hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, hb.F32)), dtype=torch.uint8, device=DEV)
+    hb.linear_bwd(B, M, Fx, Fy, hb.F32, x, w, dy, dx, dw, None, wb)
+    hb.linear_bwd_bn(B, M, Fx, Fy, hb.F32, x, w, dy, dx2, dw2, None)
+    for a, b in ((dx, dx2), (dw, dw2)):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(), b.nan_to_num())
+
+
 def test_what_is_declined():
     ok = lambda *a: hb.linear_few_supported(*a)
-    assert ok(8, 32, 1024, 512, hb.BF16) and ok(1, 1, 8, 8, hb.BF16)
-    assert not ok(8, 33, 1024, 512, hb.BF16) and not ok(8, 32, 1024, 512, hb.F32)
+    assert ok(8, 32, 1024, 512, hb.BF16) and ok(1, 1, 8, 8, hb.BF16) and ok(4, 32, 1024, 512, hb.F32) and ok(1, 1, 4, 4, hb.F32)
+    assert not ok(8, 33, 1024, 512, hb.BF16) and not ok(8, 33, 1024, 512, hb.F32)
     assert not ok(8, 32, 1028, 512, hb.BF16) and not ok(8, 32, 256, 9, hb.BF16) and not ok(16, 32, 1224, 512, hb.BF16) and not ok(1, 32, 1216, 40, hb.BF16)
+    assert not ok(4, 32, 1022, 512, hb.F32) and not ok(4, 32, 256, 10, hb.F32) and not ok(16, 16, 1216, 40, hb.F32)   # 76 k a piece
     raw, one, off = hb.raw(), C.c_void_p(256), C.c_void_p(264)
 
     def bn(X=one, W=one, M=32, act=1, mask=None, Yd=None, p=0.0, rv=one):
@@ -122,3 +154,8 @@ def test_what_is_declined():
                                       dsum, None)
     assert bwd(dY=None) == hb.EINVAL and bwd(Z=one, mean=None) == hb.EINVAL and bwd(mask=one) == hb.EINVAL and bwd(dsum=one) == hb.EINVAL
     assert bwd(dY=off) == hb.EUNSUPPORTED and bwd(M=33) == hb.EUNSUPPORTED and bwd(Fy=9) == hb.EUNSUPPORTED
+
+    def bwd_act(H=one, dY=one, mask=None, p=0.0, act=1):
+        return raw.hfta_linear_bwd_act(8, 32, 256, 64, 0, one, one, dY, one, one, None, H, act, 0.0, mask, p, None)
+    assert bwd_act(H=None) == hb.EINVAL and bwd_act(dY=None) == hb.EINVAL and bwd_act(mask=one, p=1.0) == hb.EINVAL
+    assert bwd_act(dY=off) == hb.EUNSUPPORTED and bwd_act(act=hb.ACT_GELU) == hb.EUNSUPPORTED
