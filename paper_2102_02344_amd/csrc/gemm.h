@@ -94,6 +94,7 @@ struct GemmArgs {
   float slope;
   uint32_t a_extent, b_extent;   // bytes from an operand slice's first to one past its last element
   uint32_t c_extent;             // same for one output slice, or 0 when it does not fit 31 bits
+  int m_last, n_last;            // 256x256 tiles on the ring: the last tile along m / n starts no later than here
   int c_seg;
   int64_t c_seg_stride;
   float* stat_part;              // see GemmDesc

@@ -153,6 +153,7 @@ static GemmArgs plain_args(const GemmDesc& d, int splits) {
   a.a_extent = a.b_extent = 0;
   a.c_seg = d.c_seg; a.c_seg_stride = d.c_seg_stride;
   a.stat_part = d.stat_part;
+  a.m_last = a.n_last = 0x7fffffff;
   a.bsum = nullptr;                    // set by the launchers of kernels that take it
   a.pool_part = nullptr;
   a.pool_gamma = nullptr;
@@ -269,7 +270,18 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
       // B's column sums come from the kernel with one tile per workgroup alone (gemm_big_launch); with more tiles the ring and a pass
       // over B: 32 models, 4096 rows, 512 x 2048 weight and bias gradient 360 -> 327 us, 16 models, 2048 rows, 256 x 8192 247 -> 223.
       const bool sums = d.bsum && d.bsum_done && splits == 1 && one_round;
-      if ((v16 || !(d.a_kc || d.b_kc)) && n16 && !stats && !sums) rc = gemm_ring_launch(d, b, grid, st);
+      // An operand contiguous along m / n whose rows are whole 8-byte pieces (2500 points): a last tile that ends with the matrix instead
+      // of past it has 16-byte pieces only (columns that two tiles share are formed and stored twice, alike).  6 x 16 samples of 2500
+      // points, register-staged kernel -> ring: data gradients 2048 -> 512 544 -> 493 us, 256 -> 2880 703 -> 630, forward 2880 -> 256
+      // 462 -> 425, 512 -> 2048 680 and 681.  What is left is the stores: rows that start anywhere in a cache line leave partial lines
+      // (256 -> 2880 on 2560 points 461 us, of which non-temporal stores are 70, on 2504 points 616).
+      auto back = [&](bool kc, int vec, int extent, int& last) {
+        if (kc || extent % 8 == 0) return true;
+        last = extent - 256;
+        return vec >= 1 && extent % 4 == 0 && last >= 0;
+      };
+      const bool ring = (v16 || !(d.a_kc || d.b_kc)) && (n16 || (splits == 1 && back(d.a_kc, a.a_vec, d.M, b.m_last) && back(d.b_kc, a.b_vec, d.N, b.n_last)));
+      if (ring && !stats && !sums) rc = gemm_ring_launch(d, b, grid, st);
       if (rc == HFTA_EUNSUPPORTED) rc = gemm_big_launch(d, b, v16 || !(d.a_kc || d.b_kc), n16, grid, st);
       if (rc == HFTA_OK && splits > 1 && !d.keep_partials) return reduce_partials(d, G, splits, st);
       if (rc != HFTA_EUNSUPPORTED) return rc;

@@ -24,7 +24,8 @@
 // epilogue stages 32 rows of a wavefront's block at a time in its own 4 KB of the slot that B's last k-tile has left, so no
 // barrier is needed among them, while three operand tiles of the next output tile are on their way.
 //
-// Host side guarantees (gemm_ring_launch): bf16 operands in whole aligned 16-byte pieces, slices below 2 GiB, RING_MIN_T
+// Host side guarantees (gemm_ring_launch): bf16 operands in whole 16-byte pieces (k-contiguous ones aligned; of others the rows may be
+// 8-byte aligned and the last tile start where it ends with the matrix, GemmArgs::m_last / n_last), slices below 2 GiB, RING_MIN_T
 // k-tiles or more per output tile, output rows in whole aligned pieces of VB bytes.
 #pragma once
 #include "gemm_big.h"
@@ -101,8 +102,8 @@ __global__ __launch_bounds__(RING_THREADS, 2) void gemm_ring_kernel(GemmArgs p, 
     const int wid = RING_GM * p.tiles_n, grp = bx / wid, first = grp * RING_GM, rows = min(p.tiles_m - first, RING_GM), in = bx - grp * wid;
     BigCoord c;
     const int tn = in / rows;
-    c.n0 = tn * 256;
-    c.m0 = (first + in - tn * rows) * 256;
+    c.n0 = min(tn * 256, p.n_last);
+    c.m0 = min((first + in - tn * rows) * 256, p.m_last);
     c.g = bz / p.splits;
     c.split = bz - c.g * p.splits;
     c.g0 = c.g / p.G1;
