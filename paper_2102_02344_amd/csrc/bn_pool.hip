@@ -319,6 +319,15 @@ bool act_ok(int act) { return act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || ac
 namespace hfta {
 int conv1x1_fwd_pool_part(int B, int Nb, int Ci, int Co, int L, const void* X, const int64_t xs[4], const void* W, const void* bias,
                           void* Z, const int64_t zs[4], const float* gamma, float4* part, int* cols, hipStream_t st);
+// the same product's partial sums for a tail that stores no output (conv_pool_f32_fwd.hip): 128-column tiles
+size_t pool32_pack_bytes(int B, int Co);
+int pool32_main(int B, int Nb, int Ci, int Co, int L, const float* X, const int64_t xs[4], const float* W, const float* bias,
+                const float* gamma, float4* part, void* scratch, hipStream_t st);
+// workspace of hfta_conv1x1_bn_maxpool_f32_fwd: the partial sums, then what that product wants
+static size_t pool32_part_bytes(int B, int Nb, int Ci, int Co, int L) {
+  return (hfta_conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, HFTA_F32) + 255) & ~(size_t)255;
+}
+size_t pool32_fwd_bytes(int B, int Nb, int Ci, int Co, int L) { return pool32_part_bytes(B, Nb, Ci, Co, L) + pool32_pack_bytes(B, Co); }
 }
 
 extern "C" {
@@ -407,8 +416,9 @@ int hfta_conv1x1_bn_maxpool_f32_fwd(int B, int Nb, int Ci, int Co, int L, const 
   BnPoolFwdArgs a{nullptr, V, idx, gamma, beta, running_mean, running_var, save_mean, save_invstd,
                   0, 0, 0, vs[0], vs[1], vs[2], Nb, Co, L, act, eps, momentum, act_slope};
   const int64_t zs[4] = {(int64_t)Co * L, (int64_t)B * Co * L, L, 1};
-  int cols = 0;
-  const int rc = conv1x1_fwd_pool_part(B, Nb, Ci, Co, L, X, xs, W, bias, nullptr, zs, gamma, (float4*)workspace, &cols, st);
+  int cols = POOL_MIN_COLS;
+  int rc = pool32_main(B, Nb, Ci, Co, L, X, xs, W, bias, gamma, (float4*)workspace, (char*)workspace + pool32_part_bytes(B, Nb, Ci, Co, L), st);
+  if (rc == HFTA_EUNSUPPORTED) rc = conv1x1_fwd_pool_part(B, Nb, Ci, Co, L, X, xs, W, bias, nullptr, zs, gamma, (float4*)workspace, &cols, st);
   if (rc != HFTA_OK) return rc;
   if (cols <= 0) return HFTA_EUNSUPPORTED;
   hipLaunchKernelGGL(bn_pool_parts_kernel, dim3((unsigned)((Co + PP_C - 1) / PP_C), (unsigned)B), dim3(PP_C * PP_P), 0, st, a,

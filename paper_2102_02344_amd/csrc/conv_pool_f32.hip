@@ -19,6 +19,7 @@
 
 namespace hfta {
 bool gemm_f32_big_tiles(int M, int N, int64_t G);
+size_t pool32_fwd_bytes(int B, int Nb, int Ci, int Co, int L);
 }
 
 using namespace hfta;
@@ -475,7 +476,7 @@ size_t hfta_conv1x1_bn_maxpool_f32_workspace_bytes(int B, int Nb, int Ci, int Co
   if (!supported(B, Nb, Ci, Co, L)) return 0;
   Pool32Args a{};
   a.B = B; a.Nb = Nb; a.Ci = Ci; a.Co = Co; a.L = L; a.tiles = (L + 127) / 128;
-  const size_t bwd = layout(a, nullptr), fwd = hfta_conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, HFTA_F32);
+  const size_t bwd = layout(a, nullptr), fwd = pool32_fwd_bytes(B, Nb, Ci, Co, L);
   return bwd > fwd ? bwd : fwd;
 }
 

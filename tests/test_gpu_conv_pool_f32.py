@@ -94,6 +94,27 @@ def test_pair(hb, dims, act, slope, shift):
         assert err[1] <= 2e-6 and err[1] <= 1.05 * err[0] + 2e-8, (name, err)
 
 
+@pytest.mark.parametrize("where", ["w", "x", "both"])
+@pytest.mark.parametrize("dims", [(4, 64, 68, 161, 129), (1, 300, 128, 1024, 160)])
+def test_values_without_a_split(hb, dims, where):
+    """Values below 2^-100 and infinities have no three bf16 parts: the tiles that hold them take the fp32 instruction, the others do
+    not, and the forward's results are the stored form's, bit for bit."""
+    B, Nb, Ci, Co, L = dims
+    print(f"fp32 tail {dims} without a split in {where}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X, W, gam = r(Nb, B, Ci, L), r(B, Co, Ci), r(B, Co)
+    if where != "x":
+        W[B - 1, Co - 1, 0], W[0, 40, Ci - 1] = 2.0 ** -110, -2.0 ** -120
+    if where != "w":
+        X[Nb - 1, 0, Ci - 1, L - 1], X[0, B - 1, 0, 3] = 2.0 ** -130, 2.0 ** -105
+    if where == "both":
+        W[0, 7, 2] = float("inf")
+    (a, _), (b, _) = both_ways(hb, dims, X, W, r(B, Co), gam, r(B, Co), r(B, Nb, Co), 1, 0.0)
+    for k in a:
+        assert torch.equal(a[k].view(torch.int32)[..., 8:], b[k].view(torch.int32)[..., 8:]), k
+
+
 def _padded(X):
     """Every cloud's first 96 points are one and the same, five spreads from the others."""
     X[:, :, :, :96] = X.mean((0, 3), keepdim=True) + 5.0 * X.std((0, 3), keepdim=True)
