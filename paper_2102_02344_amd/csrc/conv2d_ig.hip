@@ -483,6 +483,14 @@ __global__ __launch_bounds__(256) void ig_split_finish_kernel(const float* __res
   *reinterpret_cast<uint4*>(out + i) = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
 }
 
+// Fewer workgroups of 128-row tiles than compute units: a workgroup is then alone on its unit, its k-tile takes as long as its own
+// chain of LDS reads and matrix instructions, and half the rows take about half as long.  us with 128 and with 64 rows (data
+// gradient with the weights' regrouping), 3 models x 20 images: 64 <-> 128 channels at 16x16, 120 workgroups, forward 20.0 12.8;
+// 128 <-> 256 at 8x8, 120, 21.4 17.8, gradient 22.8 16.8; 256 <-> 512 at 4x4, 144 and 60, 21.6 20.4, gradient 35.3 28.4.  At 192
+// the gradient 39.3 36.6; at 384 30.8 29.2 and 31.2 34.0, gradients 30.2 29.8 and 52.0 52.2; at 640 74 90 and 69 78.  32 rows gain
+// nothing over 64.
+bool few_tiles(int64_t blocks) { return blocks < 256; }
+
 // k split of the forward kernel: taken when the tiles alone leave most compute units with a single workgroup and the
 // reduction is long.  512 <- 256 channels at 8x8, unsplit and split in us: 36 tiles 53 21, 96 53 30, 192 53 47, 320 67 71 (the
 // bound predates the present kernel; it stays, since another split is another order of the sums).  With 640 tiles and more, and
@@ -563,8 +571,10 @@ int conv_ig_forward(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw,
   a.part_split = (int64_t)Nb * a.o_img;
   const size_t lds = rows_fwd_lds_bytes(a, tm);
   if (lds > IG_MAX_LDS) return HFTA_EUNSUPPORTED;
-  dim3 grid((unsigned)(tiles_m * a.tiles_n), (unsigned)a.ksplit, (unsigned)B);
-  if (tm == 64) ig_launch(conv_rows_fwd_kernel<64>, grid, 256, lds, st, a);
+  // Too few 128-row tiles for the chip: tiles of 64 rows, whose sums are the same ones (the k split stays that of the 128-row tiles).
+  const bool halves = few_tiles((int64_t)tiles_m * a.tiles_n * a.ksplit * B);
+  dim3 grid((unsigned)((halves ? (Co + 63) / 64 : tiles_m) * a.tiles_n), (unsigned)a.ksplit, (unsigned)B);
+  if (tm == 64 || halves) ig_launch(conv_rows_fwd_kernel<64>, grid, 256, lds, st, a);
   else ig_launch(conv_rows_fwd_kernel<128>, grid, 256, lds, st, a);
   if (a.ksplit > 1) {
     if (launch_status() != HFTA_OK) return HFTA_ELAUNCH;
@@ -606,18 +616,19 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   IgArgs a{};
   a.X = (const bf16_raw*)dY; a.A = (const bf16_raw*)pack; a.Out = (bf16_raw*)dX; a.bias = nullptr;
   a.x_img = (int64_t)B * Co * Hq * Wq; a.x_model = (int64_t)Co * Hq * Wq;
-  const int tm = Ci <= 64 ? 64 : 128, tiles_m = (Ci + tm - 1) / tm, ktiles = (Co * 4 + 31) / 32;
-  const int64_t cls_el = (int64_t)tiles_m * tm * ktiles * 32;          // one class of one model, fragment order
+  a.Nb = Nb; a.Cx = Co; a.H = Hq; a.W = Wq;
+  dx_geometry(a, Hq, Wq);
+  const bool planes = dxp_geometry(a);
+  a.tiles_n = (int)(((int64_t)Nb * Hq * Wq + 63) / 64);
+  const int tm = Ci <= 64 || (planes && few_tiles((int64_t)((Ci + 127) / 128) * a.tiles_n * 2 * B)) ? 64 : 128;
+  const int tiles_m = (Ci + tm - 1) / tm, ktiles = (Co * 4 + 31) / 32;
+  const int64_t cls_el = (int64_t)tiles_m * tm * ktiles * 32;          // one class of one model, fragment order: at most what the query counts
   a.a_model = 4 * cls_el;
   a.o_img = (int64_t)B * Ci * H * W; a.o_model = (int64_t)Ci * H * W; a.o_m = (int64_t)H * W;
-  a.Nb = Nb; a.Cx = Co; a.H = Hq; a.W = Wq;
   a.M = Ci; a.K = Co * 4; a.N = Nb * Hq * Wq;
   if (!ig_extents(a)) return HFTA_EUNSUPPORTED;
   a.OW = W; a.oys = 2; a.oxs = 2; a.tap_step = 1;
-  dx_geometry(a, Hq, Wq);
-  const bool planes = dxp_geometry(a);
   if (!planes && !gather_geometry(a)) return HFTA_EUNSUPPORTED;
-  a.tiles_n = (a.N + 63) / 64;
   a.act = HFTA_ACT_NONE; a.slope = 0.f;
   for (int cls = 0; cls < 4; ++cls) {
     const int py = cls >> 1, px = cls & 1;
@@ -634,13 +645,13 @@ int conv_ig_dx(int B, int Nb, int Ci, int Co, int H, int W, int kh, int kw, int 
   a.kt_per_split = ktiles;
   dim3 grid((unsigned)(tiles_m * a.tiles_n), 2u, (unsigned)B);
   if (planes) {
-    const bool few = (int64_t)tiles_m * a.tiles_n * 2 * B < 256;
+    const bool few = few_tiles((int64_t)tiles_m * a.tiles_n * 2 * B);    // (of 128 rows: never)
     if (a.W == 4) {
       if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, true, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<64, true, 1>, grid, 256, lds, st, a);
-      else few ? ig_launch(conv_dx_planes_kernel<128, true, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<128, true, 1>, grid, 256, lds, st, a);
+      else ig_launch(conv_dx_planes_kernel<128, true, 1>, grid, 256, lds, st, a);
     } else {
       if (tm == 64) few ? ig_launch(conv_dx_planes_kernel<64, false, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<64, false, 1>, grid, 256, lds, st, a);
-      else few ? ig_launch(conv_dx_planes_kernel<128, false, 2>, grid, 256, lds, st, a) : ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds, st, a);
+      else ig_launch(conv_dx_planes_kernel<128, false, 1>, grid, 256, lds, st, a);
     }
   } else {
     if (tm == 64) ig_launch(conv_ig_gather_kernel<64>, grid, 256, lds, st, a);

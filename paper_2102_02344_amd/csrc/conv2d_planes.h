@@ -11,7 +11,8 @@
 // Memory -> LDS goes by direct loads (dma_load), two 16-channel k-tiles ahead; a wave rebuilds the planes from the
 // pieces it fetched itself, so that needs no barrier, and planes are double-buffered: one barrier per 64 k.
 // Weights are fragments straight from memory (ig_pack_class_w_kernel), reloaded as they are used up; launches below
-// one workgroup per compute unit keep two k-tiles of them (60 workgroups, 32 k-tiles: 33 -> 27 us), others one
+// one workgroup per compute unit keep two k-tiles of them (60 workgroups of 128 rows, 32 k-tiles: 33 -> 27 us; 32 of 64
+// rows 25.4 -> 24.9), others one
 // (a second set costs the third workgroup per compute unit: 60 -> 67 us at 1280).
 // 10 models x 64 images: 128 <- 256 channels at 8x8 75 -> 60 us, 256 <- 512 at 4x4 71 -> 53, 64 <- 128 at 16x16 98 -> 66,
 // the same products in the same order (a reduction split over k changes bits that a GAN's next layers amplify).

@@ -1,0 +1,39 @@
+"""4x4 / stride 2 convolutions and their data gradients in row tiles of 64 (few tiles) and of 128 (many): against float64, and the
+same bits whichever the launch takes."""
+import pytest
+import torch
+import torch.nn.functional as F
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2102_02344_amd import binding
+    return binding
+
+
+# rows of 128 + 2, of 64 + 2, a multiple of both, fewer than a tile of 128; images of 4x4, 8x8, 16x16 outputs; many: 256 tiles and more
+@pytest.mark.parametrize("Nb,Ci,Co,H,many", [(5, 66, 130, 16, 72), (9, 120, 66, 8, 200), (2, 100, 128, 32, 64), (17, 72, 96, 8, 66)])
+def test_row_tiles(hb, Nb, Ci, Co, H, many):
+    print(f"conv {Nb} x {Ci} -> {Co} at {H}", flush=True)
+    gen = torch.Generator().manual_seed(11)
+    r = lambda *s: torch.randn(s, generator=gen).bfloat16()
+    x, w, dy = r(Nb, Ci, H, H), 0.05 * r(Co, Ci, 4, 4), r(Nb, Co, H // 2, H // 2)
+    got = []
+    for B in (1, many):
+        X, W, dY = (v.repeat(*n).contiguous().cuda() for v, n in ((x, (1, B, 1, 1)), (w, (B, 1, 1, 1)), (dy, (1, B, 1, 1))))
+        Y, dX = torch.full_like(dY, float("nan")), torch.full_like(X, float("nan"))
+        dims = (B, Nb, Ci, Co, H, H, 4, 4, 2, 1, 1)
+        need = max(hb.conv2d_grouped_fwd_workspace_bytes(*dims), hb.conv2d_grouped_bwd_min_workspace_bytes(*dims), 4)
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+        hb.conv2d_grouped_fwd(*dims, X, W, None, Y, workspace=ws)
+        hb.conv2d_grouped_bwd(*dims, None, W, dY, dX, None, None, workspace=ws)
+        got.append((Y.cpu().view(Nb, B, Co, H // 2, H // 2), dX.cpu().view(Nb, B, Ci, H, H)))
+    x, w, dy = x.double(), w.double(), dy.double()
+    for few, lot, f, a in ((got[0][0], got[1][0], F.conv2d, x), (got[0][1], got[1][1], F.conv_transpose2d, dy)):
+        ref, mag = f(a, w, stride=2, padding=1), f(a.abs(), w.abs(), stride=2, padding=1)
+        # the result rounded to eight bits (half a unit: 2^-8 of 1.0 whose unit is 2^-7), sums of at most 16 Ci (4 Co) products in fp32 (2^-24 each)
+        assert ((few[:, 0].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 16 * max(Ci, Co) * 2.0 ** -24 * mag).all()
+        for b in range(lot.shape[1]):
+            assert torch.equal(few[:, 0].contiguous().view(torch.int16), lot[:, b].contiguous().view(torch.int16)), b
