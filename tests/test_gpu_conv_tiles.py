@@ -37,3 +37,26 @@ def test_row_tiles(hb, Nb, Ci, Co, H, many):
         assert ((few[:, 0].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 16 * max(Ci, Co) * 2.0 ** -24 * mag).all()
         for b in range(lot.shape[1]):
             assert torch.equal(few[:, 0].contiguous().view(torch.int16), lot[:, b].contiguous().view(torch.int16)), b
+
+
+# images of whole tiles of 16 rows, of one row more, of less than one; rows of more than a tile; channels of the last stage: 4, 8 of 8
+@pytest.mark.parametrize("Nb,Ci,Co,H,W,many", [(20, 3, 20, 64, 64, 13), (8, 1, 8, 34, 36, 32), (9, 4, 12, 18, 68, 29), (16, 2, 24, 14, 4, 32)])
+def test_few_channels_rows(hb, Nb, Ci, Co, H, W, many):
+    """Data gradient of a convolution of at most four channels, one and two rows of pixels a thread: as above."""
+    print(f"conv {Nb} x {Ci} -> {Co} at {H} x {W}", flush=True)
+    gen = torch.Generator().manual_seed(12)
+    r = lambda *s: torch.randn(s, generator=gen).bfloat16()
+    w, dy = 0.05 * r(Co, Ci, 4, 4), r(Nb, Co, H // 2, W // 2)
+    got = []
+    for B in (1, many):
+        Wt, dY = w.repeat(B, 1, 1, 1).cuda(), dy.repeat(1, B, 1, 1).cuda()
+        dX = torch.full((Nb, B * Ci, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dims = (B, Nb, Ci, Co, H, W, 4, 4, 2, 1, 1)
+        ws = torch.empty(max(hb.conv2d_grouped_bwd_min_workspace_bytes(*dims), 4), dtype=torch.uint8, device="cuda")
+        hb.conv2d_grouped_bwd(*dims, None, Wt, dY, dX, None, None, workspace=ws)
+        got.append(dX.cpu().view(Nb, B, Ci, H, W))
+    w, dy = w.double(), dy.double()
+    ref, mag = F.conv_transpose2d(dy, w, stride=2, padding=1), F.conv_transpose2d(dy.abs(), w.abs(), stride=2, padding=1)
+    assert ((got[0][:, 0].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 4 * Co * 2.0 ** -24 * mag).all()
+    for b in range(many):
+        assert torch.equal(got[0][:, 0].contiguous().view(torch.int16), got[1][:, b].contiguous().view(torch.int16)), b
