@@ -205,9 +205,11 @@ int hfta_conv1x1_bn_fwd(int B, int Nb, int Ci, int Co, int L, int dtype,
  * the workspace and are added in a fixed order (bit-reproducible).  With a
  * 256-byte aligned workspace of hfta_conv1x1_bwd_workspace_bytes the data
  * gradient of a narrow bf16 layer (Co <= 128) runs as a streaming k=1
- * convolution of dY with W^T, which is written to the workspace first; with
- * a smaller or NULL workspace dX takes the general GEMM path (same result up
- * to fp32 summation order).  EWORKSPACE only if dW is asked for and its
+ * convolution of dY with W^T, which is written to the workspace first, and
+ * an fp32 layer of few output tiles and a long reduction (Co >= 512) has it
+ * split across workgroups for a contiguous dX; with a smaller or NULL
+ * workspace dX takes the general GEMM path (same result up to fp32 summation
+ * order).  EWORKSPACE only if dW is asked for and its
  * partial sums do not fit. */
 size_t hfta_conv1x1_bwd_workspace_bytes(int B, int Nb, int Ci, int Co, int L, int dtype);
 int hfta_conv1x1_bwd(int B, int Nb, int Ci, int Co, int L, int dtype,

@@ -124,3 +124,27 @@ def test_sums_of_one_sign(hb, B, Nb, Ci, Co, L):
     for got, ref, K in ((Y[0, B - 1], w @ x[0], Ci), (dX[0, B - 1], w.t().contiguous() @ d[0], Co), (dW[B - 1], ref_w, Nb * L)):
         err = float((got.double() - ref).norm() / ref.norm())
         assert err <= U * (1 + (K / 16) ** 0.5), (K, err)
+
+
+@pytest.mark.parametrize("B,Nb,Ci,Co,L", [(2, 4, 128, 1024, 256), (3, 5, 70, 601, 130), (1, 1, 3, 513, 5), (2, 64, 20, 512, 60), (1, 2, 64, 2050, 67)])
+def test_data_gradient_of_few_tiles(hb, B, Nb, Ci, Co, L):
+    """Few tiles under a long reduction: split with the workspace, whole without and for a dX with gaps; no further off float64 than
+    whole, up to one rounding of the result."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Co)
+    W, dY = (torch.randn(s, generator=g, device="cuda") for s in ((B, Co, Ci), (Nb, B, Co, L)))
+    ws = torch.empty(hb.conv1x1_bwd_workspace_bytes(B, Nb, Ci, Co, L, 0), dtype=torch.uint8, device="cuda")
+    xs, ys = conv_strides(B, Ci, L), conv_strides(B, Co, L)
+    got = []
+    for gap, work in ((0, ws), (0, None), (0, ws[:64]), (8, ws)):
+        out = torch.full((Nb, B, Ci, L + gap), float("nan"), device="cuda")
+        st = (Ci * (L + gap), B * Ci * (L + gap), L + gap, 1) if gap else xs
+        hb.conv1x1_bwd(B, Nb, Ci, Co, L, 0, None, None, W, dY, ys, out, st, None, None, workspace=work)
+        assert not gap or torch.isnan(out[..., L:]).all()
+        got.append(out[..., :L].contiguous())
+    assert torch.equal(got[1], got[2]) and torch.equal(got[1], got[3])
+    ref = torch.matmul(W.double().transpose(1, 2).contiguous(), dY.double())
+    e = [((v.double() - ref).norm() / ref.norm()).item() for v in got[:2]]
+    print(e)
+    assert not torch.equal(got[0], got[1])
+    assert e[0] <= e[1] + U / 2, e
