@@ -122,7 +122,7 @@ def kernel_label(name, a):
         return "conv1x1_bn_bwd: bn_bwd_conv_kernel + conv1x1 backward kernels"
     if name == "conv1x1_fwd_sample_bias":
         B, Nb, Ci, Co, L, dt = a[:6]
-        return (big_name(B * Nb, Co, L, (Ci, L)) if dt == 1 and big_gemm(B * Nb, Co, L, Ci) else small_gemm(dt)) + "(fwd, a bias per sample)"
+        return (big_name(B * Nb, Co, L, (Ci,), (L,)) if dt == 1 and big_gemm(B * Nb, Co, L, Ci) else small_gemm(dt)) + "(fwd, a bias per sample)"
     if name == "conv1x1_fwd":
         B, Nb, Ci, Co, L, dt = a[:6]
         if dt == 1 and Ci <= 4 and L % 4 == 0:
@@ -130,15 +130,17 @@ def kernel_label(name, a):
         if dt == 1 and Ci % 8 == 0 and L >= 4 and ((Ci <= 128 and Co >= 64) or (Ci <= 256 and Co >= 512)):
             return "conv1x1_stream_kernel"
         if dt == 1 and big_gemm(B * Nb, Co, L, Ci):
-            return big_name(B * Nb, Co, L, (Ci, L)) + "(fwd)"
+            return big_name(B * Nb, Co, L, (Ci,), (L,)) + "(fwd)"
         return small_gemm(dt) + "(fwd)"
+    if name == "linear_fwd_ws" and a[1] <= 32:
+        return "linear_few_fwd_kernel"
     if name == "linear_fwd_ws" and a[1] <= 64:
         return ("gemm_pf_kernel" if a[4] == 1 else "gemm_f32_kernel") + "(fwd, split)+splitk_bias_act_kernel"
     if name in ("linear_bn_fwd", "linear_xent", "linear_bwd_bn", "linear_bwd_act"):
         return "linear_few_%s_kernel" % ("bwd" if name.startswith("linear_bwd") else "fwd")
     if name in ("linear_fwd", "linear_fwd_ws"):
         if a[4] == 1 and big_gemm(a[0], a[1], a[3], a[2]):
-            return big_name(a[0], a[1], a[3], a[2:4]) + "(fwd)"
+            return big_name(a[0], a[1], a[3], a[2:3], a[3:4]) + "(fwd)"
         return small_gemm(a[4]) + "(fwd)"
     if name == "linear_bwd":           # the MLP array asks for dX, dW and dbias in separate calls
         B, M, Fx, Fy, dt = a[:5]
@@ -148,7 +150,7 @@ def kernel_label(name, a):
             return (big_name(B, M, Fx, (Fy,)) if dt == 1 and big_gemm(B, M, Fx, Fy) else small_gemm(dt)) + "(dX)"
         if a[9] is not None:
             sp = big_splits(B, Fx, Fy, M) if dt == 1 else 0
-            return (big_name(B, Fx, Fy, (Fx, Fy), sp) if sp else small_gemm(dt)) + "(dW)"
+            return (big_name(B, Fx, Fy, (), (Fx, Fy), sp) if sp else small_gemm(dt)) + "(dW)"
         return "colsum_kernel"
     if name == "layernorm_bwd_sums":
         return "layernorm_bwd_kernel"
@@ -203,10 +205,10 @@ def kernel_label(name, a):
             if dt == 1 and Co % 8 == 0 and L >= 4 and a[15] is not None and (
                     Ci >= 64 if Co <= 128 else 192 < Co <= 256 and Ci >= 1280 and L % 4 and B * Nb * ((L + 127) // 128) >= 768):
                 return "conv1x1_stream_kernel(dX)"
-            return (big_name(B * Nb, Ci, L, (Ci, L)) if dt == 1 and big_gemm(B * Nb, Ci, L, Co) else k) + "(dX)"
+            return (big_name(B * Nb, Ci, L, (), (Ci, L)) if dt == 1 and big_gemm(B * Nb, Ci, L, Co) else k) + "(dX)"
         sp = big_splits(B, Co, Ci, L, Nb) if dt == 1 else 0
         if sp:
-            k = big_name(B, Co, Ci, (L,), sp)
+            k = big_name(B, Co, Ci, (L,), (), sp)
         return k + "(dW)+splitk_reduce_kernel"
     if name in ("bn_fwd_maxpool", "bn_bwd_maxpool"):
         return name + "_kernel"
@@ -233,11 +235,12 @@ def big_gemm(G, M, N, K):
     return M >= 192 and N >= 192 and K >= 256 and ((M + 255) // 256) * ((N + 255) // 256) * G >= 192
 
 
-def big_name(G, M, N, rows, splits=1):
-    """The 256x256-tile kernel that a product takes: the one on a ring of LDS slots where the operands' rows (`rows`: their lengths)
-    and the output's are whole aligned pieces; else, with more workgroups than compute units, the persistent form of the
-    register-staged kernel, which takes output rows (fp32 partial rows when split) of whole 8- or 16-byte pieces."""
-    if N % 4 == 0 and all(r % 8 == 0 for r in rows):
+def big_name(G, M, N, along, across=(), splits=1):
+    """The 256x256-tile kernel that a product takes: the one on a ring of LDS slots where the operands' rows (lengths of those
+    contiguous along k and across it) and the output's are whole aligned pieces, without a split 8-byte ones across k; else, with
+    more workgroups than compute units, the persistent form of the register-staged kernel, which takes output rows (fp32 partial
+    rows when split) of whole 8- or 16-byte pieces."""
+    if N % 4 == 0 and all(r % 8 == 0 for r in along) and all(r % 8 == 0 or (splits == 1 and r % 4 == 0 and r >= 256) for r in across):
         return "gemm_ring_kernel"
     tiles = ((M + 255) // 256) * ((N + 255) // 256) * G * splits
     return "gemm_bigp_kernel" if tiles > 256 and N % 4 == 0 else "gemm_big_kernel"
