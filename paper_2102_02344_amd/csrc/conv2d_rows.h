@@ -16,7 +16,7 @@
 // 10 models x 64 images, forward: 256 <- 128 channels at 8x8 80 -> 58 us, 128 <- 64 at 16x16 and 512 <- 256 at 4x4 (split over
 // k) 85 -> 72 on average, 64 <- 3 40 -> 36; weight gradients of the same layers 75 -> 68, 88 -> 81,
 // 70 -> 64 and 46 -> 38 (with k-tiles of 64 and two workgroups per compute unit 73, 83, 67 and 46).  3 models x 20 images:
-// forward 26 -> 20 us, weight gradients 22 -> 15.
+// forward 26 -> 20 us (12.8 to 20.4 with 64-row tiles, which few_tiles gives it now), weight gradients 22 -> 15.
 
 constexpr int ROWS_PITCH = 144;                          // bytes per row of the plain operand's tile: 64 k + 16 B pad
 
@@ -26,7 +26,7 @@ __device__ __forceinline__ uint32_t lane_right(uint32_t v) { return (uint32_t)__
 
 struct __attribute__((aligned(4))) Words2 { uint32_t a, b; };
 
-// TM = 128: four wavefronts of 64 x 64; TM = 64 (layers of at most 64 output rows): of 64 x 32.  A k-tile is 64 k = four
+// TM = 128: four wavefronts of 64 x 64; TM = 64 (layers of at most 64 output rows, launches of few tiles): of 64 x 32.  A k-tile is 64 k = four
 // channels; the next one is in flight in registers while this one is multiplied; one barrier per k-tile.
 template <int TM>
 __global__ __launch_bounds__(256, 3) void conv_rows_fwd_kernel(IgArgs p) {
