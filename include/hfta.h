@@ -707,6 +707,7 @@ int hfta_add(int64_t count, int dtype, const void* A, const void* B, void* Y, vo
  *                    onto an existing gradient; idx clamped to [0, L); dV, idx with strides vs)
  *   softmax_xent_points: scores [b][n][k][l], labels int32 [B][Nb][L]; per point softmax cross-entropy
  *                    over k; loss[b] (fp32) = mean over the model's Nb*L points; dlogits = its gradient.
+ *                    (A label outside [0, K) counts as a score of 0 that has no gradient.)
  *                    Workspace: hfta_softmax_xent_points_workspace_bytes (EWORKSPACE below it).
  * Y may alias A (and Z).
  * ---------------------------------------------------------------------- */
@@ -755,7 +756,8 @@ int hfta_layernorm_bwd_sums(int B, int R, int E, int dtype, const void* X, const
                             void* workspace, size_t ws_bytes, void* stream);
 /* Per-model losses with mean reduction over the model's own R rows; loss: fp32 [B];
  * dlogits in storage dtype.  No factor B appears because each model's loss is its
- * own mean (appendix "Fused Loss", eq. 3). */
+ * own mean (appendix "Fused Loss", eq. 3).  Labels (here, in hfta_softmax_xent_rows and hfta_linear_xent) lie in [0, K): a
+ * row with any other makes its model's loss NaN, its gradient is that of no class, and nothing is read at the label. */
 int hfta_softmax_xent(int B, int R, int K, int dtype, const void* logits, const int32_t* labels,
                       float* loss, void* dlogits, void* stream);
 int hfta_bce_logits(int B, int64_t R, int dtype, const void* logits, const void* targets,

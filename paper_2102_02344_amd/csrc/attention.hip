@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void xent_rows_kernel(const T* __restrict__ lo
   const float invR = 1.f / (float)R;
   for (int k = t; k < K; k += 256)
     Elem<T>::store(dz + k, (expf(Elem<T>::load(z + k) - lse) - (k == lab ? 1.f : 0.f)) * invR);
-  if (t == 0) rowloss[row] = lse - Elem<T>::load(z + lab);
+  if (t == 0) rowloss[row] = lse - label_score(z, lab, K);
 }
 
 // Rows of at most 256 * NV sixteen-byte pieces (8192 bf16 / 4096 fp32 classes at NV = 4): the row
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void xent_rows_reg_kernel(const T* __restrict_
     else
       dz[c] = make_uint4(__float_as_uint(g[0]), __float_as_uint(g[1]), __float_as_uint(g[2]), __float_as_uint(g[3]));
   }
-  if (t == 0) rowloss[row] = mx + logf(se) - Elem<T>::load(logits + row * K + lab);
+  if (t == 0) rowloss[row] = mx + logf(se) - label_score(logits + row * K, lab, K);
 }
 
 __global__ __launch_bounds__(256) void xent_rows_reduce_kernel(const float* __restrict__ rowloss, float* __restrict__ loss, int R) {

@@ -67,6 +67,11 @@ __device__ __forceinline__ float apply_act(float x, int act, float slope) {
   }
 }
 
+// the label's entry of a row of K scores; NaN for a label that is no class, without a look at memory
+template <typename T> __device__ __forceinline__ float label_score(const T* row, int label, int K) {
+  return label >= 0 && label < K ? Elem<T>::load(row + label) : __builtin_nanf("");
+}
+
 // wave64 reductions through the cross-lane shuffle network
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -474,7 +474,7 @@ __global__ __launch_bounds__(1024) void softmax_xent_kernel(const T* __restrict_
     float se = 0.f;
     for (int k = 0; k < K; ++k) se += expf(Elem<T>::load(z + k) - mx);
     const float lse = mx + logf(se);
-    acc += lse - Elem<T>::load(z + lab);
+    acc += lse - label_score(z, lab, K);
     for (int k = 0; k < K; ++k) {
       const float pk = expf(Elem<T>::load(z + k) - lse);
       Elem<T>::store(dz + k, (pk - (k == lab ? 1.f : 0.f)) * invR);

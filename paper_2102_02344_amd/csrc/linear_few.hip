@@ -249,8 +249,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES) void linear_few_fwd_kernel(FewFwdAr
       float se = 0.f;
       for (int k = 0; k < K; ++k) se += expf(zr[k] - mx);
       const float lse = mx + logf(se);
-      // a label past the classes is read where the stored form reads it
-      a += lse - (lab >= 0 && lab < K ? zr[lab] : Elem<T>::load((const T*)p.Z + ((int64_t)b * p.M + lane) * K + lab));
+      a += lse - label_score(zr, lab, K);
       for (int k = 0; k < K; ++k) {
         const float pk = expf(zr[k] - lse);
         Elem<T>::store(dz + k, (pk - (k == lab ? 1.f : 0.f)) * invR);
