@@ -577,11 +577,12 @@ __global__ __launch_bounds__(256) void linear_few_bwd_kernel(FewBwdArgs p) {
 
 bool al16(const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; }
 bool bn_act_ok(int act) { return act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || act == HFTA_ACT_LEAKY; }
-// rows of whole pieces; operand slices below 2 GiB
+// rows of whole pieces; operand slices below 2 GiB; channels of all models counted in 31 bits
 bool few_ok(int B, int M, int Fx, int Fy, int dtype) {
   const int q = dtype == HFTA_BF16 ? 8 : 4;
   return B > 0 && B <= 65535 && M > 0 && M <= FEW_ROWS && Fx > 0 && Fy > 0 && valid_dtype(dtype) && Fx % q == 0 && Fy % q == 0 &&
-         (int64_t)Fx * Fy < (int64_t)1 << 29 && Fx < 1 << 24 && Fy < 1 << 24;
+         (int64_t)Fx * Fy < (int64_t)1 << 29 && Fx < 1 << 24 && Fy < 1 << 24 &&
+         (int64_t)B * Fx < (int64_t)1 << 31 && (int64_t)B * Fy < (int64_t)1 << 31;
 }
 // fp32: pieces of the reduction that the fp32 instruction takes in the split product too
 bool few_fwd_ok(int B, int M, int Fx, int Fy, int dtype) {

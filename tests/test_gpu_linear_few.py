@@ -159,3 +159,13 @@ def test_what_is_declined():
         return raw.hfta_linear_bwd_act(8, 32, 256, 64, 0, one, one, dY, one, one, None, H, act, 0.0, mask, p, None)
     assert bwd_act(H=None) == hb.EINVAL and bwd_act(dY=None) == hb.EINVAL and bwd_act(mask=one, p=1.0) == hb.EINVAL
     assert bwd_act(dY=off) == hb.EUNSUPPORTED and bwd_act(act=hb.ACT_GELU) == hb.EUNSUPPORTED
+
+
+def test_more_channels_than_an_int_counts():
+    """A channel of a model is numbered in 32 bits."""
+    raw, one = hb.raw(), C.c_void_p(256)
+    for Fx, Fy in ((8, 32776), (32776, 8)):
+        assert not hb.linear_few_supported(65535, 32, Fx, Fy, hb.BF16)
+        rc = raw.hfta_linear_bwd_bn(65535, 32, Fx, Fy, hb.BF16, one, one, one, one, one, None, one, one, one, one, one, 1, 0.0, None, 0.0, one, one,
+                                    None, None)
+        assert rc == hb.EUNSUPPORTED
