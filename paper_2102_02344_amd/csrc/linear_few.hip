@@ -22,6 +22,7 @@
 
 namespace hfta {
 int linear_row_splits(int B, int M, int Fx, int Fy, int dtype);
+bool gemm_f32_big_tiles(int M, int N, int64_t G);
 }
 
 using namespace hfta;
@@ -621,6 +622,9 @@ int few_bwd_args(FewBwdArgs& a, int B, int M, int Fx, int Fy, int dtype, const v
                  float* dbias) {
   if (B <= 0 || M <= 0 || Fx <= 0 || Fy <= 0 || !valid_dtype(dtype) || !X || !W || !dY || !dX || !dW) return HFTA_EINVAL;
   if (!few_ok(B, M, Fx, Fy, dtype) || !al16(X) || !al16(W) || !al16(dY)) return HFTA_EUNSUPPORTED;
+  // the weight gradient is the fp32 instruction's: gemm_f32_launch takes it for all small tiles of so few rows, for large ones up to 16
+  // (the shapes of the forward are far below those)
+  if (dtype == HFTA_F32 && M > 16 && gemm_f32_big_tiles(Fx, Fy, B)) return HFTA_EUNSUPPORTED;
   a = FewBwdArgs{};
   a.X = X; a.W = W; a.dY = dY; a.dX = dX; a.dW = dW; a.dbias = dbias;
   a.M = M; a.Fx = Fx; a.Fy = Fy; a.dx_tiles = (Fx + 31) / 32; a.dw_m = (Fx + DW_BM - 1) / DW_BM;

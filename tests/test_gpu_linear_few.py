@@ -169,3 +169,26 @@ def test_more_channels_than_an_int_counts():
         rc = raw.hfta_linear_bwd_bn(65535, 32, Fx, Fy, hb.BF16, one, one, one, one, one, None, one, one, one, one, one, 1, 0.0, None, 0.0, one, one,
                                     None, None)
         assert rc == hb.EUNSUPPORTED
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,M", [(16, 32), (16, 17), (16, 16), (15, 32)])
+def test_fp32_weight_gradient_of_many_tiles(B, M):
+    """From 512 tiles of 128 x 128 outputs on and 17 rows on the single operator takes the product of three bf16 parts: declined here."""
+    Fx, Fy = 1024, 512
+    g = torch.Generator().manual_seed(B + M)
+    x, w, dy = _rand(g, hb.F32, B, M, Fx), _rand(g, hb.F32, B, Fx, Fy), _rand(g, hb.F32, B, M, Fy)
+    dx, dx2, dw, dw2, da = (torch.full(s, float("nan"), device=DEV) for s in ((B, M, Fx), (B, M, Fx), (B, Fx, Fy), (B, Fx, Fy), (B, M, Fx)))
+    wb = torch.empty(max(4, hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, hb.F32)), dtype=torch.uint8, device=DEV)
+    hb.linear_bwd(B, M, Fx, Fy, hb.F32, x, w, dy, dx, dw, None, wb)
+    if B == 16 and M > 16:
+        for call in (lambda: hb.linear_bwd_bn(B, M, Fx, Fy, hb.F32, x, w, dy, dx2, dw2, None),
+                     lambda: hb.linear_bwd_act(B, M, Fx, Fy, hb.F32, x, w, dy, da, dw2, None, x)):
+            with pytest.raises(hb.HftaError) as e:
+                call()
+            assert e.value.status == hb.EUNSUPPORTED
+        assert torch.isnan(dx2).all() and torch.isnan(dw2).all() and not hb.linear_few_supported(B, M, Fx, Fy, hb.F32)
+    else:
+        hb.linear_bwd_bn(B, M, Fx, Fy, hb.F32, x, w, dy, dx2, dw2, None)
+        _same(dx, dx2, "dX")
+        _same(dw, dw2, "dW")
