@@ -462,8 +462,9 @@ int hfta_bn_bwd_maxpool(int B, int Nb, int C, int L, int dtype,
  * maximum is not clipped; zhit fp32 [B][Nb][Co] = the convolution's output at idx (for a row that a ReLU clips as a whole, whose
  * gradient is zero, at any of its points).  Backward: dX, dW, dgamma, dbeta as hfta_bn_bwd_maxpool followed by hfta_conv1x1_bwd
  * give them, up to fp32 rounding; dbias (or NULL) exactly zero.  act: NONE, RELU, or LEAKY with slope >= 0.
- * hfta_conv1x1_bn_maxpool_f32_workspace_bytes: what either direction needs (256-byte aligned), 0 for shapes the pair is not built
- * for (64 < Ci <= 128 in multiples of four, 64 < Co <= 1024, 128 <= L < 2^21, at least 512 tiles of 128 points). */
+ * hfta_conv1x1_bn_maxpool_f32_workspace_bytes: what either direction wants (256-byte aligned), 0 for shapes the pair is not built for.
+ * Less, but what the backward needs and hfta_conv1x1_bn_pool_fwd_workspace_bytes, is taken too: the forward's product is then the
+ * general one, with the same results.  (Shapes: 64 < Ci <= 128 in multiples of four, 64 < Co <= 1024, 128 <= L < 2^21, at least 512 tiles of 128 points). */
 size_t hfta_conv1x1_bn_maxpool_f32_workspace_bytes(int B, int Nb, int Ci, int Co, int L);
 int hfta_conv1x1_bn_maxpool_f32_fwd(int B, int Nb, int Ci, int Co, int L, const float* X, const int64_t xs[4], const float* W,
                                     const float* bias, const float* gamma, const float* beta, float eps, float momentum,

@@ -327,6 +327,7 @@ int pool32_main(int B, int Nb, int Ci, int Co, int L, const float* X, const int6
 static size_t pool32_part_bytes(int B, int Nb, int Ci, int Co, int L) {
   return (hfta_conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, HFTA_F32) + 255) & ~(size_t)255;
 }
+size_t pool32_least_bytes(int B, int Nb, int Ci, int Co, int L);
 size_t pool32_fwd_bytes(int B, int Nb, int Ci, int Co, int L) { return pool32_part_bytes(B, Nb, Ci, Co, L) + pool32_pack_bytes(B, Co); }
 }
 
@@ -407,7 +408,7 @@ int hfta_conv1x1_bn_maxpool_f32_fwd(int B, int Nb, int Ci, int Co, int L, const 
     return HFTA_EINVAL;
   if ((running_mean == nullptr) != (running_var == nullptr)) return HFTA_EINVAL;
   if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || (act == HFTA_ACT_LEAKY && act_slope >= 0.f))) return HFTA_EUNSUPPORTED;
-  const size_t need = hfta_conv1x1_bn_maxpool_f32_workspace_bytes(B, Nb, Ci, Co, L);
+  const size_t need = pool32_least_bytes(B, Nb, Ci, Co, L);
   if (xs[3] != 1 || need == 0) return HFTA_EUNSUPPORTED;
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 != 0 ||
       ws_bytes < need)
@@ -417,7 +418,9 @@ int hfta_conv1x1_bn_maxpool_f32_fwd(int B, int Nb, int Ci, int Co, int L, const 
                   0, 0, 0, vs[0], vs[1], vs[2], Nb, Co, L, act, eps, momentum, act_slope};
   const int64_t zs[4] = {(int64_t)Co * L, (int64_t)B * Co * L, L, 1};
   int cols = POOL_MIN_COLS;
-  int rc = pool32_main(B, Nb, Ci, Co, L, X, xs, W, bias, gamma, (float4*)workspace, (char*)workspace + pool32_part_bytes(B, Nb, Ci, Co, L), st);
+  int rc = HFTA_EUNSUPPORTED;
+  if (ws_bytes >= pool32_fwd_bytes(B, Nb, Ci, Co, L))
+    rc = pool32_main(B, Nb, Ci, Co, L, X, xs, W, bias, gamma, (float4*)workspace, (char*)workspace + pool32_part_bytes(B, Nb, Ci, Co, L), st);
   if (rc == HFTA_EUNSUPPORTED) rc = conv1x1_fwd_pool_part(B, Nb, Ci, Co, L, X, xs, W, bias, nullptr, zs, gamma, (float4*)workspace, &cols, st);
   if (rc != HFTA_OK) return rc;
   if (cols <= 0) return HFTA_EUNSUPPORTED;

@@ -12,6 +12,7 @@
 // On 4 x 32 x 2500 points, 128 -> 1024 channels: forward 858 -> 598 us (the product without its stores), backward 1567 -> 314
 // (moments 107, dX 123, the rest 84); dX 2.2e-7 -> 5.7e-8 and dW 5.9e-7 -> 6.6e-8 off float64.
 // Bound: x read twice and dX written once; the hits, a chain of loads per tile, and the moments' phases take longer.
+#include <algorithm>
 #include "gemm_pf.h"
 #include "f32_split.h"
 #include "bn_common.h"
@@ -470,14 +471,21 @@ bool supported(int B, int Nb, int Ci, int Co, int L) {
 
 }  // namespace
 
-extern "C" {
-
-size_t hfta_conv1x1_bn_maxpool_f32_workspace_bytes(int B, int Nb, int Ci, int Co, int L) {
+namespace hfta {
+// least workspace of either direction: the backward's, or the forward's partial sums (whose product is then the general one)
+size_t pool32_least_bytes(int B, int Nb, int Ci, int Co, int L) {
   if (!supported(B, Nb, Ci, Co, L)) return 0;
   Pool32Args a{};
   a.B = B; a.Nb = Nb; a.Ci = Ci; a.Co = Co; a.L = L; a.tiles = (L + 127) / 128;
-  const size_t bwd = layout(a, nullptr), fwd = pool32_fwd_bytes(B, Nb, Ci, Co, L);
-  return bwd > fwd ? bwd : fwd;
+  return std::max(layout(a, nullptr), hfta_conv1x1_bn_pool_fwd_workspace_bytes(B, Nb, Ci, Co, L, HFTA_F32));
+}
+}  // namespace hfta
+
+extern "C" {
+
+size_t hfta_conv1x1_bn_maxpool_f32_workspace_bytes(int B, int Nb, int Ci, int Co, int L) {
+  const size_t least = pool32_least_bytes(B, Nb, Ci, Co, L);
+  return least ? std::max(least, pool32_fwd_bytes(B, Nb, Ci, Co, L)) : 0;
 }
 
 int hfta_conv1x1_bn_maxpool_f32_bwd(int B, int Nb, int Ci, int Co, int L, const float* X, const int64_t xs[4], const float* W,
@@ -491,7 +499,7 @@ int hfta_conv1x1_bn_maxpool_f32_bwd(int B, int Nb, int Ci, int Co, int L, const 
   if (!(act == HFTA_ACT_NONE || act == HFTA_ACT_RELU || (act == HFTA_ACT_LEAKY && act_slope >= 0.f))) return HFTA_EUNSUPPORTED;
   if (xs[3] != 1 || dxs[3] != 1 || xs[2] <= 0 || !supported(B, Nb, Ci, Co, L)) return HFTA_EUNSUPPORTED;
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 != 0 || reinterpret_cast<uintptr_t>(W) % 8 != 0 ||
-      ws_bytes < hfta_conv1x1_bn_maxpool_f32_workspace_bytes(B, Nb, Ci, Co, L))
+      ws_bytes < pool32_least_bytes(B, Nb, Ci, Co, L))
     return reinterpret_cast<uintptr_t>(W) % 8 != 0 ? HFTA_EUNSUPPORTED : HFTA_EWORKSPACE;
   const int64_t x_bytes = ((int64_t)(Ci - 1) * xs[2] + L) * 4;
   if (x_bytes >= (int64_t)1 << 31) return HFTA_EUNSUPPORTED;

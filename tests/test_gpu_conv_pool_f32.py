@@ -223,3 +223,27 @@ def test_array_gradients_behind_the_tail():
     lean.forward_backward()
     for n, _ in lean.shapes:
         assert torch.equal(lean.g(n), grads[0][n]), n
+
+
+def test_workspace_without_the_weights_parts(hb):
+    """A workspace that holds the partial sums and not W's parts beside them: the general product, the same results; less is refused."""
+    B, Nb, Ci, Co, L = dims = (2, 14, 68, 1024, 4000)
+    full, small = hb.conv1x1_bn_maxpool_f32_workspace_bytes(*dims), hb.conv1x1_bn_pool_fwd_workspace_bytes(*dims, 0)
+    assert small < full
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X, W, bias, gam, bet, dV = r(Nb, B, Ci, L), 0.2 * r(B, Co, Ci), r(B, Co), r(B, Co), r(B, Co), r(B, Nb, Co)
+    xs, vs = conv_strides(B, Ci, L), (Nb * Co, Co, 1)
+
+    def run(size):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        e = lambda *s: torch.full(s, float("nan"), device="cuda")
+        idx, stats = torch.full((B, Nb, Co), -1, dtype=torch.int32, device="cuda"), [torch.ones(B * Co, device="cuda") for _ in range(4)]
+        V, zhit, dX, dW, dg, dbt = e(B, Nb, Co), e(B, Nb, Co), e(Nb, B, Ci, L), e(B, Co, Ci), e(B, Co), e(B, Co)
+        hb.conv1x1_bn_maxpool_f32_fwd(*dims, X, xs, W, bias, gam, bet, 1e-5, 0.1, *stats, V, idx, vs, zhit, 1, 0.0, ws)
+        hb.conv1x1_bn_maxpool_f32_bwd(*dims, X, xs, W, bias, zhit, dV, idx, vs, gam, bet, stats[2], stats[3], dX, xs, dW, None, dg, dbt, 1, 0.0, ws)
+        return [V, idx, zhit, dX, dW, dg, dbt] + stats
+    for a, b in zip(run(full), run(small)):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    with pytest.raises(hb.HftaError):
+        run(small - 256)
