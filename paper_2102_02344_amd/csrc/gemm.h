@@ -538,7 +538,8 @@ int gemm_pick_splits(const GemmDesc& d);         // from the shape alone (worksp
 int gemm_splits(const GemmDesc& d);              // with the operands known
 size_t gemm_partial_bytes(const GemmDesc& d, int splits);
 int gemm_launch(const GemmDesc& d, hipStream_t stream);
-// both gradients of a Linear in one launch (bf16); HFTA_EUNSUPPORTED: make the two launches
+// both gradients of a Linear in one launch (bf16), where gemm_pair_takes the shapes; HFTA_EUNSUPPORTED: make the two launches
+bool gemm_pair_takes(const GemmDesc& dw, const GemmDesc& dx);
 int gemm_pair_launch(const GemmDesc& dw, const GemmDesc& dx, hipStream_t stream);
 
 }  // namespace hfta

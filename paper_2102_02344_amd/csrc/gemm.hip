@@ -192,9 +192,15 @@ static GemmArgs plain_args(const GemmDesc& d, int splits) {
   return a;
 }
 
+// Whether the two products of one Linear's gradients, on aligned operands, are one launch: shapes of the pair whose weight gradient is
+// not split (gemm_splits).
+bool gemm_pair_takes(const GemmDesc& dw, const GemmDesc& dx) {
+  return gemm_dma_pair_takes(dw, dx) && (gemm_dma_tile(dw) >= 0 || gemm_pick_splits(dw) == 1);
+}
+
 // Data gradient dx and weight gradient dw of one Linear in one launch, bits as in two.  HFTA_EUNSUPPORTED: make the two launches.
 int gemm_pair_launch(const GemmDesc& dw, const GemmDesc& dx, hipStream_t st) {
-  if (dw.splits > 1 || !gemm_dma_pair_takes(dw, dx) || !lds_operands(dw) || !lds_operands(dx)) return HFTA_EUNSUPPORTED;
+  if (dw.splits > 1 || !gemm_pair_takes(dw, dx) || !lds_operands(dw) || !lds_operands(dx)) return HFTA_EUNSUPPORTED;
   auto args = [](const GemmDesc& d) {
     GemmArgs a = plain_args(d, 1);
     a.a_extent = (uint32_t)slice_bytes(d.a_kc, d.M, d.K, d.a_ld, 2);

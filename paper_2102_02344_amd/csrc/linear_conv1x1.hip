@@ -1,7 +1,7 @@
 // Fused Linear and fused k=1 Conv1d: argument checking and mapping of the
 // forward / data-gradient / weight-gradient forms onto the batched GEMM core,
 // plus the bias-gradient reductions.
-#include "gemm_dma.h"
+#include "gemm.h"
 #include "in_norm.h"
 #include <mutex>
 
@@ -397,8 +397,8 @@ size_t hfta_linear_bwd_workspace_bytes(int B, int M, int Fx, int Fy, int dtype) 
 
 int hfta_linear_bwd_pair_supported(int B, int M, int Fx, int Fy, int dtype) {
   if (B <= 0 || M <= 0 || Fx <= 0 || Fy <= 0 || dtype != HFTA_BF16) return 0;
-  return gemm_dma_pair_takes(linear_dw_desc(B, M, Fx, Fy, dtype, nullptr, nullptr, nullptr),
-                             linear_dx_desc(B, M, Fx, Fy, dtype, nullptr, nullptr, nullptr)) ? 1 : 0;
+  return gemm_pair_takes(linear_dw_desc(B, M, Fx, Fy, dtype, nullptr, nullptr, nullptr),
+                         linear_dx_desc(B, M, Fx, Fy, dtype, nullptr, nullptr, nullptr)) ? 1 : 0;
 }
 
 int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* dY,

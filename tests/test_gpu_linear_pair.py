@@ -70,3 +70,32 @@ def test_which_products():
     assert not ok(8, 2048, 256, 1024, hb.F32) and not ok(1, 63, 256, 256, hb.BF16) and not ok(1, 64, 12, 8, hb.BF16)
     assert not ok(8, 2048, 1024, 256, hb.BF16)          # 2304 tiles
     assert not ok(16, 4096, 512, 2048, hb.BF16) and not ok(1, 8193, 64, 64, hb.BF16) and not ok(0, 64, 8, 8, hb.BF16)
+
+
+def test_split_weight_gradients_are_no_pair():
+    """What is announced as one launch is one: a weight gradient of more than 320 tiles of 128 x 128 keeps its split over the rows."""
+    assert not hb.linear_bwd_pair_supported(9, 504, 384, 1536, hb.BF16) and not hb.linear_bwd_pair_supported(7, 808, 512, 2048, hb.BF16)
+    split = 0
+    for E in (256, 384, 512):
+        for B in range(1, 17):
+            for M in range(128, 4097, 56):
+                for Fx, Fy in ((E, 4 * E), (4 * E, E)):
+                    if hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, hb.BF16) and B * -(-Fx // 128) * -(-Fy // 128) > 320:
+                        split += 1
+                        assert not hb.linear_bwd_pair_supported(B, M, Fx, Fy, hb.BF16), (B, M, Fx, Fy)
+    assert split > 100
+
+
+@pytest.mark.gpu
+def test_where_the_weight_gradient_is_split():
+    B, M, Fx, Fy = 9, 504, 384, 1536
+    g = torch.Generator(device=DEV).manual_seed(9)
+    r = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)
+    x, w, dy = r(B, M, Fx), r(B, Fx, Fy), r(B, M, Fy)
+    ws = torch.empty(hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, hb.BF16), dtype=torch.uint8, device=DEV)
+    dx, dx2, dw, dw2 = torch.empty_like(x), torch.empty_like(x), torch.empty(B, Fx, Fy, device=DEV), torch.empty(B, Fx, Fy, device=DEV)
+    hb.linear_bwd(B, M, Fx, Fy, hb.BF16, x, w, dy, dx, dw, None, ws)
+    hb.linear_bwd(B, M, Fx, Fy, hb.BF16, None, w, dy, dx2, None, None, None)
+    hb.linear_bwd(B, M, Fx, Fy, hb.BF16, x, None, dy, None, dw2, None, ws)
+    _same(dx, dx2, "dX")
+    _same(dw, dw2, "dW")
