@@ -128,9 +128,10 @@ int hfta_linear_bwd(int B, int M, int Fx, int Fy, int dtype,
 
 /* The same Linear on few rows together with the operators that stand beside it in a fully connected head, each call ONE launch
  * that leaves the bits of the single operators (at most 32 rows, Fx and Fy multiples of 8 in bf16 and of 4 in fp32, X, W and dY
- * 16-byte aligned; EUNSUPPORTED with nothing launched otherwise: make the single calls).  hfta_linear_few_supported: 1 where the two
- * forward calls take the shape (the backward calls take any such shape, in fp32 with more than 16 rows only below 512 tiles of
- * 128 x 128 weights of all models, where the single operator's weight gradient is another product).
+ * 16-byte aligned; EUNSUPPORTED with nothing launched otherwise: make the single calls).  hfta_linear_few_supported: 1 where all
+ * take the shape and are sooner than the single calls, which with many models fill the chip themselves.  (The calls take more: the
+ * backward ones any such shape, in fp32 with more than 16 rows only below 512 tiles of 128 x 128 weights of all models, where the
+ * single operator's weight gradient is another product.)
  *   hfta_linear_bn_fwd  = hfta_linear_fwd_ws (Z = X W + bias), hfta_bn_fwd over the rows (Y), and with a mask hfta_dropout (Yd).
  *   hfta_linear_xent    = hfta_linear_fwd_ws (logits), hfta_softmax_xent; K <= 32 classes.
  *   hfta_linear_bwd_bn  = hfta_linear_bwd (dW, dbias or NULL); Z == NULL: dX = dY W^T.  Otherwise Z is what the BatchNorm below

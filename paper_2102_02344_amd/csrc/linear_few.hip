@@ -593,6 +593,30 @@ bool few_fwd_ok(int B, int M, int Fx, int Fy, int dtype) {
   return splits <= FewFwd<float>::SPLITS && (Fx + splits - 1) / splits <= FEW_F32_EXACT_K;
 }
 
+// Whether a layer of such shapes is sooner in these launches than in the single operators.  A launch of few workgroups costs the wait
+// for it; one of many costs what its workgroups do, and there the single operators' larger tiles read less.  us, single operators ->
+// these, BatchNorm and dropout forward and backward, 32 rows a model:
+//   bf16, 1024 -> 512    16 models 20 -> 12, 28 -> 20     32: 24 -> 18, 37 -> 33     64: 24 -> 36, 60 -> 59    256: 89 -> 155, 257 -> 285
+//         512 -> 256     64: 20 -> 13, 32 -> 28     96: 26 -> 20, 40 -> 40    128: 19 -> 26, 45 -> 51    512: 58 -> 83, 170 -> 268
+//   fp32, 64 -> 64       32: 12 -> 6, 17 -> 7    256: 16 -> 13, 24 -> 21 (without BatchNorm 12 -> 14)   512: 18 -> 21, 29 -> 34
+//         28 -> 436      500: 51 -> 133, 47 -> 162
+// The forward's time in bf16 is its workgroups times the k that a wavefront walks (one wavefront the whole reduction where it is not split),
+// the backward's six rounds of two workgroups a compute unit; in fp32 a compute unit holds one.  Both calls of a layer,
+// 497 shapes of 1 to 622 models: 0.98 to 3.0 times as fast within these lines (2.2 at the median), 0.33 to 1.6 past them (0.90).
+bool few_pays(int B, int M, int Fx, int Fy, int dtype) {
+  const int64_t fwd = (int64_t)((Fy + 31) / 32) * B, splits = linear_row_splits(B, M, Fx, Fy, dtype);
+  const int64_t bwd = (int64_t)((Fx + 31) / 32 + (Fx + DW_BM - 1) / DW_BM * ((Fy + DW_BN - 1) / DW_BN)) * B;
+  if (dtype == HFTA_BF16) return fwd * ((Fx + splits - 1) / splits) <= 1 << 18 && bwd <= 3072;
+  return fwd <= 512 && bwd <= 640;
+}
+// The forward alone against the split product and the sum of its parts, two launches.  bf16, 32 rows, 1024 -> 512: 8 models 12 -> 6 us,
+// 24 18 -> 14, 48 22 -> 24; 53 models 776 -> 376 20 -> 22.  fp32, more pieces than wavefronts (1024 -> 512, 1 model 9.4 -> 12.3, 2 11.4 ->
+// 12.6; 4, of 16 pieces, 11.7 -> 10.3).
+bool few_ws_pays(int B, int Fx, int Fy, int dtype, int splits) {
+  const int64_t fwd = (int64_t)((Fy + 31) / 32) * B;
+  return dtype == HFTA_BF16 ? fwd * ((Fx + splits - 1) / splits) <= 3 << 16 : splits <= FWD_WAVES && fwd <= 512;
+}
+
 template <int KIND> int few_fwd_launch(int B, int dtype, FewFwdArgs a, hipStream_t st) {
   // 512 threads for the 32 columns x 16 row lanes, more where the reduction is cut finer
   const int waves = a.splits < 8 ? 8 : a.splits > FWD_WAVES ? FWD_WAVES : a.splits;
@@ -634,13 +658,14 @@ int few_bwd_args(FewBwdArgs& a, int B, int M, int Fx, int Fy, int dtype, const v
 }  // namespace
 
 namespace hfta {
-// the split forward of a Linear (linear_row_splits > 1) in one launch; HFTA_EUNSUPPORTED: not a shape, alignment or activation for it
+// the split forward of a Linear (linear_row_splits > 1) in one launch, where that is sooner; HFTA_EUNSUPPORTED: not a shape, alignment
+// or activation for it
 int linear_few_fwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* bias, void* Y, int act, float slope,
                    hipStream_t st) {
   FewFwdArgs a;
   const int rc = few_fwd_args(a, B, M, Fx, Fy, dtype, X, W, bias, Y);
   if (rc != HFTA_OK) return rc;
-  if (!bn_act_ok(act)) return HFTA_EUNSUPPORTED;
+  if (!bn_act_ok(act) || !few_ws_pays(B, Fx, Fy, dtype, a.splits)) return HFTA_EUNSUPPORTED;
   a.act = act; a.slope = slope;
   return few_fwd_launch<FEW_ACT>(B, dtype, a, st);
 }
@@ -648,7 +673,9 @@ int linear_few_fwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const
 
 extern "C" {
 
-int hfta_linear_few_supported(int B, int M, int Fx, int Fy, int dtype) { return few_fwd_ok(B, M, Fx, Fy, dtype) ? 1 : 0; }
+int hfta_linear_few_supported(int B, int M, int Fx, int Fy, int dtype) {
+  return few_fwd_ok(B, M, Fx, Fy, dtype) && few_pays(B, M, Fx, Fy, dtype) ? 1 : 0;
+}
 
 int hfta_linear_bn_fwd(int B, int M, int Fx, int Fy, int dtype, const void* X, const void* W, const void* bias, const float* gamma,
                        const float* beta, float eps, float momentum, float* running_mean, float* running_var, float* save_mean,

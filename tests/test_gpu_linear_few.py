@@ -192,3 +192,42 @@ def test_fp32_weight_gradient_of_many_tiles(B, M):
         hb.linear_bwd_bn(B, M, Fx, Fy, hb.F32, x, w, dy, dx2, dw2, None)
         _same(dx, dx2, "dX")
         _same(dw, dw2, "dW")
+
+
+def test_where_one_launch_is_the_sooner_way():
+    """Both sides of the lines: k of a wavefront times workgroups of the forward, workgroups of the backward, LDS in fp32."""
+    ok = hb.linear_few_supported
+    assert ok(32, 32, 1024, 512, hb.BF16) and not ok(33, 32, 1024, 512, hb.BF16) and not ok(64, 4, 1024, 512, hb.BF16)
+    assert ok(96, 32, 512, 256, hb.BF16) and not ok(97, 32, 512, 256, hb.BF16) and not ok(256, 13, 512, 256, hb.BF16)
+    assert ok(307, 32, 256, 16, hb.BF16) and not ok(308, 32, 256, 16, hb.BF16)
+    assert ok(64, 32, 256, 16, hb.F32) and not ok(65, 32, 256, 16, hb.F32) and not ok(512, 4, 64, 64, hb.F32)
+    assert ok(51, 4, 64, 320, hb.F32) and not ok(52, 4, 64, 320, hb.F32)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt,B,M,Fx,Fy", [(hb.BF16, 65, 32, 1024, 512), (hb.BF16, 300, 3, 88, 136), (hb.BF16, 24, 32, 1024, 512),
+                                          (hb.BF16, 25, 32, 1024, 512), (hb.F32, 300, 5, 64, 64), (hb.F32, 2, 4, 1024, 512), (hb.F32, 4, 4, 1024, 512)])
+def test_beyond_those_lines(dt, B, M, Fx, Fy):
+    """The calls take such shapes and leave the same bits; so does the forward with a workspace on either of its routes."""
+    g = torch.Generator().manual_seed(B)
+    x, w, bias, gamma, beta = _rand(g, dt, B, M, Fx), _rand(g, dt, B, Fx, Fy, scale=Fx ** -0.5), _rand(g, dt, B, Fy), _f32(g, B, Fy), _f32(g, B, Fy)
+    z, z2, z3, y, y2 = (torch.empty(B, M, Fy, dtype=TDT[dt], device=DEV) for _ in range(5))
+    ls = (M * Fy, Fy, 1, 1)
+    s1, s2 = ([torch.ones(B, Fy, device=DEV) for _ in range(4)] for _ in range(2))
+    ws = torch.empty(max(4, hb.linear_fwd_workspace_bytes(B, M, Fx, Fy, dt)), dtype=torch.uint8, device=DEV)
+    if hb.linear_fwd_workspace_bytes(B, M, Fx, Fy, dt) <= hb.linear_fwd_static_max_bytes():
+        _linear(B, M, Fx, Fy, dt, x, w, bias, z)
+    else:
+        hb.linear_fwd_ws(B, M, Fx, Fy, dt, x, w, bias, z, workspace=ws)
+    hb.bn_fwd(B, M, Fy, 1, dt, z, ls, gamma, beta, 1e-5, 0.1, *s1, y, ls, hb.ACT_RELU)
+    hb.linear_bn_fwd(B, M, Fx, Fy, dt, x, w, bias, gamma, beta, 1e-5, 0.1, *s2, z2, y2, hb.ACT_RELU)
+    hb.linear_fwd_ws(B, M, Fx, Fy, dt, x, w, bias, z3, workspace=ws)
+    for a, b, what in [(z, z2, "z"), (z, z3, "with a workspace"), (y, y2, "y")] + [(a, b, "statistics") for a, b in zip(s1, s2)]:
+        _same(a, b, what)
+    dy, dx, dx2 = _rand(g, dt, B, M, Fy, scale=0.1), torch.empty_like(x), torch.empty_like(x)
+    dw, dw2, db, db2 = torch.empty(B, Fx, Fy, device=DEV), torch.empty(B, Fx, Fy, device=DEV), torch.empty(B, Fy, device=DEV), torch.empty(B, Fy, device=DEV)
+    wb = torch.empty(max(4, hb.linear_bwd_workspace_bytes(B, M, Fx, Fy, dt)), dtype=torch.uint8, device=DEV)
+    hb.linear_bwd(B, M, Fx, Fy, dt, x, w, dy, dx, dw, db, wb)
+    hb.linear_bwd_bn(B, M, Fx, Fy, dt, x, w, dy, dx2, dw2, db2)
+    for a, b, what in ((dx, dx2, "dX"), (dw, dw2, "dW"), (db, db2, "dbias")):
+        _same(a, b, what)
