@@ -178,9 +178,10 @@ int conv_dx_fewc(int B, int Nb, int Ci, int Co, int H, int W, const void* Wt, co
   const bool pair = a.Wq % 2 == 0 && reinterpret_cast<uintptr_t>(dY) % 4 == 0;
   // two rows of q pixels a thread where that leaves two workgroups per compute unit.  us with one row and with two, 64 -> 3 channels at
   // 64 x 64, workgroups of two rows: 1280 120.6 91.3, 640 68.1 62.3, 400 (60 x 60) 45.3 38.0, 384 46.9 47.9, 120 26.3 33.4; four rows 96.7,
-  // 71.8, 39.0, 48.5, 46.9
+  // 71.8, 39.0, 48.5, 46.9.  Not for images of at most eight rows of q pixels, where it leaves as many workgroups with half of the threads
+  // idle: 64 -> 3 channels, 512 images of 16 x 16 35.8 47.6, 1280 of 8 x 8 64.9 85.4; 1280 of 20 x 20 115.6 83.8
   const int64_t two = (int64_t)a.tiles_x * ((a.Hq + 2 * FC_TY - 1) / (2 * FC_TY)) * Nb * B;
-  const int rows = pair && two >= 512 ? 2 : 1, ph = FC_TY * rows;
+  const int rows = pair && two >= 512 && a.Hq > FC_TY ? 2 : 1, ph = FC_TY * rows;
   const size_t lds = 2 * (pair && rows == 1 ? 16 : 8) * (ph + 2) * FC_PW * 2;
   const dim3 grid((unsigned)(a.tiles_x * ((a.Hq + ph - 1) / ph)), (unsigned)Nb, (unsigned)B);
 #define HFTA_FEWC(C) \
