@@ -90,7 +90,15 @@ static int64_t tiles64(const GemmDesc& d, int bm) { return (int64_t)((d.M + bm -
 // Up to 3 1/4 rounds of the 512 places and 24.8 GFLOP; more work is faster on larger tiles: 3 x 2048, 512 -> 2048 (25.8 GFLOP)
 // 43.8 -> 46.0, 4 x 2048, 256 -> 3000 (25.2) 51.6 -> 52.7, 16 x 693, 1024 -> 256 (1920 tiles) 26.3 -> 28.3, 8 x 2048, 1024 -> 256
 // (2304 tiles) 34.5 -> 35.2, 16 x 4096, 512 -> 2048 292 -> 496.  Reductions past 128 k-tiles of the weight gradient stay split.
+// Not widths that are no whole tiles of 128 where each product alone is one round of 128 x 128 tiles under a long reduction: those read
+// less than the pair's 64 columns.  102 such shapes of 40 k-tiles together and more (9 x 2138, 104 -> 2912 56.7 -> 66.7,
+// 5 x 2433, 232 -> 1944 52.8 -> 61.5) take 1.08 times as long in one launch at the median, the same with whole tiles 0.91 times
+// (121 shapes), with shorter reductions 0.89 (200).
 bool gemm_dma_pair_takes(const GemmDesc& dw, const GemmDesc& dx) {
+  auto round128 = [](const GemmDesc& d) {
+    return gemm_dma_tile(d) == 2 && (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * d.G0 <= 256;
+  };
+  if ((dw.M % 128 || dw.N % 128) && (dw.K + 63) / 64 + (dx.K + 63) / 64 >= 40 && round128(dw) && round128(dx)) return false;
   return dw.dtype == HFTA_BF16 && dw.M % 8 == 0 && dw.N % 8 == 0 && dw.K >= 64 && dw.K <= 128 * 64 &&
          tiles64(dw, 128) + tiles64(dx, 128) <= 1664 && 4.0 * dw.G0 * dw.K * dw.M * dw.N <= 24.8e9;
 }

@@ -99,3 +99,12 @@ def test_where_the_weight_gradient_is_split():
     hb.linear_bwd(B, M, Fx, Fy, hb.BF16, x, None, dy, None, dw2, None, ws)
     _same(dx, dx2, "dX")
     _same(dw, dw2, "dW")
+
+
+def test_one_round_of_large_tiles_each():
+    """Widths that are no whole tiles of 128, both products a round of 128 x 128 tiles, 40 k-tiles together: two launches."""
+    ok = lambda *a: hb.linear_bwd_pair_supported(*a, hb.BF16)
+    assert not ok(9, 2138, 104, 2912) and not ok(5, 2433, 232, 1944) and not ok(15, 1445, 128, 1856)
+    assert ok(6, 1536, 384, 1536) and ok(3, 2431, 512, 1536)            # whole tiles
+    assert ok(13, 811, 232, 912)                                       # 28 k-tiles
+    assert ok(14, 1693, 88, 2440) and ok(8, 2138, 56, 2912)             # more than a round of one, smaller tiles for the other
