@@ -247,3 +247,23 @@ def test_workspace_without_the_weights_parts(hb):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     with pytest.raises(hb.HftaError):
         run(small - 256)
+
+
+@pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
+@pytest.mark.parametrize("dims", [(1, 520, 68, 161, 129), (2, 300, 128, 1024, 160)])
+def test_channel_of_no_numbers(hb, dims, value):
+    """A channel whose weights hold no number: its statistics, its values and the point it names (the first, and never one past the row,
+    here in rows with a last tile of one and of 32 points) are those of the stored form, and the other channels do not notice."""
+    B, Nb, Ci, Co, L = dims
+    print(f"fp32 tail {dims} with {value}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X, W, gam = r(Nb, B, Ci, L), r(B, Co, Ci), r(B, Co)
+    W[0, 7, 2] = value
+    W[B - 1, Co - 1, :] = value
+    (a, _), (b, _) = both_ways(hb, dims, X, W, r(B, Co), gam, r(B, Co), r(B, Nb, Co), 1, 0.0)
+    for k in a:
+        v, w = a[k], b[k]
+        assert torch.equal(torch.isnan(v), torch.isnan(w)) and torch.equal(v.nan_to_num(), w.nan_to_num()), k
+    assert (b["idx"][0, :, 7] == 0).all() and (b["idx"][B - 1, :, Co - 1] == 0).all() and ((b["idx"] >= 0) & (b["idx"] < L)).all()
+    assert torch.isnan(b["mean"].view(B, Co)[0, 7]) or torch.isinf(b["mean"].view(B, Co)[0, 7])

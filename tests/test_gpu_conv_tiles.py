@@ -60,3 +60,32 @@ def test_few_channels_rows(hb, Nb, Ci, Co, H, W, many):
     assert ((got[0][:, 0].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 4 * Co * 2.0 ** -24 * mag).all()
     for b in range(many):
         assert torch.equal(got[0][:, 0].contiguous().view(torch.int16), got[1][:, b].contiguous().view(torch.int16)), b
+
+
+# four splits of 128 k-tiles, two of 68; channels of two row tiles of 128 and three of 64, and of one and two; `many`: 256 workgroups and more,
+# of as many splits
+@pytest.mark.parametrize("Nb,Ci,Co,H,many", [(9, 256, 130, 8, 20), (5, 136, 130, 16, 40), (17, 264, 100, 8, 30)])
+def test_row_tiles_of_a_split_reduction(hb, Nb, Ci, Co, H, many):
+    """The forward's 64-row tiles with the reduction split over workgroups: the same bits as 128-row tiles of that split, and float64."""
+    print(f"conv {Nb} x {Ci} -> {Co} at {H}, split", flush=True)
+    gen = torch.Generator().manual_seed(13)
+    r = lambda *s: torch.randn(s, generator=gen).bfloat16()
+    x, w, bias = r(Nb, Ci, H, H), 0.05 * r(Co, Ci, 4, 4), r(Co)
+    got = []
+    for B in (1, many):
+        X, W, bi = x.repeat(1, B, 1, 1).cuda(), w.repeat(B, 1, 1, 1).cuda(), bias.repeat(B).cuda()
+        dims = (B, Nb, Ci, Co, H, H, 4, 4, 2, 1, 1)
+        ws = torch.full((hb.conv2d_grouped_fwd_workspace_bytes(*dims),), 255, dtype=torch.uint8, device="cuda")
+        for work in (ws, None):
+            Y = torch.full((Nb, B * Co, H // 2, H // 2), float("nan"), dtype=torch.bfloat16, device="cuda")
+            hb.conv2d_grouped_fwd(*dims, X, W, bi, Y, 1, workspace=work)
+            got.append(Y.cpu().view(Nb, B, Co, H // 2, H // 2))
+    assert not torch.equal(got[0], got[1]) and not torch.equal(got[2], got[3])      # the split is another order of the sums
+    xd, wd, bd = x.double(), w.double(), bias.double()
+    ref = F.conv2d(xd, wd, bd, stride=2, padding=1)
+    mag = F.conv2d(xd.abs(), wd.abs(), bd.abs(), stride=2, padding=1)
+    for few in got[:2]:
+        assert ((few[:, 0].double() - ref.clamp_min(0)).abs() <= 2.0 ** -8 * ref.abs() + 16 * Ci * 2.0 ** -24 * mag).all()
+    for few, lot in ((got[0], got[2]), (got[1], got[3])):
+        for b in range(many):
+            assert torch.equal(few[:, 0].contiguous().view(torch.int16), lot[:, b].contiguous().view(torch.int16)), b

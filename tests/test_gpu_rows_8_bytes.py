@@ -85,3 +85,25 @@ def test_wide_data_gradient_either_way(hb, B, Nb, Ci, Co, L):
     wt = W[0].float().t().contiguous()
     ref = wt @ dY[0, 0].float()
     assert float((out[0][0, 0].float() - ref).norm() / ref.norm()) <= 2.0 ** -8            # one rounding to bf16
+
+
+# more than a tile per compute unit, fewer than 256 columns (points, inputs of the data gradient): no room for a tile that ends with the
+# matrix, so these stay on the register-staged kernel
+@pytest.mark.parametrize("B,Nb,Ci,Co,L,pad", [(1, 260, 256, 256, 252, 4), (2, 131, 264, 256, 196, 0), (1, 260, 252, 256, 260, 0)])
+def test_fewer_columns_than_a_tile(hb, B, Nb, Ci, Co, L, pad):
+    test_forward_and_gradients(hb, B, Nb, Ci, Co, L, pad)
+
+
+@pytest.mark.parametrize("B,M,Fx,Fy", [(9, 7424, 256, 252), (3, 22300, 256, 196)])
+def test_linear_of_fewer_columns_than_a_tile(hb, B, M, Fx, Fy):
+    """The same with a bias per column."""
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda").bfloat16()
+    x, w, bias = r(B, M, Fx), r(B, Fx, Fy) / 16, r(B, Fy)
+    y = torch.full((B, M, Fy), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hb.linear_fwd(B, M, Fx, Fy, DT["bf16"], x, w, bias, y, hb.ACT_RELU)
+    for b in range(B):
+        ref = x[b].double() @ w[b].double() + bias[b].double()
+        mag = x[b].double().abs() @ w[b].double().abs() + bias[b].double().abs()
+        # a rounding to bf16 of an fp32 sum of Fx + 1 terms
+        assert ((y[b].double() - ref.clamp_min(0)).abs() <= 2.0 ** -8 * ref.abs() + (Fx + 1) * 2.0 ** -24 * mag).all()
