@@ -91,7 +91,7 @@ def _es(dtype):
 def kernel_label(name, a):
     """Kernel symbol family an entry point launches (matches the rocprofv3 kernel names)."""
     if name == "conv1x1_bn_maxpool_f32_fwd":
-        return "conv1x1_bn_maxpool_f32_fwd: gemm_f32_kernel(+sums and maxima, not stored) + bn_pool_parts_kernel"
+        return "conv1x1_bn_maxpool_f32_fwd: pool32_pack_kernel + pool32_main_kernel + bn_pool_parts_kernel"
     if name == "conv1x1_bn_maxpool_f32_bwd":
         return "conv1x1_bn_maxpool_f32_bwd: gemm_f32_kernel(+hits) + pool32_moments_kernel + 4 small"
     if name in ("bn_fwd", "bn_bwd"):
@@ -132,7 +132,7 @@ def kernel_label(name, a):
         if dt == 1 and big_gemm(B * Nb, Co, L, Ci):
             return big_name(B * Nb, Co, L, (Ci,), (L,)) + "(fwd)"
         return small_gemm(dt) + "(fwd)"
-    if name == "linear_fwd_ws" and a[1] <= 32:
+    if name == "linear_fwd_ws" and few_forward(a[0], a[1], a[2], a[3], a[4]):
         return "linear_few_fwd_kernel"
     if name == "linear_fwd_ws" and a[1] <= 64:
         return ("gemm_pf_kernel" if a[4] == 1 else "gemm_f32_kernel") + "(fwd, split)+splitk_bias_act_kernel"
@@ -144,7 +144,10 @@ def kernel_label(name, a):
         return small_gemm(a[4]) + "(fwd)"
     if name == "linear_bwd":           # the MLP array asks for dX, dW and dbias in separate calls
         B, M, Fx, Fy, dt = a[:5]
-        if a[8] is not None and a[9] is not None:      # one call for everything (the Transformer array)
+        if a[8] is not None and a[9] is not None:      # one call for everything
+            from paper_2102_02344_amd import binding
+            if binding.linear_bwd_pair_supported(B, M, Fx, Fy, dt):
+                return "gemm_dma_pair_kernel"
             return "linear_bwd: gemm(dX) + gemm(dW, with dY's column sums where its kernel takes them)"
         if a[8] is not None:
             return (big_name(B, M, Fx, (Fy,)) if dt == 1 and big_gemm(B, M, Fx, Fy) else small_gemm(dt)) + "(dX)"
@@ -228,6 +231,17 @@ def kernel_label(name, a):
 def small_gemm(dt):
     """What products below the 256x256-tile kernel's sizes run in (bf16: by tiles and length, see gemm_dma.hip)."""
     return "gemm_pf_kernel or gemm_dma_kernel" if dt == 1 else "gemm_f32_kernel"
+
+
+def few_forward(B, M, Fx, Fy, dt):
+    """Whether a Linear's forward with a workspace is one launch: a split reduction that few_fwd_ok and few_ws_pays take (linear_few.hip)."""
+    tiles, tt = (Fy + 127) // 128 * B, (Fx + (31 if dt == 1 else 15)) // (32 if dt == 1 else 16)
+    splits = min((256 + tiles - 1) // tiles, tt // 2, 64)
+    q, fwd = 8 if dt == 1 else 4, (Fy + 31) // 32 * B
+    if M > 32 or splits < 2 or Fx % q or Fy % q or splits > 16:
+        return False
+    piece = (Fx + splits - 1) // splits
+    return fwd * piece <= 3 << 16 and Fx <= 1216 if dt == 1 else piece <= 64 and fwd <= 512
 
 
 def big_gemm(G, M, N, K):

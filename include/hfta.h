@@ -88,7 +88,8 @@ int hfta_linear_fwd(int B, int M, int Fx, int Fy, int dtype,
 /* The same operation with a workspace.  With few rows per model (M <= 64: a fully connected head
  * fed by one pooled vector per sample) the reduction over Fx is cut into pieces that run on
  * different compute units; fp32 partial products [split][B][M][Fy] pass through the workspace and a
- * second launch adds them in a fixed order, then bias and act.  Results equal hfta_linear_fwd's up
+ * second launch adds them in a fixed order, then bias and act.  (Up to 32 rows on 16-byte aligned operands
+ * may take one launch that leaves the workspace alone: the same bits.)  Results equal hfta_linear_fwd's up
  * to fp32 summation order.  hfta_linear_fwd_workspace_bytes is 0 where no split is used (then the
  * call is hfta_linear_fwd); EWORKSPACE below that size. */
 size_t hfta_linear_fwd_workspace_bytes(int B, int M, int Fx, int Fy, int dtype);
@@ -100,7 +101,7 @@ int hfta_linear_fwd_ws(int B, int M, int Fx, int Fy, int dtype,
  * tight serving loops, harnesses that forbid hipMalloc): the split partials live in a device array
  * of HFTA_LINEAR_FWD_STATIC_BYTES that is part of the library image, so the call takes no workspace
  * and makes no allocation.  Same arguments, results and validation as hfta_linear_fwd_ws (bit-equal:
- * same kernels, same split count).  HFTA_EWORKSPACE when the partials of the shape exceed the array
+ * same products, same split count; always two launches where there is a split).  HFTA_EWORKSPACE when the partials of the shape exceed the array
  * (hfta_linear_fwd_workspace_bytes(...) > hfta_linear_fwd_static_max_bytes()); HFTA_ELAUNCH when the
  * array's address cannot be obtained on the current device.  Every GPU the library runs on holds its
  * own copy of the array until the process ends; its address is looked up once per device (the one

@@ -310,7 +310,11 @@ int gemm_launch(const GemmDesc& d, hipStream_t st) {
       // An operand contiguous along m / n whose rows are whole 8-byte pieces (2500 points): a last tile that ends with the matrix instead
       // of past it has 16-byte pieces only (columns that two tiles share are formed and stored twice, alike).  6 x 16 samples of 2500
       // points, register-staged kernel -> ring: data gradients 2048 -> 512 544 -> 493 us, 256 -> 2880 703 -> 630, forward 2880 -> 256
-      // 462 -> 425, 512 -> 2048 680 and 681.  What is left is the stores: rows that start anywhere in a cache line leave partial lines
+      // 462 -> 425, 512 -> 2048 680 and 681.  The columns stored twice do not show: 6 x 16, 512 -> 2048 on 260 points (252 of them
+      // twice) forward 120 -> 114, data gradient 123 -> 107, on 516 167 -> 163 and 170 -> 161, on 772 253 -> 244 and 193 -> 178; 8 x 32,
+      // 256 -> 256 on 260 to 2500 points 1.00 to 1.13 times as fast; 16 x 2048 rows, 512 -> 260 29 -> 26, its weight gradient 50 -> 45.  The
+      // least is the forward that stores four times what it loads: 512 -> 2048 on 708 to 1020 points 0.97 to 1.03 times.  What is left is
+      // the stores: rows that start anywhere in a cache line leave partial lines
       // (256 -> 2880 on 2560 points 461 us, of which non-temporal stores are 70, on 2504 points 616).
       auto back = [&](bool kc, int vec, int extent, int& last) {
         if (kc || extent % 8 == 0) return true;

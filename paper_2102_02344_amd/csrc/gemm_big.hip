@@ -95,7 +95,8 @@ int gemm_big_launch(const GemmDesc& d, const GemmArgs& a0, bool v16, bool n16, d
       *d.stat_done = rc == HFTA_OK;
       return rc;
     } else if (!f32) {
-      // 8-byte aligned operand rows: those in whole 16-byte pieces have gone to the ring
+      // 8-byte aligned operand rows: the ring has taken those in whole 16-byte pieces, and unsplit ones across k of 256 elements and more;
+      // what is left across k is 196 to 252 wide, with more than a tile per compute unit
       if (d.a_kc && !d.b_kc && !n16) {
         if (colb) launch_bigp<true, false, bf16_raw, true, true, false>(a, ident, grid, blocks, st);
         else launch_bigp<true, false, bf16_raw, false, true, false>(a, ident, grid, blocks, st);

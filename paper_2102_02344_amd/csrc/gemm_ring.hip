@@ -24,8 +24,9 @@ static void launch_bf16(const GemmArgs& a, dim3 grid, int blocks, hipStream_t st
   else launch<A_KC, B_KC, bf16_raw, COLB, ACT, 8>(a, grid, blocks, st);
 }
 
-// `a` carries tile counts for 256x256 tiles of 64-element k-tiles and operand extents; every operand loads in whole aligned
-// 16-byte pieces.  HFTA_EUNSUPPORTED: not a launch this kernel is built for.
+// `a` carries tile counts for 256x256 tiles of 64-element k-tiles and operand extents; every operand loads in whole 16-byte pieces,
+// aligned, or (contiguous along m / n) aligned to 8 bytes with m_last / n_last set where the extent is no multiple of eight.
+// HFTA_EUNSUPPORTED: not a launch this kernel is built for.
 int gemm_ring_launch(const GemmDesc& d, const GemmArgs& a0, dim3 grid, hipStream_t st) {
   const bool partial = a0.splits > 1, f32 = d.out_f32 || partial;
   const bool colb = d.bias && d.bias_mode == 2;

@@ -4,9 +4,10 @@
 // and the way back), each as long as a launch that waits for the one before it takes: 4.5-10 us, 134 us of a bf16 step of 8 models
 // whose weights are 10 MB.  With at most 32 rows a column of a layer's output is one column of one matrix-instruction tile, so
 // everything that works by columns -- BatchNorm over the rows, its activation, the dropout behind it, and all of it backwards --
-// is done by the workgroup that has the product in hand: six launches, 50 us of that step (1376 -> 1310), and on 3 models of 13
-// clouds 114 -> 40 us (411 -> 351 a step).  In fp32 two models of 4 clouds
-// (1024 -> 256 -> 16) 58 -> 30 us (185 -> 161 a step), four of 32 clouds 2026 -> 1979 a step.
+// is done by the workgroup that has the product in hand: six launches, 51 us of that step (12, 8 and 7 forward, 8, 7 and 9 back; 1376 ->
+// 1310 a step), and on 3 models of 13 clouds 114 -> 40 us (411 -> 351 a step).  In fp32 two models of 4 clouds
+// (1024 -> 256 -> 16, no BatchNorm) 58 -> 30 us (185 -> 161 a step), four of 32 clouds 2026 -> 1979 a step.  With many models the single
+// operators are the sooner way: few_pays, few_ws_pays.
 //
 // Bound: the wait for one launch, one load of the operands (all of a workgroup's in flight at once) and the chain of the matrix
 // instructions and the row sums behind them.  Hence 32-column tiles, as many workgroups as that gives, and the forward's
@@ -34,7 +35,9 @@ constexpr int FEW_LANES = 16;                            // row lanes of BatchNo
 constexpr int FWD_WAVES = 16;                            // most wavefronts of a workgroup
 constexpr int PART_PITCH = 36;                           // floats: 32 columns and a pad
 constexpr int PART_BYTES = FEW_ROWS * PART_PITCH * 4;    // one piece of the reduction
-// bf16: W's columns in LDS, 64 bytes per k, and the partial sums over them; two workgroups a compute unit.  fp32: the partial sums.
+// bf16: W's columns in LDS, 64 bytes per k, and the partial sums over them; two workgroups a compute unit (82,048 bytes with the
+// cross-entropy's tile, one: there is one a model).  fp32: the partial sums of 32 pieces, one workgroup a compute unit whatever the split;
+// two of 128 registers spill beside BatchNorm and the cross-entropy.
 template <typename T> struct FewFwd;
 template <> struct FewFwd<bf16_raw> { static constexpr int LDS = 76 * 1024, MAX_K = LDS / 64, SPLITS = 16; };
 template <> struct FewFwd<float> { static constexpr int SPLITS = 32, LDS = SPLITS * PART_BYTES; };
