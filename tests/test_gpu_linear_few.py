@@ -231,3 +231,31 @@ def test_beyond_those_lines(dt, B, M, Fx, Fy):
     hb.linear_bwd_bn(B, M, Fx, Fy, dt, x, w, dy, dx2, dw2, db2)
     for a, b, what in ((dx, dx2, "dX"), (dw, dw2, "dW"), (db, db2, "dbias")):
         _same(a, b, what)
+
+
+# heads of which the first layer, the last, or those in between take the one-launch calls
+@pytest.mark.gpu
+@pytest.mark.parametrize("net,dt,B", [("cls", "bf16", 40), ("cls", "f32", 16), ("cls", "bf16", 8), ("clst", "bf16", 9), ("clst", "f32", 9)])
+def test_arrays_either_way(net, dt, B, monkeypatch):
+    """A step of an array whose head takes the one-launch calls layer by layer has the bits of one that makes the single calls."""
+    import hfta_inputs as hi
+    from paper_2102_02344_amd import arrays
+    if net == "cls":
+        spec = hi.spec_c1(B=B, Nb=4, L=64, dtype=dt)
+        inp, make, fc = hi.pointnet_cls_inputs(spec), arrays.FusedPointNetCls, spec.fc
+    else:
+        spec = hi.PointNetTSpec(cls=hi.spec_c1(B=B, Nb=4, L=64, dtype=dt))
+        inp, make, fc = hi.pointnet_t_inputs(spec), arrays.FusedPointNetClsT, (1024, 512, 256, 64 * 64)
+    code = hb.BF16 if dt == "bf16" else hb.F32
+    takes = [bool(hb.linear_few_supported(B, 4, a, b, code)) for a, b in zip(fc, fc[1:])]
+    print(net, dt, B, takes, flush=True)
+    assert any(takes) and (B == 8 or not all(takes))
+    got = []
+    for route in ("as it is", "single"):
+        if route == "single":
+            monkeypatch.setattr(arrays.hb, "linear_few_supported", lambda *a: False)
+        a = make(spec, inp)
+        a.forward_backward()
+        got.append([a.loss.clone(), a.grad.clone()] + [v.clone() for v in a.running.values()] + [v.clone() for v in a.saved.values()])
+    for x, y in zip(*got):
+        _same(x.contiguous().view(-1), y.contiguous().view(-1), (net, tuple(x.shape)))
