@@ -601,11 +601,11 @@ bool few_fwd_ok(int B, int M, int Fx, int Fy, int dtype) {
 // these, BatchNorm and dropout forward and backward, 32 rows a model:
 //   bf16, 1024 -> 512    16 models 20 -> 12, 28 -> 20     32: 24 -> 18, 37 -> 33     64: 24 -> 36, 60 -> 59    256: 89 -> 155, 257 -> 285
 //         512 -> 256     64: 20 -> 13, 32 -> 28     96: 26 -> 20, 40 -> 40    128: 19 -> 26, 45 -> 51    512: 58 -> 83, 170 -> 268
-//   fp32, 64 -> 64       32: 12 -> 6, 17 -> 7    256: 16 -> 13, 24 -> 21 (without BatchNorm 12 -> 14)   512: 18 -> 21, 29 -> 34
+//   fp32, 64 -> 64       32: 13 -> 6, 17 -> 6    256: 13 -> 11, 20 -> 15 (without BatchNorm 12 -> 14)   512: 18 -> 21, 29 -> 34
 //         28 -> 436      500: 51 -> 133, 47 -> 162
-// The forward's time in bf16 is its workgroups times the k that a wavefront walks (one wavefront the whole reduction where it is not split),
-// the backward's six rounds of two workgroups a compute unit; in fp32 a compute unit holds one.  Both calls of a layer,
-// 497 shapes of 1 to 622 models: 0.98 to 3.0 times as fast within these lines (2.2 at the median), 0.33 to 1.6 past them (0.90).
+// The forward's time in bf16 goes with its workgroups times the k that a wavefront walks (one wavefront the whole reduction where it is
+// not split), the backward's with its workgroups: six rounds of two a compute unit; in fp32 a compute unit holds one.  Both calls of a
+// layer, 497 shapes of 1 to 622 models: 0.98 to 3.0 times as fast within these lines (2.2 at the median), 0.33 to 1.6 past them (0.90).
 bool few_pays(int B, int M, int Fx, int Fy, int dtype) {
   const int64_t fwd = (int64_t)((Fy + 31) / 32) * B, splits = linear_row_splits(B, M, Fx, Fy, dtype);
   const int64_t bwd = (int64_t)((Fx + 31) / 32 + (Fx + DW_BM - 1) / DW_BM * ((Fy + DW_BN - 1) / DW_BN)) * B;
